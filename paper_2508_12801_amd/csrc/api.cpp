@@ -31,6 +31,7 @@ WorkspaceLayout workspace_layout(int T, int E, int k, int d)
     L.finm_off = off; off = align_up(off + sizeof(unsigned long long) * (size_t)kFinMatrixMaxE * kFinMatrixMaxE, 256);
     // finisher arc lists: one segment per key block (fin_seg_cap(rows, k) arcs of 12 bytes each) and a count per block
     L.tri_off = off; off = align_up(off + 12 * fin_tri_entries(T, k, L.max_wg) + sizeof(int) * ((size_t)L.max_wg + 1), 256);
+    L.price_off = off; off = align_up(off + price_area_bytes(L.max_wg), 256);    // tables of the price solve
     L.wt_off = off; off = align_up(off + sizeof(unsigned short) * (size_t)E * (d > 0 ? d : 0), 256);
     L.total = off;
     return L;
@@ -67,6 +68,20 @@ static bool fused_scores_ok(int dtype, int d, int E, const void *x, const void *
 {
     return gemm_softtopk_supported(dtype, d, E, x, wt) &&
            ((((uintptr_t)logits) | ((uintptr_t)scores) | ((uintptr_t)q)) % 16) == 0;
+}
+
+// More demand than capacity: a price solve takes the problem as it is; where that does not stand it is padded.
+static int32_t over_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore_opts &o, int32_t *assign,
+                        int64_t *prices, int64_t *price_scale, maxscore_stats *stats, char *ws, size_t ws_bytes,
+                        hipStream_t s, SolverGeometry *geom = nullptr, SolverAfter after = nullptr, void *ctx = nullptr)
+{
+    const size_t need = oversub_workspace_bytes(T, E, k);
+    if (need != 0 && ws_bytes >= need) {
+        const int32_t rc = solver_run(q, T, E, k, Ce, o, assign, prices, price_scale, stats, ws, s, nullptr, 0, nullptr, 0,
+                                      geom, after, ctx);
+        if (rc != kSolverPassedOn) return rc;
+    }
+    return oversub_run(q, T, E, k, Ce, o, assign, prices, price_scale, stats, ws, ws_bytes, s);
 }
 
 }  // namespace maxscore
@@ -130,8 +145,8 @@ int32_t maxscore_assign_i32(const int32_t *q, int32_t T, int32_t E, int32_t k, i
     maxscore_opts o = resolve(opts);
     if (stats) std::memset(stats, 0, sizeof(*stats));
     if ((long long)T * k > (long long)E * Ce)
-        return oversub_run(q, T, E, k, Ce, o, assign, prices, price_scale, stats, (char *)workspace, workspace_bytes,
-                           (hipStream_t)stream);
+        return over_run(q, T, E, k, Ce, o, assign, prices, price_scale, stats, (char *)workspace, workspace_bytes,
+                        (hipStream_t)stream);
     return solver_run(q, T, E, k, Ce, o, assign, prices, price_scale, stats, (char *)workspace,
                       (hipStream_t)stream);
 }
@@ -341,14 +356,11 @@ static int32_t route_from_rewards(const float *scores, const int32_t *q, int T, 
             stats->rounds = rounds;
             stats->status = src;
         }
-    } else if ((long long)T * k > (long long)E * Ce) {
-        // more demand than capacity: every expert ends full, rows come back with empty slots (-1) at their end
-        src = oversub_run(q, T, E, k, Ce, o, assign, prices, nullptr, stats, ws, ws_bytes, s);
     } else {
-        // After a converged solve the final bid pass has left every pair as a key, sorted by expert inside each block
-        // of rows: gates and dispatch come from there.  They are enqueued behind the solve before the call waits for
-        // it (the kernels stay inside their buffers on any state; if the solve did not converge the general kernels
-        // below overwrite what they wrote).
+        // A price solve leaves the number of pairs per block of rows and expert, an auction that converged every pair
+        // as a key, sorted by expert inside each block of rows: gates and dispatch come from there.  They are enqueued
+        // behind the solve before the call waits for it (the kernels stay inside their buffers on any state; if the
+        // solve did not converge the general kernels below overwrite what they wrote).
         struct AfterCtx {
             const float *scores; const int32_t *assign; int T, E, k; float *gates; int32_t *offsets, *disp_token;
             float *disp_gate; int32_t *token_pos; char *ws; hipEvent_t ev_start, ev_b;
@@ -359,12 +371,16 @@ static int32_t route_from_rewards(const float *scores, const int32_t *q, int T, 
             int32_t rc = dispatch_from_keys(g, a->scores, a->assign, a->T, a->E, a->k, a->gates, a->offsets,
                                             a->disp_token, a->disp_gate, a->token_pos, a->ws, st);
             if (rc) return rc;
-            MS_HIP(hipEventRecord(a->ev_b, st));
+            if (solve_end) MS_HIP(hipEventRecord(a->ev_b, st));
             return MAXSCORE_OK;
         };
-        SolverGeometry geom = {0, 0, 0};
-        src = solver_run(q, T, E, k, Ce, o, assign, prices, nullptr, stats, ws, s, nullptr, 0, nullptr, 0, &geom, after,
-                         &ctx);
+        SolverGeometry geom = {0, 0, 0, 0, nullptr};
+        // more demand than capacity: every expert ends full, rows come back with empty slots (-1) at their end
+        if ((long long)T * k > (long long)E * Ce)
+            src = over_run(q, T, E, k, Ce, o, assign, prices, nullptr, stats, ws, ws_bytes, s, &geom, after, &ctx);
+        else
+            src = solver_run(q, T, E, k, Ce, o, assign, prices, nullptr, stats, ws, s, nullptr, 0, nullptr, 0, &geom, after,
+                             &ctx);
         if (src == MAXSCORE_OK && geom.n_wg > 0) {
             float t = 0.f;           // the solve has waited for the stream: both events are complete
             if (stats && ctx.ev_start && hipEventElapsedTime(&t, ctx.ev_start, ev_b) == hipSuccess)

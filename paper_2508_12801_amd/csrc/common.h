@@ -58,11 +58,13 @@ struct SolverState {
     int fin_cycles;        // negative cycles cancelled so far
     int fin_dirty;         // cycles cancelled since the arc matrix was last rebuilt
     int phase_round[28];   // round index at which each phase ended (diagnostic)
+    long long t_start, t_end;    // device clock (10 ns) at the first and last kernel of a price solve (host copy only)
+    long long t_after;           // ... and at the end of the caller's work behind it
 };
 
 struct WorkspaceLayout {
     size_t state_off, theta_off, gcount_off, klist_off, wcnt_off, wmoves_off, cand_off, tiles_off, cap_off, aux_off,
-        wt_off, dbase_off, fin_off, finm_off, tri_off, total;
+        wt_off, dbase_off, fin_off, finm_off, tri_off, price_off, total;
     int n_tiles, max_wg;
 };
 
@@ -72,6 +74,8 @@ struct SolverGeometry {
     int rows;        // token rows per bid workgroup = per key block
     int n_wg;        // number of key blocks
     int tbits;       // the token id sits in the low tbits bits of a key
+    int counts;      // 1: no key blocks; the pairs per (block, expert) are counted (price solves)
+    long long *clock;    // device pointer for the end time of the work behind a price solve (SolverState::t_after)
 };
 
 WorkspaceLayout workspace_layout(int T, int E, int k, int d = 0);
@@ -90,8 +94,10 @@ inline bool hip_ok(hipError_t e) { return e == hipSuccess; }
 // It is enqueued before the call waits for the stream, so the device goes from the solve straight into it; it
 // runs whatever the solve's status turns out to be and must therefore be safe on any state the solver can leave
 // (the caller redoes it another way when the status is not MAXSCORE_OK).
+// More demand than capacity (T*k > E*Ce, no vectors): only a price solve is tried; kSolverPassedOn if it does not stand.
 // solve_end: the event the solver has just recorded behind its last kernel (it stays valid until the calling thread
 // solves again on this device); work timed from there needs no start event of its own.
+constexpr int32_t kSolverPassedOn = 1;
 typedef int32_t (*SolverAfter)(void *ctx, const SolverGeometry &g, hipStream_t s, hipEvent_t solve_end);
 int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore_opts &o, int32_t *assign,
                    int64_t *prices, int64_t *price_scale, maxscore_stats *stats, char *ws, hipStream_t s,
@@ -100,6 +106,23 @@ int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore
                    void *after_ctx = nullptr);
 // Checks a device array of T per-token k (each 0..k) and returns its sum in *demand (synchronises the stream).
 int32_t kvec_check(const int32_t *kvec, int T, int E, int k, char *ws, long long *demand, hipStream_t s);
+// --- price.hip
+// Exact assignment by equilibrium prices and shortest augmenting paths: everything is enqueued at once, the outcome is
+// left in the pinned host state (fin == 2: certified; 1: not, but another try from the prices reached may do it (retry);
+// anything else: the auction has to solve the problem).  k < E <= kPriceMaxE, one capacity for all experts, any relation of demand and capacity (rows that
+// cannot be filled end in -1).
+constexpr int kPriceMaxE = 512;
+struct PriceGeometry {
+    int rows, n_wg;          // blocks of rows over which the pairs are counted (WorkspaceLayout::wcnt_off)
+};
+bool price_supported(int T, int E, int k);
+inline size_t price_area_bytes(int max_wg) { return 864 * 1024 + 16 * (size_t)max_wg; }     // tables, and two words per block
+int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_t *prices_in, bool retry,
+                      int32_t *assign, int64_t *prices, int64_t *price_scale, char *ws, SolverState *host_state_dev, PriceGeometry *geom, hipStream_t s);
+// Runs price_enqueue and the caller's work behind it and waits.  *solved: whether the result stands.
+int32_t price_run(const int32_t *q, int T, int E, int k, int C, const maxscore_opts &o, int32_t *assign, int64_t *prices,
+                  int64_t *price_scale, maxscore_stats *stats, char *ws, hipStream_t s, SolverGeometry *geom,
+                  SolverAfter after, void *after_ctx, bool *solved);
 // --- finish.hip
 // Exact finish from a quiescent auction state at a coarse eps (every token holds its experts): cancels the negative
 // cycles of the expert graph until none is left and replaces the prices by exact ones.  One call enqueues the passes

@@ -272,6 +272,130 @@ __global__ __launch_bounds__(256) void k_keys_scatter(const long long *__restric
     }
 }
 
+// ---- a5 + a6 from the pair counts of a price solve ------------------------------------------------------------
+// The solve leaves the number of pairs per (block of rows, expert).  One scan over the blocks per expert gives every
+// block its first place in each expert's list; inside a block the place of a pair is the number of earlier rows that
+// hold the same expert, read off a bit per row.
+
+__global__ __launch_bounds__(256) void k_count_scan(const int *__restrict__ cnt, int n_wg, int E,
+                                                    int *__restrict__ dbase, int *__restrict__ totals)
+{
+    __shared__ int s_w[4];
+    const int e = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    int run = 0;
+    for (int w0 = 0; w0 < n_wg; w0 += 1024) {             // four blocks per thread and step
+        int c[4], sum = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int w = w0 + tid * 4 + i;
+            c[i] = w < n_wg ? cnt[(size_t)w * E + e] : 0;
+            sum += c[i];
+        }
+        int inc = sum;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(inc, off);
+            if (lane >= off) inc += o;
+        }
+        if (lane == 63) s_w[wv] = inc;
+        __syncthreads();
+        int at = run + inc - sum;
+        for (int v = 0; v < wv; ++v) at += s_w[v];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int w = w0 + tid * 4 + i;
+            if (w < n_wg) dbase[(size_t)w * E + e] = at;
+            at += c[i];
+        }
+        run += s_w[0] + s_w[1] + s_w[2] + s_w[3];
+        __syncthreads();
+    }
+    if (tid == 0) totals[e] = run;
+}
+
+constexpr int kCountMaxE = 512, kCountMaxRows = 128;      // of a price solve
+static_assert(kCountMaxE >= kPriceMaxE, "tables for every expert count a price solve accepts");
+
+__global__ __launch_bounds__(256) void k_count_scatter(const int *__restrict__ dbase, const int *__restrict__ totals,
+                                                       const float *__restrict__ scores,
+                                                       const int32_t *__restrict__ assign, int T, int E, int k, int rows,
+                                                       float *__restrict__ gates, int32_t *__restrict__ offsets,
+                                                       int32_t *__restrict__ disp_token, float *__restrict__ disp_gate,
+                                                       int32_t *__restrict__ token_pos, long long *clock)
+{
+    __shared__ unsigned s_mask[kCountMaxE * (kCountMaxRows / 32 + 1)];      // five words per expert: no bank conflicts
+    __shared__ int s_base[kCountMaxE], s_off[kCountMaxE];
+    __shared__ int s_w[4];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, w = blockIdx.x;
+    const int row0 = w * rows;
+    int rows_here = T - row0;
+    rows_here = rows_here < rows ? rows_here : rows;
+    const int nslots = rows_here * k;
+    const size_t n_pairs = (size_t)T * k;
+    // this thread's pairs and their gates are on their way while the offsets are worked out
+    int e_[4], lr_[4];
+    float g_[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int idx = tid + i * 256;
+        e_[i] = idx < nslots ? assign[(size_t)row0 * k + idx] : -1;
+        if (e_[i] >= E) e_[i] = -1;                         // (never in an assignment that stands)
+        lr_[i] = idx / k;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) g_[i] = e_[i] >= 0 ? scores[(size_t)(row0 + lr_[i]) * E + e_[i]] : 0.f;
+    for (int i = tid; i < E * 5; i += 256) s_mask[i] = 0;
+    for (int e = tid; e < E; e += 256) s_base[e] = dbase[(size_t)w * E + e];
+    {
+        int loc[2], sum = 0;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            loc[i] = tid * 2 + i < E ? totals[tid * 2 + i] : 0;
+            sum += loc[i];
+        }
+        int inc = sum;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(inc, off);
+            if (lane >= off) inc += o;
+        }
+        if (lane == 63) s_w[wv] = inc;
+        __syncthreads();
+        int run = inc - sum;
+        for (int v = 0; v < wv; ++v) run += s_w[v];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int e = tid * 2 + i;
+            if (e < E) {
+                s_off[e] = run;
+                if (w == 0) offsets[e] = run;
+                run += loc[i];
+                if (w == 0 && e == E - 1) offsets[E] = run;
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (e_[i] >= 0) atomicOr(&s_mask[e_[i] * 5 + (lr_[i] >> 5)], 1u << (lr_[i] & 31));
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int idx = tid + i * 256, e = e_[i], lr = lr_[i];
+        if (idx >= nslots) continue;
+        int pos = -1;
+        if (e >= 0) {
+            pos = s_base[e] + __popc(s_mask[e * 5 + (lr >> 5)] & ((1u << (lr & 31)) - 1));
+            for (int x = 0; x < (lr >> 5); ++x) pos += __popc(s_mask[e * 5 + x]);
+            const size_t dst = (size_t)s_off[e] + pos;
+            if (dst < n_pairs) {                            // (always, with the counts of a solve that stands)
+                disp_token[dst] = row0 + lr;
+                disp_gate[dst] = g_[i];
+            }
+        }
+        token_pos[(size_t)row0 * k + idx] = pos;
+        gates[(size_t)row0 * k + idx] = g_[i];
+    }
+    if (clock && w == gridDim.x - 1 && tid == 0) *clock = wall_clock64();
+}
+
 }  // namespace
 
 int32_t dispatch_from_keys(const SolverGeometry &g, const float *scores, const int32_t *assign, int T, int E, int k,
@@ -284,6 +408,14 @@ int32_t dispatch_from_keys(const SolverGeometry &g, const float *scores, const i
     const int *wcnt = (const int *)(ws + L.wcnt_off);
     int *dbase = (int *)(ws + L.dbase_off);
     int *totals = dbase + (size_t)E * L.max_wg;
+    if (g.counts) {
+        if (g.rows > kCountMaxRows || E > kCountMaxE) return MAXSCORE_ERR_SHAPE;
+        hipLaunchKernelGGL(k_count_scan, dim3(E), dim3(256), 0, s, wcnt, g.n_wg, E, dbase, totals);
+        hipLaunchKernelGGL(k_count_scatter, dim3(g.n_wg), dim3(256), 0, s, dbase, totals, scores, assign, T, E, k, g.rows,
+                           gates, offsets, disp_token, disp_gate, token_pos, g.clock);
+        MS_HIP(hipGetLastError());
+        return MAXSCORE_OK;
+    }
     hipLaunchKernelGGL(k_keys_scan, dim3(E), dim3(256), 0, s, wcnt, g.n_wg, E, dbase, totals);
     hipLaunchKernelGGL(k_keys_scatter, dim3(g.n_wg), dim3(256), 0, s, klist, wcnt, dbase, totals, scores, assign, T, E,
                        k, g.rows, g.tbits, gates, offsets, disp_token, disp_gate, token_pos);

@@ -1,0 +1,1445 @@
+// Exact assignment (Eq. 7-8, Table 1) by equilibrium prices and shortest augmenting paths.
+//
+// The dual of the transportation problem has one price per expert.  At given prices every token takes its k best
+// experts by q - price; the right prices are those at which every expert is chosen by exactly as many tokens as it
+// has places.  They are found from both sides at once:
+//
+//   price passes (k_price)   every token's k-th and (k+1)-th best value give, for each expert it takes, how far that
+//                            expert's price may rise before the token leaves, and for each it does not take, how far
+//                            the price has to fall before the token comes.  Histograms of these margins per expert
+//                            (a few bins per octave) say by how much each price has to move for its own demand to
+//                            meet its capacity; all prices move at once.  Displaced tokens spread over all the other
+//                            experts, so the simultaneous step converges fast: the excess demand of a batch of 65536
+//                            tokens over 128 experts goes 37000, 1200, 230, 110, 75, 50 tokens.  The first two
+//                            passes of a large batch look at 8192 of its tokens only.
+//   final pass               the tokens take their k best experts at the last prices, and every exchange that would
+//                            cost less than a bound is listed: arc a -> b of token u, cost (q_ua - p_a) - (q_ub - p_b),
+//                            never negative because the token holds its best experts.
+//   k_price_finish           one workgroup moves the few tokens that are one too many along shortest paths in the graph of
+//                            experts.  Paths of different branches of the shortest-path trees are disjoint, so many are
+//                            taken per search, keeping the reduced costs non-negative.  When no excess is left the
+//                            assignment is feasible, the potentials certify it, and the prices are exact.
+//
+// The list of arcs is complete below the bound; arcs left out stay non-negative if the potentials spread less than
+// the bound, which is checked at the end.  If that fails, or no path is left, up to two more tries start from the prices
+// reached with more arcs.  Whenever anything does not fit (values too wide for the packed keys, too many arcs, too much
+// excess left) the result is thrown away and the auction of solver.hip solves the problem instead.
+//
+// What bounds it: the passes read the rewards once each (34 MB for 65536 tokens over 128 experts, 17 to 28 us a pass
+// including the k-th best of every row, plus 11 us for the update between them), the search is one serial chain of
+// searches (12 to 24 us each).  65536 tokens, 128 experts, top-8, capacity 1.0: 0.42 ms against 1.75 ms for the auction,
+// whose 50 rounds each read the rewards as well; 16384 over 64 experts: 0.25 against 0.9 ms.
+//
+// Three forms of the problem, told apart by PriceArgs::mode:
+//   demand = capacity   every expert ends full;
+//   spare capacity      prices stay >= 0 and an expert with room left ends at price 0.  The spare places are counted as
+//                       tokens without rewards: they sit at experts of price 0, and node Z (index E) of the graph passes
+//                       them from expert to expert;
+//   demand > capacity   the slots a token cannot fill are held by one more column (index E) of reward 0 that a token may
+//                       hold several times and that has exactly as many places as there are slots too many.
+// Everything is integer arithmetic with fixed tie rules: the result does not depend on the order of execution.
+#include <algorithm>
+
+#include "common.h"
+
+namespace maxscore {
+namespace {
+
+constexpr int kPThreads = 256;
+constexpr int kPStride = kPriceMaxE + 8;          // columns of the per-expert tables (E + 1 used)
+constexpr int kPCopies = 8;
+constexpr int kPCols = 264;                       // columns of a histogram with kPBins bins at most (half as many bins beyond)
+constexpr int kPBins = 20;                        // margin bins per side: ten octaves, two bins each (one beyond 256 experts)
+constexpr int kPArcs = 9216;                      // arcs the one-workgroup search holds in LDS
+constexpr int kPBlocks = 4096;                    // blocks of rows of the final pass at most (four per thread of the search)
+constexpr int kPArcBuf = 16384;                   // arcs the final pass can list
+constexpr int kFThreads = 1024, kUThreads = 1024;
+constexpr int kFRegs = kPArcs / kFThreads;
+constexpr int kFirstWindow = 1 << 22;             // margins of the first pass: up to four times a score of 1
+constexpr int kSampleRows = 8192;
+constexpr int kArcsPerExpert = 16, kArcsWanted = 4500, kArcsMost = 5500;
+constexpr int kMaxBound = (1 << 21) - 1;
+constexpr int kAllArcs = 7000;                    // problems with this few exchanges in all are searched with all of them
+constexpr int kEnough = 8, kWorst = 2;            // the passes end when an eighth of a token per expert is too many, at
+                                                  // no expert more than two (its tokens leave one search at a time)
+constexpr int kLevelPairs = 4;                    // exchanges of a row that the common step looks at
+constexpr int kSmallEntries = 1 << 16;            // rewards of a batch that one workgroup passes over by itself
+constexpr int kSmallThreads = 4096;               // ... with this many lanes at work in all
+constexpr int kSmallPasses = 20;
+constexpr int kPRowsMax = 128;                    // rows of a block of the final pass at most
+enum { kModeTight = 0, kModeSlack = 1, kModeOver = 2 };
+
+struct PriceMeta {
+    int w;            // margins below this were binned by the pass
+    int done;         // the prices need no further pass
+    int bound;        // arcs cheaper than this are listed by the final pass
+    int passes;       // price passes so far (the one that checks prices the caller has given is not counted)
+    int excess;       // tokens too many in all, as the pass found them (a sample's count is scaled up)
+    int pad[3];
+};
+
+// Control words and tables inside the workspace (WorkspaceLayout::price_off).
+struct PriceArea {
+    int prices[kPStride];
+    PriceMeta meta;                               // for the pass that comes next
+    int loads[8][kPStride];                       // tokens per expert after the final pass, in eight partial counts
+    int n_arcs, fail;
+    int pad[6];
+    long long t_start;
+    long long pad2;
+    // margins and holds, one copy per chiplet: (2 * nb + 1) rows of ES columns, filled by a pass (workgroup b adds to copy
+    // b mod 8), added up and cleared by the update behind it.  With one copy for all the additions of 512 workgroups
+    // took 25 us: its lines travel from chiplet to chiplet with every addition.
+    int hist[kPCopies][(2 * kPBins + 1) * kPCols];
+    unsigned long long arc[kPArcBuf];             // cost << 32 | from << 16 | to
+    int arc_tok[kPArcBuf];
+};
+
+struct PriceArgs {
+    const int32_t *q;
+    int32_t *assign;
+    PriceArea *ar;
+    int *blkcnt;                                  // pairs per (block of rows of the final pass, expert)
+    int2 *wg_arcs;                                // first arc and number of arcs of every block
+    long long *wg_sum;                            // sum of q over the block's pairs
+    int T, E, k, C, mode;
+    int even;                                     // the passes before this one treat spare capacity as spread evenly
+    int rows, n_wg;                               // of the final pass
+    int ib, nb, bshift;                           // bits of a column id in a packed key; bins per side; their width
+    int es;                                       // columns of the histograms
+    int retry;                                    // the search has failed at the prices or the bound before
+    int arcs_wanted;                              // about so many exchanges are to lie under the bound
+};
+
+// Margins are binned relative to w0 = window / 2^9: linear up to w0, then two bins per octave (one beyond 256 experts).
+__device__ __forceinline__ int bin_of(int m, int w0, int bshift)
+{
+    return (int)((__float_as_uint((float)(m + w0)) - __float_as_uint((float)w0)) >> bshift);
+}
+__device__ __forceinline__ int bin_edge(int b, int w0, int bshift)        // lowest margin of bin b
+{
+    const float f = __uint_as_float(__float_as_uint((float)w0) + ((unsigned)b << bshift));
+    return (int)ceilf(f) - w0;
+}
+__device__ __forceinline__ int bin_w0(int w) { return (w >> 9) > 2 ? (w >> 9) : 2; }
+
+template <int G>
+__device__ __forceinline__ unsigned group_min_u32(unsigned v)
+{
+    unsigned o;
+    if constexpr (G >= 8) {
+        o = (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xf, 0xf, true); v = o < v ? o : v;    // quad_perm [1,0,3,2]
+        o = (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xf, 0xf, true); v = o < v ? o : v;    // quad_perm [2,3,0,1]
+        o = (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xf, 0xf, true); v = o < v ? o : v;   // row_half_mirror
+    }
+    if constexpr (G >= 16) {
+        o = (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xf, 0xf, true); v = o < v ? o : v;   // row_mirror
+    }
+    if constexpr (G >= 32) { o = __shfl_xor(v, 16); v = o < v ? o : v; }
+    if constexpr (G >= 64) { o = __shfl_xor(v, 32); v = o < v ? o : v; }
+    return v;
+}
+
+__device__ __forceinline__ int wave_sum(int v)        // inclusive prefix sum over the lanes, the total in lane 63
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);    // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31
+    return v;
+}
+
+__device__ __forceinline__ unsigned row_mask(int row, int ib)      // equal values are ranked by column XOR a mask of the row
+{
+    return ((unsigned)row * 0x9E3779B1u) >> (32 - ib);
+}
+
+// New prices from the histograms of a pass: of s.was to s.now, with the margins in s_h; one workgroup.
+//
+// Experts whose price counts (all of them; with spare capacity those with a price above 0) are moved towards their
+// common mean demand one by one, and all together by the step that brings the mean to the capacity: raising them all
+// displaces tokens only to the experts outside, which the single steps do not see.  Column E of the histograms holds
+// the margins of that common step.
+struct StepLds {
+    int was[kPStride], now[kPStride];
+    int cum[64];
+    int n[kUThreads / 64], s[kUThreads / 64], x[kUThreads / 64], d[kUThreads / 64], pmin[kUThreads / 64];
+    int maxd, ran_out, lam, cap, worst;
+};
+
+__device__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const PriceMeta mt, const int *s_h, StepLds &s)
+{
+    constexpr int NW = kUThreads / 64;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int E = a.E, ES = a.es, nb = a.nb;
+    const bool even = a.mode == kModeSlack && t < a.even;
+    const bool all_in = a.mode != kModeSlack || even, level = a.mode == kModeOver || (a.mode == kModeSlack && !even);
+    const bool sampled = nrows < a.T;
+    const int w0 = bin_w0(mt.w), bs = a.bshift;
+    const int Ct = sampled ? (int)(((long long)a.C * nrows + a.T / 2) / a.T) : a.C;
+    const int *s_hn = s_h + 2 * nb * ES;
+    if (tid < 64) s.cum[tid] = 0;
+    if (tid == 0) {
+        s.maxd = s.ran_out = s.lam = s.worst = 0;
+        s.cap = 0x7fffffff;
+    }
+    __syncthreads();
+    int sn = 0, ss = 0, sx = 0, sd = 0, worst = 0;
+    for (int e = tid; e < E; e += kUThreads) {
+        const int ne = s_hn[e];
+        const bool in = all_in || s.was[e] > 0;
+        sn += in ? ne : 0;
+        ss += in ? 1 : 0;
+        sx += ne > Ct ? ne - Ct : 0;
+        worst = ne - Ct > worst ? ne - Ct : worst;
+        sd += in && ne < Ct ? Ct - ne : 0;
+    }
+    // holds (0 .. nb-1) and newcomers (nb .. 2nb-1) per margin bin over all experts
+    for (int b = wv; b < 2 * nb; b += NW) {
+        int tot = 0;
+        for (int e = lane; e < E; e += 64) tot += s_h[b * ES + e];
+        tot = wave_sum(tot);
+        if (lane == 63) s.cum[b] = tot;
+    }
+    if (worst > kWorst) s.worst = 1;
+    sn = wave_sum(sn);
+    ss = wave_sum(ss);
+    sx = wave_sum(sx);
+    sd = wave_sum(sd);
+    if (lane == 63) {
+        s.n[wv] = sn;
+        s.s[wv] = ss;
+        s.x[wv] = sx;
+        s.d[wv] = sd;
+    }
+    __syncthreads();
+    sn = ss = sx = sd = 0;
+#pragma unroll
+    for (int x = 0; x < NW; ++x) {
+        sn += s.n[x];
+        ss += s.s[x];
+        sx += s.x[x];
+        sd += s.d[x];
+    }
+    sx = sd > sx ? sd : sx;                                           // tokens too many or too few
+    const int target = ss > 0 ? (2 * sn + ss) / (2 * ss) : Ct;        // mean demand of the experts that count
+    const int X = sn - Ct * ss;                                       // what the common step has to take away
+    if (level && X < 0 && a.mode == kModeSlack) {
+        // A common step down ends for an expert at price 0, and from there on that expert takes part in what the step
+        // gains: the experts without a price at most treble in one step (its margins only know the present ones).
+        const int m = 2 * (E - ss > 0 ? E - ss : 1);
+        for (int e = tid; e < E; e += kUThreads) {
+            const int p = s.was[e];
+            if (p <= 0) continue;
+            int r = 0;
+            for (int f = 0; f < E; ++f) r += s.was[f] > 0 && (s.was[f] < p || (s.was[f] == p && f < e)) ? 1 : 0;
+            if (r == m - 1) s.cap = p + 1;
+        }
+        __syncthreads();
+    }
+    for (int j = tid; j < E + (level ? 1 : 0); j += kUThreads) {
+        const bool common = j == E;
+        const int pj = s.was[j];
+        const bool in = all_in || pj > 0;
+        const int diff = common ? X : s_hn[j] - (in ? target : Ct);
+        const int side = diff < 0 ? 1 : 0;                       // side 0: the price has to rise, side 1: to fall
+        const int need = side ? (in || common ? -diff : 0) : diff;       // (room left at price 0 is fine)
+        if (need == 0) continue;
+        const int *col = s_h + side * nb * ES + j;
+        int c[kPBins];
+#pragma unroll
+        for (int x = 0; x < kPBins; ++x) c[x] = x < nb ? col[x * ES] : 0;
+        int run = 0, prev = 0, h = 1, b = nb;
+#pragma unroll
+        for (int x = 0; x < kPBins; ++x) {
+            if (b == nb && x < nb) {
+                if (run + c[x] >= need) {
+                    b = x;
+                    prev = run;
+                    h = c[x];
+                }
+            }
+            run += c[x];
+        }
+        int d = mt.w;
+        if (b < nb) {
+            const int lo = bin_edge(b, w0, bs), hi = bin_edge(b + 1, w0, bs);
+            d = lo + (int)((float)(hi - lo) * (float)(need - prev) / (float)h + 0.5f);
+        }
+        if (common && side && a.mode == kModeSlack && d > s.cap) d = s.cap;
+        else if (b == nb) s.ran_out = 1;
+        d = d < 1 ? 1 : d;
+        atomicMax(&s.maxd, d);
+        if (common) s.lam = side ? -d : d;
+        else s.now[j] = pj + (side ? -d : d);
+    }
+    __syncthreads();
+    PriceMeta m2 = mt;
+    bool reach;
+    {
+        // the bound of the arc list: about kArcsPerExpert exchanges per expert lie under it.  h holds and n newcomers make
+        // h * n / rows of them if they are spread over all rows, and the larger of the two if every row has one of each.
+        const float want = (float)a.arcs_wanted * (float)nrows / (float)a.T;
+        const float ch = (float)wave_sum(lane < nb ? s.cum[lane] : 0), cn = (float)wave_sum(lane < nb ? s.cum[nb + lane] : 0);
+        const float cmin = fminf(fminf(ch, cn), (float)nrows), cum = cmin > 0.f ? ch * cn / cmin : 0.f;
+        const unsigned long long fb = __ballot(lane < nb && cum >= want), fw = __ballot(lane < nb && cum >= 1.5f * want);
+        int bound = mt.w;
+        if (fb) {
+            const int b = __ffsll((long long)fb) - 1, lo = bin_edge(b, w0, bs), hi = bin_edge(b + 1, w0, bs);
+            const float c1 = __shfl(cum, b), c0 = b > 0 ? __shfl(cum, b - 1) : 0.f;
+            bound = lo + (int)((float)(hi - lo) * (want - c0) / (c1 - c0));
+        }
+        const int wide = fw ? bin_edge(__ffsll((long long)fw), w0, bs) : 4 * mt.w;
+        m2.bound = (long long)a.T * a.k * (E - a.k) <= kAllArcs ? kMaxBound : bound < 2 ? 2 : (bound > kMaxBound ? kMaxBound : bound);
+        reach = fb != 0;
+        int w = s.maxd > wide ? s.maxd : wide;
+        if (s.ran_out && w < 4 * mt.w) w = 4 * mt.w;
+        m2.w = w < 16 ? 16 : (w < (1 << 26) ? w : (1 << 26));
+    }
+    ++m2.passes;
+    m2.excess = sampled ? (int)((long long)sx * a.T / nrows) : sx;
+    const bool listed = !a.retry || reach;               // another try needs more exchanges than the one before
+    // enough: what is left is cheaper to move by the search, or it no longer shrinks (it ends up alternating by a few)
+    if (!sampled && !even && (s.maxd == 0 || (m2.excess * kEnough <= E && !s.worst && listed) || (listed && m2.excess <= E && m2.excess * 5 >= mt.excess * 4 && t >= a.even + 4))) {
+        m2.done = 1;
+        m2.w = mt.w;
+        if (m2.excess == 0) m2.bound = 2;                // nothing to move
+        for (int e = tid; e < E; e += kUThreads) s.now[e] = s.was[e];
+    } else {
+        // near the end the experts chase each other's last tokens: shorter steps settle sooner
+        const bool damp = !sampled && m2.excess <= E;
+        const int plim = (1 << (31 - a.ib)) - 1;
+        int pm = 0x7fffffff;
+        for (int e = tid; e < E; e += kUThreads) {
+            int dp = s.now[e] - s.was[e];
+            dp = damp ? dp - dp * 3 / 8 : dp;
+            int pn = s.was[e] + dp + (level && (all_in || s.was[e] > 0) ? s.lam : 0);
+            if (a.mode == kModeSlack && !even) pn = pn < 0 ? 0 : pn;
+            pn = pn > plim ? plim : (pn < -plim ? -plim : pn);
+            s.now[e] = pn;
+            pm = pn < pm ? pn : pm;
+        }
+        if (even) {                        // the cheapest expert at price 0
+            for (int off = 32; off > 0; off >>= 1) {
+                const int o = __shfl_xor(pm, off);
+                pm = o < pm ? o : pm;
+            }
+            if (lane == 0) s.pmin[wv] = pm;
+            __syncthreads();
+            for (int x = 0; x < NW; ++x) pm = s.pmin[x] < pm ? s.pmin[x] : pm;
+            for (int e = tid; e < E; e += kUThreads) s.now[e] -= pm;
+        }
+    }
+    return m2;
+}
+
+// One workgroup.  (As the first step of every workgroup of the next pass the same work took 10 to 20 us: several dependent
+// reads of tables that the atomics of the pass have left in memory.)
+__global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, int nrows)
+{
+    extern __shared__ __attribute__((aligned(16))) int s_h[];         // the sum of the copies
+    __shared__ StepLds s;
+    PriceArea *ar = a.ar;
+    const int tid = threadIdx.x, E = a.E;
+    // everything is requested before the state is looked at (the exit test then does not add a round trip)
+    const int quads = (2 * a.nb + 1) * a.es / 4;
+    for (int e = tid; e < E; e += kUThreads) s.was[e] = s.now[e] = ar->prices[e];
+    for (int i = tid; i < quads; i += kUThreads) {
+        int4 x[kPCopies], y = make_int4(0, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < kPCopies; ++r) x[r] = ((const int4 *)ar->hist[r])[i];
+#pragma unroll
+        for (int r = 0; r < kPCopies; ++r) {
+            if ((x[r].x | x[r].y | x[r].z | x[r].w) != 0) ((int4 *)ar->hist[r])[i] = make_int4(0, 0, 0, 0);
+            y.x += x[r].x; y.y += x[r].y; y.z += x[r].z; y.w += x[r].w;
+        }
+        ((int4 *)s_h)[i] = y;
+    }
+    const PriceMeta mt = ar->meta;
+    if (mt.done) return;                 // (passes that find the prices done add nothing: the copies stay clear)
+    const PriceMeta m2 = price_step(a, t, nrows, mt, s_h, s);
+    for (int e = tid; e < E; e += kUThreads) ar->prices[e] = s.now[e];
+    if (tid == 0) ar->meta = m2;
+}
+
+// A group of G lanes owns a row; lane l owns columns (m >> 2) * 4G + 4l + (m & 3) for m < EPL (EPL >= 4: every load of
+// the group covers whole lines), else l * EPL + m.  A value and its column are packed into one 32-bit key, so that the
+// next best entry of a row is one subtract and one unsigned minimum per entry: the largest key below x is
+// x - 1 - min over keys of (x - 1 - key), entries at or above x wrap around to large numbers.
+template <int G, int EPL>
+struct RowKeys {
+    static __device__ __forceinline__ int col(int m, int lg)
+    {
+        return EPL >= 4 ? (m >> 2) * (4 * G) + lg * 4 + (m & 3) : lg * EPL + m;
+    }
+    static __device__ __forceinline__ void load(const int32_t *__restrict__ qr, int E, bool vec, int lg, int (&v)[EPL])
+    {
+        if (EPL >= 4 && vec) {
+#pragma unroll
+            for (int m = 0; m < EPL; m += 4) {
+                const int c = col(m, lg);
+                const int4 t4 = c < E ? *(const int4 *)(qr + c) : make_int4(0, 0, 0, 0);
+                v[m] = t4.x;
+                if constexpr (EPL >= 4) { v[m + 1] = t4.y; v[m + 2] = t4.z; v[m + 3] = t4.w; }
+            }
+        } else {
+#pragma unroll
+            for (int m = 0; m < EPL; ++m) v[m] = col(m, lg) < E ? qr[col(m, lg)] : 0;
+        }
+    }
+    static __device__ __forceinline__ unsigned first(const unsigned (&key)[EPL])
+    {
+        unsigned d = ~key[0];
+#pragma unroll
+        for (int m = 1; m < EPL; ++m) d = ~key[m] < d ? ~key[m] : d;
+        return ~group_min_u32<G>(d);
+    }
+    static __device__ __forceinline__ unsigned below(const unsigned (&key)[EPL], unsigned x)
+    {
+        const unsigned x1 = x - 1;
+        unsigned d = x1 - key[0];
+#pragma unroll
+        for (int m = 1; m < EPL; ++m) {
+            const unsigned dm = x1 - key[m];
+            d = dm < d ? dm : d;
+        }
+        return x1 - group_min_u32<G>(d);
+    }
+};
+
+// The margins of rows r_first .. r_end - 1 of a pass (row i is token i * stride + shift), added to the histograms in
+// s_hist; NT threads, G of them to a row.  nx holds this lane's part of its first row.
+template <int G, int EPL, int MODE, int NT>
+__device__ __forceinline__ void price_rows(const PriceArgs &a, int t, int W, int r_first, int r_end, int stride, int shift, int (&nx)[EPL],
+                                           const int *s_p, int *s_hist)
+{
+    using RK = RowKeys<G, EPL>;
+    constexpr int NG = NT / G;
+    const int tid = threadIdx.x, lane = tid & 63, lg = tid & (G - 1), gbase = lane & ~(G - 1), grp = tid / G;
+    const int E = a.E, k = a.k, ib = a.ib, nb = a.nb;
+    const int ES = a.es;
+    const bool vec = (E & 3) == 0 && (((size_t)a.q) & 15) == 0;
+    auto group_bits = [&](unsigned long long b) {
+        return G == 64 ? b : (b >> gbase) & ((1ull << (G & 63)) - 1);
+    };
+    const int w0 = bin_w0(W), bs = a.bshift;
+    const int bias = 1 << (31 - ib);
+    const unsigned cmask = (1u << ib) - 1;
+    int pb[EPL];                                          // bias - price of this lane's columns
+    unsigned in_m = 0;                                    // spare capacity: this lane's columns with a price
+#pragma unroll
+    for (int m = 0; m < EPL; ++m) {
+        const int c = RK::col(m, lg);
+        pb[m] = c < E ? bias - s_p[c] : 0;
+        if (MODE == kModeSlack && c < E && s_p[c] > 0) in_m |= 1u << m;
+    }
+    const bool common = MODE == kModeSlack && t >= a.even;            // margins of the common step are wanted
+    const unsigned keyo = (unsigned)bias << ib;           // an unfilled slot: reward 0, price 0
+    int *s_n = s_hist + 2 * nb * ES;
+    for (int i0 = r_first + grp; i0 - grp < r_end; i0 += NG) {
+        const bool live = i0 < r_end;
+        const int row = (live ? i0 : r_end - 1) * stride + shift;
+        int v[EPL];
+#pragma unroll
+        for (int m = 0; m < EPL; ++m) v[m] = nx[m];
+        if (i0 - grp + NG < r_end) {
+            int i = i0 + NG;
+            i = i < r_end ? i : r_end - 1;
+            RK::load(a.q + (size_t)(i * stride + shift) * E, E, vec, lg, nx);
+        }
+        const unsigned rot = row_mask(row, ib);
+        unsigned key[EPL];
+#pragma unroll
+        for (int m = 0; m < EPL; ++m) {
+            const int c = RK::col(m, lg);
+            key[m] = c < E ? (((unsigned)(v[m] + pb[m])) << ib) | ((unsigned)c ^ rot) : 0u;
+        }
+        unsigned kth = RK::first(key), mine = kth;        // mine: the (lg + 1)-th best key
+        for (int r = 1; r < k; ++r) {
+            kth = RK::below(key, kth);
+            mine = lg == r ? kth : mine;
+        }
+        const unsigned nxt = RK::below(key, kth);
+        const bool slot = lg < k && live;
+        // held: key >= thr; alt: the best a hold competes with; low: what a newcomer displaces
+        unsigned thr = kth, alt = nxt, low = kth;
+        bool near = (int)((kth - nxt) >> ib) < W;
+        if (MODE == kModeOver) {
+            thr = kth > keyo ? kth : keyo + 1;
+            low = kth > keyo ? kth : keyo;
+            alt = nxt > keyo ? nxt : keyo;
+            near = true;
+        }
+        const int mc = (int)((mine & cmask) ^ rot);
+        if (slot && mine >= thr && mc < E) atomicAdd(&s_n[mc], 1);
+        if (MODE == kModeOver && slot) {
+            // raising all prices together frees the slots in the order of their values, lowering fills the next best
+            const bool real = mine > keyo;
+            const int mg = (int)((real ? mine - keyo : keyo - mine) >> ib);
+            if (mg < W) atomicAdd(&s_hist[((real ? 0 : nb) + bin_of(mg, w0, bs)) * ES + E], 1);
+        }
+        if (!near) continue;
+        if (MODE == kModeSlack && common) {
+            // the i-th lowest hold with a price against the i-th best alternative without one, and the other way round
+            const bool priced = slot && mc < E && s_p[mc < E ? mc : 0] > 0;
+            const unsigned long long bp = group_bits(__ballot(priced)), bf = group_bits(__ballot(slot && !priced));
+            const int rp = priced ? __popcll(bp >> lg) - 1 : -1, rf = slot && !priced ? __popcll(bf >> lg) - 1 : -1;
+            unsigned ku[EPL], kd[EPL];
+#pragma unroll
+            for (int m = 0; m < EPL; ++m) {
+                const bool un = key[m] < kth;
+                ku[m] = un && !((in_m >> m) & 1u) ? key[m] : 0u;
+                kd[m] = un && ((in_m >> m) & 1u) ? key[m] : 0u;
+            }
+            unsigned u = RK::first(ku), d = RK::first(kd);
+            const int pairs = k < kLevelPairs ? k : kLevelPairs;
+            for (int i = 0; i < pairs; ++i) {
+                if (i) {
+                    u = u ? RK::below(ku, u) : 0u;
+                    d = d ? RK::below(kd, d) : 0u;
+                }
+                if (rp == i && u) {
+                    const int mg = (int)((mine - u) >> ib);
+                    if (mg < W) atomicAdd(&s_hist[bin_of(mg, w0, bs) * ES + E], 1);
+                }
+                if (rf == i && d) {
+                    const int mg = (int)((mine - d) >> ib);
+                    if (mg < W) atomicAdd(&s_hist[(nb + bin_of(mg, w0, bs)) * ES + E], 1);
+                }
+            }
+        }
+        if (live) {
+#pragma unroll
+            for (int m = 0; m < EPL; ++m) {
+                const int c = RK::col(m, lg);
+                const bool held = key[m] >= thr;
+                const int mg = (int)((held ? key[m] - alt : low - key[m]) >> ib);
+                if (mg < W && c < E) atomicAdd(&s_hist[((held ? 0 : nb) + bin_of(mg, w0, bs)) * ES + c], 1);
+            }
+        }
+    }
+}
+
+// One price pass over `nrows` rows.
+template <int G, int EPL, int MODE>
+__global__ __launch_bounds__(kPThreads) void k_price(PriceArgs a, int t, int nrows, int stride, int shift, int rows_per_wg)
+{
+    using RK = RowKeys<G, EPL>;
+    extern __shared__ __attribute__((aligned(16))) int s_hist[];      // (2 * nb + 1) x ES: margins of holds, of newcomers, holds
+    __shared__ int s_p[kPStride];
+    PriceArea *ar = a.ar;
+    const int tid = threadIdx.x, lg = tid & (G - 1), grp = tid / G;
+    const int E = a.E, nb = a.nb, ES = a.es;
+    const bool vec = (E & 3) == 0 && (((size_t)a.q) & 15) == 0;
+    const int r_first = blockIdx.x * rows_per_wg;
+    int r_end = r_first + rows_per_wg;
+    r_end = r_end < nrows ? r_end : nrows;
+    // the first row is on its way while the prices are fetched
+    int nx[EPL];
+    {
+        int i = r_first + grp;
+        i = i < nrows ? i : nrows - 1;
+        RK::load(a.q + (size_t)(i * stride + shift) * E, E, vec, lg, nx);
+    }
+    const PriceMeta mt = ar->meta;
+    for (int e = tid; e < E; e += kPThreads) s_p[e] = ar->prices[e];
+    if (mt.done) return;
+    const int hquads = (2 * nb + 1) * ES / 4;
+    for (int i = tid; i < hquads; i += kPThreads) ((int4 *)s_hist)[i] = make_int4(0, 0, 0, 0);
+    __syncthreads();
+    price_rows<G, EPL, MODE, kPThreads>(a, t, mt.w, r_first, r_end, stride, shift, nx, s_p, s_hist);
+    __syncthreads();
+    int *hg = ar->hist[blockIdx.x & (kPCopies - 1)];
+    for (int i = tid; i < hquads; i += kPThreads) {
+        const int4 x = ((int4 *)s_hist)[i];
+        if (x.x) atomicAdd(hg + 4 * i, x.x);
+        if (x.y) atomicAdd(hg + 4 * i + 1, x.y);
+        if (x.z) atomicAdd(hg + 4 * i + 2, x.z);
+        if (x.w) atomicAdd(hg + 4 * i + 3, x.w);
+    }
+}
+
+// prices come in units of 1 / 2^sb
+__device__ __forceinline__ int first_price(const int64_t *__restrict__ prices_in, int e, int E, int plim)
+{
+    int sb = 0;
+    while ((1 << sb) < E + 1) ++sb;
+    const long long p = prices_in && e < E ? prices_in[e] >> sb : 0;
+    return p < 0 ? 0 : (p > plim ? plim : (int)p);
+}
+__device__ __forceinline__ PriceMeta first_meta(const PriceArea *ar, const int64_t *prices_in, int retry)
+{
+    return PriceMeta{retry ? ar->meta.w : kFirstWindow, 0, 2, retry ? ar->meta.passes : prices_in ? -1 : 0, 0x7fffffff, {0, 0, 0}};
+}
+
+// All passes of a small batch in one workgroup: a pass takes 4 to 8 us instead of two launches of 20 to 25 us together,
+// none is launched in vain, and a batch that settles slowly may take more of them.
+template <int G, int EPL, int MODE>
+__global__ __launch_bounds__(kUThreads) void k_price_small(PriceArgs a, int n_pass, int plim, const int64_t *__restrict__ prices_in)
+{
+    using RK = RowKeys<G, EPL>;
+    extern __shared__ __attribute__((aligned(16))) int s_hist[];
+    __shared__ StepLds s;
+    PriceArea *ar = a.ar;
+    const int tid = threadIdx.x, lg = tid & (G - 1), grp = tid / G, E = a.E;
+    const bool vec = (E & 3) == 0 && (((size_t)a.q) & 15) == 0;
+    const int hquads = (2 * a.nb + 1) * a.es / 4;
+    PriceMeta mt = first_meta(ar, prices_in, a.retry);
+    if (tid == 0 && !a.retry) ar->t_start = wall_clock64();
+    for (int e = tid; e < E; e += kUThreads) s.was[e] = a.retry ? ar->prices[e] : first_price(prices_in, e, E, plim);
+    for (int i = tid; i < 8 * kPStride; i += kUThreads) (&ar->loads[0][0])[i] = 0;
+    for (int t = 0; t < n_pass && !mt.done; ++t) {
+        int nx[EPL];
+        RK::load(a.q + (size_t)(grp < a.T ? grp : a.T - 1) * E, E, vec, lg, nx);
+        for (int i = tid; i < hquads; i += kUThreads) ((int4 *)s_hist)[i] = make_int4(0, 0, 0, 0);
+        __syncthreads();
+        price_rows<G, EPL, MODE, kUThreads>(a, t, mt.w, 0, a.T, 1, 0, nx, s.was, s_hist);
+        for (int e = tid; e < E; e += kUThreads) s.now[e] = s.was[e];
+        __syncthreads();
+        mt = price_step(a, t, a.T, mt, s_hist, s);
+        __syncthreads();
+        for (int e = tid; e < E; e += kUThreads) s.was[e] = s.now[e];
+    }
+    for (int e = tid; e < E; e += kUThreads) ar->prices[e] = s.was[e];
+    if (tid == 0) {
+        ar->meta = mt;
+        ar->n_arcs = ar->fail = 0;
+    }
+}
+
+// The last pass: assignment, pairs per block and expert, sum of the rewards, and the arcs under the bound.
+template <int G, int EPL, bool OS>
+__global__ __launch_bounds__(kPThreads) void k_price_assign(PriceArgs a)
+{
+    using RK = RowKeys<G, EPL>;
+    constexpr int NG = kPThreads / G;
+    __shared__ int s_p[kPStride], s_cnt[kPStride];
+    __shared__ unsigned s_thr[kPRowsMax];
+    __shared__ int s_rc[kPRowsMax];
+    __shared__ short s_queue[kPRowsMax];
+    __shared__ int s_nq, s_base, s_total, s_bad;
+    __shared__ long long s_sum[kPThreads / 64];
+    PriceArea *ar = a.ar;
+    const int tid = threadIdx.x, lane = tid & 63, lg = tid & (G - 1), gbase = lane & ~(G - 1), grp = tid / G;
+    const int E = a.E, k = a.k, ib = a.ib, w = blockIdx.x;
+    const bool vec = (E & 3) == 0 && (((size_t)a.q) & 15) == 0;
+    const int row0 = w * a.rows;
+    int nr = a.T - row0;
+    nr = nr < a.rows ? nr : a.rows;
+    auto group_bits = [&](unsigned long long b) {
+        return G == 64 ? b : (b >> gbase) & ((1ull << (G & 63)) - 1);
+    };
+    int nx[EPL];
+    RK::load(a.q + (size_t)(row0 + (grp < nr ? grp : nr - 1)) * E, E, vec, lg, nx);
+    for (int j = tid; j < kPStride; j += kPThreads) s_cnt[j] = 0;
+    for (int i = tid; i < a.rows; i += kPThreads) s_rc[i] = 0;
+    if (tid == 0) {
+        s_nq = 0;
+        s_bad = 0;
+        s_total = 0;
+    }
+    for (int e = tid; e < E; e += kPThreads) s_p[e] = ar->prices[e];
+    const int B = ar->meta.bound;
+    __syncthreads();
+    const int bias = 1 << (31 - ib);
+    const unsigned cmask = (1u << ib) - 1;
+    int pb[EPL];
+#pragma unroll
+    for (int m = 0; m < EPL; ++m) pb[m] = RK::col(m, lg) < E ? bias - s_p[RK::col(m, lg)] : 0;
+    const unsigned keyo = OS ? (unsigned)bias << ib : 0u;              // an unfilled slot: reward 0, price 0
+    bool bad = false;
+    auto make_keys = [&](int row, const int(&v)[EPL], unsigned(&key)[EPL]) {
+        const unsigned rot = row_mask(row, ib);
+#pragma unroll
+        for (int m = 0; m < EPL; ++m) {
+            const int c = RK::col(m, lg);
+            const unsigned x = (unsigned)(v[m] + pb[m]);
+            const bool wide = v[m] > (1 << 30) || v[m] < -(1 << 30) || x == 0u || (x >> (32 - ib)) != 0;
+            if (c < E) bad |= wide;
+            key[m] = c < E ? (x << ib) | ((unsigned)c ^ rot) : 0u;
+        }
+    };
+    long long sum = 0;
+    for (int l0 = grp; l0 - grp < nr; l0 += NG) {
+        const bool live = l0 < nr;
+        const int lr = live ? l0 : nr - 1, row = row0 + lr;
+        int v[EPL];
+#pragma unroll
+        for (int m = 0; m < EPL; ++m) v[m] = nx[m];
+        if (l0 - grp + NG < nr) RK::load(a.q + (size_t)(row0 + (l0 + NG < nr ? l0 + NG : nr - 1)) * E, E, vec, lg, nx);
+        unsigned key[EPL];
+        make_keys(row, v, key);
+        unsigned cur = RK::first(key), mine = 0, kth = cur, over = 0, under = 0;
+        bool have_under = false;
+        for (int r = 0; r < k; ++r) {
+            if (r) cur = RK::below(key, cur);
+            if (lg == r) mine = cur;
+            if (OS) {
+                if (cur > keyo) over = cur;
+                else if (!have_under) {
+                    under = cur;
+                    have_under = true;
+                }
+            }
+        }
+        kth = cur;
+        const unsigned nxt = RK::below(key, cur);
+        if (live) {
+            if (OS && !have_under) under = nxt;
+            const bool real = lg < k && (!OS || mine > keyo);
+            if (lg < k) {
+                const int c = (int)((mine & cmask) ^ row_mask(row, ib));
+                a.assign[(size_t)row * k + lg] = real ? c : -1;
+                if (real) {
+                    if (c < E) atomicAdd(&s_cnt[c], 1);
+                    else bad = true;
+                    sum += (long long)(int)(mine >> ib) - bias + s_p[c < E ? c : 0];
+                }
+            }
+            bool queue;
+            unsigned thr = kth;
+            if (OS) {
+                thr = kth > keyo ? kth : keyo + 1;
+                const unsigned alt = under > keyo ? under : keyo;
+                queue = (over != 0 && (int)((over - alt) >> ib) <= B) || (have_under && (int)((keyo - under) >> ib) <= B);
+            } else {
+                queue = k < E && (int)((kth >> ib) - (nxt >> ib)) < B;
+            }
+            if (queue && lg == 0) {
+                s_thr[lr] = thr;
+                s_queue[atomicAdd(&s_nq, 1)] = (short)lr;
+            }
+        }
+    }
+    if (bad) s_bad = 1;
+    for (int off = 32; off > 0; off >>= 1) {
+        const unsigned lo = __shfl_xor((unsigned)sum, off), hi = __shfl_xor((unsigned)((unsigned long long)sum >> 32), off);
+        sum += (long long)(((unsigned long long)hi << 32) | lo);
+    }
+    if (lane == 0) s_sum[tid >> 6] = sum;
+    __syncthreads();
+    for (int e = tid; e < E; e += kPThreads) {
+        const int c = s_cnt[e];
+        a.blkcnt[(size_t)w * E + e] = c;
+        if (c) atomicAdd(&ar->loads[w & 7][e], c);
+    }
+    if (tid == 0) {
+        a.wg_sum[w] = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
+        if (s_bad) ar->fail = 1;
+    }
+    // arcs: counted per row, then written in row order
+    const int nq = s_nq;
+    if (nq == 0 || s_bad) {
+        if (tid == 0) a.wg_arcs[w] = make_int2(0, 0);
+        return;
+    }
+    auto row_arcs = [&](int lr, int at) {                  // at < 0: count only
+        const int row = row0 + lr;
+        int v[EPL];
+        unsigned key[EPL];
+        RK::load(a.q + (size_t)row * E, E, vec, lg, v);
+        make_keys(row, v, key);
+        const unsigned thr = s_thr[lr], rot = row_mask(row, ib);
+        const int vo = (int)(keyo >> ib);
+        int n = 0, held = 0;
+        unsigned cur = RK::first(key);
+        auto put = [&](bool ok, int cost, int from, int to) {
+            const unsigned long long bal = group_bits(__ballot(ok));
+            if (at >= 0 && ok) {
+                const int pos = at + n + __popcll(bal & ((1ull << lg) - 1));
+                ar->arc[pos] = ((unsigned long long)(unsigned)cost << 32) | (unsigned)((from << 16) | to);
+                ar->arc_tok[pos] = row;
+            }
+            n += __popcll(bal);
+        };
+        for (int r = 0; r < k && cur >= thr; ++r) {
+            const int va = (int)(cur >> ib), from = (int)((cur & cmask) ^ rot);
+            ++held;
+#pragma unroll
+            for (int m = 0; m < EPL; ++m) {
+                const int c = RK::col(m, lg), cost = va - (int)(key[m] >> ib);
+                put(c < E && key[m] < thr && cost < B, cost, from, c);
+            }
+            if (OS) put(lg == 0 && va - vo < B, va - vo, from, E);
+            cur = RK::below(key, cur);
+        }
+        if (OS && held < k) {
+#pragma unroll
+            for (int m = 0; m < EPL; ++m) {
+                const int c = RK::col(m, lg), cost = vo - (int)(key[m] >> ib);
+                put(c < E && key[m] < thr && cost < B, cost, E, c);
+            }
+        }
+        return n;
+    };
+    for (int i = grp; i < nq; i += NG) {
+        const int lr = s_queue[i];
+        const int n = row_arcs(lr, -1);
+        if (lg == 0) s_rc[lr] = n;
+    }
+    __syncthreads();
+    if (tid < 64) {
+        int run = 0;
+        for (int i0 = 0; i0 < a.rows; i0 += 64) {
+            const int c = i0 + lane < a.rows ? s_rc[i0 + lane] : 0;
+            const int inc = wave_sum(c);
+            if (i0 + lane < a.rows) s_rc[i0 + lane] = run + inc - c;
+            run += __builtin_amdgcn_readlane(inc, 63);
+        }
+        if (lane == 0) {
+            int base = 0;
+            if (run > 0) {
+                base = atomicAdd(&ar->n_arcs, run);
+                if (base + run > kPArcBuf) {
+                    ar->fail = 1;
+                    run = 0;
+                }
+            }
+            a.wg_arcs[w] = make_int2(base, run);
+            s_base = base;
+            s_total = run;
+        }
+    }
+    __syncthreads();
+    if (s_total == 0) return;
+    for (int i = grp; i < nq; i += NG) {
+        const int lr = s_queue[i];
+        (void)row_arcs(lr, s_base + s_rc[lr]);
+    }
+}
+
+// ---- the search ----
+
+struct FinishLds {
+    unsigned ft[kPArcs];              // from << 16 | to
+    int tok[kPArcs];                  // -1: an arc of Z
+    int cost[kPArcs];                 // cost an arc enters with (kept in registers from then on)
+    int dst[kPBlocks];                // place of every block's arcs in the list
+    unsigned long long best[kPStride];
+    unsigned lab[kPStride];           // distance << 10 | hops
+    int pred[kPStride];               // last arc of the shortest path
+    int p[kPStride], pi[kPStride], ex[kPStride], sl[kPStride], dd[kPStride];
+    int list[kPStride], mtok[kPStride], ncnt[64];
+    unsigned long long wkey[kPStride];   // paths that won their branch: distance and target
+    int wroot[kPStride];                 // ... their root ...
+    int wtok[kPStride];                  // ... and the token that leaves or joins the root
+    unsigned bloom[128];
+    int chg[3], wsum[2][kFThreads / 64];
+    int bad, bad_move, dmax, n_win;       // bad: found while paths are chosen; bad_move: while tokens move
+    long long dsum;
+};
+
+constexpr unsigned kLabInf = ~0u, kLabMax = 1u << 31;      // labels from kLabMax on are not followed (distances beyond 2^21)
+constexpr unsigned kWInf = 0x7fffffffu, kWMax = 1u << 21;
+static_assert(sizeof(FinishLds) <= 160 * 1024, "one compute unit's LDS");
+static_assert(kMaxBound < (int)kWMax, "every arc under the bound can be followed");
+
+__device__ __forceinline__ int block_scan(int v, int *s_w, int &total)     // exclusive prefix over the workgroup (one barrier)
+{
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int inc = wave_sum(v);
+    if (lane == 63) s_w[wv] = inc;
+    __syncthreads();
+    const int x = lane < kFThreads / 64 ? s_w[lane] : 0;
+    const int xi = wave_sum(x);
+    total = __builtin_amdgcn_readlane(xi, 63);
+    return inc - v + __builtin_amdgcn_readlane(xi, wv) - __builtin_amdgcn_readlane(x, wv);
+}
+
+// One workgroup.  Arc i belongs to thread i mod 1024, which keeps its reduced cost in a register.
+template <int TEPL>
+__global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t *prices, int64_t *price_scale,
+                                                            SolverState *host_state)
+{
+    __shared__ FinishLds s;
+    PriceArea *ar = a.ar;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int E = a.E, k = a.k, N = E + 1, mode = a.mode;
+    const bool slack = mode == kModeSlack, os = mode == kModeOver;
+    const PriceMeta mt = ar->meta;
+    const int B = mt.bound;
+    const int *pg = ar->prices;
+    int rounds = 0, augs = 0;
+    bool close = false;                          // not solved, but near enough for another try
+    const int n_listed = ar->n_arcs;
+    bool ok = ar->fail == 0 && n_listed <= kPArcBuf && a.n_wg <= kPBlocks;
+    const int A0 = slack ? 2 * E : 0;
+    if (A0 + n_listed > kPArcs) ok = false;
+    if (tid == 0) {
+        s.bad = s.bad_move = 0;
+        s.dsum = 0;
+    }
+    for (int v = tid; v < N; v += kFThreads) {
+        int n = 0;
+        if (v < E)
+            for (int r = 0; r < 8; ++r) n += ar->loads[r][v];
+        const int p = v < E ? pg[v] : 0;
+        s.p[v] = p;
+        s.pi[v] = 0;
+        s.sl[v] = (slack && v < E && p == 0 && n < a.C) ? a.C - n : 0;
+        s.ex[v] = v < E ? n + s.sl[v] - a.C : 0;
+    }
+    __syncthreads();
+    {
+        int tot, pos;
+        const int e0 = tid < E ? s.ex[tid] : 0;
+        (void)block_scan(e0, s.wsum[0], tot);
+        (void)block_scan(e0 > 0 ? e0 : 0, s.wsum[1], pos);
+        if (tid == 0) s.ex[E] = -tot;            // Z or the unfilled slots: supply and demand match overall
+        const int most = pos > pos - tot ? pos : pos - tot;
+        if (mode == kModeTight && tot != 0) ok = false;
+        if (most > 8 * E + 64) ok = false;       // the prices are far from an equilibrium
+        close = ar->fail == 0 && most <= 2 * E + 64;
+    }
+    int n_arcs = A0 + n_listed;
+    // arcs, in block order
+    if (ok) {
+        const int per = (a.n_wg + kFThreads - 1) / kFThreads, w0 = tid * per;      // <= 4
+        int mine = 0, tot;
+        int2 bc[kPBlocks / kFThreads];
+#pragma unroll
+        for (int i = 0; i < kPBlocks / kFThreads; ++i) {
+            bc[i] = i < per && w0 + i < a.n_wg ? a.wg_arcs[w0 + i] : make_int2(0, 0);
+            mine += bc[i].y;
+        }
+        int at = A0 + block_scan(mine, s.wsum[0], tot);
+#pragma unroll
+        for (int i = 0; i < kPBlocks / kFThreads; ++i) {
+            if (i < per && w0 + i < a.n_wg) s.dst[w0 + i] = at - bc[i].x;
+            at += bc[i].y;
+        }
+        __syncthreads();
+        for (int i = tid; i < n_listed; i += kFThreads) {
+            const unsigned long long r = ar->arc[i];
+            const int u = ar->arc_tok[i];
+            const int to = i + s.dst[u / a.rows];
+            s.ft[to] = (unsigned)r;
+            s.cost[to] = (int)(r >> 32);
+            s.tok[to] = u;
+        }
+        for (int i = tid; i < A0; i += kFThreads) {
+            s.ft[i] = i < E ? (unsigned)((i << 16) | E) : (unsigned)((E << 16) | (i - E));
+            s.cost[i] = 0;
+            s.tok[i] = -1;
+        }
+    }
+    __syncthreads();
+    unsigned ft[kFRegs], w[kFRegs];
+#pragma unroll
+    for (int j = 0; j < kFRegs; ++j) {
+        const int i = tid + j * kFThreads;
+        const bool in = ok && i < n_arcs;
+        ft[j] = in ? s.ft[i] : 0u;
+        w[j] = in ? (unsigned)s.cost[i] : kWInf;
+    }
+    bool solved = false, was_forward = true;
+    const int max_rounds = 8 * E + 128;
+    for (; ok; ++rounds) {
+        if (!__syncthreads_or(tid < N && s.ex[tid] != 0)) {
+            solved = true;
+            break;
+        }
+        if (rounds >= max_rounds) break;
+        // arcs of Z: a spare place may leave an expert that has one, and may enter any expert at its price
+        if (tid < A0) {
+            const int v = tid < E ? tid : tid - E;
+            const int c = s.p[v] - s.pi[v] + s.pi[E];
+            w[0] = tid < E ? (s.sl[v] > 0 ? (unsigned)-c : kWInf) : (unsigned)c;
+            if (w[0] != kWInf && (int)w[0] < 0) s.bad = 1;
+        }
+        // Spare places, or unfilled slots: whatever is too many goes to the nearest place that lacks a token or has one to
+        // spare (the trees grow backward from all of these), and what Z then has too many to the places that lack one.
+        // Sent from expert to expert instead, nearly all paths would lead through Z, one at a time.  Otherwise the trees
+        // grow from the side with fewer nodes: a tree ends a path at every node of the other side only once, but its root
+        // can send as many paths as it has units.
+        const int ev = tid < N ? s.ex[tid] : 0;
+        const bool hub = os && tid == E;
+        const bool spare_here = slack && tid < E && ev == 0 && s.sl[tid] > 0;
+        const bool is_src = ev > 0 && (mode == kModeTight || tid < E), is_snk = ev < 0;
+        int n_both;
+        (void)block_scan((is_src ? 1 : 0) | (is_snk ? 1 << 16 : 0), s.wsum[1], n_both);
+        const bool via_z = mode != kModeTight && (n_both & 0xffff) > 0;
+        const bool forward = mode == kModeTight ? (n_both & 0xffff) <= (n_both >> 16) : !via_z;
+        if (forward != was_forward) {
+            was_forward = forward;
+#pragma unroll
+            for (int j = 0; j < kFRegs; ++j) ft[j] = __builtin_amdgcn_alignbit(ft[j], ft[j], 16);    // tail and head change places
+        }
+        const bool is_root = via_z ? hub || spare_here || (is_snk && tid < E) : forward ? ev > 0 : is_snk;
+        const bool is_target = via_z ? is_src : forward ? is_snk && tid < E + (mode == kModeTight) : is_src;
+        if (tid < N) {
+            s.lab[tid] = is_root ? 0u : kLabInf;
+            s.pred[tid] = 0x7fffffff;
+            s.best[tid] = ~0ull;
+        }
+        if (tid < 3) s.chg[tid] = 0;
+        if (tid < 128) s.bloom[tid] = 0;
+        if (tid == 0) {
+            s.dmax = 0;
+            s.n_win = 0;
+        }
+        __syncthreads();
+        // Shortest paths from (backward: to) all roots.  Labels only fall, and where they end does not depend on the order in which
+        // arcs are looked at; hops break ties of distance, so that the last arcs form trees.
+        bool settled = false;
+        for (int it = 0; it < 4 * N; ++it) {
+            bool any = false;
+#pragma unroll
+            for (int twice = 0; twice < 2; ++twice) {
+                unsigned la[kFRegs], lb[kFRegs];
+#pragma unroll
+                for (int j = 0; j < kFRegs; ++j)
+                    if (j * kFThreads < n_arcs) {
+                        la[j] = s.lab[ft[j] >> 16];
+                        lb[j] = s.lab[ft[j] & 0xffff];
+                    }
+#pragma unroll
+                for (int j = 0; j < kFRegs; ++j)
+                    if (j * kFThreads < n_arcs) {
+                        const unsigned c = la[j] + (w[j] << 10) + 1;
+                        if (w[j] < kWMax && la[j] < kLabMax && c < lb[j]) {
+                            atomicMin(&s.lab[ft[j] & 0xffff], c);
+                            any = true;
+                        }
+                    }
+            }
+            if (any) s.chg[it % 3] = 1;
+            if (tid == 0) s.chg[(it + 1) % 3] = 0;
+            __syncthreads();
+            if (!s.chg[it % 3]) {
+                settled = true;
+                break;
+            }
+        }
+        // last arcs of the paths (the lowest arc wins)
+#pragma unroll
+        for (int j = 0; j < kFRegs; ++j)
+            if (j * kFThreads < n_arcs) {
+                const unsigned la = s.lab[ft[j] >> 16];
+                if (w[j] < kWMax && la < kLabMax && la + (w[j] << 10) + 1 == s.lab[ft[j] & 0xffff])
+                    atomicMin(&s.pred[ft[j] & 0xffff], tid + j * kFThreads);
+            }
+        const unsigned lv = tid < N ? s.lab[tid] : kLabInf;
+        const bool reached = lv < kLabMax;
+        const int dist = reached ? (int)(lv >> 10) : 0;
+        __syncthreads();
+        // every branch of a root offers the path to its nearest target, a root takes as many as it has units
+        const bool target = is_target && reached;
+        int root = tid, branch = tid;
+        const int hops = (int)(lv & 1023);
+        const unsigned long long my_key = ((unsigned long long)dist << 10) | (unsigned)tid;
+        if (target) {
+            int x = tid;
+            for (int i = 0; i < hops; ++i) {
+                const int idx = s.pred[x];
+                if (idx >= n_arcs) break;
+                branch = x;
+                x = forward ? (int)(s.ft[idx] >> 16) : (int)(s.ft[idx] & 0xffff);
+            }
+            root = x;
+            atomicMin(&s.best[branch], my_key);
+        }
+        __syncthreads();
+        bool win = target && s.best[branch] == my_key;
+        int n_off;
+        const int wat = block_scan(win ? 1 : 0, s.wsum[0], n_off);
+        const bool uses_spare = slack && win && via_z && s.ex[root] == 0;
+        if (win) {
+            s.wkey[wat] = my_key;
+            s.wroot[wat] = root;
+            s.wtok[wat] = s.tok[s.pred[branch]];
+        }
+        __syncthreads();
+        if (win) {
+            const int i_tok = s.wtok[wat];
+            int before = 0;
+            for (int i = 0; i < n_off; ++i) {
+                if (s.wkey[i] >= my_key || s.wroot[i] != root) continue;
+                if (i_tok >= 0 && s.wtok[i] == i_tok) win = false;           // (the token has one place at the root)
+                ++before;
+            }
+            const int er = s.ex[root];
+            win = win && before < (os && via_z && root == E ? 1 << 30 : er != 0 ? (er > 0 ? er : -er) : s.sl[root]);
+        }
+        if (win) atomicMax(&s.dmax, dist);
+        int nm;
+        const int at = block_scan(win ? hops : 0, s.wsum[1], nm);
+        if (win && at + hops <= kPStride) {                // (always: the paths are disjoint)
+            atomicAdd(&s.n_win, 1);
+            int x = tid;
+            for (int i = 0; i < hops; ++i) {
+                const int idx = s.pred[x];
+                if (idx >= n_arcs) {
+                    s.bad = 1;
+                    break;
+                }
+                const int from = (int)(s.ft[idx] >> 16), to = (int)(s.ft[idx] & 0xffff);
+                s.list[at + i] = idx;
+                s.mtok[at + i] = s.tok[idx];
+                if (slack) {
+                    if (from == E) atomicAdd(&s.sl[to], 1);          // a spare place comes to `to`
+                    else if (to == E) atomicAdd(&s.sl[from], -1);    // a spare place leaves
+                }
+                x = forward ? from : to;
+            }
+            const int src = forward ? root : tid, snk = forward ? tid : root;
+            atomicAdd(&s.ex[src], -1);
+            if (!uses_spare) atomicAdd(&s.ex[snk], 1);
+            else {
+                atomicAdd(&s.sl[snk], -1);
+                atomicAdd(&s.ex[E], 1);
+            }
+        }
+        if (tid < N) {
+            // (no further than the paths taken: experts far from them keep their potentials close to the others)
+            const int d = reached && dist < s.dmax ? dist : s.dmax;
+            s.dd[tid] = d;
+            s.pi[tid] += forward ? d : -d;
+        }
+        __syncthreads();
+        if (s.n_win == 0 || s.bad || !settled || nm > kPStride) break;         // no way to place what is left with these arcs
+        augs += s.n_win;
+        // reduced costs under the new potentials (tail and head: potentials and arcs are both turned round backward)
+#pragma unroll
+        for (int j = 0; j < kFRegs; ++j)
+            if (w[j] != kWInf) w[j] += (unsigned)(s.dd[ft[j] >> 16] - s.dd[ft[j] & 0xffff]);
+        // The tokens of the paths move, up to 64 path arcs at a time: a wavefront takes four of them, with all rows on
+        // their way together.  The arcs a token offers from where it is now replace its old ones in the list.
+        const int n_old = n_arcs;
+        bool full = false;
+        for (int b0 = 0; b0 < nm; b0 += 64) {
+            int h[4], qv[4][TEPL];
+#pragma unroll
+            for (int y = 0; y < 4; ++y) {
+                const int i = b0 + wv + 16 * y;
+                const int u = i < nm ? s.mtok[i] : -1;
+                h[y] = (u >= 0 && lane < k) ? __hip_atomic_load(&a.assign[(size_t)u * k + lane], __ATOMIC_RELAXED,
+                                                                __HIP_MEMORY_SCOPE_AGENT)
+                                            : -2;
+#pragma unroll
+                for (int m = 0; m < TEPL; ++m)
+                    qv[y][m] = u >= 0 && lane + 64 * m < E ? a.q[(size_t)u * E + lane + 64 * m] : 0;
+            }
+            // calls put(ok, cost, from, to) for every exchange of a token: slot by slot, then column by column
+            auto each_arc = [&](int hy, const int(&qy)[TEPL], auto put) {
+                int v[TEPL];
+                unsigned heldm = 0;
+#pragma unroll
+                for (int m = 0; m < TEPL; ++m) v[m] = lane + 64 * m < E ? qy[m] - s.p[lane + 64 * m] : 0;
+                for (int sl = 0; sl < k; ++sl) {
+                    const int e = __builtin_amdgcn_readlane(hy, sl);
+                    if (e >= 0 && (e & 63) == lane) heldm |= 1u << (e >> 6);
+                }
+                int n_real = 0;
+                for (int sl = 0; sl < k; ++sl) {
+                    const int e = __builtin_amdgcn_readlane(hy, sl);
+                    if (e < 0) continue;
+                    ++n_real;
+                    int x = v[0];
+#pragma unroll
+                    for (int m = 1; m < TEPL; ++m) x = (e >> 6) == m ? v[m] : x;
+                    const int vh = __builtin_amdgcn_readlane(x, e & 63);
+#pragma unroll
+                    for (int m = 0; m < TEPL; ++m)
+                        put(lane + 64 * m < E && !((heldm >> m) & 1u) && vh - v[m] < B, vh - v[m], e, lane + 64 * m);
+                    if (os) put(lane == 0 && vh < B, vh, e, E);
+                }
+                if (os && n_real < k) {
+#pragma unroll
+                    for (int m = 0; m < TEPL; ++m)
+                        put(lane + 64 * m < E && !((heldm >> m) & 1u) && -v[m] < B, -v[m], E, lane + 64 * m);
+                }
+            };
+#pragma unroll
+            for (int y = 0; y < 4; ++y) {
+                const int i = b0 + wv + 16 * y;
+                if (i >= nm) continue;
+                const int u = s.mtok[i];
+                int n = -1;
+                bool first = u >= 0;
+                if (first)
+                    for (int x0 = 0; x0 < i; x0 += 64)
+                        if (__any(x0 + lane < i && s.mtok[x0 + lane] == u)) first = false;      // a token on two paths is taken once
+                if (first) {
+                    int32_t *ra = a.assign + (size_t)u * k;
+                    int *bcnt = a.blkcnt + (size_t)(u / a.rows) * E;
+                    bool moved = false;
+                    for (int x0 = i; x0 < nm; x0 += 64) {
+                        unsigned long long same = __ballot(x0 + lane < nm && s.mtok[x0 + lane] == u);
+                        while (same) {
+                            const int x = x0 + __ffsll((long long)same) - 1;
+                            same &= same - 1;
+                            const unsigned f = s.ft[s.list[x]];
+                            const int from = __builtin_amdgcn_readfirstlane((int)(f >> 16));
+                            const int to = __builtin_amdgcn_readfirstlane((int)(f & 0xffff));
+                            const unsigned long long bf = __ballot(h[y] == (from < E ? from : -1));
+                            const unsigned long long bt = to < E ? __ballot(h[y] == to) : 0ull;
+                            if (bf == 0 || bt != 0) {          // (never: the arcs of a token are those of its row)
+                                s.bad_move = 1;
+                                continue;
+                            }
+                            if (lane == __ffsll((long long)bf) - 1) h[y] = to < E ? to : -1;
+                            moved = true;
+                            int qt = 0, qf = 0;
+#pragma unroll
+                            for (int m = 0; m < TEPL; ++m) {
+                                if (to < E && (to >> 6) == m) qt = __builtin_amdgcn_readlane(qv[y][m], to & 63);
+                                if (from < E && (from >> 6) == m) qf = __builtin_amdgcn_readlane(qv[y][m], from & 63);
+                            }
+                            if (lane == 0) {
+                                atomicAdd((unsigned long long *)&s.dsum, (unsigned long long)((long long)qt - qf));
+                                if (from < E) atomicAdd(&bcnt[from], -1);
+                                if (to < E) atomicAdd(&bcnt[to], 1);
+                            }
+                        }
+                    }
+                    if (moved) {
+                        int dst = lane;
+                        if (os) {                              // empty slots go to the end of the row
+                            const unsigned long long be = __ballot(h[y] == -1), br = __ballot(h[y] >= 0);
+                            dst = h[y] >= 0 ? __popcll(br & ((1ull << lane) - 1))
+                                            : __popcll(br) + __popcll(be & ((1ull << lane) - 1));
+                        }
+                        if (lane < k) __hip_atomic_store(&ra[dst], h[y], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                    if (lane == 0) atomicOr(&s.bloom[(u >> 5) & 127], 1u << (u & 31));
+                    n = 0;
+                    each_arc(h[y], qv[y], [&](bool okp, int, int, int) { n += __popcll(__ballot(okp)); });
+                }
+                if (lane == 0) s.ncnt[i - b0] = n;
+            }
+            __syncthreads();
+            const int cl = b0 + lane < nm ? s.ncnt[lane] : 0;
+            const int inc = wave_sum(cl > 0 ? cl : 0);
+            const int tot = __builtin_amdgcn_readlane(inc, 63);
+            if (n_arcs + tot > kPArcs) {
+                full = true;
+                break;
+            }
+#pragma unroll
+            for (int y = 0; y < 4; ++y) {
+                const int i = b0 + wv + 16 * y;
+                if (i >= nm) continue;
+                const int c = __builtin_amdgcn_readlane(cl, i - b0);
+                if (c <= 0) continue;
+                const int u = s.mtok[i];
+                int pos0 = n_arcs + __builtin_amdgcn_readlane(inc, i - b0) - c;
+                each_arc(h[y], qv[y], [&](bool okp, int cost, int from, int to) {
+                    const unsigned long long bal = __ballot(okp);
+                    if (okp) {
+                        const int pos = pos0 + __popcll(bal & ((1ull << lane) - 1));
+                        const int wn = cost + s.pi[from] - s.pi[to];
+                        if (wn < 0) s.bad_move = 1;
+                        s.ft[pos] = (unsigned)((from << 16) | to);
+                        s.cost[pos] = wn;
+                        s.tok[pos] = u;
+                    }
+                    pos0 += __popcll(bal);
+                });
+            }
+            n_arcs += tot;
+            __syncthreads();
+        }
+        if (full || s.bad_move) break;
+#pragma unroll
+        for (int j = 0; j < kFRegs; ++j) {
+            const int i = tid + j * kFThreads;
+            if (i >= n_old && i < n_arcs) {
+                ft[j] = forward ? s.ft[i] : __builtin_amdgcn_alignbit(s.ft[i], s.ft[i], 16);
+                w[j] = (unsigned)s.cost[i];
+            } else if (w[j] != kWInf) {
+                const int u = s.tok[i];
+                if (u >= 0 && ((s.bloom[(u >> 5) & 127] >> (u & 31)) & 1u))
+                    for (int x = 0; x < nm; ++x)
+                        if (s.mtok[x] == u) w[j] = kWInf;                // its token has moved
+            }
+        }
+    }
+    __syncthreads();
+    // the arcs left out cost at least B: they stay non-negative if the potentials spread less than that
+    int lo = 0x7fffffff, hi = -0x7fffffff, pmin = 0x7fffffff;
+    for (int v = lane; v < (os ? N : E); v += 64) {
+        const int x = s.pi[v];
+        lo = x < lo ? x : lo;
+        hi = x > hi ? x : hi;
+        if (v < E) pmin = s.p[v] - x < pmin ? s.p[v] - x : pmin;
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        const int x = __shfl_xor(lo, off), y = __shfl_xor(hi, off), z = __shfl_xor(pmin, off);
+        lo = x < lo ? x : lo;
+        hi = y > hi ? y : hi;
+        pmin = z < pmin ? z : pmin;
+    }
+    const bool certified = solved && hi - lo < B;
+    int sb = 0;
+    while ((1 << sb) < E + 1) ++sb;
+    if (certified && prices) {
+        const int shift = slack ? -s.pi[E] : pmin;
+        for (int e = tid; e < E; e += kFThreads) prices[e] = (int64_t)(s.p[e] - s.pi[e] - shift) << sb;
+    }
+    if (solved && !certified) {
+        // exact for the arcs that were listed: a good start for another try with more of them
+        const int plim = (1 << (31 - a.ib)) - 1, shift = slack ? -s.pi[E] : os ? -s.pi[E] : pmin;
+        for (int e = tid; e < E; e += kFThreads) {
+            int p = s.p[e] - s.pi[e] - shift;
+            p = slack && p < 0 ? 0 : p;
+            ar->prices[e] = p > plim ? plim : (p < -plim ? -plim : p);
+        }
+    }
+    long long sum = 0;
+    for (int w2 = tid; w2 < a.n_wg; w2 += kFThreads) sum += a.wg_sum[w2];
+    if (sum) atomicAdd((unsigned long long *)&s.dsum, (unsigned long long)sum);
+    __syncthreads();
+    if (tid == 0) {
+        if (certified && price_scale) *price_scale = (int64_t)1 << sb;
+        host_state->total = s.dsum;
+        host_state->flow = os ? E * a.C : a.T * k;
+        host_state->round = mt.passes;
+        host_state->phases = 1;
+        host_state->status = MAXSCORE_OK;
+        host_state->fin = certified ? 2 : close ? 1 : 3;
+        host_state->fin_passes = 1;
+        host_state->fin_cycles = augs;
+        host_state->fin_dirty = rounds;
+        host_state->t_start = ar->t_start;
+        host_state->t_end = wall_clock64();
+    }
+}
+
+__global__ __launch_bounds__(kPThreads) void k_price_init(PriceArea *ar, int quads, int E, int plim,
+                                                          const int64_t *__restrict__ prices_in, int retry)
+{
+    const int i0 = blockIdx.x * kPThreads + threadIdx.x, n = gridDim.x * kPThreads;
+    for (int r = 0; r < kPCopies; ++r)
+        for (int i = i0; i < quads; i += n) ((int4 *)ar->hist[r])[i] = make_int4(0, 0, 0, 0);
+    for (int i = i0; i < 8 * kPStride; i += n) (&ar->loads[0][0])[i] = 0;
+    for (int i = i0; i < kPStride && !retry; i += n) ar->prices[i] = first_price(prices_in, i, E, plim);
+    if (i0 == 0) {
+        ar->n_arcs = 0;
+        ar->fail = 0;
+        ar->meta = first_meta(ar, prices_in, retry);
+        if (!retry) ar->t_start = wall_clock64();
+    }
+}
+
+}  // namespace
+
+static_assert((sizeof(PriceArea) + 15) / 16 * 16 <= 864 * 1024, "the workspace holds the tables");
+
+// Lanes per row (one per slot at least), columns per lane, rows per block of the final pass.
+static bool price_shape(int T, int E, int k, int &G, int &EPL, int &rows, int &n_wg)
+{
+    if (E < 2 || E > kPriceMaxE || k > E) return false;
+    G = 8;
+    EPL = 1;
+    while (G < k) G *= 2;
+    while (G * 16 < E) G *= 2;
+    while (G * EPL < E) EPL *= 2;
+    rows = kPThreads / G;
+    while (rows * 2 * k <= 1024 && rows * 2 <= kPRowsMax && (T + 2 * rows - 1) / (2 * rows) >= 512) rows *= 2;
+    n_wg = (T + rows - 1) / rows;
+    return rows * k <= 1024 && n_wg <= kPBlocks;
+}
+
+bool price_supported(int T, int E, int k)
+{
+    int G, EPL, rows, n_wg;
+    return price_shape(T, E, k, G, EPL, rows, n_wg);
+}
+
+int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_t *prices_in, bool retry, int32_t *assign, int64_t *prices,
+                      int64_t *price_scale, char *ws, SolverState *host_state_dev, PriceGeometry *geom, hipStream_t s)
+{
+    WorkspaceLayout L = workspace_layout(T, E, k);
+    PriceArgs a;
+    a.q = q;
+    a.assign = assign;
+    a.ar = (PriceArea *)(ws + L.price_off);
+    a.blkcnt = (int *)(ws + L.wcnt_off);
+    a.wg_arcs = (int2 *)(ws + L.price_off + (sizeof(PriceArea) + 15) / 16 * 16);
+    a.wg_sum = (long long *)(a.wg_arcs + L.max_wg);
+    a.T = T;
+    a.E = E;
+    a.k = k;
+    a.C = C;
+    const long long spare = (long long)E * C - (long long)T * k;
+    a.mode = spare == 0 ? kModeTight : spare > 0 ? kModeSlack : kModeOver;
+    // next to no spare capacity (as from rounding T*k/E up): nearly every expert ends full, and the first passes spread
+    // what is spare evenly
+    const int stride = T / kSampleRows;
+    const int n_sampled = stride >= 2 && !prices_in && !retry ? 2 : 0;
+    a.even = spare > 0 && spare * 64 <= (long long)E * C && !prices_in && !retry ? (n_sampled ? 4 : 3) : 0;
+    a.arcs_wanted = std::min(kArcsPerExpert * E, kArcsWanted);
+    a.retry = retry ? 1 : 0;
+    if (retry) a.arcs_wanted = std::min(2 * a.arcs_wanted, kArcsMost);
+    a.ib = 1;
+    while ((1 << a.ib) < E) ++a.ib;
+    a.nb = E <= 256 ? kPBins : kPBins / 2;
+    a.bshift = E <= 256 ? 22 : 23;
+    a.es = (E + (a.mode == kModeTight ? 0 : 1) + 3) & ~3;
+
+    int G, EPL, rows;
+    if (!price_shape(T, E, k, G, EPL, rows, a.n_wg) || a.n_wg > L.max_wg) return MAXSCORE_ERR_SHAPE;
+    const int ngrp = kPThreads / G;
+    a.rows = rows;
+    geom->rows = rows;
+    geom->n_wg = a.n_wg;
+
+    const bool os = a.mode == kModeOver;
+    const size_t shm = sizeof(int) * (size_t)(2 * a.nb + 1) * a.es;
+    const int n_pass = n_sampled + (retry ? 4 : a.mode == kModeSlack ? 9 : 6);
+    const bool small = (long long)T * G <= kSmallThreads && (long long)T * E <= kSmallEntries && shm + sizeof(StepLds) <= 64 * 1024;
+    const int plim = (1 << (31 - a.ib)) - 1;
+    if (!small)
+        hipLaunchKernelGGL(k_price_init, dim3(64), dim3(kPThreads), 0, s, a.ar, (2 * a.nb + 1) * a.es / 4, E, plim, prices_in, retry ? 1 : 0);
+    for (int t = small ? n_pass : 0; t <= n_pass; ++t) {
+        const bool fin = t == n_pass;
+        const int st = t < n_sampled ? stride : 1;
+        const int nrows = st > 1 ? kSampleRows : T;
+        const int shift = st > 1 ? t * (st / 2) : 0;
+        int rw = ngrp;
+        while (rw * 2 <= 128 && (nrows + 2 * rw - 1) / (2 * rw) >= 512) rw *= 2;
+        const int grid = fin ? a.n_wg : (nrows + rw - 1) / rw;
+#define MS_P(GG, PP)                                                                                                      \
+    do {                                                                                                                  \
+        if (fin) {                                                                                                        \
+            if (small) {                                                                                                  \
+                if (a.mode == kModeTight) hipLaunchKernelGGL((k_price_small<GG, PP, kModeTight>), dim3(1), dim3(kUThreads), shm, s, a, kSmallPasses, plim, prices_in); \
+                else if (os) hipLaunchKernelGGL((k_price_small<GG, PP, kModeOver>), dim3(1), dim3(kUThreads), shm, s, a, kSmallPasses, plim, prices_in); \
+                else hipLaunchKernelGGL((k_price_small<GG, PP, kModeSlack>), dim3(1), dim3(kUThreads), shm, s, a, kSmallPasses, plim, prices_in); \
+            }                                                                                                             \
+            if (os) hipLaunchKernelGGL((k_price_assign<GG, PP, true>), dim3(grid), dim3(kPThreads), 0, s, a);     \
+            else hipLaunchKernelGGL((k_price_assign<GG, PP, false>), dim3(grid), dim3(kPThreads), 0, s, a);       \
+        } else {                                                                                                          \
+            if (a.mode == kModeTight) hipLaunchKernelGGL((k_price<GG, PP, kModeTight>), dim3(grid), dim3(kPThreads), shm, s, a, t, nrows, st, shift, rw); \
+            else if (os) hipLaunchKernelGGL((k_price<GG, PP, kModeOver>), dim3(grid), dim3(kPThreads), shm, s, a, t, nrows, st, shift, rw); \
+            else hipLaunchKernelGGL((k_price<GG, PP, kModeSlack>), dim3(grid), dim3(kPThreads), shm, s, a, t, nrows, st, shift, rw); \
+        }                                                                                                                 \
+    } while (0)
+#define MS_PG(GG)                                                                                                         \
+    do {                                                                                                                  \
+        if (EPL == 1) MS_P(GG, 1);                                                                                        \
+        else if (EPL == 2) MS_P(GG, 2);                                                                                   \
+        else if (EPL == 4) MS_P(GG, 4);                                                                                   \
+        else if (EPL == 8) MS_P(GG, 8);                                                                                   \
+        else MS_P(GG, 16);                                                                                                \
+    } while (0)
+        if (G == 8) MS_PG(8);
+        else if (G == 16) MS_PG(16);
+        else if (G == 32) MS_PG(32);
+        else MS_PG(64);
+#undef MS_PG
+#undef MS_P
+        if (!fin) hipLaunchKernelGGL(k_price_update, dim3(1), dim3(kUThreads), shm, s, a, t, nrows);
+    }
+    if (E <= 64) hipLaunchKernelGGL(k_price_finish<1>, dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, host_state_dev);
+    else if (E <= 128) hipLaunchKernelGGL(k_price_finish<2>, dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, host_state_dev);
+    else if (E <= 256) hipLaunchKernelGGL(k_price_finish<4>, dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, host_state_dev);
+    else hipLaunchKernelGGL(k_price_finish<8>, dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, host_state_dev);
+    MS_HIP(hipGetLastError());
+    return MAXSCORE_OK;
+}
+
+}  // namespace maxscore

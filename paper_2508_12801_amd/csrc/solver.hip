@@ -1852,11 +1852,69 @@ static int32_t solver_host(SolverHost **out)
         }                                        \
     } while (0)
 
+// Calls with fewer rounds than this to spend go to the auction (a price solve has up to seven price passes).
+constexpr int kPriceMinRounds = 16;
+constexpr int kPriceTries = 3;
+constexpr long long kPriceMinPairs = 3;           // pairs per expert (with fewer the margins are too wide to step by)
+
+int32_t price_run(const int32_t *q, int T, int E, int k, int C, const maxscore_opts &o, int32_t *assign, int64_t *prices,
+                  int64_t *price_scale, maxscore_stats *stats, char *ws, hipStream_t s, SolverGeometry *geom,
+                  SolverAfter after, void *after_ctx, bool *solved)
+{
+    *solved = false;
+    if (!price_supported(T, E, k) || (k == E && T > C) || (E > 64 && (long long)T * k < kPriceMinPairs * E) ||
+        o.max_rounds < kPriceMinRounds ||
+        (o.flags & (MAXSCORE_FLAG_NO_TAIL_PASS | MAXSCORE_FLAG_NO_FINISHER)))
+        return MAXSCORE_OK;
+    SolverHost *hs = nullptr;
+    int32_t rc = solver_host(&hs);
+    if (rc) return rc;
+    PriceGeometry pg;
+    SolverState h;
+    for (int attempt = 0;; ++attempt) {
+        hs->state->fin = 0;
+        rc = price_enqueue(q, T, E, k, C, o.prices_in, attempt > 0, assign, prices, price_scale, ws, hs->state_dev, &pg, s);
+        if (rc == MAXSCORE_OK && after) {
+            const SolverGeometry g = {pg.rows, pg.n_wg, 0, 1, &hs->state_dev->t_after};
+            rc = after(after_ctx, g, s, nullptr);
+        }
+        if (rc != MAXSCORE_OK) {
+            (void)hipStreamSynchronize(s);
+            return rc;
+        }
+        MS_HIP(hipStreamSynchronize(s));
+        MS_HIP(hipGetLastError());
+        h = *hs->state;
+        if (h.fin == 2) break;
+        if (h.fin != 1 || attempt + 1 >= kPriceTries) return MAXSCORE_OK;
+    }
+    *solved = true;
+    if (geom) *geom = {pg.rows, pg.n_wg, 0, 1, nullptr};
+    if (stats) {
+        stats->total_score_q = h.total;
+        stats->flow_value = h.flow;
+        stats->rounds = h.round;
+        stats->phases = h.phases;
+        stats->status = h.status;
+        stats->solver_ms = (float)(h.t_end - h.t_start) * 1e-5f;          // ticks of 10 ns
+        stats->gates_dispatch_ms = after ? (float)(h.t_after - h.t_end) * 1e-5f : 0.f;
+        stats->finish_passes = h.fin_passes;
+        stats->finish_cycles = h.fin_cycles;
+    }
+    return MAXSCORE_OK;
+}
+
 int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore_opts &o, int32_t *assign,
                    int64_t *prices, int64_t *price_scale, maxscore_stats *stats, char *ws, hipStream_t s,
                    const int32_t *cap, long long room, const int32_t *kvec, long long demand, SolverGeometry *geom,
                    SolverAfter after, void *after_ctx)
 {
+    if (!cap && !kvec) {
+        bool solved = false;
+        const int32_t rc = price_run(q, T, E, k, Ce, o, assign, prices, price_scale, stats, ws, s, geom, after, after_ctx, &solved);
+        if (rc != MAXSCORE_OK || solved) return rc;
+        if ((long long)T * k > (long long)E * Ce) return kSolverPassedOn;
+    }
     WorkspaceLayout L = workspace_layout(T, E, k);
     SolverState *st = (SolverState *)(ws + L.state_off);
     long long *theta = (long long *)(ws + L.theta_off);
@@ -2054,7 +2112,7 @@ int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore
         if (after) {
             int tb = 1;                       // as k_setup computes it
             while ((1 << tb) < T) ++tb;
-            const SolverGeometry g = {rows, n_wg, tb};
+            const SolverGeometry g = {rows, n_wg, tb, 0, nullptr};
             const int32_t arc = after(after_ctx, g, s, hs->ev1);
             if (arc != MAXSCORE_OK) {
                 (void)hipStreamSynchronize(s);

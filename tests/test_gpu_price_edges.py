@@ -1,0 +1,55 @@
+"""GPU parity of the price solve at the edges of its launch shapes: lanes per row and columns per lane change at powers of
+two of E and k, small batches run in one workgroup, large ones start on a sample of their rows; capacity tight, nearly
+tight, spare and short, and as many slots as experts.  Optimality is the checker's certificate, or for a short capacity
+the checker's optimum (small sizes) or the padded auction's total; dispatch comes from the checker's lists."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+SHAPES = [  # T, E, k, C
+    (1, 2, 1, 1), (65, 2, 2, 65), (64, 8, 8, 64), (9, 17, 3, 2), (129, 63, 8, 17), (512, 64, 8, 64), (513, 65, 9, 72),
+    (300, 65, 1, 5), (257, 128, 33, 67), (31, 129, 2, 1), (255, 255, 4, 4), (256, 257, 16, 20), (2049, 512, 2, 9),
+    (100, 48, 1, 3), (600, 16, 4, 150), (600, 16, 4, 188), (600, 16, 4, 113), (40, 20, 4, 6), (2048, 96, 6, 96),
+    (16383, 32, 2, 1024), (16384, 32, 2, 1024), (16385, 33, 1, 500), (16390, 33, 1, 620), (16400, 31, 2, 800),
+]
+
+
+@pytest.fixture(scope="module")
+def ms():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2508_12801_amd as m
+    m.load_library()
+    return m
+
+
+@pytest.mark.parametrize("T,E,k,C", SHAPES)
+def test_edges(ms, T, E, k, C):
+    print(f"price edges T={T} E={E} k={k} C={C}", flush=True)
+    rng = np.random.default_rng(T + E)
+    L = (rng.standard_normal((T, E)) + 0.5 * rng.standard_normal(E)).astype(np.float32)
+    out = ms.route_logits(torch.from_numpy(L).cuda(), k, C)
+    q = out["q"].cpu().numpy().astype(np.int64)
+    a = out["assign"].cpu().numpy()
+    filled = a >= 0
+    total = int(np.take_along_axis(q, np.where(filled, a, 0).astype(np.int64), axis=1)[filled].sum())
+    assert total == out["stats"]["total_score_q"] and int(filled.sum()) == out["stats"]["flow_value"]
+    assert np.bincount(a[filled], minlength=E).max() <= min(C, T)
+    if T * k <= E * C:
+        P = oracle.assignment_matrix(a, E)
+        assert (P.sum(axis=1) == k).all() and oracle.verify_optimal(q, P, k, C)["optimal"]
+    elif T <= 100:
+        assert total == oracle.assign_literal_graph(q, k, C)["total"]
+    else:
+        plain = ms.assign_i32(out["q"], k, C, finisher=False)["stats"]
+        assert (total, int(filled.sum())) == (plain["total_score_q"], plain["flow_value"])
+    want = oracle.dispatch(a, out["gates"].cpu().numpy(), E)
+    n = int(filled.sum())
+    assert np.array_equal(out["expert_offsets"].cpu().numpy(), want["expert_offsets"])
+    assert np.array_equal(out["disp_token"].cpu().numpy()[:n], want["disp_token"][:n])
+    assert np.array_equal(out["token_pos"].cpu().numpy(), want["token_pos"])
