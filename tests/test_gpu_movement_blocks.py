@@ -1,0 +1,68 @@
+"""GPU parity of the token-block dispatch and of the chunked combine where they can go wrong: token counts around the block
+sizes, row lengths around the chunks of a wavefront, lists that are not in token order, tokens in more lists than a block
+keeps, entries outside the batch, slots that are empty or outside the buffers."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def ms():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2508_12801_amd as m
+    m.load_library()
+    return m
+
+
+@pytest.mark.parametrize("T,E,C,lists", [
+    (4095, 5, 900, "sorted"), (4096, 5, 900, "sorted"), (4099, 300, 20, "sorted"), (8193, 17, 800, "shuffled"),
+    (16385, 40, 900, "sorted"), (16384, 24, 700, "crowded"), (32771, 3, 9000, "outside"), (32768, 600, 70, "sorted"),
+])
+def test_dispatch_blocks(ms, T, E, C, lists):
+    print(f"dispatch blocks T={T} E={E} C={C} {lists}", flush=True)
+    rng = np.random.default_rng(T + E)
+    d = 8 if E > 100 else 24
+    x = torch.from_numpy(rng.integers(1, 1 << 30, (T, d)).astype(np.int32)).cuda().view(torch.float32)
+    segs = []
+    for e in range(E):
+        n = int(rng.integers(0, C + 1)) if e % 3 else (0 if e % 2 else C)
+        t = np.sort(rng.choice(T, n, replace=False))
+        if lists == "shuffled" and e % 4 == 1:
+            rng.shuffle(t)
+        if lists == "crowded" and n:
+            t[:min(n, 40)] = np.sort(rng.integers(100, 103, min(n, 40)))
+            t = np.sort(t)
+        if lists == "outside" and n:
+            t[-1], t[0] = T + 1, -3
+        segs.append(t)
+    off = np.concatenate([[0], np.cumsum([len(s) for s in segs])]).astype(np.int32)
+    tok = np.concatenate(segs).astype(np.int32)
+    buf = ms.dispatch_tokens(x, torch.from_numpy(off).cuda(), torch.from_numpy(tok).cuda(), E, C).view(torch.int32)
+    rows = torch.from_numpy(np.where((tok >= 0) & (tok < T), tok, 0).astype(np.int64)).cuda()
+    for e in range(E):
+        n = int(off[e + 1] - off[e])
+        assert torch.equal(buf[e, :n], x.view(torch.int32)[rows[off[e]:off[e + 1]]]), e
+        assert not buf[e, n:].any(), e
+
+
+@pytest.mark.parametrize("d,k,dtype", [(8, 1, "bf16"), (512, 2, "bf16"), (520, 9, "bf16"), (1032, 8, "bf16"), (2048, 3, "bf16"),
+                                       (2056, 5, "bf16"), (4104, 2, "bf16"), (4, 64, "fp32"), (256, 7, "fp32"), (2052, 3, "fp32")])
+def test_combine_chunks(ms, d, k, dtype):
+    print(f"combine chunks d={d} k={k} {dtype}", flush=True)
+    rng = np.random.default_rng(d + k)
+    T, E, C = 37, k + 3, 11
+    buf = torch.from_numpy(rng.standard_normal((E, C, d), dtype=np.float32)).cuda()
+    buf = buf.to(torch.bfloat16) if dtype == "bf16" else buf
+    a = np.argsort(rng.random((T, E)), axis=1)[:, :k].astype(np.int32)
+    pos = rng.integers(0, C, (T, k)).astype(np.int32)
+    g = rng.random((T, k), dtype=np.float32)
+    a[3], a[5, -1], pos[7, 0] = -1, E, C                      # an empty row, an expert and a place that do not exist
+    y = ms.combine(buf, torch.from_numpy(a).cuda(), torch.from_numpy(pos).cuda(), torch.from_numpy(g).cuda()).cpu().numpy()
+    ok = (a >= 0) & (a < E) & (pos < C)
+    rows = buf.float().cpu().numpy().astype(np.float64)[np.where(ok, a, 0), np.where(ok, pos, 0)]
+    terms = rows * (g.astype(np.float64) * ok)[:, :, None]
+    assert (np.abs(y - terms.sum(axis=1)) <= 1e-6 * np.abs(terms).sum(axis=1) + 1e-30).all()
