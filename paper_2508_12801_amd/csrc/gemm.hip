@@ -5,7 +5,7 @@
 // each workgroup owns 128 token rows, walks d in steps of 64, stages the x tile and the transposed
 // W tile in LDS and prefetches the next tiles into registers while the matrix cores work.  The fast
 // kernel (k_gemm_bf16_wtc) reads x with whole-line loads and restores the operand layout through LDS.
-// fp32 inputs (the tiny configuration) use a plain FMA kernel.
+// Small batches, and fp32 throughout, run a kernel that splits d over the wavefronts of a workgroup (k_gemm_split).
 #include "common.h"
 #include "softtopk_row.h"
 
@@ -424,16 +424,150 @@ __global__ __launch_bounds__(256) void k_gemm_bf16_wtc(const unsigned short *__r
     }
 }
 
-__global__ __launch_bounds__(256) void k_gemm_f32(const float *__restrict__ x, const float *__restrict__ W,
-                                                  const float *__restrict__ bias, int T, int d, int E,
-                                                  float *__restrict__ out)
+// Split kernel: 32 token rows per workgroup, one 32 x 32 tile of the output and one part of d per wavefront (ct column
+// tiles times ks parts, 16 wavefronts at most); the parts are added up through LDS in a fixed order.  Operands come
+// straight from global memory: within a step the matrix instruction may take its reduction indices in any order, so a lane
+// reads 16 consecutive bytes of its row of x and the matching elements of W, 32 columns side by side.
+// fp32 runs on v_mfma_f32_32x32x2_f32, four per step of 8 indices; bf16 on v_mfma_f32_32x32x16_bf16, one per step of 16.
+// fp32 is bound by the matrix cores' fp32 rate: 65536 x 1024 to 128 experts 0.25 ms (68 TFLOP/s), with one fused
+// multiply-add per element and thread as before 3.8 ms; 10007 x 1000 to 96: 60 and 416 us.  Small bf16 batches are bound by
+// the latency of their loads, here in flight from 16 wavefronts at once instead of 4: 256 x 2048 to 64 experts 27 us, with
+// 128 rows and all of d per workgroup 45.
+// FE > 0: the tile holds whole rows of FE experts, and the scores and rewards are computed from it (as in k_gemm_bf16_wtc).
+constexpr int kSplitDepth = 4;          // steps on their way per wavefront
+constexpr int kSplitPitch = 33;
+
+template <bool BF16, bool ALIGNED, int FE>
+__global__ __launch_bounds__(1024) void k_gemm_split(const void *__restrict__ x_, const void *__restrict__ W_,
+                                                     const float *__restrict__ bias, int T, int d, int E, int ct, int ks,
+                                                     float *__restrict__ out, float *__restrict__ scores,
+                                                     int32_t *__restrict__ q, int k, float t, float qscale)
 {
-    size_t n = (size_t)T * E;
-    for (size_t o = (size_t)blockIdx.x * blockDim.x + threadIdx.x; o < n; o += (size_t)gridDim.x * blockDim.x) {
-        int row = (int)(o / E), col = (int)(o % E);
-        float acc = 0.f;
-        for (int m = 0; m < d; ++m) acc = fmaf(x[(size_t)row * d + m], W[(size_t)m * E + col], acc);
-        out[o] = acc + (bias ? bias[col] : 0.f);
+    constexpr int STEP = BF16 ? 16 : 8, LK = STEP / 2;       // reduction indices per step, per lane and step
+    __shared__ __attribute__((aligned(16))) float s_part[16 * 32 * kSplitPitch];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = wave % ct, part = wave / ct;
+    const int row0 = blockIdx.x * 32, col0 = blockIdx.y * 128;
+    const int row = row0 + (lane & 31), kl = LK * (lane >> 5);
+    const int col = col0 + 32 * c + (lane & 31);
+    const size_t xr = (size_t)(row < T ? row : T - 1) * d;
+    const int wc = col < E ? col : E - 1;
+    struct Frag {
+        u32x4 a;
+        unsigned b[LK];
+    };
+    auto load = [&](int k0, Frag &f, bool whole) {
+        const int kk = k0 + kl;
+        if (BF16) {
+            const unsigned short *xp = (const unsigned short *)x_ + xr + kk, *wp = (const unsigned short *)W_ + (size_t)kk * E + wc;
+            if (ALIGNED && whole) {
+                f.a = *(const u32x4 *)xp;
+            } else {
+                unsigned v[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = whole || kk + i < d ? xp[i] : 0u;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) f.a[i] = v[2 * i] | (v[2 * i + 1] << 16);
+            }
+#pragma unroll
+            for (int i = 0; i < LK; ++i) f.b[i] = whole || kk + i < d ? wp[(size_t)i * E] : 0u;
+        } else {
+            const float *xp = (const float *)x_ + xr + kk, *wp = (const float *)W_ + (size_t)kk * E + wc;
+            if (ALIGNED && whole) {
+                f.a = *(const u32x4 *)xp;
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) f.a[i] = whole || kk + i < d ? __float_as_uint(xp[i]) : 0u;
+            }
+#pragma unroll
+            for (int i = 0; i < LK; ++i) f.b[i] = whole || kk + i < d ? __float_as_uint(wp[(size_t)i * E]) : 0u;
+        }
+    };
+    f32x16 acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+    auto use = [&](const Frag &f) {
+        if (BF16) {
+            u32x4 b;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) b[i] = f.b[2 * i] | (f.b[2 * i + 1] << 16);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(f.a[i]), __uint_as_float(f.b[i]), acc, 0, 0, 0);
+        }
+    };
+    // whole steps of this part, then (in the last part) what d leaves over
+    const int steps = d / STEP, s0 = (int)((long long)steps * part / ks), s1 = (int)((long long)steps * (part + 1) / ks);
+    Frag f[kSplitDepth];
+#pragma unroll
+    for (int i = 0; i < kSplitDepth; ++i)
+        if (s0 + i < s1) load((s0 + i) * STEP, f[i], true);
+    int s = s0;
+    for (; s + 2 * kSplitDepth <= s1; s += kSplitDepth) {
+#pragma unroll
+        for (int i = 0; i < kSplitDepth; ++i) {
+            const Frag cur = f[i];
+            load((s + kSplitDepth + i) * STEP, f[i], true);
+            use(cur);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kSplitDepth; ++i)
+        if (s + i < s1) {
+            const Frag cur = f[i];
+            if (s + kSplitDepth + i < s1) load((s + kSplitDepth + i) * STEP, f[i], true);
+            use(cur);
+        }
+    s += kSplitDepth;
+#pragma unroll
+    for (int i = 0; i < kSplitDepth; ++i)
+        if (s + i < s1) use(f[i]);
+    if (part == ks - 1 && steps * STEP < d) {
+        Frag g;
+        load(steps * STEP, g, false);
+        use(g);
+    }
+    // acc[4 * j + i] is row 8 * j + 4 * (lane / 32) + i, column lane % 32 of the tile
+    float *mine = s_part + wave * (32 * kSplitPitch);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) mine[(8 * j + 4 * (lane >> 5) + i) * kSplitPitch + (lane & 31)] = acc[4 * j + i];
+    __syncthreads();
+    const int width = 32 * ct;
+    if constexpr (FE == 0) {
+        for (int o = tid; o < 32 * width; o += blockDim.x) {
+            const int r = o / width, n = o - r * width;
+            float v = 0.f;
+            for (int p = 0; p < ks; ++p) v += s_part[((p * ct + (n >> 5)) * 32 + r) * kSplitPitch + (n & 31)];
+            if (row0 + r < T && col0 + n < E) out[(size_t)(row0 + r) * E + col0 + n] = v + (bias ? bias[col0 + n] : 0.f);
+        }
+    } else {
+        constexpr int EPLS = FE / 8;                // values per lane with 8 lanes per row
+        const int r = tid >> 3, lg = tid & 7;
+        if (r >= 32) return;
+        float xv[EPLS];
+#pragma unroll
+        for (int m = 0; m < EPLS; ++m) {
+            const int n = (m >> 2) * 32 + lg * 4 + (m & 3);
+            float v = 0.f;
+            for (int p = 0; p < ks; ++p) v += s_part[((p * ct + (n >> 5)) * 32 + r) * kSplitPitch + (n & 31)];
+            xv[m] = v + (bias ? bias[n] : 0.f);
+        }
+        float sc[EPLS];
+        int qq[EPLS];
+        softtopk_row<8, EPLS, true>(xv, lg, E, k, t, qscale, MAXSCORE_SOFTTOPK_A, sc, qq);
+        if (row0 + r < T) {
+#pragma unroll
+            for (int m = 0; m < EPLS; m += 4) {
+                const size_t o = (size_t)(row0 + r) * E + (m >> 2) * 32 + lg * 4;
+                if (out) *(float4 *)(out + o) = make_float4(xv[m], xv[m + 1], xv[m + 2], xv[m + 3]);
+                if (scores) *(float4 *)(scores + o) = make_float4(sc[m], sc[m + 1], sc[m + 2], sc[m + 3]);
+                if (q) *(int4 *)(q + o) = make_int4(qq[m], qq[m + 1], qq[m + 2], qq[m + 3]);
+            }
+        }
     }
 }
 
@@ -445,15 +579,28 @@ __global__ __launch_bounds__(256) void k_copy16(const u32x4 *__restrict__ src, u
 
 }  // namespace
 
+// bf16: the split kernel as long as its workgroups fill the chip once, or twice with at most three column tiles each
+// (16384 tokens of 2048: 64 experts 44 us against 48, 128 experts 66 against 60; 8192: 29 against 48, 41 against 58).
+static bool split_is_better(int T, int E)
+{
+    return (long long)((T + 31) / 32) * ((E + 127) / 128) <= (E <= 96 ? 512 : 256);
+}
+
 int32_t gemm_run(const void *x, const void *W, const float *bias, int dtype, int T, int d, int E, float *logits,
                  void *wt_scratch, hipStream_t s)
 {
-    if (dtype == MAXSCORE_DTYPE_FP32) {
-        size_t n = (size_t)T * E;
-        int grid = (int)((n + 255) / 256);
-        if (grid > 8192) grid = 8192;
-        hipLaunchKernelGGL(k_gemm_f32, dim3(grid), dim3(256), 0, s, (const float *)x, (const float *)W, bias, T, d,
-                           E, logits);
+    const bool f32 = dtype == MAXSCORE_DTYPE_FP32;
+    if (f32 || split_is_better(T, E)) {
+        const int ct = E >= 128 ? 4 : (E + 31) / 32, ks = 16 / ct;
+        const bool al = d % (f32 ? 4 : 8) == 0 && ((uintptr_t)x % 16) == 0;
+        const dim3 g((T + 31) / 32, (E + 127) / 128), blk(64 * ct * ks);
+#define MS_SPLIT(BB, AA)                                                                                            \
+    hipLaunchKernelGGL((k_gemm_split<BB, AA, 0>), g, blk, 0, s, x, W, bias, T, d, E, ct, ks, logits, (float *)nullptr, \
+                       (int32_t *)nullptr, 0, 0.f, 0.f)
+        if (f32) { if (al) MS_SPLIT(false, true); else MS_SPLIT(false, false); }
+        else if (al) MS_SPLIT(true, true);
+        else MS_SPLIT(true, false);
+#undef MS_SPLIT
         MS_HIP(hipGetLastError());
         return MAXSCORE_OK;
     }
@@ -518,9 +665,21 @@ int32_t gemm_softtopk_run(const void *x, const void *W, const float *bias, int d
     if (((((uintptr_t)logits) | ((uintptr_t)scores) | ((uintptr_t)q)) % 16) != 0) return MAXSCORE_ERR_SHAPE;
     const unsigned short *xb = (const unsigned short *)x, *wb = (const unsigned short *)W;
     unsigned short *wt = (unsigned short *)wt_scratch;
+    const float qscale = (float)(1 << shift);
+    if (split_is_better(T, E)) {
+        const int ct = E / 32, ks = 16 / ct;
+#define MS_SPLITF(FF)                                                                                                   \
+    hipLaunchKernelGGL((k_gemm_split<true, true, FF>), dim3((T + 31) / 32), dim3(1024), 0, s, x, W, bias, T, d, E, ct, ks, \
+                       logits, scores, q, k, t, qscale)
+        if (E == 32) MS_SPLITF(32);
+        else if (E == 64) MS_SPLITF(64);
+        else MS_SPLITF(128);
+#undef MS_SPLITF
+        MS_HIP(hipGetLastError());
+        return MAXSCORE_OK;
+    }
     hipLaunchKernelGGL(k_transpose_w, dim3((d + 31) / 32, (E + 31) / 32), dim3(256), 0, s, wb, wt, d, E);
     dim3 grid((T + BM - 1) / BM, 1);
-    const float qscale = (float)(1 << shift);
 #define MS_GEMMF(NT_)                                                                                         \
     hipLaunchKernelGGL((k_gemm_bf16_wtc<NT_, 1, 2, true>), grid, dim3(256), 0, s, xb, wt, bias, T, d, E, logits, \
                        scores, q, k, t, qscale)

@@ -1,0 +1,39 @@
+"""GPU parity of the router projection (and of the scores fused behind it) where its kernels change hands or have remainders:
+rows and columns around the 32 x 32 tiles, reduction lengths around a matrix instruction, misaligned rows, and the token
+counts at which bf16 leaves the split kernel."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def ms():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2508_12801_amd as m
+    m.load_library()
+    return m
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("T,d,E", [
+    (1, 1, 1), (31, 7, 33), (32, 8, 32), (33, 15, 31), (64, 16, 64), (65, 17, 65), (40, 64, 96), (95, 40, 97), (70, 1000, 127),
+    (129, 136, 128), (33, 2056, 129), (50, 72, 300), (8192, 64, 128), (8193, 64, 128), (16384, 64, 64), (16385, 64, 32), (16385, 40, 96),
+])
+def test_projection_edges(ms, T, d, E, dtype):
+    print(f"projection edges T={T} d={d} E={E} {dtype}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(T + d + E)
+    x = torch.randn(T, d, generator=gen, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    W = torch.randn(d, E, generator=gen, device="cuda").to(x.dtype)
+    b = torch.randn(E, generator=gen, device="cuda")
+    L = ms.router_logits(x, W, b)
+    xs, Ws, bs = x.double().cpu(), W.double().cpu(), b.double().cpu()
+    ref, mag = xs @ Ws + bs, xs.abs() @ Ws.abs() + bs.abs()
+    assert ((L.double().cpu() - ref).abs() <= 1e-6 * mag).all()
+    k = min(3, E)
+    both = ms.router_softtopk(x, W, b, k, t=1.0)
+    scores, q = ms.softtopk(L, k, 1.0)
+    assert torch.equal(both["logits"], L) and torch.equal(both["scores"], scores) and torch.equal(both["q"], q)
