@@ -31,7 +31,7 @@ WorkspaceLayout workspace_layout(int T, int E, int k, int d)
     L.finm_off = off; off = align_up(off + sizeof(unsigned long long) * (size_t)kFinMatrixMaxE * kFinMatrixMaxE, 256);
     // finisher arc lists: one segment per key block (fin_seg_cap(rows, k) arcs of 12 bytes each) and a count per block
     L.tri_off = off; off = align_up(off + 12 * fin_tri_entries(T, k, L.max_wg) + sizeof(int) * ((size_t)L.max_wg + 1), 256);
-    L.price_off = off; off = align_up(off + price_area_bytes(L.max_wg), 256);    // tables of the price solve
+    L.price_off = off; off = align_up(off + price_area_bytes(T, E, k, L.max_wg), 256);    // tables of the price solve
     L.wt_off = off; off = align_up(off + sizeof(unsigned short) * (size_t)E * (d > 0 ? d : 0), 256);
     L.total = off;
     return L;
@@ -190,7 +190,9 @@ int32_t maxscore_assign_iter_i32(const int32_t *q, int32_t T, int32_t E, int32_t
     int32_t rc = check_ws(workspace, workspace_bytes, T, E, k);
     if (rc) return rc;
     if (max_rounds < 0) max_rounds = 1000;
-    return iter_run(q, T, E, k, C, max_rounds, assign, total, flow, rounds, (char *)workspace, (hipStream_t)stream);
+    rc = iter_run(q, T, E, k, C, max_rounds, assign, total, flow, rounds, (char *)workspace, (hipStream_t)stream);
+    MS_HIP(hipStreamSynchronize((hipStream_t)stream));
+    return rc;
 }
 
 int32_t maxscore_assign_caps_i32(const int32_t *q, int32_t T, int32_t E, int32_t k, const int32_t *capacity,
@@ -390,6 +392,13 @@ static int32_t route_from_rewards(const float *scores, const int32_t *q, int T, 
     }
     if (src != MAXSCORE_OK && src != MAXSCORE_ERR_NOT_CONVERGED) return src;
     MS_HIP(hipEventRecord(ev_a, s));
+    if (o.assignment == MAXSCORE_ASSIGN_ITER && k <= 16 && E <= kPriceMaxE) {
+        // the rounds leave the number of pairs per 64 tokens and expert
+        const SolverGeometry g = {64, (T + 63) / 64, 0, 1, nullptr};
+        const int32_t rc = dispatch_from_keys(g, scores, assign, T, E, k, gates, expert_offsets, disp_token, disp_gate,
+                                              token_pos, ws, s);
+        return rc ? rc : finish(src);
+    }
     int32_t rc = gates_run(scores, assign, T, E, k, gates, s);
     if (rc) return rc;
     rc = dispatch_run(assign, gates, T, E, k, expert_offsets, disp_token, disp_gate, token_pos, ws, s);

@@ -116,7 +116,15 @@ struct PriceGeometry {
     int rows, n_wg;          // blocks of rows over which the pairs are counted (WorkspaceLayout::wcnt_off)
 };
 bool price_supported(int T, int E, int k);
-inline size_t price_area_bytes(int max_wg) { return 864 * 1024 + 16 * (size_t)max_wg; }     // tables, and two words per block
+// tables, and two words per block; the iterative assignment keeps its own there, with counts per (slot, 64 tokens, expert)
+inline size_t price_area_bytes(int T, int E, int k, int max_wg)
+{
+    const size_t price = 864 * 1024 + 16 * (size_t)max_wg, blocks = ((size_t)T + 63) / 64;
+    const size_t iter = 4 * (size_t)kMaxE * 16 + 16 * blocks + 4 * blocks * k * ((size_t)E + 1);
+    return price > iter ? price : iter;
+}
+// Pinned words of the calling thread (16 of them, cleared by whoever uses them), and the same as the device sees them.
+int32_t solver_words(int **host, int **dev);
 int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_t *prices_in, bool retry,
                       int32_t *assign, int64_t *prices, int64_t *price_scale, char *ws, SolverState *host_state_dev, PriceGeometry *geom, hipStream_t s);
 // Runs price_enqueue and the caller's work behind it and waits.  *solved: whether the result stands.

@@ -8,8 +8,14 @@
 //   stage 2  at the start of a round the experts with room are fixed; a token fills its holes in slot order with
 //            its best experts among those (not held, not yet proposed this round); proposals are taken by
 //            (slot, token id) and an expert accepts while it has room; rounds repeat until nobody proposes.
-// Both orders are "stable position inside the expert" of a slot-major pair list, which the dispatch kernels
-// already compute; every round is propose -> positions -> accept.
+// Stage 1 is a round of stage 2 in which everybody has room, so both run through the same two kernels:
+//   k_iter_step   a block of 64 tokens takes the outcome of the round before and proposes for the holes that are left; a
+//                 wavefront is 64 tokens of one slot, whose proposals per expert it counts
+//   k_iter_scan   per expert: an expert with room for all its proposals needs no order; for the others the counts of
+//                 the blocks before, slot by slot, become the positions that the next step compares with the room
+// Rounds are enqueued two ahead of the one that runs; the first round without proposals ends them, and what is still
+// queued leaves at once.  Both kernels are bound by latency (some 5 us each; 44032 tokens, 64 experts, top-2: nine rounds in
+// 0.12 ms, with six launches and a wait for the host every other round 0.5 ms).
 #include <climits>
 
 #include "common.h"
@@ -20,9 +26,31 @@ namespace {
 struct IterState {
     unsigned long long total;
     int flow;
-    int nprop;     // proposals of the last round
-    int rounds;    // rounds that had proposals
     int pad;
+};
+
+constexpr int kIterRows = 64;
+constexpr int kIterWordProgress = 1, kIterWordFlow = 2, kIterWordRounds = 3, kIterWordOpen = 10, kIterWordTotal = 8;
+
+// Tables of the rounds, in the workspace (WorkspaceLayout::price_off).
+struct IterArea {
+    int load[2][kMaxE];        // tokens per expert before round r, in half r & 1
+    int cnt[kMaxE];            // proposals of the last round
+    int tot[8][kMaxE];         // ... of the round in progress, in eight partial counts
+    int np[4];                 // proposals of round r in all, in word r & 3
+};
+
+struct IterArgs {
+    const int32_t *q;
+    int32_t *assign, *list;    // list: proposals, slot-major
+    IterArea *ar;
+    int *any;                  // per (slot, block): whether there are proposals
+    int *tiles;                // per (slot, block): proposals per expert, then those of the tiles before
+    int *wcnt;                 // result: pairs per (block, expert)
+    long long *bsum;           // ... reward per block
+    int *bflow;                // ... pairs per block
+    int T, E, k, C, n_wg;
+    int ebits;
 };
 
 // Best live expert of a row spread over a wavefront (lane l holds experts l, l+64, ...; bit c of `live` says
@@ -81,98 +109,280 @@ __global__ __launch_bounds__(256) void k_iter_topk(const int32_t *__restrict__ q
     }
 }
 
-// assign[i, s] <- choice if the pair is among the first C of its expert, else -1; load <- min(C, count).
-__global__ __launch_bounds__(256) void k_iter_keep(const int32_t *__restrict__ choice, const int32_t *__restrict__ pos,
-                                                   const int32_t *__restrict__ offsets, int T, int E, int k, int C,
-                                                   int32_t *__restrict__ assign, int *__restrict__ load,
-                                                   IterState *__restrict__ st)
+__device__ __forceinline__ void wave_lds_sync()
 {
-    const size_t n = (size_t)T * k;
-    const size_t a = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (a < n) {
-        const size_t i = a / k, s = a % k, idx = s * T + i;
-        assign[a] = pos[idx] < C ? choice[idx] : -1;
-    }
-    if (blockIdx.x == 0) {
-        for (int j = threadIdx.x; j < E; j += blockDim.x) {
-            const int cnt = offsets[j + 1] - offsets[j];
-            load[j] = cnt < C ? cnt : C;
-        }
-        if (threadIdx.x == 0) {
-            st->total = 0;
-            st->flow = 0;
-            st->nprop = 0;
-            st->rounds = 0;
-        }
-    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// prop[s*T + i] <- expert proposed for hole s of token i, or -1.
-template <int EPL>
-__global__ __launch_bounds__(256) void k_iter_propose(const int32_t *__restrict__ q,
-                                                      const int32_t *__restrict__ assign,
-                                                      const int *__restrict__ load, int T, int E, int k, int C,
-                                                      int32_t *__restrict__ prop)
+// lanes that hold the same expert as this one (0 for a lane without one)
+__device__ __forceinline__ unsigned long long same_expert(int e, int ebits)
 {
-    __shared__ unsigned char s_room[kMaxE];
-    for (int j = threadIdx.x; j < E; j += blockDim.x) s_room[j] = load[j] < C;
+    unsigned long long same = __ballot(e >= 0);
+    for (int b = 0; b < ebits; ++b) {
+        const unsigned long long bal = __ballot((e >> b) & 1);
+        same &= ((e >> b) & 1) ? bal : ~bal;
+    }
+    return e >= 0 ? same : 0ull;
+}
+
+template <int G>
+__device__ __forceinline__ int group_max(int v)
+{
+    for (int off = 1; off < G; off <<= 1) {
+        const int o = __shfl_xor(v, off);
+        v = o > v ? o : v;
+    }
+    return v;
+}
+
+__global__ __launch_bounds__(1024) void k_iter_init(IterArea *ar)
+{
+    int *p = (int *)ar;
+    for (int i = threadIdx.x; i < (int)(sizeof(IterArea) / 4); i += 1024) p[i] = 0;
+}
+
+// Which step of the rounds this is: 0 they have ended before, 1 the first round without proposals lies behind, 2 go on.
+__device__ __forceinline__ int iter_phase(const IterArea *ar, int r)
+{
+    if (r == 0 || ar->np[(r - 1) & 3] != 0) return 2;
+    return r == 1 || ar->np[(r - 2) & 3] != 0 ? 1 : 0;
+}
+
+// G lanes own a token row, lane l columns (m >> 2) * 4G + 4l + (m & 3) for m < EPL (EPL >= 4), else l * EPL + m.
+template <int G, int EPL>
+__global__ __launch_bounds__(256) void k_iter_step(IterArgs a, int r, int last)
+{
+    extern __shared__ int s_mem[];
+    const int E = a.E, k = a.k, T = a.T;
+    int *s_slot = s_mem;                          // [64][k]
+    int *s_prop = s_slot + kIterRows * k;         // [k][64]
+    int *s_room = s_prop + kIterRows * k;         // [E] room for the round before, then for this one
+    int *s_num = s_room + E;                      // [E] proposals of the round before
+    int *s_cnt = s_num + E;                       // [4][E]
+    __shared__ int s_queue[kIterRows];
+    __shared__ int s_nq;
+    __shared__ long long s_sum[4];
+    __shared__ int s_flow[4];
+    IterArea *ar = a.ar;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int w = blockIdx.x, row0 = w * kIterRows;
+    const int nr = T - row0 < kIterRows ? T - row0 : kIterRows;
+    const int phase = iter_phase(ar, r);
+    if (w == 0 && tid == 0) ar->np[r & 3] = 0;
+    if (phase == 0) return;
+    const bool final = phase == 1 || last;
+    for (int i = tid; i < nr * k; i += 256) s_slot[i] = r < 2 ? -1 : a.assign[(size_t)row0 * k + i];
+    if (r > 0)
+        for (int e = tid; e < E; e += 256) {
+            s_room[e] = a.C - ar->load[(r - 1) & 1][e];
+            s_num[e] = ar->cnt[e];
+        }
     __syncthreads();
-    const int lane = threadIdx.x & 63;
-    const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int n_waves = (gridDim.x * blockDim.x) >> 6;
-    for (int row = wave; row < T; row += n_waves) {
-        const int slot = lane < k ? assign[(size_t)row * k + lane] : 0;
-        unsigned long long holes = __ballot(slot < 0);
-        int mine = -1;
-        if (holes) {
-            int val[EPL];
-            unsigned live = 0;
-#pragma unroll
-            for (int c = 0; c < EPL; ++c) {
-                const int e = lane + 64 * c;
-                const bool ok = e < E && s_room[e];
-                val[c] = ok ? q[(size_t)row * E + e] : 0;
-                live |= (ok ? 1u : 0u) << c;
+    if (phase == 2 && r > 0) {
+        for (int s = wv; s < k; s += 4) {
+            const int e = lane < nr ? a.list[(size_t)s * T + row0 + lane] : -1;
+            if (!__any(e >= 0)) continue;
+            const int room = e >= 0 ? s_room[e] : 0;
+            bool take = e >= 0 && s_num[e] <= room;
+            const bool asks = e >= 0 && !take && room > 0;
+            if (__any(asks)) {
+                const unsigned long long same = same_expert(e, a.ebits);
+                if (asks) {
+                    const int pos = a.tiles[((size_t)s * a.n_wg + w) * E + e] + __popcll(same & ((1ull << lane) - 1));
+                    take = pos < room;
+                }
             }
-            for (int s = 0; s < k; ++s) live = drop_expert(live, __shfl(slot, s), lane);
-            while (holes) {
-                const int s = __ffsll((long long)holes) - 1;
-                holes &= holes - 1;
-                const int e = wave_best<EPL>(val, live);
-                if (e < 0) break;
-                live = drop_expert(live, e, lane);
-                if (lane == s) mine = e;
+            if (take) {
+                s_slot[lane * k + s] = e;
+                if (r > 1) a.assign[(size_t)(row0 + lane) * k + s] = e;
             }
         }
-        if (lane < k) prop[(size_t)lane * T + row] = mine;
+        __syncthreads();
+        if (r == 1)
+            for (int i = tid; i < nr * k; i += 256) a.assign[(size_t)row0 * k + i] = s_slot[i];
+    }
+    if (final) {
+        for (int e = tid; e < E; e += 256) s_cnt[e] = 0;
+        __syncthreads();
+        long long sum = 0;
+        int flow = 0;
+        for (int i = tid; i < nr * k; i += 256) {
+            const int e = s_slot[i];
+            if (e >= 0) {
+                atomicAdd(&s_cnt[e], 1);
+                sum += a.q[(size_t)(row0 + i / k) * E + e];
+                ++flow;
+            }
+        }
+        for (int off = 32; off >= 1; off >>= 1) {
+            sum += __shfl_xor(sum, off);
+            flow += __shfl_xor(flow, off);
+        }
+        if (lane == 0) {
+            s_sum[wv] = sum;
+            s_flow[wv] = flow;
+        }
+        __syncthreads();
+        for (int e = tid; e < E; e += 256) a.wcnt[(size_t)w * E + e] = s_cnt[e];
+        if (tid == 0) {
+            a.bsum[w] = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
+            a.bflow[w] = s_flow[0] + s_flow[1] + s_flow[2] + s_flow[3];
+        }
+        return;
+    }
+    for (int e = tid; e < E; e += 256) s_room[e] = a.C - ar->load[r & 1][e];
+    for (int i = tid; i < kIterRows * k; i += 256) s_prop[i] = -1;
+    if (wv == 0) {                                 // the rows that have holes
+        bool hole = false;
+        if (lane < nr)
+            for (int s = 0; s < k; ++s) hole |= s_slot[lane * k + s] < 0;
+        const unsigned long long b = __ballot(hole);
+        if (hole) s_queue[__popcll(b & ((1ull << lane) - 1))] = lane;
+        if (lane == 0) s_nq = __popcll(b);
+    }
+    __syncthreads();
+    const int lg = tid & (G - 1), grp = tid / G, nq = s_nq;
+    const bool vec = EPL >= 4 && (E & 3) == 0 && ((size_t)a.q & 15) == 0;
+    auto col = [&](int m) { return EPL >= 4 ? (m >> 2) * (4 * G) + lg * 4 + (m & 3) : lg * EPL + m; };
+    unsigned roomy = 0;
+#pragma unroll
+    for (int m = 0; m < EPL; ++m)
+        if (col(m) < E && s_room[col(m)] > 0) roomy |= 1u << m;
+    for (int i = grp; i < nq; i += 256 / G) {
+        const int lr = s_queue[i];
+        const int32_t *qr = a.q + (size_t)(row0 + lr) * E;
+        int v[EPL];
+        if (vec) {
+#pragma unroll
+            for (int m = 0; m < EPL; m += 4) {
+                const int4 t4 = col(m) < E ? *(const int4 *)(qr + col(m)) : make_int4(0, 0, 0, 0);
+                v[m] = t4.x;
+                if constexpr (EPL >= 4) { v[m + 1] = t4.y; v[m + 2] = t4.z; v[m + 3] = t4.w; }
+            }
+        } else {
+#pragma unroll
+            for (int m = 0; m < EPL; ++m) v[m] = col(m) < E ? qr[col(m)] : 0;
+        }
+        unsigned live = roomy;
+        for (int s = 0; s < k; ++s) {
+            const int e = s_slot[lr * k + s];
+            if (e < 0) continue;
+            const int l = EPL >= 4 ? (e >> 2) & (G - 1) : e / EPL, m = EPL >= 4 ? e / (4 * G) * 4 + (e & 3) : e % EPL;
+            if (l == lg) live &= ~(1u << m);
+        }
+        for (int s = 0; s < k; ++s) {
+            if (s_slot[lr * k + s] >= 0) continue;
+            // the largest reward, the lowest expert that has it
+            int best = INT_MIN;
+#pragma unroll
+            for (int m = 0; m < EPL; ++m)
+                if (((live >> m) & 1) && v[m] > best) best = v[m];
+            best = group_max<G>(best);
+            int low = INT_MAX;
+#pragma unroll
+            for (int m = EPL - 1; m >= 0; --m)
+                if (((live >> m) & 1) && v[m] == best) low = col(m);
+            low = ~group_max<G>(~low);
+            if (low == INT_MAX) break;                     // nobody left to ask
+            const int l = EPL >= 4 ? (low >> 2) & (G - 1) : low / EPL, m = EPL >= 4 ? low / (4 * G) * 4 + (low & 3) : low % EPL;
+            if (l == lg) live &= ~(1u << m);
+            if (lg == 0) s_prop[s * kIterRows + lr] = low;
+        }
+    }
+    __syncthreads();
+    for (int s = wv; s < k; s += 4) {
+        const int e = s_prop[s * kIterRows + lane];
+        const size_t tile = (size_t)s * a.n_wg + w;
+        if (lane < nr) a.list[(size_t)s * T + row0 + lane] = e;
+        const bool some = __any(e >= 0);
+        if (lane == 0) a.any[tile] = some;
+        if (!some) continue;
+        int *cnt = s_cnt + wv * E;
+        for (int x = lane; x < E; x += 64) cnt[x] = 0;
+        wave_lds_sync();
+        const unsigned long long same = same_expert(e, a.ebits);
+        if (e >= 0 && lane == __ffsll((long long)same) - 1) {
+            const int n = __popcll(same);
+            cnt[e] = n;
+            atomicAdd(&ar->tot[w & 7][e], n);
+        }
+        wave_lds_sync();
+        for (int x = lane; x < E; x += 64) a.tiles[tile * E + x] = cnt[x];
+        wave_lds_sync();
     }
 }
 
-// A proposal is accepted when its position among the proposals of its expert is below the room left.
-__global__ __launch_bounds__(256) void k_iter_accept(const int32_t *__restrict__ prop, const int32_t *__restrict__ pos,
-                                                     const int32_t *__restrict__ offsets,
-                                                     const int *__restrict__ load, int *__restrict__ load_next, int T,
-                                                     int E, int k, int C, int32_t *__restrict__ assign,
-                                                     IterState *__restrict__ st)
+__global__ __launch_bounds__(256) void k_iter_scan(IterArgs a, int r, int last, int max_rounds, int *host)
 {
-    const size_t n = (size_t)T * k;
-    const size_t a = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (a < n) {
-        const size_t i = a / k, s = a % k, idx = s * T + i;
-        const int e = prop[idx];
-        if (e >= 0 && pos[idx] < C - load[e]) assign[a] = e;
-    }
-    if (blockIdx.x == 0) {
-        for (int j = threadIdx.x; j < E; j += blockDim.x) {
-            const int cnt = offsets[j + 1] - offsets[j], room = C - load[j];
-            load_next[j] = load[j] + (cnt < room ? cnt : room);
+    __shared__ int s_w[4];
+    __shared__ long long s_sum[4];
+    IterArea *ar = a.ar;
+    const int e = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int phase = iter_phase(ar, r);
+    if (phase == 0) return;
+    if (phase == 1 || last) {                      // the end: what the blocks have reported
+        if (e != 0) return;
+        long long sum = 0;
+        int flow = 0;
+        for (int i = tid; i < a.n_wg; i += 256) {
+            sum += a.bsum[i];
+            flow += a.bflow[i];
         }
-        if (threadIdx.x == 0) {
-            const int np = offsets[E];
-            st->nprop = np;
-            if (np > 0) st->rounds += 1;
+        for (int off = 32; off >= 1; off >>= 1) {
+            sum += __shfl_xor(sum, off);
+            flow += __shfl_xor(flow, off);
         }
+        if (lane == 0) {
+            s_sum[wv] = sum;
+            s_w[wv] = flow;
+        }
+        __syncthreads();
+        if (tid == 0) {
+            *(volatile long long *)(host + kIterWordTotal) = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
+            ((volatile int *)host)[kIterWordFlow] = s_w[0] + s_w[1] + s_w[2] + s_w[3];
+            ((volatile int *)host)[kIterWordRounds] = phase == 1 ? (r >= 2 ? r - 2 : 0) : r - 1;
+            ((volatile int *)host)[kIterWordOpen] = phase == 2 && max_rounds > 0;
+            __threadfence_system();
+            ((volatile int *)host)[0] = 1;
+        }
+        return;
     }
+    int c = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) c += ar->tot[i][e];
+    const int load = ar->load[r & 1][e], room = a.C - load;
+    __syncthreads();
+    if (tid < 8) ar->tot[tid][e] = 0;
+    if (tid == 0) {
+        ar->load[(r + 1) & 1][e] = load + (c < room ? c : room);
+        ar->cnt[e] = c;
+        if (c > 0) atomicAdd(&ar->np[r & 3], c);
+        if (e == 0) ((volatile int *)host)[kIterWordProgress] = r + 1;
+    }
+    if (c <= room || room <= 0) return;
+    const int n = a.k * a.n_wg, per = (n + 255) / 256, t0 = tid * per, t1 = t0 + per < n ? t0 + per : n;
+    int sum = 0;
+#pragma unroll 4
+    for (int t = t0; t < t1; ++t) sum += a.any[t] ? a.tiles[(size_t)t * a.E + e] : 0;
+    int inc = sum;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(inc, off);
+        if (lane >= off) inc += o;
+    }
+    if (lane == 63) s_w[wv] = inc;
+    __syncthreads();
+    int run = inc - sum;
+    for (int v = 0; v < wv; ++v) run += s_w[v];
+    if (sum == 0) return;
+#pragma unroll 4
+    for (int t = t0; t < t1; ++t)
+        if (a.any[t]) {
+            const int x = a.tiles[(size_t)t * a.E + e];
+            a.tiles[(size_t)t * a.E + e] = run;
+            run += x;
+        }
 }
 
 __global__ __launch_bounds__(256) void k_iter_total(const int32_t *__restrict__ q, const int32_t *__restrict__ assign,
@@ -213,14 +423,6 @@ void launch_topk(const int32_t *q, int T, int E, int k, int32_t *choice, hipStre
     hipLaunchKernelGGL(k_iter_topk<EPL>, dim3(grid), dim3(256), 0, s, q, T, E, k, choice);
 }
 
-template <int EPL>
-void launch_propose(const int32_t *q, const int32_t *assign, const int *load, int T, int E, int k, int C,
-                    int32_t *prop, hipStream_t s)
-{
-    const int grid = T < 4 * 2048 ? (T + 3) / 4 : 2048;
-    hipLaunchKernelGGL(k_iter_propose<EPL>, dim3(grid), dim3(256), 0, s, q, assign, load, T, E, k, C, prop);
-}
-
 }  // namespace
 
 int32_t top1_run(const int32_t *q, int T, int E, int32_t *top1, hipStream_t s)
@@ -257,57 +459,73 @@ int32_t iter_run(const int32_t *q, int T, int E, int k, int C, int max_rounds, i
                  int32_t *flow, int32_t *rounds, char *ws, hipStream_t s)
 {
     WorkspaceLayout L = workspace_layout(T, E, k);
-    const size_t n = (size_t)T * k;
-    int32_t *list = (int32_t *)(ws + L.klist_off);     // slot-major choices, later proposals
-    int32_t *pos = list + n;
-    int32_t *offsets = (int32_t *)(ws + L.theta_off);
-    int *load = (int *)(ws + L.gcount_off);            // two buffers of kMaxE, alternating by round
-    IterState *st = (IterState *)(ws + L.state_off);
-    int *tiles = (int *)(ws + L.tiles_off);
-    const int epl = (E + 63) / 64;
-    const int pair_grid = (int)((n + 255) / 256);
-
-    if (epl <= 1) launch_topk<1>(q, T, E, k, list, s);
-    else if (epl <= 2) launch_topk<2>(q, T, E, k, list, s);
-    else if (epl <= 4) launch_topk<4>(q, T, E, k, list, s);
-    else if (epl <= 8) launch_topk<8>(q, T, E, k, list, s);
-    else launch_topk<16>(q, T, E, k, list, s);
-    int32_t rc = dispatch_core(list, nullptr, n, E, 1, offsets, nullptr, nullptr, pos, tiles, L.n_tiles, s);
+    IterArgs a;
+    a.q = q;
+    a.assign = assign;
+    a.list = (int32_t *)(ws + L.klist_off);
+    a.n_wg = (T + kIterRows - 1) / kIterRows;
+    char *at = ws + L.price_off;
+    a.ar = (IterArea *)at;
+    at += (sizeof(IterArea) + 255) / 256 * 256;
+    a.bsum = (long long *)at;
+    at += sizeof(long long) * a.n_wg;
+    a.bflow = (int *)at;
+    a.any = a.bflow + a.n_wg;
+    a.tiles = a.any + (size_t)k * a.n_wg;
+    a.wcnt = (int *)(ws + L.wcnt_off);
+    a.T = T;
+    a.E = E;
+    a.k = k;
+    a.C = C;
+    a.ebits = 0;
+    while ((1 << a.ebits) < E) ++a.ebits;
+    int *host = nullptr, *host_dev = nullptr;
+    int32_t rc = solver_words(&host, &host_dev);
     if (rc) return rc;
-    hipLaunchKernelGGL(k_iter_keep, dim3(pair_grid), dim3(256), 0, s, list, pos, offsets, T, E, k, C, assign, load, st);
+    volatile int *hw = host;
+    hw[0] = hw[kIterWordProgress] = 0;
 
-    IterState h = {};
-    int r = 0;
-    bool open = false;          // the last round still had proposals
-    while (r < max_rounds) {
-        const int batch = max_rounds - r < 2 ? max_rounds - r : 2;   // two rounds per host check
-        for (int b = 0; b < batch; ++b, ++r) {
-            const int *cur = load + (r & 1) * kMaxE;
-            int *next = load + ((r + 1) & 1) * kMaxE;
-            if (epl <= 1) launch_propose<1>(q, assign, cur, T, E, k, C, list, s);
-            else if (epl <= 2) launch_propose<2>(q, assign, cur, T, E, k, C, list, s);
-            else if (epl <= 4) launch_propose<4>(q, assign, cur, T, E, k, C, list, s);
-            else if (epl <= 8) launch_propose<8>(q, assign, cur, T, E, k, C, list, s);
-            else launch_propose<16>(q, assign, cur, T, E, k, C, list, s);
-            rc = dispatch_core(list, nullptr, n, E, 1, offsets, nullptr, nullptr, pos, tiles, L.n_tiles, s);
-            if (rc) return rc;
-            hipLaunchKernelGGL(k_iter_accept, dim3(pair_grid), dim3(256), 0, s, list, pos, offsets, cur, next, T, E,
-                               k, C, assign, st);
+    int G = 8, EPL = 1;
+    while (G * 16 < E) G *= 2;
+    while (G * EPL < E) EPL *= 2;
+    const size_t shm = sizeof(int) * ((size_t)2 * kIterRows * k + 6 * (size_t)E);
+    hipLaunchKernelGGL(k_iter_init, dim3(1), dim3(1024), 0, s, a.ar);
+    for (int r = 0; !hw[0]; ++r) {
+        const int last = r > max_rounds ? 1 : 0;
+#define MS_I(GG, PP) hipLaunchKernelGGL((k_iter_step<GG, PP>), dim3(a.n_wg), dim3(256), shm, s, a, r, last)
+        if (G == 8) {
+            if (EPL == 1) MS_I(8, 1);
+            else if (EPL == 2) MS_I(8, 2);
+            else if (EPL == 4) MS_I(8, 4);
+            else if (EPL == 8) MS_I(8, 8);
+            else MS_I(8, 16);
+        } else if (G == 16) MS_I(16, 16);
+        else if (G == 32) MS_I(32, 16);
+        else MS_I(64, 16);
+#undef MS_I
+        hipLaunchKernelGGL(k_iter_scan, dim3(E), dim3(256), 0, s, a, r, last, max_rounds, host_dev);
+        if (hipGetLastError() != hipSuccess) {
+            (void)hipStreamSynchronize(s);
+            return MAXSCORE_ERR_HIP;
         }
-        MS_HIP(hipMemcpyAsync(&h, st, sizeof(h), hipMemcpyDeviceToHost, s));
-        MS_HIP(hipStreamSynchronize(s));
-        open = h.nprop > 0;
-        if (!open) break;
+        // two rounds stay queued behind the one that runs; the stream is looked at now and then, so that an error ends
+        // the wait
+        for (unsigned spin = 1; !hw[0] && (last || r + 1 - hw[kIterWordProgress] > 2); ++spin) {
+            if ((spin & 2047) == 0) {
+                const hipError_t e = hipStreamQuery(s);
+                if (e != hipErrorNotReady && !hw[0] && (e != hipSuccess || last)) {
+                    (void)hipStreamSynchronize(s);
+                    if (hw[0]) break;
+                    return MAXSCORE_ERR_HIP;
+                }
+            }
+            __builtin_ia32_pause();
+        }
     }
-    const int tot_grid = pair_grid < 256 ? pair_grid : 256;
-    hipLaunchKernelGGL(k_iter_total, dim3(tot_grid), dim3(256), 0, s, q, assign, T, E, k, st);
-    MS_HIP(hipGetLastError());
-    MS_HIP(hipMemcpyAsync(&h, st, sizeof(h), hipMemcpyDeviceToHost, s));
-    MS_HIP(hipStreamSynchronize(s));
-    if (total) *total = (int64_t)h.total;
-    if (flow) *flow = h.flow;
-    if (rounds) *rounds = h.rounds;
-    return open ? MAXSCORE_ERR_NOT_CONVERGED : MAXSCORE_OK;
+    if (total) *total = *(volatile long long *)(host + kIterWordTotal);
+    if (flow) *flow = hw[kIterWordFlow];
+    if (rounds) *rounds = hw[kIterWordRounds];
+    return hw[kIterWordOpen] ? MAXSCORE_ERR_NOT_CONVERGED : MAXSCORE_OK;
 }
 
 }  // namespace maxscore

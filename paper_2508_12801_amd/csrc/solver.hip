@@ -1842,6 +1842,16 @@ static int32_t solver_host(SolverHost **out)
     return MAXSCORE_OK;
 }
 
+int32_t solver_words(int **host, int **dev)
+{
+    SolverHost *hs = nullptr;
+    const int32_t rc = solver_host(&hs);
+    if (rc) return rc;
+    *host = hs->flag;
+    *dev = hs->flag_dev;
+    return MAXSCORE_OK;
+}
+
 // On an error after work has been queued the stream is drained before returning, so that nothing of this solve
 // is still running on the caller's buffers.
 #define MS_HIP_SYNC(call)                        \

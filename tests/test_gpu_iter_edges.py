@@ -1,0 +1,44 @@
+"""GPU parity of the rerouting rounds and of the dispatch behind them at the edges of their kernels: token counts around a
+block, expert counts around the lanes and columns of a row, slot counts around what the counted dispatch takes."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def ms():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2508_12801_amd as m
+    m.load_library()
+    return m
+
+
+@pytest.mark.parametrize("T,E,k,C", [
+    (1, 1, 1, 1), (1, 9, 2, 1), (63, 8, 8, 63), (64, 9, 3, 20), (65, 64, 16, 17), (129, 65, 17, 36), (200, 128, 5, 7),
+    (190, 129, 2, 2), (300, 256, 16, 19), (300, 257, 4, 4), (130, 512, 3, 1), (130, 513, 3, 1), (1000, 20, 6, 200), (2049, 12, 4, 683),
+])
+def test_edges(ms, T, E, k, C):
+    print(f"iter edges T={T} E={E} k={k} C={C}", flush=True)
+    rng = np.random.default_rng(T + E + k)
+    L = (rng.standard_normal((T, E)) + rng.standard_normal(E)).astype(np.float32)
+    out = ms.route_logits(torch.from_numpy(L).cuda(), k, C, assignment="iter", allow_not_converged=True)
+    ref = oracle.iter_reroute(out["q"].cpu().numpy().astype(np.int64), k, C)
+    a = out["assign"].cpu().numpy()
+    assert np.array_equal(a, ref["assign"])
+    s = out["stats"]
+    assert (s["total_score_q"], s["flow_value"], s["rounds"]) == (ref["total"], ref["flow"], ref["rounds"])
+    g = out["gates"].cpu().numpy()
+    scores = out["scores"].cpu().numpy()
+    assert np.array_equal(g, np.where(a >= 0, np.take_along_axis(scores, np.maximum(a, 0), axis=1), 0))
+    want = oracle.dispatch(a, g, E)
+    n = ref["flow"]
+    assert np.array_equal(out["expert_offsets"].cpu().numpy(), want["expert_offsets"])
+    assert np.array_equal(out["disp_token"].cpu().numpy()[:n], want["disp_token"])
+    assert np.array_equal(out["disp_gate"].cpu().numpy()[:n], want["disp_gate"])
+    assert np.array_equal(out["token_pos"].cpu().numpy(), want["token_pos"])
