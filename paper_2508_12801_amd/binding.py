@@ -139,20 +139,30 @@ def status_string(code: int) -> str:
         return "status %d" % code
 
 
+_TORCH = None           # torch, once a GPU has been seen (a small batch spends more time in the binding than in its kernels)
+_RAW_STREAM = None      # (device index) -> handle of its current stream
+
+
 def _torch():
-    import torch
-    if not torch.cuda.is_available():
-        raise MaxScoreError(-5, "no GPU visible: the MaxScore kernels have no CPU fallback")
-    return torch
+    global _TORCH, _RAW_STREAM
+    if _TORCH is None:
+        import torch
+        if not torch.cuda.is_available():
+            raise MaxScoreError(-5, "no GPU visible: the MaxScore kernels have no CPU fallback")
+        torch.cuda.init()
+        # the handle alone, where torch offers it: the Stream object around it costs ten times as much
+        _RAW_STREAM = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+            lambda index: torch.cuda.current_stream(index).cuda_stream)
+        _TORCH = torch
+    return _TORCH
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return _RAW_STREAM(_torch().cuda.current_device())
 
 
 def _check(rc: int, where: str, allow=()):
@@ -167,18 +177,23 @@ def workspace_bytes(T: int, d: int, E: int, k: int, C: int) -> int:
     return int(load_library().maxscore_workspace_bytes(T, d, E, k, C))
 
 
-def _workspace(T, E, k, C, device, d=0):
+def _scratch(tag, need, device):
+    """One buffer per use, device and stream: calls on different streams may overlap and must not share scratch."""
     torch = _torch()
+    index = torch.cuda.current_device() if device.index is None else device.index
+    key = (tag, index, _RAW_STREAM(index))
+    buf = _WS.get(key)
+    if buf is None or buf.numel() < need:
+        buf = torch.empty(max(need, 256), dtype=torch.uint8, device=device)
+        _WS[key] = buf
+    return buf
+
+
+def _workspace(T, E, k, C, device, d=0):
     need = workspace_bytes(T, d, E, k, C)
     if need == 0:
         raise MaxScoreError(-2, "workspace_bytes")
-    # one buffer per device and stream: calls on different streams may overlap and must not share scratch
-    key = (str(device), torch.cuda.current_stream(device).cuda_stream)
-    buf = _WS.get(key)
-    if buf is None or buf.numel() < need:
-        buf = torch.empty(need, dtype=torch.uint8, device=device)
-        _WS[key] = buf
-    return buf, need
+    return _scratch("ws", need, device), need
 
 
 ASSIGNMENTS = {"exact": 0, "iter": 1}
@@ -223,11 +238,7 @@ def router_logits(x, W, bias=None, use_workspace=True):
     ws, need = (None, 0)
     if use_workspace:
         need = 2 * d * E
-        key = ("wt", str(x.device), torch.cuda.current_stream(x.device).cuda_stream)
-        ws = _WS.get(key)
-        if ws is None or ws.numel() < need:
-            ws = torch.empty(max(need, 256), dtype=torch.uint8, device=x.device)
-            _WS[key] = ws
+        ws = _scratch("wt", need, x.device)
     rc = load_library().maxscore_router_logits(_ptr(x), _ptr(W), _ptr(bias), _in_dtype(x), T, d, E, _ptr(out),
                                                _ptr(ws), need, _stream())
     _check(rc, "maxscore_router_logits")
@@ -245,11 +256,7 @@ def router_softtopk(x, W, bias, k: int, t: float, quant_shift: int = 20, want_lo
     scores = torch.empty((T, E), dtype=torch.float32, device=x.device)
     q = torch.empty((T, E), dtype=torch.int32, device=x.device)
     need = 2 * d * E
-    key = ("wt", str(x.device), torch.cuda.current_stream(x.device).cuda_stream)
-    ws = _WS.get(key)
-    if ws is None or ws.numel() < need:
-        ws = torch.empty(max(need, 256), dtype=torch.uint8, device=x.device)
-        _WS[key] = ws
+    ws = _scratch("wt", need, x.device)
     rc = load_library().maxscore_router_softtopk(_ptr(x), _ptr(W), _ptr(bias), _in_dtype(x), T, d, E, k, float(t),
                                                  quant_shift, _ptr(logits), _ptr(scores), _ptr(q), _ptr(ws), need,
                                                  _stream())
