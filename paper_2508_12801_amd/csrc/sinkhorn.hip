@@ -6,8 +6,14 @@
 //   column targets m_j = caps_j * T / sum(caps);  v = 1;  n_iter times: u_i = 1 / sum_j K_ij v_j,
 //   v_j = m_j / sum_i K_ij u_i;  plan_ij = u_i K_ij v_j;  second expert = arg-max_j plan_ij (ties to the lower
 //   id; -1 when the row is all zero).
-// One wavefront per token row, lane l holds experts l, l+64, ...; K is recomputed from the scores in every pass
-// (it is cheaper than storing it), column sums go through per-workgroup partial results added in a fixed order.
+// Three ways to do it, by size; column sums are added in a fixed order everywhere, beyond a few rows in double:
+//   small    up to 65536 scores of up to 16 experts, half as many of up to 64: the whole call is one workgroup that keeps
+//            K in registers, a thread owns whole rows.  An iteration takes 2 to 4 us (two barriers and six exchanges), two
+//            launches each 8.
+//   medium   up to 64 experts: eight lanes per row, K recomputed from the scores; one launch per iteration, whose
+//            workgroups begin by adding up the column sums of the iteration before
+//   large    one wavefront per row, lane l holds experts l, l+64, ...; rows and columns are launches of their own
+// 20 iterations: 4096 tokens, 16 experts 228 to 95 us; 16384 and 64 350 to 219 us; 65536 and 64 574 to 315 us.
 #include "common.h"
 
 namespace maxscore {
@@ -40,10 +46,20 @@ __device__ inline int sk_argmax(const float (&x)[EPL], const bool (&in)[EPL], fl
     return e;
 }
 
+constexpr int kSkCopies = 8;                 // partial counts of the top-1 choices, one per chiplet
+
+__global__ __launch_bounds__(1024) void k_sk_zero(int *counts)
+{
+    for (int i = threadIdx.x; i < kSkCopies * kMaxE; i += 1024) counts[i] = 0;
+}
+
 template <int EPL>
 __global__ __launch_bounds__(256) void k_sk_top1(const float *__restrict__ scores, int T, int E,
-                                                 int32_t *__restrict__ top1)
+                                                 int32_t *__restrict__ top1, int *__restrict__ counts)
 {
+    __shared__ int s_cnt[kMaxE];
+    for (int e = threadIdx.x; e < E; e += 256) s_cnt[e] = 0;
+    __syncthreads();
     const int lane = threadIdx.x & 63;
     const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int n_waves = (gridDim.x * blockDim.x) >> 6;
@@ -60,20 +76,25 @@ __global__ __launch_bounds__(256) void k_sk_top1(const float *__restrict__ score
         }
         mx = sk_wave_max(mx);
         const int e = sk_argmax<EPL>(x, in, mx);
-        if (lane == 0) top1[row] = e;
+        if (lane == 0) {
+            top1[row] = e;
+            if (e >= 0) atomicAdd(&s_cnt[e], 1);
+        }
     }
+    __syncthreads();
+    int *c = counts + (blockIdx.x % kSkCopies) * kMaxE;
+    for (int e = threadIdx.x; e < E; e += 256)
+        if (s_cnt[e]) atomicAdd(c + e, s_cnt[e]);
 }
 
-// caps, column targets and the starting v from the top-1 counts (one workgroup)
-__global__ __launch_bounds__(1024) void k_sk_init(const int32_t *__restrict__ offsets, int T, int E, int C,
-                                                  int32_t *__restrict__ caps, float *__restrict__ targets,
-                                                  float *__restrict__ v)
+// caps, column targets and the starting v from the top-1 counts (one workgroup; thread j: expert j)
+__device__ __forceinline__ void sk_targets(int count, int T, int E, int C, int &cap, float &target)
 {
     __shared__ long long s_w[16];
     const int j = threadIdx.x;
-    int cap = 0;
+    cap = 0;
     if (j < E) {
-        const int left = C - (offsets[j + 1] - offsets[j]);
+        const int left = C - count;
         cap = left > 0 ? left : 0;
     }
     long long sum = cap;
@@ -81,13 +102,346 @@ __global__ __launch_bounds__(1024) void k_sk_init(const int32_t *__restrict__ of
     if ((j & 63) == 0) s_w[j >> 6] = sum;
     __syncthreads();
     long long tot = 0;
-    for (int w = 0; w < 16; ++w) tot += s_w[w];
+    for (int w = 0; w < (int)blockDim.x >> 6; ++w) tot += s_w[w];
+    target = tot > 0 ? (float)((double)cap * (double)T / (double)tot) : 0.f;
+}
+
+__global__ __launch_bounds__(1024) void k_sk_init(const int *__restrict__ counts, int T, int E, int C,
+                                                  int32_t *__restrict__ caps, float *__restrict__ targets,
+                                                  float *__restrict__ v)
+{
+    const int j = threadIdx.x;
+    int n = 0, cap;
+    float target;
+    for (int c = 0; c < kSkCopies; ++c) n += j < E ? counts[c * kMaxE + j] : 0;
+    sk_targets(n, T, E, C, cap, target);
     if (j < E) {
         caps[j] = cap;
-        targets[j] = tot > 0 ? (float)((double)cap * (double)T / (double)tot) : 0.f;
+        targets[j] = target;
         v[j] = 1.f;
     }
 }
+
+__device__ __forceinline__ float sk_column(double sum, float m)
+{
+    return m > 0.f ? (float)((double)m / (sum > 1e-300 ? sum : 1e-300)) : 0.f;
+}
+
+// ---- small: everything in one workgroup ----
+
+// Column sums over a wavefront: lanes exchange halves of their columns until every lane holds the sum of one of them (the
+// last steps of EP < 64 add equal columns); in double from the sum of eight rows on.
+template <int HALF, int OFF, int N, typename V>
+__device__ __forceinline__ void sk_exchange(V (&f)[N], int lane, int &column)
+{
+    const bool up = (lane & OFF) != 0;
+    column |= up ? HALF : 0;
+#pragma unroll
+    for (int c = 0; c < HALF; ++c) {
+        const V give = up ? f[c] : f[c + HALF], keep = up ? f[c + HALF] : f[c];
+        f[c] = keep + __shfl_xor(give, OFF);
+    }
+}
+
+template <int EP>
+__device__ __forceinline__ double sk_reduce_scatter(float (&f)[EP], int lane, int &column)
+{
+    column = 0;
+    if constexpr (EP >= 64) sk_exchange<32, 32>(f, lane, column);
+    if constexpr (EP >= 32) sk_exchange<16, EP == 32 ? 32 : 16>(f, lane, column);
+    if constexpr (EP >= 16) sk_exchange<8, EP == 16 ? 32 : EP == 32 ? 16 : 8>(f, lane, column);
+    constexpr int O = EP == 8 ? 32 : EP == 16 ? 16 : EP == 32 ? 8 : 4;
+    double d[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) d[c] = (double)f[c];
+    sk_exchange<4, O>(d, lane, column);
+    sk_exchange<2, O / 2>(d, lane, column);
+    sk_exchange<1, O / 4>(d, lane, column);
+#pragma unroll
+    for (int off = O / 8; off >= 1; off >>= 1) d[0] += __shfl_xor(d[0], off);
+    return d[0];
+}
+
+// threads: as many as there are rows, up to the register budget of 64 scores each
+template <int EP>
+constexpr int kSkSmallThreads = EP <= 16 ? 1024 : 512;
+
+template <int EP>
+__global__ __launch_bounds__(kSkSmallThreads<EP>) void k_sk_small(const float *__restrict__ scores, int T, int E, int C, float inv_tau,
+                                                   int n_iter, int32_t *__restrict__ assign, float *__restrict__ plan,
+                                                   int32_t *__restrict__ caps)
+{
+    constexpr int RR = 64 / EP;                 // rows per thread: r * nt + tid
+    __shared__ int s_cnt[EP];
+    __shared__ float s_target[EP];
+    __shared__ __attribute__((aligned(16))) float s_v[EP];
+    __shared__ double s_red[16 * EP];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nt = blockDim.x, nw = nt >> 6;
+    const bool vec = (E & 3) == 0 && ((size_t)scores & 15) == 0;
+    if (tid < EP) s_cnt[tid] = 0;
+    __syncthreads();
+    float x[RR][EP], mx[RR], u[RR];
+    int t1[RR];
+#pragma unroll
+    for (int r = 0; r < RR; ++r) {
+        const int row = r * nt + tid;
+        const float *p = scores + (size_t)(row < T ? row : 0) * E;
+        if (vec) {
+#pragma unroll
+            for (int c = 0; c < EP; c += 4) {
+                const float4 f = c < E ? *(const float4 *)(p + c) : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+                x[r][c] = f.x; x[r][c + 1] = f.y; x[r][c + 2] = f.z; x[r][c + 3] = f.w;
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < EP; ++c) x[r][c] = c < E ? p[c] : -INFINITY;
+        }
+        float m = -INFINITY;
+#pragma unroll
+        for (int c = 0; c < EP; ++c) m = fmaxf(m, x[r][c]);
+        t1[r] = -1;
+#pragma unroll
+        for (int c = EP - 1; c >= 0; --c)
+            if (c < E && x[r][c] == m) t1[r] = c;
+        if (row < T && t1[r] >= 0) atomicAdd(&s_cnt[t1[r]], 1);
+        mx[r] = -INFINITY;
+        u[r] = 1.f;
+#pragma unroll
+        for (int c = 0; c < EP; ++c) {
+            if (c == t1[r]) x[r][c] = 0.f;
+            if (c < E) mx[r] = fmaxf(mx[r], x[r][c]);
+        }
+    }
+    __syncthreads();
+    int cap;
+    float target;
+    sk_targets(tid < E ? s_cnt[tid] : 0, T, E, C, cap, target);
+    if (tid < EP) {
+        s_target[tid] = tid < E ? target : 0.f;
+        s_v[tid] = tid < E && target > 0.f ? 1.f : 0.f;
+        if (tid < E) caps[tid] = cap;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < RR; ++r)
+#pragma unroll
+        for (int c = 0; c < EP; ++c) x[r][c] = s_target[c] > 0.f ? expf((x[r][c] - mx[r]) * inv_tau) : 0.f;     // K_ij
+    for (int it = 0; it < n_iter; ++it) {
+        float acc[EP];
+#pragma unroll
+        for (int c = 0; c < EP; ++c) acc[c] = 0.f;
+#pragma unroll
+        for (int r = 0; r < RR; ++r) {
+            if (r * nt + tid >= T) continue;
+            // four chains: one of EP dependent additions would set the pace
+            float s4[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int c = 0; c < EP; ++c) s4[c & 3] += x[r][c] * s_v[c];
+            u[r] = 1.f / ((s4[0] + s4[1]) + (s4[2] + s4[3]));
+#pragma unroll
+            for (int c = 0; c < EP; ++c) acc[c] += x[r][c] * u[r];
+        }
+        int column;
+        const double sum = sk_reduce_scatter<EP>(acc, lane, column);
+        if (EP == 64 || lane % (64 / EP) == 0) s_red[wv * EP + column] = sum;
+        __syncthreads();
+        if (wv == 0) {
+            double tot = 0.0;
+            for (int w = lane / EP; w < nw; w += 64 / EP) tot += s_red[w * EP + lane % EP];
+            for (int o = EP; o < 64; o <<= 1) tot += __shfl_xor(tot, o);
+            if (lane < E) s_v[lane] = sk_column(tot, s_target[lane]);
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int r = 0; r < RR; ++r) {
+        const int row = r * nt + tid;
+        if (row >= T) continue;
+        float pm = -INFINITY;
+#pragma unroll
+        for (int c = 0; c < EP; ++c) {
+            x[r][c] = c < E ? u[r] * x[r][c] * s_v[c] : -INFINITY;
+            if (plan && c < E) plan[(size_t)row * E + c] = x[r][c];
+            pm = fmaxf(pm, x[r][c]);
+        }
+        int second = -1;
+        if (pm > 0.f) {
+#pragma unroll
+            for (int c = EP - 1; c >= 0; --c)
+                if (c < E && x[r][c] == pm) second = c;
+        }
+        assign[2 * (size_t)row] = t1[r];
+        assign[2 * (size_t)row + 1] = second;
+    }
+}
+
+// ---- medium: eight lanes per row, lane l holds experts l * EPL .. ----
+
+constexpr int kSkThreads = 1024, kSkBlocks = 128;
+
+// The v of iteration `it` from the column sums of the one before; every workgroup does this for itself.
+template <int EPL>
+__device__ __forceinline__ void sk_columns(const float *__restrict__ part, int n_blocks, const float *__restrict__ targets,
+                                           int E, int it, float *s_v, float *s_t)
+{
+    constexpr int EP = 8 * EPL, NG = kSkThreads / EP;
+    __shared__ double s_red[16 * EP];
+    const int tid = threadIdx.x, lane = tid & 63, j = tid % EP, g = tid / EP;
+    double sum = 0.0;
+    if (it > 0 && j < E) {
+#pragma unroll 4
+        for (int b = g; b < n_blocks; b += NG) sum += (double)part[(size_t)b * EP + j];
+    }
+    for (int off = EP; off < 64; off <<= 1) sum += __shfl_xor(sum, off);
+    if (lane < EP) s_red[(tid >> 6) * EP + lane] = sum;
+    __syncthreads();
+    if (tid < EP) {
+        double tot = 0.0;
+#pragma unroll 4
+        for (int h = 0; h < 16; ++h) tot += s_red[h * EP + tid];
+        const float m = tid < E ? targets[tid] : 0.f;
+        s_t[tid] = m;
+        s_v[tid] = m > 0.f ? (it > 0 ? sk_column(tot, m) : 1.f) : 0.f;
+    }
+    __syncthreads();
+}
+
+template <int EPL>
+__device__ __forceinline__ void sk_row_load(const float *__restrict__ p, int E, bool vec, int c0, float (&x)[EPL])
+{
+    if (EPL >= 4 && vec) {
+#pragma unroll
+        for (int c = 0; c < EPL; c += 4) {
+            const float4 f = c0 + c < E ? *(const float4 *)(p + c0 + c) : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+            x[c] = f.x;
+            if constexpr (EPL >= 4) { x[c + 1] = f.y; x[c + 2] = f.z; x[c + 3] = f.w; }
+        }
+    } else {
+#pragma unroll
+        for (int c = 0; c < EPL; ++c) x[c] = c0 + c < E ? p[c0 + c] : -INFINITY;
+    }
+}
+
+// One iteration: u of every row, and the workgroup's part of the column sums.
+template <int EPL>
+__global__ __launch_bounds__(kSkThreads) void k_sk_iter(const float *__restrict__ scores, const int32_t *__restrict__ top1,
+                                                        const float *__restrict__ targets, const float *__restrict__ part_in,
+                                                        int it, int T, int E, float inv_tau, float *__restrict__ u,
+                                                        float *__restrict__ part)
+{
+    constexpr int EP = 8 * EPL, NG = kSkThreads / 8;
+    __shared__ float s_v[EP], s_t[EP];
+    __shared__ double s_col[16 * EP];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, c0 = (tid & 7) * EPL;
+    const bool vec = (E & 3) == 0 && ((size_t)scores & 15) == 0;
+    const int n_groups = gridDim.x * NG;
+    int row = blockIdx.x * NG + (tid >> 3);
+    float nx[EPL];
+    sk_row_load<EPL>(scores + (size_t)(row < T ? row : T - 1) * E, E, vec, c0, nx);
+    int nt = top1[row < T ? row : T - 1];
+    sk_columns<EPL>(part_in, gridDim.x, targets, E, it, s_v, s_t);
+    float vv[EPL];
+    bool open[EPL];
+    double acc[EPL];
+#pragma unroll
+    for (int c = 0; c < EPL; ++c) {
+        vv[c] = s_v[c0 + c];
+        open[c] = s_t[c0 + c] > 0.f;
+        acc[c] = 0.0;
+    }
+    for (; row - (tid >> 3) < T; row += n_groups) {
+        float x[EPL];
+        const int t1 = nt;
+#pragma unroll
+        for (int c = 0; c < EPL; ++c) x[c] = nx[c];
+        const int next = row + n_groups;
+        if (next - (tid >> 3) < T) {
+            sk_row_load<EPL>(scores + (size_t)(next < T ? next : T - 1) * E, E, vec, c0, nx);
+            nt = top1[next < T ? next : T - 1];
+        }
+        float mx = -INFINITY;
+#pragma unroll
+        for (int c = 0; c < EPL; ++c) {
+            if (c0 + c == t1) x[c] = 0.f;
+            if (c0 + c < E) mx = fmaxf(mx, x[c]);
+        }
+        for (int off = 1; off < 8; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+        float s = 0.f;
+#pragma unroll
+        for (int c = 0; c < EPL; ++c) {
+            x[c] = open[c] ? expf((x[c] - mx) * inv_tau) : 0.f;
+            s += x[c] * vv[c];
+        }
+        for (int off = 1; off < 8; off <<= 1) s += __shfl_xor(s, off);
+        const float ui = 1.f / s;
+        if (row < T) {
+            if ((tid & 7) == 0) u[row] = ui;
+#pragma unroll
+            for (int c = 0; c < EPL; ++c) acc[c] += (double)(x[c] * ui);
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < EPL; ++c) {
+        for (int off = 8; off < 64; off <<= 1) acc[c] += __shfl_xor(acc[c], off);
+        if (lane < 8) s_col[wv * EP + c0 + c] = acc[c];
+    }
+    __syncthreads();
+    if (tid < EP) {
+        double tot = 0.0;
+        for (int w = 0; w < 16; ++w) tot += s_col[w * EP + tid];
+        part[(size_t)blockIdx.x * EP + tid] = (float)tot;
+    }
+}
+
+// The plan's largest entry of every row, with the v of the last column update.
+template <int EPL>
+__global__ __launch_bounds__(kSkThreads) void k_sk_pick(const float *__restrict__ scores, const int32_t *__restrict__ top1,
+                                                        const float *__restrict__ targets, const float *__restrict__ part,
+                                                        int n_part, int n_iter, const float *__restrict__ u, int T, int E,
+                                                        float inv_tau, int32_t *__restrict__ assign, float *__restrict__ plan)
+{
+    constexpr int EP = 8 * EPL, NG = kSkThreads / 8;
+    __shared__ float s_v[EP], s_t[EP];
+    const int tid = threadIdx.x, c0 = (tid & 7) * EPL;
+    const bool vec = (E & 3) == 0 && ((size_t)scores & 15) == 0;
+    sk_columns<EPL>(part, n_part, targets, E, n_iter, s_v, s_t);
+    for (int row = blockIdx.x * NG + (tid >> 3); row < T; row += gridDim.x * NG) {
+        const int t1 = top1[row];
+        const float ui = n_iter > 0 ? u[row] : 1.f;
+        float x[EPL];
+        sk_row_load<EPL>(scores + (size_t)row * E, E, vec, c0, x);
+        float mx = -INFINITY;
+#pragma unroll
+        for (int c = 0; c < EPL; ++c) {
+            if (c0 + c == t1) x[c] = 0.f;
+            if (c0 + c < E) mx = fmaxf(mx, x[c]);
+        }
+        for (int off = 1; off < 8; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+        float pm = -INFINITY;
+#pragma unroll
+        for (int c = 0; c < EPL; ++c) {
+            const float kij = s_t[c0 + c] > 0.f ? expf((x[c] - mx) * inv_tau) : 0.f;
+            x[c] = c0 + c < E ? ui * kij * s_v[c0 + c] : -INFINITY;
+            if (plan && c0 + c < E) plan[(size_t)row * E + c0 + c] = x[c];
+            pm = fmaxf(pm, x[c]);
+        }
+        for (int off = 1; off < 8; off <<= 1) pm = fmaxf(pm, __shfl_xor(pm, off));
+        int second = 0x7fffffff;
+#pragma unroll
+        for (int c = EPL - 1; c >= 0; --c)
+            if (c0 + c < E && x[c] == pm) second = c0 + c;
+        for (int off = 1; off < 8; off <<= 1) {
+            const int o = __shfl_xor(second, off);
+            second = o < second ? o : second;
+        }
+        if ((tid & 7) == 0) {
+            assign[2 * (size_t)row] = t1;
+            assign[2 * (size_t)row + 1] = pm > 0.f && second < E ? second : -1;
+        }
+    }
+}
+
+// ---- large ----
 
 // u_i = 1 / sum_j K_ij v_j for the rows of this workgroup, and the workgroup's partial sums of K_ij u_i per
 // column.  LAST: also the plan's arg-max (and the plan itself) with the v of the last column update.
@@ -162,7 +516,7 @@ __global__ __launch_bounds__(1024) void k_sk_col(const float *__restrict__ part,
         double sum = 0.0;
         for (int g = 0; g < groups; ++g) sum += s_red[g * epad + tid];
         const float m = targets[tid];
-        v[tid] = m > 0.f ? (float)((double)m / (sum > 1e-300 ? sum : 1e-300)) : 0.f;
+        v[tid] = sk_column(sum, m);
     }
 }
 
@@ -214,13 +568,21 @@ __global__ __launch_bounds__(256) void k_sk_round(const float *__restrict__ scor
     }
 }
 
+int32_t copy_caps(const int32_t *caps, int32_t *caps_host, int E, hipStream_t s)
+{
+    if (!caps_host) return MAXSCORE_OK;
+    MS_HIP(hipMemcpyAsync(caps_host, caps, sizeof(int32_t) * E, hipMemcpyDeviceToHost, s));
+    MS_HIP(hipStreamSynchronize(s));
+    return MAXSCORE_OK;
+}
+
 template <int EPL>
 int32_t run_epl(const float *scores, int T, int E, int C, float tau, int n_iter, int32_t *assign, float *plan,
                 int32_t *caps_host, char *ws, hipStream_t s)
 {
     WorkspaceLayout L = workspace_layout(T, E, 1);
-    int32_t *top1 = (int32_t *)(ws + L.aux_off), *pos = top1 + T;
-    int32_t *offsets = (int32_t *)(ws + L.theta_off);
+    int32_t *top1 = (int32_t *)(ws + L.aux_off);
+    int *counts = (int *)(ws + L.price_off);
     float *targets = (float *)(ws + L.gcount_off), *v = targets + kMaxE;
     int32_t *caps = (int32_t *)(ws + L.cap_off);
     float *u = (float *)(ws + L.klist_off);
@@ -231,11 +593,29 @@ int32_t run_epl(const float *scores, int T, int E, int C, float tau, int n_iter,
     int epad = 1;
     while (epad < E) epad <<= 1;
 
-    hipLaunchKernelGGL(k_sk_top1<EPL>, dim3(grid), dim3(256), 0, s, scores, T, E, top1);
-    int32_t rc = dispatch_core(top1, nullptr, (size_t)T, E, 1, offsets, nullptr, nullptr, pos,
-                               (int *)(ws + L.tiles_off), L.n_tiles, s);
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_sk_init, dim3(1), dim3(1024), 0, s, offsets, T, E, C, caps, targets, v);
+    hipLaunchKernelGGL(k_sk_zero, dim3(1), dim3(1024), 0, s, counts);
+    hipLaunchKernelGGL(k_sk_top1<EPL>, dim3(grid), dim3(256), 0, s, scores, T, E, top1, counts);
+    hipLaunchKernelGGL(k_sk_init, dim3(1), dim3(1024), 0, s, counts, T, E, C, caps, targets, v);
+    if (EPL == 1) {
+        const int blocks = (T + 127) / 128 < kSkBlocks ? (T + 127) / 128 : kSkBlocks;
+        float *sums = (float *)(counts + kSkCopies * kMaxE);         // two halves: of this iteration and of the one before
+        auto half = [&](int it) { return sums + (size_t)(it & 1) * kSkBlocks * 64; };
+#define MS_SK(PP)                                                                                                          \
+    do {                                                                                                                   \
+        for (int it = 0; it < n_iter; ++it)                                                                                \
+            hipLaunchKernelGGL(k_sk_iter<PP>, dim3(blocks), dim3(kSkThreads), 0, s, scores, top1, targets, half(it + 1), it, T, E, \
+                               inv_tau, u, half(it));                                                                      \
+        hipLaunchKernelGGL(k_sk_pick<PP>, dim3((T + 127) / 128 < 512 ? (T + 127) / 128 : 512), dim3(kSkThreads), 0, s,      \
+                           scores, top1, targets, half(n_iter + 1), blocks, n_iter, u, T, E, inv_tau, assign, plan);       \
+    } while (0)
+        if (E <= 8) MS_SK(1);
+        else if (E <= 16) MS_SK(2);
+        else if (E <= 32) MS_SK(4);
+        else MS_SK(8);
+#undef MS_SK
+        MS_HIP(hipGetLastError());
+        return copy_caps(caps, caps_host, E, s);
+    }
     for (int it = 0; it < n_iter; ++it) {
         hipLaunchKernelGGL(k_sk_row<EPL>, dim3(grid), dim3(256), (size_t)4 * E * sizeof(float), s, scores, top1,
                            targets, v, T, E, inv_tau, u, part);
@@ -244,11 +624,7 @@ int32_t run_epl(const float *scores, int T, int E, int C, float tau, int n_iter,
     hipLaunchKernelGGL(k_sk_round<EPL>, dim3(grid), dim3(256), 0, s, scores, top1, targets, v, u, n_iter > 0 ? 1 : 0,
                        T, E, inv_tau, assign, plan);
     MS_HIP(hipGetLastError());
-    if (caps_host) {
-        MS_HIP(hipMemcpyAsync(caps_host, caps, sizeof(int32_t) * E, hipMemcpyDeviceToHost, s));
-        MS_HIP(hipStreamSynchronize(s));
-    }
-    return MAXSCORE_OK;
+    return copy_caps(caps, caps_host, E, s);
 }
 
 }  // namespace
@@ -257,6 +633,19 @@ int32_t sinkhorn_run(const float *scores, int T, int E, int C, float tau, int n_
                      int32_t *caps_host, char *ws, hipStream_t s)
 {
     const int epl = (E + 63) / 64;
+    const int ep = E <= 8 ? 8 : E <= 16 ? 16 : E <= 32 ? 32 : 64;
+    if (E <= 64 && T <= (ep <= 16 ? 1024 : 512) * (64 / ep)) {
+        const int most = ep <= 16 ? 1024 : 512, nt = T >= most ? most : (T + 63) / 64 * 64;
+        int32_t *caps = (int32_t *)(ws + workspace_layout(T, E, 1).cap_off);
+#define MS_SK(PP) hipLaunchKernelGGL(k_sk_small<PP>, dim3(1), dim3(nt), 0, s, scores, T, E, C, 1.f / tau, n_iter, assign, plan, caps)
+        if (ep == 8) MS_SK(8);
+        else if (ep == 16) MS_SK(16);
+        else if (ep == 32) MS_SK(32);
+        else MS_SK(64);
+#undef MS_SK
+        MS_HIP(hipGetLastError());
+        return copy_caps(caps, caps_host, E, s);
+    }
     if (epl <= 1) return run_epl<1>(scores, T, E, C, tau, n_iter, assign, plan, caps_host, ws, s);
     if (epl <= 2) return run_epl<2>(scores, T, E, C, tau, n_iter, assign, plan, caps_host, ws, s);
     if (epl <= 4) return run_epl<4>(scores, T, E, C, tau, n_iter, assign, plan, caps_host, ws, s);
