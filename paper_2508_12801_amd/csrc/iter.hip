@@ -16,9 +16,11 @@
 // Rounds are enqueued two ahead of the one that runs; the first round without proposals ends them, and what is still
 // queued leaves at once.  Both kernels are bound by latency (some 5 us each; 44032 tokens, 64 experts, top-2: nine rounds in
 // 0.12 ms, with six launches and a wait for the host every other round 0.5 ms).
+#include <algorithm>
 #include <climits>
 
 #include "common.h"
+#include "row_keys.h"
 
 namespace maxscore {
 namespace {
@@ -29,7 +31,7 @@ struct IterState {
     int pad;
 };
 
-constexpr int kIterRows = 64;
+constexpr int kIterRows = 64, kScanThreads = 1024;
 constexpr int kIterWordProgress = 1, kIterWordFlow = 2, kIterWordRounds = 3, kIterWordOpen = 10, kIterWordTotal = 8;
 
 // Tables of the rounds, in the workspace (WorkspaceLayout::price_off).
@@ -130,11 +132,7 @@ __device__ __forceinline__ unsigned long long same_expert(int e, int ebits)
 template <int G>
 __device__ __forceinline__ int group_max(int v)
 {
-    for (int off = 1; off < G; off <<= 1) {
-        const int o = __shfl_xor(v, off);
-        v = o > v ? o : v;
-    }
-    return v;
+    return (int)(~group_min_u32<G>(~((unsigned)v ^ 0x80000000u)) ^ 0x80000000u);
 }
 
 __global__ __launch_bounds__(1024) void k_iter_init(IterArea *ar)
@@ -232,7 +230,10 @@ __global__ __launch_bounds__(256) void k_iter_step(IterArgs a, int r, int last)
         }
         return;
     }
-    for (int e = tid; e < E; e += 256) s_room[e] = a.C - ar->load[r & 1][e];
+    for (int e = tid; e < E; e += 256) {
+        s_room[e] = a.C - ar->load[r & 1][e];
+        s_num[e] = 0;                              // now: proposals of this block
+    }
     for (int i = tid; i < kIterRows * k; i += 256) s_prop[i] = -1;
     if (wv == 0) {                                 // the rows that have holes
         bool hole = false;
@@ -245,32 +246,50 @@ __global__ __launch_bounds__(256) void k_iter_step(IterArgs a, int r, int last)
     __syncthreads();
     const int lg = tid & (G - 1), grp = tid / G, nq = s_nq;
     const bool vec = EPL >= 4 && (E & 3) == 0 && ((size_t)a.q & 15) == 0;
-    auto col = [&](int m) { return EPL >= 4 ? (m >> 2) * (4 * G) + lg * 4 + (m & 3) : lg * EPL + m; };
+    using RK = RowKeys<G, EPL>;
+    auto col = [&](int m) { return RK::col(m, lg); };
     unsigned roomy = 0;
 #pragma unroll
     for (int m = 0; m < EPL; ++m)
         if (col(m) < E && s_room[col(m)] > 0) roomy |= 1u << m;
+    const int ib = a.ebits > 0 ? a.ebits : 1;
     for (int i = grp; i < nq; i += 256 / G) {
         const int lr = s_queue[i];
         const int32_t *qr = a.q + (size_t)(row0 + lr) * E;
         int v[EPL];
-        if (vec) {
-#pragma unroll
-            for (int m = 0; m < EPL; m += 4) {
-                const int4 t4 = col(m) < E ? *(const int4 *)(qr + col(m)) : make_int4(0, 0, 0, 0);
-                v[m] = t4.x;
-                if constexpr (EPL >= 4) { v[m + 1] = t4.y; v[m + 2] = t4.z; v[m + 3] = t4.w; }
-            }
-        } else {
-#pragma unroll
-            for (int m = 0; m < EPL; ++m) v[m] = col(m) < E ? qr[col(m)] : 0;
-        }
+        RK::load(qr, E, vec, lg, v);
         unsigned live = roomy;
         for (int s = 0; s < k; ++s) {
             const int e = s_slot[lr * k + s];
             if (e < 0) continue;
             const int l = EPL >= 4 ? (e >> 2) & (G - 1) : e / EPL, m = EPL >= 4 ? e / (4 * G) * 4 + (e & 3) : e % EPL;
             if (l == lg) live &= ~(1u << m);
+        }
+        // rewards that span less than 2^(32 - ib), as those of scores do: packed with their columns, lower experts first
+        int lo = INT_MAX, hi = INT_MIN;
+#pragma unroll
+        for (int m = 0; m < EPL; ++m)
+            if ((live >> m) & 1) {
+                lo = v[m] < lo ? v[m] : lo;
+                hi = v[m] > hi ? v[m] : hi;
+            }
+        lo = ~group_max<G>(~lo);
+        hi = group_max<G>(hi);
+        if (hi < lo) continue;                             // nobody to ask
+        if ((((unsigned)hi - (unsigned)lo + 1) >> (32 - ib)) == 0 && (unsigned)hi - (unsigned)lo != ~0u) {
+            const unsigned cmask = (1u << ib) - 1;
+            unsigned key[EPL];
+#pragma unroll
+            for (int m = 0; m < EPL; ++m)
+                key[m] = (live >> m) & 1 ? ((unsigned)v[m] - (unsigned)lo + 1) << ib | (cmask - (unsigned)col(m)) : 0u;
+            unsigned cur = RK::first(key);
+            for (int s = 0; s < k && cur != 0; ++s) {
+                if (s_slot[lr * k + s] >= 0) continue;
+                if (lg == 0) s_prop[s * kIterRows + lr] = (int)(cmask - (cur & cmask));
+                const unsigned next = RK::below(key, cur);
+                cur = next < cur ? next : 0u;              // (below the last one the search wraps around)
+            }
+            continue;
         }
         for (int s = 0; s < k; ++s) {
             if (s_slot[lr * k + s] >= 0) continue;
@@ -306,18 +325,21 @@ __global__ __launch_bounds__(256) void k_iter_step(IterArgs a, int r, int last)
         if (e >= 0 && lane == __ffsll((long long)same) - 1) {
             const int n = __popcll(same);
             cnt[e] = n;
-            atomicAdd(&ar->tot[w & 7][e], n);
+            atomicAdd(&s_num[e], n);
         }
         wave_lds_sync();
         for (int x = lane; x < E; x += 64) a.tiles[tile * E + x] = cnt[x];
         wave_lds_sync();
     }
+    __syncthreads();
+    for (int e = tid; e < E; e += 256)
+        if (s_num[e]) atomicAdd(&ar->tot[w & 7][e], s_num[e]);
 }
 
-__global__ __launch_bounds__(256) void k_iter_scan(IterArgs a, int r, int last, int max_rounds, int *host)
+__global__ __launch_bounds__(kScanThreads) void k_iter_scan(IterArgs a, int r, int last, int max_rounds, int *host)
 {
-    __shared__ int s_w[4];
-    __shared__ long long s_sum[4];
+    __shared__ int s_w[kScanThreads / 64];
+    __shared__ long long s_sum[kScanThreads / 64];
     IterArea *ar = a.ar;
     const int e = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int phase = iter_phase(ar, r);
@@ -326,7 +348,7 @@ __global__ __launch_bounds__(256) void k_iter_scan(IterArgs a, int r, int last, 
         if (e != 0) return;
         long long sum = 0;
         int flow = 0;
-        for (int i = tid; i < a.n_wg; i += 256) {
+        for (int i = tid; i < a.n_wg; i += blockDim.x) {
             sum += a.bsum[i];
             flow += a.bflow[i];
         }
@@ -340,8 +362,14 @@ __global__ __launch_bounds__(256) void k_iter_scan(IterArgs a, int r, int last, 
         }
         __syncthreads();
         if (tid == 0) {
-            *(volatile long long *)(host + kIterWordTotal) = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
-            ((volatile int *)host)[kIterWordFlow] = s_w[0] + s_w[1] + s_w[2] + s_w[3];
+            sum = 0;
+            flow = 0;
+            for (int x = 0; x < (int)blockDim.x >> 6; ++x) {
+                sum += s_sum[x];
+                flow += s_w[x];
+            }
+            *(volatile long long *)(host + kIterWordTotal) = sum;
+            ((volatile int *)host)[kIterWordFlow] = flow;
             ((volatile int *)host)[kIterWordRounds] = phase == 1 ? (r >= 2 ? r - 2 : 0) : r - 1;
             ((volatile int *)host)[kIterWordOpen] = phase == 2 && max_rounds > 0;
             __threadfence_system();
@@ -362,27 +390,37 @@ __global__ __launch_bounds__(256) void k_iter_scan(IterArgs a, int r, int last, 
         if (e == 0) ((volatile int *)host)[kIterWordProgress] = r + 1;
     }
     if (c <= room || room <= 0) return;
-    const int n = a.k * a.n_wg, per = (n + 255) / 256, t0 = tid * per, t1 = t0 + per < n ? t0 + per : n;
-    int sum = 0;
-#pragma unroll 4
-    for (int t = t0; t < t1; ++t) sum += a.any[t] ? a.tiles[(size_t)t * a.E + e] : 0;
-    int inc = sum;
-    for (int off = 1; off < 64; off <<= 1) {
-        const int o = __shfl_up(inc, off);
-        if (lane >= off) inc += o;
-    }
-    if (lane == 63) s_w[wv] = inc;
-    __syncthreads();
-    int run = inc - sum;
-    for (int v = 0; v < wv; ++v) run += s_w[v];
-    if (sum == 0) return;
-#pragma unroll 4
-    for (int t = t0; t < t1; ++t)
-        if (a.any[t]) {
-            const int x = a.tiles[(size_t)t * a.E + e];
-            a.tiles[(size_t)t * a.E + e] = run;
-            run += x;
+    // eight tiles per thread and step, all on their way together
+    const int n = a.k * a.n_wg;
+    int before = 0;
+    for (int b0 = 0; b0 < n; b0 += 8 * blockDim.x) {
+        const int t0 = b0 + 8 * tid;
+        int x[8], sum = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = t0 + i < n ? a.any[t0 + i] : 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = x[i] ? a.tiles[(size_t)(t0 + i) * a.E + e] : 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) sum += x[i];
+        int inc = sum;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(inc, off);
+            if (lane >= off) inc += o;
         }
+        if (lane == 63) s_w[wv] = inc;
+        __syncthreads();
+        int run = before + inc - sum;
+        for (int v = 0; v < (int)blockDim.x >> 6; ++v) {
+            if (v < wv) run += s_w[v];
+            before += s_w[v];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if (x[i]) a.tiles[(size_t)(t0 + i) * a.E + e] = run;
+            run += x[i];
+        }
+    }
 }
 
 __global__ __launch_bounds__(256) void k_iter_total(const int32_t *__restrict__ q, const int32_t *__restrict__ assign,
@@ -489,6 +527,7 @@ int32_t iter_run(const int32_t *q, int T, int E, int k, int C, int max_rounds, i
     while (G * 16 < E) G *= 2;
     while (G * EPL < E) EPL *= 2;
     const size_t shm = sizeof(int) * ((size_t)2 * kIterRows * k + 6 * (size_t)E);
+    const int threads = std::min(kScanThreads, std::max(64, (k * a.n_wg + 511) / 512 * 64));     // eight tiles each
     hipLaunchKernelGGL(k_iter_init, dim3(1), dim3(1024), 0, s, a.ar);
     for (int r = 0; !hw[0]; ++r) {
         const int last = r > max_rounds ? 1 : 0;
@@ -503,7 +542,7 @@ int32_t iter_run(const int32_t *q, int T, int E, int k, int C, int max_rounds, i
         else if (G == 32) MS_I(32, 16);
         else MS_I(64, 16);
 #undef MS_I
-        hipLaunchKernelGGL(k_iter_scan, dim3(E), dim3(256), 0, s, a, r, last, max_rounds, host_dev);
+        hipLaunchKernelGGL(k_iter_scan, dim3(E), dim3(threads), 0, s, a, r, last, max_rounds, host_dev);
         if (hipGetLastError() != hipSuccess) {
             (void)hipStreamSynchronize(s);
             return MAXSCORE_ERR_HIP;
