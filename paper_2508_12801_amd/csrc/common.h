@@ -108,9 +108,10 @@ int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore
 int32_t kvec_check(const int32_t *kvec, int T, int E, int k, char *ws, long long *demand, hipStream_t s);
 // --- price.hip
 // Exact assignment by equilibrium prices and shortest augmenting paths: everything is enqueued at once, the outcome is
-// left in the pinned host state (fin == 2: certified; 1: not, but another try from the prices reached may do it (retry);
-// anything else: the auction has to solve the problem).  k < E <= kPriceMaxE, one capacity for all experts, any relation of demand and capacity (rows that
-// cannot be filled end in -1).
+// left in the pinned host state (fin == 2: certified; 1: not, but another try from the prices reached and with more
+// exchanges may do it, retry > 0 counts these; anything else: the auction has to solve the problem).
+// k <= E <= kPriceMaxE, one capacity for all experts, any relation of demand and capacity (rows that cannot be filled
+// end in -1).
 constexpr int kPriceMaxE = 512;
 struct PriceGeometry {
     int rows, n_wg;          // blocks of rows over which the pairs are counted (WorkspaceLayout::wcnt_off)
@@ -125,7 +126,7 @@ inline size_t price_area_bytes(int T, int E, int k, int max_wg)
 }
 // Pinned words of the calling thread (16 of them, cleared by whoever uses them), and the same as the device sees them.
 int32_t solver_words(int **host, int **dev);
-int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_t *prices_in, bool retry,
+int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_t *prices_in, int retry,
                       int32_t *assign, int64_t *prices, int64_t *price_scale, char *ws, SolverState *host_state_dev, PriceGeometry *geom, hipStream_t s);
 // Runs price_enqueue and the caller's work behind it and waits.  *solved: whether the result stands.
 int32_t price_run(const int32_t *q, int T, int E, int k, int C, const maxscore_opts &o, int32_t *assign, int64_t *prices,

@@ -60,8 +60,9 @@ constexpr int kFirstWindow = 1 << 22;             // margins of the first pass: 
 constexpr int kSampleRows = 8192;
 constexpr int kArcsPerExpert = 16, kArcsWanted = 4500, kArcsMost = 5500;
 constexpr int kMaxBound = (1 << 21) - 1;
-constexpr int kAllArcs = 7000;                    // problems with this few exchanges in all are searched with all of them
-constexpr int kEnough = 8, kWorst = 2;            // the passes end when an eighth of a token per expert is too many, at
+constexpr int kAllArcs = 4000;                    // problems with this few exchanges in all are searched with all of them
+constexpr int kEnough = 3, kWorst = 2;            // the passes end when a third of a token per expert (a sixth
+                                                  // beyond 128, where searches take longer) is too many, at
                                                   // no expert more than two (its tokens leave one search at a time)
 constexpr int kLevelPairs = 4;                    // exchanges of a row that the common step looks at
 constexpr int kSmallEntries = 1 << 16;            // rewards of a batch that one workgroup passes over by itself
@@ -135,6 +136,19 @@ __device__ __forceinline__ int wave_sum(int v)        // inclusive prefix sum ov
     return v;
 }
 
+__device__ __forceinline__ int wave_max(int v)        // over the lanes, uniform
+{
+    constexpr int low = -0x7fffffff - 1;
+    int o;
+    o = __builtin_amdgcn_update_dpp(low, v, 0x111, 0xf, 0xf, false); v = o > v ? o : v;
+    o = __builtin_amdgcn_update_dpp(low, v, 0x112, 0xf, 0xf, false); v = o > v ? o : v;
+    o = __builtin_amdgcn_update_dpp(low, v, 0x114, 0xf, 0xf, false); v = o > v ? o : v;
+    o = __builtin_amdgcn_update_dpp(low, v, 0x118, 0xf, 0xf, false); v = o > v ? o : v;
+    o = __builtin_amdgcn_update_dpp(low, v, 0x142, 0xa, 0xf, false); v = o > v ? o : v;
+    o = __builtin_amdgcn_update_dpp(low, v, 0x143, 0xc, 0xf, false); v = o > v ? o : v;
+    return __builtin_amdgcn_readlane(v, 63);
+}
+
 __device__ __forceinline__ unsigned row_mask(int row, int ib)      // equal values are ranked by column XOR a mask of the row
 {
     return ((unsigned)row * 0x9E3779B1u) >> (32 - ib);
@@ -149,7 +163,7 @@ __device__ __forceinline__ unsigned row_mask(int row, int ib)      // equal valu
 struct StepLds {
     int was[kPStride], now[kPStride];
     int cum[64];
-    int n[kUThreads / 64], s[kUThreads / 64], x[kUThreads / 64], d[kUThreads / 64], pmin[kUThreads / 64];
+    int n[kUThreads / 64], s[kUThreads / 64], x[kUThreads / 64], d[kUThreads / 64], z[kUThreads / 64], o[kUThreads / 64], pmin[kUThreads / 64];
     int maxd, ran_out, lam, cap, worst;
 };
 
@@ -170,15 +184,18 @@ __device__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const Pric
         s.cap = 0x7fffffff;
     }
     __syncthreads();
-    int sn = 0, ss = 0, sx = 0, sd = 0, worst = 0;
+    int sn = 0, ss = 0, sx = 0, sd = 0, sz = 0, so = 0, worst = 0;
     for (int e = tid; e < E; e += kUThreads) {
         const int ne = s_hn[e];
         const bool in = all_in || s.was[e] > 0;
         sn += in ? ne : 0;
         ss += in ? 1 : 0;
         sx += ne > Ct ? ne - Ct : 0;
-        worst = ne - Ct > worst ? ne - Ct : worst;
+        const int off = in || ne > Ct ? (ne > Ct ? ne - Ct : Ct - ne) : 0;
+        worst = off > worst ? off : worst;
         sd += in && ne < Ct ? Ct - ne : 0;
+        sz += !in && ne > Ct ? ne - Ct : 0;
+        so += !in && ne > Ct ? 1 : 0;
     }
     // holds (0 .. nb-1) and newcomers (nb .. 2nb-1) per margin bin over all experts
     for (int b = wv; b < 2 * nb; b += NW) {
@@ -192,24 +209,33 @@ __device__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const Pric
     ss = wave_sum(ss);
     sx = wave_sum(sx);
     sd = wave_sum(sd);
+    sz = wave_sum(sz);
+    so = wave_sum(so);
     if (lane == 63) {
         s.n[wv] = sn;
         s.s[wv] = ss;
         s.x[wv] = sx;
         s.d[wv] = sd;
+        s.z[wv] = sz;
+        s.o[wv] = so;
     }
     __syncthreads();
-    sn = ss = sx = sd = 0;
+    sn = ss = sx = sd = sz = so = 0;
 #pragma unroll
     for (int x = 0; x < NW; ++x) {
         sn += s.n[x];
         ss += s.s[x];
         sx += s.x[x];
         sd += s.d[x];
+        sz += s.z[x];
+        so += s.o[x];
     }
     sx = sd > sx ? sd : sx;                                           // tokens too many or too few
     const int target = ss > 0 ? (2 * sn + ss) / (2 * ss) : Ct;        // mean demand of the experts that count
-    const int X = sn - Ct * ss;                                       // what the common step has to take away
+    // What the common step has to take away: what those that count have too many, and what those that are about to join them
+    // (price 0, too many tokens) have.  These also move by more than their own margins say, which take the others of
+    // their kind to stay, the more the more of them there are: with both, 10007 tokens of 96 experts and a tenth of spare capacity need two passes less.
+    const int X0 = sn - Ct * ss, X = X0 > 0 ? X0 + sz : X0;
     if (level && X < 0 && a.mode == kModeSlack) {
         // A common step down ends for an expert at price 0, and from there on that expert takes part in what the step
         // gains: the experts without a price at most treble in one step (its margins only know the present ones).
@@ -254,6 +280,7 @@ __device__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const Pric
         }
         if (common && side && a.mode == kModeSlack && d > s.cap) d = s.cap;
         else if (b == nb) s.ran_out = 1;
+        if (!in && !common && sx > E) d += (int)((float)d * fminf(0.7f, 2.f * (float)so / (float)E));
         d = d < 1 ? 1 : d;
         atomicMax(&s.maxd, d);
         if (common) s.lam = side ? -d : d;
@@ -286,7 +313,7 @@ __device__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const Pric
     m2.excess = sampled ? (int)((long long)sx * a.T / nrows) : sx;
     const bool listed = !a.retry || reach;               // another try needs more exchanges than the one before
     // enough: what is left is cheaper to move by the search, or it no longer shrinks (it ends up alternating by a few)
-    if (!sampled && !even && (s.maxd == 0 || (m2.excess * kEnough <= E && !s.worst && listed) || (listed && m2.excess <= E && m2.excess * 5 >= mt.excess * 4 && t >= a.even + 4))) {
+    if (!sampled && !even && (s.maxd == 0 || (m2.excess * (E <= 128 && !a.retry ? kEnough : 2 * kEnough) <= E && !s.worst && listed) || (listed && m2.excess <= E && m2.excess * 5 >= mt.excess * 4 && t >= a.even + 4))) {
         m2.done = 1;
         m2.w = mt.w;
         if (m2.excess == 0) m2.bound = 2;                // nothing to move
@@ -1071,6 +1098,12 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
                     const int e = __builtin_amdgcn_readlane(hy, sl);
                     if (e >= 0 && (e & 63) == lane) heldm |= 1u << (e >> 6);
                 }
+                // only slots near the best expert the token does not hold have exchanges under the bound
+                int best = os ? 0 : -0x7fffffff;
+#pragma unroll
+                for (int m = 0; m < TEPL; ++m)
+                    if (lane + 64 * m < E && !((heldm >> m) & 1u)) best = v[m] > best ? v[m] : best;
+                best = wave_max(best);
                 int n_real = 0;
                 for (int sl = 0; sl < k; ++sl) {
                     const int e = __builtin_amdgcn_readlane(hy, sl);
@@ -1080,6 +1113,7 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
 #pragma unroll
                     for (int m = 1; m < TEPL; ++m) x = (e >> 6) == m ? v[m] : x;
                     const int vh = __builtin_amdgcn_readlane(x, e & 63);
+                    if (vh - best >= B) continue;
 #pragma unroll
                     for (int m = 0; m < TEPL; ++m)
                         put(lane + 64 * m < E && !((heldm >> m) & 1u) && vh - v[m] < B, vh - v[m], e, lane + 64 * m);
@@ -1218,15 +1252,6 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
         const int shift = slack ? -s.pi[E] : pmin;
         for (int e = tid; e < E; e += kFThreads) prices[e] = (int64_t)(s.p[e] - s.pi[e] - shift) << sb;
     }
-    if (solved && !certified) {
-        // exact for the arcs that were listed: a good start for another try with more of them
-        const int plim = (1 << (31 - a.ib)) - 1, shift = slack ? -s.pi[E] : os ? -s.pi[E] : pmin;
-        for (int e = tid; e < E; e += kFThreads) {
-            int p = s.p[e] - s.pi[e] - shift;
-            p = slack && p < 0 ? 0 : p;
-            ar->prices[e] = p > plim ? plim : (p < -plim ? -plim : p);
-        }
-    }
     long long sum = 0;
     for (int w2 = tid; w2 < a.n_wg; w2 += kFThreads) sum += a.wg_sum[w2];
     if (sum) atomicAdd((unsigned long long *)&s.dsum, (unsigned long long)sum);
@@ -1288,7 +1313,7 @@ bool price_supported(int T, int E, int k)
     return price_shape(T, E, k, G, EPL, rows, n_wg);
 }
 
-int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_t *prices_in, bool retry, int32_t *assign, int64_t *prices,
+int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_t *prices_in, int retry, int32_t *assign, int64_t *prices,
                       int64_t *price_scale, char *ws, SolverState *host_state_dev, PriceGeometry *geom, hipStream_t s)
 {
     WorkspaceLayout L = workspace_layout(T, E, k);
@@ -1311,8 +1336,8 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     const int n_sampled = stride >= 2 && !prices_in && !retry ? 2 : 0;
     a.even = spare > 0 && spare * 64 <= (long long)E * C && !prices_in && !retry ? (n_sampled ? 4 : 3) : 0;
     a.arcs_wanted = std::min(kArcsPerExpert * E, kArcsWanted);
-    a.retry = retry ? 1 : 0;
-    if (retry) a.arcs_wanted = std::min(2 * a.arcs_wanted, kArcsMost);
+    a.retry = retry > 0 ? 1 : 0;
+    if (retry) a.arcs_wanted = std::min((1 + retry) * a.arcs_wanted, kArcsMost);
     a.ib = 1;
     while ((1 << a.ib) < E) ++a.ib;
     a.nb = E <= 256 ? kPBins : kPBins / 2;
@@ -1332,7 +1357,7 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     const bool small = (long long)T * G <= kSmallThreads && (long long)T * E <= kSmallEntries && shm + sizeof(StepLds) <= 64 * 1024;
     const int plim = (1 << (31 - a.ib)) - 1;
     if (!small)
-        hipLaunchKernelGGL(k_price_init, dim3(64), dim3(kPThreads), 0, s, a.ar, (2 * a.nb + 1) * a.es / 4, E, plim, prices_in, retry ? 1 : 0);
+        hipLaunchKernelGGL(k_price_init, dim3(64), dim3(kPThreads), 0, s, a.ar, (2 * a.nb + 1) * a.es / 4, E, plim, prices_in, a.retry);
     for (int t = small ? n_pass : 0; t <= n_pass; ++t) {
         const bool fin = t == n_pass;
         const int st = t < n_sampled ? stride : 1;

@@ -1883,7 +1883,7 @@ int32_t price_run(const int32_t *q, int T, int E, int k, int C, const maxscore_o
     SolverState h;
     for (int attempt = 0;; ++attempt) {
         hs->state->fin = 0;
-        rc = price_enqueue(q, T, E, k, C, o.prices_in, attempt > 0, assign, prices, price_scale, ws, hs->state_dev, &pg, s);
+        rc = price_enqueue(q, T, E, k, C, o.prices_in, attempt, assign, prices, price_scale, ws, hs->state_dev, &pg, s);
         if (rc == MAXSCORE_OK && after) {
             const SolverGeometry g = {pg.rows, pg.n_wg, 0, 1, &hs->state_dev->t_after};
             rc = after(after_ctx, g, s, nullptr);
