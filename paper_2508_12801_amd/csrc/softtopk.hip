@@ -19,7 +19,7 @@
 namespace maxscore {
 namespace {
 
-// A group of G lanes owns one row.  Vector path (E == G*EPL): lane l owns the 4-column pieces l, l+G, l+2G, ...
+// A group of G lanes owns one row.  Vector path (E a multiple of 4): lane l owns the 4-column pieces l, l+G, l+2G, ...
 // of the row, so each 16-byte load instruction of a wavefront covers whole 128-byte lines of 64/G consecutive
 // rows.  Scalar path: lane l owns the EPL consecutive columns l*EPL .. l*EPL+EPL-1.
 template <int G, int EPL, bool VEC>
@@ -37,7 +37,8 @@ __global__ __launch_bounds__(256) void k_softtopk(const float *__restrict__ logi
         if (kVec) {
 #pragma unroll
             for (int m = 0; m < EPL; m += 4) {
-                float4 v4 = *(const float4 *)(logits + (size_t)row * E + colof(m));
+                const float4 v4 = colof(m) < E ? *(const float4 *)(logits + (size_t)row * E + colof(m))
+                                               : make_float4(-3.4e38f, -3.4e38f, -3.4e38f, -3.4e38f);
                 x[m] = v4.x; x[m + 1] = v4.y; x[m + 2] = v4.z; x[m + 3] = v4.w;
             }
         } else {
@@ -51,6 +52,7 @@ __global__ __launch_bounds__(256) void k_softtopk(const float *__restrict__ logi
         if (kVec) {
 #pragma unroll
             for (int m = 0; m < EPL; m += 4) {
+                if (colof(m) >= E) continue;
                 const size_t o = (size_t)row * E + colof(m);
                 if (scores) *(float4 *)(scores + o) = make_float4(sc[m], sc[m + 1], sc[m + 2], sc[m + 3]);
                 if (q) *(int4 *)(q + o) = make_int4(qq[m], qq[m + 1], qq[m + 2], qq[m + 3]);
@@ -106,7 +108,7 @@ int32_t softtopk_run(const float *logits, int T, int E, int k, float t, int shif
     int grid = (T + ngrp - 1) / ngrp;
     if (grid > 4096) grid = 4096;
     const float qscale = (float)(1 << shift);
-    const bool vec = (E == G * EPL) && EPL >= 4 &&
+    const bool vec = E % 4 == 0 && EPL >= 4 &&
                      ((((uintptr_t)logits) | ((uintptr_t)scores) | ((uintptr_t)q)) % 16 == 0);
 #define MS_ST2(GG, PP)                                                                                              \
     do {                                                                                                            \

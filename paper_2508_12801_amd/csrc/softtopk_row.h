@@ -6,6 +6,7 @@
 #pragma once
 
 #include "common.h"
+#include "row_keys.h"
 
 namespace maxscore {
 
@@ -24,6 +25,39 @@ __device__ __forceinline__ unsigned ord_f32(float x)
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// maximum and sum over a group of G lanes, left in all of them
+template <int G>
+__device__ __forceinline__ float max_of_group(float v)
+{
+    v = fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xf, 0xf, true)));     // quad_perm [1,0,3,2]
+    v = fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xf, 0xf, true)));     // quad_perm [2,3,0,1]
+    v = fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x141, 0xf, 0xf, true)));    // row_half_mirror
+    if constexpr (G >= 16) v = fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x140, 0xf, 0xf, true)));   // row_mirror
+    if constexpr (G >= 32) v = fmaxf(v, __shfl_xor(v, 16));
+    if constexpr (G >= 64) v = fmaxf(v, __shfl_xor(v, 32));
+    return v;
+}
+__device__ __forceinline__ int dpp_bits(float v) { return __float_as_int(v); }
+__device__ __forceinline__ int dpp_bits(int v) { return v; }
+template <typename V>
+__device__ __forceinline__ V dpp_value(int v)
+{
+    if constexpr (sizeof(V) == 4 && V(0.5f) != V(0)) return __int_as_float(v);
+    else return v;
+}
+template <int G, typename V>
+__device__ __forceinline__ V sum_of_group(V v)
+{
+    static_assert(G >= 8, "groups of 8 lanes at least");
+    v += dpp_value<V>(__builtin_amdgcn_mov_dpp(dpp_bits(v), 0xB1, 0xf, 0xf, true));
+    v += dpp_value<V>(__builtin_amdgcn_mov_dpp(dpp_bits(v), 0x4E, 0xf, 0xf, true));
+    v += dpp_value<V>(__builtin_amdgcn_mov_dpp(dpp_bits(v), 0x141, 0xf, 0xf, true));
+    if constexpr (G >= 16) v += dpp_value<V>(__builtin_amdgcn_mov_dpp(dpp_bits(v), 0x140, 0xf, 0xf, true));
+    if constexpr (G >= 32) v += __shfl_xor(v, 16);
+    if constexpr (G >= 64) v += __shfl_xor(v, 32);
+    return v;
+}
+
 // x: this lane's logits of the row (columns at or beyond E must hold -3.4e38f); sc, qq: its scores and rewards.
 template <int G, int EPL, bool kVec>
 __device__ __forceinline__ void softtopk_row(const float (&x)[EPL], int lg, int E, int k, float t, float qscale,
@@ -33,8 +67,11 @@ __device__ __forceinline__ void softtopk_row(const float (&x)[EPL], int lg, int 
     float mx = -3.4e38f;
 #pragma unroll
     for (int m = 0; m < EPL; ++m) mx = fmaxf(mx, x[m]);
+    unsigned key[EPL];                 // order of the logits; columns the row does not have come last
 #pragma unroll
-    for (int off = G / 2; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+    for (int m = 0; m < EPL; ++m) key[m] = colof(m) < E ? ord_f32(x[m]) : 0u;
+    unsigned cur = RowKeys<G, EPL>::first(key);
+    mx = max_of_group<G>(mx);
     float ex[EPL];
     float sum = 0.f;
 #pragma unroll
@@ -44,17 +81,47 @@ __device__ __forceinline__ void softtopk_row(const float (&x)[EPL], int lg, int 
         ex[m] = (colof(m) < E) ? __expf(x[m] - mx) : 0.f;
         sum += ex[m];
     }
-#pragma unroll
-    for (int off = G / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+    sum = sum_of_group<G>(sum);
     const float inv = 1.0f / sum;
 
-    // the largest entries one by one (equal logits: lower column first), each with the weight of its rank; the
-    // entries that are never picked share the weight of the ranks beyond
+    // Entries among the n_pick largest weigh by their rank, the others share the weight of the ranks beyond.  Where no two
+    // of the largest are equal the rank is the number of values above: one subtraction and minimum per entry find the next
+    // value, one comparison and addition count it.
     const int n_pick = (reading == MAXSCORE_SOFTTOPK_A1 || reading == MAXSCORE_SOFTTOPK_B) ? k : k - 1;
     float wv[EPL];
     float w_run = 0.f;                 // reading C: the weight of the rank being picked
     unsigned taken = 0;
-    if (t != 0.f) {
+    bool counted = false;
+    if (t != 0.f && reading != MAXSCORE_SOFTTOPK_C) {
+        int above[EPL];
+#pragma unroll
+        for (int m = 0; m < EPL; ++m) above[m] = 0;
+        bool distinct = true;
+        for (int r = 1; r <= n_pick; ++r) {
+#pragma unroll
+            for (int m = 0; m < EPL; ++m) above[m] += key[m] < cur ? 1 : 0;
+            if (r < n_pick) {
+                const unsigned next = RowKeys<G, EPL>::below(key, cur);
+                distinct = distinct && next < cur && next != 0u;
+                cur = next;
+            }
+        }
+        int picked = 0;
+#pragma unroll
+        for (int m = 0; m < EPL; ++m) picked += above[m] < n_pick ? 1 : 0;
+        picked = sum_of_group<G>(picked);
+        counted = distinct && picked == n_pick;
+        if (counted) {
+#pragma unroll
+            for (int m = 0; m < EPL; ++m) {
+                wv[m] = reading == MAXSCORE_SOFTTOPK_B && above[m] < n_pick ? 0.f : (float)above[m];
+                if (reading == MAXSCORE_SOFTTOPK_B && above[m] >= n_pick) wv[m] = (float)(k - 1);
+            }
+            taken = ~0u;
+        }
+    }
+    // Equal logits among the largest (lower column first), and reading C: one by one.
+    if (t != 0.f && !counted) {
         for (int r = 1; r <= n_pick; ++r) {
             unsigned bo = 0;
             int bm = -1;
