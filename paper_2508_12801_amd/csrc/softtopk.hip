@@ -19,13 +19,14 @@
 namespace maxscore {
 namespace {
 
-// A group of G lanes owns one row.  Vector path (E a multiple of 4): lane l owns the 4-column pieces l, l+G, l+2G, ...
+// A group of G lanes owns one row.  Vector path (E == G*EPL): lane l owns the 4-column pieces l, l+G, l+2G, ...
 // of the row, so each 16-byte load instruction of a wavefront covers whole 128-byte lines of 64/G consecutive
-// rows.  Scalar path: lane l owns the EPL consecutive columns l*EPL .. l*EPL+EPL-1.
+// rows.  Else lane l owns the EPL consecutive columns l*EPL .. l*EPL+EPL-1, read four at a time where `quads` says that E is a
+// multiple of 4 and all is aligned.  (Which lane adds up which columns decides the last bit of the scores.)
 template <int G, int EPL, bool VEC>
 __global__ __launch_bounds__(256) void k_softtopk(const float *__restrict__ logits, int T, int E, int k, float t,
                                                   float qscale, float *__restrict__ scores,
-                                                  int32_t *__restrict__ q, int reading)
+                                                  int32_t *__restrict__ q, int reading, bool quads)
 {
     const int tid = threadIdx.x, lane = tid & 63, lg = lane & (G - 1);
     const int grp = tid / G, ngrp = 256 / G;
@@ -37,8 +38,13 @@ __global__ __launch_bounds__(256) void k_softtopk(const float *__restrict__ logi
         if (kVec) {
 #pragma unroll
             for (int m = 0; m < EPL; m += 4) {
-                const float4 v4 = colof(m) < E ? *(const float4 *)(logits + (size_t)row * E + colof(m))
-                                               : make_float4(-3.4e38f, -3.4e38f, -3.4e38f, -3.4e38f);
+                const float4 v4 = *(const float4 *)(logits + (size_t)row * E + colof(m));
+                x[m] = v4.x; x[m + 1] = v4.y; x[m + 2] = v4.z; x[m + 3] = v4.w;
+            }
+        } else if (EPL >= 4 && quads) {
+#pragma unroll
+            for (int m = 0; m + 3 < EPL; m += 4) {
+                const float4 v4 = lg * EPL + m < E ? *(const float4 *)(lr + m) : make_float4(-3.4e38f, -3.4e38f, -3.4e38f, -3.4e38f);
                 x[m] = v4.x; x[m + 1] = v4.y; x[m + 2] = v4.z; x[m + 3] = v4.w;
             }
         } else {
@@ -52,10 +58,16 @@ __global__ __launch_bounds__(256) void k_softtopk(const float *__restrict__ logi
         if (kVec) {
 #pragma unroll
             for (int m = 0; m < EPL; m += 4) {
-                if (colof(m) >= E) continue;
                 const size_t o = (size_t)row * E + colof(m);
                 if (scores) *(float4 *)(scores + o) = make_float4(sc[m], sc[m + 1], sc[m + 2], sc[m + 3]);
                 if (q) *(int4 *)(q + o) = make_int4(qq[m], qq[m + 1], qq[m + 2], qq[m + 3]);
+            }
+        } else if (EPL >= 4 && quads) {
+#pragma unroll
+            for (int m = 0; m + 3 < EPL; m += 4) {
+                if (lg * EPL + m >= E) continue;
+                if (scores) *(float4 *)(scores + o0 + m) = make_float4(sc[m], sc[m + 1], sc[m + 2], sc[m + 3]);
+                if (q) *(int4 *)(q + o0 + m) = make_int4(qq[m], qq[m + 1], qq[m + 2], qq[m + 3]);
             }
         } else {
 #pragma unroll
@@ -108,16 +120,16 @@ int32_t softtopk_run(const float *logits, int T, int E, int k, float t, int shif
     int grid = (T + ngrp - 1) / ngrp;
     if (grid > 4096) grid = 4096;
     const float qscale = (float)(1 << shift);
-    const bool vec = E % 4 == 0 && EPL >= 4 &&
-                     ((((uintptr_t)logits) | ((uintptr_t)scores) | ((uintptr_t)q)) % 16 == 0);
+    const bool quads = E % 4 == 0 && ((((uintptr_t)logits) | ((uintptr_t)scores) | ((uintptr_t)q)) % 16 == 0);
+    const bool vec = quads && E == G * EPL && EPL >= 4;
 #define MS_ST2(GG, PP)                                                                                              \
     do {                                                                                                            \
         if (vec)                                                                                                    \
             hipLaunchKernelGGL((k_softtopk<GG, PP, true>), dim3(grid), dim3(256), 0, s, logits, T, E, k, t, qscale, \
-                               scores, q, reading);                                                                 \
+                               scores, q, reading, quads); \
         else                                                                                                        \
             hipLaunchKernelGGL((k_softtopk<GG, PP, false>), dim3(grid), dim3(256), 0, s, logits, T, E, k, t,        \
-                               qscale, scores, q, reading);                                                         \
+                               qscale, scores, q, reading, quads); \
     } while (0)
 #define MS_ST(GG)                    \
     do {                             \

@@ -45,16 +45,23 @@ __device__ __forceinline__ V dpp_value(int v)
     if constexpr (sizeof(V) == 4 && V(0.5f) != V(0)) return __int_as_float(v);
     else return v;
 }
+// (adds the value of the lane G/2 away, then of the one G/4 away and so on: after a step all values repeat with its distance,
+// and a rotation brings the same one as an exchange)
 template <int G, typename V>
 __device__ __forceinline__ V sum_of_group(V v)
 {
     static_assert(G >= 8, "groups of 8 lanes at least");
-    v += dpp_value<V>(__builtin_amdgcn_mov_dpp(dpp_bits(v), 0xB1, 0xf, 0xf, true));
-    v += dpp_value<V>(__builtin_amdgcn_mov_dpp(dpp_bits(v), 0x4E, 0xf, 0xf, true));
-    v += dpp_value<V>(__builtin_amdgcn_mov_dpp(dpp_bits(v), 0x141, 0xf, 0xf, true));
-    if constexpr (G >= 16) v += dpp_value<V>(__builtin_amdgcn_mov_dpp(dpp_bits(v), 0x140, 0xf, 0xf, true));
-    if constexpr (G >= 32) v += __shfl_xor(v, 16);
     if constexpr (G >= 64) v += __shfl_xor(v, 32);
+    if constexpr (G >= 32) v += __shfl_xor(v, 16);
+    if constexpr (G >= 16) {
+        v += dpp_value<V>(__builtin_amdgcn_mov_dpp(dpp_bits(v), 0x128, 0xf, 0xf, true));                 // row_ror:8
+        v += dpp_value<V>(__builtin_amdgcn_mov_dpp(dpp_bits(v), 0x124, 0xf, 0xf, true));                 // row_ror:4
+    } else {
+        const int from_above = __builtin_amdgcn_update_dpp(0, dpp_bits(v), 0x104, 0xf, 0x5, false);      // row_shl:4, lanes 0-3 and 8-11
+        v += dpp_value<V>(__builtin_amdgcn_update_dpp(from_above, dpp_bits(v), 0x114, 0xf, 0xa, false)); // row_shr:4, the others
+    }
+    v += dpp_value<V>(__builtin_amdgcn_mov_dpp(dpp_bits(v), 0x4E, 0xf, 0xf, true));                      // quad_perm [2,3,0,1]
+    v += dpp_value<V>(__builtin_amdgcn_mov_dpp(dpp_bits(v), 0xB1, 0xf, 0xf, true));                      // quad_perm [1,0,3,2]
     return v;
 }
 
