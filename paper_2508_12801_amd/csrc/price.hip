@@ -69,6 +69,7 @@ constexpr int kSmallEntries = 1 << 16;            // rewards of a batch that one
 constexpr int kSmallThreads = 4096;               // ... with this many lanes at work in all
 constexpr int kSmallPasses = 20;
 constexpr int kPRowsMax = 128;                    // rows of a block of the final pass at most
+constexpr int kPriceWordDone = 0, kPriceWordPasses = 1;      // pinned words of the calling thread
 enum { kModeTight = 0, kModeSlack = 1, kModeOver = 2 };
 
 struct PriceMeta {
@@ -160,18 +161,23 @@ __device__ __forceinline__ unsigned row_mask(int row, int ib)      // equal valu
 // common mean demand one by one, and all together by the step that brings the mean to the capacity: raising them all
 // displaces tokens only to the experts outside, which the single steps do not see.  Column E of the histograms holds
 // the margins of that common step.
+//
+// Bound by latency, and by what the sixteen wavefronts do alike (four of them share a SIMD): sums are taken over the
+// wavefronts that have experts only, and the bound of the arc list is worked out by the last one beside the columns.
 struct StepLds {
-    int was[kPStride], now[kPStride];
+    __attribute__((aligned(16))) int was[kPStride], now[kPStride];
     int cum[64];
-    int n[kUThreads / 64], s[kUThreads / 64], x[kUThreads / 64], d[kUThreads / 64], z[kUThreads / 64], o[kUThreads / 64], pmin[kUThreads / 64];
-    int maxd, ran_out, lam, cap, worst;
+    __attribute__((aligned(16))) int part[kPriceMaxE / 64][8];      // sums of the wavefronts that have experts
+    int pmin[kUThreads / 64];
+    int maxd, ran_out, lam, cap, worst, bound, wide, reach;
 };
 
 __device__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const PriceMeta mt, const int *s_h, StepLds &s)
 {
     constexpr int NW = kUThreads / 64;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int E = a.E, ES = a.es, nb = a.nb;
+    static_assert(kPriceMaxE / 64 < NW - 1, "the last wavefront has no experts");
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int E = a.E, ES = a.es, nb = a.nb, nwe = (E + 63) >> 6;
     const bool even = a.mode == kModeSlack && t < a.even;
     const bool all_in = a.mode != kModeSlack || even, level = a.mode == kModeOver || (a.mode == kModeSlack && !even);
     const bool sampled = nrows < a.T;
@@ -184,18 +190,16 @@ __device__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const Pric
         s.cap = 0x7fffffff;
     }
     __syncthreads();
-    int sn = 0, ss = 0, sx = 0, sd = 0, sz = 0, so = 0, worst = 0;
-    for (int e = tid; e < E; e += kUThreads) {
-        const int ne = s_hn[e];
-        const bool in = all_in || s.was[e] > 0;
-        sn += in ? ne : 0;
-        ss += in ? 1 : 0;
-        sx += ne > Ct ? ne - Ct : 0;
-        const int off = in || ne > Ct ? (ne > Ct ? ne - Ct : Ct - ne) : 0;
-        worst = off > worst ? off : worst;
-        sd += in && ne < Ct ? Ct - ne : 0;
-        sz += !in && ne > Ct ? ne - Ct : 0;
-        so += !in && ne > Ct ? 1 : 0;
+    if (wv < nwe) {
+        const int ne = tid < E ? s_hn[tid] : 0, over = tid < E && ne > Ct ? ne - Ct : 0;
+        const bool in = tid < E && (all_in || s.was[tid] > 0);
+        const int sn = wave_sum(in ? ne : 0), sx = wave_sum(over), sd = wave_sum(in && ne < Ct ? Ct - ne : 0),
+                  sz = wave_sum(in ? 0 : over), sc = wave_sum((in ? 1 : 0) | (!in && over > 0 ? 1 << 16 : 0));
+        if (in ? over > kWorst || Ct - ne > kWorst : over > kWorst) s.worst = 1;
+        if (lane == 63) {
+            *(int4 *)&s.part[wv][0] = make_int4(sn, sx, sd, sz);
+            s.part[wv][4] = sc;
+        }
     }
     // holds (0 .. nb-1) and newcomers (nb .. 2nb-1) per margin bin over all experts
     for (int b = wv; b < 2 * nb; b += NW) {
@@ -204,92 +208,76 @@ __device__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const Pric
         tot = wave_sum(tot);
         if (lane == 63) s.cum[b] = tot;
     }
-    if (worst > kWorst) s.worst = 1;
-    sn = wave_sum(sn);
-    ss = wave_sum(ss);
-    sx = wave_sum(sx);
-    sd = wave_sum(sd);
-    sz = wave_sum(sz);
-    so = wave_sum(so);
-    if (lane == 63) {
-        s.n[wv] = sn;
-        s.s[wv] = ss;
-        s.x[wv] = sx;
-        s.d[wv] = sd;
-        s.z[wv] = sz;
-        s.o[wv] = so;
-    }
     __syncthreads();
-    sn = ss = sx = sd = sz = so = 0;
-#pragma unroll
-    for (int x = 0; x < NW; ++x) {
-        sn += s.n[x];
-        ss += s.s[x];
-        sx += s.x[x];
-        sd += s.d[x];
-        sz += s.z[x];
-        so += s.o[x];
+    int sn = 0, sx = 0, sd = 0, sz = 0, sc = 0;
+    for (int x = 0; x < nwe; ++x) {
+        const int4 p4 = *(const int4 *)&s.part[x][0];
+        sn += p4.x;
+        sx += p4.y;
+        sd += p4.z;
+        sz += p4.w;
+        sc += s.part[x][4];
     }
+    const int ss = sc & 0xffff, so = sc >> 16;
     sx = sd > sx ? sd : sx;                                           // tokens too many or too few
     const int target = ss > 0 ? (2 * sn + ss) / (2 * ss) : Ct;        // mean demand of the experts that count
     // What the common step has to take away: what those that count have too many, and what those that are about to join them
     // (price 0, too many tokens) have.  These also move by more than their own margins say, which take the others of
-    // their kind to stay, the more the more of them there are: with both, 10007 tokens of 96 experts and a tenth of spare capacity need two passes less.
+    // their kind to stay, the more the more of them there are: with both, 10007 tokens of 96 experts and a tenth of spare
+    // capacity need two passes less.
     const int X0 = sn - Ct * ss, X = X0 > 0 ? X0 + sz : X0;
     if (level && X < 0 && a.mode == kModeSlack) {
         // A common step down ends for an expert at price 0, and from there on that expert takes part in what the step
         // gains: the experts without a price at most treble in one step (its margins only know the present ones).
         const int m = 2 * (E - ss > 0 ? E - ss : 1);
-        for (int e = tid; e < E; e += kUThreads) {
-            const int p = s.was[e];
-            if (p <= 0) continue;
+        const int p = tid < E ? s.was[tid] : 0;
+        if (wv < nwe && __any(p > 0)) {
             int r = 0;
-            for (int f = 0; f < E; ++f) r += s.was[f] > 0 && (s.was[f] < p || (s.was[f] == p && f < e)) ? 1 : 0;
-            if (r == m - 1) s.cap = p + 1;
+            for (int f = 0; f < E; f += 4) {
+                const int4 o = *(const int4 *)&s.was[f];              // (nothing but zeros from E on)
+                r += (o.x > 0 && (o.x < p || (o.x == p && f < tid)) ? 1 : 0) + (o.y > 0 && (o.y < p || (o.y == p && f + 1 < tid)) ? 1 : 0) +
+                     (o.z > 0 && (o.z < p || (o.z == p && f + 2 < tid)) ? 1 : 0) + (o.w > 0 && (o.w < p || (o.w == p && f + 3 < tid)) ? 1 : 0);
+            }
+            if (p > 0 && r == m - 1) s.cap = p + 1;
         }
         __syncthreads();
     }
-    for (int j = tid; j < E + (level ? 1 : 0); j += kUThreads) {
+    if (tid < E + (level ? 1 : 0)) {
+        const int j = tid;
         const bool common = j == E;
         const int pj = s.was[j];
         const bool in = all_in || pj > 0;
         const int diff = common ? X : s_hn[j] - (in ? target : Ct);
         const int side = diff < 0 ? 1 : 0;                       // side 0: the price has to rise, side 1: to fall
         const int need = side ? (in || common ? -diff : 0) : diff;       // (room left at price 0 is fine)
-        if (need == 0) continue;
-        const int *col = s_h + side * nb * ES + j;
-        int c[kPBins];
+        if (need != 0) {
+            const int *col = s_h + side * nb * ES + j;
+            int c[kPBins];
 #pragma unroll
-        for (int x = 0; x < kPBins; ++x) c[x] = x < nb ? col[x * ES] : 0;
-        int run = 0, prev = 0, h = 1, b = nb;
+            for (int x = 0; x < kPBins; ++x) c[x] = x < nb ? col[x * ES] : 0;
+            int run = 0, prev = 0, b = 0;                        // the first bin that reaches `need`, and the count before it
 #pragma unroll
-        for (int x = 0; x < kPBins; ++x) {
-            if (b == nb && x < nb) {
-                if (run + c[x] >= need) {
-                    b = x;
-                    prev = run;
-                    h = c[x];
-                }
+            for (int x = 0; x < kPBins; ++x) {
+                run += c[x];
+                const bool less = x < nb && run < need;
+                b += less ? 1 : 0;
+                prev = less ? run : prev;
             }
-            run += c[x];
+            int d = mt.w;
+            if (b < nb) {
+                const int lo = bin_edge(b, w0, bs), hi = bin_edge(b + 1, w0, bs);
+                d = lo + (int)((float)(hi - lo) * (float)(need - prev) * __builtin_amdgcn_rcpf((float)col[b * ES]) + 0.5f);
+                d = d < lo ? lo : d > hi ? hi : d;
+            }
+            if (common && side && a.mode == kModeSlack && d > s.cap) d = s.cap;
+            else if (b == nb) s.ran_out = 1;
+            if (!in && !common && sx > E) d += (int)((float)d * fminf(0.7f, 2.f * (float)so / (float)E));
+            d = d < 1 ? 1 : d;
+            atomicMax(&s.maxd, d);
+            if (common) s.lam = side ? -d : d;
+            else s.now[j] = pj + (side ? -d : d);
         }
-        int d = mt.w;
-        if (b < nb) {
-            const int lo = bin_edge(b, w0, bs), hi = bin_edge(b + 1, w0, bs);
-            d = lo + (int)((float)(hi - lo) * (float)(need - prev) / (float)h + 0.5f);
-        }
-        if (common && side && a.mode == kModeSlack && d > s.cap) d = s.cap;
-        else if (b == nb) s.ran_out = 1;
-        if (!in && !common && sx > E) d += (int)((float)d * fminf(0.7f, 2.f * (float)so / (float)E));
-        d = d < 1 ? 1 : d;
-        atomicMax(&s.maxd, d);
-        if (common) s.lam = side ? -d : d;
-        else s.now[j] = pj + (side ? -d : d);
-    }
-    __syncthreads();
-    PriceMeta m2 = mt;
-    bool reach;
-    {
+    } else if (wv == NW - 1) {
         // the bound of the arc list: about kArcsPerExpert exchanges per expert lie under it.  h holds and n newcomers make
         // h * n / rows of them if they are spread over all rows, and the larger of the two if every row has one of each.
         const float want = (float)a.arcs_wanted * (float)nrows / (float)a.T;
@@ -302,18 +290,26 @@ __device__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const Pric
             const float c1 = __shfl(cum, b), c0 = b > 0 ? __shfl(cum, b - 1) : 0.f;
             bound = lo + (int)((float)(hi - lo) * (want - c0) / (c1 - c0));
         }
-        const int wide = fw ? bin_edge(__ffsll((long long)fw), w0, bs) : 4 * mt.w;
-        m2.bound = (long long)a.T * a.k * (E - a.k) <= kAllArcs ? kMaxBound : bound < 2 ? 2 : (bound > kMaxBound ? kMaxBound : bound);
-        reach = fb != 0;
-        int w = s.maxd > wide ? s.maxd : wide;
-        if (s.ran_out && w < 4 * mt.w) w = 4 * mt.w;
-        m2.w = w < 16 ? 16 : (w < (1 << 26) ? w : (1 << 26));
+        if (lane == 0) {
+            s.bound = bound;
+            s.wide = fw ? bin_edge(__ffsll((long long)fw), w0, bs) : 4 * mt.w;
+            s.reach = fb != 0;
+        }
     }
+    __syncthreads();
+    PriceMeta m2 = mt;
+    const int bound = s.bound;
+    m2.bound = (long long)a.T * a.k * (E - a.k) <= kAllArcs ? kMaxBound : bound < 2 ? 2 : (bound > kMaxBound ? kMaxBound : bound);
+    int w = s.maxd > s.wide ? s.maxd : s.wide;
+    if (s.ran_out && w < 4 * mt.w) w = 4 * mt.w;
+    m2.w = w < 16 ? 16 : (w < (1 << 26) ? w : (1 << 26));
     ++m2.passes;
     m2.excess = sampled ? (int)((long long)sx * a.T / nrows) : sx;
-    const bool listed = !a.retry || reach;               // another try needs more exchanges than the one before
+    const bool listed = !a.retry || s.reach;             // another try needs more exchanges than the one before
     // enough: what is left is cheaper to move by the search, or it no longer shrinks (it ends up alternating by a few)
-    if (!sampled && !even && (s.maxd == 0 || (m2.excess * (E <= 128 && !a.retry ? kEnough : 2 * kEnough) <= E && !s.worst && listed) || (listed && m2.excess <= E && m2.excess * 5 >= mt.excess * 4 && t >= a.even + 4))) {
+    const bool enough = m2.excess * (E <= 128 && !a.retry ? kEnough : 2 * kEnough) <= E && !s.worst;
+    const bool stuck = m2.excess <= E && m2.excess * 5 >= mt.excess * 4 && t >= a.even + 4;
+    if (!sampled && !even && (s.maxd == 0 || (listed && (enough || stuck)))) {
         m2.done = 1;
         m2.w = mt.w;
         if (m2.excess == 0) m2.bound = 2;                // nothing to move
@@ -339,7 +335,7 @@ __device__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const Pric
             }
             if (lane == 0) s.pmin[wv] = pm;
             __syncthreads();
-            for (int x = 0; x < NW; ++x) pm = s.pmin[x] < pm ? s.pmin[x] : pm;
+            for (int x = 0; x < nwe; ++x) pm = s.pmin[x] < pm ? s.pmin[x] : pm;
             for (int e = tid; e < E; e += kUThreads) s.now[e] -= pm;
         }
     }
@@ -348,7 +344,7 @@ __device__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const Pric
 
 // One workgroup.  (As the first step of every workgroup of the next pass the same work took 10 to 20 us: several dependent
 // reads of tables that the atomics of the pass have left in memory.)
-__global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, int nrows)
+__global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, int nrows, int *host)
 {
     extern __shared__ __attribute__((aligned(16))) int s_h[];         // the sum of the copies
     __shared__ StepLds s;
@@ -356,7 +352,7 @@ __global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, 
     const int tid = threadIdx.x, E = a.E;
     // everything is requested before the state is looked at (the exit test then does not add a round trip)
     const int quads = (2 * a.nb + 1) * a.es / 4;
-    for (int e = tid; e < E; e += kUThreads) s.was[e] = s.now[e] = ar->prices[e];
+    for (int e = tid; e < kPStride; e += kUThreads) s.was[e] = s.now[e] = e < E ? ar->prices[e] : 0;
     for (int i = tid; i < quads; i += kUThreads) {
         int4 x[kPCopies], y = make_int4(0, 0, 0, 0);
 #pragma unroll
@@ -372,7 +368,11 @@ __global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, 
     if (mt.done) return;                 // (passes that find the prices done add nothing: the copies stay clear)
     const PriceMeta m2 = price_step(a, t, nrows, mt, s_h, s);
     for (int e = tid; e < E; e += kUThreads) ar->prices[e] = s.now[e];
-    if (tid == 0) ar->meta = m2;
+    if (tid == 0) {
+        ar->meta = m2;
+        __hip_atomic_store(host + (m2.done ? kPriceWordDone : kPriceWordPasses), m2.done ? 1 : t + 1, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 }
 
 // The margins of rows r_first .. r_end - 1 of a pass (row i is token i * stride + shift), added to the histograms in
@@ -554,7 +554,7 @@ __global__ __launch_bounds__(kUThreads) void k_price_small(PriceArgs a, int n_pa
     const int hquads = (2 * a.nb + 1) * a.es / 4;
     PriceMeta mt = first_meta(ar, prices_in, a.retry);
     if (tid == 0 && !a.retry) ar->t_start = wall_clock64();
-    for (int e = tid; e < E; e += kUThreads) s.was[e] = a.retry ? ar->prices[e] : first_price(prices_in, e, E, plim);
+    for (int e = tid; e < kPStride; e += kUThreads) s.was[e] = e >= E ? 0 : a.retry ? ar->prices[e] : first_price(prices_in, e, E, plim);
     for (int i = tid; i < 8 * kPStride; i += kUThreads) (&ar->loads[0][0])[i] = 0;
     for (int t = 0; t < n_pass && !mt.done; ++t) {
         int nx[EPL];
@@ -1316,6 +1316,11 @@ bool price_supported(int T, int E, int k)
 int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_t *prices_in, int retry, int32_t *assign, int64_t *prices,
                       int64_t *price_scale, char *ws, SolverState *host_state_dev, PriceGeometry *geom, hipStream_t s)
 {
+    int *words = nullptr, *words_dev = nullptr;
+    const int32_t wrc = solver_words(&words, &words_dev);
+    if (wrc) return wrc;
+    volatile int *hw = words;
+    hw[kPriceWordDone] = hw[kPriceWordPasses] = 0;
     WorkspaceLayout L = workspace_layout(T, E, k);
     PriceArgs a;
     a.q = q;
@@ -1359,6 +1364,14 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     if (!small)
         hipLaunchKernelGGL(k_price_init, dim3(64), dim3(kPThreads), 0, s, a.ar, (2 * a.nb + 1) * a.es / 4, E, plim, prices_in, a.retry);
     for (int t = small ? n_pass : 0; t <= n_pass; ++t) {
+        // One pass stays queued behind the one that runs: once the prices are done every pass still queued costs two empty
+        // launches (8 us; a batch with room to spare needs three of eleven).  The stream is looked at now and then: a
+        // stream that has drained or failed ends the wait.
+        for (unsigned spin = 1; t >= 2 && !small && !hw[kPriceWordDone] && hw[kPriceWordPasses] < t - 1; ++spin) {
+            if ((spin & 4095) == 0 && hipStreamQuery(s) != hipErrorNotReady) break;
+            __builtin_ia32_pause();
+        }
+        if (hw[kPriceWordDone]) t = n_pass;
         const bool fin = t == n_pass;
         const int st = t < n_sampled ? stride : 1;
         const int nrows = st > 1 ? kSampleRows : T;
@@ -1396,7 +1409,7 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
         else MS_PG(64);
 #undef MS_PG
 #undef MS_P
-        if (!fin) hipLaunchKernelGGL(k_price_update, dim3(1), dim3(kUThreads), shm, s, a, t, nrows);
+        if (!fin) hipLaunchKernelGGL(k_price_update, dim3(1), dim3(kUThreads), shm, s, a, t, nrows, words_dev);
     }
     if (E <= 64) hipLaunchKernelGGL(k_price_finish<1>, dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, host_state_dev);
     else if (E <= 128) hipLaunchKernelGGL(k_price_finish<2>, dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, host_state_dev);
