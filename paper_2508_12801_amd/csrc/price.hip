@@ -46,9 +46,13 @@
 namespace maxscore {
 namespace {
 
-constexpr int kPThreads = 256;
+constexpr int kPThreads = 256;                    // ... of the final pass
+constexpr int kQThreads = 512;                    // ... of a price pass
 constexpr int kPStride = kPriceMaxE + 8;          // columns of the per-expert tables (E + 1 used)
-constexpr int kPCopies = 8;
+// Copies of the histograms a pass adds to, one per chiplet; beyond 128 experts, where the one workgroup that reads them takes
+// longer than the additions of two chiplets wait for each other, half as many (16384 tokens of 256 experts: 20 us less).
+constexpr int kPCopies = 8, kPCopiesWide = 4;
+__host__ __device__ constexpr int price_copies(int E) { return E <= 128 ? kPCopies : kPCopiesWide; }
 constexpr int kPCols = 264;                       // columns of a histogram with kPBins bins at most (half as many bins beyond)
 constexpr int kPBins = 20;                        // margin bins per side: ten octaves, two bins each (one beyond 256 experts)
 constexpr int kPArcs = 9216;                      // arcs the one-workgroup search holds in LDS
@@ -342,6 +346,32 @@ __device__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const Pric
     return m2;
 }
 
+// The sum of N copies of the histograms, which are cleared: up to M 16-byte pieces per thread, all on their way together.
+constexpr int kPQuads = 2, kPQuadsWide = ((2 * kPBins + 1) * kPCols / 4 + kUThreads - 1) / kUThreads;
+static_assert((2 * kPBins + 1) * (128 + 4) / 4 <= kPQuads * kUThreads, "two pieces per thread up to 128 experts");
+template <int N, int M>
+__device__ __forceinline__ void gather_copies(PriceArea *ar, int quads, int *s_h)
+{
+    int4 x[M][N];
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        const int i = m * kUThreads + threadIdx.x;
+#pragma unroll
+        for (int r = 0; r < N; ++r) x[m][r] = i < quads ? ((const int4 *)ar->hist[r])[i] : make_int4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        const int i = m * kUThreads + threadIdx.x;
+        int4 y = make_int4(0, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < N; ++r) {
+            if ((x[m][r].x | x[m][r].y | x[m][r].z | x[m][r].w) != 0) ((int4 *)ar->hist[r])[i] = make_int4(0, 0, 0, 0);
+            y.x += x[m][r].x; y.y += x[m][r].y; y.z += x[m][r].z; y.w += x[m][r].w;
+        }
+        if (i < quads) ((int4 *)s_h)[i] = y;
+    }
+}
+
 // One workgroup.  (As the first step of every workgroup of the next pass the same work took 10 to 20 us: several dependent
 // reads of tables that the atomics of the pass have left in memory.)
 __global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, int nrows, int *host)
@@ -353,17 +383,8 @@ __global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, 
     // everything is requested before the state is looked at (the exit test then does not add a round trip)
     const int quads = (2 * a.nb + 1) * a.es / 4;
     for (int e = tid; e < kPStride; e += kUThreads) s.was[e] = s.now[e] = e < E ? ar->prices[e] : 0;
-    for (int i = tid; i < quads; i += kUThreads) {
-        int4 x[kPCopies], y = make_int4(0, 0, 0, 0);
-#pragma unroll
-        for (int r = 0; r < kPCopies; ++r) x[r] = ((const int4 *)ar->hist[r])[i];
-#pragma unroll
-        for (int r = 0; r < kPCopies; ++r) {
-            if ((x[r].x | x[r].y | x[r].z | x[r].w) != 0) ((int4 *)ar->hist[r])[i] = make_int4(0, 0, 0, 0);
-            y.x += x[r].x; y.y += x[r].y; y.z += x[r].z; y.w += x[r].w;
-        }
-        ((int4 *)s_h)[i] = y;
-    }
+    if (price_copies(E) == kPCopies) gather_copies<kPCopies, kPQuads>(ar, quads, s_h);
+    else gather_copies<kPCopiesWide, kPQuadsWide>(ar, quads, s_h);
     const PriceMeta mt = ar->meta;
     if (mt.done) return;                 // (passes that find the prices done add nothing: the copies stay clear)
     const PriceMeta m2 = price_step(a, t, nrows, mt, s_h, s);
@@ -488,9 +509,13 @@ __device__ __forceinline__ void price_rows(const PriceArgs &a, int t, int W, int
     }
 }
 
-// One price pass over `nrows` rows.
+// One price pass over `nrows` rows.  Bound by the atomics that add a workgroup's table to the sums: eight wavefronts share a
+// table, one workgroup a compute unit, and two neighbouring counts go in one 64-bit addition (a count never reaches 2^32).
+// Four wavefronts, 512 workgroups and 32-bit additions took, mean over the passes, 10.6 us at 16384 tokens of 64 experts (now
+// 5.4), 20.1 at 256 experts (12.5) and 18.3 at 65536 tokens of 128 (12.9); without any of the additions 4.0, 6.2 and 7.1.
+// Sixteen wavefronts: 5.4, 12.6 and 14.3.
 template <int G, int EPL, int MODE>
-__global__ __launch_bounds__(kPThreads) void k_price(PriceArgs a, int t, int nrows, int stride, int shift, int rows_per_wg)
+__global__ __launch_bounds__(kQThreads) void k_price(PriceArgs a, int t, int nrows, int stride, int shift, int rows_per_wg)
 {
     using RK = RowKeys<G, EPL>;
     extern __shared__ __attribute__((aligned(16))) int s_hist[];      // (2 * nb + 1) x ES: margins of holds, of newcomers, holds
@@ -510,20 +535,19 @@ __global__ __launch_bounds__(kPThreads) void k_price(PriceArgs a, int t, int nro
         RK::load(a.q + (size_t)(i * stride + shift) * E, E, vec, lg, nx);
     }
     const PriceMeta mt = ar->meta;
-    for (int e = tid; e < E; e += kPThreads) s_p[e] = ar->prices[e];
+    for (int e = tid; e < E; e += kQThreads) s_p[e] = ar->prices[e];
     if (mt.done) return;
     const int hquads = (2 * nb + 1) * ES / 4;
-    for (int i = tid; i < hquads; i += kPThreads) ((int4 *)s_hist)[i] = make_int4(0, 0, 0, 0);
+    for (int i = tid; i < hquads; i += kQThreads) ((int4 *)s_hist)[i] = make_int4(0, 0, 0, 0);
     __syncthreads();
-    price_rows<G, EPL, MODE, kPThreads>(a, t, mt.w, r_first, r_end, stride, shift, nx, s_p, s_hist);
+    price_rows<G, EPL, MODE, kQThreads>(a, t, mt.w, r_first, r_end, stride, shift, nx, s_p, s_hist);
     __syncthreads();
-    int *hg = ar->hist[blockIdx.x & (kPCopies - 1)];
-    for (int i = tid; i < hquads; i += kPThreads) {
+    int *hg = ar->hist[blockIdx.x & (price_copies(E) - 1)];
+    for (int i = tid; i < hquads; i += kQThreads) {
         const int4 x = ((int4 *)s_hist)[i];
-        if (x.x) atomicAdd(hg + 4 * i, x.x);
-        if (x.y) atomicAdd(hg + 4 * i + 1, x.y);
-        if (x.z) atomicAdd(hg + 4 * i + 2, x.z);
-        if (x.w) atomicAdd(hg + 4 * i + 3, x.w);
+        unsigned long long *h64 = (unsigned long long *)(hg + 4 * i);
+        if (x.x | x.y) atomicAdd(h64, (unsigned long long)(unsigned)x.x | ((unsigned long long)(unsigned)x.y << 32));
+        if (x.z | x.w) atomicAdd(h64 + 1, (unsigned long long)(unsigned)x.z | ((unsigned long long)(unsigned)x.w << 32));
     }
 }
 
@@ -1376,8 +1400,8 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
         const int st = t < n_sampled ? stride : 1;
         const int nrows = st > 1 ? kSampleRows : T;
         const int shift = st > 1 ? t * (st / 2) : 0;
-        int rw = ngrp;
-        while (rw * 2 <= 128 && (nrows + 2 * rw - 1) / (2 * rw) >= 512) rw *= 2;
+        int rw = kQThreads / G;
+        while (rw * 2 <= 128 && (nrows + 2 * rw - 1) / (2 * rw) >= 256) rw *= 2;
         const int grid = fin ? a.n_wg : (nrows + rw - 1) / rw;
 #define MS_P(GG, PP)                                                                                                      \
     do {                                                                                                                  \
@@ -1390,9 +1414,9 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
             if (os) hipLaunchKernelGGL((k_price_assign<GG, PP, true>), dim3(grid), dim3(kPThreads), 0, s, a);     \
             else hipLaunchKernelGGL((k_price_assign<GG, PP, false>), dim3(grid), dim3(kPThreads), 0, s, a);       \
         } else {                                                                                                          \
-            if (a.mode == kModeTight) hipLaunchKernelGGL((k_price<GG, PP, kModeTight>), dim3(grid), dim3(kPThreads), shm, s, a, t, nrows, st, shift, rw); \
-            else if (os) hipLaunchKernelGGL((k_price<GG, PP, kModeOver>), dim3(grid), dim3(kPThreads), shm, s, a, t, nrows, st, shift, rw); \
-            else hipLaunchKernelGGL((k_price<GG, PP, kModeSlack>), dim3(grid), dim3(kPThreads), shm, s, a, t, nrows, st, shift, rw); \
+            if (a.mode == kModeTight) hipLaunchKernelGGL((k_price<GG, PP, kModeTight>), dim3(grid), dim3(kQThreads), shm, s, a, t, nrows, st, shift, rw); \
+            else if (os) hipLaunchKernelGGL((k_price<GG, PP, kModeOver>), dim3(grid), dim3(kQThreads), shm, s, a, t, nrows, st, shift, rw); \
+            else hipLaunchKernelGGL((k_price<GG, PP, kModeSlack>), dim3(grid), dim3(kQThreads), shm, s, a, t, nrows, st, shift, rw); \
         }                                                                                                                 \
     } while (0)
 #define MS_PG(GG)                                                                                                         \
