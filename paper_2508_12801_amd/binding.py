@@ -162,7 +162,8 @@ def _ptr(t):
 
 
 def _stream():
-    return _RAW_STREAM(_torch().cuda.current_device())
+    index = _torch().cuda.current_device()      # before _RAW_STREAM is read: the first call of all sets it
+    return _RAW_STREAM(index)
 
 
 def _check(rc: int, where: str, allow=()):
