@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "maxscore.h"
+#include "price_tables.h"
 
 namespace maxscore {
 
@@ -112,7 +113,6 @@ int32_t kvec_check(const int32_t *kvec, int T, int E, int k, char *ws, long long
 // exchanges may do it, retry > 0 counts these; anything else: the auction has to solve the problem).
 // k <= E <= kPriceMaxE, one capacity for all experts, any relation of demand and capacity (rows that cannot be filled
 // end in -1).
-constexpr int kPriceMaxE = 512;
 struct PriceGeometry {
     int rows, n_wg;          // blocks of rows over which the pairs are counted (WorkspaceLayout::wcnt_off)
 };

@@ -53,8 +53,6 @@ constexpr int kPStride = kPriceMaxE + 8;          // columns of the per-expert t
 // longer than the additions of two chiplets wait for each other, half as many (16384 tokens of 256 experts: 20 us less).
 constexpr int kPCopies = 8, kPCopiesWide = 4;
 __host__ __device__ constexpr int price_copies(int E) { return E <= 128 ? kPCopies : kPCopiesWide; }
-constexpr int kPCols = 264;                       // columns of a histogram with kPBins bins at most (half as many bins beyond)
-constexpr int kPBins = 20;                        // margin bins per side: ten octaves, two bins each (one beyond 256 experts)
 constexpr int kPArcs = 9216;                      // arcs the one-workgroup search holds in LDS
 constexpr int kPBlocks = 4096;                    // blocks of rows of the final pass at most (four per thread of the search)
 constexpr int kPArcBuf = 16384;                   // arcs the final pass can list
@@ -97,7 +95,7 @@ struct PriceArea {
     // margins and holds, one copy per chiplet: (2 * nb + 1) rows of ES columns, filled by a pass (workgroup b adds to copy
     // b mod 8), added up and cleared by the update behind it.  With one copy for all the additions of 512 workgroups
     // took 25 us: its lines travel from chiplet to chiplet with every addition.
-    int hist[kPCopies][(2 * kPBins + 1) * kPCols];
+    int hist[kPCopies][kPTableInts];
     unsigned long long arc[kPArcBuf];             // cost << 32 | from << 16 | to
     int arc_tok[kPArcBuf];
 };
@@ -347,8 +345,9 @@ __device__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const Pric
 }
 
 // The sum of N copies of the histograms, which are cleared: up to M 16-byte pieces per thread, all on their way together.
-constexpr int kPQuads = 2, kPQuadsWide = ((2 * kPBins + 1) * kPCols / 4 + kUThreads - 1) / kUThreads;
-static_assert((2 * kPBins + 1) * (128 + 4) / 4 <= kPQuads * kUThreads, "two pieces per thread up to 128 experts");
+constexpr int kPQuads = 2, kPQuadsWide = (kPTableInts / 4 + kUThreads - 1) / kUThreads;
+static_assert(price_table_most(1, 128) / 4 <= kPQuads * kUThreads, "two pieces per thread up to 128 experts");
+static_assert(kPTableInts % 4 == 0, "every copy starts on 16 bytes");
 template <int N, int M>
 __device__ __forceinline__ void gather_copies(PriceArea *ar, int quads, int *s_h)
 {
@@ -1369,9 +1368,9 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     if (retry) a.arcs_wanted = std::min((1 + retry) * a.arcs_wanted, kArcsMost);
     a.ib = 1;
     while ((1 << a.ib) < E) ++a.ib;
-    a.nb = E <= 256 ? kPBins : kPBins / 2;
+    a.nb = price_bins(E);
     a.bshift = E <= 256 ? 22 : 23;
-    a.es = (E + (a.mode == kModeTight ? 0 : 1) + 3) & ~3;
+    a.es = price_columns(E, a.mode == kModeTight);
 
     int G, EPL, rows;
     if (!price_shape(T, E, k, G, EPL, rows, a.n_wg) || a.n_wg > L.max_wg) return MAXSCORE_ERR_SHAPE;
@@ -1381,12 +1380,12 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     geom->n_wg = a.n_wg;
 
     const bool os = a.mode == kModeOver;
-    const size_t shm = sizeof(int) * (size_t)(2 * a.nb + 1) * a.es;
+    const size_t shm = sizeof(int) * (size_t)price_table_ints(E, a.mode == kModeTight);
     const int n_pass = n_sampled + (retry ? 4 : a.mode == kModeSlack ? 9 : 6);
     const bool small = (long long)T * G <= kSmallThreads && (long long)T * E <= kSmallEntries && shm + sizeof(StepLds) <= 64 * 1024;
     const int plim = (1 << (31 - a.ib)) - 1;
     if (!small)
-        hipLaunchKernelGGL(k_price_init, dim3(64), dim3(kPThreads), 0, s, a.ar, (2 * a.nb + 1) * a.es / 4, E, plim, prices_in, a.retry);
+        hipLaunchKernelGGL(k_price_init, dim3(64), dim3(kPThreads), 0, s, a.ar, price_table_ints(E, a.mode == kModeTight) / 4, E, plim, prices_in, a.retry);
     for (int t = small ? n_pass : 0; t <= n_pass; ++t) {
         // One pass stays queued behind the one that runs: once the prices are done every pass still queued costs two empty
         // launches (8 us; a batch with room to spare needs three of eleven).  The stream is looked at now and then: a
