@@ -103,11 +103,14 @@ typedef struct {
     int32_t phases;        /* eps-scaling phases executed (restarts included) */
     int32_t status;        /* MAXSCORE_OK, MAXSCORE_ERR_RANGE or MAXSCORE_ERR_NOT_CONVERGED */
     float solver_ms;       /* device time of a4 between two events on `stream` */
-    float bid_ms;          /* summed device time of the bid-pass launches inside a4 (0 unless
-                              timing was switched on with maxscore_set_kernel_timing) */
-    int32_t bid_launches;  /* bid-pass launches that did work (0 unless timing is on) */
-    float select_ms;       /* summed device time of the select-pass launches of the same rounds, the tail pass
-                              that runs inside some of them included (0 unless timing is on) */
+    float bid_ms;          /* summed device time of the first kernel of every round inside a4 (0 unless timing was
+                              switched on with maxscore_set_kernel_timing): the price passes over the rewards of a
+                              price solve, the bid passes of an auction */
+    int32_t bid_launches;  /* launches behind bid_ms that did work (0 unless timing is on); all price passes of a
+                              small batch are one launch */
+    float select_ms;       /* summed device time of the second kernel of the same rounds: the price steps (0 where
+                              the passes are one launch), the select passes with the tail pass that runs inside
+                              some of them (0 unless timing is on) */
     float gates_dispatch_ms; /* maxscore_route_* only: device time of a5 + a6 between two events on `stream` */
     int32_t finish_passes; /* passes of the cycle-cancelling finisher (0: the auction ran to eps = 1 itself) */
     int32_t finish_cycles; /* negative cycles it cancelled */
@@ -358,8 +361,8 @@ int32_t maxscore_route_xw(const void *x, const void *W, const float *bias, int32
                           int64_t *prices, maxscore_stats *stats, void *workspace,
                           size_t workspace_bytes, void *stream);
 
-/* Switch per-launch HIP-event timing of the solver's bid and select passes on (1) or off (0, default).
- * Timing adds three event records per round; it is meant for benchmarks. */
+/* Switch per-launch HIP-event timing of the solver's rounds (price passes and steps, or bid and select passes) on (1) or
+ * off (0, default).  Timing adds three event records per round; it is meant for benchmarks. */
 void maxscore_set_kernel_timing(int32_t on);
 
 /* Plain device-to-device copy kernel of `bytes` bytes (multiple of 16), used by the benchmark to

@@ -115,6 +115,7 @@ int32_t kvec_check(const int32_t *kvec, int T, int E, int k, char *ws, long long
 // end in -1).
 struct PriceGeometry {
     int rows, n_wg;          // blocks of rows over which the pairs are counted (WorkspaceLayout::wcnt_off)
+    int one_launch;          // all price passes were one launch
 };
 bool price_supported(int T, int E, int k);
 // tables, and two words per block; the iterative assignment keeps its own there, with counts per (slot, 64 tokens, expert)
@@ -126,6 +127,9 @@ inline size_t price_area_bytes(int T, int E, int k, int max_wg)
 }
 // Pinned words of the calling thread (16 of them, cleared by whoever uses them), and the same as the device sees them.
 int32_t solver_words(int **host, int **dev);
+// With kernel timing on, records the next of the calling thread's timing events: before and after the first kernel of a round
+// (auction) or pass (price solve) and after its second, three in all.
+int32_t solver_mark(hipStream_t s);
 int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_t *prices_in, int retry,
                       int32_t *assign, int64_t *prices, int64_t *price_scale, char *ws, SolverState *host_state_dev, PriceGeometry *geom, hipStream_t s);
 // Runs price_enqueue and the caller's work behind it and waits.  *solved: whether the result stands.

@@ -1379,11 +1379,14 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     geom->rows = rows;
     geom->n_wg = a.n_wg;
 
+    int32_t mrc = MAXSCORE_OK;                    // (timing marks)
+    auto mark = [&] { mrc = mrc ? mrc : solver_mark(s); };
     const bool os = a.mode == kModeOver;
     const size_t shm = sizeof(int) * (size_t)price_table_ints(E, a.mode == kModeTight);
     const int n_pass = n_sampled + (retry ? 4 : a.mode == kModeSlack ? 9 : 6);
     const bool small = (long long)T * G <= kSmallThreads && (long long)T * E <= kSmallEntries && shm + sizeof(StepLds) <= 64 * 1024;
     const int plim = (1 << (31 - a.ib)) - 1;
+    geom->one_launch = small ? 1 : 0;
     if (!small)
         hipLaunchKernelGGL(k_price_init, dim3(64), dim3(kPThreads), 0, s, a.ar, price_table_ints(E, a.mode == kModeTight) / 4, E, plim, prices_in, a.retry);
     for (int t = small ? n_pass : 0; t <= n_pass; ++t) {
@@ -1406,16 +1409,21 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     do {                                                                                                                  \
         if (fin) {                                                                                                        \
             if (small) {                                                                                                  \
+                mark();                                                                                                   \
                 if (a.mode == kModeTight) hipLaunchKernelGGL((k_price_small<GG, PP, kModeTight>), dim3(1), dim3(kUThreads), shm, s, a, kSmallPasses, plim, prices_in); \
                 else if (os) hipLaunchKernelGGL((k_price_small<GG, PP, kModeOver>), dim3(1), dim3(kUThreads), shm, s, a, kSmallPasses, plim, prices_in); \
                 else hipLaunchKernelGGL((k_price_small<GG, PP, kModeSlack>), dim3(1), dim3(kUThreads), shm, s, a, kSmallPasses, plim, prices_in); \
+                mark();                                                                                                   \
+                mark();                                                                                                   \
             }                                                                                                             \
             if (os) hipLaunchKernelGGL((k_price_assign<GG, PP, true>), dim3(grid), dim3(kPThreads), 0, s, a);     \
             else hipLaunchKernelGGL((k_price_assign<GG, PP, false>), dim3(grid), dim3(kPThreads), 0, s, a);       \
         } else {                                                                                                          \
+            mark();                                                                                                       \
             if (a.mode == kModeTight) hipLaunchKernelGGL((k_price<GG, PP, kModeTight>), dim3(grid), dim3(kQThreads), shm, s, a, t, nrows, st, shift, rw); \
             else if (os) hipLaunchKernelGGL((k_price<GG, PP, kModeOver>), dim3(grid), dim3(kQThreads), shm, s, a, t, nrows, st, shift, rw); \
             else hipLaunchKernelGGL((k_price<GG, PP, kModeSlack>), dim3(grid), dim3(kQThreads), shm, s, a, t, nrows, st, shift, rw); \
+            mark();                                                                                                       \
         }                                                                                                                 \
     } while (0)
 #define MS_PG(GG)                                                                                                         \
@@ -1432,14 +1440,17 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
         else MS_PG(64);
 #undef MS_PG
 #undef MS_P
-        if (!fin) hipLaunchKernelGGL(k_price_update, dim3(1), dim3(kUThreads), shm, s, a, t, nrows, words_dev);
+        if (!fin) {
+            hipLaunchKernelGGL(k_price_update, dim3(1), dim3(kUThreads), shm, s, a, t, nrows, words_dev);
+            mark();
+        }
     }
     if (E <= 64) hipLaunchKernelGGL(k_price_finish<1>, dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, host_state_dev);
     else if (E <= 128) hipLaunchKernelGGL(k_price_finish<2>, dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, host_state_dev);
     else if (E <= 256) hipLaunchKernelGGL(k_price_finish<4>, dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, host_state_dev);
     else hipLaunchKernelGGL(k_price_finish<8>, dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, host_state_dev);
     MS_HIP(hipGetLastError());
-    return MAXSCORE_OK;
+    return mrc;
 }
 
 }  // namespace maxscore

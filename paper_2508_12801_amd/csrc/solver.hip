@@ -1813,7 +1813,8 @@ struct SolverHost {
     // whether the first finisher group of the last solve of this shape certified (what follows a certified solve is
     // enqueued ahead of the group's report only while that keeps happening)
     int ahead_T = 0, ahead_E = 0, ahead_k = 0, ahead_ok = 1;
-    std::vector<hipEvent_t> tev;      // pool of per-launch timing events (kernel timing only)
+    std::vector<hipEvent_t> tev;      // pool of per-launch timing events (kernel timing only), three per round or pass
+    size_t tev_used = 0;              // ... recorded by the solve in progress
     int device = -1;
 };
 
@@ -1852,6 +1853,58 @@ int32_t solver_words(int **host, int **dev)
     return MAXSCORE_OK;
 }
 
+int32_t solver_mark(hipStream_t s)
+{
+    if (!g_kernel_timing) return MAXSCORE_OK;
+    SolverHost *hs = nullptr;
+    const int32_t rc = solver_host(&hs);
+    if (rc) return rc;
+    if (hs->tev.size() == hs->tev_used) {
+        hipEvent_t e = nullptr;
+        MS_HIP(hipEventCreate(&e));
+        hs->tev.push_back(e);
+    }
+    MS_HIP(hipEventRecord(hs->tev[hs->tev_used], s));
+    ++hs->tev_used;
+    return MAXSCORE_OK;
+}
+
+// Adds the times of the `kernels` kernels of `n` rounds or passes, the first of them at mark `first`, to the statistics.  The stream
+// is idle; what a pair of event records costs with nothing between them is taken off every time.
+static int32_t add_launch_times(SolverHost *hs, size_t first, int n, int kernels, maxscore_stats *stats, hipStream_t s)
+{
+    std::vector<hipEvent_t> &tev = hs->tev;
+    const size_t have = hs->tev_used > first ? (hs->tev_used - first) / 3 : 0;
+    n = (size_t)n < have ? n : (int)have;
+    if (n <= 0 || !stats) return MAXSCORE_OK;
+    float empty_ms = 0.f;
+    constexpr int n_cal = 16;
+    const size_t cal = hs->tev_used;
+    while (tev.size() < cal + 2 * n_cal) {
+        hipEvent_t e = nullptr;
+        MS_HIP(hipEventCreate(&e));
+        tev.push_back(e);
+    }
+    for (int i = 0; i < 2 * n_cal; ++i) MS_HIP(hipEventRecord(tev[cal + i], s));
+    MS_HIP(hipStreamSynchronize(s));
+    for (int i = 0; i < n_cal; ++i) {
+        float t = 0.f;
+        (void)hipEventElapsedTime(&t, tev[cal + 2 * i], tev[cal + 2 * i + 1]);
+        empty_ms += t / n_cal;
+    }
+    for (int i = 0; i < n; ++i) {
+        float t[2] = {0.f, 0.f};
+        for (int h = 0; h < kernels; ++h) {
+            (void)hipEventElapsedTime(&t[h], tev[first + 3 * i + h], tev[first + 3 * i + h + 1]);
+            t[h] = t[h] > empty_ms ? t[h] - empty_ms : 0.f;
+        }
+        stats->bid_ms += t[0];
+        stats->select_ms += t[1];
+    }
+    stats->bid_launches += n;
+    return MAXSCORE_OK;
+}
+
 // On an error after work has been queued the stream is drained before returning, so that nothing of this solve
 // is still running on the caller's buffers.
 #define MS_HIP_SYNC(call)                        \
@@ -1881,8 +1934,10 @@ int32_t price_run(const int32_t *q, int T, int E, int k, int C, const maxscore_o
     if (rc) return rc;
     PriceGeometry pg;
     SolverState h;
+    int passes = o.prices_in ? -1 : 0;            // (the pass that checks given prices is a launch like the others)
     for (int attempt = 0;; ++attempt) {
         hs->state->fin = 0;
+        const size_t mark = hs->tev_used;
         rc = price_enqueue(q, T, E, k, C, o.prices_in, attempt, assign, prices, price_scale, ws, hs->state_dev, &pg, s);
         if (rc == MAXSCORE_OK && after) {
             const SolverGeometry g = {pg.rows, pg.n_wg, 0, 1, &hs->state_dev->t_after};
@@ -1895,6 +1950,9 @@ int32_t price_run(const int32_t *q, int T, int E, int k, int C, const maxscore_o
         MS_HIP(hipStreamSynchronize(s));
         MS_HIP(hipGetLastError());
         h = *hs->state;
+        rc = add_launch_times(hs, mark, pg.one_launch ? 1 : h.round - passes, pg.one_launch ? 1 : 2, stats, s);
+        if (rc) return rc;
+        passes = h.round;
         if (h.fin == 2) break;
         if (h.fin != 1 || attempt + 1 >= kPriceTries) return MAXSCORE_OK;
     }
@@ -1919,6 +1977,12 @@ int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore
                    const int32_t *cap, long long room, const int32_t *kvec, long long demand, SolverGeometry *geom,
                    SolverAfter after, void *after_ctx)
 {
+    SolverHost *hs = nullptr;
+    {
+        int32_t rc = solver_host(&hs);
+        if (rc) return rc;
+    }
+    hs->tev_used = 0;
     if (!cap && !kvec) {
         bool solved = false;
         const int32_t rc = price_run(q, T, E, k, Ce, o, assign, prices, price_scale, stats, ws, s, geom, after, after_ctx, &solved);
@@ -1984,11 +2048,6 @@ int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore
     const int n_wg = (T + rows - 1) / rows;
     if (n_wg > L.max_wg) return MAXSCORE_ERR_WORKSPACE;
 
-    SolverHost *hs = nullptr;
-    {
-        int32_t rc = solver_host(&hs);
-        if (rc) return rc;
-    }
     // room = total capacity (sum of the vector, or E*Ce)
     // demand = number of pairs to place (sum of the per-token k, or T*k)
     const long long want = kvec ? demand : (long long)T * k;
@@ -2033,8 +2092,7 @@ int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore
             __builtin_ia32_pause();
         }
     };
-    std::vector<hipEvent_t> &tev = hs->tev;
-    size_t tev_used = 0;
+    const size_t first_mark = hs->tev_used;
     int batch = 2;      // two to four rounds in flight: each round still queued when the solve ends costs an empty launch pair
 #ifdef MAXSCORE_DEBUG_ENV
     if (const char *ev = getenv("MAXSCORE_BATCH")) batch = std::max(1, std::min(atoi(ev), 64));
@@ -2043,14 +2101,8 @@ int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore
     auto enqueue_batch = [&](int slot) -> int32_t {
         for (int b = 0; b < batch; ++b) {
             const int par = launched & 1;
-            if (g_kernel_timing) {
-                while (tev.size() < tev_used + 3) {
-                    hipEvent_t e = nullptr;
-                    MS_HIP(hipEventCreate(&e));
-                    tev.push_back(e);
-                }
-                MS_HIP(hipEventRecord(tev[tev_used], s));
-            }
+            int32_t mrc = solver_mark(s);
+            if (mrc) return mrc;
 #define MS_BID(GG)                                                                                   \
     launch_bid_g<GG>(EPL, vec, q, assign, theta + par * kMaxE, st + par, klist, wcnt, wmoves, qmm + 2, T, E, k, \
                      rows, kvec, 0, nullptr, s)
@@ -2059,7 +2111,8 @@ int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore
             else if (G == 32) MS_BID(32);
             else MS_BID(64);
 #undef MS_BID
-            if (g_kernel_timing) MS_HIP(hipEventRecord(tev[tev_used + 1], s));
+            mrc = solver_mark(s);
+            if (mrc) return mrc;
 #define MS_SEL(TT)                                                                                             \
     hipLaunchKernelGGL(k_select<TT>, dim3(E + tail_on), dim3(kSelThreads), 0, s, klist, wcnt, wmoves, gcount, theta, \
                        st, qmm + 2, cand, q, assign, qmm + 3, hs->flag_dev, par, T, E, k, Ce, cap, n_wg, rows, tail_on, \
@@ -2070,10 +2123,8 @@ int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore
             else if (E <= 512) MS_SEL(8);
             else MS_SEL(16);
 #undef MS_SEL
-            if (g_kernel_timing) {
-                MS_HIP(hipEventRecord(tev[tev_used + 2], s));
-                tev_used += 3;
-            }
+            mrc = solver_mark(s);
+            if (mrc) return mrc;
             ++launched;
         }
         return MAXSCORE_OK;
@@ -2211,41 +2262,11 @@ int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore
     if (fin_limit_q > 0 && hs->ahead_T == T && hs->ahead_E == E && hs->ahead_k == k && hs->ahead_ok == 1 &&
         h.fin == 2 && h.fin_passes <= 1)
         hs->ahead_ok = 2;
-    float ms = 0.f, bid_ms = 0.f, select_ms = 0.f;
+    float ms = 0.f;
     (void)hipEventElapsedTime(&ms, hs->ev0, hs->ev1);
-    int timed = 0;
-    if (tev_used > 0) {
-        // what a pair of event records costs with nothing between them is taken off every launch time
-        float empty_ms = 0.f;
-        const int n_cal = 16;
-        while (tev.size() < tev_used + 2 * n_cal) {
-            hipEvent_t e = nullptr;
-            MS_HIP(hipEventCreate(&e));
-            tev.push_back(e);
-        }
-        hipEvent_t *ce = tev.data() + tev_used;
-        for (int i = 0; i < n_cal; ++i) {
-            MS_HIP(hipEventRecord(ce[2 * i], s));
-            MS_HIP(hipEventRecord(ce[2 * i + 1], s));
-        }
-        MS_HIP(hipStreamSynchronize(s));
-        for (int i = 0; i < n_cal; ++i) {
-            float t = 0.f;
-            (void)hipEventElapsedTime(&t, ce[2 * i], ce[2 * i + 1]);
-            empty_ms += t / n_cal;
-        }
-        for (size_t i = 0; i + 2 < tev_used; i += 3) {
-            if ((int)(i / 3) < h.round) {
-                float t = 0.f;
-                (void)hipEventElapsedTime(&t, tev[i], tev[i + 1]);
-                t -= empty_ms;
-                bid_ms += t > 0.f ? t : 0.f;
-                (void)hipEventElapsedTime(&t, tev[i + 1], tev[i + 2]);
-                t -= empty_ms;
-                select_ms += t > 0.f ? t : 0.f;
-                ++timed;
-            }
-        }
+    {
+        const int32_t rc = add_launch_times(hs, first_mark, h.round, 2, stats, s);
+        if (rc) return rc;
     }
 #ifdef MAXSCORE_DEBUG_ENV
     if (getenv("MAXSCORE_DEBUG"))
@@ -2287,9 +2308,6 @@ int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore
         stats->phases = h.phases;
         stats->status = h.status;
         stats->solver_ms = ms;
-        stats->bid_ms = bid_ms;
-        stats->bid_launches = timed;
-        stats->select_ms = select_ms;
         stats->finish_passes = h.fin_passes;
         stats->finish_cycles = fin_cycles;        // over all attempts (finish_passes: the last attempt's)
     }
