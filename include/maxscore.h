@@ -102,7 +102,8 @@ typedef struct {
     int32_t rounds;        /* solver rounds executed (auction rounds: bid pass + select pass) */
     int32_t phases;        /* eps-scaling phases executed (restarts included) */
     int32_t status;        /* MAXSCORE_OK, MAXSCORE_ERR_RANGE or MAXSCORE_ERR_NOT_CONVERGED */
-    float solver_ms;       /* device time of a4 between two events on `stream` */
+    float solver_ms;       /* device time of a4: from its first kernel to its last in a price solve, between two events on
+                              `stream` in an auction; with price tries that did not stand before the auction, both */
     float bid_ms;          /* summed device time of the first kernel of every round inside a4 (0 unless timing was
                               switched on with maxscore_set_kernel_timing): the price passes over the rewards of a
                               price solve, the bid passes of an auction */

@@ -170,7 +170,12 @@ int32_t oversub_run(const int32_t *q, int T, int E, int k, int Ce, const maxscor
     MS_HIP(hipStreamSynchronize(s));
     MS_HIP(hipGetLastError());
     if (stats) {
+        const maxscore_stats before = *stats;         // what the price tries took
         *stats = st2;
+        stats->solver_ms += before.solver_ms;
+        stats->bid_ms += before.bid_ms;
+        stats->select_ms += before.select_ms;
+        stats->bid_launches += before.bid_launches;
         // the solver counted the padding pairs (its own holes, after a round cap, count for nothing there)
         const long long placed2 = st2.flow_value;
         const long long pads = placed2 - ((long long)T * k - holes);

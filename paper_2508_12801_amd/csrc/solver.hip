@@ -1954,7 +1954,10 @@ int32_t price_run(const int32_t *q, int T, int E, int k, int C, const maxscore_o
         if (rc) return rc;
         passes = h.round;
         if (h.fin == 2) break;
-        if (h.fin != 1 || attempt + 1 >= kPriceTries) return MAXSCORE_OK;
+        if (h.fin != 1 || attempt + 1 >= kPriceTries) {
+            if (stats) stats->solver_ms += (float)(h.t_end - h.t_start) * 1e-5f;      // (the first try's start to here)
+            return MAXSCORE_OK;
+        }
     }
     *solved = true;
     if (geom) *geom = {pg.rows, pg.n_wg, 0, 1, nullptr};
@@ -2307,7 +2310,7 @@ int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore
         stats->rounds = h.round;
         stats->phases = h.phases;
         stats->status = h.status;
-        stats->solver_ms = ms;
+        stats->solver_ms += ms;               // (behind the price tries, if there were any)
         stats->finish_passes = h.fin_passes;
         stats->finish_cycles = fin_cycles;        // over all attempts (finish_passes: the last attempt's)
     }
