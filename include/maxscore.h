@@ -72,8 +72,10 @@ enum { MAXSCORE_DTYPE_BF16 = 0, MAXSCORE_DTYPE_FP32 = 1 };
 typedef struct {
     float t;              /* SoftTopk temperature of Eq. 6 */
     int32_t quant_shift;  /* rewards are round(A * 2^quant_shift); 1..24 */
-    int32_t max_rounds;   /* cap on solver rounds (bid pass + select pass) */
-    int32_t eps_div;      /* eps-scaling ratio between solver phases, >= 2 */
+    int32_t max_rounds;   /* cap on solver rounds.  A price solve takes at most 60 passes and is used where the cap
+                             allows that many; with a smaller cap, and where a price solve does not stand, the
+                             auction solves the problem in at most max_rounds rounds of its own */
+    int32_t eps_div;      /* auction only: eps-scaling ratio between its phases, >= 2 */
     int32_t assignment;   /* maxscore_route_* only: MAXSCORE_ASSIGN_EXACT (0, the exact solver) or
                              MAXSCORE_ASSIGN_ITER (1, iterative rerouting: prices are not written,
                              stats carry total, flow and the number of rerouting rounds) */
@@ -81,26 +83,28 @@ typedef struct {
     const int64_t *prices_in; /* exact solver: NULL, or DEVICE array of E starting prices in the units of the
                              `prices` output (1/price_scale of a q unit; price_scale depends on E only), e.g. the
                              prices a previous call returned for a batch routed by the same W_g.  Any values >= 0 are
-                             legal: the result is the same optimum, only the number of rounds changes.  (A forward
-                             auction only raises prices, so a start that is too high on some experts makes all the
-                             others climb: measured on successive batches of one router it saves nothing.) */
-    int64_t eps_start;    /* with prices_in: eps of the first phase in the same units (it is rounded down to a power
+                             legal: the result is the same optimum, only the number of rounds changes.  (A price solve
+                             moves prices both ways and starts from them as they are.  A forward auction only raises
+                             prices, so a start that is too high on some experts makes all the others climb: measured
+                             on successive batches of one router it saves nothing.) */
+    int64_t eps_start;    /* auction only, with prices_in: eps of the first phase in the same units (it is rounded down to a power
                              of eps_div; 0 = one step below the cold-start value).  A phase that runs longer than 48 rounds
                              after a start from given prices goes back up one step of the eps ladder (at most as many
                              steps in all as the start skipped). */
 } maxscore_opts;
 #define MAXSCORE_ASSIGN_EXACT 0
 #define MAXSCORE_ASSIGN_ITER 1
-#define MAXSCORE_FLAG_NO_TAIL_PASS 1u   /* exact solver: dense rounds only (slower; same optimum) */
-#define MAXSCORE_FLAG_NO_FINISHER 2u    /* exact solver: the auction runs down to eps = 1 itself instead of handing
+#define MAXSCORE_FLAG_NO_TAIL_PASS 1u   /* exact solver: the auction with dense rounds only (slower; same optimum) */
+#define MAXSCORE_FLAG_NO_FINISHER 2u    /* exact solver: the auction, and it runs down to eps = 1 itself instead of handing
                                            its last phases to the cycle-cancelling finisher (slower; same optimum) */
 
 /* Filled on the HOST when the call returns (may be NULL). */
 typedef struct {
     int64_t total_score_q; /* sum of q over the chosen pairs */
     int32_t flow_value;    /* number of chosen pairs */
-    int32_t rounds;        /* solver rounds executed (auction rounds: bid pass + select pass) */
-    int32_t phases;        /* eps-scaling phases executed (restarts included) */
+    int32_t rounds;        /* rounds of the solver the result comes from: passes over the rewards of a price solve (one
+                              that only checks given prices is not counted), bid pass + select pass of an auction */
+    int32_t phases;        /* 1 for a price solve; eps-scaling phases of an auction (restarts included) */
     int32_t status;        /* MAXSCORE_OK, MAXSCORE_ERR_RANGE or MAXSCORE_ERR_NOT_CONVERGED */
     float solver_ms;       /* device time of a4: from its first kernel to its last in a price solve, between two events on
                               `stream` in an auction; with price tries that did not stand before the auction, both */
@@ -113,8 +117,9 @@ typedef struct {
                               the passes are one launch), the select passes with the tail pass that runs inside
                               some of them (0 unless timing is on) */
     float gates_dispatch_ms; /* maxscore_route_* only: device time of a5 + a6 between two events on `stream` */
-    int32_t finish_passes; /* passes of the cycle-cancelling finisher (0: the auction ran to eps = 1 itself) */
-    int32_t finish_cycles; /* negative cycles it cancelled */
+    int32_t finish_passes; /* price solve: 1 (its search); auction: passes of the cycle-cancelling finisher (0: it ran to
+                              eps = 1 itself) */
+    int32_t finish_cycles; /* price solve: augmenting paths taken; auction: negative cycles cancelled */
 } maxscore_stats;
 
 /* Bytes of device scratch the calls below need for these sizes (0 on invalid sizes). */
@@ -149,6 +154,11 @@ int32_t maxscore_softtopk_reading(const float *logits, int32_t T, int32_t E, int
                                   int32_t quant_shift, int32_t reading, float *scores, int32_t *q, void *stream);
 
 /* a4.  Exact assignment on integer rewards q[T,E] (Eq. 7-8, Table 1: maximum flow, then maximum score).
+ * Two solvers reach the same optimum.  A price solve (equilibrium prices, then shortest augmenting paths) takes the calls
+ * with one capacity for all experts and one k for all tokens, 2 <= E <= 512, up to 524288 tokens (k <= 8; half as many for
+ * every doubling of k beyond), beyond 64 experts at least three pairs per expert, no flags and max_rounds >= 60.  An
+ * eps-scaling auction with a cycle-cancelling finisher takes all others, and those whose price solve does not stand
+ * (rewards too wide for its packed keys, too many exchanges near the equilibrium).
  *   assign[T,k] : expert ids per token, distinct, ascending slot order is arbitrary.  With more demand than
  *                 capacity (see above) a row holds fewer than k experts, first in the row, then -1; the prices
  *                 then belong to the padded problem and certify nothing by themselves.

@@ -113,6 +113,9 @@ int32_t kvec_check(const int32_t *kvec, int T, int E, int k, char *ws, long long
 // exchanges may do it, retry > 0 counts these; anything else: the auction has to solve the problem).
 // k <= E <= kPriceMaxE, one capacity for all experts, any relation of demand and capacity (rows that cannot be filled
 // end in -1).
+// Up to kPriceTries tries of up to kPriceTryPasses passes: a caller's round cap below that goes to the auction, which ends at
+// the cap with what it has.
+constexpr int kPriceTries = 3, kPriceTryPasses = 20;
 struct PriceGeometry {
     int rows, n_wg;          // blocks of rows over which the pairs are counted (WorkspaceLayout::wcnt_off)
     int one_launch;          // all price passes were one launch

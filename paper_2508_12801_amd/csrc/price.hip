@@ -69,7 +69,9 @@ constexpr int kEnough = 3, kWorst = 2;            // the passes end when a third
 constexpr int kLevelPairs = 4;                    // exchanges of a row that the common step looks at
 constexpr int kSmallEntries = 1 << 16;            // rewards of a batch that one workgroup passes over by itself
 constexpr int kSmallThreads = 4096;               // ... with this many lanes at work in all
-constexpr int kSmallPasses = 20;
+constexpr int kSmallPasses = kPriceTryPasses;
+constexpr int kSampledPasses = 2, kTightPasses = 6, kSlackPasses = 9, kRetryPasses = 4;
+static_assert(kSampledPasses + kSlackPasses <= kPriceTryPasses, "the round cap of a call allows every pass");
 constexpr int kPRowsMax = 128;                    // rows of a block of the final pass at most
 constexpr int kPriceWordDone = 0, kPriceWordPasses = 1;      // pinned words of the calling thread
 enum { kModeTight = 0, kModeSlack = 1, kModeOver = 2 };
@@ -1361,7 +1363,7 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     // next to no spare capacity (as from rounding T*k/E up): nearly every expert ends full, and the first passes spread
     // what is spare evenly
     const int stride = T / kSampleRows;
-    const int n_sampled = stride >= 2 && !prices_in && !retry ? 2 : 0;
+    const int n_sampled = stride >= 2 && !prices_in && !retry ? kSampledPasses : 0;
     a.even = spare > 0 && spare * 64 <= (long long)E * C && !prices_in && !retry ? (n_sampled ? 4 : 3) : 0;
     a.arcs_wanted = std::min(kArcsPerExpert * E, kArcsWanted);
     a.retry = retry > 0 ? 1 : 0;
@@ -1383,7 +1385,7 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     auto mark = [&] { mrc = mrc ? mrc : solver_mark(s); };
     const bool os = a.mode == kModeOver;
     const size_t shm = sizeof(int) * (size_t)price_table_ints(E, a.mode == kModeTight);
-    const int n_pass = n_sampled + (retry ? 4 : a.mode == kModeSlack ? 9 : 6);
+    const int n_pass = n_sampled + (retry ? kRetryPasses : a.mode == kModeSlack ? kSlackPasses : kTightPasses);
     const bool small = (long long)T * G <= kSmallThreads && (long long)T * E <= kSmallEntries && shm + sizeof(StepLds) <= 64 * 1024;
     const int plim = (1 << (31 - a.ib)) - 1;
     geom->one_launch = small ? 1 : 0;

@@ -1915,9 +1915,6 @@ static int32_t add_launch_times(SolverHost *hs, size_t first, int n, int kernels
         }                                        \
     } while (0)
 
-// Calls with fewer rounds than this to spend go to the auction (a price solve has up to seven price passes).
-constexpr int kPriceMinRounds = 16;
-constexpr int kPriceTries = 3;
 constexpr long long kPriceMinPairs = 3;           // pairs per expert (with fewer the margins are too wide to step by)
 
 int32_t price_run(const int32_t *q, int T, int E, int k, int C, const maxscore_opts &o, int32_t *assign, int64_t *prices,
@@ -1926,7 +1923,7 @@ int32_t price_run(const int32_t *q, int T, int E, int k, int C, const maxscore_o
 {
     *solved = false;
     if (!price_supported(T, E, k) || (k == E && T > C) || (E > 64 && (long long)T * k < kPriceMinPairs * E) ||
-        o.max_rounds < kPriceMinRounds ||
+        o.max_rounds < kPriceTries * kPriceTryPasses ||         // (it counts its passes itself: the cap has to allow them all)
         (o.flags & (MAXSCORE_FLAG_NO_TAIL_PASS | MAXSCORE_FLAG_NO_FINISHER)))
         return MAXSCORE_OK;
     SolverHost *hs = nullptr;
