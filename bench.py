@@ -31,6 +31,55 @@ def profile_value(name, key):
     return None
 
 
+def hbm_frac(nbytes, ms):
+    """Share of the HBM peak at which `nbytes` move in `ms` milliseconds (None where nothing was timed)."""
+    return nbytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS if ms > 0 else None
+
+
+def solver_roofline(st: dict, T: int, E: int, k: int, solve_ms: float, gd_ms: float):
+    """The assignment + gates + dispatch passes as a whole: the algorithmic bytes of the rounds that the solver executed, over
+    its device time and that of gates + dispatch.  `st`: statistics of a solve with kernel timing on."""
+    price = st["phases"] == 1 and st["finish_passes"] == 1       # otherwise the auction has solved it
+    blocks = (T + 127) // 128
+    q_bytes, pair_bytes, count_bytes = T * E * 4, T * k * 4, blocks * E * 4
+    # assignment and scores at the assigned pairs; gates, the two dispatch lists and the positions
+    gd_bytes = T * k * (4 + 4 + 4) + T * k * (4 + 4) + T * k * 12 + 4 * (E + 1)
+    if price:
+        # a pass reads the rewards (the first two of a large batch 8192 rows of them); the last one, which is not among the
+        # rounds, reads them and writes the assignment and the counts per block; the few thousand rows that the search
+        # reads are not counted
+        sampled = 2 if T >= 2 * 8192 else 0
+        passes = [8192 * E * 4] * min(sampled, st["rounds"]) + [q_bytes] * max(st["rounds"] - sampled, 0)
+        solver_bytes = sum(passes) + q_bytes + pair_bytes + count_bytes
+        first, second = ("k_price", sum(passes) / max(len(passes), 1)), ("k_price_update", None)
+        names = "k_price and k_price_update per pass, k_price_assign, k_price_finish"
+    else:
+        # the bid pass reads rewards and assignment and writes the bid keys, the select pass reads the keys and the counts; a
+        # pass of the finisher scans both and reads and clears its arc matrix
+        bid_bytes, sel_bytes = q_bytes + pair_bytes + T * k * 8, T * k * 8 + count_bytes
+        solver_bytes = st["rounds"] * (bid_bytes + sel_bytes) + st["finish_passes"] * (sel_bytes + 2 * E * E * 8)
+        first, second = ("k_bid", bid_bytes), ("k_select", sel_bytes)
+        names = "k_bid and k_select per round, the finisher"
+    launches = st["bid_launches"]
+
+    def per_launch(name, nbytes, total_ms):
+        out = {"launches": launches, "launch_us": total_ms * 1e3 / launches if launches else None,
+               "share_of_solver_time": total_ms / st["solver_ms"] if st["solver_ms"] > 0 else None}
+        if nbytes is not None:
+            out.update(bytes_per_launch=nbytes, frac=hbm_frac(nbytes * launches, total_ms))
+        return {name: out}
+
+    nbytes, ms = solver_bytes + gd_bytes, solve_ms + gd_ms
+    floor_bytes = q_bytes + pair_bytes + 8 * E
+    return {"bound": "hbm", "kernel": f"assignment + gates + dispatch passes ({names}, the gates and dispatch kernels)",
+            "achieved": nbytes / (ms * 1e-3) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": hbm_frac(nbytes, ms),
+            "target_frac": 0.5, "bytes": nbytes, "ms": ms, "solver": "price" if price else "auction", "rounds": st["rounds"],
+            "finisher_passes": st["finish_passes"], "finisher_cycles": st["finish_cycles"],
+            "fraction_floor": hbm_frac(floor_bytes, ms), "floor_bytes": floor_bytes,
+            "kernels": {**per_launch(*first, st["bid_ms"]), **per_launch(*second, st["select_ms"]),
+                        "gates_dispatch": {"bytes": gd_bytes, "us": gd_ms * 1e3, "frac": hbm_frac(gd_bytes, gd_ms)}}}
+
+
 def cpu_baseline(name: str, sample_T: int):
     """The CPU checker as it stands, timed on the host cores over a bounded sample of the workload."""
     import numpy as np
@@ -125,34 +174,22 @@ def main():
     soft_ms = timed(lambda: ms.softtopk(logits, k, r.t))
     # a1..a3 as the whole path runs them where it can: one kernel, the scores come out of the projection's accumulators
     fused_ms = timed(lambda: ms.router_softtopk(x, W, b, k, r.t))
-    fused_nolog_ms = timed(lambda: ms.router_softtopk(x, W, b, k, r.t, want_logits=False))
+    try:
+        fused_nolog_ms = timed(lambda: ms.router_softtopk(x, W, b, k, r.t, want_logits=False))
+    except ms.MaxScoreError:                 # sizes whose scores take a kernel of their own need the logits
+        fused_nolog_ms = None
     gates_ms = timed(lambda: ms.gates(out["scores"], out["assign"]))
     disp_ms = timed(lambda: ms.dispatch(out["assign"], out["gates"], E, C))
     solve_ms = sorted(ms.assign_i32(out["q"], k, C)["stats"]["solver_ms"] for _ in range(5))[2]   # median, untimed launches
     ms.set_kernel_timing(True)
-    a = ms.assign_i32(out["q"], k, C)
+    st = ms.assign_i32(out["q"], k, C)["stats"]
     ms.set_kernel_timing(False)
-    st = a["stats"]
-    rounds = max(st["bid_launches"], 1)
-    bid_launch_ms = st["bid_ms"] / rounds
-    sel_launch_ms = st["select_ms"] / rounds
-    # algorithmic bytes per launch: the bid pass reads rewards and assignment and writes the bid keys; the select
-    # pass reads the keys and the per-workgroup counts; gates + dispatch read assignment and scores at the assigned
-    # pairs and write gates, the two dispatch lists and the positions
-    n_wg = (T + 127) // 128
-    bid_bytes = T * E * 4 + T * k * 4 + T * k * 8
-    sel_bytes = T * k * 8 + n_wg * E * 4
-    gd_bytes = T * k * (4 + 4 + 4) + T * k * (4 + 4) + T * k * 12 + 4 * (E + 1)
-    # finisher: every pass scans the bid keys and the per-block counts and reads and clears the arc matrix; the
-    # rows it reads beyond that are a few thousand (not counted)
-    fin_bytes = st["finish_passes"] * (T * k * 8 + n_wg * E * 4 + 2 * E * E * 8)
-    pass_bytes = st["rounds"] * (bid_bytes + sel_bytes) + fin_bytes + gd_bytes
-    # gates + dispatch as the routing calls run them: from the solver's final key blocks, two launches (the separate
+    # gates + dispatch as the routing calls run them: from the solver's counts per block, two launches (the separate
     # maxscore_gates / maxscore_dispatch entry points are timed above)
     gd_ms = sorted(ms.route_scores(out["scores"], k, C)["stats"]["gates_dispatch_ms"] for _ in range(5))[2]
-    pass_ms = solve_ms + gd_ms
-    pass_gbs = pass_bytes / (pass_ms * 1e-3) / 1e9
-    floor_bytes = 4 * T * E + 4 * T * k + 8 * E
+    roofline = solver_roofline(st, T, E, k, solve_ms, gd_ms)
+    if args.config == "cfg5":
+        roofline["traffic"] = profile_value("pass_cfg5_pmc_traffic.txt", "pass_traffic_bytes")
     # plain copy kernel of the same footprint: achievable-bandwidth reference
     src = torch.empty(256 << 20, dtype=torch.uint8, device=dev)
     dst = torch.empty_like(src)
@@ -204,7 +241,7 @@ def main():
                                       "latency_ms_per_call": sum(r_[0] for r_ in res) / n_streams / n_calls * 1e3}
     del batches
 
-    # the same solve with the auction running down to eps = 1 itself (no finisher), for comparison
+    # the same problem solved by the auction, running down to eps = 1 itself (no finisher), for comparison
     auction_only = ms.assign_i32(out["q"], k, C, finisher=False)["stats"]
     auction_only = {"solver_ms": sorted(ms.assign_i32(out["q"], k, C, finisher=False)["stats"]["solver_ms"]
                                        for _ in range(3))[1], "rounds": auction_only["rounds"]}
@@ -241,7 +278,7 @@ def main():
     y = ms.combine(buf, out["assign"], out["token_pos"], out["gates"])
     dtok_ms = timed(lambda: ms.dispatch_tokens(x, out["expert_offsets"], out["disp_token"], E, C, out=buf), n=5)
     comb_ms = timed(lambda: ms.combine(buf, out["assign"], out["token_pos"], out["gates"], out=y), n=5)
-    dtok_bytes = T * k * d * eb + E * C * d * eb
+    dtok_bytes = T * d * eb + E * C * d * eb                  # every row of x once, the buffers once
     comb_bytes = T * k * d * eb + T * d * 4
     movement = {
         "dispatch_tokens": {"ms": dtok_ms, "bytes": dtok_bytes, "GBps": dtok_bytes / (dtok_ms * 1e-3) / 1e9,
@@ -324,43 +361,16 @@ def main():
         "metric": "routed tokens/sec", "value": T / (ms_per_step * 1e-3), "unit": "tokens/s",
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms_per_step,
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "bf16 inputs, fp32 accumulation and scores, int32 rewards, int64 bid keys",
+        "dtype": "bf16 inputs, fp32 accumulation and scores, int32 rewards and prices",
         "data": "synthetic",
         "config": {"workload": f"{args.config}: T={T} d={d} E={E} k={k} C={C} {r.dtype} inputs, t={r.t}, "
                                "whole path x,W -> logits -> SoftTopk -> exact assignment -> gates -> dispatch",
                    "latency_ms_per_call": ms_per_step, "latency_ms_median": srt[len(srt) // 2],
                    "latency_ms_min": srt[0], "latency_ms_max": srt[-1], "first_call_ms": first_call_ms,
                    "solver_rounds": stats["rounds"], "solver_phases": stats["phases"]},
-        # the assignment + dispatch passes as a whole: algorithmic bytes of every solver round actually executed
-        # (bid pass + select pass) plus gates and dispatch, over the device time of solver + gates + dispatch
-        "roofline": {"bound": "hbm", "kernel": "assignment + gates + dispatch passes (k_bid and k_select per "
-                                               "solver round, then the gates and dispatch kernels)",
-                     "achieved": pass_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": pass_gbs / HBM_PEAK_GBS,
-                     "target_frac": 0.5,
-                     "traffic": profile_value("pass_cfg5_pmc_traffic.txt", "pass_traffic_bytes")
-                     if args.config == "cfg5" else None,
-                     "bytes": pass_bytes, "ms": pass_ms, "rounds": st["rounds"],
-                     "finisher_passes": st["finish_passes"], "finisher_cycles": st["finish_cycles"],
-                     "fraction_floor": floor_bytes / (pass_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                     "floor_bytes": floor_bytes,
-                     "kernels": {
-                         "k_bid": {"bytes_per_launch": bid_bytes, "launch_us": bid_launch_ms * 1e3,
-                                   "launches": st["bid_launches"],
-                                   "frac": bid_bytes / (bid_launch_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                                   "share_of_solver_time": st["bid_ms"] / max(st["solver_ms"], 1e-9),
-                                   "traffic": profile_value("k_bid_cfg5_pmc_traffic.txt", "k_bid_traffic_bytes")
-                                   if args.config == "cfg5" else None},
-                         "k_select": {"bytes_per_launch": sel_bytes, "launch_us": sel_launch_ms * 1e3,
-                                      "launches": st["bid_launches"],
-                                      "frac": sel_bytes / (sel_launch_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                                      "share_of_solver_time": st["select_ms"] / max(st["solver_ms"], 1e-9),
-                                      "note": "mean over all rounds; the tail pass runs inside some of these "
-                                              "launches (one workgroup, latency-bound)"},
-                         "gates_dispatch": {"bytes": gd_bytes, "us": gd_ms * 1e3,
-                                            "frac": gd_bytes / (gd_ms * 1e-3) / 1e9 / HBM_PEAK_GBS}},
-                     "copy_kernel_GBs": copy_gbs,
-                     "note": "frac is below the 0.5 target: the passes are bound by launch and chain latency, "
-                             "not by bytes"},
+        "roofline": {**roofline, "copy_kernel_GBs": copy_gbs,
+                     "note": "frac is below the 0.5 target: the passes are few and bound by launch and chain latency, not by "
+                             "bytes"},
         "stages_ms": {"router_gemm": gemm_ms, "softtopk_quantise": soft_ms,
                       "router_gemm_softtopk_one_kernel": fused_ms,
                       "router_gemm_softtopk_one_kernel_no_logits": fused_nolog_ms,
