@@ -223,7 +223,7 @@ int32_t maxscore_scores_op(const float *logits, int32_t T, int32_t E, int32_t k,
  * with the column counts of P taken from expert_offsets[E+1] (output of maxscore_dispatch).  Device outputs:
  * loss[1]; mean_scores[E] (may be NULL); dscores_col[E] (may be NULL) = d loss / d scores[i, j], which is the
  * same for every token i: lambda / (E*T) * mean_i(P[i, j]) (P is a constant).  Column sums are accumulated in
- * a fixed order (fp32 inside a block of rows, fp64 across blocks): the result is deterministic.  Workspace as
+ * a fixed order (fp32 over 16 rows, fp64 beyond): the result is deterministic.  Workspace as
  * for the other calls (any k); only enqueues.
  *
  * maxscore_gates_backward: d loss / d logits through the gates of Eq. 2 with the SoftTopk scores of Eq. 6.

@@ -8,32 +8,45 @@
 namespace maxscore {
 namespace {
 
-constexpr int kColBlocksMax = 256;
+constexpr int kColBlocksMax = 256, kColRows = 16;
 
 // part[b][j] <- sum of scores[row][j] over the rows of block b.  blockDim = 256 = cols x rowlanes; a thread owns
-// VEC adjacent columns (VEC = 4 when E is a multiple of 4) and keeps several row loads in flight.
+// VEC adjacent columns (VEC = 4 when E is a multiple of 4) and keeps kColRows row loads in flight.  Their sum is added in fp32,
+// everything from there on in double: the mean of a column is good to kColRows roundings whatever the number of rows.
 template <int VEC>
 __global__ __launch_bounds__(256) void k_colsum(const float *__restrict__ scores, int T, int E, int cols,
                                                 int rows_per_block, float *__restrict__ part)
 {
-    extern __shared__ float s_acc[];     // [rowlanes][E]
+    extern __shared__ double s_acc[];    // [rowlanes][E]
     typedef float vec_t __attribute__((ext_vector_type(VEC)));
+    typedef double wide_t __attribute__((ext_vector_type(VEC)));
     const int rowlanes = 256 / cols, nvec = E / VEC;
     const int c = threadIdx.x % cols, rl = threadIdx.x / cols;
     const int r0 = blockIdx.x * rows_per_block;
     const int r1 = r0 + rows_per_block < T ? r0 + rows_per_block : T;
     const vec_t *src = reinterpret_cast<const vec_t *>(scores);
     for (int jv = c; jv < nvec; jv += cols) {
-        vec_t acc = 0.f;
-#pragma unroll 16
-        for (int r = r0 + rl; r < r1; r += rowlanes) acc += src[(size_t)r * nvec + jv];
-        *reinterpret_cast<vec_t *>(&s_acc[rl * E + jv * VEC]) = acc;
+        wide_t acc = 0.0;
+        for (int r = r0 + rl; r < r1; r += kColRows * rowlanes) {
+            vec_t x[kColRows];
+#pragma unroll
+            for (int u = 0; u < kColRows; ++u) {
+                const int ru = r + u * rowlanes;
+                x[u] = src[(size_t)(ru < r1 ? ru : r1 - 1) * nvec + jv];
+            }
+            vec_t sum = x[0];
+#pragma unroll
+            for (int u = 1; u < kColRows; ++u) sum += r + u * rowlanes < r1 ? x[u] : (vec_t)0.f;
+            acc += __builtin_convertvector(sum, wide_t);
+        }
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) s_acc[rl * E + jv * VEC + i] = acc[i];
     }
     __syncthreads();
     for (int j = threadIdx.x; j < E; j += 256) {
-        float acc = 0.f;
+        double acc = 0.0;
         for (int l = 0; l < rowlanes; ++l) acc += s_acc[l * E + j];
-        part[(size_t)blockIdx.x * E + j] = acc;
+        part[(size_t)blockIdx.x * E + j] = (float)acc;
     }
 }
 
@@ -176,7 +189,7 @@ int32_t aux_loss_run(const float *scores, const int32_t *offsets, int T, int E, 
     if (n_blocks > L.max_wg) n_blocks = L.max_wg;
     const int rows_per_block = (T + n_blocks - 1) / n_blocks;
     n_blocks = (T + rows_per_block - 1) / rows_per_block;
-    const size_t shm = (size_t)rowlanes * E * sizeof(float);
+    const size_t shm = (size_t)rowlanes * E * sizeof(double);
     if (vec == 4)
         hipLaunchKernelGGL(k_colsum<4>, dim3(n_blocks), dim3(256), shm, s, scores, T, E, cols, rows_per_block, part);
     else
