@@ -4,6 +4,7 @@
 // The rank multipliers of Eq. 6 are piecewise constant in the logits, so A_ij = m_ij * Softmax(L_i)_j gives
 // dA_ij/dL_il = A_ij * (delta_jl - p_il): the backward pass needs the logits (for p) and the scores, not t or k.
 #include "common.h"
+#include "sums.h"
 
 namespace maxscore {
 namespace {
@@ -134,14 +135,12 @@ __global__ __launch_bounds__(256) void k_gates_backward(const float *__restrict_
 #pragma unroll
         for (int m = 0; m < EPL; ++m) mx = fmaxf(mx, l[m]);
         for (int off = G / 2; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-        float z = 0.f, w = 0.f;
 #pragma unroll
         for (int m = 0; m < EPL; ++m) {
             l[m] = __expf(l[m] - mx);        // padded columns: exp(-inf) = 0
-            z += l[m];
             g[m] *= a[m];                    // w_j = gA_j * A_j
-            w += g[m];
         }
+        float z = tree_sum<EPL>(l), w = tree_sum<EPL>(g);
         for (int off = G / 2; off >= 1; off >>= 1) {
             z += __shfl_xor(z, off);
             w += __shfl_xor(w, off);

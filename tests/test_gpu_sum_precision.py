@@ -27,3 +27,26 @@ def test_column_means(ms, T, E):
     worst = float(((got - c.double()).abs() / c.double()).max())
     print(worst / ULP, flush=True)
     assert worst <= 17 * ULP
+
+
+@pytest.mark.parametrize("E,G,EPL", [(32, 8, 4), (64, 16, 4), (128, 16, 8), (256, 32, 8), (512, 64, 8), (1024, 64, 16)])
+def test_gate_backward_sums(ms, E, G, EPL):
+    """A row's sum of gA_j * A_j rounds log2(E) times, as a tree of its E terms does.  Here G lanes hold EPL columns each: added up
+    one by one, each of lane 0's further columns, and each of the lanes it meets, is lost in a tie beside the 1 of its first
+    column.  Softmax of equal logits and the division by their number are exact, so a column without a score shows the sum."""
+    levels = E.bit_length() - 1
+    print(f"gate backward sums E={E}", flush=True)
+    scores = torch.zeros(4, E)
+    for m in range(EPL):
+        scores[:, (m >> 2) * 4 * G + (m & 3)] = ULP if m else 1.0
+    off = 1
+    while off < G:
+        scores[:, 4 * off] = ULP
+        off *= 2
+    assign = torch.full((4, 1), -1, dtype=torch.int32, device="cuda")
+    got = ms.gates_backward(torch.zeros(4, E, device="cuda"), scores.cuda(), assign, torch.zeros(4, 1, device="cuda"),
+                            torch.ones(E, device="cuda")).cpu().double()
+    total = scores.double().sum(dim=1, keepdim=True)
+    error = float(((-got * E / total - 1)[scores == 0]).abs().max())
+    print(error / ULP, "of", levels, flush=True)
+    assert error <= levels * ULP
