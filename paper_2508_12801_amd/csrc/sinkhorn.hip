@@ -6,15 +6,20 @@
 //   column targets m_j = caps_j * T / sum(caps);  v = 1;  n_iter times: u_i = 1 / sum_j K_ij v_j,
 //   v_j = m_j / sum_i K_ij u_i;  plan_ij = u_i K_ij v_j;  second expert = arg-max_j plan_ij (ties to the lower
 //   id; -1 when the row is all zero).
-// Three ways to do it, by size; column sums are added in a fixed order everywhere, beyond a few rows in double:
+// Three ways to do it, by size; column sums are added in a fixed order everywhere, beyond four rows in double where one
+// workgroup does it all, from the first on with eight lanes to a row; row sums are trees over the columns:
 //   small    up to 65536 scores of up to 16 experts, half as many of up to 64: the whole call is one workgroup that keeps
-//            K in registers, a thread owns whole rows.  An iteration takes 2 to 4 us (two barriers and six exchanges), two
-//            launches each 8.
+//            K in registers, a thread owns whole rows.  An iteration takes 4 us (two barriers and six exchanges), two launches
+//            each 8.  The limit is that of the registers: 1024 threads of 64 entries, 512 beyond 16 columns.
 //   medium   up to 64 experts: eight lanes per row, K recomputed from the scores; one launch per iteration, whose
 //            workgroups begin by adding up the column sums of the iteration before
 //   large    one wavefront per row, lane l holds experts l, l+64, ...; rows and columns are launches of their own
-// 20 iterations: 4096 tokens, 16 experts 228 to 95 us; 16384 and 64 350 to 219 us; 65536 and 64 574 to 315 us.
+// 20 iterations, before and after the first two ways: 4096 tokens of 16 experts 228 and 90 us (4097, the first the medium way
+// takes, 142), 16384 of 64 350 and 213 us, 65536 of 64 574 and 315 us.
+#include <type_traits>
+
 #include "common.h"
+#include "sums.h"
 
 namespace maxscore {
 namespace {
@@ -130,36 +135,36 @@ __device__ __forceinline__ float sk_column(double sum, float m)
 // ---- small: everything in one workgroup ----
 
 // Column sums over a wavefront: lanes exchange halves of their columns until every lane holds the sum of one of them (the
-// last steps of EP < 64 add equal columns); in double from the sum of eight rows on.
-template <int HALF, int OFF, int N, typename V>
-__device__ __forceinline__ void sk_exchange(V (&f)[N], int lane, int &column)
+// last steps of EP < 64 add equal columns).  A thread comes with the sums of its own 64 / EP rows.  Up to four rows are added in
+// fp32, sums of four rows in double; what lanes exchange for the first of these additions is still an fp32 number.
+template <int HALF, int OFF, int N, typename V, typename W>
+__device__ __forceinline__ void sk_exchange(const V (&f)[N], W (&sum)[HALF], int lane, int &column)
 {
     const bool up = (lane & OFF) != 0;
     column |= up ? HALF : 0;
 #pragma unroll
     for (int c = 0; c < HALF; ++c) {
         const V give = up ? f[c] : f[c + HALF], keep = up ? f[c + HALF] : f[c];
-        f[c] = keep + __shfl_xor(give, OFF);
+        sum[c] = (W)keep + (W)__shfl_xor(give, OFF);
     }
 }
 
-template <int EP>
-__device__ __forceinline__ double sk_reduce_scatter(float (&f)[EP], int lane, int &column)
+template <int EP, int OFF, typename V>
+__device__ __forceinline__ double sk_reduce_scatter(const V (&f)[EP], int lane, int &column)
 {
-    column = 0;
-    if constexpr (EP >= 64) sk_exchange<32, 32>(f, lane, column);
-    if constexpr (EP >= 32) sk_exchange<16, EP == 32 ? 32 : 16>(f, lane, column);
-    if constexpr (EP >= 16) sk_exchange<8, EP == 16 ? 32 : EP == 32 ? 16 : 8>(f, lane, column);
-    constexpr int O = EP == 8 ? 32 : EP == 16 ? 16 : EP == 32 ? 8 : 4;
-    double d[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) d[c] = (double)f[c];
-    sk_exchange<4, O>(d, lane, column);
-    sk_exchange<2, O / 2>(d, lane, column);
-    sk_exchange<1, O / 4>(d, lane, column);
-#pragma unroll
-    for (int off = O / 8; off >= 1; off >>= 1) d[0] += __shfl_xor(d[0], off);
-    return d[0];
+    if constexpr (EP > 16) {                    // (one row so far with 64 columns, two with 32)
+        V h[EP / 2];
+        sk_exchange<EP / 2, OFF>(f, h, lane, column);
+        return sk_reduce_scatter<EP / 2, OFF / 2>(h, lane, column);
+    } else if constexpr (EP > 1) {
+        double h[EP / 2];
+        sk_exchange<EP / 2, OFF>(f, h, lane, column);
+        return sk_reduce_scatter<EP / 2, OFF / 2>(h, lane, column);
+    } else {
+        double d = f[0];
+        for (int off = OFF; off >= 1; off >>= 1) d += __shfl_xor(d, off);
+        return d;
+    }
 }
 
 // threads: as many as there are rows, up to the register budget of 64 scores each
@@ -172,6 +177,7 @@ __global__ __launch_bounds__(kSkSmallThreads<EP>) void k_sk_small(const float *_
                                                    int32_t *__restrict__ caps)
 {
     constexpr int RR = 64 / EP;                 // rows per thread: r * nt + tid
+    using Acc = std::conditional_t<(RR > 4), double, float>;
     __shared__ int s_cnt[EP];
     __shared__ float s_target[EP];
     __shared__ __attribute__((aligned(16))) float s_v[EP];
@@ -227,22 +233,24 @@ __global__ __launch_bounds__(kSkSmallThreads<EP>) void k_sk_small(const float *_
 #pragma unroll
         for (int c = 0; c < EP; ++c) x[r][c] = s_target[c] > 0.f ? expf((x[r][c] - mx[r]) * inv_tau) : 0.f;     // K_ij
     for (int it = 0; it < n_iter; ++it) {
-        float acc[EP];
 #pragma unroll
-        for (int c = 0; c < EP; ++c) acc[c] = 0.f;
+        for (int r = 0; r < RR; ++r) u[r] = r * nt + tid < T ? 1.f / tree_dot<EP>(x[r], s_v) : 0.f;
+        Acc acc[EP];
 #pragma unroll
-        for (int r = 0; r < RR; ++r) {
-            if (r * nt + tid >= T) continue;
-            // four chains: one of EP dependent additions would set the pace
-            float s4[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int c = 0; c < EP; ++c) {
+            float s[(RR + 3) / 4];              // of up to four rows, pairwise
 #pragma unroll
-            for (int c = 0; c < EP; ++c) s4[c & 3] += x[r][c] * s_v[c];
-            u[r] = 1.f / ((s4[0] + s4[1]) + (s4[2] + s4[3]));
-#pragma unroll
-            for (int c = 0; c < EP; ++c) acc[c] += x[r][c] * u[r];
+            for (int g = 0; g < (RR + 3) / 4; ++g) {
+                const int r = 4 * g;
+                s[g] = x[r][c] * u[r];
+                if constexpr (RR > 1) s[g] += x[r + 1][c] * u[r + 1];
+                if constexpr (RR > 2) s[g] += x[r + 2][c] * u[r + 2] + x[r + 3][c] * u[r + 3];
+            }
+            acc[c] = s[0];
+            if constexpr (RR > 4) acc[c] += (double)s[1];
         }
-        int column;
-        const double sum = sk_reduce_scatter<EP>(acc, lane, column);
+        int column = 0;
+        const double sum = sk_reduce_scatter<EP, 32>(acc, lane, column);
         if (EP == 64 || lane % (64 / EP) == 0) s_red[wv * EP + column] = sum;
         __syncthreads();
         if (wv == 0) {
@@ -366,12 +374,9 @@ __global__ __launch_bounds__(kSkThreads) void k_sk_iter(const float *__restrict_
             if (c0 + c < E) mx = fmaxf(mx, x[c]);
         }
         for (int off = 1; off < 8; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-        float s = 0.f;
 #pragma unroll
-        for (int c = 0; c < EPL; ++c) {
-            x[c] = open[c] ? expf((x[c] - mx) * inv_tau) : 0.f;
-            s += x[c] * vv[c];
-        }
+        for (int c = 0; c < EPL; ++c) x[c] = open[c] ? expf((x[c] - mx) * inv_tau) : 0.f;
+        float s = tree_dot<EPL>(x, vv);
         for (int off = 1; off < 8; off <<= 1) s += __shfl_xor(s, off);
         const float ui = 1.f / s;
         if (row < T) {

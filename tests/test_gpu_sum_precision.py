@@ -50,3 +50,28 @@ def test_gate_backward_sums(ms, E, G, EPL):
     error = float(((-got * E / total - 1)[scores == 0]).abs().max())
     print(error / ULP, "of", levels, flush=True)
     assert error <= levels * ULP
+
+
+@pytest.mark.parametrize("T,E,order", [(512, 64, "chains"), (1024, 32, "chains"), (4096, 16, "chains"), (600, 64, "lanes"), (1100, 32, "lanes")])
+def test_sinkhorn_row_sums(ms, T, E, order):
+    """u = 1 / (sum of a row of K) after one iteration, from the plan's ratio to that of a row whose sum is exactly 1.  The sum rounds
+    log2(E) times as a tree; u and the plan's entry round once each.  Beside the row's one entry of 1 there are entries just short
+    of a tie: at every fourth column, as four chains add them, or where one lane of eight adds its own one by one and then meets
+    the others."""
+    print(f"sinkhorn row sums T={T} E={E} {order}", flush=True)
+    levels, M, t = E.bit_length() - 1, 200.0, 0.99 * ULP
+    scores = torch.zeros(T, E)
+    scores[:, E - 1] = M + 1                                  # everybody's first choice: its residual affinity is 0, its K too
+    low = M + float(np.log(t))
+    epl = E // 8
+    cols = list(range(4, E - 1, 4)) if order == "chains" else list(range(1, epl)) + [epl, 2 * epl, 4 * epl]
+    scores[0::2, 0] = M
+    scores[1::2, 0] = M
+    scores[0::2, cols] = low
+    out = ms.assign_top1_sinkhorn(scores.cuda(), T, 1.0, 1, want_plan=True)
+    plan = out["plan"].cpu().double()[:, 0]
+    K = np.exp(scores.double().numpy()[0, cols] - M).sum()
+    ratio = float(plan[0] / plan[1])
+    error = abs(ratio * (1 + K) - 1)
+    print(error / ULP, "of", levels + 2, flush=True)
+    assert error <= (levels + 2) * ULP
