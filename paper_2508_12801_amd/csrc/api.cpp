@@ -31,7 +31,7 @@ WorkspaceLayout workspace_layout(int T, int E, int k, int d)
     L.finm_off = off; off = align_up(off + sizeof(unsigned long long) * (size_t)kFinMatrixMaxE * kFinMatrixMaxE, 256);
     // finisher arc lists: one segment per key block (fin_seg_cap(rows, k) arcs of 12 bytes each) and a count per block
     L.tri_off = off; off = align_up(off + 12 * fin_tri_entries(T, k, L.max_wg) + sizeof(int) * ((size_t)L.max_wg + 1), 256);
-    L.price_off = off; off = align_up(off + price_area_bytes(T, E, k, L.max_wg), 256);    // tables of the price solve
+    L.price_off = off; off = align_up(off + price_area_bytes(T, k, L.max_wg), 256);    // tables of the price solve
     L.wt_off = off; off = align_up(off + sizeof(unsigned short) * (size_t)E * (d > 0 ? d : 0), 256);
     L.total = off;
     return L;

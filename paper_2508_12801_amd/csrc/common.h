@@ -121,12 +121,21 @@ struct PriceGeometry {
     int one_launch;          // all price passes were one launch
 };
 bool price_supported(int T, int E, int k);
-// tables, and two words per block; the iterative assignment keeps its own there, with counts per (slot, 64 tokens, expert)
-inline size_t price_area_bytes(int T, int E, int k, int max_wg)
+// tables, and two words per block; the iterative assignment keeps its own there, with a word per (slot, 64 tokens)
+inline size_t price_area_bytes(int T, int k, int max_wg)
 {
     const size_t price = 864 * 1024 + 16 * (size_t)max_wg, blocks = ((size_t)T + 63) / 64;
-    const size_t iter = 4 * (size_t)kMaxE * 16 + 16 * blocks + 4 * blocks * k * ((size_t)E + 1);
+    const size_t iter = 4 * (size_t)kMaxE * 16 + 16 * blocks + 4 * blocks * k;
     return price > iter ? price : iter;
+}
+// The iterative assignment's proposals per (slot, 64 tokens, expert).  They lie behind its result, the pairs per (64 tokens,
+// expert) at WorkspaceLayout::wcnt_off, up to price_off at most: the auction, the finisher and the dispatch, whose regions these
+// are, run after it or not at all.  A word each where that fits, which it does up to 128 experts or 34 slots, else a byte.
+inline size_t iter_tiles(int T, int E, int k) { return ((size_t)T + 63) / 64 * k * E; }
+inline size_t iter_tiles_off(const WorkspaceLayout &L, int T, int E) { return L.wcnt_off + (4 * (((size_t)T + 63) / 64) * E + 255) / 256 * 256; }
+inline bool iter_tiles_are_words(const WorkspaceLayout &L, int T, int E, int k)
+{
+    return iter_tiles_off(L, T, E) + 4 * iter_tiles(T, E, k) <= L.price_off;
 }
 // Pinned words of the calling thread (16 of them, cleared by whoever uses them), and the same as the device sees them.
 int32_t solver_words(int **host, int **dev);

@@ -12,7 +12,7 @@
 //   k_iter_step   a block of 64 tokens takes the outcome of the round before and proposes for the holes that are left; a
 //                 wavefront is 64 tokens of one slot, whose proposals per expert it counts
 //   k_iter_scan   per expert: an expert with room for all its proposals needs no order; for the others the counts of
-//                 the blocks before, slot by slot, become the positions that the next step compares with the room
+//                 the blocks before, slot by slot, tell how many of a block's proposals there is room for
 // Rounds are enqueued two ahead of the one that runs; the first round without proposals ends them, and what is still
 // queued leaves at once.  Both kernels are bound by latency (some 5 us each; 44032 tokens, 64 experts, top-2: nine rounds in
 // 0.12 ms, with six launches and a wait for the host every other round 0.5 ms).
@@ -47,7 +47,7 @@ struct IterArgs {
     int32_t *assign, *list;    // list: proposals, slot-major
     IterArea *ar;
     int *any;                  // per (slot, block): whether there are proposals
-    int *tiles;                // per (slot, block): proposals per expert, then those of the tiles before
+    void *tiles;               // per (slot, block): proposals per expert, 64 at most; then how many of them there is room for
     int *wcnt;                 // result: pairs per (block, expert)
     long long *bsum;           // ... reward per block
     int *bflow;                // ... pairs per block
@@ -149,7 +149,7 @@ __device__ __forceinline__ int iter_phase(const IterArea *ar, int r)
 }
 
 // G lanes own a token row, lane l columns (m >> 2) * 4G + 4l + (m & 3) for m < EPL (EPL >= 4), else l * EPL + m.
-template <int G, int EPL>
+template <int G, int EPL, typename Tile>
 __global__ __launch_bounds__(256) void k_iter_step(IterArgs a, int r, int last)
 {
     extern __shared__ int s_mem[];
@@ -188,8 +188,7 @@ __global__ __launch_bounds__(256) void k_iter_step(IterArgs a, int r, int last)
             if (__any(asks)) {
                 const unsigned long long same = same_expert(e, a.ebits);
                 if (asks) {
-                    const int pos = a.tiles[((size_t)s * a.n_wg + w) * E + e] + __popcll(same & ((1ull << lane) - 1));
-                    take = pos < room;
+                    take = __popcll(same & ((1ull << lane) - 1)) < (int)((const Tile *)a.tiles)[((size_t)s * a.n_wg + w) * E + e];
                 }
             }
             if (take) {
@@ -328,7 +327,7 @@ __global__ __launch_bounds__(256) void k_iter_step(IterArgs a, int r, int last)
             atomicAdd(&s_num[e], n);
         }
         wave_lds_sync();
-        for (int x = lane; x < E; x += 64) a.tiles[tile * E + x] = cnt[x];
+        for (int x = lane; x < E; x += 64) ((Tile *)a.tiles)[tile * E + x] = (Tile)cnt[x];
         wave_lds_sync();
     }
     __syncthreads();
@@ -336,6 +335,7 @@ __global__ __launch_bounds__(256) void k_iter_step(IterArgs a, int r, int last)
         if (s_num[e]) atomicAdd(&ar->tot[w & 7][e], s_num[e]);
 }
 
+template <typename Tile>
 __global__ __launch_bounds__(kScanThreads) void k_iter_scan(IterArgs a, int r, int last, int max_rounds, int *host)
 {
     __shared__ int s_w[kScanThreads / 64];
@@ -392,6 +392,7 @@ __global__ __launch_bounds__(kScanThreads) void k_iter_scan(IterArgs a, int r, i
     if (c <= room || room <= 0) return;
     // eight tiles per thread and step, all on their way together
     const int n = a.k * a.n_wg;
+    Tile *tiles = (Tile *)a.tiles;
     int before = 0;
     for (int b0 = 0; b0 < n; b0 += 8 * blockDim.x) {
         const int t0 = b0 + 8 * tid;
@@ -399,7 +400,7 @@ __global__ __launch_bounds__(kScanThreads) void k_iter_scan(IterArgs a, int r, i
 #pragma unroll
         for (int i = 0; i < 8; ++i) x[i] = t0 + i < n ? a.any[t0 + i] : 0;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = x[i] ? a.tiles[(size_t)(t0 + i) * a.E + e] : 0;
+        for (int i = 0; i < 8; ++i) x[i] = x[i] ? (int)tiles[(size_t)(t0 + i) * a.E + e] : 0;
 #pragma unroll
         for (int i = 0; i < 8; ++i) sum += x[i];
         int inc = sum;
@@ -417,7 +418,8 @@ __global__ __launch_bounds__(kScanThreads) void k_iter_scan(IterArgs a, int r, i
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            if (x[i]) a.tiles[(size_t)(t0 + i) * a.E + e] = run;
+            const int left = room - run;
+            if (x[i]) tiles[(size_t)(t0 + i) * a.E + e] = (Tile)(left < 0 ? 0 : left < kIterRows ? left : kIterRows);
             run += x[i];
         }
     }
@@ -509,7 +511,12 @@ int32_t iter_run(const int32_t *q, int T, int E, int k, int C, int max_rounds, i
     at += sizeof(long long) * a.n_wg;
     a.bflow = (int *)at;
     a.any = a.bflow + a.n_wg;
-    a.tiles = a.any + (size_t)k * a.n_wg;
+    // Words, or bytes where only these fit (more than 34 slots and 128 experts): stores of bytes to lines that several
+    // chiplets write cost 44032 tokens of 64 experts, top-2, 140 us instead of 133.
+    const size_t tiles_off = iter_tiles_off(L, T, E);
+    const bool words = iter_tiles_are_words(L, T, E, k);
+    if (!words && (E <= 128 || tiles_off + iter_tiles(T, E, k) > L.price_off)) return MAXSCORE_ERR_WORKSPACE;
+    a.tiles = ws + tiles_off;
     a.wcnt = (int *)(ws + L.wcnt_off);
     a.T = T;
     a.E = E;
@@ -531,18 +538,25 @@ int32_t iter_run(const int32_t *q, int T, int E, int k, int C, int max_rounds, i
     hipLaunchKernelGGL(k_iter_init, dim3(1), dim3(1024), 0, s, a.ar);
     for (int r = 0; !hw[0]; ++r) {
         const int last = r > max_rounds ? 1 : 0;
-#define MS_I(GG, PP) hipLaunchKernelGGL((k_iter_step<GG, PP>), dim3(a.n_wg), dim3(256), shm, s, a, r, last)
+#define MS_I(GG, PP) hipLaunchKernelGGL((k_iter_step<GG, PP, int>), dim3(a.n_wg), dim3(256), shm, s, a, r, last)
+#define MS_IB(GG)                                                                                                     \
+    do {                                                                                                              \
+        if (words) MS_I(GG, 16);                                                                                      \
+        else hipLaunchKernelGGL((k_iter_step<GG, 16, unsigned char>), dim3(a.n_wg), dim3(256), shm, s, a, r, last);   \
+    } while (0)
         if (G == 8) {
             if (EPL == 1) MS_I(8, 1);
             else if (EPL == 2) MS_I(8, 2);
             else if (EPL == 4) MS_I(8, 4);
             else if (EPL == 8) MS_I(8, 8);
             else MS_I(8, 16);
-        } else if (G == 16) MS_I(16, 16);
-        else if (G == 32) MS_I(32, 16);
-        else MS_I(64, 16);
+        } else if (G == 16) MS_IB(16);
+        else if (G == 32) MS_IB(32);
+        else MS_IB(64);
+#undef MS_IB
 #undef MS_I
-        hipLaunchKernelGGL(k_iter_scan, dim3(E), dim3(threads), 0, s, a, r, last, max_rounds, host_dev);
+        hipLaunchKernelGGL(words ? k_iter_scan<int> : k_iter_scan<unsigned char>, dim3(E), dim3(threads), 0, s, a, r, last, max_rounds,
+                           host_dev);
         if (hipGetLastError() != hipSuccess) {
             (void)hipStreamSynchronize(s);
             return MAXSCORE_ERR_HIP;

@@ -42,3 +42,15 @@ def test_edges(ms, T, E, k, C):
     assert np.array_equal(out["disp_token"].cpu().numpy()[:n], want["disp_token"])
     assert np.array_equal(out["disp_gate"].cpu().numpy()[:n], want["disp_gate"])
     assert np.array_equal(out["token_pos"].cpu().numpy(), want["token_pos"])
+
+
+@pytest.mark.parametrize("T,E,k,C", [(9000, 320, 64, 1700), (9003, 257, 60, 2300), (3000, 1024, 64, 180)])
+def test_many_slots_and_experts(ms, T, E, k, C):
+    """Where the counts per (slot, 64 tokens, expert) only fit as bytes."""
+    print(f"iter byte tiles T={T} E={E} k={k} C={C}", flush=True)
+    rng = np.random.default_rng(T + E + k)
+    q = rng.integers(0, 1 << 18, (T, E)) + (rng.standard_normal(E) * (1 << 17)).astype(np.int64)
+    ref = oracle.iter_reroute(q, k, C)
+    out = ms.assign_iter_i32(torch.from_numpy(q.astype(np.int32)).cuda(), k, C, allow_not_converged=True)
+    assert np.array_equal(out["assign"].cpu().numpy(), ref["assign"])
+    assert (out["total"], out["flow"], out["rounds"]) == (ref["total"], ref["flow"], ref["rounds"])
