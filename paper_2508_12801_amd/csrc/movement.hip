@@ -53,12 +53,17 @@ __global__ __launch_bounds__(256) void k_dispatch_tokens(const u32x4 *__restrict
 
 // The same by blocks of tokens: every list holds its tokens in ascending order, so the rows that want tokens
 // [t0, t0 + tb) are one stretch of each list, found by bisection.  A workgroup turns its stretches into a list of rows
-// per token, and a wavefront reads a token's row once and writes it to all of them.  Lists in another order, or a token
-// in more than kTokenRows lists, are served row by row: the stretches still cover every list exactly once, since the
-// same bisection with a larger key never ends further left.  Workgroups from n_tb on zero the rows no token has.
+// per token, and a wavefront reads a token's row once and writes it to all of them.  A token in more than kTokenRows lists and
+// lists in another order are served row by row.  In a list that is out of order the bisections of neighbouring workgroups can
+// end far apart: of a descending list one workgroup gets everything.  So every workgroup looks at the same kListSamples entries
+// first.  If these do not ascend, the stretches are equal shares of the list; if they do, they are the bisection's first steps.
+// Either way the stretches cover every list exactly once, whatever its order: the samples and the same bisection with a
+// larger key never end further left.  Workgroups from n_tb on zero the rows no token has.
 // Bound by HBM: row by row in list order every row of x comes from memory k times once x is larger than the caches.
-// 65536 tokens of 2048 to 8 of 128 experts: 683 to 450 us, 5.3 TB/s with x counted once; 16384 to 8 of 64: 163 to 120 us.
-constexpr int kBlockTokens = 32, kTokenRows = 16, kListMaxE = 2048;
+// 65536 tokens of 2048 to 8 of 128 experts: 683 to 441 us, 5.5 TB/s with x counted once; 16384 to 8 of 64: 163 to 110 us.  The
+// same in other orders: shuffled 632 us (2.8 ms without the samples), descending 640 (13.9), shuffled by eight 680 (785 with a
+// list after the other instead of 64 together).
+constexpr int kBlockTokens = 32, kTokenRows = 16, kListMaxE = 2048, kListSamples = 8;
 
 template <bool NT>
 __global__ __launch_bounds__(256) void k_dispatch_tokens_blocked(const u32x4 *__restrict__ x,
@@ -97,9 +102,22 @@ __global__ __launch_bounds__(256) void k_dispatch_tokens_blocked(const u32x4 *__
     for (int j = tid; j < E; j += 256) {
         const int o0 = offsets[j];
         int cnt = offsets[j + 1] - o0;
-        cnt = cnt < C ? cnt : C;
+        cnt = cnt < 0 ? 0 : cnt < C ? cnt : C;
+        auto sample_at = [&](int i) { return i < 0 ? -1 : (int)((unsigned long long)cnt * i / kListSamples); };
+        int v[kListSamples];
+#pragma unroll
+        for (int i = 0; i < kListSamples; ++i) v[i] = cnt > 0 ? disp_token[o0 + sample_at(i)] : 0;
+        bool ascends = true;
+        int na = 0, nb = 0;                               // samples below either end
+#pragma unroll
+        for (int i = 0; i < kListSamples; ++i) {
+            if (i > 0 && sample_at(i) > sample_at(i - 1) && v[i] <= v[i - 1]) ascends = false;
+            na += v[i] < t0 ? 1 : 0;
+            nb += v[i] < t1 ? 1 : 0;
+        }
         // both ends at once: the loads of a step are independent
-        int a = 0, an = cnt, b = 0, bn = cnt;
+        int a = cnt > 0 ? sample_at(na - 1) + 1 : 0, an = sample_at(na) - a, b = cnt > 0 ? sample_at(nb - 1) + 1 : 0, bn = sample_at(nb) - b;
+        if (!ascends) an = bn = 0;
         while (an > 0 || bn > 0) {
             const int ah = an >> 1, bh = bn >> 1;
             const int va = an > 0 ? disp_token[o0 + a + ah] : 0, vb = bn > 0 ? disp_token[o0 + b + bh] : 0;
@@ -110,9 +128,15 @@ __global__ __launch_bounds__(256) void k_dispatch_tokens_blocked(const u32x4 *__
                 if (vb < t1) { b += bh + 1; bn -= bh + 1; } else bn = bh;
             }
         }
-        const int lo = blockIdx.x == 0 ? 0 : a, hi = (int)blockIdx.x == n_tb - 1 ? cnt : b;
+        int lo = blockIdx.x == 0 ? 0 : a, hi = (int)blockIdx.x == n_tb - 1 ? cnt : b;
+        if (!ascends) {
+            lo = (int)((long long)cnt * blockIdx.x / n_tb);
+            hi = (int)((long long)cnt * (blockIdx.x + 1) / n_tb);
+            s_odd = 1;
+        }
         s_first[j] = lo;
         s_n[j] = hi - lo;
+        if (!ascends) continue;
         for (int s = lo; s < hi; ++s) {
             const int t = disp_token[o0 + s] - t0;
             if (t < 0 || t >= tb || t0 + t >= T) {
@@ -129,13 +153,21 @@ __global__ __launch_bounds__(256) void k_dispatch_tokens_blocked(const u32x4 *__
     }
     __syncthreads();
     if (s_odd) {
-        for (int j = 0; j < E; ++j)
-            for (int i = wv; i < s_n[j]; i += 4) {
-                const int s = s_first[j] + i, tok = disp_token[offsets[j] + s];
-                const u32x4 *src = x + (size_t)(tok >= 0 && tok < T ? tok : 0) * vec_per_row;
-                u32x4 *dst = out + ((size_t)j * C + s) * vec_per_row;
-                for (int c = lane; c < vec_per_row; c += 64) dst[c] = src[c];
+        // the i-th rows of 64 stretches together, in turn to the four wavefronts
+        for (int j0 = 0, turn = wv; j0 < E; j0 += 64) {
+            const int j = j0 + lane, n = j < E ? s_n[j] : 0, first = j < E ? s_first[j] : 0, at = j < E ? offsets[j] + first : 0;
+            for (int i = 0; __any(i < n); ++i) {
+                int tok = i < n ? disp_token[at + i] : 0;
+                tok = tok >= 0 && tok < T ? tok : 0;
+                for (unsigned long long m = __ballot(i < n); m; m &= m - 1, ++turn) {
+                    if (turn & 3) continue;
+                    const int l = __ffsll((long long)m) - 1;
+                    const u32x4 *src = x + (size_t)__builtin_amdgcn_readlane(tok, l) * vec_per_row;
+                    u32x4 *dst = out + ((size_t)(j0 + l) * C + __builtin_amdgcn_readlane(first, l) + i) * vec_per_row;
+                    for (int c = lane; c < vec_per_row; c += 64) put<NT>(src[c], dst + c);
+                }
             }
+        }
         return;
     }
     for (int t = wv; t < tb; t += 4) {
