@@ -122,8 +122,8 @@ def test_route_logits_with_short_capacity(ms):
 
 
 def test_two_hundred_experts(ms):
-    """E = 200, k = 6 with 70 % of the capacity asked for: with the padding experts the solver works on 206 experts,
-    the range in which the cycle-cancelling finisher runs with four experts per lane."""
+    """E = 200, k = 6 with 70 % of the capacity asked for: a price solve with one column for the unfilled slots; the auction, where
+    it takes such a problem, works on 206 experts with the padding."""
     print("oversubscribed E=200", flush=True)
     rng = np.random.default_rng(23)
     T, E, k = 900, 200, 6
@@ -133,8 +133,8 @@ def test_two_hundred_experts(ms):
     C = int(0.7 * T * k / E)
     out, load = solve_and_check(ms, q, k, C)
     assert (load == C).all()
-    # the auction starts at the padding level (prices of the real experts far above zero): a few dozen rounds, where
-    # the climb from zero prices took thousands
+    # (an auction starts at the padding level, prices of the real experts far above zero: a few dozen rounds, where the climb
+    # from zero prices took thousands)
     assert out["stats"]["rounds"] < 400, out["stats"]
 
 

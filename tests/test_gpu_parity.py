@@ -278,7 +278,7 @@ def test_route_scores_end_to_end(ms, name, T):
 
 
 def test_route_scores_with_256_experts(ms):
-    """a3..a6 with E = 256, k = 8 (the fine-grained shape): the solve ends in the cycle-cancelling finisher and the
+    """a3..a6 with E = 256, k = 8 (the fine-grained shape): the solve ends in its search for augmenting paths and the
     gates and dispatch lists are built from its key blocks; everything equal to the checker's."""
     print("route_scores E=256", flush=True)
     rng = np.random.default_rng(77)

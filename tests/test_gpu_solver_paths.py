@@ -1,6 +1,11 @@
 """GPU parity of the assignment step (a4) on the solver's different code paths: 32-bit quick checks and
 64-bit full evaluation, with and without the tail pass, zero slack and slack capacity, several seeds,
-and the error statuses.  Every optimum is compared bit for bit with the CPU checker's."""
+and the error statuses.  Every optimum is compared bit for bit with the CPU checker's.
+
+A call without a flag that a price solve takes (up to 512 experts, rewards that fit its keys) is one: there the tests with
+"finisher" in their names compare the price solve with the auction alone, and `rounds`, `finish_passes` and `finish_cycles` are
+its passes, its search and its augmenting paths.  What they say of the finisher itself holds beyond 512 experts, with wider
+rewards and with vectors; the auction with its accelerators at every size is in test_gpu_auction_paths.py."""
 import numpy as np
 import pytest
 
@@ -95,7 +100,7 @@ def test_same_input_same_output(ms):
 
 @pytest.mark.parametrize("eps_div", [2, 5, 64])
 def test_eps_schedule_does_not_change_the_optimum(ms, eps_div):
-    print(f"eps_div {eps_div}", flush=True)
+    print(f"eps_div {eps_div}", flush=True)                       # (a price solve has no such schedule: it is ignored here)
     q = skewed_rewards(np.random.default_rng(9), 1024, 32, 20)
     solve_and_check(ms, q, 4, 128, eps_div=eps_div)
 
