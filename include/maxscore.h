@@ -36,9 +36,9 @@
  *     Eq. 7's equalities cannot all hold then; with the capacities of Table 1 the problem is still a flow problem
  *     (Section 3.2), and the exact assignment is its solution: every expert ends full (E*min(C,T) pairs, the
  *     maximum flow) and the placed pairs have the maximum score.  Rows come back with their experts first and -1
- *     in the slots left empty; gates are 0 there and the dispatch lists hold the placed pairs only.  It is solved
- *     with k padding experts, so it needs E + k <= 1024 (MAXSCORE_ERR_OVERSUBSCRIBED otherwise) and the larger
- *     workspace that maxscore_workspace_bytes reports for such T, E, k, C.
+ *     in the slots left empty; gates are 0 there and the dispatch lists hold the placed pairs only.  An auction
+ *     solves it with k padding experts, so it needs E + k <= 1024 (MAXSCORE_ERR_OVERSUBSCRIBED otherwise) and the
+ *     larger workspace that maxscore_workspace_bytes reports for such T, E, k, C, also where a price solve takes it.
  */
 #ifndef MAXSCORE_H
 #define MAXSCORE_H

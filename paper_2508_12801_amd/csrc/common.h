@@ -95,6 +95,7 @@ inline bool hip_ok(hipError_t e) { return e == hipSuccess; }
 // It is enqueued before the call waits for the stream, so the device goes from the solve straight into it; it
 // runs whatever the solve's status turns out to be and must therefore be safe on any state the solver can leave
 // (the caller redoes it another way when the status is not MAXSCORE_OK).
+// Without vectors a price solve is tried first; the auction runs where it does not stand, and with vectors.
 // More demand than capacity (T*k > E*Ce, no vectors): only a price solve is tried; kSolverPassedOn if it does not stand.
 // solve_end: the event the solver has just recorded behind its last kernel (it stays valid until the calling thread
 // solves again on this device); work timed from there needs no start event of its own.
@@ -108,9 +109,10 @@ int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore
 // Checks a device array of T per-token k (each 0..k) and returns its sum in *demand (synchronises the stream).
 int32_t kvec_check(const int32_t *kvec, int T, int E, int k, char *ws, long long *demand, hipStream_t s);
 // --- price.hip
-// Exact assignment by equilibrium prices and shortest augmenting paths: everything is enqueued at once, the outcome is
-// left in the pinned host state (fin == 2: certified; 1: not, but another try from the prices reached and with more
-// exchanges may do it, retry > 0 counts these; anything else: the auction has to solve the problem).
+// Exact assignment by equilibrium prices and shortest augmenting paths.  The host enqueues the passes as they are needed (it
+// polls the calling thread's pinned words), then the last pass and the search behind them, and does not wait for these.  The
+// outcome is left in the pinned host state (fin == 2: certified; 1: not, but another try from the prices reached and with
+// more exchanges may do it, retry > 0 counts these; anything else: the auction has to solve the problem).
 // k <= E <= kPriceMaxE, one capacity for all experts, any relation of demand and capacity (rows that cannot be filled
 // end in -1).
 // Up to kPriceTries tries of up to kPriceTryPasses passes: a caller's round cap below that goes to the auction, which ends at

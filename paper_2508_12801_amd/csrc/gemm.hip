@@ -585,8 +585,11 @@ __global__ __launch_bounds__(256) void k_copy16(const u32x4 *__restrict__ src, u
 
 }  // namespace
 
-// bf16: the split kernel as long as its workgroups fill the chip once, or twice with at most three column tiles each
-// (16384 tokens of 2048: 64 experts 44 us against 48, 128 experts 66 against 60; 8192: 29 against 48, 41 against 58).
+// bf16: the split kernel as long as its workgroups fill the chip once, or twice with at most three column tiles each.  Tokens of
+// 2048, split against whole, scores in the projection: 64 experts, 8192 tokens 18 us against 32, 16384 34 against 33 (logits
+// alone 30 against 28), 16385 42 against 43; 128 experts, 8192 31 against 43, 8193 43 against 61, 16384 54 against 45.
+// Logits of 96 experts: 8192 22 against 34, 16384 42 against 35.  So the line lies right at 64 and 128 experts and a factor
+// of two too far at 96.
 static bool split_is_better(int T, int E)
 {
     return (long long)((T + 31) / 32) * ((E + 127) / 128) <= (E <= 96 ? 512 : 256);

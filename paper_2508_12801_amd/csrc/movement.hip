@@ -218,8 +218,9 @@ __device__ __forceinline__ float bf16_to_f32(unsigned short b) { return __uint_a
 
 // One wavefront per token: every lane owns the 16-byte chunks lane, lane+64, ... of the row (NCH of them at a time),
 // accumulates the k gate-weighted expert rows in fp32, slot by slot, and writes fp32.  The indices of the slots (64 at most) are
-// read by one lane each, and the rows of kRegChunks / NCH slots are on their way together.  Bound by HBM (5.2 TB/s; a copy
-// reaches 4.9): 65536 tokens of 2048 from 8 of 128 experts 550 to 512 us, 44032 of 1024 from 2 of 64 98 to 86 us.
+// read by one lane each, and the rows of kRegChunks / NCH slots are on their way together.  Bound by HBM (5.4 TB/s; a copy of
+// 1 GiB reaches 5.0, of 256 MiB, half of which the last cache holds, 5.9): 65536 tokens of 2048 from 8 of 128 experts 550 to
+// 497 us, 44032 of 1024 from 2 of 64 98 to 85 us.
 constexpr int kRegChunks = 8;
 
 template <bool BF16, int NCH, bool NT>
@@ -325,7 +326,7 @@ __global__ __launch_bounds__(256) void k_combine_elem(const void *__restrict__ b
 }  // namespace
 
 // Traffic beyond the 256 MB of the last cache goes past it (non-temporal): 16384 tokens of 2048 to 8 of 64 experts
-// (512 MB of buffers) out and back 235 us instead of 282, while of 128 MB the way back finds more in the cache: 71 us, not 79.
+// (512 MB of buffers) out and back 231 us instead of 282, while of 128 MB the way back finds more in the cache: 71 us, not 79.
 static bool beyond_caches(size_t bytes) { return bytes >= (size_t)256 << 20; }
 
 int32_t dispatch_tokens_run(const void *x, int dtype, const int32_t *offsets, const int32_t *disp_token, int T, int d,

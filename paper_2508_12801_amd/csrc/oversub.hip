@@ -1,4 +1,5 @@
-// Exact assignment when demand exceeds capacity (T*k > E*min(C,T)): maximum flow first, then maximum score.
+// Exact assignment when demand exceeds capacity (T*k > E*min(C,T)): maximum flow first, then maximum score.  (A price solve,
+// price.hip, takes such a problem as it is and is tried first.)
 //
 // Eq. 7 prints equalities that cannot all hold in this case; Table 1 gives every arc a capacity, so the problem
 // read as a flow problem still has a solution: every expert ends up full, E*C pairs are placed, and among all such

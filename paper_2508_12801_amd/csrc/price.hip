@@ -25,10 +25,11 @@
 // reached with more arcs.  Whenever anything does not fit (values too wide for the packed keys, too many arcs, too much
 // excess left) the result is thrown away and the auction of solver.hip solves the problem instead.
 //
-// What bounds it: the passes read the rewards once each (34 MB for 65536 tokens over 128 experts, 17 to 28 us a pass
-// including the k-th best of every row, plus 11 us for the update between them), the search is one serial chain of
-// searches (12 to 24 us each).  65536 tokens, 128 experts, top-8, capacity 1.0: 0.42 ms against 1.75 ms for the auction,
-// whose 50 rounds each read the rewards as well; 16384 over 64 experts: 0.25 against 0.9 ms.
+// What bounds it: the passes read the rewards once each (34 MB for 65536 tokens over 128 experts, 13 us a pass including the
+// k-th best of every row, plus 10 us for the step between them, which one workgroup takes), the search is one serial chain of
+// searches.  65536 tokens, 128 experts, top-8, capacity 1.0: 0.36 to 0.43 ms, of which seven passes and their steps take 0.17,
+// the last pass 0.03 and the search 0.15 to 0.17; 1.6 to 1.8 ms for the auction, whose 46 rounds each read the rewards as
+// well.  16384 over 64 experts: 0.22 to 0.23 against 0.8 to 1.3 ms.
 //
 // Three forms of the problem, told apart by PriceArgs::mode:
 //   demand = capacity   every expert ends full;
@@ -50,7 +51,7 @@ constexpr int kPThreads = 256;                    // ... of the final pass
 constexpr int kQThreads = 512;                    // ... of a price pass
 constexpr int kPStride = kPriceMaxE + 8;          // columns of the per-expert tables (E + 1 used)
 // Copies of the histograms a pass adds to, one per chiplet; beyond 128 experts, where the one workgroup that reads them takes
-// longer than the additions of two chiplets wait for each other, half as many (16384 tokens of 256 experts: 20 us less).
+// longer than the additions of two chiplets wait for each other, half as many (a solve of 16384 tokens of 256 experts: 20 us less).
 constexpr int kPCopies = 8, kPCopiesWide = 4;
 __host__ __device__ constexpr int price_copies(int E) { return E <= 128 ? kPCopies : kPCopiesWide; }
 constexpr int kPArcs = 9216;                      // arcs the one-workgroup search holds in LDS
@@ -94,9 +95,9 @@ struct PriceArea {
     int pad[6];
     long long t_start;
     long long pad2;
-    // margins and holds, one copy per chiplet: (2 * nb + 1) rows of ES columns, filled by a pass (workgroup b adds to copy
-    // b mod 8), added up and cleared by the update behind it.  With one copy for all the additions of 512 workgroups
-    // took 25 us: its lines travel from chiplet to chiplet with every addition.
+    // margins and holds, price_copies(E) times: (2 * nb + 1) rows of ES columns, filled by a pass (workgroup b adds to copy b
+    // modulo their number), added up and cleared by the update behind it.  With one copy for all the additions took 25 us
+    // (of 512 workgroups then): its lines travel from chiplet to chiplet with every addition.
     int hist[kPCopies][kPTableInts];
     unsigned long long arc[kPArcBuf];             // cost << 32 | from << 16 | to
     int arc_tok[kPArcBuf];
@@ -373,8 +374,8 @@ __device__ __forceinline__ void gather_copies(PriceArea *ar, int quads, int *s_h
     }
 }
 
-// One workgroup.  (As the first step of every workgroup of the next pass the same work took 10 to 20 us: several dependent
-// reads of tables that the atomics of the pass have left in memory.)
+// One workgroup: 5.5 us at 16 experts, 8.0 at 64, 9.8 at 128 and 256.  (As the first step of every workgroup of the next pass
+// the same work took 10 to 20 us: several dependent reads of tables that the atomics of the pass have left in memory.)
 __global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, int nrows, int *host)
 {
     extern __shared__ __attribute__((aligned(16))) int s_h[];         // the sum of the copies
@@ -513,7 +514,7 @@ __device__ __forceinline__ void price_rows(const PriceArgs &a, int t, int W, int
 // One price pass over `nrows` rows.  Bound by the atomics that add a workgroup's table to the sums: eight wavefronts share a
 // table, one workgroup a compute unit, and two neighbouring counts go in one 64-bit addition (a count never reaches 2^32).
 // Four wavefronts, 512 workgroups and 32-bit additions took, mean over the passes, 10.6 us at 16384 tokens of 64 experts (now
-// 5.4), 20.1 at 256 experts (12.5) and 18.3 at 65536 tokens of 128 (12.9); without any of the additions 4.0, 6.2 and 7.1.
+// 5.6), 20.1 at 256 experts (13.1) and 18.3 at 65536 tokens of 128 (12.8); without any of the additions 4.0, 6.2 and 7.1.
 // Sixteen wavefronts: 5.4, 12.6 and 14.3.
 template <int G, int EPL, int MODE>
 __global__ __launch_bounds__(kQThreads) void k_price(PriceArgs a, int t, int nrows, int stride, int shift, int rows_per_wg)
@@ -565,8 +566,8 @@ __device__ __forceinline__ PriceMeta first_meta(const PriceArea *ar, const int64
     return PriceMeta{retry ? ar->meta.w : kFirstWindow, 0, 2, retry ? ar->meta.passes : prices_in ? -1 : 0, 0x7fffffff, {0, 0, 0}};
 }
 
-// All passes of a small batch in one workgroup: a pass takes 4 to 8 us instead of two launches of 20 to 25 us together,
-// none is launched in vain, and a batch that settles slowly may take more of them.
+// All passes of a small batch in one workgroup: a pass takes 4 to 8 us (64 tokens of 8 experts: three in 14 us; 256 of 64: 54)
+// instead of two launches of 9 to 20 us together, none is launched in vain, and a batch that settles slowly may take more.
 template <int G, int EPL, int MODE>
 __global__ __launch_bounds__(kUThreads) void k_price_small(PriceArgs a, int n_pass, int plim, const int64_t *__restrict__ prices_in)
 {
@@ -1392,9 +1393,9 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     if (!small)
         hipLaunchKernelGGL(k_price_init, dim3(64), dim3(kPThreads), 0, s, a.ar, price_table_ints(E, a.mode == kModeTight) / 4, E, plim, prices_in, a.retry);
     for (int t = small ? n_pass : 0; t <= n_pass; ++t) {
-        // One pass stays queued behind the one that runs: once the prices are done every pass still queued costs two empty
-        // launches (8 us; a batch with room to spare needs three of eleven).  The stream is looked at now and then: a
-        // stream that has drained or failed ends the wait.
+        // Pass t is enqueued when pass t - 2 has ended, so that one stays queued behind the one that runs: a pass that is still
+        // queued when the prices are done costs two empty launches (5 us; a batch with room to spare needs three of eleven).
+        // The stream is looked at now and then: a stream that has drained or failed ends the wait.
         for (unsigned spin = 1; t >= 2 && !small && !hw[kPriceWordDone] && hw[kPriceWordPasses] < t - 1; ++spin) {
             if ((spin & 4095) == 0 && hipStreamQuery(s) != hipErrorNotReady) break;
             __builtin_ia32_pause();

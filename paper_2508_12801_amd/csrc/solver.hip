@@ -1,5 +1,7 @@
 // Exact capacity-constrained maximum-score assignment (Section 3.2, Eq. 7-8, Table 1) as a
-// synchronous forward auction with epsilon-scaling on the bipartite token/expert network.
+// synchronous forward auction with epsilon-scaling on the bipartite token/expert network.  (solver_run tries a price solve,
+// price.hip, first; the auction takes what that does not: vectors of capacities or of k, more than 512 experts, very large
+// batches, rewards too wide for packed keys, many equal rows.)
 //
 // The paper solves the min-cost max-flow by sequential cheapest-path augmentation and calls it
 // inherently sequential; this solver is a different, data-parallel method for the same optimum:

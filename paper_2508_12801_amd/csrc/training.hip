@@ -93,7 +93,7 @@ __global__ __launch_bounds__(1024) void k_aux_final(const float *__restrict__ pa
 }
 
 // G lanes own a token row, lane l the 4-column pieces l, l+G, ... of it: a wavefront has 64 / G rows on their way, in whole
-// lines.  Bound by HBM: 65536 rows of 128 experts 31 us with a wavefront per row and 4-byte loads, 23 us so (4.6 TB/s).
+// lines.  Bound by HBM: 65536 rows of 128 experts 31 us with a wavefront per row and 4-byte loads, 24 us so (4.4 TB/s).
 template <int G, int EPL>
 __global__ __launch_bounds__(256) void k_gates_backward(const float *__restrict__ logits,
                                                         const float *__restrict__ scores,
