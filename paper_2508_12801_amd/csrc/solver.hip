@@ -1931,6 +1931,7 @@ int32_t price_run(const int32_t *q, int T, int E, int k, int C, const maxscore_o
     SolverHost *hs = nullptr;
     int32_t rc = solver_host(&hs);
     if (rc) return rc;
+    hs->tev_used = 0;
     PriceGeometry pg;
     SolverState h;
     int passes = o.prices_in ? -1 : 0;            // (the pass that checks given prices is a launch like the others)
@@ -1979,12 +1980,6 @@ int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore
                    const int32_t *cap, long long room, const int32_t *kvec, long long demand, SolverGeometry *geom,
                    SolverAfter after, void *after_ctx)
 {
-    SolverHost *hs = nullptr;
-    {
-        int32_t rc = solver_host(&hs);
-        if (rc) return rc;
-    }
-    hs->tev_used = 0;
     if (!cap && !kvec) {
         bool solved = false;
         const int32_t rc = price_run(q, T, E, k, Ce, o, assign, prices, price_scale, stats, ws, s, geom, after, after_ctx, &solved);
@@ -2050,6 +2045,12 @@ int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore
     const int n_wg = (T + rows - 1) / rows;
     if (n_wg > L.max_wg) return MAXSCORE_ERR_WORKSPACE;
 
+    SolverHost *hs = nullptr;
+    {
+        int32_t rc = solver_host(&hs);
+        if (rc) return rc;
+    }
+    hs->tev_used = 0;                     // (the marks of price tries have been read)
     // room = total capacity (sum of the vector, or E*Ce)
     // demand = number of pairs to place (sum of the per-token k, or T*k)
     const long long want = kvec ? demand : (long long)T * k;
@@ -2094,7 +2095,6 @@ int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore
             __builtin_ia32_pause();
         }
     };
-    const size_t first_mark = hs->tev_used;
     int batch = 2;      // two to four rounds in flight: each round still queued when the solve ends costs an empty launch pair
 #ifdef MAXSCORE_DEBUG_ENV
     if (const char *ev = getenv("MAXSCORE_BATCH")) batch = std::max(1, std::min(atoi(ev), 64));
@@ -2267,7 +2267,7 @@ int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore
     float ms = 0.f;
     (void)hipEventElapsedTime(&ms, hs->ev0, hs->ev1);
     {
-        const int32_t rc = add_launch_times(hs, first_mark, h.round, 2, stats, s);
+        const int32_t rc = add_launch_times(hs, 0, h.round, 2, stats, s);
         if (rc) return rc;
     }
 #ifdef MAXSCORE_DEBUG_ENV
