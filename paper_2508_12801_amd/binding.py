@@ -306,7 +306,8 @@ def scores_op(logits, k: int, op: str, quant_shift: int = 20):
 def assign_i32(q, k: int, C: int, max_rounds: int = 200000, eps_div: int = 12, allow_not_converged=False,
                tail_pass: bool = True, prices_in=None, eps_start: int = 0, finisher: bool = True):
     """a4: exact assignment on int32 rewards.  Returns dict(assign, prices, price_scale, stats).  prices_in: int64
-    device tensor of E starting prices (the `prices` of an earlier call), eps_start: first-phase eps with them."""
+    device tensor of E starting prices (the `prices` of an earlier call).  eps_div and eps_start (first-phase eps with
+    given prices) steer the auction, which takes the calls that a price solve does not."""
     torch = _torch()
     T, E = q.shape
     assert q.dtype == torch.int32 and q.is_contiguous()
