@@ -27,9 +27,9 @@
 //
 // What bounds it: the passes read the rewards once each (34 MB for 65536 tokens over 128 experts, 13 us a pass including the
 // k-th best of every row, plus 10 us for the step between them, which one workgroup takes), the search is one serial chain of
-// searches.  65536 tokens, 128 experts, top-8, capacity 1.0: 0.36 to 0.43 ms, of which seven passes and their steps take 0.17,
-// the last pass 0.03 and the search 0.15 to 0.17; 1.6 to 1.8 ms for the auction, whose 46 rounds each read the rewards as
-// well.  16384 over 64 experts: 0.22 to 0.23 against 0.8 to 1.3 ms.
+// searches.  65536 tokens, 128 experts, top-8, capacity 1.0: 0.26 to 0.28 ms, of which seven passes and their steps take 0.17,
+// the last pass 0.02 and the search 0.06 to 0.09; 1.6 to 1.8 ms for the auction, whose 46 rounds each read the rewards as
+// well.  16384 over 64 experts: 0.16 against 0.8 to 1.3 ms.
 //
 // Three forms of the problem, told apart by PriceArgs::mode:
 //   demand = capacity   every expert ends full;
@@ -40,6 +40,7 @@
 //                       hold several times and that has exactly as many places as there are slots too many.
 // Everything is integer arithmetic with fixed tie rules: the result does not depend on the order of execution.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "row_keys.h"
@@ -55,10 +56,10 @@ constexpr int kPStride = kPriceMaxE + 8;          // columns of the per-expert t
 constexpr int kPCopies = 8, kPCopiesWide = 4;
 __host__ __device__ constexpr int price_copies(int E) { return E <= 128 ? kPCopies : kPCopiesWide; }
 constexpr int kPArcs = 9216;                      // arcs the one-workgroup search holds in LDS
-constexpr int kPBlocks = 4096;                    // blocks of rows of the final pass at most (four per thread of the search)
+constexpr int kPBlocks = 4096;                    // blocks of rows of the final pass at most
 constexpr int kPArcBuf = 16384;                   // arcs the final pass can list
+constexpr int kBlockArcs = 512;                   // ... of one block, gathered in LDS
 constexpr int kFThreads = 1024, kUThreads = 1024;
-constexpr int kFRegs = kPArcs / kFThreads;
 constexpr int kFirstWindow = 1 << 22;             // margins of the first pass: up to four times a score of 1
 constexpr int kSampleRows = 8192;
 constexpr int kArcsPerExpert = 16, kArcsWanted = 4500, kArcsMost = 5500;
@@ -108,7 +109,6 @@ struct PriceArgs {
     int32_t *assign;
     PriceArea *ar;
     int *blkcnt;                                  // pairs per (block of rows of the final pass, expert)
-    int2 *wg_arcs;                                // first arc and number of arcs of every block
     long long *wg_sum;                            // sum of q over the block's pairs
     int T, E, k, C, mode;
     int even;                                     // the passes before this one treat spare capacity as spread evenly
@@ -601,7 +601,9 @@ __global__ __launch_bounds__(kUThreads) void k_price_small(PriceArgs a, int n_pa
     }
 }
 
-// The last pass: assignment, pairs per block and expert, sum of the rewards, and the arcs under the bound.
+// The last pass: assignment, pairs per block and expert, sum of the rewards, and the arcs under the bound.  A row near a change is
+// evaluated a second time for its arcs, which a block gathers in LDS: 20 us for 65536 tokens of 128 experts, 12 for 16384 of 64 (30 and
+// 16 while the rows were evaluated three times, to count the arcs and to write them in the order of the rows).
 template <int G, int EPL, bool OS>
 __global__ __launch_bounds__(kPThreads) void k_price_assign(PriceArgs a)
 {
@@ -609,9 +611,10 @@ __global__ __launch_bounds__(kPThreads) void k_price_assign(PriceArgs a)
     constexpr int NG = kPThreads / G;
     __shared__ int s_p[kPStride], s_cnt[kPStride];
     __shared__ unsigned s_thr[kPRowsMax];
-    __shared__ int s_rc[kPRowsMax];
     __shared__ short s_queue[kPRowsMax];
-    __shared__ int s_nq, s_base, s_total, s_bad;
+    __shared__ unsigned long long s_arc[kBlockArcs];
+    __shared__ int s_arc_tok[kBlockArcs];
+    __shared__ int s_nq, s_narcs, s_base, s_bad;
     __shared__ long long s_sum[kPThreads / 64];
     PriceArea *ar = a.ar;
     const int tid = threadIdx.x, lane = tid & 63, lg = tid & (G - 1), gbase = lane & ~(G - 1), grp = tid / G;
@@ -626,12 +629,7 @@ __global__ __launch_bounds__(kPThreads) void k_price_assign(PriceArgs a)
     int nx[EPL];
     RK::load(a.q + (size_t)(row0 + (grp < nr ? grp : nr - 1)) * E, E, vec, lg, nx);
     for (int j = tid; j < kPStride; j += kPThreads) s_cnt[j] = 0;
-    for (int i = tid; i < a.rows; i += kPThreads) s_rc[i] = 0;
-    if (tid == 0) {
-        s_nq = 0;
-        s_bad = 0;
-        s_total = 0;
-    }
+    if (tid == 0) s_nq = s_narcs = s_bad = 0;
     for (int e = tid; e < E; e += kPThreads) s_p[e] = ar->prices[e];
     const int B = ar->meta.bound;
     __syncthreads();
@@ -721,130 +719,120 @@ __global__ __launch_bounds__(kPThreads) void k_price_assign(PriceArgs a)
         a.wg_sum[w] = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
         if (s_bad) ar->fail = 1;
     }
-    // arcs: counted per row, then written in row order
-    const int nq = s_nq;
-    if (nq == 0 || s_bad) {
-        if (tid == 0) a.wg_arcs[w] = make_int2(0, 0);
-        return;
-    }
-    auto row_arcs = [&](int lr, int at) {                  // at < 0: count only
-        const int row = row0 + lr;
+    if (s_bad) return;
+    // arcs, gathered in LDS first (their order does not matter)
+    auto store = [&](int at, int cost, int from, int to, int row) {
+        const unsigned long long r = ((unsigned long long)(unsigned)cost << 32) | (unsigned)((from << 16) | to);
+        if (at < kBlockArcs) {
+            s_arc[at] = r;
+            s_arc_tok[at] = row;
+        } else {                                           // (batches whose exchanges are all listed, in few blocks)
+            const int pos = atomicAdd(&ar->n_arcs, 1);
+            if (pos < kPArcBuf) {
+                ar->arc[pos] = r;
+                ar->arc_tok[pos] = row;
+            }
+        }
+    };
+    const int nq = s_nq, vo = (int)(keyo >> ib);
+    for (int i = grp; i < nq; i += NG) {
+        const int lr = s_queue[i], row = row0 + lr;
         int v[EPL];
         unsigned key[EPL];
         RK::load(a.q + (size_t)row * E, E, vec, lg, v);
         make_keys(row, v, key);
         const unsigned thr = s_thr[lr], rot = row_mask(row, ib);
-        const int vo = (int)(keyo >> ib);
-        int n = 0, held = 0;
-        unsigned cur = RK::first(key);
-        auto put = [&](bool ok, int cost, int from, int to) {
-            const unsigned long long bal = group_bits(__ballot(ok));
-            if (at >= 0 && ok) {
-                const int pos = at + n + __popcll(bal & ((1ull << lg) - 1));
-                ar->arc[pos] = ((unsigned long long)(unsigned)cost << 32) | (unsigned)((from << 16) | to);
-                ar->arc_tok[pos] = row;
-            }
-            n += __popcll(bal);
+        const int vb = (int)(RK::below(key, thr) >> ib);   // the best expert the token does not hold (0: there is none)
+        auto from_slot = [&](int va, int from) {           // to this lane's columns
+            unsigned in = 0;
+#pragma unroll
+            for (int m = 0; m < EPL; ++m) in |= (RK::col(m, lg) < E && key[m] < thr && va - (int)(key[m] >> ib) < B ? 1u : 0u) << m;
+            if (!in) return;
+            int at = atomicAdd(&s_narcs, __popc(in));
+#pragma unroll
+            for (int m = 0; m < EPL; ++m)
+                if ((in >> m) & 1u) store(at++, va - (int)(key[m] >> ib), from, RK::col(m, lg), row);
         };
+        int held = 0;
+        unsigned cur = RK::first(key);
         for (int r = 0; r < k && cur >= thr; ++r) {
             const int va = (int)(cur >> ib), from = (int)((cur & cmask) ^ rot);
             ++held;
-#pragma unroll
-            for (int m = 0; m < EPL; ++m) {
-                const int c = RK::col(m, lg), cost = va - (int)(key[m] >> ib);
-                put(c < E && key[m] < thr && cost < B, cost, from, c);
-            }
-            if (OS) put(lg == 0 && va - vo < B, va - vo, from, E);
+            if (va - vb < B) from_slot(va, from);
+            if (OS && lg == 0 && va - vo < B) store(atomicAdd(&s_narcs, 1), va - vo, from, E, row);
             cur = RK::below(key, cur);
         }
-        if (OS && held < k) {
-#pragma unroll
-            for (int m = 0; m < EPL; ++m) {
-                const int c = RK::col(m, lg), cost = vo - (int)(key[m] >> ib);
-                put(c < E && key[m] < thr && cost < B, cost, E, c);
-            }
-        }
-        return n;
-    };
-    for (int i = grp; i < nq; i += NG) {
-        const int lr = s_queue[i];
-        const int n = row_arcs(lr, -1);
-        if (lg == 0) s_rc[lr] = n;
+        if (OS && held < k) from_slot(vo, E);
     }
     __syncthreads();
-    if (tid < 64) {
-        int run = 0;
-        for (int i0 = 0; i0 < a.rows; i0 += 64) {
-            const int c = i0 + lane < a.rows ? s_rc[i0 + lane] : 0;
-            const int inc = wave_sum(c);
-            if (i0 + lane < a.rows) s_rc[i0 + lane] = run + inc - c;
-            run += __builtin_amdgcn_readlane(inc, 63);
-        }
-        if (lane == 0) {
-            int base = 0;
-            if (run > 0) {
-                base = atomicAdd(&ar->n_arcs, run);
-                if (base + run > kPArcBuf) {
-                    ar->fail = 1;
-                    run = 0;
-                }
-            }
-            a.wg_arcs[w] = make_int2(base, run);
-            s_base = base;
-            s_total = run;
-        }
-    }
+    const int n = s_narcs < kBlockArcs ? s_narcs : kBlockArcs;
+    if (n == 0) return;
+    if (tid == 0) s_base = atomicAdd(&ar->n_arcs, n);
     __syncthreads();
-    if (s_total == 0) return;
-    for (int i = grp; i < nq; i += NG) {
-        const int lr = s_queue[i];
-        (void)row_arcs(lr, s_base + s_rc[lr]);
-    }
+    for (int i = tid; i < n; i += kPThreads)
+        if (s_base + i < kPArcBuf) {                       // (beyond: the search sees the count)
+            ar->arc[s_base + i] = s_arc[i];
+            ar->arc_tok[s_base + i] = s_arc_tok[i];
+        }
 }
 
 // ---- the search ----
 
+constexpr int kMovedSlots = 1024;     // at least half of them stay free
+static_assert(kMovedSlots >= 2 * kPriceMaxE && (kMovedSlots & (kMovedSlots - 1)) == 0, "paths are disjoint: one arc into every node but the roots");
+
 struct FinishLds {
     unsigned ft[kPArcs];              // from << 16 | to
     int tok[kPArcs];                  // -1: an arc of Z
-    int cost[kPArcs];                 // cost an arc enters with (kept in registers from then on)
-    int dst[kPBlocks];                // place of every block's arcs in the list
-    unsigned long long best[kPStride];
+    unsigned cost[kPArcs];            // reduced cost; kWInf: the arc is gone
+    unsigned short near[kPArcs];      // arcs within the search's reach
     unsigned lab[kPStride];           // distance << 10 | hops
-    int pred[kPStride];               // last arc of the shortest path
+    unsigned pred[kPStride];          // last arc of the shortest path: its token + 1 (0: an arc of Z) << 10 | the node it comes from
+    unsigned best[kPStride];          // of a branch: distance << 10 | target
     int p[kPStride], pi[kPStride], ex[kPStride], sl[kPStride], dd[kPStride];
-    int list[kPStride], mtok[kPStride], ncnt[64];
-    unsigned long long wkey[kPStride];   // paths that won their branch: distance and target
-    int wroot[kPStride];                 // ... their root ...
-    int wtok[kPStride];                  // ... and the token that leaves or joins the root
-    unsigned bloom[128];
+    unsigned mft[kPStride];           // path arcs ...
+    int mtok[kPStride];               // ... and their tokens
+    unsigned wkey[kPStride];          // paths offered by their branches: distance << 10 | target ...
+    int wroot[kPStride];              // ... their root ...
+    unsigned wtok[kPStride];          // ... the token that leaves or joins the root (+ 1) ...
+    int wlen[kPStride];               // ... and their arcs, 0 if the root has no unit left for them
+    int moved[kMovedSlots];           // tokens of the paths, hashed
     int chg[3], wsum[2][kFThreads / 64];
-    int bad, bad_move, dmax, n_win;       // bad: found while paths are chosen; bad_move: while tokens move
+    int bad, bad_move, dmax, n_win, n_near, n_off, n_arcs;       // bad: found while paths are chosen; bad_move: while tokens move
     long long dsum;
 };
 
-constexpr unsigned kLabInf = ~0u, kLabMax = 1u << 31;      // labels from kLabMax on are not followed (distances beyond 2^21)
-constexpr unsigned kWInf = 0x7fffffffu, kWMax = 1u << 21;
+constexpr int kSpareBit = 1 << 16, kReachShift = 2, kRelax = 4, kSearchRegs = 2;
+constexpr unsigned kLabInf = ~0u, kPredNone = ~0u;
+constexpr unsigned kWInf = 0x7fffffffu, kWMax = 1u << 21;  // distances from kWMax on are not followed
 static_assert(sizeof(FinishLds) <= 160 * 1024, "one compute unit's LDS");
 static_assert(kMaxBound < (int)kWMax, "every arc under the bound can be followed");
+static_assert(kMaxTBits <= 21, "a token + 1 and a node fit the words of the shortest paths, none of which is kPredNone");
 
-__device__ __forceinline__ int block_scan(int v, int *s_w, int &total)     // exclusive prefix over the workgroup (one barrier)
+__device__ __forceinline__ int wave_total(int v) { return __builtin_amdgcn_readlane(wave_sum(v), 63); }
+__device__ __forceinline__ int moved_slot(int u) { return (int)(((unsigned)u * 0x9E3779B1u) >> 22) & (kMovedSlots - 1); }
+
+template <int NW>
+__device__ __forceinline__ int block_total(int v, int *s_w)     // over the workgroup (one barrier)
 {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int inc = wave_sum(v);
-    if (lane == 63) s_w[wv] = inc;
+    const int sum = wave_total(v);
+    if (lane == 0) s_w[wv] = sum;
     __syncthreads();
-    const int x = lane < kFThreads / 64 ? s_w[lane] : 0;
-    const int xi = wave_sum(x);
-    total = __builtin_amdgcn_readlane(xi, 63);
-    return inc - v + __builtin_amdgcn_readlane(xi, wv) - __builtin_amdgcn_readlane(x, wv);
+    return wave_total(lane < NW ? s_w[lane] : 0);
 }
 
-// One workgroup.  Arc i belongs to thread i mod 1024, which keeps its reduced cost in a register.
+// One workgroup.  Bound by latency: about ten dependent steps between barriers per search, each a few LDS round trips, and one read of
+// the moved tokens' rows (2 us of the 10 to 14 a search takes).  What made it shorter (65536 tokens of 128 experts 154 -> 89 us, 10007
+// of 96 169 -> 96, 16384 of 256 242 -> 126, 16384 of 64 75 -> 43, 64 of 8 17 -> 12): arcs in LDS and rolled loops instead of nine arcs
+// of every thread in registers (14 KB of code instead of 32 to 40, which had to be fetched anew by every launch), only arcs within reach
+// looked at, ties broken by token instead of by place in the list (so the list needs no order and a moved token's arcs are put there
+// as they are found), a wavefront per offered path instead of a loop over all of them in every thread, and moved tokens hashed.
+// With 512 threads 330 instead of 302 us for a solve of 65536 tokens, with 256 387.
 template <int TEPL>
-__global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t *prices, int64_t *price_scale,
-                                                            SolverState *host_state)
+__global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t *prices, int64_t *price_scale, SolverState *host_state)
 {
+    constexpr int NT = kFThreads, NW = NT / 64;
     __shared__ FinishLds s;
     PriceArea *ar = a.ar;
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -856,14 +844,15 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
     int rounds = 0, augs = 0;
     bool close = false;                          // not solved, but near enough for another try
     const int n_listed = ar->n_arcs;
-    bool ok = ar->fail == 0 && n_listed <= kPArcBuf && a.n_wg <= kPBlocks;
+    bool ok = ar->fail == 0 && n_listed <= kPArcBuf;
     const int A0 = slack ? 2 * E : 0;
     if (A0 + n_listed > kPArcs) ok = false;
     if (tid == 0) {
         s.bad = s.bad_move = 0;
         s.dsum = 0;
+        s.n_arcs = A0 + n_listed;
     }
-    for (int v = tid; v < N; v += kFThreads) {
+    for (int v = tid; v < N; v += NT) {
         int n = 0;
         if (v < E)
             for (int r = 0; r < 8; ++r) n += ar->loads[r][v];
@@ -873,388 +862,380 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
         s.sl[v] = (slack && v < E && p == 0 && n < a.C) ? a.C - n : 0;
         s.ex[v] = v < E ? n + s.sl[v] - a.C : 0;
     }
+    if (ok)
+        for (int i = tid; i < A0 + n_listed; i += NT) {
+            const unsigned long long r = i >= A0 ? ar->arc[i - A0] : (unsigned)(i < E ? (i << 16) | E : (E << 16) | (i - E));
+            s.ft[i] = (unsigned)r;
+            s.cost[i] = (unsigned)(r >> 32);
+            s.tok[i] = i >= A0 ? ar->arc_tok[i - A0] : -1;
+        }
+    long long sum = 0;
+    for (int w2 = tid; w2 < a.n_wg; w2 += NT) sum += a.wg_sum[w2];
     __syncthreads();
     {
-        int tot, pos;
         const int e0 = tid < E ? s.ex[tid] : 0;
-        (void)block_scan(e0, s.wsum[0], tot);
-        (void)block_scan(e0 > 0 ? e0 : 0, s.wsum[1], pos);
+        const int tot = block_total<NW>(e0, s.wsum[0]), pos = block_total<NW>(e0 > 0 ? e0 : 0, s.wsum[1]);
         if (tid == 0) s.ex[E] = -tot;            // Z or the unfilled slots: supply and demand match overall
         const int most = pos > pos - tot ? pos : pos - tot;
         if (mode == kModeTight && tot != 0) ok = false;
         if (most > 8 * E + 64) ok = false;       // the prices are far from an equilibrium
         close = ar->fail == 0 && most <= 2 * E + 64;
     }
-    int n_arcs = A0 + n_listed;
-    // arcs, in block order
-    if (ok) {
-        const int per = (a.n_wg + kFThreads - 1) / kFThreads, w0 = tid * per;      // <= 4
-        int mine = 0, tot;
-        int2 bc[kPBlocks / kFThreads];
-#pragma unroll
-        for (int i = 0; i < kPBlocks / kFThreads; ++i) {
-            bc[i] = i < per && w0 + i < a.n_wg ? a.wg_arcs[w0 + i] : make_int2(0, 0);
-            mine += bc[i].y;
-        }
-        int at = A0 + block_scan(mine, s.wsum[0], tot);
-#pragma unroll
-        for (int i = 0; i < kPBlocks / kFThreads; ++i) {
-            if (i < per && w0 + i < a.n_wg) s.dst[w0 + i] = at - bc[i].x;
-            at += bc[i].y;
-        }
-        __syncthreads();
-        for (int i = tid; i < n_listed; i += kFThreads) {
-            const unsigned long long r = ar->arc[i];
-            const int u = ar->arc_tok[i];
-            const int to = i + s.dst[u / a.rows];
-            s.ft[to] = (unsigned)r;
-            s.cost[to] = (int)(r >> 32);
-            s.tok[to] = u;
-        }
-        for (int i = tid; i < A0; i += kFThreads) {
-            s.ft[i] = i < E ? (unsigned)((i << 16) | E) : (unsigned)((E << 16) | (i - E));
-            s.cost[i] = 0;
-            s.tok[i] = -1;
-        }
-    }
     __syncthreads();
-    unsigned ft[kFRegs], w[kFRegs];
-#pragma unroll
-    for (int j = 0; j < kFRegs; ++j) {
-        const int i = tid + j * kFThreads;
-        const bool in = ok && i < n_arcs;
-        ft[j] = in ? s.ft[i] : 0u;
-        w[j] = in ? (unsigned)s.cost[i] : kWInf;
-    }
-    bool solved = false, was_forward = true;
+    bool solved = false, forward = true;
+    int n_old = 0;                               // arcs that were there when the last paths were taken
     const int max_rounds = 8 * E + 128;
     for (; ok; ++rounds) {
-        if (!__syncthreads_or(tid < N && s.ex[tid] != 0)) {
+        const int ev = tid < N ? s.ex[tid] : 0, n_arcs = s.n_arcs;
+        const bool hub = os && tid == E;
+        const bool is_src = ev > 0 && (mode == kModeTight || tid < E), is_snk = ev < 0;
+        if (tid == 0) s.n_near = s.n_off = s.dmax = s.n_win = 0;
+        // sources, sinks, and nodes out of balance
+        const int n_all = block_total<NW>((is_src ? 1 : 0) | (is_snk ? 1 << 10 : 0) | (ev != 0 ? 1 << 20 : 0), s.wsum[rounds & 1]);
+        if (n_all == 0) {
             solved = true;
             break;
         }
         if (rounds >= max_rounds) break;
-        // arcs of Z: a spare place may leave an expert that has one, and may enter any expert at its price
-        if (tid < A0) {
-            const int v = tid < E ? tid : tid - E;
-            const int c = s.p[v] - s.pi[v] + s.pi[E];
-            w[0] = tid < E ? (s.sl[v] > 0 ? (unsigned)-c : kWInf) : (unsigned)c;
-            if (w[0] != kWInf && (int)w[0] < 0) s.bad = 1;
-        }
+        const int n_src = n_all & 1023, n_snk = (n_all >> 10) & 1023;
         // Spare places, or unfilled slots: whatever is too many goes to the nearest place that lacks a token or has one to
         // spare (the trees grow backward from all of these), and what Z then has too many to the places that lack one.
         // Sent from expert to expert instead, nearly all paths would lead through Z, one at a time.  Otherwise the trees
         // grow from the side with fewer nodes: a tree ends a path at every node of the other side only once, but its root
         // can send as many paths as it has units.
-        const int ev = tid < N ? s.ex[tid] : 0;
-        const bool hub = os && tid == E;
         const bool spare_here = slack && tid < E && ev == 0 && s.sl[tid] > 0;
-        const bool is_src = ev > 0 && (mode == kModeTight || tid < E), is_snk = ev < 0;
-        int n_both;
-        (void)block_scan((is_src ? 1 : 0) | (is_snk ? 1 << 16 : 0), s.wsum[1], n_both);
-        const bool via_z = mode != kModeTight && (n_both & 0xffff) > 0;
-        const bool forward = mode == kModeTight ? (n_both & 0xffff) <= (n_both >> 16) : !via_z;
-        if (forward != was_forward) {
-            was_forward = forward;
-#pragma unroll
-            for (int j = 0; j < kFRegs; ++j) ft[j] = __builtin_amdgcn_alignbit(ft[j], ft[j], 16);    // tail and head change places
-        }
+        const bool via_z = mode != kModeTight && n_src > 0;
+        const bool was_forward = forward;
+        forward = mode == kModeTight ? n_src <= n_snk : !via_z;
         const bool is_root = via_z ? hub || spare_here || (is_snk && tid < E) : forward ? ev > 0 : is_snk;
         const bool is_target = via_z ? is_src : forward ? is_snk && tid < E + (mode == kModeTight) : is_src;
-        if (tid < N) {
-            s.lab[tid] = is_root ? 0u : kLabInf;
-            s.pred[tid] = 0x7fffffff;
-            s.best[tid] = ~0ull;
-        }
-        if (tid < 3) s.chg[tid] = 0;
-        if (tid < 128) s.bloom[tid] = 0;
-        if (tid == 0) {
-            s.dmax = 0;
-            s.n_win = 0;
-        }
-        __syncthreads();
-        // Shortest paths from (backward: to) all roots.  Labels only fall, and where they end does not depend on the order in which
-        // arcs are looked at; hops break ties of distance, so that the last arcs form trees.
-        bool settled = false;
-        for (int it = 0; it < 4 * N; ++it) {
-            bool any = false;
-#pragma unroll
-            for (int twice = 0; twice < 2; ++twice) {
-                unsigned la[kFRegs], lb[kFRegs];
-#pragma unroll
-                for (int j = 0; j < kFRegs; ++j)
-                    if (j * kFThreads < n_arcs) {
-                        la[j] = s.lab[ft[j] >> 16];
-                        lb[j] = s.lab[ft[j] & 0xffff];
-                    }
-#pragma unroll
-                for (int j = 0; j < kFRegs; ++j)
-                    if (j * kFThreads < n_arcs) {
-                        const unsigned c = la[j] + (w[j] << 10) + 1;
-                        if (w[j] < kWMax && la[j] < kLabMax && c < lb[j]) {
-                            atomicMin(&s.lab[ft[j] & 0xffff], c);
-                            any = true;
-                        }
-                    }
+        // Shortest paths from (backward: to) all roots, up to a reach that starts at a quarter of the bound and is doubled until some
+        // target lies within it.  Only arcs shorter than the reach can be on such a path: they are listed densely first, so
+        // that few arcs meet in a bank of LDS, whose look-ups bound the search.  Labels only fall, and where they end does not depend
+        // on the order in which arcs are looked at; hops break ties of distance, so that the last arcs form trees.
+        unsigned limit = 0;
+        bool settled = false, target = false;
+        int nc = 0;
+        auto turned = [&](unsigned f) { return forward ? f : __builtin_amdgcn_alignbit(f, f, 16); };     // tail << 16 | head
+        bool fresh = n_old > 0;                  // reduced costs are those before the last paths
+        for (unsigned reach = (unsigned)B >> kReachShift;; reach *= 2, fresh = false) {
+            reach = reach < 1 ? 1 : reach > kWMax ? kWMax : reach;
+            limit = reach << 10;
+            if (tid == 0) s.lab[kPStride - 1] = kLabInf;
+            if (tid < N) {
+                s.lab[tid] = is_root ? 0u : kLabInf;
+                s.pred[tid] = kPredNone;
+                s.best[tid] = kLabInf;
             }
-            if (any) s.chg[it % 3] = 1;
-            if (tid == 0) s.chg[(it + 1) % 3] = 0;
+            if (tid < 3) s.chg[tid] = 0;
+            for (int i0 = wv * 64; i0 < n_arcs; i0 += NT) {
+                const int i = i0 + lane;
+                unsigned c = i < n_arcs ? s.cost[i] : kWInf;
+                if (i < A0) {        // a spare place may leave an expert that has one, and may enter any expert at its price
+                    const int v = i < E ? i : i - E, x = s.p[v] - s.pi[v] + s.pi[E];
+                    c = i < E ? (s.sl[v] > 0 ? (unsigned)-x : kWInf) : (unsigned)x;
+                    if (c != kWInf && (int)c < 0) s.bad = 1;
+                    s.cost[i] = c;
+                } else if (fresh && i < n_old && c != kWInf) {
+                    const unsigned f = s.ft[i];
+                    const int u = s.tok[i], df = s.dd[f >> 16] - s.dd[f & 0xffff];
+                    int x = moved_slot(u), o;
+                    while ((o = s.moved[x]) != u && o != -1) x = (x + 1) & (kMovedSlots - 1);
+                    c = o == u ? kWInf : c + (unsigned)(was_forward ? df : -df);       // (a moved token has new arcs in the list)
+                    s.cost[i] = c;
+                }
+                const bool in = c < reach;
+                const unsigned long long bal = __ballot(in);
+                if (bal) {
+                    int at = 0;
+                    if (lane == 0) at = atomicAdd(&s.n_near, (int)__popcll(bal));
+                    at = __builtin_amdgcn_readfirstlane(at);
+                    if (in) s.near[at + __popcll(bal & ((1ull << lane) - 1))] = (unsigned short)i;
+                }
+            }
             __syncthreads();
-            if (!s.chg[it % 3]) {
-                settled = true;
-                break;
-            }
-        }
-        // last arcs of the paths (the lowest arc wins)
+            nc = s.n_near;
+            // Each wavefront with arcs keeps them in registers, R to a lane; straight code, as taken branches cost more than the
+            // look-ups.  (Spread over fewer wavefronts, several arcs to a lane, it took longer.)
+            auto search = [&](auto regs) {
+                constexpr int R = decltype(regs)::value;
+                unsigned from[R], to[R], x[R], seen[R];
 #pragma unroll
-        for (int j = 0; j < kFRegs; ++j)
-            if (j * kFThreads < n_arcs) {
-                const unsigned la = s.lab[ft[j] >> 16];
-                if (w[j] < kWMax && la < kLabMax && la + (w[j] << 10) + 1 == s.lab[ft[j] & 0xffff])
-                    atomicMin(&s.pred[ft[j] & 0xffff], tid + j * kFThreads);
-            }
+                for (int j = 0; j < R; ++j) {
+                    from[j] = to[j] = kPStride - 1;                      // a node whose label stays
+                    x[j] = 0;
+                    seen[j] = kLabInf;
+                    const int y = tid + j * NT;
+                    if (y < nc) {
+                        const int i = s.near[y];
+                        const unsigned f = turned(s.ft[i]);
+                        from[j] = f >> 16;
+                        to[j] = f & 0xffff;
+                        x[j] = (s.cost[i] << 10) + 1;
+                    }
+                }
+                for (int it = 0; it < 4 * N; ++it) {
+                    if (wv * 64 < nc) {
+                        bool any = false;
+                        // (no look at the head's label first: the round trip would be as long as the one behind it)
+#pragma unroll
+                        for (int again = 0; again < kRelax; ++again) {
+                            unsigned la[R];
+#pragma unroll
+                            for (int j = 0; j < R; ++j) la[j] = __hip_atomic_load(&s.lab[from[j]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+                            for (int j = 0; j < R; ++j) {
+                                const bool fell = la[j] != seen[j];      // (a label that has fallen is below the limit)
+                                seen[j] = la[j];
+                                any |= fell;
+                                if (fell && la[j] + x[j] < limit) atomicMin(&s.lab[to[j]], la[j] + x[j]);
+                            }
+                            if (R == kSearchRegs)
+                                for (int y = tid + R * NT; y < nc; y += NT) {
+                                    const int i = s.near[y];
+                                    const unsigned f = turned(s.ft[i]), l = s.lab[f >> 16], c = l + (s.cost[i] << 10) + 1;
+                                    if (l < limit && c < limit && c < s.lab[f & 0xffff]) {
+                                        atomicMin(&s.lab[f & 0xffff], c);
+                                        any = true;
+                                    }
+                                }
+                        }
+                        if (any) s.chg[it % 3] = 1;
+                        if (tid == 0) s.chg[(it + 1) % 3] = 0;
+                    }
+                    __syncthreads();
+                    if (!s.chg[it % 3]) return true;
+                }
+                return false;
+            };
+            if (nc <= NT) settled = search(std::integral_constant<int, 1>());
+            else settled = search(std::integral_constant<int, kSearchRegs>());
+            target = is_target && s.lab[tid] < limit;
+            if (!settled || reach >= kWMax) break;
+            if (tid == 0) s.n_near = 0;
+            if (__syncthreads_or(target)) break;
+        }
+        // last arcs of the paths (the lowest token wins, then the lowest node)
+        for (int x = tid; x < nc; x += NT) {
+            const int i = s.near[x];
+            const unsigned f = turned(s.ft[i]), la = s.lab[f >> 16];
+            if (la < limit && la + (s.cost[i] << 10) + 1 == s.lab[f & 0xffff])
+                atomicMin(&s.pred[f & 0xffff], ((unsigned)(s.tok[i] + 1) << 10) | (f >> 16));
+        }
         const unsigned lv = tid < N ? s.lab[tid] : kLabInf;
-        const bool reached = lv < kLabMax;
-        const int dist = reached ? (int)(lv >> 10) : 0;
+        const bool reached = lv < limit;
+        const int dist = reached ? (int)(lv >> 10) : 0, hops = (int)(lv & 1023);
         __syncthreads();
         // every branch of a root offers the path to its nearest target, a root takes as many as it has units
-        const bool target = is_target && reached;
         int root = tid, branch = tid;
-        const int hops = (int)(lv & 1023);
-        const unsigned long long my_key = ((unsigned long long)dist << 10) | (unsigned)tid;
+        const unsigned my_key = ((unsigned)dist << 10) | (unsigned)tid;
         if (target) {
-            int x = tid;
             for (int i = 0; i < hops; ++i) {
-                const int idx = s.pred[x];
-                if (idx >= n_arcs) break;
-                branch = x;
-                x = forward ? (int)(s.ft[idx] >> 16) : (int)(s.ft[idx] & 0xffff);
+                const unsigned l = s.pred[root];
+                if (l == kPredNone) break;
+                branch = root;
+                root = (int)(l & 1023);
             }
-            root = x;
             atomicMin(&s.best[branch], my_key);
         }
         __syncthreads();
-        bool win = target && s.best[branch] == my_key;
-        int n_off;
-        const int wat = block_scan(win ? 1 : 0, s.wsum[0], n_off);
-        const bool uses_spare = slack && win && via_z && s.ex[root] == 0;
-        if (win) {
-            s.wkey[wat] = my_key;
-            s.wroot[wat] = root;
-            s.wtok[wat] = s.tok[s.pred[branch]];
+        if (target && s.best[branch] == my_key) {
+            const int i = atomicAdd(&s.n_off, 1);
+            s.wkey[i] = my_key;
+            s.wroot[i] = root;
+            s.wtok[i] = s.pred[branch] >> 10;
+        }
+        for (int i = tid; i < kMovedSlots; i += NT) s.moved[i] = -1;
+        __syncthreads();
+        const int n_off = s.n_off;
+        // (the i-th path offered belongs to wavefront i modulo their number)
+        for (int i = wv; i < n_off; i += NW) {
+            const unsigned key = s.wkey[i], tk = s.wtok[i];
+            const int rt = s.wroot[i], er = s.ex[rt];
+            int before = 0;
+            bool clash = false;
+            for (int c = lane; c - lane < n_off; c += 64) {
+                const bool ahead = c < n_off && s.wkey[c] < key && s.wroot[c] == rt;
+                before += __popcll(__ballot(ahead));
+                clash |= __any(ahead && tk != 0 && s.wtok[c] == tk) != 0;       // (the token has one place at the root)
+            }
+            const int units = os && via_z && rt == E ? 1 << 30 : er != 0 ? (er > 0 ? er : -er) : s.sl[rt];
+            const bool win = !clash && before < units;
+            if (lane == 0) {
+                // (a root that has no token too many or too few gives a spare place)
+                s.wlen[i] = win ? (int)(s.lab[key & 1023] & 1023) | (slack && via_z && er == 0 ? kSpareBit : 0) : 0;
+                if (win) {
+                    atomicMax(&s.dmax, (int)(key >> 10));
+                    atomicAdd(&s.n_win, 1);
+                }
+            }
         }
         __syncthreads();
-        if (win) {
-            const int i_tok = s.wtok[wat];
-            int before = 0;
-            for (int i = 0; i < n_off; ++i) {
-                if (s.wkey[i] >= my_key || s.wroot[i] != root) continue;
-                if (i_tok >= 0 && s.wtok[i] == i_tok) win = false;           // (the token has one place at the root)
-                ++before;
-            }
-            const int er = s.ex[root];
-            win = win && before < (os && via_z && root == E ? 1 << 30 : er != 0 ? (er > 0 ? er : -er) : s.sl[root]);
-        }
-        if (win) atomicMax(&s.dmax, dist);
-        int nm;
-        const int at = block_scan(win ? hops : 0, s.wsum[1], nm);
-        if (win && at + hops <= kPStride) {                // (always: the paths are disjoint)
-            atomicAdd(&s.n_win, 1);
-            int x = tid;
-            for (int i = 0; i < hops; ++i) {
-                const int idx = s.pred[x];
-                if (idx >= n_arcs) {
-                    s.bad = 1;
-                    break;
+        int nm = 0;                              // path arcs in all
+        {
+            int mine = -1, at = 0, y = 0;
+            for (int i0 = 0; i0 < n_off; i0 += 64) {
+                const int len = i0 + lane < n_off ? s.wlen[i0 + lane] & (kSpareBit - 1) : 0;
+                const int inc = wave_sum(len);
+                for (int i = i0 + wv; i < i0 + 64 && i < n_off; i += NW, ++y) {
+                    const int x = nm + __builtin_amdgcn_readlane(inc - len, i - i0);
+                    if (lane == y) {
+                        mine = i;
+                        at = x;
+                    }
                 }
-                const int from = (int)(s.ft[idx] >> 16), to = (int)(s.ft[idx] & 0xffff);
-                s.list[at + i] = idx;
-                s.mtok[at + i] = s.tok[idx];
-                if (slack) {
-                    if (from == E) atomicAdd(&s.sl[to], 1);          // a spare place comes to `to`
-                    else if (to == E) atomicAdd(&s.sl[from], -1);    // a spare place leaves
-                }
-                x = forward ? from : to;
+                nm += __builtin_amdgcn_readlane(inc, 63);
             }
-            const int src = forward ? root : tid, snk = forward ? tid : root;
-            atomicAdd(&s.ex[src], -1);
-            if (!uses_spare) atomicAdd(&s.ex[snk], 1);
-            else {
-                atomicAdd(&s.sl[snk], -1);
-                atomicAdd(&s.ex[E], 1);
+            const int word = mine >= 0 ? s.wlen[mine] : 0, len = word & (kSpareBit - 1);
+            if (len > 0 && nm <= kPStride) {                 // (always: the paths are disjoint)
+                const int tgt = (int)(s.wkey[mine] & 1023), rt = s.wroot[mine];
+                int x = tgt;
+                for (int i = 0; i < len; ++i) {
+                    const unsigned l = s.pred[x];
+                    if (l == kPredNone) {
+                        s.bad = 1;
+                        break;
+                    }
+                    const int tail = (int)(l & 1023), from = forward ? tail : x, to = forward ? x : tail;
+                    s.mft[at + i] = (unsigned)((from << 16) | to);
+                    s.mtok[at + i] = (int)(l >> 10) - 1;
+                    if (slack) {
+                        if (from == E) atomicAdd(&s.sl[to], 1);          // a spare place comes to `to`
+                        else if (to == E) atomicAdd(&s.sl[from], -1);    // a spare place leaves
+                    }
+                    x = tail;
+                }
+                const int src = forward ? rt : tgt, snk = forward ? tgt : rt;
+                atomicAdd(&s.ex[src], -1);
+                if (!(word & kSpareBit)) atomicAdd(&s.ex[snk], 1);
+                else {
+                    atomicAdd(&s.sl[snk], -1);
+                    atomicAdd(&s.ex[E], 1);
+                }
             }
         }
         if (tid < N) {
             // (no further than the paths taken: experts far from them keep their potentials close to the others)
-            const int d = reached && dist < s.dmax ? dist : s.dmax;
+            const int dm = s.dmax, d = reached && dist < dm ? dist : dm;
             s.dd[tid] = d;
             s.pi[tid] += forward ? d : -d;
         }
         __syncthreads();
         if (s.n_win == 0 || s.bad || !settled || nm > kPStride) break;         // no way to place what is left with these arcs
         augs += s.n_win;
-        // reduced costs under the new potentials (tail and head: potentials and arcs are both turned round backward)
+        n_old = n_arcs;
+        // The tokens of the paths move, one per wavefront at a time, with the next one's row on its way.  The arcs a token
+        // offers from where it is now replace its old ones in the list.
+        auto load_row = [&](int i, int &u, int &h, int (&qv)[TEPL]) {
+            u = i < nm ? s.mtok[i] : -1;
+            // (rows that an earlier search has changed were written by this workgroup)
+            h = u >= 0 && lane < k ? __hip_atomic_load(&a.assign[(size_t)u * k + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : -2;
 #pragma unroll
-        for (int j = 0; j < kFRegs; ++j)
-            if (w[j] != kWInf) w[j] += (unsigned)(s.dd[ft[j] >> 16] - s.dd[ft[j] & 0xffff]);
-        // The tokens of the paths move, up to 64 path arcs at a time: a wavefront takes four of them, with all rows on
-        // their way together.  The arcs a token offers from where it is now replace its old ones in the list.
-        const int n_old = n_arcs;
-        bool full = false;
-        for (int b0 = 0; b0 < nm; b0 += 64) {
-            int h[4], qv[4][TEPL];
+            for (int m = 0; m < TEPL; ++m) qv[m] = u >= 0 && lane + 64 * m < E ? a.q[(size_t)u * E + lane + 64 * m] : 0;
+        };
+        int un, hn, qn[TEPL];
+        load_row(wv, un, hn, qn);
+        for (int i = wv; i < nm; i += NW) {
+            int u = un, h = hn, qv[TEPL];
 #pragma unroll
-            for (int y = 0; y < 4; ++y) {
-                const int i = b0 + wv + 16 * y;
-                const int u = i < nm ? s.mtok[i] : -1;
-                h[y] = (u >= 0 && lane < k) ? __hip_atomic_load(&a.assign[(size_t)u * k + lane], __ATOMIC_RELAXED,
-                                                                __HIP_MEMORY_SCOPE_AGENT)
-                                            : -2;
-#pragma unroll
-                for (int m = 0; m < TEPL; ++m)
-                    qv[y][m] = u >= 0 && lane + 64 * m < E ? a.q[(size_t)u * E + lane + 64 * m] : 0;
+            for (int m = 0; m < TEPL; ++m) qv[m] = qn[m];
+            load_row(i + NW, un, hn, qn);
+            bool first = u >= 0;                                  // a token on two paths is taken once
+            for (int x0 = 0; x0 < i && first; x0 += 64) first = !__any(x0 + lane < i && s.mtok[x0 + lane] == u);
+            if (!first) continue;
+            if (lane == 0) {
+                int x = moved_slot(u);
+                for (int o; (o = atomicCAS(&s.moved[x], -1, u)) != -1 && o != u;) x = (x + 1) & (kMovedSlots - 1);
             }
-            // calls put(ok, cost, from, to) for every exchange of a token: slot by slot, then column by column
-            auto each_arc = [&](int hy, const int(&qy)[TEPL], auto put) {
-                int v[TEPL];
-                unsigned heldm = 0;
+            int *bcnt = a.blkcnt + (size_t)(u / a.rows) * E;
+            for (int x0 = i & ~63; x0 < nm; x0 += 64) {
+                unsigned long long same = __ballot(x0 + lane >= i && x0 + lane < nm && s.mtok[x0 + lane] == u);
+                for (; same; same &= same - 1) {
+                    const unsigned f = s.mft[x0 + __ffsll((long long)same) - 1];
+                    const int from = __builtin_amdgcn_readfirstlane((int)(f >> 16));
+                    const int to = __builtin_amdgcn_readfirstlane((int)(f & 0xffff));
+                    const unsigned long long bf = __ballot(h == (from < E ? from : -1));
+                    const unsigned long long bt = to < E ? __ballot(h == to) : 0ull;
+                    if (bf == 0 || bt != 0) {          // (never: the arcs of a token are those of its row)
+                        s.bad_move = 1;
+                        continue;
+                    }
+                    if (lane == __ffsll((long long)bf) - 1) h = to < E ? to : -1;
+                    int qt = 0, qf = 0;
 #pragma unroll
-                for (int m = 0; m < TEPL; ++m) v[m] = lane + 64 * m < E ? qy[m] - s.p[lane + 64 * m] : 0;
-                for (int sl = 0; sl < k; ++sl) {
-                    const int e = __builtin_amdgcn_readlane(hy, sl);
-                    if (e >= 0 && (e & 63) == lane) heldm |= 1u << (e >> 6);
+                    for (int m = 0; m < TEPL; ++m) {
+                        if (to < E && (to >> 6) == m) qt = __builtin_amdgcn_readlane(qv[m], to & 63);
+                        if (from < E && (from >> 6) == m) qf = __builtin_amdgcn_readlane(qv[m], from & 63);
+                    }
+                    if (lane == 0) {
+                        atomicAdd((unsigned long long *)&s.dsum, (unsigned long long)((long long)qt - qf));
+                        if (from < E) atomicAdd(&bcnt[from], -1);
+                        if (to < E) atomicAdd(&bcnt[to], 1);
+                    }
                 }
-                // only slots near the best expert the token does not hold have exchanges under the bound
-                int best = os ? 0 : -0x7fffffff;
-#pragma unroll
-                for (int m = 0; m < TEPL; ++m)
-                    if (lane + 64 * m < E && !((heldm >> m) & 1u)) best = v[m] > best ? v[m] : best;
-                best = wave_max(best);
-                int n_real = 0;
-                for (int sl = 0; sl < k; ++sl) {
-                    const int e = __builtin_amdgcn_readlane(hy, sl);
-                    if (e < 0) continue;
-                    ++n_real;
-                    int x = v[0];
-#pragma unroll
-                    for (int m = 1; m < TEPL; ++m) x = (e >> 6) == m ? v[m] : x;
-                    const int vh = __builtin_amdgcn_readlane(x, e & 63);
-                    if (vh - best >= B) continue;
-#pragma unroll
-                    for (int m = 0; m < TEPL; ++m)
-                        put(lane + 64 * m < E && !((heldm >> m) & 1u) && vh - v[m] < B, vh - v[m], e, lane + 64 * m);
-                    if (os) put(lane == 0 && vh < B, vh, e, E);
+            }
+            {
+                int dst = lane;
+                if (os) {                              // empty slots go to the end of the row
+                    const unsigned long long be = __ballot(h == -1), br = __ballot(h >= 0);
+                    dst = h >= 0 ? __popcll(br & ((1ull << lane) - 1)) : __popcll(br) + __popcll(be & ((1ull << lane) - 1));
                 }
-                if (os && n_real < k) {
+                if (lane < k) __hip_atomic_store(&a.assign[(size_t)u * k + dst], h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+            // Its exchanges: only slots near the best expert it does not hold have any under the bound.
+            unsigned heldm = 0;                                   // this lane's columns that the token holds
+            for (int sl = 0; sl < k; ++sl) {
+                const int e = __builtin_amdgcn_readlane(h, sl);
+                if (e >= 0 && (e & 63) == lane) heldm |= 1u << (e >> 6);
+            }
+            int v[TEPL], best = os ? 0 : -0x7fffffff, vs = 0;     // vs: value of the expert in slot `lane`
 #pragma unroll
-                    for (int m = 0; m < TEPL; ++m)
-                        put(lane + 64 * m < E && !((heldm >> m) & 1u) && -v[m] < B, -v[m], E, lane + 64 * m);
+            for (int m = 0; m < TEPL; ++m) {
+                const int c = lane + 64 * m;
+                v[m] = c < E ? qv[m] - s.p[c] : 0;
+                const int x = __shfl(v[m], h & 63);
+                vs = (h >> 6) == m ? x : vs;
+                const bool free = c < E && !((heldm >> m) & 1u);
+                if (!free) v[m] = -0x7fffffff;                    // (no exchange)
+                best = v[m] > best ? v[m] : best;
+            }
+            best = wave_max(best);
+            auto put = [&](int vh, int from) {
+#pragma unroll
+                for (int m = 0; m < TEPL; ++m) {
+                    const bool in = v[m] != -0x7fffffff && vh - v[m] < B;
+                    const unsigned long long bal = __ballot(in);
+                    if (!bal) continue;
+                    int at = 0;
+                    if (lane == 0) at = atomicAdd(&s.n_arcs, (int)__popcll(bal));
+                    at = __builtin_amdgcn_readfirstlane(at) + __popcll(bal & ((1ull << lane) - 1));
+                    if (in && at < kPArcs) {
+                        const int to = lane + 64 * m, wn = vh - v[m] + s.pi[from] - s.pi[to];
+                        if (wn < 0) s.bad_move = 1;
+                        s.ft[at] = (unsigned)((from << 16) | to);
+                        s.cost[at] = (unsigned)wn;
+                        s.tok[at] = u;
+                    }
                 }
             };
-#pragma unroll
-            for (int y = 0; y < 4; ++y) {
-                const int i = b0 + wv + 16 * y;
-                if (i >= nm) continue;
-                const int u = s.mtok[i];
-                int n = -1;
-                bool first = u >= 0;
-                if (first)
-                    for (int x0 = 0; x0 < i; x0 += 64)
-                        if (__any(x0 + lane < i && s.mtok[x0 + lane] == u)) first = false;      // a token on two paths is taken once
-                if (first) {
-                    int32_t *ra = a.assign + (size_t)u * k;
-                    int *bcnt = a.blkcnt + (size_t)(u / a.rows) * E;
-                    bool moved = false;
-                    for (int x0 = i; x0 < nm; x0 += 64) {
-                        unsigned long long same = __ballot(x0 + lane < nm && s.mtok[x0 + lane] == u);
-                        while (same) {
-                            const int x = x0 + __ffsll((long long)same) - 1;
-                            same &= same - 1;
-                            const unsigned f = s.ft[s.list[x]];
-                            const int from = __builtin_amdgcn_readfirstlane((int)(f >> 16));
-                            const int to = __builtin_amdgcn_readfirstlane((int)(f & 0xffff));
-                            const unsigned long long bf = __ballot(h[y] == (from < E ? from : -1));
-                            const unsigned long long bt = to < E ? __ballot(h[y] == to) : 0ull;
-                            if (bf == 0 || bt != 0) {          // (never: the arcs of a token are those of its row)
-                                s.bad_move = 1;
-                                continue;
-                            }
-                            if (lane == __ffsll((long long)bf) - 1) h[y] = to < E ? to : -1;
-                            moved = true;
-                            int qt = 0, qf = 0;
-#pragma unroll
-                            for (int m = 0; m < TEPL; ++m) {
-                                if (to < E && (to >> 6) == m) qt = __builtin_amdgcn_readlane(qv[y][m], to & 63);
-                                if (from < E && (from >> 6) == m) qf = __builtin_amdgcn_readlane(qv[y][m], from & 63);
-                            }
-                            if (lane == 0) {
-                                atomicAdd((unsigned long long *)&s.dsum, (unsigned long long)((long long)qt - qf));
-                                if (from < E) atomicAdd(&bcnt[from], -1);
-                                if (to < E) atomicAdd(&bcnt[to], 1);
-                            }
-                        }
-                    }
-                    if (moved) {
-                        int dst = lane;
-                        if (os) {                              // empty slots go to the end of the row
-                            const unsigned long long be = __ballot(h[y] == -1), br = __ballot(h[y] >= 0);
-                            dst = h[y] >= 0 ? __popcll(br & ((1ull << lane) - 1))
-                                            : __popcll(br) + __popcll(be & ((1ull << lane) - 1));
-                        }
-                        if (lane < k) __hip_atomic_store(&ra[dst], h[y], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    }
-                    if (lane == 0) atomicOr(&s.bloom[(u >> 5) & 127], 1u << (u & 31));
-                    n = 0;
-                    each_arc(h[y], qv[y], [&](bool okp, int, int, int) { n += __popcll(__ballot(okp)); });
-                }
-                if (lane == 0) s.ncnt[i - b0] = n;
-            }
-            __syncthreads();
-            const int cl = b0 + lane < nm ? s.ncnt[lane] : 0;
-            const int inc = wave_sum(cl > 0 ? cl : 0);
-            const int tot = __builtin_amdgcn_readlane(inc, 63);
-            if (n_arcs + tot > kPArcs) {
-                full = true;
-                break;
-            }
-#pragma unroll
-            for (int y = 0; y < 4; ++y) {
-                const int i = b0 + wv + 16 * y;
-                if (i >= nm) continue;
-                const int c = __builtin_amdgcn_readlane(cl, i - b0);
-                if (c <= 0) continue;
-                const int u = s.mtok[i];
-                int pos0 = n_arcs + __builtin_amdgcn_readlane(inc, i - b0) - c;
-                each_arc(h[y], qv[y], [&](bool okp, int cost, int from, int to) {
-                    const unsigned long long bal = __ballot(okp);
-                    if (okp) {
-                        const int pos = pos0 + __popcll(bal & ((1ull << lane) - 1));
-                        const int wn = cost + s.pi[from] - s.pi[to];
+            for (unsigned long long r = __ballot(lane < k && h >= 0 && vs - best < B); r; r &= r - 1) {
+                const int sl = __ffsll((long long)r) - 1;
+                const int e = __builtin_amdgcn_readlane(h, sl), vh = __builtin_amdgcn_readlane(vs, sl);
+                put(vh, e);
+                if (os && vh < B && lane == 0) {                  // ... for an unfilled slot
+                    const int at = atomicAdd(&s.n_arcs, 1), wn = vh + s.pi[e] - s.pi[E];
+                    if (at < kPArcs) {
                         if (wn < 0) s.bad_move = 1;
-                        s.ft[pos] = (unsigned)((from << 16) | to);
-                        s.cost[pos] = wn;
-                        s.tok[pos] = u;
+                        s.ft[at] = (unsigned)((e << 16) | E);
+                        s.cost[at] = (unsigned)wn;
+                        s.tok[at] = u;
                     }
-                    pos0 += __popcll(bal);
-                });
+                }
             }
-            n_arcs += tot;
-            __syncthreads();
+            if (os && __any(lane < k && h == -1)) put(0, E);
         }
-        if (full || s.bad_move) break;
-#pragma unroll
-        for (int j = 0; j < kFRegs; ++j) {
-            const int i = tid + j * kFThreads;
-            if (i >= n_old && i < n_arcs) {
-                ft[j] = forward ? s.ft[i] : __builtin_amdgcn_alignbit(s.ft[i], s.ft[i], 16);
-                w[j] = (unsigned)s.cost[i];
-            } else if (w[j] != kWInf) {
-                const int u = s.tok[i];
-                if (u >= 0 && ((s.bloom[(u >> 5) & 127] >> (u & 31)) & 1u))
-                    for (int x = 0; x < nm; ++x)
-                        if (s.mtok[x] == u) w[j] = kWInf;                // its token has moved
-            }
-        }
+        __syncthreads();
+        if (s.n_arcs > kPArcs || s.bad_move) break;
     }
     __syncthreads();
     // the arcs left out cost at least B: they stay non-negative if the potentials spread less than that
@@ -1276,10 +1257,8 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
     while ((1 << sb) < E + 1) ++sb;
     if (certified && prices) {
         const int shift = slack ? -s.pi[E] : pmin;
-        for (int e = tid; e < E; e += kFThreads) prices[e] = (int64_t)(s.p[e] - s.pi[e] - shift) << sb;
+        for (int e = tid; e < E; e += NT) prices[e] = (int64_t)(s.p[e] - s.pi[e] - shift) << sb;
     }
-    long long sum = 0;
-    for (int w2 = tid; w2 < a.n_wg; w2 += kFThreads) sum += a.wg_sum[w2];
     if (sum) atomicAdd((unsigned long long *)&s.dsum, (unsigned long long)sum);
     __syncthreads();
     if (tid == 0) {
@@ -1353,8 +1332,7 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     a.assign = assign;
     a.ar = (PriceArea *)(ws + L.price_off);
     a.blkcnt = (int *)(ws + L.wcnt_off);
-    a.wg_arcs = (int2 *)(ws + L.price_off + (sizeof(PriceArea) + 15) / 16 * 16);
-    a.wg_sum = (long long *)(a.wg_arcs + L.max_wg);
+    a.wg_sum = (long long *)(ws + L.price_off + (sizeof(PriceArea) + 15) / 16 * 16);
     a.T = T;
     a.E = E;
     a.k = k;
@@ -1448,10 +1426,12 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
             mark();
         }
     }
-    if (E <= 64) hipLaunchKernelGGL(k_price_finish<1>, dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, host_state_dev);
-    else if (E <= 128) hipLaunchKernelGGL(k_price_finish<2>, dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, host_state_dev);
-    else if (E <= 256) hipLaunchKernelGGL(k_price_finish<4>, dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, host_state_dev);
-    else hipLaunchKernelGGL(k_price_finish<8>, dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, host_state_dev);
+#define MS_F(PP) hipLaunchKernelGGL(k_price_finish<PP>, dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, host_state_dev)
+    if (E <= 64) MS_F(1);
+    else if (E <= 128) MS_F(2);
+    else if (E <= 256) MS_F(4);
+    else MS_F(8);
+#undef MS_F
     MS_HIP(hipGetLastError());
     return mrc;
 }

@@ -1,0 +1,44 @@
+"""GPU parity of the search behind the price passes where its lists change form: more exchanges in one block of rows than are
+gathered in LDS and more within reach than are kept in registers, all nodes of the largest expert count with and without spare
+capacity and with unfilled slots, tokens on several paths.  Optimality is the checker's certificate (or its optimum); the lists are
+filled in no fixed order, so three runs have to give the same assignment."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+SHAPES = [  # T, E, k, C, largest reward
+    (20, 32, 8, 5, 1 << 20), (20, 32, 8, 5, 60), (25, 21, 10, 12, 1 << 20), (100, 9, 4, 45, 200),      # every exchange listed
+    (1536, 512, 8, 24, 1 << 20), (1500, 512, 8, 24, 1 << 20), (3000, 256, 4, 47, 1 << 20), (1200, 257, 3, 14, 1 << 18),
+    (1000, 64, 16, 250, 1 << 20), (3000, 24, 12, 1500, 1 << 20), (90, 30, 3, 8, 1 << 20),
+]
+
+
+@pytest.mark.parametrize("T,E,k,C,top", SHAPES)
+def test_search(T, E, k, C, top):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2508_12801_amd as ms
+    print(f"price search T={T} E={E} k={k} C={C} top={top}", flush=True)
+    rng = np.random.default_rng(T * 31 + E + top)
+    popular = rng.random(E) ** 3
+    q = ((rng.random((T, E)) ** 2 + popular) / 2 * top).astype(np.int64)
+    qd = torch.from_numpy(q.astype(np.int32)).cuda()
+    runs = [ms.assign_i32(qd, k, C) for _ in range(3)]
+    a = runs[0]["assign"].cpu().numpy()
+    print(runs[0]["stats"], flush=True)
+    for r in runs[1:]:
+        assert np.array_equal(r["assign"].cpu().numpy(), a)
+    filled = a >= 0
+    total = int(np.take_along_axis(q, np.where(filled, a, 0).astype(np.int64), axis=1)[filled].sum())
+    assert total == runs[0]["stats"]["total_score_q"] and int(filled.sum()) == min(T * k, E * C)
+    if T * k <= E * C:
+        P = oracle.assignment_matrix(a, E)
+        assert (P.sum(axis=1) == k).all() and P.sum(axis=0).max() <= C and oracle.verify_optimal(q, P, k, C)["optimal"]
+    else:
+        assert np.bincount(a[filled], minlength=E).max() <= C
+        assert total == oracle.assign_literal_graph(q, k, C)["total"]
