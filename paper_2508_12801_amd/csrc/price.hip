@@ -25,11 +25,11 @@
 // reached with more arcs.  Whenever anything does not fit (values too wide for the packed keys, too many arcs, too much
 // excess left) the result is thrown away and the auction of solver.hip solves the problem instead.
 //
-// What bounds it: the passes read the rewards once each (34 MB for 65536 tokens over 128 experts, 13 us a pass including the
-// k-th best of every row, plus 10 us for the step between them, which one workgroup takes), the search is one serial chain of
-// searches.  65536 tokens, 128 experts, top-8, capacity 1.0: 0.26 to 0.28 ms, of which seven passes and their steps take 0.17,
+// What bounds it: the passes read the rewards once each (34 MB for 65536 tokens over 128 experts, 11 us a pass including the
+// k-th best of every row, plus 7 us for the step between them, which one workgroup takes), the search is one serial chain of
+// searches.  65536 tokens, 128 experts, top-8, capacity 1.0: 0.22 to 0.24 ms, of which seven passes and their steps take 0.12,
 // the last pass 0.02 and the search 0.06 to 0.09; 1.6 to 1.8 ms for the auction, whose 46 rounds each read the rewards as
-// well.  16384 over 64 experts: 0.16 against 0.8 to 1.3 ms.
+// well.  16384 over 64 experts: 0.14 against 0.8 to 1.3 ms.
 //
 // Three forms of the problem, told apart by PriceArgs::mode:
 //   demand = capacity   every expert ends full;
@@ -51,10 +51,12 @@ namespace {
 constexpr int kPThreads = 256;                    // ... of the final pass
 constexpr int kQThreads = 512;                    // ... of a price pass
 constexpr int kPStride = kPriceMaxE + 8;          // columns of the per-expert tables (E + 1 used)
-// Copies of the histograms a pass adds to, one per chiplet; beyond 128 experts, where the one workgroup that reads them takes
-// longer than the additions of two chiplets wait for each other, half as many (a solve of 16384 tokens of 256 experts: 20 us less).
-constexpr int kPCopies = 8, kPCopiesWide = 4;
-__host__ __device__ constexpr int price_copies(int E) { return E <= 128 ? kPCopies : kPCopiesWide; }
+// Copies of the histograms a pass adds to, at most one per chiplet.  The workgroup that reads them all waits for their bytes, so a pass
+// of few workgroups makes do with fewer (a solve of 2000 tokens of 128 experts, 32 workgroups: 234 us with eight copies, 222 with four,
+// 218 with two; 16384 of 64, 256 workgroups: 144, 151, 150), and counts that cannot reach 2^16 take 16 bits each, four to an addition:
+// 65536 tokens of 128 experts 271 -> 242 us, 16384 of 256 324 -> 295, 10007 of 96 267 -> 240, none slower.
+constexpr int kPCopies = 8;
+constexpr int kPWgPerCopy = 32;
 constexpr int kPArcs = 9216;                      // arcs the one-workgroup search holds in LDS
 constexpr int kPBlocks = 4096;                    // blocks of rows of the final pass at most
 constexpr int kPArcBuf = 16384;                   // arcs the final pass can list
@@ -96,7 +98,7 @@ struct PriceArea {
     int pad[6];
     long long t_start;
     long long pad2;
-    // margins and holds, price_copies(E) times: (2 * nb + 1) rows of ES columns, filled by a pass (workgroup b adds to copy b
+    // margins and holds, PriceArgs::copies times: (2 * nb + 1) rows of ES columns, filled by a pass (workgroup b adds to copy b
     // modulo their number), added up and cleared by the update behind it.  With one copy for all the additions took 25 us
     // (of 512 workgroups then): its lines travel from chiplet to chiplet with every addition.
     int hist[kPCopies][kPTableInts];
@@ -115,6 +117,8 @@ struct PriceArgs {
     int rows, n_wg;                               // of the final pass
     int ib, nb, bshift;                           // bits of a column id in a packed key; bins per side; their width
     int es;                                       // columns of the histograms
+    int copies;                                   // ... their copies, a power of two ...
+    int half;                                     // ... with counts of 16 bits (no copy's can reach 2^16), else of 32
     int retry;                                    // the search has failed at the prices or the bound before
     int arcs_wanted;                              // about so many exchanges are to lie under the bound
 };
@@ -168,7 +172,8 @@ __device__ __forceinline__ unsigned row_mask(int row, int ib)      // equal valu
 // the margins of that common step.
 //
 // Bound by latency, and by what the sixteen wavefronts do alike (four of them share a SIMD): sums are taken over the
-// wavefronts that have experts only, and the bound of the arc list is worked out by the last one beside the columns.
+// wavefronts that have experts only, and the bound of the arc list is worked out by the last one beside the columns.  The largest
+// step is reduced by lane moves: an atomic maximum of all lanes on one word is compiled into a loop over the lanes (1.5 us).
 struct StepLds {
     __attribute__((aligned(16))) int was[kPStride], now[kPStride];
     int cum[64];
@@ -177,7 +182,18 @@ struct StepLds {
     int maxd, ran_out, lam, cap, worst, bound, wide, reach;
 };
 
-__device__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const PriceMeta mt, const int *s_h, StepLds &s)
+__device__ __forceinline__ void step_clear(StepLds &s)
+{
+    if (threadIdx.x < 64) s.cum[threadIdx.x] = 0;
+    if (threadIdx.x == 0) {
+        s.maxd = s.ran_out = s.lam = s.worst = 0;
+        s.cap = 0x7fffffff;
+    }
+}
+
+// Behind step_clear and a barrier.  CUM: s.cum holds the sums of the bins already.
+template <bool CUM>
+__device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const PriceMeta mt, const int *s_h, StepLds &s)
 {
     constexpr int NW = kUThreads / 64;
     static_assert(kPriceMaxE / 64 < NW - 1, "the last wavefront has no experts");
@@ -189,12 +205,6 @@ __device__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const Pric
     const int w0 = bin_w0(mt.w), bs = a.bshift;
     const int Ct = sampled ? (int)(((long long)a.C * nrows + a.T / 2) / a.T) : a.C;
     const int *s_hn = s_h + 2 * nb * ES;
-    if (tid < 64) s.cum[tid] = 0;
-    if (tid == 0) {
-        s.maxd = s.ran_out = s.lam = s.worst = 0;
-        s.cap = 0x7fffffff;
-    }
-    __syncthreads();
     if (wv < nwe) {
         const int ne = tid < E ? s_hn[tid] : 0, over = tid < E && ne > Ct ? ne - Ct : 0;
         const bool in = tid < E && (all_in || s.was[tid] > 0);
@@ -207,7 +217,7 @@ __device__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const Pric
         }
     }
     // holds (0 .. nb-1) and newcomers (nb .. 2nb-1) per margin bin over all experts
-    for (int b = wv; b < 2 * nb; b += NW) {
+    for (int b = wv; !CUM && b < 2 * nb; b += NW) {
         int tot = 0;
         for (int e = lane; e < E; e += 64) tot += s_h[b * ES + e];
         tot = wave_sum(tot);
@@ -247,14 +257,16 @@ __device__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const Pric
         }
         __syncthreads();
     }
-    if (tid < E + (level ? 1 : 0)) {
+    if (wv * 64 < E + (level ? 1 : 0)) {
         const int j = tid;
         const bool common = j == E;
-        const int pj = s.was[j];
+        const int pj = j <= E ? s.was[j] : 0;
         const bool in = all_in || pj > 0;
-        const int diff = common ? X : s_hn[j] - (in ? target : Ct);
+        int diff = 0;
+        if (j < E + (level ? 1 : 0)) diff = common ? X : s_hn[j] - (in ? target : Ct);
         const int side = diff < 0 ? 1 : 0;                       // side 0: the price has to rise, side 1: to fall
         const int need = side ? (in || common ? -diff : 0) : diff;       // (room left at price 0 is fine)
+        int most = 0;
         if (need != 0) {
             const int *col = s_h + side * nb * ES + j;
             int c[kPBins];
@@ -278,10 +290,12 @@ __device__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const Pric
             else if (b == nb) s.ran_out = 1;
             if (!in && !common && sx > E) d += (int)((float)d * fminf(0.7f, 2.f * (float)so / (float)E));
             d = d < 1 ? 1 : d;
-            atomicMax(&s.maxd, d);
+            most = d;
             if (common) s.lam = side ? -d : d;
             else s.now[j] = pj + (side ? -d : d);
         }
+        most = wave_max(most);               // (an atomic of every lane is compiled into a loop over the lanes)
+        if (lane == 0 && most > 0) atomicMax(&s.maxd, most);
     } else if (wv == NW - 1) {
         // the bound of the arc list: about kArcsPerExpert exchanges per expert lie under it.  h holds and n newcomers make
         // h * n / rows of them if they are spread over all rows, and the larger of the two if every row has one of each.
@@ -348,34 +362,56 @@ __device__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const Pric
 }
 
 // The sum of N copies of the histograms, which are cleared: up to M 16-byte pieces per thread, all on their way together.
-constexpr int kPQuads = 2, kPQuadsWide = (kPTableInts / 4 + kUThreads - 1) / kUThreads;
-static_assert(price_table_most(1, 128) / 4 <= kPQuads * kUThreads, "two pieces per thread up to 128 experts");
-static_assert(kPTableInts % 4 == 0, "every copy starts on 16 bytes");
-template <int N, int M>
-__device__ __forceinline__ void gather_copies(PriceArea *ar, int quads, int *s_h)
+template <int N, int M, bool HALF>
+__device__ __forceinline__ void gather_copies(const PriceArgs &a, int *s_h, StepLds &s)
 {
-    int4 x[M][N];
+    constexpr int Q = HALF ? 2 : 1;                                   // quads of counts in a piece
+    const int quads = (2 * a.nb + 1) * a.es / 4, pieces = (quads + Q - 1) / Q;
+    uint4 x[M][N];
 #pragma unroll
     for (int m = 0; m < M; ++m) {
         const int i = m * kUThreads + threadIdx.x;
 #pragma unroll
-        for (int r = 0; r < N; ++r) x[m][r] = i < quads ? ((const int4 *)ar->hist[r])[i] : make_int4(0, 0, 0, 0);
+        for (int r = 0; r < N; ++r) x[m][r] = i < pieces ? ((const uint4 *)a.ar->hist[r])[i] : make_uint4(0, 0, 0, 0);
     }
 #pragma unroll
     for (int m = 0; m < M; ++m) {
         const int i = m * kUThreads + threadIdx.x;
-        int4 y = make_int4(0, 0, 0, 0);
+        int4 y[Q];
+#pragma unroll
+        for (int h = 0; h < Q; ++h) y[h] = make_int4(0, 0, 0, 0);
 #pragma unroll
         for (int r = 0; r < N; ++r) {
-            if ((x[m][r].x | x[m][r].y | x[m][r].z | x[m][r].w) != 0) ((int4 *)ar->hist[r])[i] = make_int4(0, 0, 0, 0);
-            y.x += x[m][r].x; y.y += x[m][r].y; y.z += x[m][r].z; y.w += x[m][r].w;
+            const uint4 z = x[m][r];
+            if ((z.x | z.y | z.z | z.w) != 0) ((uint4 *)a.ar->hist[r])[i] = make_uint4(0, 0, 0, 0);
+            if constexpr (HALF) {
+                y[0].x += z.x & 0xffff; y[0].y += z.x >> 16; y[0].z += z.y & 0xffff; y[0].w += z.y >> 16;
+                y[1].x += z.z & 0xffff; y[1].y += z.z >> 16; y[1].z += z.w & 0xffff; y[1].w += z.w >> 16;
+            } else {
+                y[0].x += z.x; y[0].y += z.y; y[0].z += z.z; y[0].w += z.w;
+            }
         }
-        if (i < quads) ((int4 *)s_h)[i] = y;
+#pragma unroll
+        for (int h = 0; h < Q; ++h) {
+            const int u = i * Q + h;
+            if (u >= quads) continue;
+            ((int4 *)s_h)[u] = y[h];
+            // the sums of the bins on the way (the columns beyond the experts do not belong to them)
+            const int row = u / (a.es / 4), c = 4 * (u - row * (a.es / 4));
+            const int sum = (c < a.E ? y[h].x : 0) + (c + 1 < a.E ? y[h].y : 0) + (c + 2 < a.E ? y[h].z : 0) + (c + 3 < a.E ? y[h].w : 0);
+            if (row < 2 * a.nb && sum) atomicAdd(&s.cum[row], sum);
+        }
     }
 }
+static_assert(kPTableInts % 4 == 0, "every copy starts on 16 bytes");
+static_assert(2 * kPBins + 1 <= 64, "a sum per bin");
+constexpr int price_pieces(bool half) { return (kPTableInts / (half ? 8 : 4) + kUThreads) / kUThreads; }      // per thread, at most
 
-// One workgroup: 5.5 us at 16 experts, 8.0 at 64, 9.8 at 128 and 256.  (As the first step of every workgroup of the next pass
-// the same work took 10 to 20 us: several dependent reads of tables that the atomics of the pass have left in memory.)
+// One workgroup.  Half of it is the wait for the copies, which the pass's additions have left in memory; the rest two barriers' worth of
+// sums and searches: 4.8 us at 16 experts, 5.8 at 64, 7.0 at 128, 9.2 at 256 (5.7, 7.5, 9.8 and 9.7 with counts of 32 bits, and with the
+// sums of the bins and the largest step taken behind the copies).  As the first step of every workgroup of the next pass the same
+// work took 10 to 20 us.
+template <int N, int M, bool HALF>
 __global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, int nrows, int *host)
 {
     extern __shared__ __attribute__((aligned(16))) int s_h[];         // the sum of the copies
@@ -383,13 +419,14 @@ __global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, 
     PriceArea *ar = a.ar;
     const int tid = threadIdx.x, E = a.E;
     // everything is requested before the state is looked at (the exit test then does not add a round trip)
-    const int quads = (2 * a.nb + 1) * a.es / 4;
     for (int e = tid; e < kPStride; e += kUThreads) s.was[e] = s.now[e] = e < E ? ar->prices[e] : 0;
-    if (price_copies(E) == kPCopies) gather_copies<kPCopies, kPQuads>(ar, quads, s_h);
-    else gather_copies<kPCopiesWide, kPQuadsWide>(ar, quads, s_h);
+    step_clear(s);
+    __syncthreads();
+    gather_copies<N, M, HALF>(a, s_h, s);
     const PriceMeta mt = ar->meta;
     if (mt.done) return;                 // (passes that find the prices done add nothing: the copies stay clear)
-    const PriceMeta m2 = price_step(a, t, nrows, mt, s_h, s);
+    __syncthreads();
+    const PriceMeta m2 = price_step<true>(a, t, nrows, mt, s_h, s);
     for (int e = tid; e < E; e += kUThreads) ar->prices[e] = s.now[e];
     if (tid == 0) {
         ar->meta = m2;
@@ -512,10 +549,10 @@ __device__ __forceinline__ void price_rows(const PriceArgs &a, int t, int W, int
 }
 
 // One price pass over `nrows` rows.  Bound by the atomics that add a workgroup's table to the sums: eight wavefronts share a
-// table, one workgroup a compute unit, and two neighbouring counts go in one 64-bit addition (a count never reaches 2^32).
-// Four wavefronts, 512 workgroups and 32-bit additions took, mean over the passes, 10.6 us at 16384 tokens of 64 experts (now
-// 5.6), 20.1 at 256 experts (13.1) and 18.3 at 65536 tokens of 128 (12.8); without any of the additions 4.0, 6.2 and 7.1.
-// Sixteen wavefronts: 5.4, 12.6 and 14.3.
+// table, one workgroup a compute unit, and four neighbouring counts of 16 bits (or two of 32) go in one 64-bit addition: mean over the
+// passes 4.9 us at 16384 tokens of 64 experts, 10.2 at 256 experts and 11.0 at 65536 tokens of 128.  Two counts to an addition took
+// 5.7, 13.0 and 13.0, one, with half as many wavefronts to a table, 10.6, 20.1 and 18.3; without any of the additions it would be 4.0,
+// 6.2 and 7.1.
 template <int G, int EPL, int MODE>
 __global__ __launch_bounds__(kQThreads) void k_price(PriceArgs a, int t, int nrows, int stride, int shift, int rows_per_wg)
 {
@@ -544,9 +581,15 @@ __global__ __launch_bounds__(kQThreads) void k_price(PriceArgs a, int t, int nro
     __syncthreads();
     price_rows<G, EPL, MODE, kQThreads>(a, t, mt.w, r_first, r_end, stride, shift, nx, s_p, s_hist);
     __syncthreads();
-    int *hg = ar->hist[blockIdx.x & (price_copies(E) - 1)];
+    int *hg = ar->hist[blockIdx.x & (a.copies - 1)];
     for (int i = tid; i < hquads; i += kQThreads) {
         const int4 x = ((int4 *)s_hist)[i];
+        if (a.half) {
+            const unsigned lo = (unsigned)x.x | ((unsigned)x.y << 16), hi = (unsigned)x.z | ((unsigned)x.w << 16);
+            const unsigned long long four = lo | ((unsigned long long)hi << 32);
+            if (four) atomicAdd((unsigned long long *)hg + i, four);
+            continue;
+        }
         unsigned long long *h64 = (unsigned long long *)(hg + 4 * i);
         if (x.x | x.y) atomicAdd(h64, (unsigned long long)(unsigned)x.x | ((unsigned long long)(unsigned)x.y << 32));
         if (x.z | x.w) atomicAdd(h64 + 1, (unsigned long long)(unsigned)x.z | ((unsigned long long)(unsigned)x.w << 32));
@@ -589,8 +632,9 @@ __global__ __launch_bounds__(kUThreads) void k_price_small(PriceArgs a, int n_pa
         __syncthreads();
         price_rows<G, EPL, MODE, kUThreads>(a, t, mt.w, 0, a.T, 1, 0, nx, s.was, s_hist);
         for (int e = tid; e < E; e += kUThreads) s.now[e] = s.was[e];
+        step_clear(s);
         __syncthreads();
-        mt = price_step(a, t, a.T, mt, s_hist, s);
+        mt = price_step<false>(a, t, a.T, mt, s_hist, s);
         __syncthreads();
         for (int e = tid; e < E; e += kUThreads) s.was[e] = s.now[e];
     }
@@ -1312,6 +1356,16 @@ static bool price_shape(int T, int E, int k, int &G, int &EPL, int &rows, int &n
     return rows * k <= 1024 && n_wg <= kPBlocks;
 }
 
+// Rows per workgroup of a price pass.
+static int price_pass_rows(int nrows, int E, int k)
+{
+    int G, EPL, rows, n_wg;
+    (void)price_shape(nrows, E, k, G, EPL, rows, n_wg);
+    int rw = kQThreads / G;
+    while (rw * 2 <= 128 && (nrows + 2 * rw - 1) / (2 * rw) >= 256) rw *= 2;
+    return rw;
+}
+
 bool price_supported(int T, int E, int k)
 {
     int G, EPL, rows, n_wg;
@@ -1344,6 +1398,14 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     const int stride = T / kSampleRows;
     const int n_sampled = stride >= 2 && !prices_in && !retry ? kSampledPasses : 0;
     a.even = spare > 0 && spare * 64 <= (long long)E * C && !prices_in && !retry ? (n_sampled ? 4 : 3) : 0;
+    {
+        const int rw = price_pass_rows(T, E, k), wgs = (T + rw - 1) / rw;
+        a.copies = kPCopies;
+        while (a.copies > 2 && a.copies * kPWgPerCopy > wgs) a.copies /= 2;
+        // what one row adds to a count at most: one, or to that of the common step a slot or pair each
+        const long long each = a.mode == kModeTight ? 1 : a.mode == kModeSlack ? kLevelPairs : k;
+        a.half = (wgs + a.copies - 1) / a.copies * (long long)rw * each < (1 << 16) ? 1 : 0;
+    }
     a.arcs_wanted = std::min(kArcsPerExpert * E, kArcsWanted);
     a.retry = retry > 0 ? 1 : 0;
     if (retry) a.arcs_wanted = std::min((1 + retry) * a.arcs_wanted, kArcsMost);
@@ -1364,12 +1426,13 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     auto mark = [&] { mrc = mrc ? mrc : solver_mark(s); };
     const bool os = a.mode == kModeOver;
     const size_t shm = sizeof(int) * (size_t)price_table_ints(E, a.mode == kModeTight);
+    const int hquads = price_table_ints(E, a.mode == kModeTight) / 4;
     const int n_pass = n_sampled + (retry ? kRetryPasses : a.mode == kModeSlack ? kSlackPasses : kTightPasses);
     const bool small = (long long)T * G <= kSmallThreads && (long long)T * E <= kSmallEntries && shm + sizeof(StepLds) <= 64 * 1024;
     const int plim = (1 << (31 - a.ib)) - 1;
     geom->one_launch = small ? 1 : 0;
     if (!small)
-        hipLaunchKernelGGL(k_price_init, dim3(64), dim3(kPThreads), 0, s, a.ar, price_table_ints(E, a.mode == kModeTight) / 4, E, plim, prices_in, a.retry);
+        hipLaunchKernelGGL(k_price_init, dim3(64), dim3(kPThreads), 0, s, a.ar, hquads, E, plim, prices_in, a.retry);
     for (int t = small ? n_pass : 0; t <= n_pass; ++t) {
         // Pass t is enqueued when pass t - 2 has ended, so that one stays queued behind the one that runs: a pass that is still
         // queued when the prices are done costs two empty launches (5 us; a batch with room to spare needs three of eleven).
@@ -1383,8 +1446,7 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
         const int st = t < n_sampled ? stride : 1;
         const int nrows = st > 1 ? kSampleRows : T;
         const int shift = st > 1 ? t * (st / 2) : 0;
-        int rw = kQThreads / G;
-        while (rw * 2 <= 128 && (nrows + 2 * rw - 1) / (2 * rw) >= 256) rw *= 2;
+        const int rw = price_pass_rows(nrows, E, k);
         const int grid = fin ? a.n_wg : (nrows + rw - 1) / rw;
 #define MS_P(GG, PP)                                                                                                      \
     do {                                                                                                                  \
@@ -1422,7 +1484,16 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
 #undef MS_PG
 #undef MS_P
         if (!fin) {
-            hipLaunchKernelGGL(k_price_update, dim3(1), dim3(kUThreads), shm, s, a, t, nrows, words_dev);
+#define MS_U(NN)                                                                                                          \
+    do {                                                                                                                  \
+        if (!a.half) hipLaunchKernelGGL((k_price_update<NN, price_pieces(false), false>), dim3(1), dim3(kUThreads), shm, s, a, t, nrows, words_dev); \
+        else if (hquads <= 2 * kUThreads) hipLaunchKernelGGL((k_price_update<NN, 1, true>), dim3(1), dim3(kUThreads), shm, s, a, t, nrows, words_dev); \
+        else hipLaunchKernelGGL((k_price_update<NN, price_pieces(true), true>), dim3(1), dim3(kUThreads), shm, s, a, t, nrows, words_dev); \
+    } while (0)
+            if (a.copies == 8) MS_U(8);
+            else if (a.copies == 4) MS_U(4);
+            else MS_U(2);
+#undef MS_U
             mark();
         }
     }
