@@ -6,6 +6,8 @@
 // W tile in LDS and prefetches the next tiles into registers while the matrix cores work.  The fast
 // kernel (k_gemm_bf16_wtc) reads x with whole-line loads and restores the operand layout through LDS.
 // Small batches, and fp32 throughout, run a kernel that splits d over the wavefronts of a workgroup (k_gemm_split).
+#include <type_traits>
+
 #include "common.h"
 #include "softtopk_row.h"
 
@@ -388,6 +390,7 @@ __global__ __launch_bounds__(256) void k_gemm_bf16_wtc(const unsigned short *__r
             for (int pass = 0; pass < 2; ++pass) {
                 const int r_local = 8 * pass + rl;
                 const int row = row0 + wave * RW + 16 * half + r_local;
+                if (row >= T) continue;          // (rows of zeros are all ties: 10 to 17 us at a batch that is no multiple of 128)
                 float xv[EPLS];
 #pragma unroll
                 for (int m = 0; m < EPLS; m += 4) {
@@ -397,14 +400,12 @@ __global__ __launch_bounds__(256) void k_gemm_bf16_wtc(const unsigned short *__r
                 float sc[EPLS];
                 int qq[EPLS];
                 softtopk_row<8, EPLS, true>(xv, lg, E, k, t, qscale, MAXSCORE_SOFTTOPK_A, sc, qq);
-                if (row < T) {
 #pragma unroll
-                    for (int m = 0; m < EPLS; m += 4) {
-                        const size_t o = (size_t)row * E + (m >> 2) * 32 + lg * 4;
-                        if (out) *(float4 *)(out + o) = make_float4(xv[m], xv[m + 1], xv[m + 2], xv[m + 3]);
-                        if (scores) *(float4 *)(scores + o) = make_float4(sc[m], sc[m + 1], sc[m + 2], sc[m + 3]);
-                        if (q) *(int4 *)(q + o) = make_int4(qq[m], qq[m + 1], qq[m + 2], qq[m + 3]);
-                    }
+                for (int m = 0; m < EPLS; m += 4) {
+                    const size_t o = (size_t)row * E + (m >> 2) * 32 + lg * 4;
+                    if (out) *(float4 *)(out + o) = make_float4(xv[m], xv[m + 1], xv[m + 2], xv[m + 3]);
+                    if (scores) *(float4 *)(scores + o) = make_float4(sc[m], sc[m + 1], sc[m + 2], sc[m + 3]);
+                    if (q) *(int4 *)(q + o) = make_int4(qq[m], qq[m + 1], qq[m + 2], qq[m + 3]);
                 }
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -430,148 +431,189 @@ __global__ __launch_bounds__(256) void k_gemm_bf16_wtc(const unsigned short *__r
     }
 }
 
-// Split kernel: 32 token rows per workgroup, one 32 x 32 tile of the output and one part of d per wavefront (ct column
-// tiles times ks parts, 16 wavefronts at most); the parts are added up through LDS in a fixed order.  Operands come
-// straight from global memory: within a step the matrix instruction may take its reduction indices in any order, so a lane
-// reads 16 consecutive bytes of its row of x and the matching elements of W, 32 columns side by side.
+// Split kernel: RT x 32 token rows per workgroup and up to 128 columns, d split over its KS wavefronts, whose parts are added up through
+// LDS in a fixed order.  Operands come straight from global memory: within a step the matrix instruction may take its reduction
+// indices in any order, so a lane reads 16 consecutive bytes of its row of x; and a tile may hold any 32 columns, so tile c takes the
+// columns CT * j + c, and a lane reads its CT neighbouring columns of a row of W with one instruction.
 // fp32 runs on v_mfma_f32_32x32x2_f32, four per step of 8 indices; bf16 on v_mfma_f32_32x32x16_bf16, one per step of 16.
-// fp32 is bound by the matrix cores' fp32 rate: 65536 x 1024 to 128 experts 0.25 ms (68 TFLOP/s), with one fused
-// multiply-add per element and thread as before 3.8 ms; 10007 x 1000 to 96: 60 and 416 us.  Small bf16 batches are bound by
-// the latency of their loads, here in flight from 16 wavefronts at once instead of 4: 256 x 2048 to 64 experts 27 us, with
-// 128 rows and all of d per workgroup 45.
+// bf16 is bound by the latency of its loads and by the operands of W (from L2, once per 32 or 64 rows), fp32 by the matrix cores' fp32
+// rate.  With a load for every element of W and a wavefront to a column tile (so that x was read up to four times) bf16, scores
+// in the projection, took 40.5 us at 16384 x 2048 to 64 experts (now 25.5), 15.5 at 256 x 2048 to 64 (11.6), 35 at 8192 x 2048 to 128 (23);
+// fp32 47 us at 10007 x 1000 to 96 (34), 236 at 65536 x 1024 to 128 (171: 101 TFLOP/s).
 // FE > 0: the tile holds whole rows of FE experts, and the scores and rewards are computed from it (as in k_gemm_bf16_wtc).
-constexpr int kSplitDepth = 4;          // steps on their way per wavefront
 constexpr int kSplitPitch = 33;
 
-template <bool BF16, bool ALIGNED, int FE>
-__global__ __launch_bounds__(1024) void k_gemm_split(const void *__restrict__ x_, const void *__restrict__ W_,
-                                                     const float *__restrict__ bias, int T, int d, int E, int ct, int ks,
-                                                     float *__restrict__ out, float *__restrict__ scores,
-                                                     int32_t *__restrict__ q, int k, float t, float qscale)
+template <int N>
+struct __attribute__((packed, aligned(4))) Words {
+    unsigned v[N];
+};
+
+template <bool BF16, bool XV, int FE, int CT, int RT, int KS>
+__global__ __launch_bounds__(64 * KS) void k_gemm_split(const void *__restrict__ x_, const void *__restrict__ W_,
+                                                        const float *__restrict__ bias, int T, int d, int E,
+                                                        float *__restrict__ out, float *__restrict__ scores,
+                                                        int32_t *__restrict__ q, int k, float t, float qscale)
 {
+    using El = std::conditional_t<BF16, unsigned short, unsigned>;      // (fp32 as bits)
     constexpr int STEP = BF16 ? 16 : 8, LK = STEP / 2;       // reduction indices per step, per lane and step
-    __shared__ __attribute__((aligned(16))) float s_part[16 * 32 * kSplitPitch];
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int c = wave % ct, part = wave / ct;
-    const int row0 = blockIdx.x * 32, col0 = blockIdx.y * 128;
-    const int row = row0 + (lane & 31), kl = LK * (lane >> 5);
-    const int col = col0 + 32 * c + (lane & 31);
-    const size_t xr = (size_t)(row < T ? row : T - 1) * d;
-    const int wc = col < E ? col : E - 1;
+    constexpr int DEPTH = RT * CT > 4 || (KS > 8 && (RT > 1 || (CT > 1 && FE == 0))) ? 3 : 4;      // steps on their way (what the registers hold)
+    constexpr int NW = BF16 && CT > 1 ? CT / 2 : CT;         // words of a lane's columns
+    constexpr int RS = KS * RT * CT * 32 * kSplitPitch * 4 <= 144 * 1024 ? RT : 1;       // row tiles added up at a time
+    __shared__ __attribute__((aligned(16))) float s_part[KS * RS * CT * 32 * kSplitPitch];
+    const int tid = threadIdx.x, lane = tid & 63, part = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row0 = blockIdx.x * (32 * RT), col0 = blockIdx.y * (32 * CT);
+    const int kl = LK * (lane >> 5);
+    const El *xp[RT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+        const int row = row0 + 32 * r + (lane & 31);
+        xp[r] = (const El *)x_ + (size_t)(row < T ? row : T - 1) * d + kl;
+    }
+    const int col = col0 + CT * (lane & 31);                 // (columns beyond E are computed from others and dropped)
+    const El *wp = (const El *)W_ + (size_t)kl * E;
+    const int wc = col < E ? col : 0;
     struct Frag {
-        u32x4 a;
-        unsigned b[LK];
+        u32x4 a[RT];
+        unsigned b[LK][NW];
     };
     auto load = [&](int k0, Frag &f, bool whole) {
-        const int kk = k0 + kl;
-        if (BF16) {
-            const unsigned short *xp = (const unsigned short *)x_ + xr + kk, *wp = (const unsigned short *)W_ + (size_t)kk * E + wc;
-            if (ALIGNED && whole) {
-                f.a = *(const u32x4 *)xp;
-            } else {
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+            if (XV && whole) {
+                f.a[r] = __builtin_bit_cast(u32x4, *(const Words<4> *)(xp[r] + k0));
+            } else if (BF16) {
                 unsigned v[8];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) v[i] = whole || kk + i < d ? xp[i] : 0u;
+                for (int i = 0; i < 8; ++i) v[i] = whole || k0 + kl + i < d ? xp[r][k0 + i] : 0u;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) f.a[i] = v[2 * i] | (v[2 * i + 1] << 16);
-            }
-#pragma unroll
-            for (int i = 0; i < LK; ++i) f.b[i] = whole || kk + i < d ? wp[(size_t)i * E] : 0u;
-        } else {
-            const float *xp = (const float *)x_ + xr + kk, *wp = (const float *)W_ + (size_t)kk * E + wc;
-            if (ALIGNED && whole) {
-                f.a = *(const u32x4 *)xp;
+                for (int i = 0; i < 4; ++i) f.a[r][i] = v[2 * i] | (v[2 * i + 1] << 16);
             } else {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) f.a[i] = whole || kk + i < d ? __float_as_uint(xp[i]) : 0u;
+                for (int i = 0; i < 4; ++i) f.a[r][i] = whole || k0 + kl + i < d ? xp[r][k0 + i] : 0u;
             }
+        }
 #pragma unroll
-            for (int i = 0; i < LK; ++i) f.b[i] = whole || kk + i < d ? __float_as_uint(wp[(size_t)i * E]) : 0u;
+        for (int i = 0; i < LK; ++i) {
+            const El *w = wp + (size_t)(k0 + i) * E;
+            const bool in = whole || k0 + kl + i < d;
+            if constexpr (BF16 && CT == 1) {
+                f.b[i][0] = in ? w[wc] : (El)0;
+            } else {
+                Words<NW> v = {};
+                if (in) v = *(const Words<NW> *)(w + wc);
+#pragma unroll
+                for (int c = 0; c < NW; ++c) f.b[i][c] = v.v[c];
+            }
         }
     };
-    f32x16 acc;
+    f32x16 acc[RT][CT];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[r][c][i] = 0.f;
     auto use = [&](const Frag &f) {
-        if (BF16) {
-            u32x4 b;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) b[i] = f.b[2 * i] | (f.b[2 * i + 1] << 16);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
-        } else {
+        for (int c = 0; c < CT; ++c) {
+            if constexpr (BF16) {
+                u32x4 b;
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(f.a[i]), __uint_as_float(f.b[i]), acc, 0, 0, 0);
+                for (int i = 0; i < 4; ++i)
+                    if constexpr (NW < CT) b[i] = __builtin_amdgcn_perm(f.b[2 * i + 1][c / 2], f.b[2 * i][c / 2], c % 2 ? 0x07060302u : 0x05040100u);
+                    else b[i] = f.b[2 * i][c] | (f.b[2 * i + 1][c] << 16);
+#pragma unroll
+                for (int r = 0; r < RT; ++r)
+                    acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.a[r]), __builtin_bit_cast(bf16x8, b), acc[r][c], 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int r = 0; r < RT; ++r)
+                        acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(f.a[r][i]), __uint_as_float(f.b[i][c]), acc[r][c], 0, 0, 0);
+            }
         }
     };
     // whole steps of this part, then (in the last part) what d leaves over
-    const int steps = d / STEP, s0 = (int)((long long)steps * part / ks), s1 = (int)((long long)steps * (part + 1) / ks);
-    Frag f[kSplitDepth];
+    const int steps = d / STEP, s0 = steps * part / KS, s1 = steps * (part + 1) / KS;
+    Frag f[DEPTH];
 #pragma unroll
-    for (int i = 0; i < kSplitDepth; ++i)
+    for (int i = 0; i < DEPTH; ++i)
         if (s0 + i < s1) load((s0 + i) * STEP, f[i], true);
     int s = s0;
-    for (; s + 2 * kSplitDepth <= s1; s += kSplitDepth) {
+    for (; s + 2 * DEPTH <= s1; s += DEPTH) {
 #pragma unroll
-        for (int i = 0; i < kSplitDepth; ++i) {
+        for (int i = 0; i < DEPTH; ++i) {
             const Frag cur = f[i];
-            load((s + kSplitDepth + i) * STEP, f[i], true);
+            load((s + DEPTH + i) * STEP, f[i], true);
             use(cur);
         }
     }
 #pragma unroll
-    for (int i = 0; i < kSplitDepth; ++i)
+    for (int i = 0; i < DEPTH; ++i)
         if (s + i < s1) {
             const Frag cur = f[i];
-            if (s + kSplitDepth + i < s1) load((s + kSplitDepth + i) * STEP, f[i], true);
+            if (s + DEPTH + i < s1) load((s + DEPTH + i) * STEP, f[i], true);
             use(cur);
         }
-    s += kSplitDepth;
+    s += DEPTH;
 #pragma unroll
-    for (int i = 0; i < kSplitDepth; ++i)
+    for (int i = 0; i < DEPTH; ++i)
         if (s + i < s1) use(f[i]);
-    if (part == ks - 1 && steps * STEP < d) {
+    if (part == KS - 1 && steps * STEP < d) {
         Frag g;
         load(steps * STEP, g, false);
         use(g);
     }
-    // acc[4 * j + i] is row 8 * j + 4 * (lane / 32) + i, column lane % 32 of the tile
-    float *mine = s_part + wave * (32 * kSplitPitch);
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int r0 = 0; r0 < RT; r0 += RS) {
+        if (r0 > 0) __syncthreads();
+        // acc[4 * j + i] is row 8 * j + 4 * (lane / 32) + i, column lane % 32 of the tile
 #pragma unroll
-        for (int i = 0; i < 4; ++i) mine[(8 * j + 4 * (lane >> 5) + i) * kSplitPitch + (lane & 31)] = acc[4 * j + i];
-    __syncthreads();
-    const int width = 32 * ct;
-    if constexpr (FE == 0) {
-        for (int o = tid; o < 32 * width; o += blockDim.x) {
-            const int r = o / width, n = o - r * width;
+        for (int r = 0; r < RS; ++r)
+#pragma unroll
+            for (int c = 0; c < CT; ++c) {
+                float *mine = s_part + ((part * RS + r) * CT + c) * (32 * kSplitPitch);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) mine[(8 * j + 4 * (lane >> 5) + i) * kSplitPitch + (lane & 31)] = acc[r0 + r][c][4 * j + i];
+            }
+        __syncthreads();
+        auto total = [&](int r, int n) {                // of row r (of RS * 32) and column n
+            const float *p0 = s_part + (((r >> 5) * CT + n % CT) * 32 + (r & 31)) * kSplitPitch + n / CT;
             float v = 0.f;
-            for (int p = 0; p < ks; ++p) v += s_part[((p * ct + (n >> 5)) * 32 + r) * kSplitPitch + (n & 31)];
-            if (row0 + r < T && col0 + n < E) out[(size_t)(row0 + r) * E + col0 + n] = v + (bias ? bias[col0 + n] : 0.f);
-        }
-    } else {
-        constexpr int EPLS = FE / 8;                // values per lane with 8 lanes per row
-        const int r = tid >> 3, lg = tid & 7;
-        if (r >= 32) return;
-        float xv[EPLS];
 #pragma unroll
-        for (int m = 0; m < EPLS; ++m) {
-            const int n = (m >> 2) * 32 + lg * 4 + (m & 3);
-            float v = 0.f;
-            for (int p = 0; p < ks; ++p) v += s_part[((p * ct + (n >> 5)) * 32 + r) * kSplitPitch + (n & 31)];
-            xv[m] = v + (bias ? bias[n] : 0.f);
-        }
-        float sc[EPLS];
-        int qq[EPLS];
-        softtopk_row<8, EPLS, true>(xv, lg, E, k, t, qscale, MAXSCORE_SOFTTOPK_A, sc, qq);
-        if (row0 + r < T) {
+            for (int p = 0; p < KS; ++p) v += p0[p * (RS * CT * 32 * kSplitPitch)];
+            return v;
+        };
+        const int row1 = row0 + 32 * r0;
+        if constexpr (FE == 0) {
+            for (int o = tid; o < RS * 32 * 32 * CT; o += 64 * KS) {
+                const int r = o / (32 * CT), n = o - r * (32 * CT);
+                if (row1 + r < T && col0 + n < E) out[(size_t)(row1 + r) * E + col0 + n] = total(r, n) + (bias ? bias[col0 + n] : 0.f);
+            }
+        } else {
+            constexpr int EPLS = FE / 8;                // values per lane with 8 lanes per row
+            static_assert(RS * 256 <= 64 * KS, "a group of lanes per row");
+            const int r = tid >> 3, lg = tid & 7;
+            if (r < RS * 32 && row1 + r < T) {
+                float xv[EPLS];
 #pragma unroll
-            for (int m = 0; m < EPLS; m += 4) {
-                const size_t o = (size_t)(row0 + r) * E + (m >> 2) * 32 + lg * 4;
-                if (out) *(float4 *)(out + o) = make_float4(xv[m], xv[m + 1], xv[m + 2], xv[m + 3]);
-                if (scores) *(float4 *)(scores + o) = make_float4(sc[m], sc[m + 1], sc[m + 2], sc[m + 3]);
-                if (q) *(int4 *)(q + o) = make_int4(qq[m], qq[m + 1], qq[m + 2], qq[m + 3]);
+                for (int m = 0; m < EPLS; ++m) {
+                    const int n = (m >> 2) * 32 + lg * 4 + (m & 3);
+                    xv[m] = total(r, n) + (bias ? bias[n] : 0.f);
+                }
+                float sc[EPLS];
+                int qq[EPLS];
+                softtopk_row<8, EPLS, true>(xv, lg, E, k, t, qscale, MAXSCORE_SOFTTOPK_A, sc, qq);
+#pragma unroll
+                for (int m = 0; m < EPLS; m += 4) {
+                    const size_t o = (size_t)(row1 + r) * E + (m >> 2) * 32 + lg * 4;
+                    if (out) *(float4 *)(out + o) = make_float4(xv[m], xv[m + 1], xv[m + 2], xv[m + 3]);
+                    if (scores) *(float4 *)(scores + o) = make_float4(sc[m], sc[m + 1], sc[m + 2], sc[m + 3]);
+                    if (q) *(int4 *)(q + o) = make_int4(qq[m], qq[m + 1], qq[m + 2], qq[m + 3]);
+                }
             }
         }
     }
@@ -585,31 +627,71 @@ __global__ __launch_bounds__(256) void k_copy16(const u32x4 *__restrict__ src, u
 
 }  // namespace
 
-// bf16: the split kernel as long as its workgroups fill the chip once, or twice with at most three column tiles each.  Tokens of
-// 2048, split against whole, scores in the projection: 64 experts, 8192 tokens 18 us against 32, 16384 34 against 33 (logits
-// alone 30 against 28), 16385 42 against 43; 128 experts, 8192 31 against 43, 8193 43 against 61, 16384 54 against 45.
-// Logits of 96 experts: 8192 22 against 34, 16384 42 against 35.  So the line lies right at 64 and 128 experts and a factor
-// of two too far at 96.
-static bool split_is_better(int T, int E)
+// The split kernel takes 32 rows to a workgroup while these fill the chip no more than once, and 64, which share the operands of W,
+// beyond: 16384 tokens of 2048 to 64 experts 25.5 us, with scores; with 32 rows (one column tile to a wavefront) it was 40.5.
+static int split_rows(int T, int E) { return (long long)((T + 31) / 32) * ((E + 127) / 128) <= 256 ? 32 : 64; }
+
+// bf16: the split kernel as long as its workgroups of 64 rows fill the chip no more than once.  Tokens of 2048, split against
+// whole (with the transposition of W), scores in the projection: 64 experts, 16384 tokens 25.5 us against 39, 20000 43.7 against 38;
+// 128 experts, 8192 23 against 45, 16384 39 against 48.  Logits: 96 experts, 16384 31 against 40, 32768 57 against 43; 256 experts,
+// 8192 27 against 44, 16384 55 against 45.
+static bool split_is_better(int T, int E) { return (long long)((T + 31) / 32) * ((E + 127) / 128) <= 512; }
+
+// Column tiles of a workgroup: neighbouring columns that a lane can read together, as many as there are tiles where that divides E (and
+// the words of W have four bytes' alignment).
+static int split_tiles(const void *W, bool bf16, int E)
 {
-    return (long long)((T + 31) / 32) * ((E + 127) / 128) <= (E <= 96 ? 512 : 256);
+    if (bf16 && (uintptr_t)W % 4 != 0) return 1;
+    if (E <= 32) return 1;
+    if (!bf16 && E > 64 && E <= 96 && E % 3 == 0) return 3;
+    return E > 64 && E % 4 == 0 ? 4 : E % 2 == 0 ? 2 : 1;
+}
+
+// Whether a lane can read 16 bytes of its row of x at once (four bytes' alignment will do).
+static bool split_xvec(const void *x, bool bf16, int d) { return !bf16 || (d % 2 == 0 && (uintptr_t)x % 4 == 0); }
+
+template <bool BF16, int FE, int CT>
+static void split_launch(const void *x, const void *W, const float *bias, int T, int d, int E, float *logits, float *scores, int32_t *q, int k,
+                         float t, float qscale, hipStream_t s)
+{
+    constexpr int KS1 = CT <= 2 ? 16 : 8, KS2 = CT == 1 ? 16 : 8;
+    const bool xv = split_xvec(x, BF16, d);
+    constexpr bool wide = BF16 || CT > 1;       // (fp32 up to 32 experts: 28 us with 32 rows, 30 with 64 at 16384 x 1024 to 16)
+    const int rows = xv && wide ? split_rows(T, E) : 32;
+    const dim3 g((T + rows - 1) / rows, (E + 32 * CT - 1) / (32 * CT));
+#define MS_SPLIT(VV, RR, KK)                                                                                                       \
+    hipLaunchKernelGGL((k_gemm_split<BF16, VV, FE, CT, RR, KK>), g, dim3(64 * KK), 0, s, x, W, bias, T, d, E, logits, scores, q, k, t, qscale)
+    if (rows == 64) {
+        if constexpr (wide) MS_SPLIT(true, 2, KS2);
+    } else if (xv) MS_SPLIT(true, 1, KS1);
+    else if constexpr (BF16 && FE == 0) MS_SPLIT(false, 1, KS1);
+#undef MS_SPLIT
+}
+
+// Scores in the projection: by the split kernel, if W allows whole rows in one workgroup.
+static bool split_scores(const void *x, const void *W, int T, int d, int E)
+{
+    return split_is_better(T, E) && split_tiles(W, true, E) == E / 32 && split_xvec(x, true, d);
 }
 
 int32_t gemm_run(const void *x, const void *W, const float *bias, int dtype, int T, int d, int E, float *logits,
                  void *wt_scratch, hipStream_t s)
 {
     const bool f32 = dtype == MAXSCORE_DTYPE_FP32;
-    if (f32 || split_is_better(T, E)) {
-        const int ct = E >= 128 ? 4 : (E + 31) / 32, ks = 16 / ct;
-        const bool al = d % (f32 ? 4 : 8) == 0 && ((uintptr_t)x % 16) == 0;
-        const dim3 g((T + 31) / 32, (E + 127) / 128), blk(64 * ct * ks);
-#define MS_SPLIT(BB, AA)                                                                                            \
-    hipLaunchKernelGGL((k_gemm_split<BB, AA, 0>), g, blk, 0, s, x, W, bias, T, d, E, ct, ks, logits, (float *)nullptr, \
-                       (int32_t *)nullptr, 0, 0.f, 0.f)
-        if (f32) { if (al) MS_SPLIT(false, true); else MS_SPLIT(false, false); }
-        else if (al) MS_SPLIT(true, true);
-        else MS_SPLIT(true, false);
-#undef MS_SPLIT
+    // (where the scores could come with the logits both have to come from the same kernel)
+    const bool as_scores = gemm_softtopk_supported(dtype, d, E, x, wt_scratch);
+    if (f32 || (as_scores ? split_scores(x, W, T, d, E) : split_is_better(T, E))) {
+        const int ct = split_tiles(W, !f32, E);
+#define MS_L(BB, CC) split_launch<BB, 0, CC>(x, W, bias, T, d, E, logits, nullptr, nullptr, 0, 0.f, 0.f, s)
+        if (f32) {
+            if (ct == 1) MS_L(false, 1);
+            else if (ct == 2) MS_L(false, 2);
+            else if (ct == 3) MS_L(false, 3);
+            else MS_L(false, 4);
+        } else if (ct == 1) MS_L(true, 1);
+        else if (ct == 2) MS_L(true, 2);
+        else MS_L(true, 4);
+#undef MS_L
         MS_HIP(hipGetLastError());
         return MAXSCORE_OK;
     }
@@ -675,15 +757,12 @@ int32_t gemm_softtopk_run(const void *x, const void *W, const float *bias, int d
     const unsigned short *xb = (const unsigned short *)x, *wb = (const unsigned short *)W;
     unsigned short *wt = (unsigned short *)wt_scratch;
     const float qscale = (float)(1 << shift);
-    if (split_is_better(T, E)) {
-        const int ct = E / 32, ks = 16 / ct;
-#define MS_SPLITF(FF)                                                                                                   \
-    hipLaunchKernelGGL((k_gemm_split<true, true, FF>), dim3((T + 31) / 32), dim3(1024), 0, s, x, W, bias, T, d, E, ct, ks, \
-                       logits, scores, q, k, t, qscale)
-        if (E == 32) MS_SPLITF(32);
-        else if (E == 64) MS_SPLITF(64);
-        else MS_SPLITF(128);
-#undef MS_SPLITF
+    if (split_scores(x, W, T, d, E)) {
+#define MS_LF(FF) split_launch<true, FF, FF / 32>(x, W, bias, T, d, E, logits, scores, q, k, t, qscale, s)
+        if (E == 32) MS_LF(32);
+        else if (E == 64) MS_LF(64);
+        else MS_LF(128);
+#undef MS_LF
         MS_HIP(hipGetLastError());
         return MAXSCORE_OK;
     }

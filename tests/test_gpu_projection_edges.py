@@ -22,6 +22,8 @@ def ms():
 @pytest.mark.parametrize("T,d,E", [
     (1, 1, 1), (31, 7, 33), (32, 8, 32), (33, 15, 31), (64, 16, 64), (65, 17, 65), (40, 64, 96), (95, 40, 97), (70, 1000, 127),
     (129, 136, 128), (33, 2056, 129), (50, 72, 300), (8192, 64, 128), (8193, 64, 128), (16384, 64, 64), (16385, 64, 32), (16385, 40, 96),
+    (8193, 33, 128), (8200, 50, 70), (8250, 34, 90), (8193, 100, 80), (4097, 48, 160), (16384, 64, 128), (16385, 64, 128), (8255, 37, 48),
+    (8195, 20, 20), (8193, 31, 97),
 ])
 def test_projection_edges(ms, T, d, E, dtype):
     print(f"projection edges T={T} d={d} E={E} {dtype}", flush=True)
@@ -36,4 +38,20 @@ def test_projection_edges(ms, T, d, E, dtype):
     k = min(3, E)
     both = ms.router_softtopk(x, W, b, k, t=1.0)
     scores, q = ms.softtopk(L, k, 1.0)
+    assert torch.equal(both["logits"], L) and torch.equal(both["scores"], scores) and torch.equal(both["q"], q)
+
+
+@pytest.mark.parametrize("dtype,xo,wo", [("bf16", 1, 0), ("bf16", 0, 1), ("bf16", 2, 2), ("bf16", 3, 3), ("fp32", 1, 1)])
+@pytest.mark.parametrize("T,d,E", [(70, 64, 64), (40, 66, 128), (8200, 64, 32), (33, 40, 96)])
+def test_operands_off_their_alignment(ms, T, d, E, dtype, xo, wo):
+    print(f"projection operands T={T} d={d} E={E} {dtype} {xo} {wo}", flush=True)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(T + d + E)
+    x = torch.randn(T * d + 8, generator=gen, device="cuda").to(dt)[xo:xo + T * d].view(T, d)
+    W = torch.randn(d * E + 8, generator=gen, device="cuda").to(dt)[wo:wo + d * E].view(d, E)
+    L = ms.router_logits(x, W, None)
+    xs, Ws = x.double().cpu(), W.double().cpu()
+    assert ((L.double().cpu() - xs @ Ws).abs() <= 1e-6 * (xs.abs() @ Ws.abs())).all()
+    both = ms.router_softtopk(x, W, None, 3, t=1.0)
+    scores, q = ms.softtopk(L, 3, 1.0)
     assert torch.equal(both["logits"], L) and torch.equal(both["scores"], scores) and torch.equal(both["q"], q)
