@@ -217,11 +217,19 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
         }
     }
     // holds (0 .. nb-1) and newcomers (nb .. 2nb-1) per margin bin over all experts
-    for (int b = wv; !CUM && b < 2 * nb; b += NW) {
-        int tot = 0;
-        for (int e = lane; e < E; e += 64) tot += s_h[b * ES + e];
-        tot = wave_sum(tot);
-        if (lane == 63) s.cum[b] = tot;
+    if constexpr (!CUM) {
+        constexpr int NB = (2 * kPBins + NW - 1) / NW;
+        int tot[NB];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) tot[i] = 0;
+        for (int e = lane; e < E; e += 64)
+#pragma unroll
+            for (int i = 0; i < NB; ++i) tot[i] += s_h[(wv + i * NW < 2 * nb ? wv + i * NW : 0) * ES + e];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            tot[i] = wave_sum(tot[i]);
+            if (lane == 63 && wv + i * NW < 2 * nb) s.cum[wv + i * NW] = tot[i];
+        }
     }
     __syncthreads();
     int sn = 0, sx = 0, sd = 0, sz = 0, sc = 0;
@@ -248,6 +256,7 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
         const int p = tid < E ? s.was[tid] : 0;
         if (wv < nwe && __any(p > 0)) {
             int r = 0;
+#pragma unroll 4
             for (int f = 0; f < E; f += 4) {
                 const int4 o = *(const int4 *)&s.was[f];              // (nothing but zeros from E on)
                 r += (o.x > 0 && (o.x < p || (o.x == p && f < tid)) ? 1 : 0) + (o.y > 0 && (o.y < p || (o.y == p && f + 1 < tid)) ? 1 : 0) +
@@ -269,17 +278,24 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
         int most = 0;
         if (need != 0) {
             const int *col = s_h + side * nb * ES + j;
-            int c[kPBins];
+            int c[kPBins];                                       // (one branch for all: nb is kPBins or half of it)
 #pragma unroll
-            for (int x = 0; x < kPBins; ++x) c[x] = x < nb ? col[x * ES] : 0;
+            for (int x = 0; x < kPBins / 2; ++x) c[x] = col[x * ES];
+#pragma unroll
+            for (int x = kPBins / 2; x < kPBins; ++x) c[x] = 0;
+            if (nb > kPBins / 2) {
+#pragma unroll
+                for (int x = kPBins / 2; x < kPBins; ++x) c[x] = col[x * ES];
+            }
             int run = 0, prev = 0, b = 0;                        // the first bin that reaches `need`, and the count before it
 #pragma unroll
             for (int x = 0; x < kPBins; ++x) {
                 run += c[x];
-                const bool less = x < nb && run < need;
+                const bool less = run < need;
                 b += less ? 1 : 0;
                 prev = less ? run : prev;
             }
+            b = b < nb ? b : nb;
             int d = mt.w;
             if (b < nb) {
                 const int lo = bin_edge(b, w0, bs), hi = bin_edge(b + 1, w0, bs);
@@ -367,6 +383,7 @@ __device__ __forceinline__ void gather_copies(const PriceArgs &a, int *s_h, Step
 {
     constexpr int Q = HALF ? 2 : 1;                                   // quads of counts in a piece
     const int quads = (2 * a.nb + 1) * a.es / 4, pieces = (quads + Q - 1) / Q;
+    const float inv = __builtin_amdgcn_rcpf((float)(a.es / 4));       // (u + 1/2 quads are 1/2 from a row's edge: 1e-7 of 3000 is less)
     uint4 x[M][N];
 #pragma unroll
     for (int m = 0; m < M; ++m) {
@@ -397,7 +414,7 @@ __device__ __forceinline__ void gather_copies(const PriceArgs &a, int *s_h, Step
             if (u >= quads) continue;
             ((int4 *)s_h)[u] = y[h];
             // the sums of the bins on the way (the columns beyond the experts do not belong to them)
-            const int row = u / (a.es / 4), c = 4 * (u - row * (a.es / 4));
+            const int row = (int)(((float)u + 0.5f) * inv), c = 4 * (u - row * (a.es / 4));
             const int sum = (c < a.E ? y[h].x : 0) + (c + 1 < a.E ? y[h].y : 0) + (c + 2 < a.E ? y[h].z : 0) + (c + 3 < a.E ? y[h].w : 0);
             if (row < 2 * a.nb && sum) atomicAdd(&s.cum[row], sum);
         }
@@ -462,6 +479,7 @@ __device__ __forceinline__ void price_rows(const PriceArgs &a, int t, int W, int
         if (MODE == kModeSlack && c < E && s_p[c] > 0) in_m |= 1u << m;
     }
     const bool common = MODE == kModeSlack && t >= a.even;            // margins of the common step are wanted
+    const bool any_in = MODE == kModeSlack && __any(in_m != 0) != 0;  // (without a price there is none)
     const unsigned keyo = (unsigned)bias << ib;           // an unfilled slot: reward 0, price 0
     int *s_n = s_hist + 2 * nb * ES;
     for (int i0 = r_first + grp; i0 - grp < r_end; i0 += NG) {
@@ -507,7 +525,7 @@ __device__ __forceinline__ void price_rows(const PriceArgs &a, int t, int W, int
             if (mg < W) atomicAdd(&s_hist[((real ? 0 : nb) + bin_of(mg, w0, bs)) * ES + E], 1);
         }
         if (!near) continue;
-        if (MODE == kModeSlack && common) {
+        if (MODE == kModeSlack && common && any_in) {
             // the i-th lowest hold with a price against the i-th best alternative without one, and the other way round
             const bool priced = slot && mc < E && s_p[mc < E ? mc : 0] > 0;
             const unsigned long long bp = group_bits(__ballot(priced)), bf = group_bits(__ballot(slot && !priced));
@@ -526,14 +544,18 @@ __device__ __forceinline__ void price_rows(const PriceArgs &a, int t, int W, int
                     u = u ? RK::below(ku, u) : 0u;
                     d = d ? RK::below(kd, d) : 0u;
                 }
+                bool near_i = false;
                 if (rp == i && u) {
                     const int mg = (int)((mine - u) >> ib);
-                    if (mg < W) atomicAdd(&s_hist[bin_of(mg, w0, bs) * ES + E], 1);
+                    near_i = mg < W;
+                    if (near_i) atomicAdd(&s_hist[bin_of(mg, w0, bs) * ES + E], 1);
                 }
                 if (rf == i && d) {
                     const int mg = (int)((mine - d) >> ib);
-                    if (mg < W) atomicAdd(&s_hist[(nb + bin_of(mg, w0, bs)) * ES + E], 1);
+                    near_i = mg < W;
+                    if (near_i) atomicAdd(&s_hist[(nb + bin_of(mg, w0, bs)) * ES + E], 1);
                 }
+                if (!__any(near_i)) break;                // (the margins of the pairs behind are wider)
             }
         }
         if (live) {
