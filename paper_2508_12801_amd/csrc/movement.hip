@@ -216,88 +216,71 @@ __global__ __launch_bounds__(256) void k_dispatch_tokens_elem(const TElem *__res
 
 __device__ __forceinline__ float bf16_to_f32(unsigned short b) { return __uint_as_float((unsigned)b << 16); }
 
-// One wavefront per token: every lane owns the 16-byte chunks lane, lane+64, ... of the row (NCH of them at a time),
-// accumulates the k gate-weighted expert rows in fp32, slot by slot, and writes fp32.  The indices of the slots (64 at most) are
-// read by one lane each, and the rows of kRegChunks / NCH slots are on their way together.  Bound by HBM (5.4 TB/s; a copy of
-// 1 GiB reaches 5.0, of 256 MiB, half of which the last cache holds, 5.9): 65536 tokens of 2048 from 8 of 128 experts 550 to
-// 497 us, 44032 of 1024 from 2 of 64 98 to 85 us.
-constexpr int kRegChunks = 8;
+// A wavefront takes a kilobyte of a token's row, its neighbours the next ones, and ends: the k gate-weighted pieces are accumulated in
+// fp32, slot by slot, and written as fp32.  The indices of the slots (64 at most) are read by one lane each, and the pieces of
+// kCombineSlots slots are on their way together.  Bound by HBM, which takes short-lived wavefronts in the order of the addresses best
+// (a plain fill: 6.8 TB/s with 16 bytes a thread and no loop, 4.0 to 5.6 with loops over a fixed grid): 65536 tokens of 2048 from 8 of 128
+// experts 472 us (5.7 TB/s), 505 with whole rows and a loop over the tokens in every wavefront; 44032 of 1024 from 2 of 64 79 to
+// 72, 32768 of 2048 from 8 of 64 246 to 234, up to 16384 the same.
+constexpr int kCombineSlots = 8;
 
-template <bool BF16, int NCH, bool NT>
+template <bool BF16, bool NT>
 __global__ __launch_bounds__(256) void k_combine(const u32x4 *__restrict__ buf, const int32_t *__restrict__ assign,
                                                  const int32_t *__restrict__ token_pos,
                                                  const float *__restrict__ gates, int T, int d, int E, int k, int C,
-                                                 int vec_per_row, float *__restrict__ y)
+                                                 int vec_per_row, int nch, float *__restrict__ y)
 {
     constexpr int EPV = BF16 ? 8 : 4;         // elements per 16-byte vector
-    constexpr int SL = kRegChunks / NCH;
     const int lane = threadIdx.x & 63;
-    const long long wave0 = (long long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    const long long n_waves = (long long)gridDim.x * (blockDim.x >> 6);
-    for (long long i = wave0; i < T; i += n_waves) {
-        for (int c0 = 0; c0 < vec_per_row; c0 += 64 * NCH) {
-            float acc[NCH][EPV];
+    const unsigned item = blockIdx.x * 4u + (threadIdx.x >> 6), i = __builtin_amdgcn_readfirstlane(item / (unsigned)nch);
+    if (i >= (unsigned)T) return;
+    const int c = (int)(item - i * (unsigned)nch) * 64 + lane;
+    const bool in = c < vec_per_row;
+    int e = -1, pos = 0;
+    float g = 0.f;
+    if (lane < k) {
+        const size_t at = (size_t)i * k + lane;
+        e = assign[at];
+        pos = token_pos[at];
+        g = gates[at];
+        // an empty slot, or a place outside the expert's buffer (an assignment made with another capacity)
+        if (e >= E || pos < 0 || pos >= C) e = -1;
+    }
+    float acc[EPV];
 #pragma unroll
-            for (int u = 0; u < NCH; ++u)
+    for (int v = 0; v < EPV; ++v) acc[v] = 0.f;
+    for (int s = 0; s < k; s += kCombineSlots) {
+        u32x4 vals[kCombineSlots];
+        bool have[kCombineSlots];
 #pragma unroll
-                for (int v = 0; v < EPV; ++v) acc[u][v] = 0.f;
-            int e = -1, pos = 0;
-            float g = 0.f;
-            if (lane < k) {
-                const size_t at = (size_t)i * k + lane;
-                e = assign[at];
-                pos = token_pos[at];
-                g = gates[at];
-                // an empty slot, or a place outside the expert's buffer (an assignment made with another capacity)
-                if (e >= E || pos < 0 || pos >= C) e = -1;
-            }
-            for (int s = 0; s < k; s += SL) {
-                u32x4 vals[SL][NCH];
-                bool have[SL];
+        for (int z = 0; z < kCombineSlots; ++z) {
+            const int es = s + z < k ? __builtin_amdgcn_readlane(e, s + z) : -1;
+            have[z] = es >= 0;
+            if (!have[z]) continue;
+            const u32x4 *src = buf + ((size_t)es * C + __builtin_amdgcn_readlane(pos, s + z)) * vec_per_row;
+            vals[z] = in ? get<NT>(src + c) : u32x4{0u, 0u, 0u, 0u};
+        }
 #pragma unroll
-                for (int z = 0; z < SL; ++z) {
-                    const int es = s + z < k ? __builtin_amdgcn_readlane(e, s + z) : -1;
-                    have[z] = es >= 0;
-                    if (!have[z]) continue;
-                    const u32x4 *src = buf + ((size_t)es * C + __builtin_amdgcn_readlane(pos, s + z)) * vec_per_row;
+        for (int z = 0; z < kCombineSlots; ++z) {
+            if (!have[z]) continue;
+            const float gs = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g), s + z));
+            if (BF16) {
 #pragma unroll
-                    for (int u = 0; u < NCH; ++u) {
-                        const int c = c0 + lane + 64 * u;
-                        vals[z][u] = c < vec_per_row ? get<NT>(src + c) : u32x4{0u, 0u, 0u, 0u};
-                    }
+                for (int w = 0; w < 4; ++w) {
+                    const unsigned word = vals[z][w];
+                    acc[2 * w] = fmaf(gs, bf16_to_f32((unsigned short)(word & 0xffffu)), acc[2 * w]);
+                    acc[2 * w + 1] = fmaf(gs, bf16_to_f32((unsigned short)(word >> 16)), acc[2 * w + 1]);
                 }
+            } else {
 #pragma unroll
-                for (int z = 0; z < SL; ++z) {
-                    if (!have[z]) continue;
-                    const float gs = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g), s + z));
-#pragma unroll
-                    for (int u = 0; u < NCH; ++u) {
-                        if (BF16) {
-#pragma unroll
-                            for (int w = 0; w < 4; ++w) {
-                                const unsigned word = vals[z][u][w];
-                                acc[u][2 * w] = fmaf(gs, bf16_to_f32((unsigned short)(word & 0xffffu)), acc[u][2 * w]);
-                                acc[u][2 * w + 1] = fmaf(gs, bf16_to_f32((unsigned short)(word >> 16)), acc[u][2 * w + 1]);
-                            }
-                        } else {
-#pragma unroll
-                            for (int w = 0; w < 4; ++w) acc[u][w] = fmaf(gs, __uint_as_float(vals[z][u][w]), acc[u][w]);
-                        }
-                    }
-                }
-            }
-            float *yr = y + (size_t)i * d;
-#pragma unroll
-            for (int u = 0; u < NCH; ++u) {
-                const int c = c0 + lane + 64 * u;
-                if (c < vec_per_row) {
-                    f32x4 *dst = (f32x4 *)(yr + (size_t)c * EPV);
-                    put<NT>(f32x4{acc[u][0], acc[u][1], acc[u][2], acc[u][3]}, dst);
-                    if (BF16) put<NT>(f32x4{acc[u][4], acc[u][5], acc[u][6], acc[u][7]}, dst + 1);
-                }
+                for (int w = 0; w < 4; ++w) acc[w] = fmaf(gs, __uint_as_float(vals[z][w]), acc[w]);
             }
         }
     }
+    if (!in) return;
+    f32x4 *dst = (f32x4 *)(y + (size_t)i * d + (size_t)c * EPV);
+    put<NT>(f32x4{acc[0], acc[1], acc[2], acc[3]}, dst);
+    if (BF16) put<NT>(f32x4{acc[4], acc[5], acc[6], acc[7]}, dst + 1);
 }
 
 template <bool BF16>
@@ -367,25 +350,22 @@ int32_t combine_run(const void *buf, int dtype, const int32_t *assign, const int
     const int eb = dtype == MAXSCORE_DTYPE_BF16 ? 2 : 4;
     const bool vec = ((size_t)d * eb) % 16 == 0 && ((uintptr_t)buf % 16) == 0 && ((uintptr_t)y % 16) == 0;
     if (vec) {
-        long long grid = ((long long)T + 3) / 4;
-        if (grid > 256 * 16) grid = 256 * 16;
-        if (grid < 1) grid = 1;
-        const int vpr = (int)((size_t)d * eb / 16);
+        const int vpr = (int)((size_t)d * eb / 16), nch = (vpr + 63) / 64;
+        const int most = std::max(1, (1 << 24) / nch);              // tokens a launch (its threads are counted in 32 bits)
         const bool nt = beyond_caches((size_t)E * C * d * eb + (size_t)T * d * 4);
-#define MS_COMBINE(BB, NN)                                                                                               \
-    hipLaunchKernelGGL((nt ? k_combine<BB, NN, true> : k_combine<BB, NN, false>), dim3((unsigned)grid), dim3(256), 0, s, \
-                       (const u32x4 *)buf, assign, token_pos, gates, T, d, E, k, C, vpr, y)
-#define MS_COMBINE_N(BB)                     \
-    do {                                     \
-        if (vpr <= 64) MS_COMBINE(BB, 1);    \
-        else if (vpr <= 128) MS_COMBINE(BB, 2); \
-        else if (vpr <= 256) MS_COMBINE(BB, 4); \
-        else MS_COMBINE(BB, 8);              \
-    } while (0)
-        if (eb == 2) MS_COMBINE_N(true);
-        else MS_COMBINE_N(false);
-#undef MS_COMBINE_N
+        for (int i0 = 0; i0 < T; i0 += most) {
+            const int n = std::min(most, T - i0);
+            const size_t at = (size_t)i0 * k;
+#define MS_COMBINE(BB, NN)                                                                                                      \
+    hipLaunchKernelGGL((k_combine<BB, NN>), dim3((unsigned)(((size_t)n * nch + 3) / 4)), dim3(256), 0, s, (const u32x4 *)buf, assign + at, \
+                       token_pos + at, gates + at, n, d, E, k, C, vpr, nch, y + (size_t)i0 * d)
+            if (eb == 2) {
+                if (nt) MS_COMBINE(true, true);
+                else MS_COMBINE(true, false);
+            } else if (nt) MS_COMBINE(false, true);
+            else MS_COMBINE(false, false);
 #undef MS_COMBINE
+        }
     } else {
         size_t n = (size_t)T * d;
         long long grid = (long long)((n + 255) / 256);

@@ -37,6 +37,7 @@ def routed_case(ms, T, E, k, C, seed):
     (257, 100, 7, 3, 120, "bf16"),      # 200-byte rows: not a whole number of 16-byte vectors
     (513, 33, 5, 2, 300, "fp32"),       # odd row length, slack capacity (zero padding)
     (64, 4096, 128, 8, 4, "bf16"),      # rows longer than one pass of the combine kernel
+    (131, 520, 24, 9, 60, "bf16"), (77, 1028, 40, 17, 40, "fp32"),      # pieces of rows that end early, more slots than at once
 ])
 def test_dispatch_tokens_and_combine(ms, T, d, E, k, C, dtype):
     print(f"movement T={T} d={d} E={E} k={k} C={C} {dtype}", flush=True)
@@ -143,3 +144,20 @@ def test_movement_argument_errors(ms):
         ms.dispatch_tokens(x, off, tok, 2000, 4)            # more experts than supported
     with pytest.raises(TypeError):
         ms.dispatch_tokens(x.double(), off, tok, 2, 4)      # unsupported element type
+
+
+def test_combine_in_several_launches(ms):
+    """More pieces of rows than one launch takes (2^24): rows on both sides of the cut, and the last one."""
+    print("combine in several launches", flush=True)
+    T, d, C = 1 << 21, 4608, 8
+    cut = (1 << 24) // 9
+    buf = torch.randn(1, C, d, device="cuda").to(torch.bfloat16)
+    assign = torch.full((T, 1), -1, dtype=torch.int32, device="cuda")
+    pos, gates = torch.zeros_like(assign), torch.ones((T, 1), device="cuda")
+    rows = [0, cut - 1, cut, cut + 1, T - 1]
+    for n, i in enumerate(rows):
+        assign[i], pos[i], gates[i] = 0, n, 0.5 + n
+    y = ms.combine(buf, assign, pos, gates)
+    for n, i in enumerate(rows):
+        assert torch.equal(y[i], buf[0, n].float() * (0.5 + n))
+    assert not y[cut - 3:cut - 1].any() and not y[cut + 2:cut + 4].any() and not y[1].any() and not y[T - 2].any()
