@@ -52,29 +52,34 @@ __global__ __launch_bounds__(256) void k_colsum(const float *__restrict__ scores
 }
 
 // One workgroup: column means, the loss and its derivative with respect to the scores of a column.  Thread
-// (j, g) adds the partial sums g, g+groups, ... of column j; the groups are then added in order.
+// (j, g) adds the partial sums g, g+groups, ... of column j (of VEC columns: all on their way at once up to 128 experts; beyond, where
+// each thread has more of them, one column a thread is as fast); the groups are then added in order.
+template <int VEC>
 __global__ __launch_bounds__(1024) void k_aux_final(const float *__restrict__ part, int n_blocks,
                                                     const int32_t *__restrict__ offsets, int T, int E, int epad,
                                                     float lam, float *__restrict__ loss,
                                                     float *__restrict__ mean_scores, float *__restrict__ dscores_col)
 {
-    __shared__ double s_red[1024];
+    typedef float vec_t __attribute__((ext_vector_type(VEC)));
+    typedef double wide_t __attribute__((ext_vector_type(VEC)));
+    __shared__ __attribute__((aligned(32))) double s_red[1024 * VEC];
     __shared__ double s_w[16];
-    const int tid = threadIdx.x, groups = 1024 / epad;
+    const int tid = threadIdx.x, groups = 1024 * VEC / epad;
     {
-        const int j = tid % epad, g = tid / epad;
-        double sum = 0.0;
+        const int j = tid % (epad / VEC) * VEC, g = tid / (epad / VEC);
+        wide_t sum = 0.0;
         if (j < E) {
 #pragma unroll 16
-            for (int b = g; b < n_blocks; b += groups) sum += (double)part[(size_t)b * E + j];
+            for (int b = g; b < n_blocks; b += groups) sum += __builtin_convertvector(*(const vec_t *)(part + (size_t)b * E + j), wide_t);
         }
-        s_red[g * epad + j] = sum;
+        *(wide_t *)&s_red[g * epad + j] = sum;
     }
     __syncthreads();
     const int j = tid;
     double term = 0.0;
     if (j < E) {
         double sum = 0.0;
+#pragma unroll 8
         for (int g = 0; g < groups; ++g) sum += s_red[g * epad + j];
         const double mean_a = sum / T;
         const double mean_p = (double)(offsets[j + 1] - offsets[j]) / T;
@@ -93,7 +98,9 @@ __global__ __launch_bounds__(1024) void k_aux_final(const float *__restrict__ pa
 }
 
 // G lanes own a token row, lane l the 4-column pieces l, l+G, ... of it: a wavefront has 64 / G rows on their way, in whole
-// lines.  Bound by HBM: 65536 rows of 128 experts 31 us with a wavefront per row and 4-byte loads, 24 us so (4.4 TB/s).
+// lines.  The gradients of a row's gates are put in their columns through LDS, each read by one lane (read by all of them and compared
+// with every column: 16 loads and 200 instructions a row).  Bound by HBM: 65536 rows of 128 experts 17.4 us (6.0 TB/s; 23.0 the other
+// way), of 64 12.9 (14.2).
 template <int G, int EPL>
 __global__ __launch_bounds__(256) void k_gates_backward(const float *__restrict__ logits,
                                                         const float *__restrict__ scores,
@@ -103,7 +110,9 @@ __global__ __launch_bounds__(256) void k_gates_backward(const float *__restrict_
                                                         int vec, float *__restrict__ dlogits)
 {
     constexpr int NG = 256 / G;
+    __shared__ __attribute__((aligned(16))) float s_d[NG][G * EPL];      // gradients of a row's gates, at their experts
     const int lg = threadIdx.x & (G - 1);
+    float *mine = s_d[threadIdx.x / G];
     auto col = [&](int m) { return (m >> 2) * (4 * G) + lg * 4 + (m & 3); };
     auto load = [&](const float *__restrict__ p, float fill, float(&x)[EPL]) {
 #pragma unroll
@@ -118,19 +127,30 @@ __global__ __launch_bounds__(256) void k_gates_backward(const float *__restrict_
             }
         }
     };
+    auto row_sync = [] {                     // (a row's lanes are of one wavefront)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
     for (int row = blockIdx.x * NG + threadIdx.x / G; row < T; row += gridDim.x * NG) {
-        float l[EPL], a[EPL], g[EPL];
+        float l[EPL], a[EPL], g[EPL] = {};
         load(logits + (size_t)row * E, -INFINITY, l);
         load(scores + (size_t)row * E, 0.f, a);
+        if (dscores_col) load(dscores_col, 0.f, g);
 #pragma unroll
-        for (int m = 0; m < EPL; ++m) g[m] = (dscores_col && col(m) < E) ? dscores_col[col(m)] : 0.f;
-        for (int s = 0; s < k; ++s) {
+        for (int m = 0; m < EPL; m += 4) *(float4 *)(mine + col(m)) = make_float4(0.f, 0.f, 0.f, 0.f);
+        row_sync();
+        for (int s = lg; s < k; s += G) {
             const int e = assign[(size_t)row * k + s];
-            const float d = dgates[(size_t)row * k + s];
-#pragma unroll
-            for (int m = 0; m < EPL; ++m)
-                if (e == col(m)) g[m] += d;
+            if (e >= 0 && e < E) atomicAdd(mine + e, dgates[(size_t)row * k + s]);
         }
+        row_sync();
+#pragma unroll
+        for (int m = 0; m < EPL; m += 4) {
+            const float4 f = *(const float4 *)(mine + col(m));
+            g[m] += f.x; g[m + 1] += f.y; g[m + 2] += f.z; g[m + 3] += f.w;
+        }
+        row_sync();
         float mx = -INFINITY;
 #pragma unroll
         for (int m = 0; m < EPL; ++m) mx = fmaxf(mx, l[m]);
@@ -167,7 +187,7 @@ void launch_bwd(const float *logits, const float *scores, const int32_t *assign,
                 const float *dcol, int T, int E, int k, float *dlogits, hipStream_t s)
 {
     const int ng = 256 / G, grid = (T + ng - 1) / ng < 8192 ? (T + ng - 1) / ng : 8192;
-    const int vec = E % 4 == 0 && (((uintptr_t)logits | (uintptr_t)scores | (uintptr_t)dlogits) % 16) == 0 ? 1 : 0;
+    const int vec = E % 4 == 0 && (((uintptr_t)logits | (uintptr_t)scores | (uintptr_t)dlogits | (uintptr_t)dcol) % 16) == 0 ? 1 : 0;
     hipLaunchKernelGGL((k_gates_backward<G, EPL>), dim3(grid), dim3(256), 0, s, logits, scores, assign, dgates, dcol, T, E,
                        k, vec, dlogits);
 }
@@ -195,8 +215,8 @@ int32_t aux_loss_run(const float *scores, const int32_t *offsets, int T, int E, 
         hipLaunchKernelGGL(k_colsum<1>, dim3(n_blocks), dim3(256), shm, s, scores, T, E, cols, rows_per_block, part);
     int epad = 1;
     while (epad < E) epad <<= 1;
-    hipLaunchKernelGGL(k_aux_final, dim3(1), dim3(1024), 0, s, part, n_blocks, offsets, T, E, epad, lam, loss,
-                       mean_scores, dscores_col);
+    if (E % 4 == 0 && E <= 128) hipLaunchKernelGGL(k_aux_final<4>, dim3(1), dim3(1024), 0, s, part, n_blocks, offsets, T, E, epad, lam, loss, mean_scores, dscores_col);
+    else hipLaunchKernelGGL(k_aux_final<1>, dim3(1), dim3(1024), 0, s, part, n_blocks, offsets, T, E, epad, lam, loss, mean_scores, dscores_col);
     MS_HIP(hipGetLastError());
     return MAXSCORE_OK;
 }
