@@ -139,7 +139,9 @@ inline bool iter_tiles_are_words(const WorkspaceLayout &L, int T, int E, int k)
 {
     return iter_tiles_off(L, T, E) + 4 * iter_tiles(T, E, k) <= L.price_off;
 }
-// Pinned words of the calling thread (16 of them, cleared by whoever uses them), and the same as the device sees them.
+// Pinned words of the calling thread (kSolverWords of them, cleared by whoever uses them, and kMaxE more behind them for results per
+// expert), and the same as the device sees them.
+constexpr int kSolverWords = 16;
 int32_t solver_words(int **host, int **dev);
 // With kernel timing on, records the next of the calling thread's timing events: before and after the first kernel of a round
 // (auction) or pass (price solve) and after its second, three in all.

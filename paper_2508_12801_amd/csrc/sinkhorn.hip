@@ -9,13 +9,13 @@
 // Three ways to do it, by size; column sums are added in a fixed order everywhere, beyond four rows in double where one
 // workgroup does it all, from the first on with eight lanes to a row; row sums are trees over the columns:
 //   small    up to 65536 scores of up to 16 experts, half as many of up to 64: the whole call is one workgroup that keeps
-//            K in registers, a thread owns whole rows.  An iteration takes 4 us (two barriers and six exchanges), two launches
-//            each 8.  The limit is that of the registers: 1024 threads of 64 entries, 512 beyond 16 columns.
+//            K in registers, a thread owns whole rows.  An iteration takes 2.5 us (two barriers, 300 instructions of every
+//            wavefront), two launches each 8.  The limit is that of the registers: 1024 threads of 64 entries, 512 beyond 16 columns.
 //   medium   up to 64 experts: eight lanes per row, K recomputed from the scores; one launch per iteration, whose
 //            workgroups begin by adding up the column sums of the iteration before
 //   large    one wavefront per row, lane l holds experts l, l+64, ...; rows and columns are launches of their own
-// 20 iterations, before and after the first two ways: 4096 tokens of 16 experts 228 and 90 us (4097, the first the medium way
-// takes, 142), 16384 of 64 350 and 213 us, 65536 of 64 574 and 315 us.
+// 20 iterations, before and after the first two ways: 4096 tokens of 16 experts 228 and 74 us (4097, the first the medium way
+// takes, 116), 16384 of 64 350 and 178 us.
 #include <type_traits>
 
 #include "common.h"
@@ -121,7 +121,7 @@ __global__ __launch_bounds__(1024) void k_sk_init(const int *__restrict__ counts
     for (int c = 0; c < kSkCopies; ++c) n += j < E ? counts[c * kMaxE + j] : 0;
     sk_targets(n, T, E, C, cap, target);
     if (j < E) {
-        caps[j] = cap;
+        if (caps) caps[j] = cap;
         targets[j] = target;
         v[j] = 1.f;
     }
@@ -137,6 +137,57 @@ __device__ __forceinline__ float sk_column(double sum, float m)
 // Column sums over a wavefront: lanes exchange halves of their columns until every lane holds the sum of one of them (the
 // last steps of EP < 64 add equal columns).  A thread comes with the sums of its own 64 / EP rows.  Up to four rows are added in
 // fp32, sums of four rows in double; what lanes exchange for the first of these additions is still an fp32 number.
+// (Values move between lanes by swaps and lane moves: shuffles through LDS were a third of an iteration.)
+template <int OFF>
+__device__ __forceinline__ int sk_move(int v)            // from the lane OFF away, within sixteen lanes
+{
+    static_assert(OFF <= 8, "within a row of lanes");
+    if constexpr (OFF == 8) return __builtin_amdgcn_mov_dpp(v, 0x128, 0xf, 0xf, true);                   // row_ror:8
+    else if constexpr (OFF == 4) {
+        const int from_above = __builtin_amdgcn_update_dpp(0, v, 0x104, 0xf, 0x5, false);                // row_shl:4, lanes 0-3 and 8-11
+        return __builtin_amdgcn_update_dpp(from_above, v, 0x114, 0xf, 0xa, false);                       // row_shr:4, the others
+    } else return __builtin_amdgcn_mov_dpp(v, OFF == 2 ? 0x4E : 0xB1, 0xf, 0xf, true);                   // quad_perm
+}
+template <int OFF>
+__device__ __forceinline__ float sk_move(float v) { return __int_as_float(sk_move<OFF>(__float_as_int(v))); }
+template <int OFF>
+__device__ __forceinline__ double sk_move(double v)
+{
+    return __hiloint2double(sk_move<OFF>(__double2hiint(v)), sk_move<OFF>(__double2loint(v)));
+}
+// a of the lanes without bit OFF stays, that of the others goes to the lane OFF below; b the other way round
+template <int OFF>
+__device__ __forceinline__ void sk_swap(unsigned &a, unsigned &b)
+{
+    static_assert(OFF == 16 || OFF == 32, "rows of lanes");
+    if constexpr (OFF == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+        a = r[0];
+        b = r[1];
+    } else {
+        const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+        a = r[0];
+        b = r[1];
+    }
+}
+template <int OFF>
+__device__ __forceinline__ void sk_swap(float &a, float &b)
+{
+    unsigned x = __float_as_uint(a), y = __float_as_uint(b);
+    sk_swap<OFF>(x, y);
+    a = __uint_as_float(x);
+    b = __uint_as_float(y);
+}
+template <int OFF>
+__device__ __forceinline__ void sk_swap(double &a, double &b)
+{
+    unsigned x = (unsigned)__double2loint(a), y = (unsigned)__double2loint(b), z = (unsigned)__double2hiint(a), w = (unsigned)__double2hiint(b);
+    sk_swap<OFF>(x, y);
+    sk_swap<OFF>(z, w);
+    a = __hiloint2double((int)z, (int)x);
+    b = __hiloint2double((int)w, (int)y);
+}
+
 template <int HALF, int OFF, int N, typename V, typename W>
 __device__ __forceinline__ void sk_exchange(const V (&f)[N], W (&sum)[HALF], int lane, int &column)
 {
@@ -144,8 +195,14 @@ __device__ __forceinline__ void sk_exchange(const V (&f)[N], W (&sum)[HALF], int
     column |= up ? HALF : 0;
 #pragma unroll
     for (int c = 0; c < HALF; ++c) {
-        const V give = up ? f[c] : f[c + HALF], keep = up ? f[c + HALF] : f[c];
-        sum[c] = (W)keep + (W)__shfl_xor(give, OFF);
+        if constexpr (OFF >= 16) {
+            V a = f[c], b = f[c + HALF];
+            sk_swap<OFF>(a, b);
+            sum[c] = (W)a + (W)b;
+        } else {
+            const V give = up ? f[c] : f[c + HALF], keep = up ? f[c + HALF] : f[c];
+            sum[c] = (W)keep + (W)sk_move<OFF>(give);
+        }
     }
 }
 
@@ -162,7 +219,10 @@ __device__ __forceinline__ double sk_reduce_scatter(const V (&f)[EP], int lane, 
         return sk_reduce_scatter<EP / 2, OFF / 2>(h, lane, column);
     } else {
         double d = f[0];
-        for (int off = OFF; off >= 1; off >>= 1) d += __shfl_xor(d, off);
+        if constexpr (OFF >= 4) d += sk_move<4>(d);
+        if constexpr (OFF >= 2) d += sk_move<2>(d);
+        if constexpr (OFF >= 1) d += sk_move<1>(d);
+        static_assert(OFF <= 4, "eight columns at least");
         return d;
     }
 }
@@ -174,7 +234,7 @@ constexpr int kSkSmallThreads = EP <= 16 ? 1024 : 512;
 template <int EP>
 __global__ __launch_bounds__(kSkSmallThreads<EP>) void k_sk_small(const float *__restrict__ scores, int T, int E, int C, float inv_tau,
                                                    int n_iter, int32_t *__restrict__ assign, float *__restrict__ plan,
-                                                   int32_t *__restrict__ caps)
+                                                   int32_t *__restrict__ caps)          // (of the host, or null)
 {
     constexpr int RR = 64 / EP;                 // rows per thread: r * nt + tid
     using Acc = std::conditional_t<(RR > 4), double, float>;
@@ -225,7 +285,7 @@ __global__ __launch_bounds__(kSkSmallThreads<EP>) void k_sk_small(const float *_
     if (tid < EP) {
         s_target[tid] = tid < E ? target : 0.f;
         s_v[tid] = tid < E && target > 0.f ? 1.f : 0.f;
-        if (tid < E) caps[tid] = cap;
+        if (tid < E && caps) caps[tid] = cap;
     }
     __syncthreads();
 #pragma unroll
@@ -255,8 +315,19 @@ __global__ __launch_bounds__(kSkSmallThreads<EP>) void k_sk_small(const float *_
         __syncthreads();
         if (wv == 0) {
             double tot = 0.0;
+#pragma unroll 4
             for (int w = lane / EP; w < nw; w += 64 / EP) tot += s_red[w * EP + lane % EP];
-            for (int o = EP; o < 64; o <<= 1) tot += __shfl_xor(tot, o);
+            if constexpr (EP <= 8) tot += sk_move<8>(tot);
+            if constexpr (EP <= 16) {
+                double o = tot;
+                sk_swap<16>(tot, o);
+                tot += o;
+            }
+            if constexpr (EP <= 32) {
+                double o = tot;
+                sk_swap<32>(tot, o);
+                tot += o;
+            }
             if (lane < E) s_v[lane] = sk_column(tot, s_target[lane]);
         }
         __syncthreads();
@@ -573,11 +644,21 @@ __global__ __launch_bounds__(256) void k_sk_round(const float *__restrict__ scor
     }
 }
 
-int32_t copy_caps(const int32_t *caps, int32_t *caps_host, int E, hipStream_t s)
+// The capacities go to pinned words of the calling thread (a copy of a few bytes is a kernel of its own, 4 us).
+int32_t caps_words(int32_t *caps_host, int **words, int **words_dev)
+{
+    *words = *words_dev = nullptr;
+    if (!caps_host) return MAXSCORE_OK;
+    const int32_t rc = solver_words(words, words_dev);
+    *words += kSolverWords;
+    *words_dev += kSolverWords;
+    return rc;
+}
+int32_t copy_caps(const int *words, int32_t *caps_host, int E, hipStream_t s)
 {
     if (!caps_host) return MAXSCORE_OK;
-    MS_HIP(hipMemcpyAsync(caps_host, caps, sizeof(int32_t) * E, hipMemcpyDeviceToHost, s));
     MS_HIP(hipStreamSynchronize(s));
+    for (int e = 0; e < E; ++e) caps_host[e] = ((const volatile int *)words)[e];
     return MAXSCORE_OK;
 }
 
@@ -589,7 +670,9 @@ int32_t run_epl(const float *scores, int T, int E, int C, float tau, int n_iter,
     int32_t *top1 = (int32_t *)(ws + L.aux_off);
     int *counts = (int *)(ws + L.price_off);
     float *targets = (float *)(ws + L.gcount_off), *v = targets + kMaxE;
-    int32_t *caps = (int32_t *)(ws + L.cap_off);
+    int *words, *caps;
+    const int32_t rc = caps_words(caps_host, &words, &caps);
+    if (rc) return rc;
     float *u = (float *)(ws + L.klist_off);
     float *part = (float *)(ws + L.wcnt_off);
     int grid = T < 4 * kSkBlocksMax ? (T + 3) / 4 : kSkBlocksMax;
@@ -619,7 +702,7 @@ int32_t run_epl(const float *scores, int T, int E, int C, float tau, int n_iter,
         else MS_SK(8);
 #undef MS_SK
         MS_HIP(hipGetLastError());
-        return copy_caps(caps, caps_host, E, s);
+        return copy_caps(words, caps_host, E, s);
     }
     for (int it = 0; it < n_iter; ++it) {
         hipLaunchKernelGGL(k_sk_row<EPL>, dim3(grid), dim3(256), (size_t)4 * E * sizeof(float), s, scores, top1,
@@ -629,7 +712,7 @@ int32_t run_epl(const float *scores, int T, int E, int C, float tau, int n_iter,
     hipLaunchKernelGGL(k_sk_round<EPL>, dim3(grid), dim3(256), 0, s, scores, top1, targets, v, u, n_iter > 0 ? 1 : 0,
                        T, E, inv_tau, assign, plan);
     MS_HIP(hipGetLastError());
-    return copy_caps(caps, caps_host, E, s);
+    return copy_caps(words, caps_host, E, s);
 }
 
 }  // namespace
@@ -641,7 +724,9 @@ int32_t sinkhorn_run(const float *scores, int T, int E, int C, float tau, int n_
     const int ep = E <= 8 ? 8 : E <= 16 ? 16 : E <= 32 ? 32 : 64;
     if (E <= 64 && T <= (ep <= 16 ? 1024 : 512) * (64 / ep)) {
         const int most = ep <= 16 ? 1024 : 512, nt = T >= most ? most : (T + 63) / 64 * 64;
-        int32_t *caps = (int32_t *)(ws + workspace_layout(T, E, 1).cap_off);
+        int *words, *caps;
+        const int32_t rc = caps_words(caps_host, &words, &caps);
+        if (rc) return rc;
 #define MS_SK(PP) hipLaunchKernelGGL(k_sk_small<PP>, dim3(1), dim3(nt), 0, s, scores, T, E, C, 1.f / tau, n_iter, assign, plan, caps)
         if (ep == 8) MS_SK(8);
         else if (ep == 16) MS_SK(16);
@@ -649,7 +734,7 @@ int32_t sinkhorn_run(const float *scores, int T, int E, int C, float tau, int n_
         else MS_SK(64);
 #undef MS_SK
         MS_HIP(hipGetLastError());
-        return copy_caps(caps, caps_host, E, s);
+        return copy_caps(words, caps_host, E, s);
     }
     if (epl <= 1) return run_epl<1>(scores, T, E, C, tau, n_iter, assign, plan, caps_host, ws, s);
     if (epl <= 2) return run_epl<2>(scores, T, E, C, tau, n_iter, assign, plan, caps_host, ws, s);

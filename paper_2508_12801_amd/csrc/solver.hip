@@ -1807,7 +1807,7 @@ int32_t kvec_check(const int32_t *kvec, int T, int E, int k, char *ws, long long
 // Per-host-thread objects of the solver that outlive a call: the pinned flag the select pass writes `done` into,
 // and the events (created once, reused by every solve of the thread, never destroyed: a few handles per thread).
 struct SolverHost {
-    // pinned and mapped, 16 words: [0] the solve has ended, [4..7] the finisher's report, [kHostRoundWord] rounds done
+    // pinned and mapped, kSolverWords and one per expert: [0] the solve has ended, [4..7] the finisher's report, [kHostRoundWord] rounds done
     int *flag = nullptr;
     int *flag_dev = nullptr;    // the same words as the device sees them
     SolverState *state = nullptr, *state_dev = nullptr;      // pinned and mapped: the final state of the last solve
@@ -1833,7 +1833,7 @@ static int32_t solver_host(SolverHost **out)
         }
     if (!h) return MAXSCORE_ERR_HIP;
     if (h->device < 0) {
-        MS_HIP(hipHostMalloc((void **)&h->flag, 64, hipHostMallocMapped));
+        MS_HIP(hipHostMalloc((void **)&h->flag, sizeof(int) * (kSolverWords + kMaxE), hipHostMallocMapped));
         MS_HIP(hipHostGetDevicePointer((void **)&h->flag_dev, h->flag, 0));
         MS_HIP(hipHostMalloc((void **)&h->state, sizeof(SolverState), hipHostMallocMapped));
         MS_HIP(hipHostGetDevicePointer((void **)&h->state_dev, h->state, 0));
