@@ -60,13 +60,13 @@ __global__ __launch_bounds__(256) void k_dispatch_tokens(const u32x4 *__restrict
 // Either way the stretches cover every list exactly once, whatever its order: the samples and the same bisection with a
 // larger key never end further left.  Workgroups from n_tb on zero the rows no token has.
 // Bound by HBM: row by row in list order every row of x comes from memory k times once x is larger than the caches.
-// 65536 tokens of 2048 to 8 of 128 experts: 683 to 441 us, 5.5 TB/s with x counted once; 16384 to 8 of 64: 163 to 110 us.  The
+// 65536 tokens of 2048 to 8 of 128 experts: 683 to 441 us, 5.5 TB/s with x counted once (474 behind a projection of so many tokens); 16384 to 8 of 64: 163 to 110 us.  The
 // same in other orders: shuffled 632 us (2.8 ms without the samples), descending 640 (13.9), shuffled by eight 680 (785 with a
 // list after the other instead of 64 together).
 constexpr int kBlockTokens = 32, kTokenRows = 16, kListMaxE = 2048, kListSamples = 8;
 
-template <bool NT>
-__global__ __launch_bounds__(256) void k_dispatch_tokens_blocked(const u32x4 *__restrict__ x,
+template <bool NT, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_dispatch_tokens_blocked(const u32x4 *__restrict__ x,
                                                                  const int32_t *__restrict__ offsets,
                                                                  const int32_t *__restrict__ disp_token, int T, int E,
                                                                  int C, int vec_per_row, int tb, int n_tb,
@@ -80,8 +80,8 @@ __global__ __launch_bounds__(256) void k_dispatch_tokens_blocked(const u32x4 *__
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     if ((int)blockIdx.x >= n_tb) {
         const long long n_rows = (long long)E * C;
-        const long long step = (long long)(gridDim.x - n_tb) * 256;
-        for (long long r0 = (long long)(blockIdx.x - n_tb) * 256 + wv * 64; r0 < n_rows; r0 += step) {
+        const long long step = (long long)(gridDim.x - n_tb) * THREADS;
+        for (long long r0 = (long long)(blockIdx.x - n_tb) * THREADS + wv * 64; r0 < n_rows; r0 += step) {
             const long long r = r0 + lane;
             bool pad = false;
             if (r < n_rows) {
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(256) void k_dispatch_tokens_blocked(const u32x4 *__
     if (tid < kBlockTokens) s_cnt[tid] = 0;
     if (tid == 0) s_odd = 0;
     __syncthreads();
-    for (int j = tid; j < E; j += 256) {
+    for (int j = tid; j < E; j += THREADS) {
         const int o0 = offsets[j];
         int cnt = offsets[j + 1] - o0;
         cnt = cnt < 0 ? 0 : cnt < C ? cnt : C;
@@ -153,14 +153,14 @@ __global__ __launch_bounds__(256) void k_dispatch_tokens_blocked(const u32x4 *__
     }
     __syncthreads();
     if (s_odd) {
-        // the i-th rows of 64 stretches together, in turn to the four wavefronts
+        // the i-th rows of 64 stretches together, in turn to the wavefronts
         for (int j0 = 0, turn = wv; j0 < E; j0 += 64) {
             const int j = j0 + lane, n = j < E ? s_n[j] : 0, first = j < E ? s_first[j] : 0, at = j < E ? offsets[j] + first : 0;
             for (int i = 0; __any(i < n); ++i) {
                 int tok = i < n ? disp_token[at + i] : 0;
                 tok = tok >= 0 && tok < T ? tok : 0;
                 for (unsigned long long m = __ballot(i < n); m; m &= m - 1, ++turn) {
-                    if (turn & 3) continue;
+                    if (turn % (THREADS / 64)) continue;
                     const int l = __ffsll((long long)m) - 1;
                     const u32x4 *src = x + (size_t)__builtin_amdgcn_readlane(tok, l) * vec_per_row;
                     u32x4 *dst = out + ((size_t)(j0 + l) * C + __builtin_amdgcn_readlane(first, l) + i) * vec_per_row;
@@ -170,7 +170,7 @@ __global__ __launch_bounds__(256) void k_dispatch_tokens_blocked(const u32x4 *__
         }
         return;
     }
-    for (int t = wv; t < tb; t += 4) {
+    for (int t = wv; t < tb; t += THREADS / 64) {
         const int n = s_cnt[t];
         if (n == 0) continue;
         const unsigned mine = lane < n ? s_row[t * kTokenRows + lane] : 0u;
@@ -323,13 +323,20 @@ int32_t dispatch_tokens_run(const void *x, int dtype, const int32_t *offsets, co
     const bool vec = ((size_t)d * eb) % 16 == 0 && ((uintptr_t)x % 16) == 0 && ((uintptr_t)out % 16) == 0;
     // Blocks of tokens from 4096 tokens on (four blocks per compute unit; smaller batches are bound by latency, and their
     // rows of x stay in the caches), as long as the lists to search are not many more than the rows a block moves.
-    const int tb = T >= 32 * 1024 ? 32 : T >= 16 * 1024 ? 16 : T >= 8 * 1024 ? 8 : 4;
+    // Where neither x nor the buffers fit the last cache, sixteen wavefronts to a workgroup and half as many tokens: fewer rows of x and
+    // places of the lists are in use at a time (65536 tokens of 2048 to 8 of 128 experts, behind the projection 505 -> 474 us; 32768 to 64, where x
+    // does fit, 259 -> 268).
+    const bool nt = beyond_caches((size_t)n_rows * d * eb), wide = nt && T >= 16 * 1024 && E <= 128 * 16 && beyond_caches((size_t)T * d * eb);
+    const int tb = wide ? 16 : T >= 32 * 1024 ? 32 : T >= 16 * 1024 ? 16 : T >= 8 * 1024 ? 8 : 4;
     if (vec && T >= 4096 && E <= 128 * tb && E <= kListMaxE && n_rows < (1ll << 32)) {
         const int n_tb = (T + tb - 1) / tb, n_pad = (int)std::min<long long>((n_rows + 255) / 256, 1024);
-        const bool nt = beyond_caches((size_t)n_rows * d * eb);
-        hipLaunchKernelGGL(nt ? k_dispatch_tokens_blocked<true> : k_dispatch_tokens_blocked<false>, dim3(n_tb + n_pad),
-                           dim3(256), sizeof(int) * 2 * E, s, (const u32x4 *)x, offsets, disp_token, T, E, C,
-                           (int)((size_t)d * eb / 16), tb, n_tb, (u32x4 *)out);
+#define MS_BLOCKED(NN, TT)                                                                                                  \
+    hipLaunchKernelGGL((k_dispatch_tokens_blocked<NN, TT>), dim3(n_tb + n_pad), dim3(TT), sizeof(int) * 2 * E, s, (const u32x4 *)x, \
+                       offsets, disp_token, T, E, C, (int)((size_t)d * eb / 16), tb, n_tb, (u32x4 *)out)
+        if (wide) MS_BLOCKED(true, 1024);
+        else if (nt) MS_BLOCKED(true, 256);
+        else MS_BLOCKED(false, 256);
+#undef MS_BLOCKED
     } else if (vec) {
         hipLaunchKernelGGL(k_dispatch_tokens, dim3((unsigned)grid), dim3(256), 0, s, (const u32x4 *)x, offsets,
                            disp_token, T, E, C, (int)((size_t)d * eb / 16), (u32x4 *)out);

@@ -32,6 +32,23 @@ def lists(rng, T, E, k, C, order, some=1):
     return np.concatenate(segs).astype(np.int32), np.array(off, dtype=np.int32)
 
 
+@pytest.mark.parametrize("order", ["ascending", "random", "two runs", "one out of place"])
+def test_rows_beyond_the_caches(order):
+    """x and the buffers larger than the last cache: workgroups of sixteen wavefronts."""
+    import paper_2508_12801_amd as ms
+    T, E, k, d = 16391, 70, 2, 8200
+    print(f"dispatch orders beyond the caches {order}", flush=True)
+    rng = np.random.default_rng(T)
+    C = T * k // E + 60
+    tok, off = lists(rng, T, E, k, C, order, 3)
+    x = torch.randn(T, d, device="cuda").to(torch.bfloat16)
+    buf = ms.dispatch_tokens(x, torch.from_numpy(off).cuda(), torch.from_numpy(tok).cuda(), E, C)
+    at = torch.from_numpy(tok.astype(np.int64)).cuda()
+    for e in range(E):
+        n = int(off[e + 1] - off[e])
+        assert torch.equal(buf[e, :n], x[at[off[e]:off[e + 1]]]) and not buf[e, n:].any(), e
+
+
 ORDERS = ["random", "descending", "two runs", "shuffled by eight", "one out of place"]
 
 
