@@ -246,6 +246,11 @@ bool gemm_softtopk_supported(int dtype, int d, int E, const void *x, const void 
 int32_t gemm_softtopk_run(const void *x, const void *W, const float *bias, int dtype, int T, int d, int E, int k,
                           float t, int shift, float *logits, float *scores, int32_t *q, void *wt_scratch,
                           hipStream_t s);
+// The same for other expert counts up to 128 and for fp32, where the split projection runs; logits are written.  Bit for bit what
+// gemm_run and softtopk_run give.
+bool gemm_split_scores_supported(int dtype, int T, int d, int E, const void *x, const void *W);
+int32_t gemm_split_scores_run(const void *x, const void *W, const float *bias, int dtype, int T, int d, int E, int k, float t, int shift,
+                              float *logits, float *scores, int32_t *q, hipStream_t s);
 int32_t copy_run(const void *src, void *dst, size_t bytes, hipStream_t s);
 
 extern int g_kernel_timing;

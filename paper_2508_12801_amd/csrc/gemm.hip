@@ -440,7 +440,7 @@ __global__ __launch_bounds__(256) void k_gemm_bf16_wtc(const unsigned short *__r
 // rate.  With a load for every element of W and a wavefront to a column tile (so that x was read up to four times) bf16, scores
 // in the projection, took 40.5 us at 16384 x 2048 to 64 experts (now 25.5), 15.5 at 256 x 2048 to 64 (11.6), 35 at 8192 x 2048 to 128 (23);
 // fp32 47 us at 10007 x 1000 to 96 (34), 236 at 65536 x 1024 to 128 (171: 101 TFLOP/s).
-// FE > 0: the tile holds whole rows of FE experts, and the scores and rewards are computed from it (as in k_gemm_bf16_wtc).
+// EPLS > 0: the tile holds whole rows of up to 8 * EPLS experts, and the scores and rewards are computed from it (as in k_gemm_bf16_wtc).
 constexpr int kSplitPitch = 33;
 
 template <int N>
@@ -448,7 +448,7 @@ struct __attribute__((packed, aligned(4))) Words {
     unsigned v[N];
 };
 
-template <bool BF16, bool XV, int FE, int CT, int RT, int KS>
+template <bool BF16, bool XV, int EPLS, bool VL, int CT, int RT, int KS>
 __global__ __launch_bounds__(64 * KS) void k_gemm_split(const void *__restrict__ x_, const void *__restrict__ W_,
                                                         const float *__restrict__ bias, int T, int d, int E,
                                                         float *__restrict__ out, float *__restrict__ scores,
@@ -456,7 +456,7 @@ __global__ __launch_bounds__(64 * KS) void k_gemm_split(const void *__restrict__
 {
     using El = std::conditional_t<BF16, unsigned short, unsigned>;      // (fp32 as bits)
     constexpr int STEP = BF16 ? 16 : 8, LK = STEP / 2;       // reduction indices per step, per lane and step
-    constexpr int DEPTH = RT * CT > 4 || (KS > 8 && (RT > 1 || (CT > 1 && FE == 0))) ? 3 : 4;      // steps on their way (what the registers hold)
+    constexpr int DEPTH = RT * CT > 4 || (KS > 8 && (RT > 1 || (CT > 1 && EPLS == 0))) ? 3 : 4;      // steps on their way (what the registers hold)
     constexpr int NW = BF16 && CT > 1 ? CT / 2 : CT;         // words of a lane's columns
     constexpr int RS = KS * RT * CT * 32 * kSplitPitch * 4 <= 144 * 1024 ? RT : 1;       // row tiles added up at a time
     __shared__ __attribute__((aligned(16))) float s_part[KS * RS * CT * 32 * kSplitPitch];
@@ -588,31 +588,46 @@ __global__ __launch_bounds__(64 * KS) void k_gemm_split(const void *__restrict__
             return v;
         };
         const int row1 = row0 + 32 * r0;
-        if constexpr (FE == 0) {
+        if constexpr (EPLS == 0) {
             for (int o = tid; o < RS * 32 * 32 * CT; o += 64 * KS) {
                 const int r = o / (32 * CT), n = o - r * (32 * CT);
                 if (row1 + r < T && col0 + n < E) out[(size_t)(row1 + r) * E + col0 + n] = total(r, n) + (bias ? bias[col0 + n] : 0.f);
             }
         } else {
-            constexpr int EPLS = FE / 8;                // values per lane with 8 lanes per row
+            // eight lanes per row, in the layout of the score kernel for as many experts (its sums have to be the same)
             static_assert(RS * 256 <= 64 * KS, "a group of lanes per row");
+            auto col_of = [](int m, int lg) { return VL ? (m >> 2) * 32 + lg * 4 + (m & 3) : lg * EPLS + m; };
+            const bool quads = EPLS >= 4 && E % 4 == 0 && ((((uintptr_t)out) | ((uintptr_t)scores) | ((uintptr_t)q)) % 16) == 0;
             const int r = tid >> 3, lg = tid & 7;
             if (r < RS * 32 && row1 + r < T) {
                 float xv[EPLS];
 #pragma unroll
                 for (int m = 0; m < EPLS; ++m) {
-                    const int n = (m >> 2) * 32 + lg * 4 + (m & 3);
-                    xv[m] = total(r, n) + (bias ? bias[n] : 0.f);
+                    const int n = col_of(m, lg);
+                    xv[m] = VL || n < E ? total(r, n) + (bias ? bias[n] : 0.f) : -3.4e38f;
                 }
                 float sc[EPLS];
                 int qq[EPLS];
-                softtopk_row<8, EPLS, true>(xv, lg, E, k, t, qscale, MAXSCORE_SOFTTOPK_A, sc, qq);
+                softtopk_row<8, EPLS, VL>(xv, lg, E, k, t, qscale, MAXSCORE_SOFTTOPK_A, sc, qq);
+                const size_t o0 = (size_t)(row1 + r) * E;
+                if (VL || quads) {
 #pragma unroll
-                for (int m = 0; m < EPLS; m += 4) {
-                    const size_t o = (size_t)(row1 + r) * E + (m >> 2) * 32 + lg * 4;
-                    if (out) *(float4 *)(out + o) = make_float4(xv[m], xv[m + 1], xv[m + 2], xv[m + 3]);
-                    if (scores) *(float4 *)(scores + o) = make_float4(sc[m], sc[m + 1], sc[m + 2], sc[m + 3]);
-                    if (q) *(int4 *)(q + o) = make_int4(qq[m], qq[m + 1], qq[m + 2], qq[m + 3]);
+                    for (int m = 0; m + 3 < EPLS; m += 4) {
+                        const size_t o = o0 + col_of(m, lg);
+                        if (!VL && col_of(m, lg) >= E) continue;
+                        if (out) *(float4 *)(out + o) = make_float4(xv[m], xv[m + 1], xv[m + 2], xv[m + 3]);
+                        if (scores) *(float4 *)(scores + o) = make_float4(sc[m], sc[m + 1], sc[m + 2], sc[m + 3]);
+                        if (q) *(int4 *)(q + o) = make_int4(qq[m], qq[m + 1], qq[m + 2], qq[m + 3]);
+                    }
+                } else {
+#pragma unroll
+                    for (int m = 0; m < EPLS; ++m)
+                        if (col_of(m, lg) < E) {
+                            const size_t o = o0 + col_of(m, lg);
+                            if (out) out[o] = xv[m];
+                            if (scores) scores[o] = sc[m];
+                            if (q) q[o] = qq[m];
+                        }
                 }
             }
         }
@@ -650,7 +665,7 @@ static int split_tiles(const void *W, bool bf16, int E)
 // Whether a lane can read 16 bytes of its row of x at once (four bytes' alignment will do).
 static bool split_xvec(const void *x, bool bf16, int d) { return !bf16 || (d % 2 == 0 && (uintptr_t)x % 4 == 0); }
 
-template <bool BF16, int FE, int CT>
+template <bool BF16, int EPLS, bool VL, int CT>
 static void split_launch(const void *x, const void *W, const float *bias, int T, int d, int E, float *logits, float *scores, int32_t *q, int k,
                          float t, float qscale, hipStream_t s)
 {
@@ -660,11 +675,11 @@ static void split_launch(const void *x, const void *W, const float *bias, int T,
     const int rows = xv && wide ? split_rows(T, E) : 32;
     const dim3 g((T + rows - 1) / rows, (E + 32 * CT - 1) / (32 * CT));
 #define MS_SPLIT(VV, RR, KK)                                                                                                       \
-    hipLaunchKernelGGL((k_gemm_split<BF16, VV, FE, CT, RR, KK>), g, dim3(64 * KK), 0, s, x, W, bias, T, d, E, logits, scores, q, k, t, qscale)
+    hipLaunchKernelGGL((k_gemm_split<BF16, VV, EPLS, VL, CT, RR, KK>), g, dim3(64 * KK), 0, s, x, W, bias, T, d, E, logits, scores, q, k, t, qscale)
     if (rows == 64) {
         if constexpr (wide) MS_SPLIT(true, 2, KS2);
     } else if (xv) MS_SPLIT(true, 1, KS1);
-    else if constexpr (BF16 && FE == 0) MS_SPLIT(false, 1, KS1);
+    else if constexpr (BF16 && EPLS == 0) MS_SPLIT(false, 1, KS1);
 #undef MS_SPLIT
 }
 
@@ -682,7 +697,7 @@ int32_t gemm_run(const void *x, const void *W, const float *bias, int dtype, int
     const bool as_scores = gemm_softtopk_supported(dtype, d, E, x, wt_scratch);
     if (f32 || (as_scores ? split_scores(x, W, T, d, E) : split_is_better(T, E))) {
         const int ct = split_tiles(W, !f32, E);
-#define MS_L(BB, CC) split_launch<BB, 0, CC>(x, W, bias, T, d, E, logits, nullptr, nullptr, 0, 0.f, 0.f, s)
+#define MS_L(BB, CC) split_launch<BB, 0, false, CC>(x, W, bias, T, d, E, logits, nullptr, nullptr, 0, 0.f, 0.f, s)
         if (f32) {
             if (ct == 1) MS_L(false, 1);
             else if (ct == 2) MS_L(false, 2);
@@ -758,7 +773,7 @@ int32_t gemm_softtopk_run(const void *x, const void *W, const float *bias, int d
     unsigned short *wt = (unsigned short *)wt_scratch;
     const float qscale = (float)(1 << shift);
     if (split_scores(x, W, T, d, E)) {
-#define MS_LF(FF) split_launch<true, FF, FF / 32>(x, W, bias, T, d, E, logits, scores, q, k, t, qscale, s)
+#define MS_LF(FF) split_launch<true, FF / 8, true, FF / 32>(x, W, bias, T, d, E, logits, scores, q, k, t, qscale, s)
         if (E == 32) MS_LF(32);
         else if (E == 64) MS_LF(64);
         else MS_LF(128);
@@ -775,6 +790,48 @@ int32_t gemm_softtopk_run(const void *x, const void *W, const float *bias, int d
     else if (E == 64) MS_GEMMF(2);
     else MS_GEMMF(4);
 #undef MS_GEMMF
+    MS_HIP(hipGetLastError());
+    return MAXSCORE_OK;
+}
+
+// Whole rows of up to 128 experts in a workgroup of the split kernel: the scores of other expert counts, and in fp32, from its sums.
+// With the score kernel behind the projection 4096 x 1024 to 16 took 14.2 us (now 11.5), 64 x 64 to 8 in fp32 14.0 (11.2), 20000 x 512 to 20
+// 24.7 (20.7), 10007 x 1000 to 96 43.9 (43.1).  Beyond 64 experts and 16384 tokens the score kernel's wavefronts are the better ones
+// (fp32, 65536 x 1024 to 128: 191, in the projection 195).
+bool gemm_split_scores_supported(int dtype, int T, int d, int E, const void *x, const void *W)
+{
+    const bool bf16 = dtype == MAXSCORE_DTYPE_BF16;
+    return E <= 128 && (E <= 64 || T <= 16384) && 32 * split_tiles(W, bf16, E) >= E && split_xvec(x, bf16, d) && (!bf16 || (split_is_better(T, E) && E != 32 && E != 64 && E != 128));
+}
+
+int32_t gemm_split_scores_run(const void *x, const void *W, const float *bias, int dtype, int T, int d, int E, int k, float t, int shift,
+                              float *logits, float *scores, int32_t *q, hipStream_t s)
+{
+    if (!gemm_split_scores_supported(dtype, T, d, E, x, W)) return MAXSCORE_ERR_SHAPE;
+    const float qscale = (float)(1 << shift);
+    const bool bf16 = dtype == MAXSCORE_DTYPE_BF16;
+    // (the score kernel reads whole rows in pieces of four columns where it can: the layouts have to agree)
+    const bool vl = (E == 32 || E == 64 || E == 128) && ((((uintptr_t)logits) | ((uintptr_t)scores) | ((uintptr_t)q)) % 16) == 0;
+    const int ct = split_tiles(W, bf16, E);
+#define MS_LS(BB, PP, VV, CC) split_launch<BB, PP, VV, CC>(x, W, bias, T, d, E, logits, scores, q, k, t, qscale, s)
+    if (bf16) {
+        if (E <= 8) MS_LS(true, 1, false, 1);
+        else if (E <= 16) MS_LS(true, 2, false, 1);
+        else if (E < 32) MS_LS(true, 4, false, 1);
+        else if (ct == 2) MS_LS(true, 8, false, 2);
+        else MS_LS(true, 16, false, 4);
+    } else if (ct == 1) {
+        if (E <= 8) MS_LS(false, 1, false, 1);
+        else if (E <= 16) MS_LS(false, 2, false, 1);
+        else if (vl) MS_LS(false, 4, true, 1);
+        else MS_LS(false, 4, false, 1);
+    } else if (ct == 2) {
+        if (vl) MS_LS(false, 8, true, 2);
+        else MS_LS(false, 8, false, 2);
+    } else if (ct == 3) MS_LS(false, 16, false, 3);
+    else if (vl) MS_LS(false, 16, true, 4);
+    else MS_LS(false, 16, false, 4);
+#undef MS_LS
     MS_HIP(hipGetLastError());
     return MAXSCORE_OK;
 }

@@ -23,7 +23,7 @@ def ms():
     (1, 1, 1), (31, 7, 33), (32, 8, 32), (33, 15, 31), (64, 16, 64), (65, 17, 65), (40, 64, 96), (95, 40, 97), (70, 1000, 127),
     (129, 136, 128), (33, 2056, 129), (50, 72, 300), (8192, 64, 128), (8193, 64, 128), (16384, 64, 64), (16385, 64, 32), (16385, 40, 96),
     (8193, 33, 128), (8200, 50, 70), (8250, 34, 90), (8193, 100, 80), (4097, 48, 160), (16384, 64, 128), (16385, 64, 128), (8255, 37, 48),
-    (8195, 20, 20), (8193, 31, 97),
+    (8195, 20, 20), (8193, 31, 97), (77, 24, 8), (300, 34, 16), (16384, 16, 80), (16385, 16, 100), (16385, 16, 64), (100, 18, 66), (90, 20, 100),
 ])
 def test_projection_edges(ms, T, d, E, dtype):
     print(f"projection edges T={T} d={d} E={E} {dtype}", flush=True)
