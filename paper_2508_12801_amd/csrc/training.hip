@@ -52,35 +52,33 @@ __global__ __launch_bounds__(256) void k_colsum(const float *__restrict__ scores
 }
 
 // One workgroup: column means, the loss and its derivative with respect to the scores of a column.  Thread
-// (j, g) adds the partial sums g, g+groups, ... of column j (of VEC columns: all on their way at once up to 128 experts; beyond, where
-// each thread has more of them, one column a thread is as fast); the groups are then added in order.
-template <int VEC>
+// (j, g) adds the partial sums g, g+groups, ... of column j; the groups that have any are then added in order.  Bound by latency: a
+// load, a barrier and that serial sum: 65536 tokens of 128 experts 4.6 us, of 8 4.1, 256 tokens of 8 2.4 (3.7 over all groups).
+// With four columns a thread the serial sum is four times as long: 5.4, 8.0 and 7.8 us (5.3, 5.3 and 2.4 over the groups that have any).
 __global__ __launch_bounds__(1024) void k_aux_final(const float *__restrict__ part, int n_blocks,
                                                     const int32_t *__restrict__ offsets, int T, int E, int epad,
                                                     float lam, float *__restrict__ loss,
                                                     float *__restrict__ mean_scores, float *__restrict__ dscores_col)
 {
-    typedef float vec_t __attribute__((ext_vector_type(VEC)));
-    typedef double wide_t __attribute__((ext_vector_type(VEC)));
-    __shared__ __attribute__((aligned(32))) double s_red[1024 * VEC];
+    __shared__ double s_red[1024];
     __shared__ double s_w[16];
-    const int tid = threadIdx.x, groups = 1024 * VEC / epad;
+    const int tid = threadIdx.x, groups = 1024 / epad;
     {
-        const int j = tid % (epad / VEC) * VEC, g = tid / (epad / VEC);
-        wide_t sum = 0.0;
+        const int j = tid % epad, g = tid / epad;
+        double sum = 0.0;
         if (j < E) {
 #pragma unroll 16
-            for (int b = g; b < n_blocks; b += groups) sum += __builtin_convertvector(*(const vec_t *)(part + (size_t)b * E + j), wide_t);
+            for (int b = g; b < n_blocks; b += groups) sum += (double)part[(size_t)b * E + j];
         }
-        *(wide_t *)&s_red[g * epad + j] = sum;
+        s_red[g * epad + j] = sum;
     }
     __syncthreads();
-    const int j = tid;
+    const int j = tid, filled = groups < n_blocks ? groups : n_blocks;
     double term = 0.0;
     if (j < E) {
         double sum = 0.0;
 #pragma unroll 8
-        for (int g = 0; g < groups; ++g) sum += s_red[g * epad + j];
+        for (int g = 0; g < filled; ++g) sum += s_red[g * epad + j];
         const double mean_a = sum / T;
         const double mean_p = (double)(offsets[j + 1] - offsets[j]) / T;
         term = mean_a * mean_p;
@@ -215,8 +213,7 @@ int32_t aux_loss_run(const float *scores, const int32_t *offsets, int T, int E, 
         hipLaunchKernelGGL(k_colsum<1>, dim3(n_blocks), dim3(256), shm, s, scores, T, E, cols, rows_per_block, part);
     int epad = 1;
     while (epad < E) epad <<= 1;
-    if (E % 4 == 0 && E <= 128) hipLaunchKernelGGL(k_aux_final<4>, dim3(1), dim3(1024), 0, s, part, n_blocks, offsets, T, E, epad, lam, loss, mean_scores, dscores_col);
-    else hipLaunchKernelGGL(k_aux_final<1>, dim3(1), dim3(1024), 0, s, part, n_blocks, offsets, T, E, epad, lam, loss, mean_scores, dscores_col);
+    hipLaunchKernelGGL(k_aux_final, dim3(1), dim3(1024), 0, s, part, n_blocks, offsets, T, E, epad, lam, loss, mean_scores, dscores_col);
     MS_HIP(hipGetLastError());
     return MAXSCORE_OK;
 }
