@@ -456,7 +456,9 @@ __global__ __launch_bounds__(64 * KS) void k_gemm_split(const void *__restrict__
 {
     using El = std::conditional_t<BF16, unsigned short, unsigned>;      // (fp32 as bits)
     constexpr int STEP = BF16 ? 16 : 8, LK = STEP / 2;       // reduction indices per step, per lane and step
-    constexpr int DEPTH = RT * CT > 4 || (KS > 8 && (RT > 1 || (CT > 1 && EPLS == 0))) ? 3 : 4;      // steps on their way (what the registers hold)
+    // Steps on their way: what the registers hold, of which a lane of sixteen wavefronts has 128.  Two row tiles there hold two steps, with
+    // 17 to 32 experts' scores behind them three: logits of 16384 x 2048 to 16 22 us (30 with three, 19 registers spilled), scores 23 (29).
+    constexpr int DEPTH = KS > 8 && RT > 1 ? (EPLS < 4 ? 2 : 3) : RT * CT > 4 || (KS > 8 && CT > 1 && EPLS == 0) ? 3 : 4;
     constexpr int NW = BF16 && CT > 1 ? CT / 2 : CT;         // words of a lane's columns
     constexpr int RS = KS * RT * CT * 32 * kSplitPitch * 4 <= 144 * 1024 ? RT : 1;       // row tiles added up at a time
     __shared__ __attribute__((aligned(16))) float s_part[KS * RS * CT * 32 * kSplitPitch];
