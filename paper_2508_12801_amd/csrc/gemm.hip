@@ -645,8 +645,17 @@ __global__ __launch_bounds__(256) void k_copy16(const u32x4 *__restrict__ src, u
 }  // namespace
 
 // The split kernel takes 32 rows to a workgroup while these fill the chip no more than once, and 64, which share the operands of W,
-// beyond: 16384 tokens of 2048 to 64 experts 25.5 us, with scores; with 32 rows (one column tile to a wavefront) it was 40.5.
-static int split_rows(int T, int E) { return (long long)((T + 31) / 32) * ((E + 127) / 128) <= 256 ? 32 : 64; }
+// beyond (up to 16384 tokens; 32 rows against 64, of 256, 1024 and 2048 in bf16, with scores): 64 experts, 8192 tokens 11.7 12.2 17.3
+// against 11.5 12.5 20.8 us, 10007 tokens 14.3 19.8 31.4 against 11.6 13.0 22.6; 128 experts, 8192 tokens 11.9 15.6 23.3 against
+// 16.0 22.6 33.7, 16384 tokens 19.0 29.8 45.4 against 18.1 26.7 39.2.
+// fp32 has no such end.  From three column tiles on a workgroup has its compute unit to itself and one of 64 rows takes 1.6 to 1.8 times
+// one of 32, so that 32 rows are the better ones wherever the fullest unit gets fewer than 1.7 times as many of them: 10007 tokens of
+// 256, 1000 and 2048 to 256 experts 38 78 133 against 45 90 154 us, 20000 to 128 experts 37 83 139 against 45 92 156.
+static int split_rows(int T, int E, bool own_unit)
+{
+    const long long cols = (E + 127) / 128, in32 = ((T + 31) / 32 * cols + 255) / 256, in64 = ((T + 63) / 64 * cols + 255) / 256;
+    return in32 <= 1 || (own_unit && in32 * 10 < in64 * 17) ? 32 : 64;
+}
 
 // bf16: the split kernel as long as its workgroups of 64 rows fill the chip no more than once.  Tokens of 2048, split against
 // whole (with the transposition of W), scores in the projection: 64 experts, 16384 tokens 25.5 us against 39, 20000 43.7 against 38;
@@ -674,7 +683,7 @@ static void split_launch(const void *x, const void *W, const float *bias, int T,
     constexpr int KS1 = CT <= 2 ? 16 : 8, KS2 = CT == 1 ? 16 : 8;
     const bool xv = split_xvec(x, BF16, d);
     constexpr bool wide = BF16 || CT > 1;       // (fp32 up to 32 experts: 28 us with 32 rows, 30 with 64 at 16384 x 1024 to 16)
-    const int rows = xv && wide ? split_rows(T, E) : 32;
+    const int rows = xv && wide ? split_rows(T, E, !BF16 && CT > 2) : 32;
     const dim3 g((T + rows - 1) / rows, (E + 32 * CT - 1) / (32 * CT));
 #define MS_SPLIT(VV, RR, KK)                                                                                                       \
     hipLaunchKernelGGL((k_gemm_split<BF16, VV, EPLS, VL, CT, RR, KK>), g, dim3(64 * KK), 0, s, x, W, bias, T, d, E, logits, scores, q, k, t, qscale)

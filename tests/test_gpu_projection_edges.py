@@ -55,3 +55,18 @@ def test_operands_off_their_alignment(ms, T, d, E, dtype, xo, wo):
     both = ms.router_softtopk(x, W, None, 3, t=1.0)
     scores, q = ms.softtopk(L, 3, 1.0)
     assert torch.equal(both["logits"], L) and torch.equal(both["scores"], scores) and torch.equal(both["q"], q)
+
+
+@pytest.mark.parametrize("T,d,E", [(8192, 24, 256), (8193, 24, 256), (12288, 20, 160), (12289, 24, 132), (16384, 24, 100), (16385, 24, 128),
+                                   (24576, 16, 96), (24577, 20, 66), (20011, 24, 78), (40000, 8, 128)])
+def test_fp32_rows_do_not_depend_on_their_number(ms, T, d, E):
+    """Workgroups of 32 and of 64 rows add up the same parts in the same order: the ends of a batch and what is beyond a workgroup's
+    rows have to agree with the same rows in batches of one workgroup each."""
+    print(f"projection rows T={T} d={d} E={E}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(T + d + E)
+    x = torch.randn(T, d, generator=gen, device="cuda")
+    W = torch.randn(d, E, generator=gen, device="cuda")
+    out = ms.router_softtopk(x, W, None, 3, t=1.0)
+    assert torch.equal(out["logits"], ms.router_logits(x, W, None))
+    for a in (0, 32, 8160, T // 64 * 32, (T - 1) // 64 * 64, (T - 1) // 32 * 32, T - 32):
+        assert torch.equal(out["logits"][a:a + 32], ms.router_logits(x[a:a + 32].contiguous(), W, None)), a
