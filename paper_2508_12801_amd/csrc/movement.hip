@@ -58,9 +58,12 @@ __global__ __launch_bounds__(256) void k_dispatch_tokens(const u32x4 *__restrict
 // end far apart: of a descending list one workgroup gets everything.  So every workgroup looks at the same kListSamples entries
 // first.  If these do not ascend, the stretches are equal shares of the list; if they do, they are the bisection's first steps.
 // Either way the stretches cover every list exactly once, whatever its order: the samples and the same bisection with a
-// larger key never end further left.  Workgroups from n_tb on zero the rows no token has.
+// larger key never end further left.  Workgroups from n_tb on zero the rows no token has.  These are neighbours, at the end of every
+// list: a wavefront looks at rows that are as far apart as there are wavefronts, so that all of them get a share (a workgroup that took
+// neighbouring rows could have nothing else: 7573 tokens of 1600 to 6 of 16 experts with room to spare 34 us, not 38; 65536 of 2048 to 6 of 8
+// 400, not 436).
 // Bound by HBM: row by row in list order every row of x comes from memory k times once x is larger than the caches.
-// 65536 tokens of 2048 to 8 of 128 experts: 683 to 441 us, 5.5 TB/s with x counted once (474 behind a projection of so many tokens); 16384 to 8 of 64: 163 to 110 us.  The
+// 65536 tokens of 2048 to 8 of 128 experts: 683 to 441 us, 5.5 TB/s with x counted once (492 in a layer, behind the projection); 16384 to 8 of 64: 163 to 110 us.  The
 // same in other orders: shuffled 632 us (2.8 ms without the samples), descending 640 (13.9), shuffled by eight 680 (785 with a
 // list after the other instead of 64 together).
 constexpr int kBlockTokens = 32, kTokenRows = 16, kListMaxE = 2048, kListSamples = 8;
@@ -79,17 +82,16 @@ __global__ __launch_bounds__(THREADS) void k_dispatch_tokens_blocked(const u32x4
     __shared__ int s_odd;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     if ((int)blockIdx.x >= n_tb) {
-        const long long n_rows = (long long)E * C;
-        const long long step = (long long)(gridDim.x - n_tb) * THREADS;
-        for (long long r0 = (long long)(blockIdx.x - n_tb) * THREADS + wv * 64; r0 < n_rows; r0 += step) {
-            const long long r = r0 + lane;
+        const long long n_rows = (long long)E * C, n_waves = (long long)(gridDim.x - n_tb) * (THREADS / 64);
+        for (long long r0 = (long long)(blockIdx.x - n_tb) * (THREADS / 64) + wv; r0 < n_rows; r0 += 64 * n_waves) {
+            const long long r = r0 + lane * n_waves;
             bool pad = false;
             if (r < n_rows) {
                 const int j = (int)(r / C), s = (int)(r - (long long)j * C);
                 pad = s >= offsets[j + 1] - offsets[j];
             }
             for (unsigned long long m = __ballot(pad); m; m &= m - 1) {
-                u32x4 *dst = out + (r0 + __ffsll((long long)m) - 1) * vec_per_row;
+                u32x4 *dst = out + (r0 + (__ffsll((long long)m) - 1) * n_waves) * vec_per_row;
                 for (int c = lane; c < vec_per_row; c += 64) put<NT>(u32x4{0u, 0u, 0u, 0u}, dst + c);
             }
         }
@@ -324,8 +326,9 @@ int32_t dispatch_tokens_run(const void *x, int dtype, const int32_t *offsets, co
     // Blocks of tokens from 4096 tokens on (four blocks per compute unit; smaller batches are bound by latency, and their
     // rows of x stay in the caches), as long as the lists to search are not many more than the rows a block moves.
     // Where neither x nor the buffers fit the last cache, sixteen wavefronts to a workgroup and half as many tokens: fewer rows of x and
-    // places of the lists are in use at a time (65536 tokens of 2048 to 8 of 128 experts, behind the projection 505 -> 474 us; 32768 to 64, where x
-    // does fit, 259 -> 268).
+    // places of the lists are in use at a time.  In a layer, tight and with a quarter more room: 65536 tokens of 2048 to 8 of 128 experts
+    // 512 -> 492 us, to 2 of 32 157 -> 138 and 187 -> 169, 33000 of 4096 to 4 of 32 262 -> 241 and 304 -> 285.  Of 128 to 192 MiB of x it
+    // depends: 65536 of 1536 to 8 of 128 370 -> 340, to 4 of 64 167 -> 171.  A single expert a token: 117 -> 106 to 128, 92 -> 92 to 8.
     const bool nt = beyond_caches((size_t)n_rows * d * eb), wide = nt && T >= 16 * 1024 && E <= 128 * 16 && beyond_caches((size_t)T * d * eb);
     const int tb = wide ? 16 : T >= 32 * 1024 ? 32 : T >= 16 * 1024 ? 16 : T >= 8 * 1024 ? 8 : 4;
     if (vec && T >= 4096 && E <= 128 * tb && E <= kListMaxE && n_rows < (1ll << 32)) {

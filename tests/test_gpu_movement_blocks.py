@@ -66,3 +66,22 @@ def test_combine_chunks(ms, d, k, dtype):
     rows = buf.float().cpu().numpy().astype(np.float64)[np.where(ok, a, 0), np.where(ok, pos, 0)]
     terms = rows * (g.astype(np.float64) * ok)[:, :, None]
     assert (np.abs(y - terms.sum(axis=1)) <= 1e-6 * np.abs(terms).sum(axis=1) + 1e-30).all()
+
+
+@pytest.mark.parametrize("T,d,E,C", [(4096, 8, 1, 7), (4096, 8, 3, 21), (5000, 8, 7, 1031), (4099, 8, 5, 70001), (16384, 8192, 3, 9001)])
+def test_rows_without_a_token(ms, T, d, E, C):
+    """The rows behind every list's end are zeros: fewer rows than a workgroup looks at, more than all of them look at in one turn, and
+    buffers and tokens beyond the last cache (workgroups of sixteen wavefronts)."""
+    print(f"rows without a token T={T} d={d} E={E} C={C}", flush=True)
+    rng = np.random.default_rng(T + C)
+    x = torch.randint(1, 1 << 15, (T, d), dtype=torch.int16, device="cuda").view(torch.bfloat16)
+    n = np.minimum(rng.integers(0, C + 1, E), T)
+    n[0] = min(C, T)
+    tok = np.concatenate([np.sort(rng.choice(T, c, replace=False)) for c in n]).astype(np.int32)
+    off = np.concatenate([[0], np.cumsum(n)]).astype(np.int32)
+    buf = torch.full((E, C, d), -1, dtype=torch.int16, device="cuda").view(torch.bfloat16)
+    ms.dispatch_tokens(x, torch.from_numpy(off).cuda(), torch.from_numpy(tok).cuda(), E, C, out=buf)
+    rows = torch.from_numpy(tok.astype(np.int64)).cuda()
+    for e in range(E):
+        assert torch.equal(buf.view(torch.int16)[e, :n[e]], x.view(torch.int16)[rows[off[e]:off[e + 1]]]), e
+        assert not buf.view(torch.int16)[e, n[e]:].any(), e
