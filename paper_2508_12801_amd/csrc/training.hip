@@ -53,8 +53,9 @@ __global__ __launch_bounds__(256) void k_colsum(const float *__restrict__ scores
 
 // One workgroup: column means, the loss and its derivative with respect to the scores of a column.  Thread
 // (j, g) adds the partial sums g, g+groups, ... of column j; the groups that have any are then added in order.  Bound by latency: a
-// load, a barrier and that serial sum: 65536 tokens of 128 experts 4.6 us, of 8 4.1, 256 tokens of 8 2.4 (3.7 over all groups).
-// With four columns a thread the serial sum is four times as long: 5.4, 8.0 and 7.8 us (5.3, 5.3 and 2.4 over the groups that have any).
+// load, a barrier and that serial sum: 65536 tokens of 128 experts 4.8 us, of 8 4.3, 4096 of 128 3.1 (4.4 with sixteen loads a turn, of
+// which there are eight), 256 of 8 2.5 (3.7 over all groups).  With four columns a thread the serial sum is four times as long: 5.4,
+// 8.0, 3.6 and 7.9 us (5.3, 5.3, 3.5 and 2.4 over the groups that have any).
 __global__ __launch_bounds__(1024) void k_aux_final(const float *__restrict__ part, int n_blocks,
                                                     const int32_t *__restrict__ offsets, int T, int E, int epad,
                                                     float lam, float *__restrict__ loss,
@@ -67,7 +68,7 @@ __global__ __launch_bounds__(1024) void k_aux_final(const float *__restrict__ pa
         const int j = tid % epad, g = tid / epad;
         double sum = 0.0;
         if (j < E) {
-#pragma unroll 16
+#pragma unroll 8
             for (int b = g; b < n_blocks; b += groups) sum += (double)part[(size_t)b * E + j];
         }
         s_red[g * epad + j] = sum;
