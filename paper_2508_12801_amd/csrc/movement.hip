@@ -218,26 +218,25 @@ __global__ __launch_bounds__(256) void k_dispatch_tokens_elem(const TElem *__res
 
 __device__ __forceinline__ float bf16_to_f32(unsigned short b) { return __uint_as_float((unsigned)b << 16); }
 
-// A wavefront takes a kilobyte of a token's row, its neighbours the next ones, and ends: the k gate-weighted pieces are accumulated in
-// fp32, slot by slot, and written as fp32.  The indices of the slots (64 at most) are read by one lane each, and the pieces of
-// kCombineSlots slots are on their way together.  Bound by HBM, which takes short-lived wavefronts in the order of the addresses best
-// (a plain fill: 6.8 TB/s with 16 bytes a thread and no loop, 4.0 to 5.6 with loops over a fixed grid): 65536 tokens of 2048 from 8 of 128
-// experts 472 us (5.7 TB/s), 505 with whole rows and a loop over the tokens in every wavefront; 44032 of 1024 from 2 of 64 79 to
-// 72, 32768 of 2048 from 8 of 64 246 to 234, up to 16384 the same.
-constexpr int kCombineSlots = 8;
+// A wavefront takes PIECES kilobytes of a token's row, its neighbours the next ones, and ends: the k gate-weighted pieces are accumulated
+// in fp32, slot by slot, and written as fp32.  The indices of the slots (64 at most) are read by one lane each, and kCombineLoads pieces
+// of them are on their way together.  Bound by HBM beyond the last cache, which takes short-lived wavefronts in the order of the addresses
+// best (a plain fill: 6.8 TB/s with 16 bytes a thread and no loop, 4.0 to 5.6 with loops over a fixed grid): 65536 tokens of 2048 from 8 of
+// 128 experts 460 us (5.8 TB/s), 496 with whole rows and a loop over the tokens in every wavefront; 44032 of 1024 from 2 of 64 75 to 69.
+constexpr int kCombineLoads = 4;
 
-template <bool BF16, bool NT>
+template <bool BF16, bool NT, int PIECES>
 __global__ __launch_bounds__(256) void k_combine(const u32x4 *__restrict__ buf, const int32_t *__restrict__ assign,
                                                  const int32_t *__restrict__ token_pos,
                                                  const float *__restrict__ gates, int T, int d, int E, int k, int C,
-                                                 int vec_per_row, int nch, float *__restrict__ y)
+                                                 int vec_per_row, int parts, float *__restrict__ y)
 {
     constexpr int EPV = BF16 ? 8 : 4;         // elements per 16-byte vector
+    constexpr int SLOTS = kCombineLoads / PIECES;
     const int lane = threadIdx.x & 63;
-    const unsigned item = blockIdx.x * 4u + (threadIdx.x >> 6), i = __builtin_amdgcn_readfirstlane(item / (unsigned)nch);
+    const unsigned item = blockIdx.x * 4u + (threadIdx.x >> 6), i = __builtin_amdgcn_readfirstlane(item / (unsigned)parts);
     if (i >= (unsigned)T) return;
-    const int c = (int)(item - i * (unsigned)nch) * 64 + lane;
-    const bool in = c < vec_per_row;
+    const int c = (int)(item - i * (unsigned)parts) * (64 * PIECES) + lane;
     int e = -1, pos = 0;
     float g = 0.f;
     if (lane < k) {
@@ -248,41 +247,50 @@ __global__ __launch_bounds__(256) void k_combine(const u32x4 *__restrict__ buf, 
         // an empty slot, or a place outside the expert's buffer (an assignment made with another capacity)
         if (e >= E || pos < 0 || pos >= C) e = -1;
     }
-    float acc[EPV];
+    float acc[PIECES][EPV];
 #pragma unroll
-    for (int v = 0; v < EPV; ++v) acc[v] = 0.f;
-    for (int s = 0; s < k; s += kCombineSlots) {
-        u32x4 vals[kCombineSlots];
-        bool have[kCombineSlots];
+    for (int u = 0; u < PIECES; ++u)
 #pragma unroll
-        for (int z = 0; z < kCombineSlots; ++z) {
+        for (int v = 0; v < EPV; ++v) acc[u][v] = 0.f;
+    for (int s = 0; s < k; s += SLOTS) {
+        u32x4 vals[SLOTS][PIECES];
+        bool have[SLOTS];
+#pragma unroll
+        for (int z = 0; z < SLOTS; ++z) {
             const int es = s + z < k ? __builtin_amdgcn_readlane(e, s + z) : -1;
             have[z] = es >= 0;
             if (!have[z]) continue;
             const u32x4 *src = buf + ((size_t)es * C + __builtin_amdgcn_readlane(pos, s + z)) * vec_per_row;
-            vals[z] = in ? get<NT>(src + c) : u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int u = 0; u < PIECES; ++u) vals[z][u] = c + 64 * u < vec_per_row ? get<NT>(src + c + 64 * u) : u32x4{0u, 0u, 0u, 0u};
         }
 #pragma unroll
-        for (int z = 0; z < kCombineSlots; ++z) {
+        for (int z = 0; z < SLOTS; ++z) {
             if (!have[z]) continue;
             const float gs = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g), s + z));
-            if (BF16) {
 #pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    const unsigned word = vals[z][w];
-                    acc[2 * w] = fmaf(gs, bf16_to_f32((unsigned short)(word & 0xffffu)), acc[2 * w]);
-                    acc[2 * w + 1] = fmaf(gs, bf16_to_f32((unsigned short)(word >> 16)), acc[2 * w + 1]);
+            for (int u = 0; u < PIECES; ++u) {
+                if (BF16) {
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        const unsigned word = vals[z][u][w];
+                        acc[u][2 * w] = fmaf(gs, bf16_to_f32((unsigned short)(word & 0xffffu)), acc[u][2 * w]);
+                        acc[u][2 * w + 1] = fmaf(gs, bf16_to_f32((unsigned short)(word >> 16)), acc[u][2 * w + 1]);
+                    }
+                } else {
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) acc[u][w] = fmaf(gs, __uint_as_float(vals[z][u][w]), acc[u][w]);
                 }
-            } else {
-#pragma unroll
-                for (int w = 0; w < 4; ++w) acc[w] = fmaf(gs, __uint_as_float(vals[z][w]), acc[w]);
             }
         }
     }
-    if (!in) return;
-    f32x4 *dst = (f32x4 *)(y + (size_t)i * d + (size_t)c * EPV);
-    put<NT>(f32x4{acc[0], acc[1], acc[2], acc[3]}, dst);
-    if (BF16) put<NT>(f32x4{acc[4], acc[5], acc[6], acc[7]}, dst + 1);
+#pragma unroll
+    for (int u = 0; u < PIECES; ++u) {
+        if (c + 64 * u >= vec_per_row) continue;
+        f32x4 *dst = (f32x4 *)(y + (size_t)i * d + (size_t)(c + 64 * u) * EPV);
+        put<NT>(f32x4{acc[u][0], acc[u][1], acc[u][2], acc[u][3]}, dst);
+        if (BF16) put<NT>(f32x4{acc[u][4], acc[u][5], acc[u][6], acc[u][7]}, dst + 1);
+    }
 }
 
 template <bool BF16>
@@ -360,20 +368,34 @@ int32_t combine_run(const void *buf, int dtype, const int32_t *assign, const int
     const int eb = dtype == MAXSCORE_DTYPE_BF16 ? 2 : 4;
     const bool vec = ((size_t)d * eb) % 16 == 0 && ((uintptr_t)buf % 16) == 0 && ((uintptr_t)y % 16) == 0;
     if (vec) {
-        const int vpr = (int)((size_t)d * eb / 16), nch = (vpr + 63) / 64;
-        const int most = std::max(1, (1 << 24) / nch);              // tokens a launch (its threads are counted in 32 bits)
-        const bool nt = beyond_caches((size_t)E * C * d * eb + (size_t)T * d * 4);
+        const int vpr = (int)((size_t)d * eb / 16);
+        const size_t traffic = (size_t)E * C * d * eb + (size_t)T * d * 4;
+        const bool nt = beyond_caches(traffic);
+        // Two kilobytes of a row to a wavefront where the rows come from the last cache: there a second wavefront on the same row costs more
+        // than it brings (4361 tokens of 552 from 4 of 64 experts 7.2 us, 9.1 with one; 10007 of 1000 in fp32 from 6 of 96 56 and 59; 7988 of
+        // 832 from 6 of 32 15.8 and 17.4).  Below some 24 MiB in all the chip is not full with half as many wavefronts (1003 of 1664 from 4
+        // of 16 5.8 and 6.6), beyond some 448 memory decides as above, and with one or two slots the result does, which is written either
+        // way.  With three or four an odd number of pieces leaves too many lanes idle (21892 of 1536 from 4 of 32 75 and 70).
+        const bool two = vpr > 64 && (k > 4 || (k > 2 && (vpr + 63) / 64 % 2 == 0)) && traffic >= (size_t)24 << 20 && traffic < (size_t)448 << 20;
+        const int piece = two ? 128 : 64, parts = (vpr + piece - 1) / piece;
+        const int most = std::max(1, (1 << 24) / parts);            // tokens a launch (its threads are counted in 32 bits)
         for (int i0 = 0; i0 < T; i0 += most) {
             const int n = std::min(most, T - i0);
             const size_t at = (size_t)i0 * k;
-#define MS_COMBINE(BB, NN)                                                                                                      \
-    hipLaunchKernelGGL((k_combine<BB, NN>), dim3((unsigned)(((size_t)n * nch + 3) / 4)), dim3(256), 0, s, (const u32x4 *)buf, assign + at, \
-                       token_pos + at, gates + at, n, d, E, k, C, vpr, nch, y + (size_t)i0 * d)
+#define MS_COMBINE(BB, NN, PP)                                                                                                      \
+    hipLaunchKernelGGL((k_combine<BB, NN, PP>), dim3((unsigned)(((size_t)n * parts + 3) / 4)), dim3(256), 0, s, (const u32x4 *)buf, assign + at, \
+                       token_pos + at, gates + at, n, d, E, k, C, vpr, parts, y + (size_t)i0 * d)
+#define MS_COMBINE_P(BB, NN)            \
+    do {                                \
+        if (two) MS_COMBINE(BB, NN, 2); \
+        else MS_COMBINE(BB, NN, 1);     \
+    } while (0)
             if (eb == 2) {
-                if (nt) MS_COMBINE(true, true);
-                else MS_COMBINE(true, false);
-            } else if (nt) MS_COMBINE(false, true);
-            else MS_COMBINE(false, false);
+                if (nt) MS_COMBINE_P(true, true);
+                else MS_COMBINE_P(true, false);
+            } else if (nt) MS_COMBINE_P(false, true);
+            else MS_COMBINE_P(false, false);
+#undef MS_COMBINE_P
 #undef MS_COMBINE
         }
     } else {

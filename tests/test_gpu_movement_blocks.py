@@ -85,3 +85,28 @@ def test_rows_without_a_token(ms, T, d, E, C):
     for e in range(E):
         assert torch.equal(buf.view(torch.int16)[e, :n[e]], x.view(torch.int16)[rows[off[e]:off[e + 1]]]), e
         assert not buf.view(torch.int16)[e, n[e]:].any(), e
+
+
+@pytest.mark.parametrize("d,k,dtype", [(520, 3, "bf16"), (1024, 4, "bf16"), (1032, 5, "bf16"), (1544, 9, "bf16"), (2048, 8, "bf16"),
+                                       (260, 4, "fp32"), (1000, 6, "fp32"), (4100, 64, "fp32")])
+def test_combine_two_pieces(ms, d, k, dtype):
+    """Buffers of at least 24 MiB take two kilobytes of a row to a wavefront: the same sums in the same order as from buffers just
+    large enough for the rows."""
+    print(f"combine two pieces d={d} k={k} {dtype}", flush=True)
+    rng = np.random.default_rng(d + k)
+    T, E, C = 53, k + 2, 7
+    far = (24 << 20) // (E * d * (2 if dtype == "bf16" else 4)) + 1
+    small = torch.from_numpy(rng.standard_normal((E, C, d), dtype=np.float32)).cuda()
+    small = small.to(torch.bfloat16) if dtype == "bf16" else small
+    large = torch.zeros(E, far, d, dtype=small.dtype, device="cuda")
+    places = torch.from_numpy(np.sort(rng.choice(far, C, replace=False))).cuda()
+    large[:, places] = small
+    a = torch.from_numpy(np.argsort(rng.random((T, E)), axis=1)[:, :k].astype(np.int32)).cuda()
+    a[3], a[5, -1] = -1, E
+    pos = torch.from_numpy(rng.integers(0, C, (T, k))).cuda()
+    g = torch.from_numpy(rng.random((T, k), dtype=np.float32)).cuda()
+    y = ms.combine(large, a, places[pos].int(), g)
+    assert torch.equal(y, ms.combine(small, a, pos.int(), g))
+    ok = (a >= 0) & (a < E)
+    terms = small.double()[torch.where(ok, a, 0).long(), pos] * (g.double() * ok)[:, :, None]
+    assert ((y - terms.sum(dim=1)).abs() <= 1e-6 * terms.abs().sum(dim=1) + 1e-30).all()
