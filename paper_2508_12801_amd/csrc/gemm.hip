@@ -437,7 +437,8 @@ __global__ __launch_bounds__(256) void k_gemm_bf16_wtc(const unsigned short *__r
 // columns CT * j + c, and a lane reads its CT neighbouring columns of a row of W with one instruction.
 // fp32 runs on v_mfma_f32_32x32x2_f32, four per step of 8 indices; bf16 on v_mfma_f32_32x32x16_bf16, one per step of 16.
 // bf16 is bound by the latency of its loads and by the operands of W (from L2, once per 32 or 64 rows), fp32 by the matrix cores' fp32
-// rate.  With a load for every element of W and a wavefront to a column tile (so that x was read up to four times) bf16, scores
+// rate where its workgroups fill the chip (65536 rows: 101 TFLOP/s; the 157 workgroups of 10007 rows leave 99 of 256 compute units idle:
+// 55).  With a load for every element of W and a wavefront to a column tile (so that x was read up to four times) bf16, scores
 // in the projection, took 40.5 us at 16384 x 2048 to 64 experts (now 25.5), 15.5 at 256 x 2048 to 64 (11.6), 35 at 8192 x 2048 to 128 (23);
 // fp32 47 us at 10007 x 1000 to 96 (34), 236 at 65536 x 1024 to 128 (171: 101 TFLOP/s).
 // EPLS > 0: the tile holds whole rows of up to 8 * EPLS experts, and the scores and rewards are computed from it (as in k_gemm_bf16_wtc).
@@ -657,10 +658,12 @@ static int split_rows(int T, int E, bool own_unit)
     return in32 <= 1 || (own_unit && in32 * 10 < in64 * 17) ? 32 : 64;
 }
 
-// bf16: the split kernel as long as its workgroups of 64 rows fill the chip no more than once.  Tokens of 2048, split against
-// whole (with the transposition of W), scores in the projection: 64 experts, 16384 tokens 25.5 us against 39, 20000 43.7 against 38;
-// 128 experts, 8192 23 against 45, 16384 39 against 48.  Logits: 96 experts, 16384 31 against 40, 32768 57 against 43; 256 experts,
-// 8192 27 against 44, 16384 55 against 45.
+// bf16: the split kernel as long as its workgroups of 64 rows fill the chip no more than once.  Tokens of 256, 512, 1024, 2048 and 4096,
+// split against whole (with the transposition of W), scores in the projection: 64 experts, 16384 tokens 12 12 16 26 41 against 16 19 26
+// 38 60 us, 20000 tokens 15 18 28 44 72 against 17 20 26 39 60; 128 experts, 16384 tokens 18 21 27 39 62 against 21 25 33 48 77, 20000
+// tokens 30 35 47 70 112 against 23 26 35 49 79.  Logits: 96 experts, 16384 tokens 10 13 19 32 53 against 14 18 25 39 65, 20000 tokens 16 21
+// 33 54 95 against 15 18 26 39 66; 256 experts, 8192 tokens 10 13 17 27 47 against 17 20 27 43 74, 12288 tokens 17 22 30 49 84 against 17 21
+// 28 45 75 (scores below 12 us and logits below 8 are the host's time).
 static bool split_is_better(int T, int E) { return (long long)((T + 31) / 32) * ((E + 127) / 128) <= 512; }
 
 // Column tiles of a workgroup: neighbouring columns that a lane can read together, as many as there are tiles where that divides E (and
@@ -806,6 +809,8 @@ int32_t gemm_softtopk_run(const void *x, const void *W, const float *bias, int d
 }
 
 // Whole rows of up to 128 experts in a workgroup of the split kernel: the scores of other expert counts, and in fp32, from its sums.
+// (In bf16 not of 32, 64 and 128 experts: where these do not come from gemm_softtopk_run, d is no multiple of 64 or there is no workspace,
+// the score kernel runs behind the projection: 4096 x 1000 to 64 7.8 + 4.0 us, to 48 in one kernel 9.8.)
 // With the score kernel behind the projection 4096 x 1024 to 16 took 14.2 us (now 11.5), 64 x 64 to 8 in fp32 14.0 (11.2), 20000 x 512 to 20
 // 24.7 (20.7), 10007 x 1000 to 96 43.9 (43.1).  Beyond 64 experts and 16384 tokens the score kernel's wavefronts are the better ones
 // (fp32, 65536 x 1024 to 128: 191, in the projection 195).

@@ -26,7 +26,7 @@
 // excess left) the result is thrown away and the auction of solver.hip solves the problem instead.
 //
 // What bounds it: the passes read the rewards once each (34 MB for 65536 tokens over 128 experts, 11 us a pass including the
-// k-th best of every row, plus 7 us for the step between them, which one workgroup takes), the search is one serial chain of
+// k-th best of every row, plus 6.4 us for the step between them, which one workgroup takes), the search is one serial chain of
 // searches.  65536 tokens, 128 experts, top-8, capacity 1.0: 0.22 to 0.24 ms, of which seven passes and their steps take 0.12,
 // the last pass 0.02 and the search 0.06 to 0.09; 1.6 to 1.8 ms for the auction, whose 46 rounds each read the rewards as
 // well.  16384 over 64 experts: 0.14 against 0.8 to 1.3 ms.
@@ -425,7 +425,7 @@ static_assert(2 * kPBins + 1 <= 64, "a sum per bin");
 constexpr int price_pieces(bool half) { return (kPTableInts / (half ? 8 : 4) + kUThreads) / kUThreads; }      // per thread, at most
 
 // One workgroup.  Half of it is the wait for the copies, which the pass's additions have left in memory; the rest two barriers' worth of
-// sums and searches: 4.8 us at 16 experts, 5.8 at 64, 7.0 at 128, 9.2 at 256 (5.7, 7.5, 9.8 and 9.7 with counts of 32 bits, and with the
+// sums and searches: 4.4 us at 16 experts, 5.3 at 64, 6.4 at 128, 8.4 at 256 (5.7, 7.5, 9.8 and 9.7 with counts of 32 bits, and with the
 // sums of the bins and the largest step taken behind the copies).  As the first step of every workgroup of the next pass the same
 // work took 10 to 20 us.
 template <int N, int M, bool HALF>
@@ -631,8 +631,8 @@ __device__ __forceinline__ PriceMeta first_meta(const PriceArea *ar, const int64
     return PriceMeta{retry ? ar->meta.w : kFirstWindow, 0, 2, retry ? ar->meta.passes : prices_in ? -1 : 0, 0x7fffffff, {0, 0, 0}};
 }
 
-// All passes of a small batch in one workgroup: a pass takes 4 to 8 us (64 tokens of 8 experts: three in 14 us; 256 of 64: 54)
-// instead of two launches of 9 to 20 us together, none is launched in vain, and a batch that settles slowly may take more.
+// All passes of a small batch in one workgroup: a pass takes 4 to 11 us (64 tokens of 8 experts: three in 11 us; 256 of 64: four in 46)
+// instead of two launches and their distance, none is launched in vain, and a batch that settles slowly may take more.
 template <int G, int EPL, int MODE>
 __global__ __launch_bounds__(kUThreads) void k_price_small(PriceArgs a, int n_pass, int plim, const int64_t *__restrict__ prices_in)
 {
