@@ -42,3 +42,31 @@ def test_search(T, E, k, C, top):
     else:
         assert np.bincount(a[filled], minlength=E).max() <= C
         assert total == oracle.assign_literal_graph(q, k, C)["total"]
+
+
+@pytest.mark.parametrize("T,E,k,room", [(1000, 20, 2, 1.0), (1000, 20, 2, 0.75), (1500, 64, 6, 1.1), (1500, 64, 6, 1.0), (700, 100, 4, 1.05), (400, 24, 3, 0.8)])
+def test_targets_out_of_reach(T, E, k, room):
+    """Experts so uneven that searches find no target within the first reaches, and tries that end without one at any: the search
+    goes on from the bound to all arcs at once, and the total is the optimum whichever try or solver ends with it."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2508_12801_amd as ms
+    C = -int(-room * T * k // E)
+    print(f"targets out of reach T={T} E={E} k={k} C={C}", flush=True)
+    rng = np.random.default_rng(T + E)
+    L = (rng.standard_normal((T, E)) + 2.0 * rng.standard_normal(E)).astype(np.float32)
+    q = ms.softtopk(torch.from_numpy(L).cuda(), k, 1.0)[1]
+    runs = [ms.assign_i32(q, k, C) for _ in range(2)]
+    print(runs[0]["stats"], flush=True)
+    assert torch.equal(runs[0]["assign"], runs[1]["assign"])
+    a, qh = runs[0]["assign"].cpu().numpy(), q.cpu().numpy().astype(np.int64)
+    filled = a >= 0
+    total = int(np.take_along_axis(qh, np.where(filled, a, 0).astype(np.int64), axis=1)[filled].sum())
+    assert total == runs[0]["stats"]["total_score_q"] and int(filled.sum()) == min(T * k, E * C)
+    if room >= 1:
+        P = oracle.assignment_matrix(a, E)
+        assert (P.sum(axis=1) == k).all() and P.sum(axis=0).max() <= C and oracle.verify_optimal(qh, P, k, C)["optimal"]
+    else:
+        assert np.bincount(a[filled], minlength=E).max() <= C
+        plain = ms.assign_i32(q, k, C, finisher=False)["stats"]
+        assert (total, int(filled.sum())) == (plain["total_score_q"], plain["flow_value"])
