@@ -61,7 +61,8 @@ __global__ __launch_bounds__(256) void k_dispatch_tokens(const u32x4 *__restrict
 // larger key never end further left.  Workgroups from n_tb on zero the rows no token has.  These are neighbours, at the end of every
 // list: a wavefront looks at rows that are as far apart as there are wavefronts, so that all of them get a share (a workgroup that took
 // neighbouring rows could have nothing else: 7573 tokens of 1600 to 6 of 16 experts with room to spare 34 us, not 38; 65536 of 2048 to 6 of 8
-// 400, not 436).
+// 400, not 436), and at another place between its neighbours each time (64 lists are as long as there are wavefronts, so that without
+// it a wavefront would see the same place of every list: 10000 of 1024 to 1 of 64 with a tenth more room 9.0 us, 13.2 so, 9.9 with neighbouring rows).
 // Bound by HBM: row by row in list order every row of x comes from memory k times once x is larger than the caches.
 // 65536 tokens of 2048 to 8 of 128 experts: 683 to 441 us, 5.5 TB/s with x counted once (492 in a layer, behind the projection); 16384 to 8 of 64: 163 to 110 us.  The
 // same in other orders: shuffled 632 us (2.8 ms without the samples), descending 640 (13.9), shuffled by eight 680 (785 with a
@@ -82,16 +83,19 @@ __global__ __launch_bounds__(THREADS) void k_dispatch_tokens_blocked(const u32x4
     __shared__ int s_odd;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     if ((int)blockIdx.x >= n_tb) {
-        const long long n_rows = (long long)E * C, n_waves = (long long)(gridDim.x - n_tb) * (THREADS / 64);
-        for (long long r0 = (long long)(blockIdx.x - n_tb) * (THREADS / 64) + wv; r0 < n_rows; r0 += 64 * n_waves) {
-            const long long r = r0 + lane * n_waves;
+        const long long n_rows = (long long)E * C;
+        const unsigned n_waves = (gridDim.x - n_tb) * (THREADS / 64), w = (blockIdx.x - n_tb) * (THREADS / 64) + wv;
+        // row `lane` of a turn's 64: one of every n_waves, moved on by 0.617 n_waves each time
+        const unsigned mine = lane * n_waves + (w + lane * (unsigned)((unsigned long long)n_waves * 158 >> 8)) % n_waves;
+        for (long long r0 = 0; r0 < n_rows; r0 += 64ll * n_waves) {
+            const long long r = r0 + mine;
             bool pad = false;
             if (r < n_rows) {
                 const int j = (int)(r / C), s = (int)(r - (long long)j * C);
                 pad = s >= offsets[j + 1] - offsets[j];
             }
             for (unsigned long long m = __ballot(pad); m; m &= m - 1) {
-                u32x4 *dst = out + (r0 + (__ffsll((long long)m) - 1) * n_waves) * vec_per_row;
+                u32x4 *dst = out + (r0 + (unsigned)__builtin_amdgcn_readlane((int)mine, __ffsll((long long)m) - 1)) * vec_per_row;
                 for (int c = lane; c < vec_per_row; c += 64) put<NT>(u32x4{0u, 0u, 0u, 0u}, dst + c);
             }
         }

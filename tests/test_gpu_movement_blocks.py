@@ -68,7 +68,8 @@ def test_combine_chunks(ms, d, k, dtype):
     assert (np.abs(y - terms.sum(axis=1)) <= 1e-6 * np.abs(terms).sum(axis=1) + 1e-30).all()
 
 
-@pytest.mark.parametrize("T,d,E,C", [(4096, 8, 1, 7), (4096, 8, 3, 21), (5000, 8, 7, 1031), (4099, 8, 5, 70001), (16384, 8192, 3, 9001)])
+@pytest.mark.parametrize("T,d,E,C", [(4096, 8, 1, 7), (4096, 8, 3, 21), (5000, 8, 7, 1031), (4099, 8, 5, 70001), (10000, 8, 64, 172),
+                                     (4096, 8, 1024, 513), (16384, 8192, 3, 9001)])
 def test_rows_without_a_token(ms, T, d, E, C):
     """The rows behind every list's end are zeros: fewer rows than a workgroup looks at, more than all of them look at in one turn, and
     buffers and tokens beyond the last cache (workgroups of sixteen wavefronts)."""
