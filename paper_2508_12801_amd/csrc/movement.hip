@@ -377,10 +377,13 @@ int32_t combine_run(const void *buf, int dtype, const int32_t *assign, const int
         const bool nt = beyond_caches(traffic);
         // Two kilobytes of a row to a wavefront where the rows come from the last cache: there a second wavefront on the same row costs more
         // than it brings (4361 tokens of 552 from 4 of 64 experts 7.2 us, 9.1 with one; 10007 of 1000 in fp32 from 6 of 96 56 and 59; 7988 of
-        // 832 from 6 of 32 15.8 and 17.4).  Below some 24 MiB in all the chip is not full with half as many wavefronts (1003 of 1664 from 4
-        // of 16 5.8 and 6.6), beyond some 448 memory decides as above, and with one or two slots the result does, which is written either
-        // way.  With three or four an odd number of pieces leaves too many lanes idle (21892 of 1536 from 4 of 32 75 and 70).
-        const bool two = vpr > 64 && (k > 4 || (k > 2 && (vpr + 63) / 64 % 2 == 0)) && traffic >= (size_t)24 << 20 && traffic < (size_t)448 << 20;
+        // 832 from 6 of 32 15.8 and 17.4).  Below some 24 MiB in all, or ten wavefronts to a compute unit, the chip is not full with half as
+        // many (1024 of 1024 from 8 of 64 5.4 and 5.0), beyond some 448 MiB memory decides as above, and with one or two slots the result
+        // does, which is written either way.  With three or four an odd number of pieces leaves too many lanes idle (21892 of 1536 from 4 of 32
+        // 75 and 70).
+        const int pieces = (vpr + 63) / 64;
+        const bool two = vpr > 64 && (k > 4 || (k > 2 && pieces % 2 == 0)) && (long long)T * ((pieces + 1) / 2) >= 2560 &&
+                         traffic >= (size_t)24 << 20 && traffic < (size_t)448 << 20;
         const int piece = two ? 128 : 64, parts = (vpr + piece - 1) / piece;
         const int most = std::max(1, (1 << 24) / parts);            // tokens a launch (its threads are counted in 32 bits)
         for (int i0 = 0; i0 < T; i0 += most) {

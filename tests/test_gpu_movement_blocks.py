@@ -91,11 +91,11 @@ def test_rows_without_a_token(ms, T, d, E, C):
 @pytest.mark.parametrize("d,k,dtype", [(520, 3, "bf16"), (1024, 4, "bf16"), (1032, 5, "bf16"), (1544, 9, "bf16"), (2048, 8, "bf16"),
                                        (260, 4, "fp32"), (1000, 6, "fp32"), (4100, 64, "fp32")])
 def test_combine_two_pieces(ms, d, k, dtype):
-    """Buffers of at least 24 MiB take two kilobytes of a row to a wavefront: the same sums in the same order as from buffers just
-    large enough for the rows."""
+    """Buffers of at least 24 MiB, and tokens for 2560 wavefronts, take two kilobytes of a row to a wavefront: the same sums in the same
+    order as from buffers just large enough for the rows."""
     print(f"combine two pieces d={d} k={k} {dtype}", flush=True)
     rng = np.random.default_rng(d + k)
-    T, E, C = 53, k + 2, 7
+    T, E, C = 2563 if k < 16 else 641, k + 2, 7
     far = (24 << 20) // (E * d * (2 if dtype == "bf16" else 4)) + 1
     small = torch.from_numpy(rng.standard_normal((E, C, d), dtype=np.float32)).cuda()
     small = small.to(torch.bfloat16) if dtype == "bf16" else small
