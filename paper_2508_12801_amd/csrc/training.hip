@@ -52,10 +52,10 @@ __global__ __launch_bounds__(256) void k_colsum(const float *__restrict__ scores
 }
 
 // One workgroup: column means, the loss and its derivative with respect to the scores of a column.  Thread
-// (j, g) adds the partial sums g, g+groups, ... of column j; the groups that have any are then added in order.  Bound by latency: a
-// load, a barrier and that serial sum: 65536 tokens of 128 experts 4.8 us, of 8 4.3, 4096 of 128 3.1 (4.4 with sixteen loads a turn, of
-// which there are eight), 256 of 8 2.5 (3.7 over all groups).  With four columns a thread the serial sum is four times as long: 5.4,
-// 8.0, 3.6 and 7.9 us (5.3, 5.3, 3.5 and 2.4 over the groups that have any).
+// (j, g) adds the partial sums g, g+groups, ... of column j, eight at a time; the groups that have any are then added in order.  Bound by
+// latency: these loads, a barrier and that serial sum: 65536 tokens of 128 experts 4.8 us, 20000 of 128 4.7 (6.0 with the last ones of a
+// thread one after the other), 65536 of 8 4.2, 256 of 8 2.5 (3.7 over all groups).  With four columns a thread the serial sum is four
+// times as long: 5.4, 5.4, 8.0 and 7.9 us (5.3, 5.3, 5.3 and 2.4 over the groups that have any).
 __global__ __launch_bounds__(1024) void k_aux_final(const float *__restrict__ part, int n_blocks,
                                                     const int32_t *__restrict__ offsets, int T, int E, int epad,
                                                     float lam, float *__restrict__ loss,
@@ -67,9 +67,24 @@ __global__ __launch_bounds__(1024) void k_aux_final(const float *__restrict__ pa
     {
         const int j = tid % epad, g = tid / epad;
         double sum = 0.0;
-        if (j < E) {
-#pragma unroll 8
-            for (int b = g; b < n_blocks; b += groups) sum += (double)part[(size_t)b * E + j];
+        if (j < E && g < n_blocks) {
+            constexpr int L = 8;
+            int b = g;
+            for (; b + (L - 1) * groups < n_blocks; b += L * groups) {
+                float x[L];
+#pragma unroll
+                for (int u = 0; u < L; ++u) x[u] = part[(size_t)(b + u * groups) * E + j];
+#pragma unroll
+                for (int u = 0; u < L; ++u) sum += (double)x[u];
+            }
+            // the rest, together as well
+            if (b < n_blocks) {
+                float x[L - 1];
+#pragma unroll
+                for (int u = 0; u < L - 1; ++u) x[u] = part[(size_t)(b + u * groups < n_blocks ? b + u * groups : b) * E + j];
+#pragma unroll
+                for (int u = 0; u < L - 1; ++u) sum += b + u * groups < n_blocks ? (double)x[u] : 0.0;
+            }
         }
         s_red[g * epad + j] = sum;
     }

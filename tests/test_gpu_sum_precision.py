@@ -16,7 +16,8 @@ def ms():
     return m
 
 
-@pytest.mark.parametrize("T,E", [(1, 4), (15, 8), (65, 130), (4097, 3), (65536, 128), (262144, 128), (262145, 129), (300001, 64)])
+@pytest.mark.parametrize("T,E", [(1, 4), (15, 8), (65, 130), (4097, 3), (65536, 128), (262144, 128), (262145, 129), (300001, 64),
+                                 (3584, 128), (4033, 128), (4096, 128), (4160, 100), (450, 1024), (513, 1023), (20000, 128)])
 def test_column_means(ms, T, E):
     """A column of equal values: 15 roundings of the 16 rows a thread adds up in fp32, one of a block's sum and one of the mean."""
     print(f"column means T={T} E={E}", flush=True)
