@@ -28,7 +28,7 @@
 // What bounds it: the passes read the rewards once each (34 MB for 65536 tokens over 128 experts, 11 us a pass including the
 // k-th best of every row, plus 6.4 us for the step between them, which one workgroup takes), the search is one serial chain of
 // searches.  65536 tokens, 128 experts, top-8, capacity 1.0: 0.22 to 0.24 ms, of which seven passes and their steps take 0.12,
-// the last pass 0.02 and the search 0.06 to 0.09; 1.6 to 1.8 ms for the auction, whose 46 rounds each read the rewards as
+// the last pass 0.02 and the search 0.05 to 0.08; 1.6 to 1.8 ms for the auction, whose 46 rounds each read the rewards as
 // well.  16384 over 64 experts: 0.14 against 0.8 to 1.3 ms.
 //
 // Three forms of the problem, told apart by PriceArgs::mode:
@@ -855,114 +855,238 @@ struct FinishLds {
     unsigned lab[kPStride];           // distance << 10 | hops
     unsigned pred[kPStride];          // last arc of the shortest path: its token + 1 (0: an arc of Z) << 10 | the node it comes from
     unsigned best[kPStride];          // of a branch: distance << 10 | target
-    int p[kPStride], pi[kPStride], ex[kPStride], sl[kPStride], dd[kPStride];
+    int p[kPStride], pi[kPStride], ex[kPStride], sl[kPStride], dd[kPStride];       // dd: what the last search added to pi
     unsigned mft[kPStride];           // path arcs ...
     int mtok[kPStride];               // ... and their tokens
     unsigned wkey[kPStride];          // paths offered by their branches: distance << 10 | target ...
     int wroot[kPStride];              // ... their root ...
     unsigned wtok[kPStride];          // ... the token that leaves or joins the root (+ 1) ...
     int wlen[kPStride];               // ... and their arcs, 0 if the root has no unit left for them
-    int moved[kMovedSlots];           // tokens of the paths, hashed
+    unsigned moved[kMovedSlots];      // path arcs, hashed by their tokens: token << 10 | arc
     int chg[3], wsum[2][kFThreads / 64];
-    int bad, bad_move, dmax, n_win, n_near, n_off, n_arcs;       // bad: found while paths are chosen; bad_move: while tokens move
+    int bad, bad_move, dmax, n_win, n_near[2], n_off, n_arcs, hit;       // bad: found while paths are chosen; bad_move: while tokens move
     long long dsum;
 };
 
-constexpr int kSpareBit = 1 << 16, kReachShift = 2, kRelax = 4, kSearchRegs = 2;
-constexpr unsigned kLabInf = ~0u, kPredNone = ~0u;
+constexpr int kSpareBit = 1 << 16, kReachShift = 2, kManyArcs = 3 * kFThreads, kSearches = 8, kRelax = 4, kSearchRegs = 2;
+constexpr unsigned kLabInf = ~0u, kPredNone = ~0u, kMovedNone = ~0u;
 constexpr unsigned kWInf = 0x7fffffffu, kWMax = 1u << 21;  // distances from kWMax on are not followed
 static_assert(sizeof(FinishLds) <= 160 * 1024, "one compute unit's LDS");
 static_assert(kMaxBound < (int)kWMax, "every arc under the bound can be followed");
 static_assert(kMaxTBits <= 21, "a token + 1 and a node fit the words of the shortest paths, none of which is kPredNone");
+static_assert(kPriceMaxE < 1024 && kPStride <= 1024, "ten bits for a node, and for an arc of a search's paths");
 
-__device__ __forceinline__ int wave_total(int v) { return __builtin_amdgcn_readlane(wave_sum(v), 63); }
-__device__ __forceinline__ int moved_slot(int u) { return (int)(((unsigned)u * 0x9E3779B1u) >> 22) & (kMovedSlots - 1); }
-
-template <int NW>
-__device__ __forceinline__ int block_total(int v, int *s_w)     // over the workgroup (one barrier)
+// A move in the log: token, what it cost (nothing, if it gained), from, to.  Arcs of Z (no token) have Z at one end.
+constexpr int kLogCostBits = 23;
+__device__ __forceinline__ unsigned long long log_word(int u, int cost, int from, int to)
 {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int sum = wave_total(v);
-    if (lane == 0) s_w[wv] = sum;
-    __syncthreads();
-    return wave_total(lane < NW ? s_w[lane] : 0);
+    const int c = cost < 0 ? 0 : cost < (1 << kLogCostBits) ? cost : (1 << kLogCostBits) - 1;
+    return ((unsigned long long)(unsigned)(u < 0 ? 0 : u) << (20 + kLogCostBits)) | ((unsigned long long)(unsigned)c << 20) | (unsigned)(from << 10 | to);
 }
 
-// One workgroup.  Bound by latency: about ten dependent steps between barriers per search, each a few LDS round trips, and one read of
-// the moved tokens' rows (2 us of the 10 to 14 a search takes).  What made it shorter (65536 tokens of 128 experts 154 -> 89 us, 10007
-// of 96 169 -> 96, 16384 of 256 242 -> 126, 16384 of 64 75 -> 43, 64 of 8 17 -> 12): arcs in LDS and rolled loops instead of nine arcs
-// of every thread in registers (14 KB of code instead of 32 to 40, which had to be fetched anew by every launch), only arcs within reach
-// looked at, ties broken by token instead of by place in the list (so the list needs no order and a moved token's arcs are put there
-// as they are found), a wavefront per offered path instead of a loop over all of them in every thread, and moved tokens hashed.
-// With 512 threads 330 instead of 302 us for a solve of 65536 tokens, with 256 387.
-template <int TEPL>
+__device__ __forceinline__ int wave_total(int v) { return __builtin_amdgcn_readlane(wave_sum(v), 63); }
+__device__ __forceinline__ int moved_slot(int u) { return (u ^ (u >> 10)) & (kMovedSlots - 1); }
+
+// One workgroup.  Bound by latency: about eight dependent steps between barriers per search, each a few LDS round trips, 6 to 9 us in all.
+// What made it shorter (65536 tokens of 128 experts 154 -> 89 us, 10007 of 96 169 -> 96, 16384 of 256 242 -> 126, 16384 of 64 75 -> 43, 64
+// of 8 17 -> 12): arcs in LDS and rolled loops instead of nine arcs of every thread in registers (14 KB of code instead of 32 to 40, which
+// had to be fetched anew by every launch), only arcs within reach looked at, ties broken by token instead of by place in the list (so the
+// list needs no order), a wavefront per offered path instead of a loop over all of them in every thread, and moved tokens hashed.  With
+// 512 threads 330 instead of 302 us for a solve of 65536 tokens, with 256 387.
+//
+// A token that moves from a to b keeps its arcs: those of a become those of b, and what led to b leads to a.  Their reduced costs stay as
+// they are, as the arc of the path has none left: the potentials of a and b make up for the difference in value.  So a search reads no
+// row, and the list neither grows nor keeps arcs that are gone.  The moves are made at the end, where what the list then lacks of a moved
+// token is checked.  With unfilled slots (OS) a token that gives one up may still have others, which its arcs do not say: there the arcs
+// of moved tokens are listed anew, from their rows, in every search.  In the kernel's own clock, rows read in every search against moves at
+// the end: 65536 tokens of 128 experts 66 and 101 (two instances) -> 50 and 76 us, 16384 of 256 145 and 115 -> 93 and 73, 10007 of 96 80 ->
+// 64, 16384 of 64 45 -> 35, 4096 of 16 37 -> 31.
+template <int TEPL, bool OS>
 __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t *prices, int64_t *price_scale, SolverState *host_state)
 {
     constexpr int NT = kFThreads, NW = NT / 64;
+    constexpr int FIRST = 4;                     // arcs of every thread that are requested before their number is known
+    static_assert(FIRST * NT <= kPArcBuf && kPArcs <= kPArcBuf, "inside the buffer; the moves fit where the arcs were");
     __shared__ FinishLds s;
     PriceArea *ar = a.ar;
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int E = a.E, k = a.k, N = E + 1, mode = a.mode;
-    const bool slack = mode == kModeSlack, os = mode == kModeOver;
+    const bool slack = !OS && mode == kModeSlack;
     const PriceMeta mt = ar->meta;
-    const int B = mt.bound;
+    const int B = mt.bound, n_listed = ar->n_arcs, fail = ar->fail;
     const int *pg = ar->prices;
+    unsigned long long arc0[FIRST];
+    int tok0[FIRST];
+#pragma unroll
+    for (int j = 0; j < FIRST; ++j) {
+        arc0[j] = ar->arc[tid + j * NT];
+        tok0[j] = ar->arc_tok[tid + j * NT];
+    }
     int rounds = 0, augs = 0;
     bool close = false;                          // not solved, but near enough for another try
-    const int n_listed = ar->n_arcs;
-    bool ok = ar->fail == 0 && n_listed <= kPArcBuf;
+    bool ok = fail == 0 && n_listed <= kPArcBuf;
     const int A0 = slack ? 2 * E : 0;
     if (A0 + n_listed > kPArcs) ok = false;
     if (tid == 0) {
-        s.bad = s.bad_move = 0;
+        s.bad = s.bad_move = s.n_near[0] = 0;
         s.dsum = 0;
         s.n_arcs = A0 + n_listed;
     }
-    for (int v = tid; v < N; v += NT) {
-        int n = 0;
-        if (v < E)
-            for (int r = 0; r < 8; ++r) n += ar->loads[r][v];
-        const int p = v < E ? pg[v] : 0;
-        s.p[v] = p;
-        s.pi[v] = 0;
-        s.sl[v] = (slack && v < E && p == 0 && n < a.C) ? a.C - n : 0;
-        s.ex[v] = v < E ? n + s.sl[v] - a.C : 0;
-    }
-    if (ok)
-        for (int i = tid; i < A0 + n_listed; i += NT) {
-            const unsigned long long r = i >= A0 ? ar->arc[i - A0] : (unsigned)(i < E ? (i << 16) | E : (E << 16) | (i - E));
-            s.ft[i] = (unsigned)r;
-            s.cost[i] = (unsigned)(r >> 32);
-            s.tok[i] = i >= A0 ? ar->arc_tok[i - A0] : -1;
-        }
     long long sum = 0;
     for (int w2 = tid; w2 < a.n_wg; w2 += NT) sum += a.wg_sum[w2];
-    __syncthreads();
+    int tot;
     {
-        const int e0 = tid < E ? s.ex[tid] : 0;
-        const int tot = block_total<NW>(e0, s.wsum[0]), pos = block_total<NW>(e0 > 0 ? e0 : 0, s.wsum[1]);
-        if (tid == 0) s.ex[E] = -tot;            // Z or the unfilled slots: supply and demand match overall
+        int e0 = 0;
+        if (tid < N) {
+            const int v = tid;
+            int n = 0;
+            if (v < E)
+                for (int r = 0; r < 8; ++r) n += ar->loads[r][v];
+            const int p = v < E ? pg[v] : 0, sl = (slack && v < E && p == 0 && n < a.C) ? a.C - n : 0;
+            s.p[v] = p;
+            s.pi[v] = 0;
+            s.sl[v] = sl;
+            e0 = v < E ? n + sl - a.C : 0;
+            s.ex[v] = e0;
+        }
+        if (ok) {
+            for (int i = tid; i < A0; i += NT) {
+                s.ft[i] = i < E ? (i << 16) | E : (E << 16) | (i - E);
+                s.cost[i] = 0;
+                s.tok[i] = -1;
+            }
+            auto keep = [&](int i, unsigned long long r, int t) {
+                s.ft[A0 + i] = (unsigned)r;
+                s.cost[A0 + i] = (unsigned)(r >> 32);
+                s.tok[A0 + i] = t;
+            };
+#pragma unroll
+            for (int j = 0; j < FIRST; ++j)
+                if (tid + j * NT < n_listed) keep(tid + j * NT, arc0[j], tok0[j]);
+            for (int i = tid + FIRST * NT; i < n_listed; i += NT) keep(i, ar->arc[i], ar->arc_tok[i]);
+        }
+        const int t0 = wave_total(e0), q0 = wave_total(e0 > 0 ? e0 : 0);
+        if (lane == 0) {
+            s.wsum[0][wv] = t0;
+            s.wsum[1][wv] = q0;
+        }
+        __syncthreads();
+        tot = wave_total(lane < NW ? s.wsum[0][lane] : 0);
+        const int pos = wave_total(lane < NW ? s.wsum[1][lane] : 0);
+        if (tid == E) s.ex[E] = -tot;            // Z or the unfilled slots: supply and demand match overall (only this thread reads it first)
         const int most = pos > pos - tot ? pos : pos - tot;
         if (mode == kModeTight && tot != 0) ok = false;
         if (most > 8 * E + 64) ok = false;       // the prices are far from an equilibrium
-        close = ar->fail == 0 && most <= 2 * E + 64;
+        close = fail == 0 && most <= 2 * E + 64;
     }
     __syncthreads();
+    // A token's slots and rewards, lane by lane.
+    auto load_row = [&](int u, int &h, int (&qv)[TEPL]) {
+        // (rows that an earlier search has changed were written by this workgroup)
+        h = u >= 0 && lane < k ? __hip_atomic_load(&a.assign[(size_t)u * k + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : -2;
+#pragma unroll
+        for (int m = 0; m < TEPL; ++m) qv[m] = u >= 0 && lane + 64 * m < E ? a.q[(size_t)u * E + lane + 64 * m] : 0;
+    };
+    auto held_columns = [&](int h) {             // this lane's columns that the token holds
+        unsigned held = 0;
+        for (int sl = 0; sl < k; ++sl) {
+            const int e = __builtin_amdgcn_readlane(h, sl);
+            if (e >= 0 && (e & 63) == lane) held |= 1u << (e >> 6);
+        }
+        return held;
+    };
+    auto spread = [&] {                          // of the potentials
+        int lo = -0x7fffffff, hi = -0x7fffffff;
+        for (int v = lane; v < (OS ? N : E); v += 64) {
+            const int x = s.pi[v];
+            lo = -x > lo ? -x : lo;
+            hi = x > hi ? x : hi;
+        }
+        return wave_max(hi) + wave_max(lo);
+    };
     bool solved = false, forward = true;
     int n_old = 0;                               // arcs that were there when the last paths were taken
+    int n_log = 0;                               // moves so far
+    unsigned turn = 0;
     const int max_rounds = 8 * E + 128;
     for (; ok; ++rounds) {
         const int ev = tid < N ? s.ex[tid] : 0, n_arcs = s.n_arcs;
-        const bool hub = os && tid == E;
+        const bool hub = OS && tid == E;
         const bool is_src = ev > 0 && (mode == kModeTight || tid < E), is_snk = ev < 0;
-        if (tid == 0) s.n_near = s.n_off = s.dmax = s.n_win = 0;
-        // sources, sinks, and nodes out of balance
-        const int n_all = block_total<NW>((is_src ? 1 : 0) | (is_snk ? 1 << 10 : 0) | (ev != 0 ? 1 << 20 : 0), s.wsum[rounds & 1]);
+        // sources, sinks, and nodes out of balance: counted while the arcs are listed
+        {
+            const int c = wave_total((is_src ? 1 : 0) | (is_snk ? 1 << 10 : 0) | (ev != 0 ? 1 << 20 : 0));
+            if (lane == 0) s.wsum[rounds & 1][wv] = c;
+        }
+        // Shortest paths from (backward: to) all roots, up to a reach that starts at a quarter of the bound (an eighth, if there are so many
+        // arcs that a quarter of them is more than one to a lane: 16384 tokens of 256 experts 93 -> 83 us) and is doubled up to it until some
+        // target lies within it; beyond the bound everything is looked at (doubled on and on, searches of very uneven experts took up
+        // to 16 turns: 3000 tokens to 4 of 256, failed tries included, 1224 us, now 583).  Potentials that spread as far as the bound
+        // hardly come together again: then, before a longer reach and after more searches than most solves need, this try ends (640 tokens
+        // to 2 of 160, two such tries and the auction 2.9 -> 2.4 ms).  Only arcs shorter than the reach can be on such a path: they are
+        // listed densely first, so that few arcs meet in a bank of LDS, whose look-ups bound the search.  Labels only fall, and where they
+        // end does not depend on the order in which arcs are looked at; hops break ties of distance, so that the last arcs form trees.
+        auto list_arcs = [&](unsigned reach, bool fresh, int *n_near) {          // fresh: reduced costs are those before the last paths
+            auto near = [&](unsigned c, int i) {
+                const bool in = c < reach;
+                const unsigned long long bal = __ballot(in);
+                if (bal) {
+                    int at = 0;
+                    if (lane == 0) at = atomicAdd(n_near, (int)__popcll(bal));
+                    at = __builtin_amdgcn_readfirstlane(at);
+                    if (in) s.near[__builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, (unsigned)at))] = (unsigned short)i;
+                }
+            };
+            if (slack)
+                for (int i = tid; i - lane < A0; i += NT) {      // a spare place may leave an expert that has one, and may enter any expert at its price
+                    unsigned c = kWInf;
+                    if (i < A0) {
+                        const int v = i < E ? i : i - E, x = s.p[v] - s.pi[v] + s.pi[E];
+                        c = i < E ? (s.sl[v] > 0 ? (unsigned)-x : kWInf) : (unsigned)x;
+                        if (c != kWInf && (int)c < 0) s.bad = 1;
+                        s.cost[i] = c;
+                    }
+                    near(c, i);
+                }
+            for (int i = A0 + tid; i - lane < n_arcs; i += NT) {
+                unsigned c = i < n_arcs ? s.cost[i] : kWInf;
+                if (fresh && i < n_old && c != kWInf) {
+                    const unsigned f = s.ft[i];
+                    const int u = s.tok[i], from = (int)(f >> 16), to = (int)(f & 0xffff);
+                    int x = moved_slot(u);
+                    unsigned o = s.moved[x];
+                    c += (unsigned)(s.dd[from] - s.dd[to]);
+                    if (o != kMovedNone) {
+                        int nf = from, nt = to;
+                        for (; o != kMovedNone; o = s.moved[x]) {
+                            x = (x + 1) & (kMovedSlots - 1);
+                            if ((int)(o >> 10) != u) continue;
+                            if (OS) {
+                                c = kWInf;                 // (a moved token has new arcs in the list)
+                                break;
+                            }
+                            // (the places of a token that moves twice in a search are four different ones: two it held and two it did not)
+                            const unsigned m = s.mft[o & 1023];
+                            if (from == (int)(m >> 16)) nf = (int)(m & 0xffff);
+                            if (to == (int)(m & 0xffff)) nt = (int)(m >> 16);
+                        }
+                        if (!OS && (nf != from || nt != to)) s.ft[i] = (unsigned)((nf << 16) | nt);
+                    }
+                    s.cost[i] = c;
+                }
+                near(c, i);
+            }
+            __syncthreads();
+        };
+        unsigned reach = (unsigned)B >> (n_arcs > kManyArcs ? kReachShift + 1 : kReachShift);
+        reach = reach < 1 ? 1 : reach > kWMax ? kWMax : reach;
+        list_arcs(reach, n_old > 0, &s.n_near[turn & 1]);
+        const int n_all = wave_total(lane < NW ? s.wsum[rounds & 1][lane] : 0);
         if (n_all == 0) {
             solved = true;
             break;
         }
-        if (rounds >= max_rounds) break;
+        if (rounds >= max_rounds || (rounds >= kSearches && spread() >= B)) break;
         const int n_src = n_all & 1023, n_snk = (n_all >> 10) & 1023;
         // Spare places, or unfilled slots: whatever is too many goes to the nearest place that lacks a token or has one to
         // spare (the trees grow backward from all of these), and what Z then has too many to the places that lack one.
@@ -971,58 +1095,27 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
         // can send as many paths as it has units.
         const bool spare_here = slack && tid < E && ev == 0 && s.sl[tid] > 0;
         const bool via_z = mode != kModeTight && n_src > 0;
-        const bool was_forward = forward;
         forward = mode == kModeTight ? n_src <= n_snk : !via_z;
         const bool is_root = via_z ? hub || spare_here || (is_snk && tid < E) : forward ? ev > 0 : is_snk;
         const bool is_target = via_z ? is_src : forward ? is_snk && tid < E + (mode == kModeTight) : is_src;
-        // Shortest paths from (backward: to) all roots, up to a reach that starts at a quarter of the bound and is doubled up to it
-        // until some target lies within it; beyond the bound everything is looked at (doubled on and on, searches of very uneven
-        // experts took up to 16 turns: 3000 tokens to 4 of 256, failed tries included, 1224 us, now 583).  Only arcs shorter than the
-        // reach can be on such a path: they are listed densely first, so that few arcs meet in a bank of LDS, whose look-ups bound
-        // the search.  Labels only fall, and where they end does not depend on the order in which arcs are looked at; hops break ties of
-        // distance, so that the last arcs form trees.
         unsigned limit = 0;
         bool settled = false, target = false;
         int nc = 0;
         auto turned = [&](unsigned f) { return forward ? f : __builtin_amdgcn_alignbit(f, f, 16); };     // tail << 16 | head
-        bool fresh = n_old > 0;                  // reduced costs are those before the last paths
-        for (unsigned reach = (unsigned)B >> kReachShift;; reach = reach < (unsigned)B ? 2 * reach : kWMax, fresh = false) {
-            reach = reach < 1 ? 1 : reach > kWMax ? kWMax : reach;
+        for (;;) {
             limit = reach << 10;
-            if (tid == 0) s.lab[kPStride - 1] = kLabInf;
+            nc = s.n_near[turn & 1];
+            ++turn;
+            if (tid == 0) {
+                s.lab[kPStride - 1] = kLabInf;
+                s.n_off = s.dmax = s.n_win = s.hit = s.n_near[turn & 1] = 0;
+            }
             if (tid < N) {
                 s.lab[tid] = is_root ? 0u : kLabInf;
                 s.pred[tid] = kPredNone;
                 s.best[tid] = kLabInf;
             }
             if (tid < 3) s.chg[tid] = 0;
-            for (int i0 = wv * 64; i0 < n_arcs; i0 += NT) {
-                const int i = i0 + lane;
-                unsigned c = i < n_arcs ? s.cost[i] : kWInf;
-                if (i < A0) {        // a spare place may leave an expert that has one, and may enter any expert at its price
-                    const int v = i < E ? i : i - E, x = s.p[v] - s.pi[v] + s.pi[E];
-                    c = i < E ? (s.sl[v] > 0 ? (unsigned)-x : kWInf) : (unsigned)x;
-                    if (c != kWInf && (int)c < 0) s.bad = 1;
-                    s.cost[i] = c;
-                } else if (fresh && i < n_old && c != kWInf) {
-                    const unsigned f = s.ft[i];
-                    const int u = s.tok[i], df = s.dd[f >> 16] - s.dd[f & 0xffff];
-                    int x = moved_slot(u), o;
-                    while ((o = s.moved[x]) != u && o != -1) x = (x + 1) & (kMovedSlots - 1);
-                    c = o == u ? kWInf : c + (unsigned)(was_forward ? df : -df);       // (a moved token has new arcs in the list)
-                    s.cost[i] = c;
-                }
-                const bool in = c < reach;
-                const unsigned long long bal = __ballot(in);
-                if (bal) {
-                    int at = 0;
-                    if (lane == 0) at = atomicAdd(&s.n_near, (int)__popcll(bal));
-                    at = __builtin_amdgcn_readfirstlane(at);
-                    if (in) s.near[at + __popcll(bal & ((1ull << lane) - 1))] = (unsigned short)i;
-                }
-            }
-            __syncthreads();
-            nc = s.n_near;
             // Each wavefront with arcs keeps them in registers, R to a lane; straight code, as taken branches cost more than the
             // look-ups.  (Spread over fewer wavefronts, several arcs to a lane, it took longer.)
             auto search = [&](auto regs) {
@@ -1042,6 +1135,7 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
                         x[j] = (s.cost[i] << 10) + 1;
                     }
                 }
+                __syncthreads();
                 for (int it = 0; it < 4 * N; ++it) {
                     if (wv * 64 < nc) {
                         bool any = false;
@@ -1079,21 +1173,26 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
             if (nc <= NT) settled = search(std::integral_constant<int, 1>());
             else settled = search(std::integral_constant<int, kSearchRegs>());
             target = is_target && s.lab[tid] < limit;
-            if (!settled || reach >= kWMax) break;
-            if (tid == 0) s.n_near = 0;
-            if (__syncthreads_or(target)) break;
-        }
-        // last arcs of the paths (the lowest token wins, then the lowest node)
-        for (int x = tid; x < nc; x += NT) {
-            const int i = s.near[x];
-            const unsigned f = turned(s.ft[i]), la = s.lab[f >> 16];
-            if (la < limit && la + (s.cost[i] << 10) + 1 == s.lab[f & 0xffff])
-                atomicMin(&s.pred[f & 0xffff], ((unsigned)(s.tok[i] + 1) << 10) | (f >> 16));
+            if (target) s.hit = 1;
+            // last arcs of the paths (the lowest token wins, then the lowest node)
+            for (int x = tid; x < nc; x += NT) {
+                const int i = s.near[x];
+                const unsigned f = turned(s.ft[i]), la = s.lab[f >> 16];
+                if (la < limit && la + (s.cost[i] << 10) + 1 == s.lab[f & 0xffff])
+                    atomicMin(&s.pred[f & 0xffff], ((unsigned)(s.tok[i] + 1) << 10) | (f >> 16));
+            }
+            __syncthreads();
+            if (s.hit || !settled || reach >= kWMax) break;
+            if (spread() >= B) {
+                settled = false;
+                break;
+            }
+            reach = reach >= (unsigned)B ? kWMax : 2 * reach < (unsigned)B ? 2 * reach : (unsigned)B;
+            list_arcs(reach, false, &s.n_near[turn & 1]);
         }
         const unsigned lv = tid < N ? s.lab[tid] : kLabInf;
         const bool reached = lv < limit;
         const int dist = reached ? (int)(lv >> 10) : 0, hops = (int)(lv & 1023);
-        __syncthreads();
         // every branch of a root offers the path to its nearest target, a root takes as many as it has units
         int root = tid, branch = tid;
         const unsigned my_key = ((unsigned)dist << 10) | (unsigned)tid;
@@ -1113,7 +1212,7 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
             s.wroot[i] = root;
             s.wtok[i] = s.pred[branch] >> 10;
         }
-        for (int i = tid; i < kMovedSlots; i += NT) s.moved[i] = -1;
+        for (int i = tid; i < kMovedSlots; i += NT) s.moved[i] = kMovedNone;
         __syncthreads();
         const int n_off = s.n_off;
         // (the i-th path offered belongs to wavefront i modulo their number)
@@ -1127,7 +1226,7 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
                 before += __popcll(__ballot(ahead));
                 clash |= __any(ahead && tk != 0 && s.wtok[c] == tk) != 0;       // (the token has one place at the root)
             }
-            const int units = os && via_z && rt == E ? 1 << 30 : er != 0 ? (er > 0 ? er : -er) : s.sl[rt];
+            const int units = OS && via_z && rt == E ? 1 << 30 : er != 0 ? (er > 0 ? er : -er) : s.sl[rt];
             const bool win = !clash && before < units;
             if (lane == 0) {
                 // (a root that has no token too many or too few gives a spare place)
@@ -1155,7 +1254,7 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
                 nm += __builtin_amdgcn_readlane(inc, 63);
             }
             const int word = mine >= 0 ? s.wlen[mine] : 0, len = word & (kSpareBit - 1);
-            if (len > 0 && nm <= kPStride) {                 // (always: the paths are disjoint)
+            if (len > 0 && nm <= kPStride && n_log + nm <= kPArcs) {        // (nm: always, the paths are disjoint)
                 const int tgt = (int)(s.wkey[mine] & 1023), rt = s.wroot[mine];
                 int x = tgt;
                 for (int i = 0; i < len; ++i) {
@@ -1185,36 +1284,43 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
         if (tid < N) {
             // (no further than the paths taken: experts far from them keep their potentials close to the others)
             const int dm = s.dmax, d = reached && dist < dm ? dist : dm;
-            s.dd[tid] = d;
+            s.dd[tid] = forward ? d : -d;
             s.pi[tid] += forward ? d : -d;
         }
         __syncthreads();
-        if (s.n_win == 0 || s.bad || !settled || nm > kPStride) break;         // no way to place what is left with these arcs
+        if (s.n_win == 0 || s.bad || !settled || nm > kPStride || n_log + nm > kPArcs) break;         // no way to place what is left with these arcs
         augs += s.n_win;
         n_old = n_arcs;
-        // The tokens of the paths move, one per wavefront at a time, with the next one's row on its way.  The arcs a token
+        // the moves: a hash by token for the list, and for the end, with what each costs, where the arcs were
+        if (tid < nm) {
+            const int u = s.mtok[tid];
+            const unsigned f = s.mft[tid];
+            if (u >= 0)
+                for (int y = moved_slot(u); atomicCAS(&s.moved[y], kMovedNone, (unsigned)(u << 10 | tid)) != kMovedNone;) y = (y + 1) & (kMovedSlots - 1);
+            if (!OS) {
+                const int from = (int)(f >> 16), to = (int)(f & 0xffff), cost = s.pi[to] - s.pi[from];
+                if (u >= 0) sum += (long long)(s.p[to] - s.p[from]) - cost;        // (the arc has no reduced cost left)
+                __hip_atomic_store(&ar->arc[n_log + tid], log_word(u, cost, from, to), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+        }
+        n_log += OS ? 0 : nm;
+        if constexpr (!OS) {
+            __syncthreads();
+            continue;
+        }
+        // OS: the tokens of the paths move, one per wavefront at a time, with the next one's row on its way.  The arcs a token
         // offers from where it is now replace its old ones in the list.
-        auto load_row = [&](int i, int &u, int &h, int (&qv)[TEPL]) {
-            u = i < nm ? s.mtok[i] : -1;
-            // (rows that an earlier search has changed were written by this workgroup)
-            h = u >= 0 && lane < k ? __hip_atomic_load(&a.assign[(size_t)u * k + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : -2;
-#pragma unroll
-            for (int m = 0; m < TEPL; ++m) qv[m] = u >= 0 && lane + 64 * m < E ? a.q[(size_t)u * E + lane + 64 * m] : 0;
-        };
-        int un, hn, qn[TEPL];
-        load_row(wv, un, hn, qn);
+        int un = wv < nm ? s.mtok[wv] : -1, hn, qn[TEPL];
+        load_row(un, hn, qn);
         for (int i = wv; i < nm; i += NW) {
             int u = un, h = hn, qv[TEPL];
 #pragma unroll
             for (int m = 0; m < TEPL; ++m) qv[m] = qn[m];
-            load_row(i + NW, un, hn, qn);
+            un = i + NW < nm ? s.mtok[i + NW] : -1;
+            load_row(un, hn, qn);
             bool first = u >= 0;                                  // a token on two paths is taken once
             for (int x0 = 0; x0 < i && first; x0 += 64) first = !__any(x0 + lane < i && s.mtok[x0 + lane] == u);
             if (!first) continue;
-            if (lane == 0) {
-                int x = moved_slot(u);
-                for (int o; (o = atomicCAS(&s.moved[x], -1, u)) != -1 && o != u;) x = (x + 1) & (kMovedSlots - 1);
-            }
             int *bcnt = a.blkcnt + (size_t)(u / a.rows) * E;
             for (int x0 = i & ~63; x0 < nm; x0 += 64) {
                 unsigned long long same = __ballot(x0 + lane >= i && x0 + lane < nm && s.mtok[x0 + lane] == u);
@@ -1242,21 +1348,14 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
                     }
                 }
             }
-            {
-                int dst = lane;
-                if (os) {                              // empty slots go to the end of the row
-                    const unsigned long long be = __ballot(h == -1), br = __ballot(h >= 0);
-                    dst = h >= 0 ? __popcll(br & ((1ull << lane) - 1)) : __popcll(br) + __popcll(be & ((1ull << lane) - 1));
-                }
+            {                                          // empty slots go to the end of the row
+                const unsigned long long be = __ballot(h == -1), br = __ballot(h >= 0);
+                const int dst = h >= 0 ? __popcll(br & ((1ull << lane) - 1)) : __popcll(br) + __popcll(be & ((1ull << lane) - 1));
                 if (lane < k) __hip_atomic_store(&a.assign[(size_t)u * k + dst], h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
             // Its exchanges: only slots near the best expert it does not hold have any under the bound.
-            unsigned heldm = 0;                                   // this lane's columns that the token holds
-            for (int sl = 0; sl < k; ++sl) {
-                const int e = __builtin_amdgcn_readlane(h, sl);
-                if (e >= 0 && (e & 63) == lane) heldm |= 1u << (e >> 6);
-            }
-            int v[TEPL], best = os ? 0 : -0x7fffffff, vs = 0;     // vs: value of the expert in slot `lane`
+            const unsigned heldm = held_columns(h);
+            int v[TEPL], best = 0, vs = 0;     // vs: value of the expert in slot `lane`
 #pragma unroll
             for (int m = 0; m < TEPL; ++m) {
                 const int c = lane + 64 * m;
@@ -1290,7 +1389,7 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
                 const int sl = __ffsll((long long)r) - 1;
                 const int e = __builtin_amdgcn_readlane(h, sl), vh = __builtin_amdgcn_readlane(vs, sl);
                 put(vh, e);
-                if (os && vh < B && lane == 0) {                  // ... for an unfilled slot
+                if (vh < B && lane == 0) {                  // ... for an unfilled slot
                     const int at = atomicAdd(&s.n_arcs, 1), wn = vh + s.pi[e] - s.pi[E];
                     if (at < kPArcs) {
                         if (wn < 0) s.bad_move = 1;
@@ -1300,39 +1399,111 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
                     }
                 }
             }
-            if (os && __any(lane < k && h == -1)) put(0, E);
+            if (__any(lane < k && h == -1)) put(0, E);
         }
         __syncthreads();
         if (s.n_arcs > kPArcs || s.bad_move) break;
     }
     __syncthreads();
     // the arcs left out cost at least B: they stay non-negative if the potentials spread less than that
-    int lo = 0x7fffffff, hi = -0x7fffffff, pmin = 0x7fffffff;
-    for (int v = lane; v < (os ? N : E); v += 64) {
-        const int x = s.pi[v];
-        lo = x < lo ? x : lo;
-        hi = x > hi ? x : hi;
-        if (v < E) pmin = s.p[v] - x < pmin ? s.p[v] - x : pmin;
+    const int apart = spread();
+    int pmin = 0x7fffffff;
+    for (int v = lane; v < E; v += 64) pmin = s.p[v] - s.pi[v] < pmin ? s.p[v] - s.pi[v] : pmin;
+    pmin = -wave_max(-pmin);
+    if (!OS && solved && apart < B && n_log > 0) {
+        // The moves are made, one thread for all of a token.  An exchange of a token that has moved is in the list unless it costs the bound
+        // less what the moves cost; where the potentials spread as far as that its row is looked at (as good as never): none of its
+        // experts may be worth less than one that it does not hold.
+        constexpr unsigned short none = 0xffff;
+        static_assert(kPArcs < none, "a word of `near` links two moves");
+        for (int i = tid; i < kMovedSlots; i += NT) s.moved[i] = kMovedNone;
+        if (tid == 0) s.n_off = 0;
+        for (int i = tid; i < n_log; i += NT) {
+            const unsigned long long r = __hip_atomic_load(&ar->arc[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            const unsigned from = (unsigned)(r >> 10) & 1023, to = (unsigned)r & 1023;
+            s.tok[i] = (int)from == E || (int)to == E ? -1 : (int)(r >> (20 + kLogCostBits));
+            s.cost[i] = (unsigned)(r >> 20) & ((1u << kLogCostBits) - 1);
+            s.ft[i] = from << 16 | to;
+        }
+        __syncthreads();
+        for (int i = tid; i < n_log; i += NT) {
+            const int u = s.tok[i];
+            if (u < 0) continue;
+            const unsigned o = atomicExch(&s.moved[moved_slot(u)], (unsigned)i);
+            s.near[i] = o == kMovedNone ? none : (unsigned short)o;
+        }
+        __syncthreads();
+        for (int i = tid; i < n_log; i += NT) {
+            const int u = s.tok[i];
+            bool first = u >= 0;
+            unsigned head = kMovedNone;
+            if (first) {
+                head = s.moved[moved_slot(u)];
+                for (unsigned o = head; o != none; o = s.near[o]) first = first && !(s.tok[o] == u && (int)o < i);
+            }
+            if (!first) continue;
+            int *row = a.assign + (size_t)u * k, *bcnt = a.blkcnt + (size_t)(u / a.rows) * E;
+            long long cost = 0;
+            for (int at = i; at < n_log;) {
+                const unsigned f = s.ft[at];
+                const int from = (int)(f >> 16), to = (int)(f & 0xffff);
+                cost += s.cost[at];
+                int sl = -1;
+#pragma unroll 8
+                for (int x = 0; x < k; ++x)
+                    if (__hip_atomic_load(row + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == from) sl = x;
+                if (sl < 0) s.bad_move = 1;                  // (never: the arcs of a token are those of its row)
+                else __hip_atomic_store(row + sl, to, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                atomicAdd(&bcnt[from], -1);
+                atomicAdd(&bcnt[to], 1);
+                int then = n_log;
+                for (unsigned o = head; o != none; o = s.near[o])
+                    if (s.tok[o] == u && (int)o > at && (int)o < then) then = (int)o;
+                at = then;
+            }
+            if (cost + apart >= B) {
+                const int x = atomicAdd(&s.n_off, 1);
+                if (x < kPStride) s.mtok[x] = u;
+                else s.bad_move = 1;
+            }
+        }
+        __syncthreads();
+        const int n_far = s.n_off < kPStride ? s.n_off : kPStride;
+        for (int i = wv; i < n_far; i += NW) {
+            int h, qv[TEPL];
+            load_row(s.mtok[i], h, qv);
+            const unsigned held = held_columns(h);
+            int least = 0x7fffffff, most = -0x7fffffff;
+#pragma unroll
+            for (int m = 0; m < TEPL; ++m) {
+                const int c = lane + 64 * m;
+                if (c >= E) continue;
+                const int v = qv[m] - s.p[c] + s.pi[c];
+                if ((held >> m) & 1u) least = v < least ? v : least;
+                else most = v > most ? v : most;
+            }
+            if (wave_max(most) > -wave_max(-least) && lane == 0) s.bad_move = 1;
+        }
+        __syncthreads();
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        const int x = __shfl_xor(lo, off), y = __shfl_xor(hi, off), z = __shfl_xor(pmin, off);
-        lo = x < lo ? x : lo;
-        hi = y > hi ? y : hi;
-        pmin = z < pmin ? z : pmin;
-    }
-    const bool certified = solved && hi - lo < B;
+    const bool certified = solved && apart < B && !s.bad_move;
     int sb = 0;
     while ((1 << sb) < E + 1) ++sb;
     if (certified && prices) {
         const int shift = slack ? -s.pi[E] : pmin;
         for (int e = tid; e < E; e += NT) prices[e] = (int64_t)(s.p[e] - s.pi[e] - shift) << sb;
     }
-    if (sum) atomicAdd((unsigned long long *)&s.dsum, (unsigned long long)sum);
+    // (one addition a wavefront: those of all lanes to one word are compiled into a loop over the lanes, 2 us)
+    for (int off = 32; off > 0; off >>= 1) {
+        const unsigned x = __shfl_xor((unsigned)sum, off), y = __shfl_xor((unsigned)((unsigned long long)sum >> 32), off);
+        sum += (long long)(((unsigned long long)y << 32) | x);
+    }
+    if (lane == 0 && sum) atomicAdd((unsigned long long *)&s.dsum, (unsigned long long)sum);
     __syncthreads();
     if (tid == 0) {
         if (certified && price_scale) *price_scale = (int64_t)1 << sb;
         host_state->total = s.dsum;
-        host_state->flow = os ? E * a.C : a.T * k;
+        host_state->flow = OS ? E * a.C : a.T * k;
         host_state->round = mt.passes;
         host_state->phases = 1;
         host_state->status = MAXSCORE_OK;
@@ -1521,7 +1692,11 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
             mark();
         }
     }
-#define MS_F(PP) hipLaunchKernelGGL(k_price_finish<PP>, dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, host_state_dev)
+#define MS_F(PP)                                                                                                                            \
+    do {                                                                                                                                    \
+        if (os) hipLaunchKernelGGL((k_price_finish<PP, true>), dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, host_state_dev);     \
+        else hipLaunchKernelGGL((k_price_finish<PP, false>), dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, host_state_dev);       \
+    } while (0)
     if (E <= 64) MS_F(1);
     else if (E <= 128) MS_F(2);
     else if (E <= 256) MS_F(4);

@@ -70,3 +70,29 @@ def test_targets_out_of_reach(T, E, k, room):
         assert np.bincount(a[filled], minlength=E).max() <= C
         plain = ms.assign_i32(q, k, C, finisher=False)["stats"]
         assert (total, int(filled.sum())) == (plain["total_score_q"], plain["flow_value"])
+
+
+@pytest.mark.parametrize("T,E,k,room,uneven", [(200, 16, 8, 1.0, 1.0), (1024, 256, 1, 1.0, 0.0), (600, 65, 5, 1.0, 1.5), (5623, 96, 2, 1.02, 1.5),
+                                               (1300, 129, 6, 1.0, 1.0), (640, 160, 2, 0.9, 1.5), (1600, 512, 4, 1.0, 0.5)])
+def test_moved_tokens_and_their_places(T, E, k, room, uneven):
+    """Tokens that move more than once, in one search and in several: slots, lists, counts and positions are those of where they end,
+    the reported total is the sum of their rewards, and the certificate holds with the exchanges that the list does not have."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2508_12801_amd as ms
+    C = -int(-room * T * k // E)
+    print(f"moved tokens T={T} E={E} k={k} C={C} uneven={uneven}", flush=True)
+    rng = np.random.default_rng(T + 7 * E)
+    L = (rng.standard_normal((T, E)) + uneven * rng.standard_normal(E)).astype(np.float32)
+    r = ms.route_logits(torch.from_numpy(L).cuda(), k, C)
+    print(r["stats"], flush=True)
+    a, q = r["assign"].cpu().numpy(), r["q"].cpu().numpy().astype(np.int64)
+    filled = a >= 0
+    assert int(filled.sum()) == min(T * k, E * C) and np.bincount(a[filled], minlength=E).max() <= C
+    assert int(np.take_along_axis(q, np.where(filled, a, 0).astype(np.int64), axis=1)[filled].sum()) == r["stats"]["total_score_q"]
+    if room >= 1:
+        P = oracle.assignment_matrix(a, E)
+        assert oracle.verify_optimal(q, P, k, C)["optimal"]
+    d = oracle.dispatch(a, r["gates"].cpu().numpy(), E)
+    for name in ("expert_offsets", "disp_token", "token_pos"):
+        assert np.array_equal(r[name].cpu().numpy(), d[name]), name
