@@ -190,7 +190,7 @@ int32_t maxscore_assign_iter_i32(const int32_t *q, int32_t T, int32_t E, int32_t
     int32_t rc = check_ws(workspace, workspace_bytes, T, E, k);
     if (rc) return rc;
     if (max_rounds < 0) max_rounds = 1000;
-    rc = iter_run(q, T, E, k, C, max_rounds, assign, total, flow, rounds, (char *)workspace, (hipStream_t)stream);
+    rc = iter_run(q, T, E, k, C, max_rounds, assign, total, flow, rounds, (char *)workspace, (hipStream_t)stream, nullptr, nullptr);
     MS_HIP(hipStreamSynchronize((hipStream_t)stream));
     return rc;
 }
@@ -351,12 +351,33 @@ static int32_t route_from_rewards(const float *scores, const int32_t *q, int T, 
     if (o.assignment == MAXSCORE_ASSIGN_ITER) {
         int64_t total = 0;
         int32_t flow = 0, rounds = 0;
-        src = iter_run(q, T, E, k, C, o.max_rounds, assign, &total, &flow, &rounds, ws, s);
+        // the rounds leave the number of pairs per 64 tokens and expert: gates and dispatch are enqueued behind the last one
+        struct AfterCtx {
+            const float *scores; const int32_t *assign; int T, E, k; float *gates; int32_t *offsets, *disp_token;
+            float *disp_gate; int32_t *token_pos; char *ws; hipEvent_t ev_a, ev_b; bool called;
+        } ctx = {scores, assign, T, E, k, gates, expert_offsets, disp_token, disp_gate, token_pos, ws, ev_a, ev_b, false};
+        const IterAfter after = [](void *c, hipStream_t st) -> int32_t {
+            AfterCtx *a = (AfterCtx *)c;
+            a->called = true;
+            MS_HIP(hipEventRecord(a->ev_a, st));
+            const SolverGeometry g = {64, (a->T + 63) / 64, 0, 1, nullptr};
+            const int32_t rc = dispatch_from_keys(g, a->scores, a->assign, a->T, a->E, a->k, a->gates, a->offsets, a->disp_token, a->disp_gate,
+                                                  a->token_pos, a->ws, st);
+            if (rc) return rc;
+            MS_HIP(hipEventRecord(a->ev_b, st));
+            return MAXSCORE_OK;
+        };
+        src = iter_run(q, T, E, k, C, o.max_rounds, assign, &total, &flow, &rounds, ws, s, k <= 16 && E <= kPriceMaxE ? after : nullptr, &ctx);
         if (stats) {
             stats->total_score_q = total;
             stats->flow_value = flow;
             stats->rounds = rounds;
             stats->status = src;
+        }
+        if (ctx.called && (src == MAXSCORE_OK || src == MAXSCORE_ERR_NOT_CONVERGED)) {
+            float t = 0.f;               // (the rounds have waited for the stream)
+            if (stats && hipEventElapsedTime(&t, ev_a, ev_b) == hipSuccess) stats->gates_dispatch_ms = t;
+            return src;
         }
     } else {
         // A price solve leaves the number of pairs per block of rows and expert, an auction that converged every pair
@@ -392,13 +413,6 @@ static int32_t route_from_rewards(const float *scores, const int32_t *q, int T, 
     }
     if (src != MAXSCORE_OK && src != MAXSCORE_ERR_NOT_CONVERGED) return src;
     MS_HIP(hipEventRecord(ev_a, s));
-    if (o.assignment == MAXSCORE_ASSIGN_ITER && k <= 16 && E <= kPriceMaxE) {
-        // the rounds leave the number of pairs per 64 tokens and expert
-        const SolverGeometry g = {64, (T + 63) / 64, 0, 1, nullptr};
-        const int32_t rc = dispatch_from_keys(g, scores, assign, T, E, k, gates, expert_offsets, disp_token, disp_gate,
-                                              token_pos, ws, s);
-        return rc ? rc : finish(src);
-    }
     int32_t rc = gates_run(scores, assign, T, E, k, gates, s);
     if (rc) return rc;
     rc = dispatch_run(assign, gates, T, E, k, expert_offsets, disp_token, disp_gate, token_pos, ws, s);

@@ -13,9 +13,11 @@
 //                 wavefront is 64 tokens of one slot, whose proposals per expert it counts
 //   k_iter_scan   per expert: an expert with room for all its proposals needs no order; for the others the counts of
 //                 the blocks before, slot by slot, tell how many of a block's proposals there is room for
-// Rounds are enqueued two ahead of the one that runs; the first round without proposals ends them, and what is still
-// queued leaves at once.  Both kernels are bound by latency (6.2 and 4.8 us; 44032 tokens, 64 experts, top-2: ten steps in
-// 0.13 ms, with six launches and a wait for the host every other round 0.5 ms).
+// Once few pairs are left the step makes a list of them and a workgroup of the scan goes through all further rounds (iter_tail).
+// The next round is enqueued when the step of one has begun; the first round without proposals, or of which no expert has room left, or
+// the tail ends them, and what follows is enqueued while that runs.  All bound by latency: a step 6 to 8 us, a scan 5 to 7, the tail 26 for
+// five rounds.  A layer of 44032 tokens, 64 experts, top-2: 319 us with nine rounds of two launches, two of them enqueued ahead and what
+// follows behind the host's wait, 296 now; route_logits of 60 batches of 64 to 65536 tokens to 8 to 256 experts 15 % less on average.
 #include <algorithm>
 #include <climits>
 
@@ -32,6 +34,11 @@ struct IterState {
 };
 
 constexpr int kIterRows = 64, kScanThreads = 1024;
+// Pairs that one workgroup takes through the rounds that are left: as many as it proposes for in the time of a round of two launches
+// (a row takes 150 instructions of eight lanes, and one compute unit issues them all: with 2048 pairs 14493 tokens of 32 experts 193 us a
+// call, with 1024 173).
+constexpr int kTailMost = 1024, kTailEntries = 1 << 16, kTailSlots = 8192, kTailMaxK = 32, kTailMaxBlocks = 8192;
+constexpr int kIterEnds = INT_MAX;                        // progress: steps that have begun, or that the last one has
 constexpr int kIterWordProgress = 1, kIterWordFlow = 2, kIterWordRounds = 3, kIterWordOpen = 10, kIterWordTotal = 8;
 
 // Tables of the rounds, in the workspace (WorkspaceLayout::price_off).
@@ -39,7 +46,9 @@ struct IterArea {
     int load[2][kMaxE];        // tokens per expert before round r, in half r & 1
     int cnt[kMaxE];            // proposals of the last round
     int tot[8][kMaxE];         // ... of the round in progress, in eight partial counts
-    int np[4];                 // proposals of round r in all, in word r & 3
+    int any[4];                // whether there were proposals in round r, in word r & 3
+    int rej[4];                // ... those there was no room for
+    int room[4];               // ... whether an expert has room left
 };
 
 struct IterArgs {
@@ -53,6 +62,8 @@ struct IterArgs {
     int *bflow;                // ... pairs per block
     int T, E, k, C, n_wg;
     int ebits;
+    int tail;                  // pairs that one workgroup takes at most (-1: none)
+    int scan;                  // threads of a workgroup that a scan needs
 };
 
 // Best live expert of a row spread over a wavefront (lane l holds experts l, l+64, ...; bit c of `live` says
@@ -141,16 +152,21 @@ __global__ __launch_bounds__(1024) void k_iter_init(IterArea *ar)
     for (int i = threadIdx.x; i < (int)(sizeof(IterArea) / 4); i += 1024) p[i] = 0;
 }
 
-// Which step of the rounds this is: 0 they have ended before, 1 the first round without proposals lies behind, 2 go on.
-__device__ __forceinline__ int iter_phase(const IterArea *ar, int r)
+// Which step of the rounds this is.  No step is enqueued behind one that ends them.
+enum { kIterOn, kIterTail, kIterFull, kIterNone };        // ends them: in one workgroup, nobody has room, there were no proposals
+__device__ __forceinline__ int iter_phase(const IterArgs &a, int r, int last)
 {
-    if (r == 0 || ar->np[(r - 1) & 3] != 0) return 2;
-    return r == 1 || ar->np[(r - 2) & 3] != 0 ? 1 : 0;
+    const IterArea *ar = a.ar;
+    const int w = (r - 1) & 3, any = ar->any[w], rej = ar->rej[w], room = ar->room[w];      // (requested together)
+    if (r == 0) return kIterOn;
+    if (any == 0) return kIterNone;
+    if (last) return kIterOn;
+    return room == 0 ? kIterFull : rej <= a.tail ? kIterTail : kIterOn;
 }
 
 // G lanes own a token row, lane l columns (m >> 2) * 4G + 4l + (m & 3) for m < EPL (EPL >= 4), else l * EPL + m.
 template <int G, int EPL, typename Tile>
-__global__ __launch_bounds__(256) void k_iter_step(IterArgs a, int r, int last)
+__global__ __launch_bounds__(256) void k_iter_step(IterArgs a, int r, int last, int *host)
 {
     extern __shared__ int s_mem[];
     const int E = a.E, k = a.k, T = a.T;
@@ -167,18 +183,21 @@ __global__ __launch_bounds__(256) void k_iter_step(IterArgs a, int r, int last)
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int w = blockIdx.x, row0 = w * kIterRows;
     const int nr = T - row0 < kIterRows ? T - row0 : kIterRows;
-    const int phase = iter_phase(ar, r);
-    if (w == 0 && tid == 0) ar->np[r & 3] = 0;
-    if (phase == 0) return;
-    const bool final = phase == 1 || last;
+    const int phase = iter_phase(a, r, last);
+    if (w == 0 && tid == 0) {
+        ((volatile int *)host)[kIterWordProgress] = phase == kIterOn ? r + 1 : kIterEnds;
+        ar->any[r & 3] = ar->rej[r & 3] = ar->room[r & 3] = 0;
+    }
+    const bool final = phase != kIterOn || last;
     for (int i = tid; i < nr * k; i += 256) s_slot[i] = r < 2 ? -1 : a.assign[(size_t)row0 * k + i];
     if (r > 0)
         for (int e = tid; e < E; e += 256) {
             s_room[e] = a.C - ar->load[(r - 1) & 1][e];
             s_num[e] = ar->cnt[e];
         }
+    if (tid < kIterRows) s_queue[tid] = 0;        // kIterTail: the slots of a row that go on
     __syncthreads();
-    if (phase == 2 && r > 0) {
+    if (phase != kIterNone && r > 0) {
         for (int s = wv; s < k; s += 4) {
             const int e = lane < nr ? a.list[(size_t)s * T + row0 + lane] : -1;
             if (!__any(e >= 0)) continue;
@@ -194,13 +213,23 @@ __global__ __launch_bounds__(256) void k_iter_step(IterArgs a, int r, int last)
             if (take) {
                 s_slot[lane * k + s] = e;
                 if (r > 1) a.assign[(size_t)(row0 + lane) * k + s] = e;
-            }
+            } else if (phase == kIterTail && e >= 0) atomicOr((unsigned *)&s_queue[lane], 1u << s);
         }
         __syncthreads();
         if (r == 1)
             for (int i = tid; i < nr * k; i += 256) a.assign[(size_t)row0 * k + i] = s_slot[i];
     }
     if (final) {
+        if (phase == kIterTail && wv == 0) {
+            const unsigned mask = (unsigned)s_queue[lane];
+            const unsigned long long b = __ballot(mask != 0);
+            const int at = row0 + __popcll(b & ((1ull << lane) - 1));
+            if (mask) {
+                a.list[at] = row0 + lane;
+                if (k > 1) a.list[T + at] = (int)mask;
+            }
+            if (lane == 0) a.any[w] = __popcll(b);
+        }
         for (int e = tid; e < E; e += 256) s_cnt[e] = 0;
         __syncthreads();
         long long sum = 0;
@@ -335,48 +364,326 @@ __global__ __launch_bounds__(256) void k_iter_step(IterArgs a, int r, int last)
         if (s_num[e]) atomicAdd(&ar->tot[w & 7][e], s_num[e]);
 }
 
-template <typename Tile>
-__global__ __launch_bounds__(kScanThreads) void k_iter_scan(IterArgs a, int r, int last, int max_rounds, int *host)
+// What the blocks have reported and what came later, to the host (one workgroup; every thread comes with its share).
+__device__ __forceinline__ void iter_report(const IterArgs &a, long long sum, int flow, int rounds, int open, int *host)
 {
     __shared__ int s_w[kScanThreads / 64];
     __shared__ long long s_sum[kScanThreads / 64];
-    IterArea *ar = a.ar;
-    const int e = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int phase = iter_phase(ar, r);
-    if (phase == 0) return;
-    if (phase == 1 || last) {                      // the end: what the blocks have reported
-        if (e != 0) return;
-        long long sum = 0;
-        int flow = 0;
-        for (int i = tid; i < a.n_wg; i += blockDim.x) {
-            sum += a.bsum[i];
-            flow += a.bflow[i];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    for (int i = tid; i < a.n_wg; i += blockDim.x) {
+        sum += a.bsum[i];
+        flow += a.bflow[i];
+    }
+    for (int off = 32; off >= 1; off >>= 1) {
+        sum += __shfl_xor(sum, off);
+        flow += __shfl_xor(flow, off);
+    }
+    if (lane == 0) {
+        s_sum[wv] = sum;
+        s_w[wv] = flow;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        sum = 0;
+        flow = 0;
+        for (int x = 0; x < (int)blockDim.x >> 6; ++x) {
+            sum += s_sum[x];
+            flow += s_w[x];
         }
-        for (int off = 32; off >= 1; off >>= 1) {
-            sum += __shfl_xor(sum, off);
-            flow += __shfl_xor(flow, off);
+        *(volatile long long *)(host + kIterWordTotal) = sum;
+        ((volatile int *)host)[kIterWordFlow] = flow;
+        ((volatile int *)host)[kIterWordRounds] = rounds;
+        ((volatile int *)host)[kIterWordOpen] = open;
+        ((volatile int *)host)[0] = 1;              // (read when the stream has been waited for: a fence here took 3 us)
+    }
+}
+
+// The best but `skip` of a row's live columns (bit m of `live`: this lane's m-th), ties to the lower expert; -1 if there are no more.
+template <int G, int EPL>
+__device__ __forceinline__ int iter_best(const int (&v)[EPL], unsigned live, int lg, int ib, int skip)
+{
+    using RK = RowKeys<G, EPL>;
+    int lo = INT_MAX, hi = INT_MIN;
+#pragma unroll
+    for (int m = 0; m < EPL; ++m)
+        if ((live >> m) & 1) {
+            lo = v[m] < lo ? v[m] : lo;
+            hi = v[m] > hi ? v[m] : hi;
         }
-        if (lane == 0) {
-            s_sum[wv] = sum;
-            s_w[wv] = flow;
+    lo = ~group_max<G>(~lo);
+    hi = group_max<G>(hi);
+    if (hi < lo) return -1;
+    if ((((unsigned)hi - (unsigned)lo + 1) >> (32 - ib)) == 0 && (unsigned)hi - (unsigned)lo != ~0u) {       // (packed with their columns)
+        const unsigned cmask = (1u << ib) - 1;
+        unsigned key[EPL];
+#pragma unroll
+        for (int m = 0; m < EPL; ++m)
+            key[m] = (live >> m) & 1 ? ((unsigned)v[m] - (unsigned)lo + 1) << ib | (cmask - (unsigned)RK::col(m, lg)) : 0u;
+        unsigned cur = RK::first(key);
+        for (int x = 0; x < skip && cur != 0; ++x) {
+            const unsigned next = RK::below(key, cur);
+            cur = next < cur ? next : 0u;                  // (below the last one the search wraps around)
+        }
+        return cur != 0 ? (int)(cmask - (cur & cmask)) : -1;
+    }
+    for (int x = 0;; ++x) {
+        int best = INT_MIN;
+#pragma unroll
+        for (int m = 0; m < EPL; ++m)
+            if (((live >> m) & 1) && v[m] > best) best = v[m];
+        best = group_max<G>(best);
+        int low = INT_MAX;
+#pragma unroll
+        for (int m = EPL - 1; m >= 0; --m)
+            if (((live >> m) & 1) && v[m] == best) low = RK::col(m, lg);
+        low = ~group_max<G>(~low);
+        if (low == INT_MAX) return -1;
+        if (x == skip) return low;
+        const int l = EPL >= 4 ? (low >> 2) & (G - 1) : low / EPL, m = EPL >= 4 ? low / (4 * G) * 4 + (low & 3) : low % EPL;
+        if (l == lg) live &= ~(1u << m);
+    }
+}
+
+// LDS of the tail, in words: tokens, open slots and slots of its rows, room and proposals per expert, its pairs twice, their proposals
+// (half words), proposals per (64 pairs, expert), before that open slots per (64 rows, slot).  The blocks' first rows lie where the pairs go.
+inline int tail_words(int most, int E, int k, int n_wg)
+{
+    const int tiles = (most + 63) / 64, pairs = 2 * most + (most + 1) / 2, tab = tiles * std::max(E, kTailMaxK) + 1;
+    return (2 + k) * most + 2 * E + std::max(pairs + tab, n_wg + 1);
+}
+
+// Rounds r, r + 1, ... of the pairs the step has listed, in one workgroup: round by round a proposal of every pair, by G lanes each; a
+// rank among the proposals for an expert without room for all of them; the pairs that were turned away go on, in their order (slot,
+// token).  A pair that finds nobody to ask drops out: from round to round a token's open slots do not lose more slots before it than
+// experts it could ask.  Bound by latency, 2 us a round of few pairs; 44032 tokens of 64 experts, top-2: four rounds of 672 pairs and less.
+template <int G, int EPL>
+__device__ __forceinline__ void iter_tail(const IterArgs &a, int r, int max_rounds, int *host)
+{
+    using RK = RowKeys<G, EPL>;
+    extern __shared__ int s_mem[];
+    __shared__ int s_w[kScanThreads / 64], s_tile[kTailMost / 64], s_flag[2];
+    constexpr int NT = kScanThreads, NW = NT / 64, TILES = kTailMost / 64 / NW;      // tiles of 64 pairs a wavefront
+    const int E = a.E, k = a.k, N = a.tail, tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int *s_tok = s_mem, *s_slot = s_tok + 2 * N, *s_room = s_slot + k * N, *s_cnt = s_room + E, *s_pre = s_cnt + E;
+    unsigned *s_open = (unsigned *)s_tok + N, *s_ent = (unsigned *)s_pre, *s_ent2 = s_ent + N;
+    unsigned short *s_prop = (unsigned short *)(s_ent2 + N);
+    int *s_tab = s_pre + 2 * N + (N + 1) / 2;
+    constexpr unsigned short none = 0xffff;
+    auto before_me = [&](int v, int &total) {            // exclusive sum over the workgroup (two barriers)
+        int inc = v;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(inc, off);
+            if (lane >= off) inc += o;
+        }
+        if (lane == 63) s_w[wv] = inc;
+        __syncthreads();
+        int base = 0, all = 0;
+        for (int x = 0; x < NW; ++x) {
+            const int y = s_w[x];
+            base += x < wv ? y : 0;
+            all += y;
         }
         __syncthreads();
-        if (tid == 0) {
-            sum = 0;
-            flow = 0;
-            for (int x = 0; x < (int)blockDim.x >> 6; ++x) {
-                sum += s_sum[x];
-                flow += s_w[x];
-            }
-            *(volatile long long *)(host + kIterWordTotal) = sum;
-            ((volatile int *)host)[kIterWordFlow] = flow;
-            ((volatile int *)host)[kIterWordRounds] = phase == 1 ? (r >= 2 ? r - 2 : 0) : r - 1;
-            ((volatile int *)host)[kIterWordOpen] = phase == 2 && max_rounds > 0;
-            __threadfence_system();
-            ((volatile int *)host)[0] = 1;
+        total = all;
+        return base + inc - v;
+    };
+    // the rows, in token order
+    int H = 0;
+    for (int w0 = 0; w0 < a.n_wg; w0 += NT) {
+        const int w = w0 + tid, c = w < a.n_wg ? a.any[w] : 0;
+        int all;
+        const int at = H + before_me(c, all);
+        if (w < a.n_wg) s_pre[w] = at;
+        H += all;
+    }
+    if (tid == 0) s_pre[a.n_wg] = H;
+    for (int e = tid; e < E; e += NT) s_room[e] = a.C - a.ar->load[r & 1][e];
+    if (tid < 2) s_flag[tid] = -1;
+    __syncthreads();
+    H = H < N ? H : N;                                   // (never more)
+    for (int h = tid; h < H; h += NT) {
+        int lo = 0, hi = a.n_wg;                         // the last block whose first row is not behind h
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (s_pre[mid] <= h) lo = mid;
+            else hi = mid;
         }
+        const int at = lo * kIterRows + (h - s_pre[lo]);
+        s_tok[h] = a.list[at];
+        s_open[h] = k > 1 ? (unsigned)a.list[a.T + at] : 1u;
+    }
+    __syncthreads();
+    for (int i = tid; i < H * k; i += NT) s_slot[i] = a.assign[(size_t)s_tok[i / k] * k + i % k];
+    // their pairs, by slot, then by token
+    const int chunks = (H + 63) / 64;
+    for (int c = wv; c < chunks; c += NW) {
+        const unsigned m = c * 64 + lane < H ? s_open[c * 64 + lane] : 0u;
+        for (int s = 0; s < k; ++s) {
+            const int cnt = __popcll(__ballot((m >> s) & 1u));
+            if (lane == 0) s_tab[s * chunks + c] = cnt;
+        }
+    }
+    __syncthreads();
+    int n = 0;
+    for (int i0 = 0; i0 < k * chunks; i0 += NT) {
+        const int i = i0 + tid, c = i < k * chunks ? s_tab[i] : 0;
+        int all;
+        const int at = n + before_me(c, all);
+        if (i < k * chunks) s_tab[i] = at;
+        n += all;
+    }
+    __syncthreads();
+    for (int c = wv; c < chunks; c += NW) {
+        const int row = c * 64 + lane;
+        const unsigned m = row < H ? s_open[row] : 0u;
+        for (int s = 0; s < k; ++s) {
+            const unsigned long long b = __ballot((m >> s) & 1u);
+            const int at = s_tab[s * chunks + c] + __popcll(b & ((1ull << lane) - 1));
+            if (((m >> s) & 1u) && at < N) s_ent[at] = (unsigned)(row << 8 | s);
+        }
+    }
+    n = n < N ? n : N;
+    const int lg = tid & (G - 1), grp = tid / G;
+    const bool vec = EPL >= 4 && (E & 3) == 0 && ((size_t)a.q & 15) == 0;
+    const int ib = a.ebits > 0 ? a.ebits : 1;
+    long long sum = 0;
+    int flow = 0, rounds = 0, open = 0, got[TILES] = {};          // got: rewards on their way
+    for (int round = r;; ++round) {
+        for (int e = tid; e < E; e += NT) s_cnt[e] = 0;
+        __syncthreads();
+        unsigned roomy = 0;
+#pragma unroll
+        for (int m = 0; m < EPL; ++m)
+            if (RK::col(m, lg) < E && s_room[RK::col(m, lg)] > 0) roomy |= 1u << m;
+        int nx[EPL];                                     // the next pair's row is on its way
+        if (grp < n) RK::load(a.q + (size_t)s_tok[s_ent[grp] >> 8] * E, E, vec, lg, nx);
+        for (int i = grp; i < n; i += NT / G) {
+            const unsigned ent = s_ent[i];
+            const int row = (int)(ent >> 8), s = (int)(ent & 255);
+            const int skip = __popc(s_open[row] & ((1u << s) - 1));          // open slots before this one take the best first
+            int v[EPL];
+#pragma unroll
+            for (int m = 0; m < EPL; ++m) v[m] = nx[m];
+            if (i + NT / G < n) RK::load(a.q + (size_t)s_tok[s_ent[i + NT / G] >> 8] * E, E, vec, lg, nx);
+            unsigned live = roomy;
+            for (int x = 0; x < k; ++x) {
+                const int e = s_slot[row * k + x];
+                if (e < 0) continue;
+                const int l = EPL >= 4 ? (e >> 2) & (G - 1) : e / EPL, m = EPL >= 4 ? e / (4 * G) * 4 + (e & 3) : e % EPL;
+                if (l == lg) live &= ~(1u << m);
+            }
+            const int best = iter_best<G, EPL>(v, live, lg, ib, skip);
+            if (lg == 0) {
+                s_prop[i] = best < 0 ? none : (unsigned short)best;
+                if (best >= 0) atomicAdd(&s_cnt[best], 1);
+            }
+        }
+        __syncthreads();
+        for (int e = tid; e < E; e += NT) {
+            if (s_cnt[e] > 0) s_flag[0] = round;
+            if (s_cnt[e] > s_room[e]) s_flag[1] = round;
+        }
+        __syncthreads();
+        if (s_flag[0] != round) {
+            rounds = round - 1;
+            break;
+        }
+        const int tiles = (n + 63) / 64;
+        const bool ranks = s_flag[1] == round;
+        int prop[TILES];
+        unsigned long long same[TILES];
+#pragma unroll
+        for (int j = 0; j < TILES; ++j) {
+            const int t = wv + j * NW, i = t * 64 + lane;
+            prop[j] = t < tiles && i < n && s_prop[i] != none ? (int)s_prop[i] : -1;
+            same[j] = 0;
+            if (!ranks || t >= tiles) continue;
+            same[j] = same_expert(prop[j], a.ebits);
+            for (int e = lane; e < E; e += 64) s_tab[t * E + e] = 0;
+            wave_lds_sync();
+            if (prop[j] >= 0 && lane == __ffsll((long long)same[j]) - 1) s_tab[t * E + prop[j]] = __popcll(same[j]);
+        }
+        if (ranks) __syncthreads();
+        bool take[TILES];
+        unsigned ent[TILES];
+#pragma unroll
+        for (int j = 0; j < TILES; ++j) {
+            sum += got[j];
+            got[j] = 0;
+        }
+#pragma unroll
+        for (int j = 0; j < TILES; ++j) {
+            const int t = wv + j * NW, e = prop[j];
+            take[j] = e >= 0;
+            ent[j] = 0;
+            if (t >= tiles) continue;
+            if (e >= 0) {
+                ent[j] = s_ent[t * 64 + lane];
+                const int room = s_room[e];
+                if (s_cnt[e] > room) {
+                    int rank = __popcll(same[j] & ((1ull << lane) - 1));
+                    for (int x = 0; x < t; ++x) rank += s_tab[x * E + e];
+                    take[j] = rank < room;
+                }
+                if (take[j]) {
+                    const int row = (int)(ent[j] >> 8), s = (int)(ent[j] & 255), tok = s_tok[row];
+                    s_slot[row * k + s] = a.assign[(size_t)tok * k + s] = e;
+                    atomicAnd(&s_open[row], ~(1u << s));
+                    atomicAdd(&a.wcnt[(size_t)(tok / kIterRows) * E + e], 1);
+                    got[j] = a.q[(size_t)tok * E + e];
+                    ++flow;
+                }
+            }
+            const int keep = __popcll(__ballot(e >= 0 && !take[j]));
+            if (lane == 0) s_tile[t] = keep;
+        }
+        __syncthreads();
+        for (int e = tid; e < E; e += NT) s_room[e] -= s_cnt[e] < s_room[e] ? s_cnt[e] : s_room[e];
+        int left = 0, at[TILES] = {};
+        for (int t = 0; t < tiles; ++t) {
+#pragma unroll
+            for (int j = 0; j < TILES; ++j)
+                if (t == wv + j * NW) at[j] = left;
+            left += s_tile[t];
+        }
+#pragma unroll
+        for (int j = 0; j < TILES; ++j) {
+            const bool go_on = prop[j] >= 0 && !take[j];
+            const unsigned long long b = __ballot(go_on);
+            if (go_on) s_ent2[at[j] + __popcll(b & ((1ull << lane) - 1))] = ent[j];
+        }
+        unsigned *x = s_ent;
+        s_ent = s_ent2;
+        s_ent2 = x;
+        n = left;
+        if (round >= max_rounds) {
+            rounds = max_rounds;
+            open = max_rounds > 0;
+            break;
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < TILES; ++j) sum += got[j];
+    iter_report(a, sum, flow, rounds, open, host);
+}
+
+template <int G, int EPL, typename Tile>
+__global__ __launch_bounds__(kScanThreads) void k_iter_scan(IterArgs a, int r, int last, int max_rounds, int *host)
+{
+    __shared__ int s_w[kScanThreads / 64];
+    IterArea *ar = a.ar;
+    const int e = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int phase = iter_phase(a, r, last);
+    if (phase == kIterTail) {
+        if (e == 0) iter_tail<G, EPL>(a, r, max_rounds, host);
         return;
     }
+    if (phase != kIterOn || last) {                // the end
+        if (e == 0) iter_report(a, 0, 0, phase == kIterNone ? (r >= 2 ? r - 2 : 0) : r - 1, phase == kIterOn && max_rounds > 0, host);
+        return;
+    }
+    if (tid >= a.scan) return;                     // (whole wavefronts; the barriers do not wait for them)
     int c = 0;
 #pragma unroll
     for (int i = 0; i < 8; ++i) c += ar->tot[i][e];
@@ -386,15 +693,16 @@ __global__ __launch_bounds__(kScanThreads) void k_iter_scan(IterArgs a, int r, i
     if (tid == 0) {
         ar->load[(r + 1) & 1][e] = load + (c < room ? c : room);
         ar->cnt[e] = c;
-        if (c > 0) atomicAdd(&ar->np[r & 3], c);
-        if (e == 0) ((volatile int *)host)[kIterWordProgress] = r + 1;
+        if (c > 0) ar->any[r & 3] = 1;
+        if (c < room) ar->room[r & 3] = 1;
+        if (c > room) atomicAdd(&ar->rej[r & 3], c - (room > 0 ? room : 0));
     }
     if (c <= room || room <= 0) return;
     // eight tiles per thread and step, all on their way together
     const int n = a.k * a.n_wg;
     Tile *tiles = (Tile *)a.tiles;
     int before = 0;
-    for (int b0 = 0; b0 < n; b0 += 8 * blockDim.x) {
+    for (int b0 = 0; b0 < n; b0 += 8 * a.scan) {
         const int t0 = b0 + 8 * tid;
         int x[8], sum = 0;
 #pragma unroll
@@ -411,7 +719,7 @@ __global__ __launch_bounds__(kScanThreads) void k_iter_scan(IterArgs a, int r, i
         if (lane == 63) s_w[wv] = inc;
         __syncthreads();
         int run = before + inc - sum;
-        for (int v = 0; v < (int)blockDim.x >> 6; ++v) {
+        for (int v = 0; v < (int)a.scan >> 6; ++v) {
             if (v < wv) run += s_w[v];
             before += s_w[v];
         }
@@ -496,7 +804,7 @@ int32_t assign_total_run(const int32_t *q, const int32_t *assign, int T, int E, 
 }
 
 int32_t iter_run(const int32_t *q, int T, int E, int k, int C, int max_rounds, int32_t *assign, int64_t *total,
-                 int32_t *flow, int32_t *rounds, char *ws, hipStream_t s)
+                 int32_t *flow, int32_t *rounds, char *ws, hipStream_t s, IterAfter after, void *after_ctx)
 {
     WorkspaceLayout L = workspace_layout(T, E, k);
     IterArgs a;
@@ -534,47 +842,57 @@ int32_t iter_run(const int32_t *q, int T, int E, int k, int C, int max_rounds, i
     while (G * 16 < E) G *= 2;
     while (G * EPL < E) EPL *= 2;
     const size_t shm = sizeof(int) * ((size_t)2 * kIterRows * k + 6 * (size_t)E);
-    const int threads = std::min(kScanThreads, std::max(64, (k * a.n_wg + 511) / 512 * 64));     // eight tiles each
+    a.tail = k <= kTailMaxK && a.n_wg <= kTailMaxBlocks ? std::min({kTailMost, kTailEntries / E, kTailSlots / k}) : -1;
+    a.scan = std::min(kScanThreads, std::max(64, (k * a.n_wg + 511) / 512 * 64));       // eight tiles each
+    const int threads = a.tail > 0 ? kScanThreads : a.scan;
+    const size_t tail_shm = a.tail > 0 ? sizeof(int) * (size_t)tail_words(a.tail, E, k, a.n_wg) : 0;
     hipLaunchKernelGGL(k_iter_init, dim3(1), dim3(1024), 0, s, a.ar);
-    for (int r = 0; !hw[0]; ++r) {
+    bool ends = false;
+    for (int r = 0; !ends; ++r) {
         const int last = r > max_rounds ? 1 : 0;
-#define MS_I(GG, PP) hipLaunchKernelGGL((k_iter_step<GG, PP, int>), dim3(a.n_wg), dim3(256), shm, s, a, r, last)
+#define MS_IT(GG, PP, TT)                                                                                             \
+    do {                                                                                                              \
+        hipLaunchKernelGGL((k_iter_step<GG, PP, TT>), dim3(a.n_wg), dim3(256), shm, s, a, r, last, host_dev);         \
+        hipLaunchKernelGGL((k_iter_scan<GG, PP, TT>), dim3(E), dim3(threads), tail_shm, s, a, r, last, max_rounds, host_dev); \
+    } while (0)
 #define MS_IB(GG)                                                                                                     \
     do {                                                                                                              \
-        if (words) MS_I(GG, 16);                                                                                      \
-        else hipLaunchKernelGGL((k_iter_step<GG, 16, unsigned char>), dim3(a.n_wg), dim3(256), shm, s, a, r, last);   \
+        if (words) MS_IT(GG, 16, int);                                                                                \
+        else MS_IT(GG, 16, unsigned char);                                                                            \
     } while (0)
         if (G == 8) {
-            if (EPL == 1) MS_I(8, 1);
-            else if (EPL == 2) MS_I(8, 2);
-            else if (EPL == 4) MS_I(8, 4);
-            else if (EPL == 8) MS_I(8, 8);
-            else MS_I(8, 16);
+            if (EPL == 1) MS_IT(8, 1, int);
+            else if (EPL == 2) MS_IT(8, 2, int);
+            else if (EPL == 4) MS_IT(8, 4, int);
+            else if (EPL == 8) MS_IT(8, 8, int);
+            else MS_IT(8, 16, int);
         } else if (G == 16) MS_IB(16);
         else if (G == 32) MS_IB(32);
         else MS_IB(64);
 #undef MS_IB
-#undef MS_I
-        hipLaunchKernelGGL(words ? k_iter_scan<int> : k_iter_scan<unsigned char>, dim3(E), dim3(threads), 0, s, a, r, last, max_rounds,
-                           host_dev);
+#undef MS_IT
         if (hipGetLastError() != hipSuccess) {
             (void)hipStreamSynchronize(s);
             return MAXSCORE_ERR_HIP;
         }
-        // two rounds stay queued behind the one that runs; the stream is looked at now and then, so that an error ends
-        // the wait
-        for (unsigned spin = 1; !hw[0] && (last || r + 1 - hw[kIterWordProgress] > 2); ++spin) {
-            if ((spin & 2047) == 0) {
-                const hipError_t e = hipStreamQuery(s);
-                if (e != hipErrorNotReady && !hw[0] && (e != hipSuccess || last)) {
-                    (void)hipStreamSynchronize(s);
-                    if (hw[0]) break;
-                    return MAXSCORE_ERR_HIP;
-                }
+        // The next round is enqueued when the step of this one has begun, unless that is the last: a launch that is queued in vain costs
+        // 2 us, and the host is ready before this round ends.  The stream is looked at now and then, so that an error ends the wait.
+        for (unsigned spin = 1;; ++spin) {
+            const int begun = hw[kIterWordProgress];
+            ends = last || begun == kIterEnds;
+            if (ends || begun > r) break;
+            if ((spin & 2047) == 0 && hipStreamQuery(s) != hipErrorNotReady && hw[kIterWordProgress] == begun) {
+                (void)hipStreamSynchronize(s);
+                return MAXSCORE_ERR_HIP;
             }
             __builtin_ia32_pause();
         }
     }
+    // what follows is enqueued while the last round runs
+    const int32_t arc = after ? after(after_ctx, s) : MAXSCORE_OK;
+    MS_HIP(hipStreamSynchronize(s));
+    if (arc) return arc;
+    if (!hw[0]) return MAXSCORE_ERR_HIP;
     if (total) *total = *(volatile long long *)(host + kIterWordTotal);
     if (flow) *flow = hw[kIterWordFlow];
     if (rounds) *rounds = hw[kIterWordRounds];

@@ -54,3 +54,21 @@ def test_many_slots_and_experts(ms, T, E, k, C):
     out = ms.assign_iter_i32(torch.from_numpy(q.astype(np.int32)).cuda(), k, C, allow_not_converged=True)
     assert np.array_equal(out["assign"].cpu().numpy(), ref["assign"])
     assert (out["total"], out["flow"], out["rounds"]) == (ref["total"], ref["flow"], ref["rounds"])
+
+
+@pytest.mark.parametrize("T,E,k,C,hi", [
+    (3000, 32, 32, 2900, 1 << 20), (2000, 33, 32, 2000, 5),          # as many slots as the last rounds' workgroup takes
+    (6000, 8, 4, 2900, 1 << 20), (6000, 8, 4, 3000, 4),              # tokens whose slots run out of experts to ask
+    (66, 2, 1, 33, 3), (130, 16, 2, 9, 1 << 10), (20000, 4, 1, 5001, 2),      # one round of all tokens, then the last ones
+    (4100, 512, 2, 17, 1 << 20), (4100, 1024, 3, 13, 1 << 16), (40000, 64, 2, 1250, 1 << 29),        # the fewest pairs, keys that do not pack
+])
+@pytest.mark.parametrize("max_rounds", [-1, 2, 4])
+def test_last_rounds(ms, T, E, k, C, hi, max_rounds):
+    """The rounds one workgroup goes through by itself: uneven experts, so that many rounds follow, and rounds that are cut short."""
+    print(f"iter last rounds T={T} E={E} k={k} C={C} hi={hi} max_rounds={max_rounds}", flush=True)
+    rng = np.random.default_rng(T + E + k + hi)
+    q = rng.integers(0, hi, (T, E)) + (rng.random(E) ** 3 * hi).astype(np.int64)
+    ref = oracle.iter_reroute(q, k, C, max_rounds=max_rounds if max_rounds >= 0 else None)
+    out = ms.assign_iter_i32(torch.from_numpy(q.astype(np.int32)).cuda(), k, C, max_rounds=max_rounds, allow_not_converged=True)
+    assert np.array_equal(out["assign"].cpu().numpy(), ref["assign"])
+    assert (out["total"], out["flow"], out["rounds"]) == (ref["total"], ref["flow"], ref["rounds"])
