@@ -351,6 +351,13 @@ int32_t maxscore_route_scores(const float *scores, int32_t T, int32_t E, int32_t
                               int32_t *token_pos, int64_t *prices, maxscore_stats *stats, void *workspace,
                               size_t workspace_bytes, void *stream);
 
+/* a4..a6 from scores and the rewards made of them (of maxscore_router_softtopk or maxscore_softtopk): what
+ * maxscore_route_logits does once it has these.  Synchronises `stream`. */
+int32_t maxscore_route_rewards(const float *scores, const int32_t *q, int32_t T, int32_t E, int32_t k, int32_t C,
+                               const maxscore_opts *opts, int32_t *assign, float *gates, int32_t *expert_offsets,
+                               int32_t *disp_token, float *disp_gate, int32_t *token_pos, int64_t *prices,
+                               maxscore_stats *stats, void *workspace, size_t workspace_bytes, void *stream);
+
 /* a1 + a2 + a3: scores[T,E] and/or q[T,E] from x and W_g (Eq. 2, then Eq. 6 and the rounding), in one kernel where
  * maxscore_route_xw can do so (same conditions, `workspace` as for maxscore_router_logits; logits_out may then be
  * NULL), else by the two kernels of maxscore_router_logits and maxscore_softtopk through logits_out (required

@@ -91,6 +91,8 @@ _SIGS = {
     "maxscore_route_scores": (ctypes.c_int32, [ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32,
                                                ctypes.c_int32, ctypes.c_void_p] + [ctypes.c_void_p] * 10 +
                               [ctypes.c_size_t, ctypes.c_void_p]),
+    "maxscore_route_rewards": (ctypes.c_int32, [ctypes.c_void_p] * 2 + [ctypes.c_int32] * 4 + [ctypes.c_void_p] * 10 +
+                               [ctypes.c_size_t, ctypes.c_void_p]),
     "maxscore_route_xw": (ctypes.c_int32, [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32,
                                            ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32,
                                            ctypes.c_int32, ctypes.c_void_p] + [ctypes.c_void_p] * 12 +
@@ -535,10 +537,15 @@ def combine(expert_out, assign, token_pos, gate, out=None):
     return out
 
 
-def _route_outputs(T, E, k, dev):
+def _score_outputs(T, E, dev):
     torch = _torch()
     return dict(scores=torch.empty((T, E), dtype=torch.float32, device=dev),
-                q=torch.empty((T, E), dtype=torch.int32, device=dev),
+                q=torch.empty((T, E), dtype=torch.int32, device=dev))
+
+
+def _route_outputs(T, E, k, dev, scored=None):
+    torch = _torch()
+    return dict(scored if scored is not None else _score_outputs(T, E, dev),
                 assign=torch.empty((T, k), dtype=torch.int32, device=dev),
                 gates=torch.empty((T, k), dtype=torch.float32, device=dev),
                 expert_offsets=torch.empty(E + 1, dtype=torch.int32, device=dev),
@@ -600,12 +607,31 @@ def route_xw(x, W, bias, k: int, C: int, t: float = 1.0, quant_shift: int = 20, 
     T, d = x.shape
     E = W.shape[1]
     assert W.shape[0] == d and x.is_contiguous() and W.is_contiguous() and x.dtype == W.dtype
-    o = out if out is not None else _route_outputs(T, E, k, x.device)
-    if "logits" not in o:
-        o["logits"] = torch.empty((T, E), dtype=torch.float32, device=x.device) if want_logits else None
-    ws, need = _workspace(T, E, k, C, x.device, d)
     stats = Stats()
     opts = _opts(t, quant_shift, max_rounds, eps_div, assignment)
+    if out is None:
+        # The projection is under way while the other outputs are allocated (eight of them, 10 us).
+        scored = _score_outputs(T, E, x.device)
+        scored["logits"] = torch.empty((T, E), dtype=torch.float32, device=x.device) if want_logits else None
+        ws, need = _workspace(T, E, k, C, x.device, d)
+        rc = load_library().maxscore_router_softtopk(
+            _ptr(x), _ptr(W), _ptr(bias), _in_dtype(x), T, d, E, k, t, quant_shift, _ptr(scored["logits"]), _ptr(scored["scores"]),
+            _ptr(scored["q"]), _ptr(ws), need, _stream())
+        o = _route_outputs(T, E, k, x.device, scored)
+        if rc == OK:
+            rc = load_library().maxscore_route_rewards(
+                _ptr(o["scores"]), _ptr(o["q"]), T, E, k, C, ctypes.byref(opts), _ptr(o["assign"]), _ptr(o["gates"]),
+                _ptr(o["expert_offsets"]), _ptr(o["disp_token"]), _ptr(o["disp_gate"]), _ptr(o["token_pos"]), _ptr(o["prices"]),
+                ctypes.byref(stats), _ptr(ws), need, _stream())
+            _check(rc, "maxscore_route_xw")
+            o["stats"] = stats.as_dict()
+            return o
+        # (refused: the one call below says why)
+    else:
+        o = out
+        if "logits" not in o:
+            o["logits"] = torch.empty((T, E), dtype=torch.float32, device=x.device) if want_logits else None
+        ws, need = _workspace(T, E, k, C, x.device, d)
     rc = load_library().maxscore_route_xw(
         _ptr(x), _ptr(W), _ptr(bias), _in_dtype(x), T, d, E, k, C, ctypes.byref(opts), _ptr(o["logits"]),
         _ptr(o["scores"]), _ptr(o["q"]), _ptr(o["assign"]), _ptr(o["gates"]), _ptr(o["expert_offsets"]),

@@ -454,6 +454,20 @@ int32_t maxscore_route_scores(const float *scores, int32_t T, int32_t E, int32_t
                               token_pos, prices, stats, (char *)workspace, workspace_bytes, s);
 }
 
+int32_t maxscore_route_rewards(const float *scores, const int32_t *q, int32_t T, int32_t E, int32_t k, int32_t C,
+                               const maxscore_opts *opts, int32_t *assign, float *gates, int32_t *expert_offsets,
+                               int32_t *disp_token, float *disp_gate, int32_t *token_pos, int64_t *prices,
+                               maxscore_stats *stats, void *workspace, size_t workspace_bytes, void *stream)
+{
+    if (!scores || !q || !assign || !gates || !expert_offsets || !disp_token || !disp_gate || !token_pos) return MAXSCORE_ERR_NULL;
+    const maxscore_opts o = resolve(opts);
+    const int32_t rc = route_check(T, E, k, C, o, workspace, workspace_bytes);
+    if (rc) return rc;
+    if (stats) std::memset(stats, 0, sizeof(*stats));
+    return route_from_rewards(scores, q, T, E, k, C, o, assign, gates, expert_offsets, disp_token, disp_gate, token_pos, prices,
+                              stats, (char *)workspace, workspace_bytes, (hipStream_t)stream);
+}
+
 int32_t maxscore_route_logits(const float *logits, int32_t T, int32_t E, int32_t k, int32_t C,
                               const maxscore_opts *opts, float *scores_out, int32_t *q_out, int32_t *assign,
                               float *gates, int32_t *expert_offsets, int32_t *disp_token, float *disp_gate,

@@ -80,6 +80,18 @@ def test_argument_errors_are_found_on_the_host(lib):
         assert len(lib.maxscore_status_string(code)) > 1
 
 
+def test_routing_from_rewards_checks_its_arguments(lib):
+    one, null = ctypes.c_void_p(256), None
+    args = dict(scores=one, q=one, T=8, E=4, k=2, C=4, opts=null, assign=one, gates=one, offsets=one, tok=one, gate=one, pos=one, prices=null,
+                stats=null, ws=one, need=1 << 24, stream=null)
+    call = lambda **kw: lib.maxscore_route_rewards(*dict(args, **kw).values())
+    for name in ("scores", "q", "assign", "gates", "offsets", "tok", "gate", "pos"):
+        assert call(**{name: null}) == -1, name
+    assert call(k=5) == -2 and call(C=0) == -2 and call(T=0) == -2
+    assert call(ws=null) == -3 and call(ws=ctypes.c_void_p(260)) == -3 and call(need=16) == -3
+    assert call(T=40, E=1000, k=30, C=1) == -6
+
+
 def test_compute_without_gpu_fails_loudly():
     import torch
     if torch.cuda.is_available():

@@ -101,3 +101,31 @@ def test_route_xw_without_logits_at_the_headline_size(ms):
     assert torch.equal(logits, a["logits"])
     s2, q2 = ms.softtopk(logits, r.k, r.t)
     assert torch.equal(s2, a["scores"]) and torch.equal(q2, a["q"])
+
+
+@pytest.mark.parametrize("T,d,E,k,dtype", [(100, 64, 32, 2, torch.bfloat16), (3000, 256, 64, 8, torch.bfloat16), (777, 100, 24, 3, torch.float32),
+                                           (500, 66, 130, 2, torch.bfloat16)])
+@pytest.mark.parametrize("assignment", ["exact", "iter"])
+def test_outputs_given_and_made(ms, T, d, E, k, dtype, assignment):
+    """route_xw with its own outputs (projection first, the rest in a second call) and with the caller's (one call): the same."""
+    print(f"route_xw outputs T={T} d={d} E={E} k={k} {dtype} {assignment}", flush=True)
+    gen = torch.Generator().manual_seed(T)
+    x = torch.randn(T, d, generator=gen).to(dtype).cuda()
+    W = (torch.randn(d, E, generator=gen) / d ** 0.5).to(dtype).cuda()
+    C = -(-T * k // E)
+    made = ms.route_xw(x, W, None, k, C, assignment=assignment)
+    given = {n: torch.empty_like(t) for n, t in made.items() if n != "stats"}
+    r = ms.route_xw(x, W, None, k, C, assignment=assignment, out=given)
+    n = made["stats"]["flow_value"]
+    for name in given:
+        if name == "prices" and assignment == "iter":
+            continue
+        a, b = made[name], r[name]
+        if name in ("disp_token", "disp_gate"):
+            a, b = a[:n], b[:n]
+        assert torch.equal(a, b), name
+    assert made["stats"]["total_score_q"] == r["stats"]["total_score_q"]
+    for bad in (dict(C=0), dict(k=E + 1), dict(t=-1.0)):
+        with pytest.raises(ms.MaxScoreError) as e:
+            ms.route_xw(x, W, None, **dict(dict(k=k, C=C, assignment=assignment), **bad))
+        assert e.value.code == -2
