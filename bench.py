@@ -45,10 +45,10 @@ def solver_roofline(st: dict, T: int, E: int, k: int, solve_ms: float, gd_ms: fl
     # assignment and scores at the assigned pairs; gates, the two dispatch lists and the positions
     gd_bytes = T * k * (4 + 4 + 4) + T * k * (4 + 4) + T * k * 12 + 4 * (E + 1)
     if price:
-        # a pass reads the rewards (the first two of a large batch 8192 rows of them); the last one, which is not among the
+        # a pass reads the rewards (the first two of 131072 tokens and more 8192 rows of them); the last one, which is not among the
         # rounds, reads them and writes the assignment and the counts per block; the few thousand rows that the search
         # reads are not counted
-        sampled = 2 if T >= 2 * 8192 else 0
+        sampled = 2 if T >= 16 * 8192 else 0
         passes = [8192 * E * 4] * min(sampled, st["rounds"]) + [q_bytes] * max(st["rounds"] - sampled, 0)
         solver_bytes = sum(passes) + q_bytes + pair_bytes + count_bytes
         first, second = ("k_price", sum(passes) / max(len(passes), 1)), ("k_price_update", None)

@@ -64,12 +64,21 @@ constexpr int kBlockArcs = 512;                   // ... of one block, gathered 
 constexpr int kFThreads = 1024, kUThreads = 1024;
 constexpr int kFirstWindow = 1 << 22;             // margins of the first pass: up to four times a score of 1
 constexpr int kSampleRows = 8192;
+// A sample of one row in kSampleFrom and less.  What a sample leaves is its own noise: the first pass over all rows finds nearly as many
+// tokens too many as the second one behind a full first one (16384 tokens of 64 experts: 1000), so that it has to save two passes to be worth
+// it.  Without and with two passes over samples before the others, solves of 16384 to 32768 tokens take 0.84 to 0.86, to 65536 0.82 to
+// 0.86, to 131072 0.79 to 0.94, to 185000 1.01, to 262144 1.06, beyond 1.16 to 1.19 of the time (230 batches to 8 to 256 experts).
+constexpr int kSampleFrom = 16;
 constexpr int kArcsPerExpert = 16, kArcsWanted = 4500, kArcsMost = 5500;
 constexpr int kMaxBound = (1 << 21) - 1;
 constexpr int kAllArcs = 4000;                    // problems with this few exchanges in all are searched with all of them
 constexpr int kEnough = 3, kWorst = 2;            // the passes end when a third of a token per expert (a sixth
                                                   // beyond 128, where searches take longer) is too many, at
                                                   // no expert more than two (its tokens leave one search at a time)
+// Steps are shortened by an eighth when few tokens are too many: experts that chase each other's last tokens settle sooner.  Of 500 drawn
+// batches (64 to 65536 tokens, 8 to 256 experts) solves took 3.6 % longer with three eighths (6 % at 64 and 128 experts, 1 % at 8 and 16); with a sixth,
+// a sixteenth or none within 1 % of an eighth; with half a token per expert left to the search 0.5 % longer.
+constexpr int kDamp = 8;
 constexpr int kLevelPairs = 4;                    // exchanges of a row that the common step looks at
 constexpr int kSmallEntries = 1 << 16;            // rewards of a batch that one workgroup passes over by itself
 constexpr int kSmallThreads = 4096;               // ... with this many lanes at work in all
@@ -350,13 +359,12 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
         if (m2.excess == 0) m2.bound = 2;                // nothing to move
         for (int e = tid; e < E; e += kUThreads) s.now[e] = s.was[e];
     } else {
-        // near the end the experts chase each other's last tokens: shorter steps settle sooner
         const bool damp = !sampled && m2.excess <= E;
         const int plim = (1 << (31 - a.ib)) - 1;
         int pm = 0x7fffffff;
         for (int e = tid; e < E; e += kUThreads) {
             int dp = s.now[e] - s.was[e];
-            dp = damp ? dp - dp * 3 / 8 : dp;
+            dp = damp ? dp - dp / kDamp : dp;
             int pn = s.was[e] + dp + (level && (all_in || s.was[e] > 0) ? s.lam : 0);
             if (a.mode == kModeSlack && !even) pn = pn < 0 ? 0 : pn;
             pn = pn > plim ? plim : (pn < -plim ? -plim : pn);
@@ -1591,7 +1599,7 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     // next to no spare capacity (as from rounding T*k/E up): nearly every expert ends full, and the first passes spread
     // what is spare evenly
     const int stride = T / kSampleRows;
-    const int n_sampled = stride >= 2 && !prices_in && !retry ? kSampledPasses : 0;
+    const int n_sampled = stride >= kSampleFrom && !prices_in && !retry ? kSampledPasses : 0;
     a.even = spare > 0 && spare * 64 <= (long long)E * C && !prices_in && !retry ? (n_sampled ? 4 : 3) : 0;
     {
         const int rw = price_pass_rows(T, E, k), wgs = (T + rw - 1) / rw;
