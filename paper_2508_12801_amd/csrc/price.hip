@@ -10,8 +10,8 @@
 //                            (a few bins per octave) say by how much each price has to move for its own demand to
 //                            meet its capacity; all prices move at once.  Displaced tokens spread over all the other
 //                            experts, so the simultaneous step converges fast: the excess demand of a batch of 65536
-//                            tokens over 128 experts goes 37000, 1200, 230, 110, 75, 50 tokens.  The first two
-//                            passes of a large batch look at 8192 of its tokens only.
+//                            tokens over 128 experts goes 37000, 1200, 230, 110, 55, 40 tokens.  The first two
+//                            passes of 131072 tokens and more look at 8192 of them only.
 //   final pass               the tokens take their k best experts at the last prices, and every exchange that would
 //                            cost less than a bound is listed: arc a -> b of token u, cost (q_ua - p_a) - (q_ub - p_b),
 //                            never negative because the token holds its best experts.
@@ -27,9 +27,9 @@
 //
 // What bounds it: the passes read the rewards once each (34 MB for 65536 tokens over 128 experts, 11 us a pass including the
 // k-th best of every row, plus 6.4 us for the step between them, which one workgroup takes), the search is one serial chain of
-// searches.  65536 tokens, 128 experts, top-8, capacity 1.0: 0.22 to 0.24 ms, of which seven passes and their steps take 0.12,
+// searches.  65536 tokens, 128 experts, top-8, capacity 1.0: 0.17 to 0.20 ms, of which five or six passes and their steps take 0.10,
 // the last pass 0.02 and the search 0.05 to 0.08; 1.6 to 1.8 ms for the auction, whose 46 rounds each read the rewards as
-// well.  16384 over 64 experts: 0.14 against 0.8 to 1.3 ms.
+// well.  16384 over 64 experts: 0.10 against 0.8 to 1.3 ms.
 //
 // Three forms of the problem, told apart by PriceArgs::mode:
 //   demand = capacity   every expert ends full;
@@ -79,7 +79,6 @@ constexpr int kEnough = 3, kWorst = 2;            // the passes end when a third
 // batches (64 to 65536 tokens, 8 to 256 experts) solves took 3.6 % longer with three eighths (6 % at 64 and 128 experts, 1 % at 8 and 16); with a sixth,
 // a sixteenth or none within 1 % of an eighth; with half a token per expert left to the search 0.5 % longer.
 constexpr int kDamp = 8;
-constexpr int kLevelPairs = 4;                    // exchanges of a row that the common step looks at
 constexpr int kSmallEntries = 1 << 16;            // rewards of a batch that one workgroup passes over by itself
 constexpr int kSmallThreads = 4096;               // ... with this many lanes at work in all
 constexpr int kSmallPasses = kPriceTryPasses;
@@ -122,7 +121,6 @@ struct PriceArgs {
     int *blkcnt;                                  // pairs per (block of rows of the final pass, expert)
     long long *wg_sum;                            // sum of q over the block's pairs
     int T, E, k, C, mode;
-    int even;                                     // the passes before this one treat spare capacity as spread evenly
     int rows, n_wg;                               // of the final pass
     int ib, nb, bshift;                           // bits of a column id in a packed key; bins per side; their width
     int es;                                       // columns of the histograms
@@ -175,10 +173,17 @@ __device__ __forceinline__ unsigned row_mask(int row, int ib)      // equal valu
 
 // New prices from the histograms of a pass: of s.was to s.now, with the margins in s_h; one workgroup.
 //
-// Experts whose price counts (all of them; with spare capacity those with a price above 0) are moved towards their
-// common mean demand one by one, and all together by the step that brings the mean to the capacity: raising them all
-// displaces tokens only to the experts outside, which the single steps do not see.  Column E of the histograms holds
-// the margins of that common step.
+// Demand = capacity: every expert's price is moved to where its own demand meets the capacity.  Demand > capacity: towards the mean demand
+// one by one, and all together by the step that brings the mean to the capacity, whose margins are in column E of the histograms.
+//
+// Spare capacity: an expert's demand is taken to depend on how far its price moves beyond the level, the common move of the prices a token
+// compares it with.  Its own margins say at which distance from the level it ends full; prices stay >= 0, and an expert that would have to
+// fall below that ends with room, and with the tokens that its newcomers' margins (or those of its holds) give it at that distance.  The
+// level is the one at which all demands add up to the tokens there are.  Moved one by one, the experts with too many tokens pushed them
+// onto others that were as good as full, and so on: 10007 tokens of 96 experts and a tenth of spare capacity took nine passes (excess
+// 25000, 14000, 8300, 4100, 1500, 350, 80, 35, 20), now six or seven (25000, 1200, 160, 65, 35, 20), each without the search for the exchanges
+// of a common step (7.9 -> 6.0 us).  Solves of 250 batches with 2 to 100 % of spare capacity take 0.88 of the time (0.83 at 64 to 128
+// experts, 0.92 to 0.95 at 16 and 32, 1.05 at 8).
 //
 // Bound by latency, and by what the sixteen wavefronts do alike (four of them share a SIMD): sums are taken over the
 // wavefronts that have experts only, and the bound of the arc list is worked out by the last one beside the columns.  The largest
@@ -187,8 +192,8 @@ struct StepLds {
     __attribute__((aligned(16))) int was[kPStride], now[kPStride];
     int cum[64];
     __attribute__((aligned(16))) int part[kPriceMaxE / 64][8];      // sums of the wavefronts that have experts
-    int pmin[kUThreads / 64];
-    int maxd, ran_out, lam, cap, worst, bound, wide, reach;
+    float level[2][kUThreads / 64];                                 // demand beyond the tokens there are, at so many levels
+    int maxd, ran_out, lam, worst, bound, wide, reach;
 };
 
 __device__ __forceinline__ void step_clear(StepLds &s)
@@ -196,34 +201,40 @@ __device__ __forceinline__ void step_clear(StepLds &s)
     if (threadIdx.x < 64) s.cum[threadIdx.x] = 0;
     if (threadIdx.x == 0) {
         s.maxd = s.ran_out = s.lam = s.worst = 0;
-        s.cap = 0x7fffffff;
     }
 }
 
-// Behind step_clear and a barrier.  CUM: s.cum holds the sums of the bins already.
+__device__ __forceinline__ float wave_sum_f(float v)        // the total in lane 63
+{
+    auto add = [](float x, int y) { return x + __int_as_float(y); };
+    v = add(v, __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x111, 0xf, 0xf, true));
+    v = add(v, __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x112, 0xf, 0xf, true));
+    v = add(v, __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x114, 0xf, 0xf, true));
+    v = add(v, __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x118, 0xf, 0xf, true));
+    v = add(v, __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x142, 0xa, 0xf, false));
+    v = add(v, __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x143, 0xc, 0xf, false));
+    return v;
+}
+
+// Behind step_clear and a barrier.  CUM: s.cum holds the sums of the bins already.  With spare capacity the columns of s_h are summed up.
 template <bool CUM>
-__device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const PriceMeta mt, const int *s_h, StepLds &s)
+__device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const PriceMeta mt, int *s_h, StepLds &s)
 {
     constexpr int NW = kUThreads / 64;
     static_assert(kPriceMaxE / 64 < NW - 1, "the last wavefront has no experts");
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int E = a.E, ES = a.es, nb = a.nb, nwe = (E + 63) >> 6;
-    const bool even = a.mode == kModeSlack && t < a.even;
-    const bool all_in = a.mode != kModeSlack || even, level = a.mode == kModeOver || (a.mode == kModeSlack && !even);
+    const bool slack = a.mode == kModeSlack, over_all = a.mode == kModeOver;
     const bool sampled = nrows < a.T;
     const int w0 = bin_w0(mt.w), bs = a.bshift;
     const int Ct = sampled ? (int)(((long long)a.C * nrows + a.T / 2) / a.T) : a.C;
     const int *s_hn = s_h + 2 * nb * ES;
     if (wv < nwe) {
         const int ne = tid < E ? s_hn[tid] : 0, over = tid < E && ne > Ct ? ne - Ct : 0;
-        const bool in = tid < E && (all_in || s.was[tid] > 0);
-        const int sn = wave_sum(in ? ne : 0), sx = wave_sum(over), sd = wave_sum(in && ne < Ct ? Ct - ne : 0),
-                  sz = wave_sum(in ? 0 : over), sc = wave_sum((in ? 1 : 0) | (!in && over > 0 ? 1 << 16 : 0));
+        const bool in = tid < E && (!slack || s.was[tid] > 0);
+        const int sn = wave_sum(ne), sx = wave_sum(over), sd = wave_sum(in && ne < Ct ? Ct - ne : 0);
         if (in ? over > kWorst || Ct - ne > kWorst : over > kWorst) s.worst = 1;
-        if (lane == 63) {
-            *(int4 *)&s.part[wv][0] = make_int4(sn, sx, sd, sz);
-            s.part[wv][4] = sc;
-        }
+        if (lane == 63) *(int4 *)&s.part[wv][0] = make_int4(sn, sx, sd, 0);
     }
     // holds (0 .. nb-1) and newcomers (nb .. 2nb-1) per margin bin over all experts
     if constexpr (!CUM) {
@@ -241,86 +252,74 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
         }
     }
     __syncthreads();
-    int sn = 0, sx = 0, sd = 0, sz = 0, sc = 0;
+    int sn = 0, sx = 0, sd = 0;
     for (int x = 0; x < nwe; ++x) {
         const int4 p4 = *(const int4 *)&s.part[x][0];
         sn += p4.x;
         sx += p4.y;
         sd += p4.z;
-        sz += p4.w;
-        sc += s.part[x][4];
     }
-    const int ss = sc & 0xffff, so = sc >> 16;
     sx = sd > sx ? sd : sx;                                           // tokens too many or too few
-    const int target = ss > 0 ? (2 * sn + ss) / (2 * ss) : Ct;        // mean demand of the experts that count
-    // What the common step has to take away: what those that count have too many, and what those that are about to join them
-    // (price 0, too many tokens) have.  These also move by more than their own margins say, which take the others of
-    // their kind to stay, the more the more of them there are: with both, 10007 tokens of 96 experts and a tenth of spare
-    // capacity need two passes less.
-    const int X0 = sn - Ct * ss, X = X0 > 0 ? X0 + sz : X0;
-    if (level && X < 0 && a.mode == kModeSlack) {
-        // A common step down ends for an expert at price 0, and from there on that expert takes part in what the step
-        // gains: the experts without a price at most treble in one step (its margins only know the present ones).
-        const int m = 2 * (E - ss > 0 ? E - ss : 1);
-        const int p = tid < E ? s.was[tid] : 0;
-        if (wv < nwe && __any(p > 0)) {
-            int r = 0;
-#pragma unroll 4
-            for (int f = 0; f < E; f += 4) {
-                const int4 o = *(const int4 *)&s.was[f];              // (nothing but zeros from E on)
-                r += (o.x > 0 && (o.x < p || (o.x == p && f < tid)) ? 1 : 0) + (o.y > 0 && (o.y < p || (o.y == p && f + 1 < tid)) ? 1 : 0) +
-                     (o.z > 0 && (o.z < p || (o.z == p && f + 2 < tid)) ? 1 : 0) + (o.w > 0 && (o.w < p || (o.w == p && f + 3 < tid)) ? 1 : 0);
-            }
-            if (p > 0 && r == m - 1) s.cap = p + 1;
-        }
-        __syncthreads();
-    }
-    if (wv * 64 < E + (level ? 1 : 0)) {
+    // enough: what is left is cheaper to move by the search
+    const int excess = sampled ? (int)((long long)sx * a.T / nrows) : sx;
+    const bool enough = !sampled && excess * (E <= 128 && !a.retry ? kEnough : 2 * kEnough) <= E && !s.worst;
+    const bool moves = !enough || a.retry;               // (another try may have to go on all the same)
+    const int target = slack ? Ct : (2 * sn + E) / (2 * E);           // the capacity, or the mean demand
+    if (moves && wv * 64 < E + (over_all ? 1 : 0)) {
         const int j = tid;
         const bool common = j == E;
         const int pj = j <= E ? s.was[j] : 0;
-        const bool in = all_in || pj > 0;
         int diff = 0;
-        if (j < E + (level ? 1 : 0)) diff = common ? X : s_hn[j] - (in ? target : Ct);
-        const int side = diff < 0 ? 1 : 0;                       // side 0: the price has to rise, side 1: to fall
-        const int need = side ? (in || common ? -diff : 0) : diff;       // (room left at price 0 is fine)
+        if (j < E + (over_all ? 1 : 0)) diff = common ? sn - Ct * E : s_hn[j] - target;
+        const int side = diff < 0 ? 1 : 0, need = side ? -diff : diff;      // side 0: the price has to rise, side 1: to fall
         int most = 0;
-        if (need != 0) {
-            const int *col = s_h + side * nb * ES + j;
-            int c[kPBins];                                       // (one branch for all: nb is kPBins or half of it)
+        if (need != 0 || (slack && j < E)) {
+            int prev = 0, b = 0, in_b = 0;                       // the first bin that reaches `need`, its count and the one before it
+            for (int way = slack ? 0 : side; way <= (slack ? 1 : side); ++way) {
+                int *col = s_h + way * nb * ES + j;
+                int c[kPBins];                                   // (one branch for all: nb is kPBins or half of it)
 #pragma unroll
-            for (int x = 0; x < kPBins / 2; ++x) c[x] = col[x * ES];
+                for (int x = 0; x < kPBins / 2; ++x) c[x] = col[x * ES];
 #pragma unroll
-            for (int x = kPBins / 2; x < kPBins; ++x) c[x] = 0;
-            if (nb > kPBins / 2) {
+                for (int x = kPBins / 2; x < kPBins; ++x) c[x] = 0;
+                if (nb > kPBins / 2) {
 #pragma unroll
-                for (int x = kPBins / 2; x < kPBins; ++x) c[x] = col[x * ES];
-            }
-            int run = 0, prev = 0, b = 0;                        // the first bin that reaches `need`, and the count before it
+                    for (int x = kPBins / 2; x < kPBins; ++x) c[x] = col[x * ES];
+                }
+                int run = 0, less = 0, n = 0, at = 0;
 #pragma unroll
-            for (int x = 0; x < kPBins; ++x) {
-                run += c[x];
-                const bool less = run < need;
-                b += less ? 1 : 0;
-                prev = less ? run : prev;
+                for (int x = 0; x < kPBins; ++x) {
+                    const int before = run;
+                    run += c[x];
+                    n += run < need ? 1 : 0;
+                    less = run < need ? run : less;
+                    at = run >= need && before < need ? c[x] : at;
+                    if (slack && x < nb) col[x * ES] = run;
+                }
+                if (way == side) {
+                    b = n;
+                    prev = less;
+                    in_b = at;
+                }
             }
             b = b < nb ? b : nb;
             int d = mt.w;
             if (b < nb) {
                 const int lo = bin_edge(b, w0, bs), hi = bin_edge(b + 1, w0, bs);
-                d = lo + (int)((float)(hi - lo) * (float)(need - prev) * __builtin_amdgcn_rcpf((float)col[b * ES]) + 0.5f);
+                d = lo + (int)((float)(hi - lo) * (float)(need - prev) * __builtin_amdgcn_rcpf((float)in_b) + 0.5f);
                 d = d < lo ? lo : d > hi ? hi : d;
             }
-            if (common && side && a.mode == kModeSlack && d > s.cap) d = s.cap;
-            else if (b == nb) s.ran_out = 1;
-            if (!in && !common && sx > E) d += (int)((float)d * fminf(0.7f, 2.f * (float)so / (float)E));
-            d = d < 1 ? 1 : d;
+            if (b == nb && (!slack || !side || pj > 0)) s.ran_out = 1;
+            d = need == 0 ? 0 : d < 1 ? 1 : d;
             most = d;
-            if (common) s.lam = side ? -d : d;
+            if (slack) s.now[j] = side ? -d : d;                 // distance from the level at which the expert ends full
+            else if (common) s.lam = side ? -d : d;
             else s.now[j] = pj + (side ? -d : d);
         }
-        most = wave_max(most);               // (an atomic of every lane is compiled into a loop over the lanes)
-        if (lane == 0 && most > 0) atomicMax(&s.maxd, most);
+        if (!slack) {
+            most = wave_max(most);           // (an atomic of every lane is compiled into a loop over the lanes)
+            if (lane == 0 && most > 0) atomicMax(&s.maxd, most);
+        }
     } else if (wv == NW - 1) {
         // the bound of the arc list: about kArcsPerExpert exchanges per expert lie under it.  h holds and n newcomers make
         // h * n / rows of them if they are spread over all rows, and the larger of the two if every row has one of each.
@@ -341,6 +340,67 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
         }
     }
     __syncthreads();
+    float level = 0.f;
+    if (slack && moves) {
+        // sixteen levels at a time, one to a wavefront, the first ones closer to each other the closer to none: by how much the demands
+        // add up to more than they do now
+        float lo = -(float)mt.w, hi = (float)mt.w, flo = 0.f, fhi = 0.f;
+        bool above = false, below = false;                       // flo, fhi are known
+        for (int turn = 0; turn < 2; ++turn) {
+            const float from = lo, span = hi - lo;
+            auto level_of = [&](int x) {                         // of 0 .. NW + 1
+                const float u = (float)x * (1.f / (NW + 1)), c = 2.f * u - 1.f;
+                return turn == 0 ? (float)mt.w * c * c * c : from + span * u;
+            };
+            const float at = level_of(wv + 1);
+            float f = 0.f;
+            for (int e = lane; e < E; e += 64) {
+                const float p = (float)s.was[e], own = (float)s.now[e];
+                float n = (float)(Ct - s_hn[e]);                 // full
+                if (at + own <= -p) {                            // at price 0: as far from the level as that leaves it
+                    const float x = -p - at, m = fabsf(x);
+                    const int *col = s_h + (x > 0.f ? 0 : nb) * ES + e;
+                    const int mi = m < (float)mt.w ? (int)m : mt.w, b = bin_of(mi, w0, bs);
+                    if (b >= nb) n = (float)col[(nb - 1) * ES];
+                    else {
+                        const float c0 = b > 0 ? (float)col[(b - 1) * ES] : 0.f, c1 = (float)col[b * ES];
+                        const float e0 = (float)bin_edge(b, w0, bs), e1 = (float)bin_edge(b + 1, w0, bs);
+                        n = c0 + (c1 - c0) * fmaxf(m - e0, 0.f) * __builtin_amdgcn_rcpf(e1 - e0);
+                    }
+                    n = x > 0.f ? -n : n;
+                }
+                f += n;
+            }
+            f = wave_sum_f(f);
+            if (lane == 63) s.level[turn & 1][wv] = f;
+            __syncthreads();
+            const float y = s.level[turn & 1][lane & (NW - 1)];
+            const unsigned many = (unsigned)__ballot(lane < NW && y >= 0.f);
+            const int x = many ? __ffs((int)many) - 1 : NW;          // the first level with too many
+            if (x < NW) {
+                hi = level_of(x + 1);
+                fhi = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(y), x));
+                below = true;
+            }
+            if (x > 0) {
+                lo = level_of(x);
+                flo = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(y), x - 1));
+                above = true;
+            }
+        }
+        level = above && below ? lo + (hi - lo) * (flo < fhi ? -flo / (fhi - flo) : 0.5f) : below ? hi : lo;
+        if (wv < nwe) {
+            int dp = 0;
+            if (tid < E) {
+                const float x = level + (float)s.now[tid], p = (float)s.was[tid];
+                dp = x <= -p ? -s.was[tid] : (int)rintf(x);
+                s.now[tid] = s.was[tid] + dp;
+            }
+            const int most = wave_max(dp < 0 ? -dp : dp);
+            if (lane == 0 && most > 0) atomicMax(&s.maxd, most);
+        }
+        __syncthreads();
+    }
     PriceMeta m2 = mt;
     const int bound = s.bound;
     m2.bound = (long long)a.T * a.k * (E - a.k) <= kAllArcs ? kMaxBound : bound < 2 ? 2 : (bound > kMaxBound ? kMaxBound : bound);
@@ -348,12 +408,11 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
     if (s.ran_out && w < 4 * mt.w) w = 4 * mt.w;
     m2.w = w < 16 ? 16 : (w < (1 << 26) ? w : (1 << 26));
     ++m2.passes;
-    m2.excess = sampled ? (int)((long long)sx * a.T / nrows) : sx;
+    m2.excess = excess;
     const bool listed = !a.retry || s.reach;             // another try needs more exchanges than the one before
-    // enough: what is left is cheaper to move by the search, or it no longer shrinks (it ends up alternating by a few)
-    const bool enough = m2.excess * (E <= 128 && !a.retry ? kEnough : 2 * kEnough) <= E && !s.worst;
-    const bool stuck = m2.excess <= E && m2.excess * 5 >= mt.excess * 4 && t >= a.even + 4;
-    if (!sampled && !even && (s.maxd == 0 || (listed && (enough || stuck)))) {
+    // stuck: it no longer shrinks (it ends up alternating by a few)
+    const bool stuck = m2.excess <= E && m2.excess * 5 >= mt.excess * 4 && t >= 4;
+    if (!sampled && (s.maxd == 0 || (listed && (enough || stuck)))) {
         m2.done = 1;
         m2.w = mt.w;
         if (m2.excess == 0) m2.bound = 2;                // nothing to move
@@ -361,25 +420,12 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
     } else {
         const bool damp = !sampled && m2.excess <= E;
         const int plim = (1 << (31 - a.ib)) - 1;
-        int pm = 0x7fffffff;
         for (int e = tid; e < E; e += kUThreads) {
             int dp = s.now[e] - s.was[e];
             dp = damp ? dp - dp / kDamp : dp;
-            int pn = s.was[e] + dp + (level && (all_in || s.was[e] > 0) ? s.lam : 0);
-            if (a.mode == kModeSlack && !even) pn = pn < 0 ? 0 : pn;
-            pn = pn > plim ? plim : (pn < -plim ? -plim : pn);
-            s.now[e] = pn;
-            pm = pn < pm ? pn : pm;
-        }
-        if (even) {                        // the cheapest expert at price 0
-            for (int off = 32; off > 0; off >>= 1) {
-                const int o = __shfl_xor(pm, off);
-                pm = o < pm ? o : pm;
-            }
-            if (lane == 0) s.pmin[wv] = pm;
-            __syncthreads();
-            for (int x = 0; x < nwe; ++x) pm = s.pmin[x] < pm ? s.pmin[x] : pm;
-            for (int e = tid; e < E; e += kUThreads) s.now[e] -= pm;
+            int pn = s.was[e] + dp + (over_all ? s.lam : 0);
+            if (slack) pn = pn < 0 ? 0 : pn;
+            s.now[e] = pn > plim ? plim : (pn < -plim ? -plim : pn);
         }
     }
     return m2;
@@ -434,7 +480,7 @@ constexpr int price_pieces(bool half) { return (kPTableInts / (half ? 8 : 4) + k
 
 // One workgroup.  Half of it is the wait for the copies, which the pass's additions have left in memory; the rest two barriers' worth of
 // sums and searches: 4.4 us at 16 experts, 5.3 at 64, 6.4 at 128, 8.4 at 256 (5.7, 7.5, 9.8 and 9.7 with counts of 32 bits, and with the
-// sums of the bins and the largest step taken behind the copies).  As the first step of every workgroup of the next pass the same
+// sums of the bins and the largest step taken behind the copies); with spare capacity 9 at 96, and 4.8 where the passes end.  As the first step of every workgroup of the next pass the same
 // work took 10 to 20 us.
 template <int N, int M, bool HALF>
 __global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, int nrows, int *host)
@@ -462,8 +508,8 @@ __global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, 
 
 // The margins of rows r_first .. r_end - 1 of a pass (row i is token i * stride + shift), added to the histograms in
 // s_hist; NT threads, G of them to a row.  nx holds this lane's part of its first row.
-template <int G, int EPL, int MODE, int NT>
-__device__ __forceinline__ void price_rows(const PriceArgs &a, int t, int W, int r_first, int r_end, int stride, int shift, int (&nx)[EPL],
+template <int G, int EPL, bool OS, int NT>
+__device__ __forceinline__ void price_rows(const PriceArgs &a, int W, int r_first, int r_end, int stride, int shift, int (&nx)[EPL],
                                            const int *s_p, int *s_hist)
 {
     using RK = RowKeys<G, EPL>;
@@ -472,22 +518,15 @@ __device__ __forceinline__ void price_rows(const PriceArgs &a, int t, int W, int
     const int E = a.E, k = a.k, ib = a.ib, nb = a.nb;
     const int ES = a.es;
     const bool vec = (E & 3) == 0 && (((size_t)a.q) & 15) == 0;
-    auto group_bits = [&](unsigned long long b) {
-        return G == 64 ? b : (b >> gbase) & ((1ull << (G & 63)) - 1);
-    };
     const int w0 = bin_w0(W), bs = a.bshift;
     const int bias = 1 << (31 - ib);
     const unsigned cmask = (1u << ib) - 1;
     int pb[EPL];                                          // bias - price of this lane's columns
-    unsigned in_m = 0;                                    // spare capacity: this lane's columns with a price
 #pragma unroll
     for (int m = 0; m < EPL; ++m) {
         const int c = RK::col(m, lg);
         pb[m] = c < E ? bias - s_p[c] : 0;
-        if (MODE == kModeSlack && c < E && s_p[c] > 0) in_m |= 1u << m;
     }
-    const bool common = MODE == kModeSlack && t >= a.even;            // margins of the common step are wanted
-    const bool any_in = MODE == kModeSlack && __any(in_m != 0) != 0;  // (without a price there is none)
     const unsigned keyo = (unsigned)bias << ib;           // an unfilled slot: reward 0, price 0
     int *s_n = s_hist + 2 * nb * ES;
     for (int i0 = r_first + grp; i0 - grp < r_end; i0 += NG) {
@@ -518,7 +557,7 @@ __device__ __forceinline__ void price_rows(const PriceArgs &a, int t, int W, int
         // held: key >= thr; alt: the best a hold competes with; low: what a newcomer displaces
         unsigned thr = kth, alt = nxt, low = kth;
         bool near = (int)((kth - nxt) >> ib) < W;
-        if (MODE == kModeOver) {
+        if (OS) {
             thr = kth > keyo ? kth : keyo + 1;
             low = kth > keyo ? kth : keyo;
             alt = nxt > keyo ? nxt : keyo;
@@ -526,46 +565,13 @@ __device__ __forceinline__ void price_rows(const PriceArgs &a, int t, int W, int
         }
         const int mc = (int)((mine & cmask) ^ rot);
         if (slot && mine >= thr && mc < E) atomicAdd(&s_n[mc], 1);
-        if (MODE == kModeOver && slot) {
+        if (OS && slot) {
             // raising all prices together frees the slots in the order of their values, lowering fills the next best
             const bool real = mine > keyo;
             const int mg = (int)((real ? mine - keyo : keyo - mine) >> ib);
             if (mg < W) atomicAdd(&s_hist[((real ? 0 : nb) + bin_of(mg, w0, bs)) * ES + E], 1);
         }
         if (!near) continue;
-        if (MODE == kModeSlack && common && any_in) {
-            // the i-th lowest hold with a price against the i-th best alternative without one, and the other way round
-            const bool priced = slot && mc < E && s_p[mc < E ? mc : 0] > 0;
-            const unsigned long long bp = group_bits(__ballot(priced)), bf = group_bits(__ballot(slot && !priced));
-            const int rp = priced ? __popcll(bp >> lg) - 1 : -1, rf = slot && !priced ? __popcll(bf >> lg) - 1 : -1;
-            unsigned ku[EPL], kd[EPL];
-#pragma unroll
-            for (int m = 0; m < EPL; ++m) {
-                const bool un = key[m] < kth;
-                ku[m] = un && !((in_m >> m) & 1u) ? key[m] : 0u;
-                kd[m] = un && ((in_m >> m) & 1u) ? key[m] : 0u;
-            }
-            unsigned u = RK::first(ku), d = RK::first(kd);
-            const int pairs = k < kLevelPairs ? k : kLevelPairs;
-            for (int i = 0; i < pairs; ++i) {
-                if (i) {
-                    u = u ? RK::below(ku, u) : 0u;
-                    d = d ? RK::below(kd, d) : 0u;
-                }
-                bool near_i = false;
-                if (rp == i && u) {
-                    const int mg = (int)((mine - u) >> ib);
-                    near_i = mg < W;
-                    if (near_i) atomicAdd(&s_hist[bin_of(mg, w0, bs) * ES + E], 1);
-                }
-                if (rf == i && d) {
-                    const int mg = (int)((mine - d) >> ib);
-                    near_i = mg < W;
-                    if (near_i) atomicAdd(&s_hist[(nb + bin_of(mg, w0, bs)) * ES + E], 1);
-                }
-                if (!__any(near_i)) break;                // (the margins of the pairs behind are wider)
-            }
-        }
         if (live) {
 #pragma unroll
             for (int m = 0; m < EPL; ++m) {
@@ -583,8 +589,8 @@ __device__ __forceinline__ void price_rows(const PriceArgs &a, int t, int W, int
 // passes 4.9 us at 16384 tokens of 64 experts, 10.2 at 256 experts and 11.0 at 65536 tokens of 128.  Two counts to an addition took
 // 5.7, 13.0 and 13.0, one, with half as many wavefronts to a table, 10.6, 20.1 and 18.3; without any of the additions it would be 4.0,
 // 6.2 and 7.1.
-template <int G, int EPL, int MODE>
-__global__ __launch_bounds__(kQThreads) void k_price(PriceArgs a, int t, int nrows, int stride, int shift, int rows_per_wg)
+template <int G, int EPL, bool OS>
+__global__ __launch_bounds__(kQThreads) void k_price(PriceArgs a, int nrows, int stride, int shift, int rows_per_wg)
 {
     using RK = RowKeys<G, EPL>;
     extern __shared__ __attribute__((aligned(16))) int s_hist[];      // (2 * nb + 1) x ES: margins of holds, of newcomers, holds
@@ -609,7 +615,7 @@ __global__ __launch_bounds__(kQThreads) void k_price(PriceArgs a, int t, int nro
     const int hquads = (2 * nb + 1) * ES / 4;
     for (int i = tid; i < hquads; i += kQThreads) ((int4 *)s_hist)[i] = make_int4(0, 0, 0, 0);
     __syncthreads();
-    price_rows<G, EPL, MODE, kQThreads>(a, t, mt.w, r_first, r_end, stride, shift, nx, s_p, s_hist);
+    price_rows<G, EPL, OS, kQThreads>(a, mt.w, r_first, r_end, stride, shift, nx, s_p, s_hist);
     __syncthreads();
     int *hg = ar->hist[blockIdx.x & (a.copies - 1)];
     for (int i = tid; i < hquads; i += kQThreads) {
@@ -641,7 +647,7 @@ __device__ __forceinline__ PriceMeta first_meta(const PriceArea *ar, const int64
 
 // All passes of a small batch in one workgroup: a pass takes 4 to 11 us (64 tokens of 8 experts: three in 11 us; 256 of 64: four in 46)
 // instead of two launches and their distance, none is launched in vain, and a batch that settles slowly may take more.
-template <int G, int EPL, int MODE>
+template <int G, int EPL, bool OS>
 __global__ __launch_bounds__(kUThreads) void k_price_small(PriceArgs a, int n_pass, int plim, const int64_t *__restrict__ prices_in)
 {
     using RK = RowKeys<G, EPL>;
@@ -660,7 +666,7 @@ __global__ __launch_bounds__(kUThreads) void k_price_small(PriceArgs a, int n_pa
         RK::load(a.q + (size_t)(grp < a.T ? grp : a.T - 1) * E, E, vec, lg, nx);
         for (int i = tid; i < hquads; i += kUThreads) ((int4 *)s_hist)[i] = make_int4(0, 0, 0, 0);
         __syncthreads();
-        price_rows<G, EPL, MODE, kUThreads>(a, t, mt.w, 0, a.T, 1, 0, nx, s.was, s_hist);
+        price_rows<G, EPL, OS, kUThreads>(a, mt.w, 0, a.T, 1, 0, nx, s.was, s_hist);
         for (int e = tid; e < E; e += kUThreads) s.now[e] = s.was[e];
         step_clear(s);
         __syncthreads();
@@ -1596,17 +1602,14 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     a.C = C;
     const long long spare = (long long)E * C - (long long)T * k;
     a.mode = spare == 0 ? kModeTight : spare > 0 ? kModeSlack : kModeOver;
-    // next to no spare capacity (as from rounding T*k/E up): nearly every expert ends full, and the first passes spread
-    // what is spare evenly
     const int stride = T / kSampleRows;
     const int n_sampled = stride >= kSampleFrom && !prices_in && !retry ? kSampledPasses : 0;
-    a.even = spare > 0 && spare * 64 <= (long long)E * C && !prices_in && !retry ? (n_sampled ? 4 : 3) : 0;
     {
         const int rw = price_pass_rows(T, E, k), wgs = (T + rw - 1) / rw;
         a.copies = kPCopies;
         while (a.copies > 2 && a.copies * kPWgPerCopy > wgs) a.copies /= 2;
-        // what one row adds to a count at most: one, or to that of the common step a slot or pair each
-        const long long each = a.mode == kModeTight ? 1 : a.mode == kModeSlack ? kLevelPairs : k;
+        // what one row adds to a count at most: one, or to that of the unfilled slots one a slot
+        const long long each = a.mode == kModeOver ? k : 1;
         a.half = (wgs + a.copies - 1) / a.copies * (long long)rw * each < (1 << 16) ? 1 : 0;
     }
     a.arcs_wanted = std::min(kArcsPerExpert * E, kArcsWanted);
@@ -1616,7 +1619,7 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     while ((1 << a.ib) < E) ++a.ib;
     a.nb = price_bins(E);
     a.bshift = E <= 256 ? 22 : 23;
-    a.es = price_columns(E, a.mode == kModeTight);
+    a.es = price_columns(E, a.mode != kModeOver);
 
     int G, EPL, rows;
     if (!price_shape(T, E, k, G, EPL, rows, a.n_wg) || a.n_wg > L.max_wg) return MAXSCORE_ERR_SHAPE;
@@ -1628,8 +1631,8 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     int32_t mrc = MAXSCORE_OK;                    // (timing marks)
     auto mark = [&] { mrc = mrc ? mrc : solver_mark(s); };
     const bool os = a.mode == kModeOver;
-    const size_t shm = sizeof(int) * (size_t)price_table_ints(E, a.mode == kModeTight);
-    const int hquads = price_table_ints(E, a.mode == kModeTight) / 4;
+    const size_t shm = sizeof(int) * (size_t)price_table_ints(E, a.mode != kModeOver);
+    const int hquads = price_table_ints(E, a.mode != kModeOver) / 4;
     const int n_pass = n_sampled + (retry ? kRetryPasses : a.mode == kModeSlack ? kSlackPasses : kTightPasses);
     const bool small = (long long)T * G <= kSmallThreads && (long long)T * E <= kSmallEntries && shm + sizeof(StepLds) <= 64 * 1024;
     const int plim = (1 << (31 - a.ib)) - 1;
@@ -1638,7 +1641,7 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
         hipLaunchKernelGGL(k_price_init, dim3(64), dim3(kPThreads), 0, s, a.ar, hquads, E, plim, prices_in, a.retry);
     for (int t = small ? n_pass : 0; t <= n_pass; ++t) {
         // Pass t is enqueued when pass t - 2 has ended, so that one stays queued behind the one that runs: a pass that is still
-        // queued when the prices are done costs two empty launches (5 us; a batch with room to spare needs three of eleven).
+        // queued when the prices are done costs two empty launches (5 us; a batch with room to spare needs one of nine).
         // The stream is looked at now and then: a stream that has drained or failed ends the wait.
         for (unsigned spin = 1; t >= 2 && !small && !hw[kPriceWordDone] && hw[kPriceWordPasses] < t - 1; ++spin) {
             if ((spin & 4095) == 0 && hipStreamQuery(s) != hipErrorNotReady) break;
@@ -1656,9 +1659,8 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
         if (fin) {                                                                                                        \
             if (small) {                                                                                                  \
                 mark();                                                                                                   \
-                if (a.mode == kModeTight) hipLaunchKernelGGL((k_price_small<GG, PP, kModeTight>), dim3(1), dim3(kUThreads), shm, s, a, kSmallPasses, plim, prices_in); \
-                else if (os) hipLaunchKernelGGL((k_price_small<GG, PP, kModeOver>), dim3(1), dim3(kUThreads), shm, s, a, kSmallPasses, plim, prices_in); \
-                else hipLaunchKernelGGL((k_price_small<GG, PP, kModeSlack>), dim3(1), dim3(kUThreads), shm, s, a, kSmallPasses, plim, prices_in); \
+                if (os) hipLaunchKernelGGL((k_price_small<GG, PP, true>), dim3(1), dim3(kUThreads), shm, s, a, kSmallPasses, plim, prices_in); \
+                else hipLaunchKernelGGL((k_price_small<GG, PP, false>), dim3(1), dim3(kUThreads), shm, s, a, kSmallPasses, plim, prices_in);   \
                 mark();                                                                                                   \
                 mark();                                                                                                   \
             }                                                                                                             \
@@ -1666,9 +1668,8 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
             else hipLaunchKernelGGL((k_price_assign<GG, PP, false>), dim3(grid), dim3(kPThreads), 0, s, a);       \
         } else {                                                                                                          \
             mark();                                                                                                       \
-            if (a.mode == kModeTight) hipLaunchKernelGGL((k_price<GG, PP, kModeTight>), dim3(grid), dim3(kQThreads), shm, s, a, t, nrows, st, shift, rw); \
-            else if (os) hipLaunchKernelGGL((k_price<GG, PP, kModeOver>), dim3(grid), dim3(kQThreads), shm, s, a, t, nrows, st, shift, rw); \
-            else hipLaunchKernelGGL((k_price<GG, PP, kModeSlack>), dim3(grid), dim3(kQThreads), shm, s, a, t, nrows, st, shift, rw); \
+            if (os) hipLaunchKernelGGL((k_price<GG, PP, true>), dim3(grid), dim3(kQThreads), shm, s, a, nrows, st, shift, rw); \
+            else hipLaunchKernelGGL((k_price<GG, PP, false>), dim3(grid), dim3(kQThreads), shm, s, a, nrows, st, shift, rw);   \
             mark();                                                                                                       \
         }                                                                                                                 \
     } while (0)

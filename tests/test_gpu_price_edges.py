@@ -53,3 +53,34 @@ def test_edges(ms, T, E, k, C):
     assert np.array_equal(out["expert_offsets"].cpu().numpy(), want["expert_offsets"])
     assert np.array_equal(out["disp_token"].cpu().numpy()[:n], want["disp_token"][:n])
     assert np.array_equal(out["token_pos"].cpu().numpy(), want["token_pos"])
+
+
+@pytest.mark.parametrize("T,E,k,room,uneven", [(300, 2, 1, 1.3, 3.0), (500, 8, 2, 1.01, 1.5), (64, 64, 8, 1.1, 1.0), (2000, 65, 3, 1.002, 1.0),
+                                               (1500, 96, 6, 1.1, 2.0), (1200, 256, 4, 2.0, 1.0), (1100, 257, 2, 1.25, 1.0), (900, 512, 1, 1.5, 0.7),
+                                               (4099, 16, 2, 1.25, 0.0)])
+def test_spare_room(ms, T, E, k, room, uneven):
+    """The level of the prices with next to no, some and much spare capacity, experts as popular as each other and not: the optimum, and
+    started from the prices it ended with the same one."""
+    C = min(T, -int(-room * T * k // E))
+    print(f"spare room T={T} E={E} k={k} C={C} uneven={uneven}", flush=True)
+    rng = np.random.default_rng(T + E + k)
+    L = (rng.standard_normal((T, E)) + uneven * rng.standard_normal(E)).astype(np.float32)
+    out = ms.route_logits(torch.from_numpy(L).cuda(), k, C)
+    q = out["q"].cpu().numpy().astype(np.int64)
+    a = out["assign"].cpu().numpy()
+    P = oracle.assignment_matrix(a, E)
+    assert (P.sum(axis=1) == k).all() and P.sum(axis=0).max() <= C and oracle.verify_optimal(q, P, k, C)["optimal"]
+    again = ms.assign_i32(out["q"], k, C, prices_in=out["prices"])
+    assert again["stats"]["total_score_q"] == out["stats"]["total_score_q"]
+
+
+@pytest.mark.parametrize("T", [131071, 131072, 131080])
+@pytest.mark.parametrize("C", [32768, 36000, 25000])
+def test_first_sampled_batches(ms, T, C):
+    """Where the first two passes begin to look at a sample of the rows: the auction's totals."""
+    print(f"sampled passes T={T} C={C}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(T + C)
+    L = torch.randn(T, 8, generator=gen, device="cuda") + torch.randn(8, generator=gen, device="cuda")
+    q = ms.softtopk(L, 2, 1.0)[1]
+    got, plain = ms.assign_i32(q, 2, C)["stats"], ms.assign_i32(q, 2, C, finisher=False)["stats"]
+    assert (got["total_score_q"], got["flow_value"]) == (plain["total_score_q"], plain["flow_value"])
