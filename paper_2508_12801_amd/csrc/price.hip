@@ -61,6 +61,10 @@ constexpr int kPArcs = 9216;                      // arcs the one-workgroup sear
 constexpr int kPBlocks = 4096;                    // blocks of rows of the final pass at most
 constexpr int kPArcBuf = 16384;                   // arcs the final pass can list
 constexpr int kBlockArcs = 512;                   // ... of one block, gathered in LDS
+// ... in so many lists, which the blocks take in turn: a block reserves its places with one addition, and additions to one word are 11 ns
+// apart (512 blocks of 16384 tokens of 64 experts: 11.6 -> 8.4 us for the last pass; of 65536 of 128 20.5 -> 17.1).  Few blocks share one list, which then
+// has room for what a few of them find.
+constexpr int kPLists = 8, kPListsFrom = 128;
 constexpr int kFThreads = 1024, kUThreads = 1024;
 constexpr int kFirstWindow = 1 << 22;             // margins of the first pass: up to four times a score of 1
 constexpr int kSampleRows = 8192;
@@ -102,16 +106,17 @@ struct PriceArea {
     int prices[kPStride];
     PriceMeta meta;                               // for the pass that comes next
     int loads[8][kPStride];                       // tokens per expert after the final pass, in eight partial counts
-    int n_arcs, fail;
-    int pad[6];
+    int fail;
+    int pad[7];
     long long t_start;
     long long pad2;
     // margins and holds, PriceArgs::copies times: (2 * nb + 1) rows of ES columns, filled by a pass (workgroup b adds to copy b
     // modulo their number), added up and cleared by the update behind it.  With one copy for all the additions took 25 us
     // (of 512 workgroups then): its lines travel from chiplet to chiplet with every addition.
     int hist[kPCopies][kPTableInts];
-    unsigned long long arc[kPArcBuf];             // cost << 32 | from << 16 | to
+    unsigned long long arc[kPArcBuf];             // cost << 32 | from << 16 | to, in PriceArgs::lists equal parts
     int arc_tok[kPArcBuf];
+    int n_arcs[kPLists][32];                      // arcs of each part (a line to itself)
 };
 
 struct PriceArgs {
@@ -128,6 +133,7 @@ struct PriceArgs {
     int half;                                     // ... with counts of 16 bits (no copy's can reach 2^16), else of 32
     int retry;                                    // the search has failed at the prices or the bound before
     int arcs_wanted;                              // about so many exchanges are to lie under the bound
+    int lists;                                    // of arcs: one or kPLists
 };
 
 // Margins are binned relative to w0 = window / 2^9: linear up to w0, then two bins per octave (one beyond 256 experts).
@@ -677,12 +683,13 @@ __global__ __launch_bounds__(kUThreads) void k_price_small(PriceArgs a, int n_pa
     for (int e = tid; e < E; e += kUThreads) ar->prices[e] = s.was[e];
     if (tid == 0) {
         ar->meta = mt;
-        ar->n_arcs = ar->fail = 0;
+        ar->fail = 0;
     }
+    if (tid < kPLists) ar->n_arcs[tid][0] = 0;
 }
 
 // The last pass: assignment, pairs per block and expert, sum of the rewards, and the arcs under the bound.  A row near a change is
-// evaluated a second time for its arcs, which a block gathers in LDS: 20 us for 65536 tokens of 128 experts, 12 for 16384 of 64 (30 and
+// evaluated a second time for its arcs, which a block gathers in LDS: 17 us for 65536 tokens of 128 experts, 8.4 for 16384 of 64 (30 and
 // 16 while the rows were evaluated three times, to count the arcs and to write them in the order of the rows).
 template <int G, int EPL, bool OS>
 __global__ __launch_bounds__(kPThreads) void k_price_assign(PriceArgs a)
@@ -801,16 +808,18 @@ __global__ __launch_bounds__(kPThreads) void k_price_assign(PriceArgs a)
     }
     if (s_bad) return;
     // arcs, gathered in LDS first (their order does not matter)
+    const int list = w & (a.lists - 1), list_room = kPArcBuf / a.lists, list0 = list * list_room;
+    int *n_list = ar->n_arcs[list];
     auto store = [&](int at, int cost, int from, int to, int row) {
         const unsigned long long r = ((unsigned long long)(unsigned)cost << 32) | (unsigned)((from << 16) | to);
         if (at < kBlockArcs) {
             s_arc[at] = r;
             s_arc_tok[at] = row;
         } else {                                           // (batches whose exchanges are all listed, in few blocks)
-            const int pos = atomicAdd(&ar->n_arcs, 1);
-            if (pos < kPArcBuf) {
-                ar->arc[pos] = r;
-                ar->arc_tok[pos] = row;
+            const int pos = atomicAdd(n_list, 1);
+            if (pos < list_room) {
+                ar->arc[list0 + pos] = r;
+                ar->arc_tok[list0 + pos] = row;
             }
         }
     };
@@ -847,12 +856,12 @@ __global__ __launch_bounds__(kPThreads) void k_price_assign(PriceArgs a)
     __syncthreads();
     const int n = s_narcs < kBlockArcs ? s_narcs : kBlockArcs;
     if (n == 0) return;
-    if (tid == 0) s_base = atomicAdd(&ar->n_arcs, n);
+    if (tid == 0) s_base = atomicAdd(n_list, n);
     __syncthreads();
     for (int i = tid; i < n; i += kPThreads)
-        if (s_base + i < kPArcBuf) {                       // (beyond: the search sees the count)
-            ar->arc[s_base + i] = s_arc[i];
-            ar->arc_tok[s_base + i] = s_arc_tok[i];
+        if (s_base + i < list_room) {                      // (beyond: the search sees the count)
+            ar->arc[list0 + s_base + i] = s_arc[i];
+            ar->arc_tok[list0 + s_base + i] = s_arc_tok[i];
         }
 }
 
@@ -927,18 +936,24 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
     const int E = a.E, k = a.k, N = E + 1, mode = a.mode;
     const bool slack = !OS && mode == kModeSlack;
     const PriceMeta mt = ar->meta;
-    const int B = mt.bound, n_listed = ar->n_arcs, fail = ar->fail;
+    const int B = mt.bound, fail = ar->fail;
+    const int n_list = lane < a.lists ? ar->n_arcs[lane][0] : 0;            // of list `lane`
+    const bool many = a.lists > 1;
+    const int per_list = many ? FIRST * NT / kPLists : FIRST * NT, list_room = many ? kPArcBuf / kPLists : kPArcBuf;
+    static_assert(FIRST * NT / kPLists % 64 == 0, "a wavefront looks at one list at a time");
     const int *pg = ar->prices;
     unsigned long long arc0[FIRST];
     int tok0[FIRST];
 #pragma unroll
     for (int j = 0; j < FIRST; ++j) {
-        arc0[j] = ar->arc[tid + j * NT];
-        tok0[j] = ar->arc_tok[tid + j * NT];
+        const int f = tid + j * NT, x = many ? __builtin_amdgcn_readfirstlane(f / (FIRST * NT / kPLists)) : 0, at = x * list_room + (f - x * per_list);
+        arc0[j] = ar->arc[at];
+        tok0[j] = ar->arc_tok[at];
     }
+    const int n_upto = wave_sum(n_list), n_listed = __builtin_amdgcn_readlane(n_upto, 63);
+    bool ok = fail == 0 && !__any(n_list > list_room);
     int rounds = 0, augs = 0;
     bool close = false;                          // not solved, but near enough for another try
-    bool ok = fail == 0 && n_listed <= kPArcBuf;
     const int A0 = slack ? 2 * E : 0;
     if (A0 + n_listed > kPArcs) ok = false;
     if (tid == 0) {
@@ -975,9 +990,16 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
                 s.tok[A0 + i] = t;
             };
 #pragma unroll
-            for (int j = 0; j < FIRST; ++j)
-                if (tid + j * NT < n_listed) keep(tid + j * NT, arc0[j], tok0[j]);
-            for (int i = tid + FIRST * NT; i < n_listed; i += NT) keep(i, ar->arc[i], ar->arc_tok[i]);
+            for (int j = 0; j < FIRST; ++j) {
+                const int f = tid + j * NT, x = many ? __builtin_amdgcn_readfirstlane(f / (FIRST * NT / kPLists)) : 0, i = f - x * per_list;
+                const int n = __builtin_amdgcn_readlane(n_list, x);
+                if (i < n) keep(__builtin_amdgcn_readlane(n_upto, x) - n + i, arc0[j], tok0[j]);
+            }
+            if (__any(n_list > per_list))
+                for (int x = 0; x < a.lists; ++x) {
+                    const int n = __builtin_amdgcn_readlane(n_list, x), first = __builtin_amdgcn_readlane(n_upto, x) - n;
+                    for (int i = per_list + tid; i < n; i += NT) keep(first + i, ar->arc[x * list_room + i], ar->arc_tok[x * list_room + i]);
+                }
         }
         const int t0 = wave_total(e0), q0 = wave_total(e0 > 0 ? e0 : 0);
         if (lane == 0) {
@@ -1537,9 +1559,9 @@ __global__ __launch_bounds__(kPThreads) void k_price_init(PriceArea *ar, int qua
     for (int r = 0; r < kPCopies; ++r)
         for (int i = i0; i < quads; i += n) ((int4 *)ar->hist[r])[i] = make_int4(0, 0, 0, 0);
     for (int i = i0; i < 8 * kPStride; i += n) (&ar->loads[0][0])[i] = 0;
+    for (int i = i0; i < kPLists; i += n) ar->n_arcs[i][0] = 0;
     for (int i = i0; i < kPStride && !retry; i += n) ar->prices[i] = first_price(prices_in, i, E, plim);
     if (i0 == 0) {
-        ar->n_arcs = 0;
         ar->fail = 0;
         ar->meta = first_meta(ar, prices_in, retry);
         if (!retry) ar->t_start = wall_clock64();
@@ -1623,8 +1645,8 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
 
     int G, EPL, rows;
     if (!price_shape(T, E, k, G, EPL, rows, a.n_wg) || a.n_wg > L.max_wg) return MAXSCORE_ERR_SHAPE;
-    const int ngrp = kPThreads / G;
     a.rows = rows;
+    a.lists = a.n_wg >= kPListsFrom ? kPLists : 1;
     geom->rows = rows;
     geom->n_wg = a.n_wg;
 
