@@ -62,7 +62,7 @@ constexpr int kPBlocks = 4096;                    // blocks of rows of the final
 constexpr int kPArcBuf = 16384;                   // arcs the final pass can list
 constexpr int kBlockArcs = 512;                   // ... of one block, gathered in LDS
 // ... in so many lists, which the blocks take in turn: a block reserves its places with one addition, and additions to one word are 11 ns
-// apart (512 blocks of 16384 tokens of 64 experts: 11.6 -> 8.4 us for the last pass; of 65536 of 128 20.5 -> 17.1).  Few blocks share one list, which then
+// apart (512 blocks of 16384 tokens of 64 experts: 12.6 -> 8.6 us for the last pass; of 65536 of 128 19.9 -> 18.0).  Few blocks share one list, which then
 // has room for what a few of them find.
 constexpr int kPLists = 8, kPListsFrom = 128;
 constexpr int kFThreads = 1024, kUThreads = 1024;
@@ -292,20 +292,24 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
 #pragma unroll
                     for (int x = kPBins / 2; x < kPBins; ++x) c[x] = col[x * ES];
                 }
-                int run = 0, less = 0, n = 0, at = 0;
 #pragma unroll
-                for (int x = 0; x < kPBins; ++x) {
-                    const int before = run;
-                    run += c[x];
-                    n += run < need ? 1 : 0;
-                    less = run < need ? run : less;
-                    at = run >= need && before < need ? c[x] : at;
-                    if (slack && x < nb) col[x * ES] = run;
-                }
+                for (int x = 1; x < kPBins; ++x) c[x] += c[x - 1];
                 if (way == side) {
-                    b = n;
-                    prev = less;
-                    in_b = at;
+#pragma unroll
+                    for (int x = 0; x < kPBins; ++x) {
+                        const bool less = c[x] < need;
+                        b += less ? 1 : 0;
+                        prev = less ? c[x] : prev;
+                    }
+                    if (b < nb) in_b = col[b * ES];
+                }
+                if (slack) {
+#pragma unroll
+                    for (int x = 0; x < kPBins / 2; ++x) col[x * ES] = c[x];
+                    if (nb > kPBins / 2) {
+#pragma unroll
+                        for (int x = kPBins / 2; x < kPBins; ++x) col[x * ES] = c[x];
+                    }
                 }
             }
             b = b < nb ? b : nb;
@@ -689,7 +693,7 @@ __global__ __launch_bounds__(kUThreads) void k_price_small(PriceArgs a, int n_pa
 }
 
 // The last pass: assignment, pairs per block and expert, sum of the rewards, and the arcs under the bound.  A row near a change is
-// evaluated a second time for its arcs, which a block gathers in LDS: 17 us for 65536 tokens of 128 experts, 8.4 for 16384 of 64 (30 and
+// evaluated a second time for its arcs, which a block gathers in LDS: 18 us for 65536 tokens of 128 experts, 8.6 for 16384 of 64 (30 and
 // 16 while the rows were evaluated three times, to count the arcs and to write them in the order of the rows).
 template <int G, int EPL, bool OS>
 __global__ __launch_bounds__(kPThreads) void k_price_assign(PriceArgs a)
