@@ -527,6 +527,13 @@ int32_t maxscore_route_xw(const void *x, const void *W, const float *bias, int32
         return route_from_rewards(scores_out, q_out, T, E, k, C, o, assign, gates, expert_offsets, disp_token,
                                   disp_gate, token_pos, prices, stats, (char *)workspace, workspace_bytes, s);
     }
+    if (gemm_wide_scores_supported(in_dtype, T, d, E, x, wt)) {
+        if (stats) std::memset(stats, 0, sizeof(*stats));
+        rc = gemm_wide_scores_run(x, W, bias, in_dtype, T, d, E, k, o.t, o.quant_shift, logits_out, scores_out, q_out, wt, s);
+        if (rc) return rc;
+        return route_from_rewards(scores_out, q_out, T, E, k, C, o, assign, gates, expert_offsets, disp_token,
+                                  disp_gate, token_pos, prices, stats, (char *)workspace, workspace_bytes, s);
+    }
     rc = gemm_run(x, W, bias, in_dtype, T, d, E, logits_out, wt, s);
     if (rc) return rc;
     return maxscore_route_logits(logits_out, T, E, k, C, opts, scores_out, q_out, assign, gates, expert_offsets,
@@ -550,6 +557,8 @@ int32_t maxscore_router_softtopk(const void *x, const void *W, const float *bias
     if (!logits_out) return MAXSCORE_ERR_NULL;
     if (gemm_split_scores_supported(in_dtype, T, d, E, x, W))
         return gemm_split_scores_run(x, W, bias, in_dtype, T, d, E, k, t, quant_shift, logits_out, scores, q, s);
+    if (gemm_wide_scores_supported(in_dtype, T, d, E, x, wt))
+        return gemm_wide_scores_run(x, W, bias, in_dtype, T, d, E, k, t, quant_shift, logits_out, scores, q, wt, s);
     int32_t rc = gemm_run(x, W, bias, in_dtype, T, d, E, logits_out, wt, s);
     if (rc) return rc;
     return softtopk_run(logits_out, T, E, k, t, quant_shift, scores, q, s);

@@ -253,6 +253,10 @@ int32_t gemm_softtopk_run(const void *x, const void *W, const float *bias, int d
 bool gemm_split_scores_supported(int dtype, int T, int d, int E, const void *x, const void *W);
 int32_t gemm_split_scores_run(const void *x, const void *W, const float *bias, int dtype, int T, int d, int E, int k, float t, int shift,
                               float *logits, float *scores, int32_t *q, hipStream_t s);
+// The same for 129 to 256 experts in bf16, whole rows of them in a workgroup.
+bool gemm_wide_scores_supported(int dtype, int T, int d, int E, const void *x, const void *wt_scratch);
+int32_t gemm_wide_scores_run(const void *x, const void *W, const float *bias, int dtype, int T, int d, int E, int k, float t, int shift,
+                             float *logits, float *scores, int32_t *q, void *wt_scratch, hipStream_t s);
 int32_t copy_run(const void *src, void *dst, size_t bytes, hipStream_t s);
 
 extern int g_kernel_timing;

@@ -433,6 +433,169 @@ __global__ __launch_bounds__(256) void k_gemm_bf16_wtc(const unsigned short *__r
     }
 }
 
+// The router weight in the order in which k_gemm_bf16_wide's lanes take it: 32 columns (fewer in the last block) after the other, of each
+// 16 indices of d after the other, of these the lower 8 of every column, then the upper 8.  d is a multiple of 64.
+__global__ __launch_bounds__(256) void k_operand_w(const unsigned short *__restrict__ W, unsigned short *__restrict__ wt, int d, int E)
+{
+    const int k0 = blockIdx.x * BK, n0 = blockIdx.y * 32, cols = E - n0 < 32 ? E - n0 : 32;
+    const int j = threadIdx.x >> 6, h = (threadIdx.x >> 5) & 1, c = threadIdx.x & 31;
+    if (c >= cols) return;
+    const unsigned short *src = W + (size_t)(k0 + 16 * j + 8 * h) * E + n0 + c;
+    unsigned v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = src[(size_t)i * E];
+    *(u32x4 *)(wt + (size_t)n0 * d + ((size_t)(k0 / 8 + 2 * j + h) * cols + c) * 8) =
+        u32x4{v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16)};
+}
+
+// 129 to 256 experts: a workgroup of eight wavefronts takes 64 whole rows, a wavefront 32 columns of them, so that the scores come from the
+// sums as in k_gemm_bf16_wtc, in the layout of the score kernel for as many experts (16 lanes a row).  x goes through LDS in slabs that all
+// wavefronts read; of W every wavefront has columns of its own, so that these come straight from L2, in operand order (k_operand_w: whole
+// lines).  Three slabs of both are on their way.  The sums are those of k_gemm_bf16_wtc bit for bit: the same instructions in the same order
+// of d.  Bound by the slabs: of x 8 KB from memory (3.4 TB/s on the whole chip), of W 32 KB from L2, and as many reads of LDS as matrix
+// instructions, which take 0.6 us a slab together (0.2 each at their rates); and by the three arrays written at the end.  16384 x 2048 to 256
+// 43.6 us, to 160 42.5; with two workgroups of 128 columns each, logits and the score kernel behind them 57.4 and 55.2 (W through LDS as
+// well: 53 and 50).
+template <bool VL>
+__global__ __launch_bounds__(512) void k_gemm_bf16_wide(const unsigned short *__restrict__ x, const unsigned short *__restrict__ wt,
+                                                        const float *__restrict__ bias, int T, int d, int E, float *__restrict__ out,
+                                                        float *__restrict__ scores, int32_t *__restrict__ q, int k, float t, float qscale,
+                                                        int quads)
+{
+    constexpr int BN = 256, RW = 64, NS = 4, NB = BK / 16;
+    constexpr int SP = BN + 4;                   // pitch of a staged row in floats
+    __shared__ __attribute__((aligned(16))) unsigned short sA[2][RW * LDP];
+    __shared__ __attribute__((aligned(16))) float stage[RW * SP];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int row0 = blockIdx.x * RW, kq = 8 * (lane >> 5);
+    const int lr = tid >> 3, lc = (tid & 7) * 8;             // loader: row, column of the slab
+    const int col = wave * 32 + (lane & 31);
+    // (rows and columns beyond the matrix are computed from others and dropped: a register that is zeroed or loaded is waited for around the
+    // load, and with it every slab on its way)
+    const int n0 = wave * 32 < E ? wave * 32 : 0, cols = E - n0 < 32 ? E - n0 : 32;
+    const unsigned short *wp = wt + (size_t)n0 * d;
+    const unsigned wo = ((lane >> 5) * cols + ((lane & 31) < cols ? (lane & 31) : cols - 1)) * 8;
+    const unsigned short *xp = x + (size_t)(row0 + lr < T ? row0 + lr : T - 1) * d + lc;
+    u32x4 ra[NS], rb[NS][NB];
+    auto fetch_w = [&](int k0, u32x4(&b)[NB]) {
+        const unsigned short *w0 = wp + (size_t)k0 * cols;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) b[j] = *(const u32x4 *)(w0 + (16 * cols * j + wo));
+    };
+    auto fetch_x = [&](int k0, u32x4 &a) { a = *(const u32x4 *)(xp + k0); };
+    // (d in the order of the workgroup of 128 rows that k_gemm_bf16_wtc would have)
+    const int nslab = d / BK;
+    const unsigned block = blockIdx.x / (BM / RW);
+    const int rot = (int)((block * 7u + (block >> 5)) % (unsigned)nslab);
+    auto kof = [&](int i) {
+        int sidx = i + rot;
+        if (sidx >= nslab) sidx -= nslab;
+        return sidx * BK;
+    };
+    f32x16 acc[2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+        if (i < nslab) {
+            fetch_x(kof(i), ra[i]);
+            fetch_w(kof(i), rb[i]);
+        }
+    // The matrix instructions of a slab run while the operands of the next one come from LDS: straight behind each other they left the matrix
+    // cores idle between the barriers.  W stays in the registers that it was loaded to until they have run, and x goes to LDS from its own: a
+    // copy would be made early, and would wait for the load.
+    bf16x8 av[2][2 * NB];
+    auto put = [&](int it, auto part, auto cond) {
+        constexpr int I = decltype(part)::value, P = I & 1;
+        unsigned short *tA = sA[P];                          // (free: read two slabs ago, before the barrier of the last one)
+        *(u32x4 *)&tA[lr * LDP + lc] = ra[I];
+        __syncthreads();
+        if (!decltype(cond)::value || it + NS < nslab) fetch_x(kof(it + NS), ra[I]);
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int r = 0; r < 2; ++r) av[P][2 * j + r] = *(const bf16x8 *)&tA[(32 * r + (lane & 31)) * LDP + 16 * j + kq];
+    };
+    auto use = [&](int it, auto part, auto cond) {
+        constexpr int I = decltype(part)::value, P = I & 1;
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+                acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[P][2 * j + r], __builtin_bit_cast(bf16x8, rb[I][j]), acc[r], 0, 0, 0);
+        if (!decltype(cond)::value || it + NS < nslab) fetch_w(kof(it + NS), rb[I]);
+    };
+    static_assert(NS == 4, "four slabs a turn");
+    constexpr std::integral_constant<int, 0> i0;
+    constexpr std::integral_constant<int, 1> i1;
+    constexpr std::integral_constant<int, 2> i2;
+    constexpr std::integral_constant<int, 3> i3;
+    auto turn = [&](int it, auto first, auto cond) {         // slabs it to it + 3 into registers, the products up to the last but one of them
+        constexpr bool C = decltype(cond)::value;
+        put(it, i0, cond);
+        if (!decltype(first)::value) use(it - 1, i3, cond);
+        if (!C || it + 1 < nslab) put(it + 1, i1, cond), use(it, i0, cond);
+        if (!C || it + 2 < nslab) put(it + 2, i2, cond), use(it + 1, i1, cond);
+        if (!C || it + 3 < nslab) put(it + 3, i3, cond), use(it + 2, i2, cond);
+    };
+    constexpr std::true_type yes;
+    constexpr std::false_type no;
+    int it = NS;
+    if (nslab >= 2 * NS) turn(0, yes, no);       // (loads that may not be made are waited for early: only in the last two turns)
+    else turn(0, yes, yes);
+    for (; it + 2 * NS <= nslab; it += NS) turn(it, no, no);
+    for (; it < nslab; it += NS) turn(it, no, yes);
+    switch ((nslab - 1) % NS) {
+    case 0: use(nslab - 1, i0, yes); break;
+    case 1: use(nslab - 1, i1, yes); break;
+    case 2: use(nslab - 1, i2, yes); break;
+    default: use(nslab - 1, i3, yes);
+    }
+    const float bv = bias && col < E ? bias[col] : 0.f;
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) stage[(32 * r + 8 * j + 4 * (lane >> 5) + i) * SP + col] = acc[r][4 * j + i] + bv;
+    __syncthreads();
+    const int lg = tid & 15;
+    auto col_of = [&](int m) { return VL ? (m >> 2) * 64 + lg * 4 + (m & 3) : lg * 16 + m; };
+    for (int r = tid >> 4; r < RW && row0 + r < T; r += 32) {
+        float xv[16], sc[16];
+        int qq[16];
+#pragma unroll
+        for (int m = 0; m < 16; m += 4) {
+            const float4 v4 = *(const float4 *)&stage[r * SP + col_of(m)];
+            const float v[4] = {v4.x, v4.y, v4.z, v4.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) xv[m + i] = VL || col_of(m + i) < E ? v[i] : -3.4e38f;
+        }
+        softtopk_row<16, 16, VL>(xv, lg, E, k, t, qscale, MAXSCORE_SOFTTOPK_A, sc, qq);
+        const size_t o0 = (size_t)(row0 + r) * E;
+        if (VL || quads) {
+#pragma unroll
+            for (int m = 0; m < 16; m += 4) {
+                if (!VL && col_of(m) >= E) continue;
+                const size_t o = o0 + col_of(m);
+                *(float4 *)(out + o) = make_float4(xv[m], xv[m + 1], xv[m + 2], xv[m + 3]);
+                if (scores) *(float4 *)(scores + o) = make_float4(sc[m], sc[m + 1], sc[m + 2], sc[m + 3]);
+                if (q) *(int4 *)(q + o) = make_int4(qq[m], qq[m + 1], qq[m + 2], qq[m + 3]);
+            }
+        } else {
+#pragma unroll
+            for (int m = 0; m < 16; ++m)
+                if (col_of(m) < E) {
+                    out[o0 + col_of(m)] = xv[m];
+                    if (scores) scores[o0 + col_of(m)] = sc[m];
+                    if (q) q[o0 + col_of(m)] = qq[m];
+                }
+        }
+    }
+}
+
 // Split kernel: RT x 32 token rows per workgroup and up to 128 columns, d split over its KS wavefronts, whose parts are added up through
 // LDS in a fixed order.  Operands come straight from global memory: within a step the matrix instruction may take its reduction
 // indices in any order, so a lane reads 16 consecutive bytes of its row of x; and a tile may hold any 32 columns, so tile c takes the
@@ -850,6 +1013,42 @@ int32_t gemm_split_scores_run(const void *x, const void *W, const float *bias, i
     else if (vl) MS_LS(false, 16, true, 4);
     else MS_LS(false, 16, false, 4);
 #undef MS_LS
+    MS_HIP(hipGetLastError());
+    return MAXSCORE_OK;
+}
+
+// Whether k_gemm_bf16_wide is the better one.  Of its workgroups each of the 256 compute units holds one at a time, so that a last set that
+// leaves many units idle costs as much as a full one; the two kernels with their smaller workgroups lose less to it.  Against them, 2048 to
+// 256: 9000 tokens 31.8 us to 48.2, 16384 43.6 to 57.4; then 20000 71.5 to 66.2 and 24576 75.2 to 73.0, 28672 75.2 to 75.5, 32768 75.2 to
+// 79.6, 45056 115.7 to 127.8, 65536 155 to 180.  Hence one set, or sets that fill 7/8 of the places.
+static bool wide_is_better(int T)
+{
+    const long long blocks = (T + 63) / 64, sets = (blocks + 255) / 256;
+    return sets == 1 || blocks * 8 >= sets * 256 * 7;
+}
+
+// The scores of 129 to 256 experts in the projection, where gemm_run would take k_gemm_bf16_wtc.
+bool gemm_wide_scores_supported(int dtype, int T, int d, int E, const void *x, const void *wt_scratch)
+{
+    return dtype == MAXSCORE_DTYPE_BF16 && E > 128 && E <= 256 && d >= BK && d % BK == 0 && wt_scratch && ((uintptr_t)x % 16) == 0 &&
+           ((uintptr_t)wt_scratch % 16) == 0 && !split_is_better(T, E) && wide_is_better(T);
+}
+
+int32_t gemm_wide_scores_run(const void *x, const void *W, const float *bias, int dtype, int T, int d, int E, int k, float t, int shift,
+                             float *logits, float *scores, int32_t *q, void *wt_scratch, hipStream_t s)
+{
+    if (!gemm_wide_scores_supported(dtype, T, d, E, x, wt_scratch)) return MAXSCORE_ERR_SHAPE;
+    const unsigned short *xb = (const unsigned short *)x, *wb = (const unsigned short *)W;
+    unsigned short *wt = (unsigned short *)wt_scratch;
+    const float qscale = (float)(1 << shift);
+    // (as the score kernel chooses: the layouts have to agree)
+    const bool aligned = ((((uintptr_t)logits) | ((uintptr_t)scores) | ((uintptr_t)q)) % 16) == 0;
+    hipLaunchKernelGGL(k_operand_w, dim3(d / BK, (E + 31) / 32), dim3(256), 0, s, wb, wt, d, E);
+    if (E == 256 && aligned)
+        hipLaunchKernelGGL(k_gemm_bf16_wide<true>, dim3((T + 63) / 64), dim3(512), 0, s, xb, wt, bias, T, d, E, logits, scores, q, k, t, qscale, 1);
+    else
+        hipLaunchKernelGGL(k_gemm_bf16_wide<false>, dim3((T + 63) / 64), dim3(512), 0, s, xb, wt, bias, T, d, E, logits, scores, q, k, t, qscale,
+                           E % 4 == 0 && aligned ? 1 : 0);
     MS_HIP(hipGetLastError());
     return MAXSCORE_OK;
 }

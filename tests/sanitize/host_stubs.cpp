@@ -117,6 +117,12 @@ int32_t gemm_softtopk_run(const void *, const void *, const float *, int, int, i
 {
     return MAXSCORE_OK;
 }
+bool gemm_wide_scores_supported(int, int, int, int, const void *, const void *) { return false; }
+int32_t gemm_wide_scores_run(const void *, const void *, const float *, int, int, int, int, int, float, int, float *, float *, int32_t *,
+                             void *, hipStream_t)
+{
+    return MAXSCORE_OK;
+}
 bool gemm_split_scores_supported(int, int, int, int E, const void *, const void *) { return E <= 128; }
 int32_t gemm_split_scores_run(const void *, const void *, const float *, int, int, int, int, int, float, int, float *, float *,
                               int32_t *, hipStream_t)

@@ -70,3 +70,30 @@ def test_fp32_rows_do_not_depend_on_their_number(ms, T, d, E):
     assert torch.equal(out["logits"], ms.router_logits(x, W, None))
     for a in (0, 32, 8160, T // 64 * 32, (T - 1) // 64 * 64, (T - 1) // 32 * 32, T - 32):
         assert torch.equal(out["logits"][a:a + 32], ms.router_logits(x[a:a + 32].contiguous(), W, None)), a
+
+
+@pytest.mark.parametrize("T,d,E,k,bias", [
+    (8193, 64, 256, 8, True), (8250, 128, 129, 3, False), (8255, 192, 160, 8, True), (9000, 256, 132, 1, True), (16384, 64, 256, 8, False),
+    (16383, 320, 255, 5, True), (16385, 64, 256, 8, True), (28608, 64, 130, 2, True), (28609, 64, 130, 2, True), (28673, 448, 224, 8, True),
+    (8200, 512, 193, 64, True), (8200, 576, 256, 33, False), (8222, 768, 161, 4, True)])
+def test_whole_rows_of_more_than_128_experts(ms, T, d, E, k, bias):
+    """129 to 256 experts in one workgroup (8193 to 16384 tokens, and where sets of 256 workgroups are nearly full): the same bits as the
+    projection kernel and the score kernel behind it, with one to twelve slabs of d, a last workgroup of few rows and a last block of
+    few columns."""
+    print(f"whole rows T={T} d={d} E={E} k={k}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(T + d + E)
+    x = torch.randn(T, d, generator=gen, device="cuda").to(torch.bfloat16)
+    W = (torch.randn(d, E, generator=gen, device="cuda") / d ** 0.5).to(torch.bfloat16)
+    W[:, E - 1] *= 3.0                       # (the column that stands in for those beyond the last one is a large one)
+    b = torch.randn(E, generator=gen, device="cuda") if bias else None
+    out = ms.router_softtopk(x, W, b, k, 1.0)
+    L = ms.router_logits(x, W, b)
+    scores, q = ms.softtopk(L, k, 1.0)
+    assert torch.equal(out["logits"], L) and torch.equal(out["scores"], scores) and torch.equal(out["q"], q)
+    rows = slice(T - 70, T)
+    ref, mag = x[rows].double().cpu() @ W.double().cpu(), x[rows].double().cpu().abs() @ W.double().cpu().abs()
+    if bias:
+        ref, mag = ref + b.double().cpu(), mag + b.double().cpu().abs()
+    assert ((L[rows].double().cpu() - ref).abs() <= 1e-6 * mag).all()
+    with pytest.raises(ms.MaxScoreError):
+        ms.router_softtopk(x, W, b, k, 1.0, want_logits=False)
