@@ -229,7 +229,9 @@ __device__ __forceinline__ float bf16_to_f32(unsigned short b) { return __uint_a
 // 128 experts 460 us (5.8 TB/s), 496 with whole rows and a loop over the tokens in every wavefront; 44032 of 1024 from 2 of 64 75 to 69.
 constexpr int kCombineLoads = 4;
 
-template <bool BF16, bool NT, int PIECES>
+// AHEAD: the pieces of those slots are really on their way together.  A load under a condition is waited for before the next one (its register
+// could hold something else), so a slot that is empty then reads what the one before it did, and a lane beyond the row its end; neither is used.
+template <bool BF16, bool NT, int PIECES, bool AHEAD>
 __global__ __launch_bounds__(256) void k_combine(const u32x4 *__restrict__ buf, const int32_t *__restrict__ assign,
                                                  const int32_t *__restrict__ token_pos,
                                                  const float *__restrict__ gates, int T, int d, int E, int k, int C,
@@ -256,11 +258,23 @@ __global__ __launch_bounds__(256) void k_combine(const u32x4 *__restrict__ buf, 
     for (int u = 0; u < PIECES; ++u)
 #pragma unroll
         for (int v = 0; v < EPV; ++v) acc[u][v] = 0.f;
+    int at[PIECES];
+#pragma unroll
+    for (int u = 0; u < PIECES; ++u) at[u] = c + 64 * u < vec_per_row ? c + 64 * u : vec_per_row - 1;
+    const u32x4 *row = buf;
     for (int s = 0; s < k; s += SLOTS) {
         u32x4 vals[SLOTS][PIECES];
         bool have[SLOTS];
 #pragma unroll
         for (int z = 0; z < SLOTS; ++z) {
+            if (AHEAD) {
+                const int sl = s + z < k ? s + z : k - 1, ea = __builtin_amdgcn_readlane(e, sl);
+                have[z] = s + z < k && ea >= 0;
+                row = ea >= 0 ? buf + ((size_t)ea * C + __builtin_amdgcn_readlane(pos, sl)) * vec_per_row : row;
+#pragma unroll
+                for (int u = 0; u < PIECES; ++u) vals[z][u] = get<NT>(row + at[u]);
+                continue;
+            }
             const int es = s + z < k ? __builtin_amdgcn_readlane(e, s + z) : -1;
             have[z] = es >= 0;
             if (!have[z]) continue;
@@ -380,22 +394,27 @@ int32_t combine_run(const void *buf, int dtype, const int32_t *assign, const int
         // 832 from 6 of 32 15.8 and 17.4).  Below some 24 MiB in all, or ten wavefronts to a compute unit, the chip is not full with half as
         // many (1024 of 1024 from 8 of 64 5.4 and 5.0), beyond some 448 MiB memory decides as above, and with one or two slots the result
         // does, which is written either way.  With three or four an odd number of pieces leaves too many lanes idle (21892 of 1536 from 4 of 32
-        // 75 and 70).
+        // 75 and 70).  Up to the same 448 MiB the loads of several slots go ahead of their use (10007 of 1000 in fp32 48.0 -> 43.2, 32768 of 1024
+        // from 4 of 32 72.8 -> 65.8, 21892 of 1536 70.7 -> 65.3); from memory the rows come better one after the other (16384 of 2048 from 8
+        // of 64 118 us, 122 with loads ahead, 65536 of 2048 470 and 473), and with two slots the rest would be read for nothing (4096 of 1024
+        // 8.4 and 8.9).
         const int pieces = (vpr + 63) / 64;
-        const bool two = vpr > 64 && (k > 4 || (k > 2 && pieces % 2 == 0)) && (long long)T * ((pieces + 1) / 2) >= 2560 &&
-                         traffic >= (size_t)24 << 20 && traffic < (size_t)448 << 20;
+        const bool ahead = k > 2 && traffic < (size_t)448 << 20;
+        const bool two = ahead && vpr > 64 && (k > 4 || pieces % 2 == 0) && (long long)T * ((pieces + 1) / 2) >= 2560 &&
+                         traffic >= (size_t)24 << 20;
         const int piece = two ? 128 : 64, parts = (vpr + piece - 1) / piece;
         const int most = std::max(1, (1 << 24) / parts);            // tokens a launch (its threads are counted in 32 bits)
         for (int i0 = 0; i0 < T; i0 += most) {
             const int n = std::min(most, T - i0);
             const size_t at = (size_t)i0 * k;
-#define MS_COMBINE(BB, NN, PP)                                                                                                      \
-    hipLaunchKernelGGL((k_combine<BB, NN, PP>), dim3((unsigned)(((size_t)n * parts + 3) / 4)), dim3(256), 0, s, (const u32x4 *)buf, assign + at, \
+#define MS_COMBINE(BB, NN, PP, AA)                                                                                                   \
+    hipLaunchKernelGGL((k_combine<BB, NN, PP, AA>), dim3((unsigned)(((size_t)n * parts + 3) / 4)), dim3(256), 0, s, (const u32x4 *)buf, assign + at, \
                        token_pos + at, gates + at, n, d, E, k, C, vpr, parts, y + (size_t)i0 * d)
-#define MS_COMBINE_P(BB, NN)            \
-    do {                                \
-        if (two) MS_COMBINE(BB, NN, 2); \
-        else MS_COMBINE(BB, NN, 1);     \
+#define MS_COMBINE_P(BB, NN)                         \
+    do {                                             \
+        if (two) MS_COMBINE(BB, NN, 2, true);        \
+        else if (ahead) MS_COMBINE(BB, NN, 1, true); \
+        else MS_COMBINE(BB, NN, 1, false);           \
     } while (0)
             if (eb == 2) {
                 if (nt) MS_COMBINE_P(true, true);

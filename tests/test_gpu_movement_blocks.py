@@ -111,3 +111,34 @@ def test_combine_two_pieces(ms, d, k, dtype):
     ok = (a >= 0) & (a < E)
     terms = small.double()[torch.where(ok, a, 0).long(), pos] * (g.double() * ok)[:, :, None]
     assert ((y - terms.sum(dim=1)).abs() <= 1e-6 * terms.abs().sum(dim=1) + 1e-30).all()
+
+
+@pytest.mark.parametrize("T,d,E,k,C,dtype", [
+    (1, 8, 4, 3, 2, "bf16"), (5, 520, 3, 3, 6, "bf16"), (70, 504, 8, 4, 40, "fp32"), (33, 1032, 6, 5, 30, "bf16"), (257, 512, 16, 8, 130, "bf16"),
+    (65, 64, 16, 9, 50, "bf16"), (2600, 1016, 8, 6, 2000, "bf16"), (2570, 1032, 8, 4, 1300, "fp32"), (2561, 2040, 4, 3, 2000, "bf16"),
+    (40, 72, 4, 2, 30, "bf16"), (40, 72, 4, 1, 30, "fp32")])
+def test_combine_with_slots_read_ahead(ms, T, d, E, k, C, dtype):
+    """Slots that are empty (the first, the last, all of a token's) and lanes beyond a row add nothing, whatever they read: the first row of
+    the buffer and every place that nothing points to hold NaN."""
+    print(f"combine read ahead T={T} d={d} E={E} k={k} C={C} {dtype}", flush=True)
+    rng = np.random.default_rng(T + d + k)
+    places = 1 + rng.permutation(E * C - 1)                  # (place 0 stays unused)
+    keep = rng.random((T, k)) < 0.7
+    keep[0, 0] = False
+    keep[T // 2] = False
+    keep[T - 1, k - 1] = False
+    n = int(keep.sum())
+    assert n <= len(places)
+    at = np.full((T, k), -1, np.int64)
+    at[keep] = places[:n]
+    a = np.where(keep, at // C, -1).astype(np.int32)
+    pos = np.where(keep, at % C, 0).astype(np.int32)
+    g = rng.random((T, k)).astype(np.float32)
+    buf = torch.full((E * C, d), float("nan"), device="cuda", dtype=torch.bfloat16 if dtype == "bf16" else torch.float32)
+    rows = torch.from_numpy(rng.standard_normal((n, d)).astype(np.float32)).cuda().to(buf.dtype)
+    buf[torch.from_numpy(at[keep]).cuda()] = rows
+    y = ms.combine(buf.view(E, C, d), torch.from_numpy(a).cuda(), torch.from_numpy(pos).cuda(), torch.from_numpy(g).cuda()).cpu().numpy()
+    terms = np.zeros((T, k, d))
+    terms[keep] = rows.double().cpu().numpy() * g.astype(np.float64)[keep][:, None]
+    # k fused multiply-adds in fp32: each rounds a partial sum once
+    assert (np.abs(y - terms.sum(1)) <= k * 2.0 ** -24 * np.abs(terms).sum(1)).all()
