@@ -705,17 +705,25 @@ __global__ __launch_bounds__(64 * KS) void k_gemm_split(const void *__restrict__
     // whole steps of this part, then (in the last part) what d leaves over
     const int steps = d / STEP, s0 = steps * part / KS, s1 = steps * (part + 1) / KS;
     Frag f[DEPTH];
-#pragma unroll
-    for (int i = 0; i < DEPTH; ++i)
-        if (s0 + i < s1) load((s0 + i) * STEP, f[i], true);
     int s = s0;
-    for (; s + 2 * DEPTH <= s1; s += DEPTH) {
+    // (a part that is long enough enters its loop with all its loads made: behind loads that may not have been made the first steps of every
+    // turn wait for all; 16384 x 1024 to 16 in fp32 22.2 -> 20.0 us, to 64 29.3 -> 28.1, 16384 x 2048 to 16 in bf16 21.3 -> 20.0)
+    if (s + 2 * DEPTH <= s1) {
 #pragma unroll
-        for (int i = 0; i < DEPTH; ++i) {
-            const Frag cur = f[i];
-            load((s + DEPTH + i) * STEP, f[i], true);
-            use(cur);
-        }
+        for (int i = 0; i < DEPTH; ++i) load((s + i) * STEP, f[i], true);
+        do {
+#pragma unroll
+            for (int i = 0; i < DEPTH; ++i) {
+                const Frag cur = f[i];
+                load((s + DEPTH + i) * STEP, f[i], true);
+                use(cur);
+            }
+            s += DEPTH;
+        } while (s + 2 * DEPTH <= s1);
+    } else {
+#pragma unroll
+        for (int i = 0; i < DEPTH; ++i)
+            if (s + i < s1) load((s + i) * STEP, f[i], true);
     }
 #pragma unroll
     for (int i = 0; i < DEPTH; ++i)
