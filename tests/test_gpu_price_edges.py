@@ -84,3 +84,16 @@ def test_first_sampled_batches(ms, T, C):
     q = ms.softtopk(L, 2, 1.0)[1]
     got, plain = ms.assign_i32(q, 2, C)["stats"], ms.assign_i32(q, 2, C, finisher=False)["stats"]
     assert (got["total_score_q"], got["flow_value"]) == (plain["total_score_q"], plain["flow_value"])
+
+
+@pytest.mark.parametrize("seed", [0, 1, 2, 3])
+def test_near_copies_with_spare_room(ms, seed):
+    """A quarter of the rows alike but for a little noise, a quarter more room than demand: the price solve has to get there itself (the
+    auction takes some 50 rounds), at the optimum that the auction finds."""
+    print(f"near copies with spare room seed={seed}", flush=True)
+    from workloads import CONFIGS, make_logits
+    c = CONFIGS["cfg4b_near"]
+    q = ms.softtopk(torch.from_numpy(make_logits("cfg4b_near", seed)).cuda(), c["k"], c["t"])[1]
+    st = ms.assign_i32(q, c["k"], c["C"])["stats"]
+    auction = ms.assign_i32(q, c["k"], c["C"], finisher=False)["stats"]
+    assert st["total_score_q"] == auction["total_score_q"] and st["rounds"] <= 20 + 4
