@@ -87,9 +87,15 @@ constexpr int kSmallEntries = 1 << 16;            // rewards of a batch that one
 constexpr int kSmallThreads = 4096;               // ... with this many lanes at work in all
 constexpr int kSmallPasses = kPriceTryPasses;
 constexpr int kSampledPasses = 2, kTightPasses = 6, kSlackPasses = 16, kRetryPasses = 4;
-static_assert(kSampledPasses + kSlackPasses <= kPriceTryPasses, "the round cap of a call allows every pass");
+static_assert(kSampledPasses + kSlackPasses <= kPriceTryPasses && kSampledPasses + kTightPasses + 4 <= kPriceTryPasses, "the round cap of a call allows every pass");
 constexpr int kPRowsMax = 128;                    // rows of a block of the final pass at most
 constexpr int kPriceWordDone = 0, kPriceWordPasses = 1;      // pinned words of the calling thread
+constexpr int kPriceFarBit = 16;                             // of the passes' word, from a pass that found more than kFar tokens per expert to move
+// Where demand and capacity leave no room, rows that are nearly alike need more passes than others, and what more than eight tokens per expert
+// have to be moved the search does not take on.  Whether they are needed shows two passes before the last, when the host decides (later it
+// would cost every batch two empty launches).  16384 rows over 64 experts, top-8, half of them alike up to 0.1: 179 us in ten passes, a tenth
+// alike up to 3e-2 222 us, with a quarter less room and a quarter of them alike 190 us; in six passes the auction took over, 1.2 to 6.8 ms.
+constexpr int kFar = 4, kFarPasses = 4;
 enum { kModeTight = 0, kModeSlack = 1, kModeOver = 2 };
 
 struct PriceMeta {
@@ -98,7 +104,8 @@ struct PriceMeta {
     int bound;        // arcs cheaper than this are listed by the final pass
     int passes;       // price passes so far (the one that checks prices the caller has given is not counted)
     int excess;       // tokens too many in all, as the pass found them (a sample's count is scaled up)
-    int pad[3];
+    int far;          // 1: too far from the end when the passes were nearly used up; some more follow
+    int pad[2];
 };
 
 // Control words and tables inside the workspace (WorkspaceLayout::price_off).
@@ -134,6 +141,7 @@ struct PriceArgs {
     int retry;                                    // the search has failed at the prices or the bound before
     int arcs_wanted;                              // about so many exchanges are to lie under the bound
     int lists;                                    // of arcs: one or kPLists
+    int look;                                     // the pass that tells whether more than the usual ones are needed, or -1
 };
 
 // Margins are binned relative to w0 = window / 2^9: linear up to w0, then two bins per octave (one beyond 256 experts).
@@ -512,11 +520,12 @@ __global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, 
     const PriceMeta mt = ar->meta;
     if (mt.done) return;                 // (passes that find the prices done add nothing: the copies stay clear)
     __syncthreads();
-    const PriceMeta m2 = price_step<true>(a, t, nrows, mt, s_h, s);
+    PriceMeta m2 = price_step<true>(a, t, nrows, mt, s_h, s);
+    if (t == a.look) m2.far = m2.excess > kFar * E;
     for (int e = tid; e < E; e += kUThreads) ar->prices[e] = s.now[e];
     if (tid == 0) {
         ar->meta = m2;
-        __hip_atomic_store(host + (m2.done ? kPriceWordDone : kPriceWordPasses), m2.done ? 1 : t + 1, __ATOMIC_RELAXED,
+        __hip_atomic_store(host + (m2.done ? kPriceWordDone : kPriceWordPasses), m2.done ? 1 : (t + 1) | (m2.far << kPriceFarBit), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
@@ -657,7 +666,7 @@ __device__ __forceinline__ int first_price(const int64_t *__restrict__ prices_in
 }
 __device__ __forceinline__ PriceMeta first_meta(const PriceArea *ar, const int64_t *prices_in, int retry)
 {
-    return PriceMeta{retry ? ar->meta.w : kFirstWindow, 0, 2, retry ? ar->meta.passes : prices_in ? -1 : 0, 0x7fffffff, {0, 0, 0}};
+    return PriceMeta{retry ? ar->meta.w : kFirstWindow, 0, 2, retry ? ar->meta.passes : prices_in ? -1 : 0, 0x7fffffff, 0, {0, 0}};
 }
 
 // All passes of a small batch in one workgroup: a pass takes 4 to 11 us (64 tokens of 8 experts: three in 11 us; 256 of 64: four in 46)
@@ -1656,6 +1665,7 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     if (!price_shape(T, E, k, G, EPL, rows, a.n_wg) || a.n_wg > L.max_wg) return MAXSCORE_ERR_SHAPE;
     a.rows = rows;
     a.lists = a.n_wg >= kPListsFrom ? kPLists : 1;
+    a.look = a.mode != kModeSlack && !retry ? n_sampled + kTightPasses - 2 : -1;
     geom->rows = rows;
     geom->n_wg = a.n_wg;
 
@@ -1664,7 +1674,7 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     const bool os = a.mode == kModeOver;
     const size_t shm = sizeof(int) * (size_t)price_table_ints(E, a.mode != kModeOver);
     const int hquads = price_table_ints(E, a.mode != kModeOver) / 4;
-    const int n_pass = n_sampled + (retry ? kRetryPasses : a.mode == kModeSlack ? kSlackPasses : kTightPasses);
+    int n_pass = n_sampled + (retry ? kRetryPasses : a.mode == kModeSlack ? kSlackPasses : kTightPasses);
     const bool small = (long long)T * G <= kSmallThreads && (long long)T * E <= kSmallEntries && shm + sizeof(StepLds) <= 64 * 1024;
     const int plim = (1 << (31 - a.ib)) - 1;
     geom->one_launch = small ? 1 : 0;
@@ -1674,10 +1684,11 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
         // Pass t is enqueued when pass t - 2 has ended, so that one stays queued behind the one that runs: a pass that is still
         // queued when the prices are done costs two empty launches (5 us; a batch with room to spare needs one of nine).
         // The stream is looked at now and then: a stream that has drained or failed ends the wait.
-        for (unsigned spin = 1; t >= 2 && !small && !hw[kPriceWordDone] && hw[kPriceWordPasses] < t - 1; ++spin) {
+        for (unsigned spin = 1; t >= 2 && !small && !hw[kPriceWordDone] && (hw[kPriceWordPasses] & ((1 << kPriceFarBit) - 1)) < t - 1; ++spin) {
             if ((spin & 4095) == 0 && hipStreamQuery(s) != hipErrorNotReady) break;
             __builtin_ia32_pause();
         }
+        if (t == a.look + 2 && a.look >= 0 && !small && hw[kPriceWordPasses] >> kPriceFarBit) n_pass += kFarPasses;
         if (hw[kPriceWordDone]) t = n_pass;
         const bool fin = t == n_pass;
         const int st = t < n_sampled ? stride : 1;
