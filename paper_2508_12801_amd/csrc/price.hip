@@ -86,7 +86,7 @@ constexpr int kDamp = 8;
 constexpr int kSmallEntries = 1 << 16;            // rewards of a batch that one workgroup passes over by itself
 constexpr int kSmallThreads = 4096;               // ... with this many lanes at work in all
 constexpr int kSmallPasses = kPriceTryPasses;
-constexpr int kSampledPasses = 2, kTightPasses = 6, kSlackPasses = 16, kRetryPasses = 4;
+constexpr int kSampledPasses = 2, kTightPasses = 6, kSlackPasses = 18, kRetryPasses = 4;
 static_assert(kSampledPasses + kSlackPasses <= kPriceTryPasses && kSampledPasses + kTightPasses + 4 <= kPriceTryPasses, "the round cap of a call allows every pass");
 constexpr int kPRowsMax = 128;                    // rows of a block of the final pass at most
 constexpr int kPriceWordDone = 0, kPriceWordPasses = 1;      // pinned words of the calling thread
@@ -442,7 +442,7 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
             int dp = s.now[e] - s.was[e];
             // Rows that are nearly alike all move on to the same next expert, so that a step reaches one expert further where many are
             // needed.  Where the excess has not halved, rises go twice as far and falls half: a quarter of 32768 rows over 64 experts alike up
-            // to 3e-2, a quarter more room, 0.27 to 0.45 ms in 12 to 16 passes (without it 16 to 20, 0.30 to 0.62; nine passes are not
+            // to 3e-2, a quarter more room, 0.27 to 0.39 ms in 12 to 18 passes (without it 16 to 20, 0.30 to 0.62; nine passes are not
             // enough and the auction takes 1.3 to 1.6).  Other batches hardly ever come to it: 110 solves within 1 %.
             const bool slow = slack && 2ll * m2.excess > mt.excess;
             dp = damp ? dp - dp / kDamp : !slow ? dp : dp <= 0 ? dp / 2 : dp < (1 << 28) ? 2 * dp : dp;      // (a price has 31 bits)
