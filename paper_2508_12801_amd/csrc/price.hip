@@ -105,7 +105,8 @@ struct PriceMeta {
     int passes;       // price passes so far (the one that checks prices the caller has given is not counted)
     int excess;       // tokens too many in all, as the pass found them (a sample's count is scaled up)
     int far;          // 1: too far from the end when the passes were nearly used up; some more follow
-    int pad[2];
+    int together;     // spare capacity: the step that comes next moves the experts that have a price together
+    int pad;
 };
 
 // Control words and tables inside the workspace (WorkspaceLayout::price_off).
@@ -135,7 +136,7 @@ struct PriceArgs {
     int T, E, k, C, mode;
     int rows, n_wg;                               // of the final pass
     int ib, nb, bshift;                           // bits of a column id in a packed key; bins per side; their width
-    int es;                                       // columns of the histograms
+    int es, quads;                                // columns of the histograms; 16-byte pieces of 32-bit counts of a copy
     int copies;                                   // ... their copies, a power of two ...
     int half;                                     // ... with counts of 16 bits (no copy's can reach 2^16), else of 32
     int retry;                                    // the search has failed at the prices or the bound before
@@ -199,6 +200,16 @@ __device__ __forceinline__ unsigned row_mask(int row, int ib)      // equal valu
 // of a common step (7.9 -> 6.0 us).  Solves of 250 batches with 2 to 100 % of spare capacity take 0.88 of the time (0.83 at 64 to 128
 // experts, 0.92 to 0.95 at 16 and 32, 1.05 at 8).
 //
+// Rows that are nearly alike all move on to the same next expert, which no expert's own margins show: a step at the level reaches one expert
+// further where many are needed.  Where the excess has not halved, the level's rises go twice as far and its falls half, and the next step is
+// one of the other kind: the experts with a price move towards their mean demand one by one, and up together by what they have too many in all
+// (of each row the margin of the lowest hold that has a price to the best alternative that has none), the others as far as their own margins
+// say.  Neither kind gets there by itself.  Solves of 40 batches of 4096 to 65536 tokens to 16 to 256 experts, a twentieth to half of them
+// alike up to 0.1 or 3e-2 and 2 to 50 % more room than demand, against these steps alone (most then go on to the auction): 0.52 with the
+// level's alone, 0.42 in turn; a tenth of 16384 rows over 256 experts alike 1.83 and 0.90; a quarter of 32768 rows over 64 experts alike up
+// to 3e-2, a quarter more room, 0.21 to 0.25 ms in 10 or 11 passes, 0.25 to 0.39 in 10 to 18, and 0.19 to 0.28 in 10 to 14.  Other
+// batches hardly ever come to it: 100 solves within 1 %.
+//
 // Bound by latency, and by what the sixteen wavefronts do alike (four of them share a SIMD): sums are taken over the
 // wavefronts that have experts only, and the bound of the arc list is worked out by the last one beside the columns.  The largest
 // step is reduced by lane moves: an atomic maximum of all lanes on one word is compiled into a loop over the lanes (1.5 us).
@@ -230,25 +241,30 @@ __device__ __forceinline__ float wave_sum_f(float v)        // the total in lane
     return v;
 }
 
-// Behind step_clear and a barrier.  CUM: s.cum holds the sums of the bins already.  With spare capacity the columns of s_h are summed up.
-template <bool CUM>
+// Behind step_clear and a barrier.  CUM: s.cum holds the sums of the bins already.  SPARE: there may be spare capacity; the columns of s_h are
+// summed up with it.
+template <bool CUM, bool SPARE>
 __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const PriceMeta mt, int *s_h, StepLds &s)
 {
     constexpr int NW = kUThreads / 64;
-    static_assert(kPriceMaxE / 64 < NW - 1, "the last wavefront has no experts");
+    static_assert(kPriceMaxE / 64 < NW - 2, "the last two wavefronts have no experts");
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int E = a.E, ES = a.es, nb = a.nb, nwe = (E + 63) >> 6;
-    const bool slack = a.mode == kModeSlack, over_all = a.mode == kModeOver;
+    const bool spare = SPARE && a.mode == kModeSlack, together = spare && mt.together, slack = spare && !together, over_all = a.mode == kModeOver;
     const bool sampled = nrows < a.T;
     const int w0 = bin_w0(mt.w), bs = a.bshift;
     const int Ct = sampled ? (int)(((long long)a.C * nrows + a.T / 2) / a.T) : a.C;
     const int *s_hn = s_h + 2 * nb * ES;
     if (wv < nwe) {
         const int ne = tid < E ? s_hn[tid] : 0, over = tid < E && ne > Ct ? ne - Ct : 0;
-        const bool in = tid < E && (!slack || s.was[tid] > 0);
-        const int sn = wave_sum(ne), sx = wave_sum(over), sd = wave_sum(in && ne < Ct ? Ct - ne : 0);
+        const bool in = tid < E && (!spare || s.was[tid] > 0);
+        const int sn = wave_sum(in ? ne : 0), sx = wave_sum(over), sd = wave_sum(in && ne < Ct ? Ct - ne : 0);
         if (in ? over > kWorst || Ct - ne > kWorst : over > kWorst) s.worst = 1;
         if (lane == 63) *(int4 *)&s.part[wv][0] = make_int4(sn, sx, sd, 0);
+        if (together) {
+            const int ss = wave_sum(in ? 1 : 0), sz = wave_sum(in ? 0 : over);
+            if (lane == 63) *(int2 *)&s.part[wv][4] = make_int2(ss, sz);
+        }
     }
     // holds (0 .. nb-1) and newcomers (nb .. 2nb-1) per margin bin over all experts
     if constexpr (!CUM) {
@@ -266,25 +282,33 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
         }
     }
     __syncthreads();
-    int sn = 0, sx = 0, sd = 0;
+    int sn = 0, sx = 0, sd = 0, ss = 0, sz = 0;              // ss: experts whose price counts; sz: tokens too many at the others
     for (int x = 0; x < nwe; ++x) {
         const int4 p4 = *(const int4 *)&s.part[x][0];
         sn += p4.x;
         sx += p4.y;
         sd += p4.z;
+        if (together) {
+            const int2 p2 = *(const int2 *)&s.part[x][4];
+            ss += p2.x;
+            sz += p2.y;
+        }
     }
+    if (!together) ss = E;
     sx = sd > sx ? sd : sx;                                           // tokens too many or too few
     // enough: what is left is cheaper to move by the search
     const int excess = sampled ? (int)((long long)sx * a.T / nrows) : sx;
     const bool enough = !sampled && excess * (E <= 128 && !a.retry ? kEnough : 2 * kEnough) <= E && !s.worst;
     const bool moves = !enough || a.retry;               // (another try may have to go on all the same)
-    const int target = slack ? Ct : (2 * sn + E) / (2 * E);           // the capacity, or the mean demand
+    const int target = slack || ss == 0 ? Ct : (2 * sn + ss) / (2 * ss);      // the capacity, or the mean demand
     if (moves && wv * 64 < E + (over_all ? 1 : 0)) {
         const int j = tid;
         const bool common = j == E;
         const int pj = j <= E ? s.was[j] : 0;
+        const bool alone = together && pj == 0;              // (has no price: room is left there)
         int diff = 0;
-        if (j < E + (over_all ? 1 : 0)) diff = common ? sn - Ct * E : s_hn[j] - target;
+        if (j < E + (over_all ? 1 : 0)) diff = common ? sn - Ct * E : s_hn[j] - (alone ? Ct : target);
+        if (alone && diff < 0) diff = 0;
         const int side = diff < 0 ? 1 : 0, need = side ? -diff : diff;      // side 0: the price has to rise, side 1: to fall
         int most = 0;
         if (need != 0 || (slack && j < E)) {
@@ -337,6 +361,24 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
         if (!slack) {
             most = wave_max(most);           // (an atomic of every lane is compiled into a loop over the lanes)
             if (lane == 0 && most > 0) atomicMax(&s.maxd, most);
+        }
+    } else if (together && moves && wv == NW - 2) {
+        // up together, by what those that have a price and those that are about to get one have too many
+        const int need = sn - Ct * ss, x = lane < nb ? s_h[(2 * nb + 1) * ES + lane] : 0, cum = wave_sum(x);
+        if (need > 0) {
+            const unsigned long long far = __ballot(lane < nb && cum >= need + sz);
+            int d = mt.w;
+            if (far) {
+                const int b = __ffsll((long long)far) - 1, lo = bin_edge(b, w0, bs), hi = bin_edge(b + 1, w0, bs);
+                const int in_b = __builtin_amdgcn_readlane(x, b), before = __builtin_amdgcn_readlane(cum, b) - in_b;
+                d = lo + (int)((float)(hi - lo) * (float)(need + sz - before) * __builtin_amdgcn_rcpf((float)in_b) + 0.5f);
+                d = d < lo ? lo : d > hi ? hi : d;
+            }
+            if (lane == 0) {
+                if (!far) s.ran_out = 1;
+                s.lam = d < 1 ? 1 : d;
+                atomicMax(&s.maxd, s.lam);
+            }
         }
     } else if (wv == NW - 1) {
         // the bound of the arc list: about kArcsPerExpert exchanges per expert lie under it.  h holds and n newcomers make
@@ -429,27 +471,23 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
     m2.excess = excess;
     const bool listed = !a.retry || s.reach;             // another try needs more exchanges than the one before
     // stuck: it no longer shrinks (it ends up alternating by a few)
-    const bool stuck = m2.excess <= E && m2.excess * 5 >= mt.excess * 4 && t >= 4;
+    const bool stuck = m2.excess * (spare ? 4 : 1) <= E && m2.excess * 5 >= mt.excess * 4 && t >= 4;
     if (!sampled && (s.maxd == 0 || (listed && (enough || stuck)))) {
         m2.done = 1;
         m2.w = mt.w;
         if (m2.excess == 0) m2.bound = 2;                // nothing to move
         for (int e = tid; e < E; e += kUThreads) s.now[e] = s.was[e];
     } else {
-        const bool damp = !sampled && m2.excess <= E;
+        const bool damp = !sampled && m2.excess <= E, slow = spare && 2 * m2.excess > E && 2ll * m2.excess > mt.excess;
         const int plim = (1 << (31 - a.ib)) - 1;
         for (int e = tid; e < E; e += kUThreads) {
             int dp = s.now[e] - s.was[e];
-            // Rows that are nearly alike all move on to the same next expert, so that a step reaches one expert further where many are
-            // needed.  Where the excess has not halved, rises go twice as far and falls half: a quarter of 32768 rows over 64 experts alike up
-            // to 3e-2, a quarter more room, 0.27 to 0.39 ms in 12 to 18 passes (without it 16 to 20, 0.30 to 0.62; nine passes are not
-            // enough and the auction takes 1.3 to 1.6).  Other batches hardly ever come to it: 110 solves within 1 %.
-            const bool slow = slack && 2ll * m2.excess > mt.excess;
-            dp = damp ? dp - dp / kDamp : !slow ? dp : dp <= 0 ? dp / 2 : dp < (1 << 28) ? 2 * dp : dp;      // (a price has 31 bits)
-            int pn = s.was[e] + dp + (over_all ? s.lam : 0);
-            if (slack) pn = pn < 0 ? 0 : pn;
+            dp = damp ? dp - dp / kDamp : !(slow && slack) ? dp : dp <= 0 ? dp / 2 : dp < (1 << 28) ? 2 * dp : dp;      // (a price has 31 bits)
+            int pn = s.was[e] + dp + (over_all || (together && s.was[e] > 0) ? s.lam : 0);
+            if (spare) pn = pn < 0 ? 0 : pn;
             s.now[e] = pn > plim ? plim : (pn < -plim ? -plim : pn);
         }
+        if (slow) m2.together = !mt.together;
     }
     return m2;
 }
@@ -459,7 +497,7 @@ template <int N, int M, bool HALF>
 __device__ __forceinline__ void gather_copies(const PriceArgs &a, int *s_h, StepLds &s)
 {
     constexpr int Q = HALF ? 2 : 1;                                   // quads of counts in a piece
-    const int quads = (2 * a.nb + 1) * a.es / 4, pieces = (quads + Q - 1) / Q;
+    const int quads = a.quads, pieces = (quads + Q - 1) / Q;
     const float inv = __builtin_amdgcn_rcpf((float)(a.es / 4));       // (u + 1/2 quads are 1/2 from a row's edge: 1e-7 of 3000 is less)
     uint4 x[M][N];
 #pragma unroll
@@ -520,7 +558,7 @@ __global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, 
     const PriceMeta mt = ar->meta;
     if (mt.done) return;                 // (passes that find the prices done add nothing: the copies stay clear)
     __syncthreads();
-    PriceMeta m2 = price_step<true>(a, t, nrows, mt, s_h, s);
+    PriceMeta m2 = price_step<true, true>(a, t, nrows, mt, s_h, s);
     if (t == a.look) m2.far = m2.excess > kFar * E;
     for (int e = tid; e < E; e += kUThreads) ar->prices[e] = s.now[e];
     if (tid == 0) {
@@ -532,7 +570,7 @@ __global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, 
 
 // The margins of rows r_first .. r_end - 1 of a pass (row i is token i * stride + shift), added to the histograms in
 // s_hist; NT threads, G of them to a row.  nx holds this lane's part of its first row.
-template <int G, int EPL, bool OS, int NT>
+template <int G, int EPL, bool OS, bool TOGETHER, int NT>
 __device__ __forceinline__ void price_rows(const PriceArgs &a, int W, int r_first, int r_end, int stride, int shift, int (&nx)[EPL],
                                            const int *s_p, int *s_hist)
 {
@@ -596,6 +634,18 @@ __device__ __forceinline__ void price_rows(const PriceArgs &a, int W, int r_firs
             if (mg < W) atomicAdd(&s_hist[((real ? 0 : nb) + bin_of(mg, w0, bs)) * ES + E], 1);
         }
         if (!near) continue;
+        if (TOGETHER) {
+            unsigned held[EPL], free[EPL];
+#pragma unroll
+            for (int m = 0; m < EPL; ++m) {
+                const bool p = RK::col(m, lg) < E && pb[m] < bias;              // it has a price
+                held[m] = p && key[m] >= kth ? ~key[m] : 0u;
+                free[m] = p || key[m] >= kth ? 0u : key[m];
+            }
+            const unsigned h = ~RK::first(held), f = RK::first(free);
+            const int mg = (int)((h - f) >> ib);
+            if (lg == 0 && live && h != ~0u && f != 0u && mg < W) atomicAdd(&s_hist[(2 * nb + 1) * ES + bin_of(mg, w0, bs)], 1);
+        }
         if (live) {
 #pragma unroll
             for (int m = 0; m < EPL; ++m) {
@@ -613,7 +663,7 @@ __device__ __forceinline__ void price_rows(const PriceArgs &a, int W, int r_firs
 // passes 4.9 us at 16384 tokens of 64 experts, 10.2 at 256 experts and 11.0 at 65536 tokens of 128.  Two counts to an addition took
 // 5.7, 13.0 and 13.0, one, with half as many wavefronts to a table, 10.6, 20.1 and 18.3; without any of the additions it would be 4.0,
 // 6.2 and 7.1.
-template <int G, int EPL, bool OS>
+template <int G, int EPL, int MODE>
 __global__ __launch_bounds__(kQThreads) void k_price(PriceArgs a, int nrows, int stride, int shift, int rows_per_wg)
 {
     using RK = RowKeys<G, EPL>;
@@ -636,10 +686,12 @@ __global__ __launch_bounds__(kQThreads) void k_price(PriceArgs a, int nrows, int
     const PriceMeta mt = ar->meta;
     for (int e = tid; e < E; e += kQThreads) s_p[e] = ar->prices[e];
     if (mt.done) return;
-    const int hquads = (2 * nb + 1) * ES / 4;
+    const int hquads = a.quads;
     for (int i = tid; i < hquads; i += kQThreads) ((int4 *)s_hist)[i] = make_int4(0, 0, 0, 0);
     __syncthreads();
-    price_rows<G, EPL, OS, kQThreads>(a, mt.w, r_first, r_end, stride, shift, nx, s_p, s_hist);
+    // (the margins of the experts together in a loop of their own: a branch in the other one took 0.3 us of 5.9, 10007 rows of 96 experts)
+    if (MODE == kModeSlack && mt.together) price_rows<G, EPL, false, true, kQThreads>(a, mt.w, r_first, r_end, stride, shift, nx, s_p, s_hist);
+    else price_rows<G, EPL, MODE == kModeOver, false, kQThreads>(a, mt.w, r_first, r_end, stride, shift, nx, s_p, s_hist);
     __syncthreads();
     int *hg = ar->hist[blockIdx.x & (a.copies - 1)];
     for (int i = tid; i < hquads; i += kQThreads) {
@@ -666,12 +718,12 @@ __device__ __forceinline__ int first_price(const int64_t *__restrict__ prices_in
 }
 __device__ __forceinline__ PriceMeta first_meta(const PriceArea *ar, const int64_t *prices_in, int retry)
 {
-    return PriceMeta{retry ? ar->meta.w : kFirstWindow, 0, 2, retry ? ar->meta.passes : prices_in ? -1 : 0, 0x7fffffff, 0, {0, 0}};
+    return PriceMeta{retry ? ar->meta.w : kFirstWindow, 0, 2, retry ? ar->meta.passes : prices_in ? -1 : 0, 0x7fffffff, 0, 0, 0};
 }
 
 // All passes of a small batch in one workgroup: a pass takes 4 to 11 us (64 tokens of 8 experts: three in 11 us; 256 of 64: four in 46)
 // instead of two launches and their distance, none is launched in vain, and a batch that settles slowly may take more.
-template <int G, int EPL, bool OS>
+template <int G, int EPL, int MODE>
 __global__ __launch_bounds__(kUThreads) void k_price_small(PriceArgs a, int n_pass, int plim, const int64_t *__restrict__ prices_in)
 {
     using RK = RowKeys<G, EPL>;
@@ -680,7 +732,7 @@ __global__ __launch_bounds__(kUThreads) void k_price_small(PriceArgs a, int n_pa
     PriceArea *ar = a.ar;
     const int tid = threadIdx.x, lg = tid & (G - 1), grp = tid / G, E = a.E;
     const bool vec = (E & 3) == 0 && (((size_t)a.q) & 15) == 0;
-    const int hquads = (2 * a.nb + 1) * a.es / 4;
+    const int hquads = a.quads;
     PriceMeta mt = first_meta(ar, prices_in, a.retry);
     if (tid == 0 && !a.retry) ar->t_start = wall_clock64();
     for (int e = tid; e < kPStride; e += kUThreads) s.was[e] = e >= E ? 0 : a.retry ? ar->prices[e] : first_price(prices_in, e, E, plim);
@@ -690,11 +742,12 @@ __global__ __launch_bounds__(kUThreads) void k_price_small(PriceArgs a, int n_pa
         RK::load(a.q + (size_t)(grp < a.T ? grp : a.T - 1) * E, E, vec, lg, nx);
         for (int i = tid; i < hquads; i += kUThreads) ((int4 *)s_hist)[i] = make_int4(0, 0, 0, 0);
         __syncthreads();
-        price_rows<G, EPL, OS, kUThreads>(a, mt.w, 0, a.T, 1, 0, nx, s.was, s_hist);
+        if (MODE == kModeSlack && mt.together) price_rows<G, EPL, false, true, kUThreads>(a, mt.w, 0, a.T, 1, 0, nx, s.was, s_hist);
+        else price_rows<G, EPL, MODE == kModeOver, false, kUThreads>(a, mt.w, 0, a.T, 1, 0, nx, s.was, s_hist);
         for (int e = tid; e < E; e += kUThreads) s.now[e] = s.was[e];
         step_clear(s);
         __syncthreads();
-        mt = price_step<false>(a, t, a.T, mt, s_hist, s);
+        mt = price_step<false, MODE == kModeSlack>(a, t, a.T, mt, s_hist, s);
         __syncthreads();
         for (int e = tid; e < E; e += kUThreads) s.was[e] = s.now[e];
     }
@@ -1660,6 +1713,7 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     a.nb = price_bins(E);
     a.bshift = E <= 256 ? 22 : 23;
     a.es = price_columns(E, a.mode != kModeOver);
+    a.quads = price_table_ints(E, a.mode != kModeOver, a.mode == kModeSlack) / 4;
 
     int G, EPL, rows;
     if (!price_shape(T, E, k, G, EPL, rows, a.n_wg) || a.n_wg > L.max_wg) return MAXSCORE_ERR_SHAPE;
@@ -1672,17 +1726,16 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     int32_t mrc = MAXSCORE_OK;                    // (timing marks)
     auto mark = [&] { mrc = mrc ? mrc : solver_mark(s); };
     const bool os = a.mode == kModeOver;
-    const size_t shm = sizeof(int) * (size_t)price_table_ints(E, a.mode != kModeOver);
-    const int hquads = price_table_ints(E, a.mode != kModeOver) / 4;
+    const size_t shm = sizeof(int4) * (size_t)a.quads;
     int n_pass = n_sampled + (retry ? kRetryPasses : a.mode == kModeSlack ? kSlackPasses : kTightPasses);
     const bool small = (long long)T * G <= kSmallThreads && (long long)T * E <= kSmallEntries && shm + sizeof(StepLds) <= 64 * 1024;
     const int plim = (1 << (31 - a.ib)) - 1;
     geom->one_launch = small ? 1 : 0;
     if (!small)
-        hipLaunchKernelGGL(k_price_init, dim3(64), dim3(kPThreads), 0, s, a.ar, hquads, E, plim, prices_in, a.retry);
+        hipLaunchKernelGGL(k_price_init, dim3(64), dim3(kPThreads), 0, s, a.ar, a.quads, E, plim, prices_in, a.retry);
     for (int t = small ? n_pass : 0; t <= n_pass; ++t) {
         // Pass t is enqueued when pass t - 2 has ended, so that one stays queued behind the one that runs: a pass that is still
-        // queued when the prices are done costs two empty launches (5 us; a batch with room to spare needs one of nine).
+        // queued when the prices are done costs two empty launches (5 us; a batch with room to spare needs one of eighteen).
         // The stream is looked at now and then: a stream that has drained or failed ends the wait.
         for (unsigned spin = 1; t >= 2 && !small && !hw[kPriceWordDone] && (hw[kPriceWordPasses] & ((1 << kPriceFarBit) - 1)) < t - 1; ++spin) {
             if ((spin & 4095) == 0 && hipStreamQuery(s) != hipErrorNotReady) break;
@@ -1701,8 +1754,9 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
         if (fin) {                                                                                                        \
             if (small) {                                                                                                  \
                 mark();                                                                                                   \
-                if (os) hipLaunchKernelGGL((k_price_small<GG, PP, true>), dim3(1), dim3(kUThreads), shm, s, a, kSmallPasses, plim, prices_in); \
-                else hipLaunchKernelGGL((k_price_small<GG, PP, false>), dim3(1), dim3(kUThreads), shm, s, a, kSmallPasses, plim, prices_in);   \
+                if (a.mode == kModeTight) hipLaunchKernelGGL((k_price_small<GG, PP, kModeTight>), dim3(1), dim3(kUThreads), shm, s, a, kSmallPasses, plim, prices_in); \
+                else if (os) hipLaunchKernelGGL((k_price_small<GG, PP, kModeOver>), dim3(1), dim3(kUThreads), shm, s, a, kSmallPasses, plim, prices_in); \
+                else hipLaunchKernelGGL((k_price_small<GG, PP, kModeSlack>), dim3(1), dim3(kUThreads), shm, s, a, kSmallPasses, plim, prices_in); \
                 mark();                                                                                                   \
                 mark();                                                                                                   \
             }                                                                                                             \
@@ -1710,8 +1764,9 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
             else hipLaunchKernelGGL((k_price_assign<GG, PP, false>), dim3(grid), dim3(kPThreads), 0, s, a);       \
         } else {                                                                                                          \
             mark();                                                                                                       \
-            if (os) hipLaunchKernelGGL((k_price<GG, PP, true>), dim3(grid), dim3(kQThreads), shm, s, a, nrows, st, shift, rw); \
-            else hipLaunchKernelGGL((k_price<GG, PP, false>), dim3(grid), dim3(kQThreads), shm, s, a, nrows, st, shift, rw);   \
+            if (a.mode == kModeTight) hipLaunchKernelGGL((k_price<GG, PP, kModeTight>), dim3(grid), dim3(kQThreads), shm, s, a, nrows, st, shift, rw); \
+            else if (os) hipLaunchKernelGGL((k_price<GG, PP, kModeOver>), dim3(grid), dim3(kQThreads), shm, s, a, nrows, st, shift, rw); \
+            else hipLaunchKernelGGL((k_price<GG, PP, kModeSlack>), dim3(grid), dim3(kQThreads), shm, s, a, nrows, st, shift, rw); \
             mark();                                                                                                       \
         }                                                                                                                 \
     } while (0)
@@ -1733,7 +1788,7 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
 #define MS_U(NN)                                                                                                          \
     do {                                                                                                                  \
         if (!a.half) hipLaunchKernelGGL((k_price_update<NN, price_pieces(false), false>), dim3(1), dim3(kUThreads), shm, s, a, t, nrows, words_dev); \
-        else if (hquads <= 2 * kUThreads) hipLaunchKernelGGL((k_price_update<NN, 1, true>), dim3(1), dim3(kUThreads), shm, s, a, t, nrows, words_dev); \
+        else if (a.quads <= 2 * kUThreads) hipLaunchKernelGGL((k_price_update<NN, 1, true>), dim3(1), dim3(kUThreads), shm, s, a, t, nrows, words_dev); \
         else hipLaunchKernelGGL((k_price_update<NN, price_pieces(true), true>), dim3(1), dim3(kUThreads), shm, s, a, t, nrows, words_dev); \
     } while (0)
             if (a.copies == 8) MS_U(8);

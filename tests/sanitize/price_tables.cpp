@@ -16,6 +16,12 @@ int main()
                 std::printf("E=%d extra=%d: %d words written, a copy has %d\n", E, extra, written, kPTableInts);
                 ++bad;
             }
+            // (with spare capacity one more row of bins)
+            const int more = price_table_ints(E, true, true) - price_table_ints(E, true);
+            if (more < bins || more % 4 != 0 || price_table_ints(E, true, true) > kPTableInts) {
+                std::printf("E=%d: %d more words with spare capacity\n", E, more);
+                ++bad;
+            }
         }
     std::puts(bad ? "tables overlap" : "ok");
     return bad != 0;

@@ -96,7 +96,40 @@ def test_near_copies_with_spare_room(ms, seed):
     q = ms.softtopk(torch.from_numpy(make_logits("cfg4b_near", seed)).cuda(), c["k"], c["t"])[1]
     st = ms.assign_i32(q, c["k"], c["C"])["stats"]
     auction = ms.assign_i32(q, c["k"], c["C"], finisher=False)["stats"]
-    assert st["total_score_q"] == auction["total_score_q"] and st["rounds"] <= 20 + 4
+    assert st["total_score_q"] == auction["total_score_q"] and st["rounds"] <= 14
+    assert (st["phases"], st["finish_passes"]) == (1, 1)               # the price solve, at its first try
+
+
+@pytest.mark.parametrize("k,noise,passes", [(4, 0.1, 14), (8, 0.1, 10), (2, 0.1, 15)])
+def test_few_near_copies_with_spare_room(ms, k, noise, passes):
+    """A tenth of the rows alike, many experts: the steps of both kinds, at the auction's optimum."""
+    print(f"few near copies k={k} noise={noise}", flush=True)
+    T, E = 16384, 256
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    logits = torch.randn(T, E, generator=gen, device="cuda")
+    n = T // 10
+    logits[:n] = logits[0] + noise * torch.randn(n, E, generator=gen, device="cuda")
+    q = ms.softtopk(logits, k, 1.0)[1]
+    C = -(-5 * T * k // (4 * E))
+    st = ms.assign_i32(q, k, C)["stats"]
+    auction = ms.assign_i32(q, k, C, finisher=False)["stats"]
+    assert st["total_score_q"] == auction["total_score_q"]
+    assert (st["phases"], st["finish_passes"]) == (1, 1) and st["rounds"] <= passes
+
+
+@pytest.mark.parametrize("T,E,k,C", [(64, 8, 2, 20), (96, 6, 1, 18), (500, 8, 3, 200), (900, 33, 2, 60), (2000, 257, 1, 9), (131080, 8, 2, 36000)])
+def test_copies_on_the_edges(ms, T, E, k, C):
+    """Half the rows alike up to 3e-2 where the steps' tables are at their edges: passes of one workgroup, column counts off the pieces, bins
+    of one an octave, sampled passes."""
+    print(f"copies on the edges T={T} E={E} k={k} C={C}", flush=True)
+    rng = np.random.default_rng(T + E)
+    L = rng.standard_normal((T, E)).astype(np.float32)
+    L[: T // 2] = L[0] + 0.03 * rng.standard_normal((T // 2, E)).astype(np.float32)
+    q = ms.softtopk(torch.from_numpy(L).cuda(), k, 1.0)[1]
+    out, plain = ms.assign_i32(q, k, C), ms.assign_i32(q, k, C, finisher=False)
+    assert out["stats"]["total_score_q"] == plain["stats"]["total_score_q"]
+    a = out["assign"].cpu().numpy()
+    assert (a >= 0).all() and np.bincount(a.ravel(), minlength=E).max() <= C and (np.diff(np.sort(a, axis=1), axis=1) > 0).all()
 
 
 @pytest.mark.parametrize("T,E,k,room,part,noise", [(16384, 64, 8, 1.0, 0.5, 0.1), (16384, 64, 8, 1.0, 0.1, 0.03), (16384, 64, 8, 0.75, 0.25, 0.03),
@@ -114,3 +147,4 @@ def test_near_copies_without_spare_room(ms, T, E, k, room, part, noise):
     st = ms.assign_i32(q, k, C)["stats"]
     auction = ms.assign_i32(q, k, C, finisher=False)["stats"]
     assert st["total_score_q"] == auction["total_score_q"] and st["rounds"] < 24
+    assert (st["phases"], st["finish_passes"]) == (1, 1)
