@@ -22,6 +22,7 @@
 #include <climits>
 
 #include "common.h"
+#include "iter_tail.h"
 #include "row_keys.h"
 
 namespace maxscore {
@@ -34,10 +35,6 @@ struct IterState {
 };
 
 constexpr int kIterRows = 64, kScanThreads = 1024;
-// Pairs that one workgroup takes through the rounds that are left: as many as it proposes for in the time of a round of two launches
-// (a row takes 150 instructions of eight lanes, and one compute unit issues them all: with 2048 pairs 14493 tokens of 32 experts 193 us a
-// call, with 1024 173).
-constexpr int kTailMost = 1024, kTailEntries = 1 << 16, kTailSlots = 8192, kTailMaxK = 32, kTailMaxBlocks = 8192;
 constexpr int kIterEnds = INT_MAX;                        // progress: steps that have begun, or that the last one has
 constexpr int kIterWordProgress = 1, kIterWordFlow = 2, kIterWordRounds = 3, kIterWordOpen = 10, kIterWordTotal = 8;
 
@@ -444,14 +441,6 @@ __device__ __forceinline__ int iter_best(const int (&v)[EPL], unsigned live, int
     }
 }
 
-// LDS of the tail, in words: tokens, open slots and slots of its rows, room and proposals per expert, its pairs twice, their proposals
-// (half words), proposals per (64 pairs, expert), before that open slots per (64 rows, slot).  The blocks' first rows lie where the pairs go.
-inline int tail_words(int most, int E, int k, int n_wg)
-{
-    const int tiles = (most + 63) / 64, pairs = 2 * most + (most + 1) / 2, tab = tiles * std::max(E, kTailMaxK) + 1;
-    return (2 + k) * most + 2 * E + std::max(pairs + tab, n_wg + 1);
-}
-
 // Rounds r, r + 1, ... of the pairs the step has listed, in one workgroup: round by round a proposal of every pair, by G lanes each; a
 // rank among the proposals for an expert without room for all of them; the pairs that were turned away go on, in their order (slot,
 // token).  A pair that finds nobody to ask drops out: from round to round a token's open slots do not lose more slots before it than
@@ -842,7 +831,7 @@ int32_t iter_run(const int32_t *q, int T, int E, int k, int C, int max_rounds, i
     while (G * 16 < E) G *= 2;
     while (G * EPL < E) EPL *= 2;
     const size_t shm = sizeof(int) * ((size_t)2 * kIterRows * k + 6 * (size_t)E);
-    a.tail = k <= kTailMaxK && a.n_wg <= kTailMaxBlocks ? std::min({kTailMost, kTailEntries / E, kTailSlots / k}) : -1;
+    a.tail = tail_most(E, k, a.n_wg);
     a.scan = std::min(kScanThreads, std::max(64, (k * a.n_wg + 511) / 512 * 64));       // eight tiles each
     const int threads = a.tail > 0 ? kScanThreads : a.scan;
     const size_t tail_shm = a.tail > 0 ? sizeof(int) * (size_t)tail_words(a.tail, E, k, a.n_wg) : 0;

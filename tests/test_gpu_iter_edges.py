@@ -72,3 +72,17 @@ def test_last_rounds(ms, T, E, k, C, hi, max_rounds):
     out = ms.assign_iter_i32(torch.from_numpy(q.astype(np.int32)).cuda(), k, C, max_rounds=max_rounds, allow_not_converged=True)
     assert np.array_equal(out["assign"].cpu().numpy(), ref["assign"])
     assert (out["total"], out["flow"], out["rounds"]) == (ref["total"], ref["flow"], ref["rounds"])
+
+
+@pytest.mark.parametrize("T", [358336, 358337])
+def test_last_rounds_of_many_blocks(ms, T):
+    """Eight slots of 16 experts at the largest number of 64-token blocks whose first rows fit beside a workgroup's rounds, and one more."""
+    E, k = 16, 8
+    C = T * k // E + T // 100
+    print(f"iter many blocks T={T}", flush=True)
+    rng = np.random.default_rng(T)
+    q = (rng.random((T, E)) * 1e6).astype(np.int64) + (rng.random(E) * 1e5).astype(np.int64)
+    ref = oracle.iter_reroute(q, k, C)
+    out = ms.assign_iter_i32(torch.from_numpy(q.astype(np.int32)).cuda(), k, C, allow_not_converged=True)
+    assert np.array_equal(out["assign"].cpu().numpy(), ref["assign"])
+    assert (out["total"], out["flow"], out["rounds"]) == (ref["total"], ref["flow"], ref["rounds"])

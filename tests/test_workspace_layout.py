@@ -23,3 +23,10 @@ def test_iterative_assignment_fits(tmp_path):
     r = subprocess.run([exe], stdout=subprocess.PIPE, text=True)
     print(r.stdout)
     assert r.returncode == 0, r.stdout
+
+
+def test_the_last_rerouting_rounds_fit_one_launch(tmp_path):
+    exe = str(tmp_path / "iter_tail")
+    subprocess.check_call(["g++", "-std=c++17", "-I", CSRC, os.path.join(SAN, "iter_tail.cpp"), "-o", exe])
+    r = subprocess.run([exe], stdout=subprocess.PIPE, text=True)
+    assert r.returncode == 0, r.stdout
