@@ -200,6 +200,7 @@ def _workspace(T, E, k, C, device, d=0):
 
 
 ASSIGNMENTS = {"exact": 0, "iter": 1}
+MAX_EXPERTS = 1024
 
 
 FLAG_NO_TAIL_PASS = 1
@@ -609,8 +610,10 @@ def route_xw(x, W, bias, k: int, C: int, t: float = 1.0, quant_shift: int = 20, 
     assert W.shape[0] == d and x.is_contiguous() and W.is_contiguous() and x.dtype == W.dtype
     stats = Stats()
     opts = _opts(t, quant_shift, max_rounds, eps_div, assignment)
-    if out is None:
-        # The projection is under way while the other outputs are allocated (eight of them, 10 us).
+    # The projection is under way while the other outputs are allocated (eight of them, 10 us), unless the assignment would refuse the call
+    # then: more demand than capacity takes k more experts (everything else the projection's call checks as well).
+    refused = opts.assignment == ASSIGNMENTS["exact"] and T * k > E * min(C, T) and E + k > MAX_EXPERTS
+    if out is None and not refused:
         scored = _score_outputs(T, E, x.device)
         scored["logits"] = torch.empty((T, E), dtype=torch.float32, device=x.device) if want_logits else None
         ws, need = _workspace(T, E, k, C, x.device, d)
@@ -628,7 +631,7 @@ def route_xw(x, W, bias, k: int, C: int, t: float = 1.0, quant_shift: int = 20, 
             return o
         # (refused: the one call below says why)
     else:
-        o = out
+        o = out if out is not None else _route_outputs(T, E, k, x.device)
         if "logits" not in o:
             o["logits"] = torch.empty((T, E), dtype=torch.float32, device=x.device) if want_logits else None
         ws, need = _workspace(T, E, k, C, x.device, d)

@@ -92,6 +92,33 @@ def test_routing_from_rewards_checks_its_arguments(lib):
     assert call(T=40, E=1000, k=30, C=1) == -6
 
 
+def test_a_refused_call_projects_nothing(lib, monkeypatch):
+    """route_xw with its own outputs starts with the projection, which must not run where the assignment refuses the call."""
+    import torch
+    calls = []
+
+    class Recorder:
+        def __getattr__(self, name):
+            fn = getattr(lib, name)
+            return lambda *a: (calls.append(name), fn(*a))[1]
+
+    T, d, E, k = 40, 64, 1000, 30
+    need = ms.workspace_bytes(T, d, E, k, 1)
+    area = torch.empty(need + 256, dtype=torch.uint8)
+    ws = area[-area.data_ptr() % 256:]
+    monkeypatch.setattr(binding, "_torch", lambda: torch)
+    monkeypatch.setattr(binding, "_stream", lambda: None)
+    monkeypatch.setattr(binding, "_workspace", lambda *a: (ws, need))
+    monkeypatch.setattr(binding, "load_library", lambda: Recorder())
+    x, W = torch.zeros(T, d), torch.zeros(d, E)
+    with pytest.raises(ms.MaxScoreError) as e:
+        binding.route_xw(x, W, None, k, 1)
+    assert e.value.code == -6 and calls[0] == "maxscore_route_xw"
+    assert "maxscore_router_softtopk" not in calls
+    assert binding.MAX_EXPERTS == int(re.search(r"constexpr int kMaxE = (\d+)", open(os.path.join(
+        ROOT, "paper_2508_12801_amd", "csrc", "common.h")).read()).group(1))
+
+
 def test_compute_without_gpu_fails_loudly():
     import torch
     if torch.cuda.is_available():
