@@ -106,7 +106,7 @@ struct PriceMeta {
     int excess;       // tokens too many in all, as the pass found them (a sample's count is scaled up)
     int far;          // 1: too far from the end when the passes were nearly used up; some more follow
     int together;     // spare capacity: the step that comes next moves the experts that have a price together
-    int pad;
+    int stalled;      // ... the last pass found few tokens less than the one before it
 };
 
 // Control words and tables inside the workspace (WorkspaceLayout::price_off).
@@ -206,8 +206,8 @@ __device__ __forceinline__ unsigned row_mask(int row, int ib)      // equal valu
 // (of each row the margin of the lowest hold that has a price to the best alternative that has none), the others as far as their own margins
 // say.  Neither kind gets there by itself.  Solves of 40 batches of 4096 to 65536 tokens to 16 to 256 experts, a twentieth to half of them
 // alike up to 0.1 or 3e-2 and 2 to 50 % more room than demand, against these steps alone (most then go on to the auction): 0.52 with the
-// level's alone, 0.42 in turn; a tenth of 16384 rows over 256 experts alike 1.83 and 0.90; a quarter of 32768 rows over 64 experts alike up
-// to 3e-2, a quarter more room, 0.21 to 0.25 ms in 10 or 11 passes, 0.25 to 0.39 in 10 to 18, and 0.19 to 0.28 in 10 to 14.  Other
+// level's alone, 0.41 in turn; a tenth of 16384 rows over 256 experts alike 1.83 and 0.96; a quarter of 32768 rows over 64 experts alike up
+// to 3e-2, a quarter more room, 0.21 to 0.25 ms in 10 or 11 passes, 0.25 to 0.39 in 10 to 18, and 0.19 to 0.28 in 10 to 13.  Other
 // batches hardly ever come to it: 100 solves within 1 %.
 //
 // Bound by latency, and by what the sixteen wavefronts do alike (four of them share a SIMD): sums are taken over the
@@ -470,8 +470,10 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
     ++m2.passes;
     m2.excess = excess;
     const bool listed = !a.retry || s.reach;             // another try needs more exchanges than the one before
-    // stuck: it no longer shrinks (it ends up alternating by a few)
-    const bool stuck = m2.excess * (spare ? 4 : 1) <= E && m2.excess * 5 >= mt.excess * 4 && t >= 4;
+    // stuck: it no longer shrinks (it ends up alternating by a few); with spare capacity the step of the other kind is to be tried first, unless
+    // there are few left (16384 tokens, a tenth of them alike, to 8 of 256: a search of 137 tokens took longer than the passes it saved)
+    const bool stalls = m2.excess <= E && m2.excess * 5 >= mt.excess * 4 && t >= 4, stuck = stalls && (!spare || 4 * m2.excess <= E || (mt.stalled && 2 * m2.excess <= E));
+    m2.stalled = stalls;
     if (!sampled && (s.maxd == 0 || (listed && (enough || stuck)))) {
         m2.done = 1;
         m2.w = mt.w;
