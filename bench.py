@@ -36,7 +36,7 @@ def hbm_frac(nbytes, ms):
     return nbytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS if ms > 0 else None
 
 
-def solver_roofline(st: dict, T: int, E: int, k: int, solve_ms: float, gd_ms: float, sampled=2):
+def solver_roofline(st: dict, T: int, E: int, k: int, solve_ms: float, gd_ms: float):
     """The assignment + gates + dispatch passes as a whole: the algorithmic bytes of the rounds that the solver executed, over
     its device time and that of gates + dispatch.  `st`: statistics of a solve with kernel timing on."""
     price = st["phases"] == 1 and st["finish_passes"] == 1       # otherwise the auction has solved it
@@ -45,10 +45,10 @@ def solver_roofline(st: dict, T: int, E: int, k: int, solve_ms: float, gd_ms: fl
     # assignment and scores at the assigned pairs; gates, the two dispatch lists and the positions
     gd_bytes = T * k * (4 + 4 + 4) + T * k * (4 + 4) + T * k * 12 + 4 * (E + 1)
     if price:
-        # a pass reads the rewards (the first `sampled` ones 8192 rows of them); the last one, which is not among the
-        # rounds, reads them and writes the assignment and the counts per block; the few thousand rows that the search
+        # a pass reads the rewards (from 131072 tokens on the first two 8192 rows of them); the last one, which is not among the
+        # rounds, reads them and writes the assignment and the counts per block; the few rows that the search
         # reads are not counted
-        sampled = sampled if T >= 2 * 8192 else 0
+        sampled = 2 if T >= 16 * 8192 else 0
         passes = [8192 * E * 4] * min(sampled, st["rounds"]) + [q_bytes] * max(st["rounds"] - sampled, 0)
         solver_bytes = sum(passes) + q_bytes + pair_bytes + count_bytes
         first, second = ("k_price", sum(passes) / max(len(passes), 1)), ("k_price_update", None)
@@ -187,7 +187,7 @@ def main():
     # gates + dispatch as the routing calls run them: from the solver's counts per block, two launches (the separate
     # maxscore_gates / maxscore_dispatch entry points are timed above)
     gd_ms = sorted(ms.route_scores(out["scores"], k, C)["stats"]["gates_dispatch_ms"] for _ in range(5))[2]
-    roofline = solver_roofline(st, T, E, k, solve_ms, gd_ms, sampled=2 if T >= 131072 else 0)     # (the solver samples from there on)
+    roofline = solver_roofline(st, T, E, k, solve_ms, gd_ms)
     if args.config == "cfg5":
         roofline["traffic"] = profile_value("pass_cfg5_pmc_traffic.txt", "pass_traffic_bytes")
     # plain copy kernel of the same footprint: achievable-bandwidth reference
