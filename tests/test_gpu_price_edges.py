@@ -70,6 +70,8 @@ def test_spare_room(ms, T, E, k, room, uneven):
     a = out["assign"].cpu().numpy()
     P = oracle.assignment_matrix(a, E)
     assert (P.sum(axis=1) == k).all() and P.sum(axis=0).max() <= C and oracle.verify_optimal(q, P, k, C)["optimal"]
+    if E < 512:
+        assert (out["stats"]["phases"], out["stats"]["finish_passes"]) == (1, 1)         # not by the auction
     again = ms.assign_i32(out["q"], k, C, prices_in=out["prices"])
     assert again["stats"]["total_score_q"] == out["stats"]["total_score_q"]
 
@@ -97,7 +99,7 @@ def test_near_copies_with_spare_room(ms, seed):
     st = ms.assign_i32(q, c["k"], c["C"])["stats"]
     auction = ms.assign_i32(q, c["k"], c["C"], finisher=False)["stats"]
     assert st["total_score_q"] == auction["total_score_q"] and st["rounds"] <= 14
-    assert (st["phases"], st["finish_passes"]) == (1, 1)               # the price solve, at its first try
+    assert (st["phases"], st["finish_passes"]) == (1, 1)               # not by the auction
 
 
 @pytest.mark.parametrize("k,noise,passes", [(4, 0.1, 14), (8, 0.1, 10), (2, 0.1, 15)])

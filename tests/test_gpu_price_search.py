@@ -91,6 +91,8 @@ def test_moved_tokens_and_their_places(T, E, k, room, uneven):
     assert int(filled.sum()) == min(T * k, E * C) and np.bincount(a[filled], minlength=E).max() <= C
     assert int(np.take_along_axis(q, np.where(filled, a, 0).astype(np.int64), axis=1)[filled].sum()) == r["stats"]["total_score_q"]
     if room >= 1:
+        st = r["stats"]                      # (an auction would end at the same optimum)
+        assert (st["phases"], st["finish_passes"]) == (1, 1) and st["finish_cycles"] >= 5
         P = oracle.assignment_matrix(a, E)
         assert oracle.verify_optimal(q, P, k, C)["optimal"]
     d = oracle.dispatch(a, r["gates"].cpu().numpy(), E)
