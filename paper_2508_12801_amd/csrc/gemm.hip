@@ -392,7 +392,7 @@ __global__ __launch_bounds__(256) void k_gemm_bf16_wtc(const unsigned short *__r
             for (int pass = 0; pass < 2; ++pass) {
                 const int r_local = 8 * pass + rl;
                 const int row = row0 + wave * RW + 16 * half + r_local;
-                if (row >= T) continue;          // (rows of zeros are all ties: 10 to 17 us at a batch that is no multiple of 128)
+                if (row >= T) continue;          // (rows beyond the batch; 10 to 17 us at one that is no multiple of 128, while they were zeros and all ties)
                 float xv[EPLS];
 #pragma unroll
                 for (int m = 0; m < EPLS; m += 4) {

@@ -15,8 +15,8 @@
 //                 the blocks before, slot by slot, tell how many of a block's proposals there is room for
 // Once few pairs are left the step makes a list of them and a workgroup of the scan goes through all further rounds (iter_tail).
 // The next round is enqueued when the step of one has begun; the first round without proposals, or of which no expert has room left, or
-// the tail ends them, and what follows is enqueued while that runs.  All bound by latency: a step 6 to 8 us, a scan 5 to 7, the tail 26 for
-// five rounds.  A layer of 44032 tokens, 64 experts, top-2: 319 us with nine rounds of two launches, two of them enqueued ahead and what
+// the tail ends them, and what follows is enqueued while that runs.  All bound by latency: a step 6 to 8 us, a scan 6 to 7, the tail 25 for
+// four rounds.  (The tail's LDS and threads cost a scan 0.5 us; as a kernel of its own it costs a launch instead, which is as much.)  A layer of 44032 tokens, 64 experts, top-2: 319 us with nine rounds of two launches, two of them enqueued ahead and what
 // follows behind the host's wait, 296 now; route_logits of 60 batches of 64 to 65536 tokens to 8 to 256 experts 15 % less on average.
 #include <algorithm>
 #include <climits>

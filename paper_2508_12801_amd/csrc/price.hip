@@ -86,16 +86,16 @@ constexpr int kDamp = 8;
 constexpr int kSmallEntries = 1 << 16;            // rewards of a batch that one workgroup passes over by itself
 constexpr int kSmallThreads = 4096;               // ... with this many lanes at work in all
 constexpr int kSmallPasses = kPriceTryPasses;
-constexpr int kSampledPasses = 2, kTightPasses = 6, kSlackPasses = 18, kRetryPasses = 4;
-static_assert(kSampledPasses + kSlackPasses <= kPriceTryPasses && kSampledPasses + kTightPasses + 4 <= kPriceTryPasses, "the round cap of a call allows every pass");
-constexpr int kPRowsMax = 128;                    // rows of a block of the final pass at most
-constexpr int kPriceWordDone = 0, kPriceWordPasses = 1;      // pinned words of the calling thread
-constexpr int kPriceFarBit = 16;                             // of the passes' word, from a pass that found more than kFar tokens per expert to move
 // Where demand and capacity leave no room, rows that are nearly alike need more passes than others, and what more than eight tokens per expert
 // have to be moved the search does not take on.  Whether they are needed shows two passes before the last, when the host decides (later it
 // would cost every batch two empty launches).  16384 rows over 64 experts, top-8, half of them alike up to 0.1: 179 us in ten passes, a tenth
 // alike up to 3e-2 222 us, with a quarter less room and a quarter of them alike 190 us; in six passes the auction took over, 1.2 to 6.8 ms.
 constexpr int kFar = 4, kFarPasses = 4;
+constexpr int kSampledPasses = 2, kTightPasses = 6, kSlackPasses = 18, kRetryPasses = 4;
+static_assert(kSampledPasses + kSlackPasses <= kPriceTryPasses && kSampledPasses + kTightPasses + kFarPasses <= kPriceTryPasses, "the round cap of a call allows every pass");
+constexpr int kPRowsMax = 128;                    // rows of a block of the final pass at most
+constexpr int kPriceWordDone = 0, kPriceWordPasses = 1;      // pinned words of the calling thread
+constexpr int kPriceFarBit = 16;                             // of the passes' word, from a pass that found more than kFar tokens per expert to move
 enum { kModeTight = 0, kModeSlack = 1, kModeOver = 2 };
 
 struct PriceMeta {
@@ -208,7 +208,7 @@ __device__ __forceinline__ unsigned row_mask(int row, int ib)      // equal valu
 // alike up to 0.1 or 3e-2 and 2 to 50 % more room than demand, against these steps alone (most then go on to the auction): 0.52 with the
 // level's alone, 0.41 in turn; a tenth of 16384 rows over 256 experts alike 1.83 and 0.96; a quarter of 32768 rows over 64 experts alike up
 // to 3e-2, a quarter more room, 0.21 to 0.25 ms in 10 or 11 passes, 0.25 to 0.39 in 10 to 18, and 0.19 to 0.28 in 10 to 13.  Other
-// batches hardly ever come to it: 100 solves within 1 %.
+// batches hardly ever come to it: 50 solves within 1 %.
 //
 // Bound by latency, and by what the sixteen wavefronts do alike (four of them share a SIMD): sums are taken over the
 // wavefronts that have experts only, and the bound of the arc list is worked out by the last one beside the columns.  The largest
@@ -723,7 +723,7 @@ __device__ __forceinline__ PriceMeta first_meta(const PriceArea *ar, const int64
     return PriceMeta{retry ? ar->meta.w : kFirstWindow, 0, 2, retry ? ar->meta.passes : prices_in ? -1 : 0, 0x7fffffff, 0, 0, 0};
 }
 
-// All passes of a small batch in one workgroup: a pass takes 4 to 11 us (64 tokens of 8 experts: three in 11 us; 256 of 64: four in 46)
+// All passes of a small batch in one workgroup: a pass takes 4 to 11 us (64 tokens of 8 experts: three to five in 9 us; 256 of 64: 28)
 // instead of two launches and their distance, none is launched in vain, and a batch that settles slowly may take more.
 template <int G, int EPL, int MODE>
 __global__ __launch_bounds__(kUThreads) void k_price_small(PriceArgs a, int n_pass, int plim, const int64_t *__restrict__ prices_in)
@@ -994,9 +994,9 @@ __device__ __forceinline__ int moved_slot(int u) { return (u ^ (u >> 10)) & (kMo
 // they are, as the arc of the path has none left: the potentials of a and b make up for the difference in value.  So a search reads no
 // row, and the list neither grows nor keeps arcs that are gone.  The moves are made at the end, where what the list then lacks of a moved
 // token is checked.  With unfilled slots (OS) a token that gives one up may still have others, which its arcs do not say: there the arcs
-// of moved tokens are listed anew, from their rows, in every search.  In the kernel's own clock, rows read in every search against moves at
-// the end: 65536 tokens of 128 experts 66 and 101 (two instances) -> 50 and 76 us, 16384 of 256 145 and 115 -> 93 and 73, 10007 of 96 80 ->
-// 64, 16384 of 64 45 -> 35, 4096 of 16 37 -> 31.
+// of moved tokens are listed anew, from their rows, in every search.  Rows read in every search against moves at the end, means of eight
+// batches each: 65536 tokens of 128 experts 77 -> 61 us, 16384 of 256 155 -> 97, 10007 of 96 77 -> 47, 16384 of 64 52 -> 37, 4096 of 16 23
+// -> 18, 64 of 8 18 -> 15.  (The prices the passes end at are others since; a single batch may go the other way.)
 template <int TEPL, bool OS>
 __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t *prices, int64_t *price_scale, SolverState *host_state)
 {
