@@ -242,15 +242,16 @@ __device__ __forceinline__ float wave_sum_f(float v)        // the total in lane
 }
 
 // Behind step_clear and a barrier.  CUM: s.cum holds the sums of the bins already.  SPARE: there may be spare capacity; the columns of s_h are
-// summed up with it.
-template <bool CUM, bool SPARE>
+// summed up with it.  TOGETHER: the step of the other kind (apart, as its branches in this one took 0.4 us of 7.2 at 96 experts).
+template <bool CUM, bool SPARE, bool TOGETHER>
 __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const PriceMeta mt, int *s_h, StepLds &s)
 {
     constexpr int NW = kUThreads / 64;
     static_assert(kPriceMaxE / 64 < NW - 2, "the last two wavefronts have no experts");
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int E = a.E, ES = a.es, nb = a.nb, nwe = (E + 63) >> 6;
-    const bool spare = SPARE && a.mode == kModeSlack, together = spare && mt.together, slack = spare && !together, over_all = a.mode == kModeOver;
+    constexpr bool together = SPARE && TOGETHER;
+    const bool spare = together || (SPARE && a.mode == kModeSlack), slack = spare && !together, over_all = !together && a.mode == kModeOver;
     const bool sampled = nrows < a.T;
     const int w0 = bin_w0(mt.w), bs = a.bshift;
     const int Ct = sampled ? (int)(((long long)a.C * nrows + a.T / 2) / a.T) : a.C;
@@ -560,7 +561,9 @@ __global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, 
     const PriceMeta mt = ar->meta;
     if (mt.done) return;                 // (passes that find the prices done add nothing: the copies stay clear)
     __syncthreads();
-    PriceMeta m2 = price_step<true, true>(a, t, nrows, mt, s_h, s);
+    PriceMeta m2;
+    if (__builtin_expect(mt.together, 0)) m2 = price_step<true, true, true>(a, t, nrows, mt, s_h, s);
+    else m2 = price_step<true, true, false>(a, t, nrows, mt, s_h, s);
     if (t == a.look) m2.far = m2.excess > kFar * E;
     for (int e = tid; e < E; e += kUThreads) ar->prices[e] = s.now[e];
     if (tid == 0) {
@@ -578,18 +581,19 @@ __device__ __forceinline__ void price_rows(const PriceArgs &a, int W, int r_firs
 {
     using RK = RowKeys<G, EPL>;
     constexpr int NG = NT / G;
-    const int tid = threadIdx.x, lane = tid & 63, lg = tid & (G - 1), gbase = lane & ~(G - 1), grp = tid / G;
-    const int E = a.E, k = a.k, ib = a.ib, nb = a.nb;
-    const int ES = a.es;
+    const int tid = threadIdx.x, E = a.E, k = a.k, ib = a.ib, nb = a.nb, ES = a.es, bs = a.bshift;
+    const int lg = tid & (G - 1), grp = tid / G;
     const bool vec = (E & 3) == 0 && (((size_t)a.q) & 15) == 0;
-    const int w0 = bin_w0(W), bs = a.bshift;
+    const int w0 = bin_w0(W);
     const int bias = 1 << (31 - ib);
     const unsigned cmask = (1u << ib) - 1;
     int pb[EPL];                                          // bias - price of this lane's columns
+    unsigned priced = 0;                                  // TOGETHER: those with a price, and those beyond the experts
 #pragma unroll
     for (int m = 0; m < EPL; ++m) {
         const int c = RK::col(m, lg);
         pb[m] = c < E ? bias - s_p[c] : 0;
+        if (TOGETHER && pb[m] < bias) priced |= 1u << m;
     }
     const unsigned keyo = (unsigned)bias << ib;           // an unfilled slot: reward 0, price 0
     int *s_n = s_hist + 2 * nb * ES;
@@ -637,14 +641,16 @@ __device__ __forceinline__ void price_rows(const PriceArgs &a, int W, int r_firs
         }
         if (!near) continue;
         if (TOGETHER) {
-            unsigned held[EPL], free[EPL];
+            unsigned h = ~0u, f = 0u;                    // the lowest hold with a price, the best of the others without
+            asm volatile("" : "+v"(priced));             // (else a condition of every column is kept in registers: 50 of them spilled)
 #pragma unroll
             for (int m = 0; m < EPL; ++m) {
-                const bool p = RK::col(m, lg) < E && pb[m] < bias;              // it has a price
-                held[m] = p && key[m] >= kth ? ~key[m] : 0u;
-                free[m] = p || key[m] >= kth ? 0u : key[m];
+                const bool p = (priced >> m) & 1u, held = key[m] >= kth;
+                h = p && held && key[m] < h ? key[m] : h;
+                f = p || held || key[m] < f ? f : key[m];
             }
-            const unsigned h = ~RK::first(held), f = RK::first(free);
+            h = group_min_u32<G>(h);
+            f = ~group_min_u32<G>(~f);
             const int mg = (int)((h - f) >> ib);
             if (lg == 0 && live && h != ~0u && f != 0u && mg < W) atomicAdd(&s_hist[(2 * nb + 1) * ES + bin_of(mg, w0, bs)], 1);
         }
@@ -691,8 +697,8 @@ __global__ __launch_bounds__(kQThreads) void k_price(PriceArgs a, int nrows, int
     const int hquads = a.quads;
     for (int i = tid; i < hquads; i += kQThreads) ((int4 *)s_hist)[i] = make_int4(0, 0, 0, 0);
     __syncthreads();
-    // (the margins of the experts together in a loop of their own: a branch in the other one took 0.3 us of 5.9, 10007 rows of 96 experts)
-    if (MODE == kModeSlack && mt.together) price_rows<G, EPL, false, true, kQThreads>(a, mt.w, r_first, r_end, stride, shift, nx, s_p, s_hist);
+    // (the margins of the experts together in a loop of their own, behind the other one: a branch in that took 0.3 us of 5.7, 10007 rows of 96)
+    if (MODE == kModeSlack && __builtin_expect(mt.together, 0)) price_rows<G, EPL, false, true, kQThreads>(a, mt.w, r_first, r_end, stride, shift, nx, s_p, s_hist);
     else price_rows<G, EPL, MODE == kModeOver, false, kQThreads>(a, mt.w, r_first, r_end, stride, shift, nx, s_p, s_hist);
     __syncthreads();
     int *hg = ar->hist[blockIdx.x & (a.copies - 1)];
@@ -744,12 +750,13 @@ __global__ __launch_bounds__(kUThreads) void k_price_small(PriceArgs a, int n_pa
         RK::load(a.q + (size_t)(grp < a.T ? grp : a.T - 1) * E, E, vec, lg, nx);
         for (int i = tid; i < hquads; i += kUThreads) ((int4 *)s_hist)[i] = make_int4(0, 0, 0, 0);
         __syncthreads();
-        if (MODE == kModeSlack && mt.together) price_rows<G, EPL, false, true, kUThreads>(a, mt.w, 0, a.T, 1, 0, nx, s.was, s_hist);
+        if (MODE == kModeSlack && __builtin_expect(mt.together, 0)) price_rows<G, EPL, false, true, kUThreads>(a, mt.w, 0, a.T, 1, 0, nx, s.was, s_hist);
         else price_rows<G, EPL, MODE == kModeOver, false, kUThreads>(a, mt.w, 0, a.T, 1, 0, nx, s.was, s_hist);
         for (int e = tid; e < E; e += kUThreads) s.now[e] = s.was[e];
         step_clear(s);
         __syncthreads();
-        mt = price_step<false, MODE == kModeSlack>(a, t, a.T, mt, s_hist, s);
+        mt = MODE == kModeSlack && mt.together ? price_step<false, MODE == kModeSlack, true>(a, t, a.T, mt, s_hist, s)
+                                               : price_step<false, MODE == kModeSlack, false>(a, t, a.T, mt, s_hist, s);
         __syncthreads();
         for (int e = tid; e < E; e += kUThreads) s.was[e] = s.now[e];
     }
