@@ -241,8 +241,9 @@ __device__ __forceinline__ float wave_sum_f(float v)        // the total in lane
     return v;
 }
 
-// Behind step_clear and a barrier.  CUM: s.cum holds the sums of the bins already.  SPARE: there may be spare capacity; the columns of s_h are
-// summed up with it.  TOGETHER: the step of the other kind (apart, as its branches in this one took 0.4 us of 7.2 at 96 experts).
+// Behind step_clear and a barrier.  CUM: s.cum holds the sums of the bins already.  SPARE: there is spare capacity; the columns of s_h are
+// summed up then.  TOGETHER: the step of the other kind.  (Three kinds of code, as the branches of the others cost every step: 4.1 us at 16
+// experts and 5.8 at 64 and 128 without them, 4.5 and 6.3 with those of spare capacity; 7.2 at 96 with spare capacity, 7.6 with both.)
 template <bool CUM, bool SPARE, bool TOGETHER>
 __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const PriceMeta mt, int *s_h, StepLds &s)
 {
@@ -250,8 +251,8 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
     static_assert(kPriceMaxE / 64 < NW - 2, "the last two wavefronts have no experts");
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int E = a.E, ES = a.es, nb = a.nb, nwe = (E + 63) >> 6;
-    constexpr bool together = SPARE && TOGETHER;
-    const bool spare = together || (SPARE && a.mode == kModeSlack), slack = spare && !together, over_all = !together && a.mode == kModeOver;
+    constexpr bool spare = SPARE, together = SPARE && TOGETHER, slack = SPARE && !TOGETHER;
+    const bool over_all = !SPARE && a.mode == kModeOver;
     const bool sampled = nrows < a.T;
     const int w0 = bin_w0(mt.w), bs = a.bshift;
     const int Ct = sampled ? (int)(((long long)a.C * nrows + a.T / 2) / a.T) : a.C;
@@ -546,7 +547,7 @@ constexpr int price_pieces(bool half) { return (kPTableInts / (half ? 8 : 4) + k
 // sums and searches: 4.4 us at 16 experts, 5.3 at 64, 6.4 at 128, 8.4 at 256 (5.7, 7.5, 9.8 and 9.7 with counts of 32 bits, and with the
 // sums of the bins and the largest step taken behind the copies); with spare capacity 9 at 96, and 4.8 where the passes end.  As the first step of every workgroup of the next pass the same
 // work took 10 to 20 us.
-template <int N, int M, bool HALF>
+template <int N, int M, bool HALF, bool SPARE>
 __global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, int nrows, int *host)
 {
     extern __shared__ __attribute__((aligned(16))) int s_h[];         // the sum of the copies
@@ -562,8 +563,8 @@ __global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, 
     if (mt.done) return;                 // (passes that find the prices done add nothing: the copies stay clear)
     __syncthreads();
     PriceMeta m2;
-    if (__builtin_expect(mt.together, 0)) m2 = price_step<true, true, true>(a, t, nrows, mt, s_h, s);
-    else m2 = price_step<true, true, false>(a, t, nrows, mt, s_h, s);
+    if (SPARE && __builtin_expect(mt.together, 0)) m2 = price_step<true, SPARE, true>(a, t, nrows, mt, s_h, s);
+    else m2 = price_step<true, SPARE, false>(a, t, nrows, mt, s_h, s);
     if (t == a.look) m2.far = m2.excess > kFar * E;
     for (int e = tid; e < E; e += kUThreads) ar->prices[e] = s.now[e];
     if (tid == 0) {
@@ -1794,15 +1795,21 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
 #undef MS_PG
 #undef MS_P
         if (!fin) {
-#define MS_U(NN)                                                                                                          \
+#define MS_U(NN, SS)                                                                                                      \
     do {                                                                                                                  \
-        if (!a.half) hipLaunchKernelGGL((k_price_update<NN, price_pieces(false), false>), dim3(1), dim3(kUThreads), shm, s, a, t, nrows, words_dev); \
-        else if (a.quads <= 2 * kUThreads) hipLaunchKernelGGL((k_price_update<NN, 1, true>), dim3(1), dim3(kUThreads), shm, s, a, t, nrows, words_dev); \
-        else hipLaunchKernelGGL((k_price_update<NN, price_pieces(true), true>), dim3(1), dim3(kUThreads), shm, s, a, t, nrows, words_dev); \
+        if (!a.half) hipLaunchKernelGGL((k_price_update<NN, price_pieces(false), false, SS>), dim3(1), dim3(kUThreads), shm, s, a, t, nrows, words_dev); \
+        else if (a.quads <= 2 * kUThreads) hipLaunchKernelGGL((k_price_update<NN, 1, true, SS>), dim3(1), dim3(kUThreads), shm, s, a, t, nrows, words_dev); \
+        else hipLaunchKernelGGL((k_price_update<NN, price_pieces(true), true, SS>), dim3(1), dim3(kUThreads), shm, s, a, t, nrows, words_dev); \
     } while (0)
-            if (a.copies == 8) MS_U(8);
-            else if (a.copies == 4) MS_U(4);
-            else MS_U(2);
+#define MS_US(NN)                                  \
+    do {                                           \
+        if (a.mode == kModeSlack) MS_U(NN, true);  \
+        else MS_U(NN, false);                      \
+    } while (0)
+            if (a.copies == 8) MS_US(8);
+            else if (a.copies == 4) MS_US(4);
+            else MS_US(2);
+#undef MS_US
 #undef MS_U
             mark();
         }
