@@ -206,8 +206,8 @@ __device__ __forceinline__ unsigned row_mask(int row, int ib)      // equal valu
 // (of each row the margin of the lowest hold that has a price to the best alternative that has none), the others as far as their own margins
 // say.  Neither kind gets there by itself.  Solves of 40 batches of 4096 to 65536 tokens to 16 to 256 experts, a twentieth to half of them
 // alike up to 0.1 or 3e-2 and 2 to 50 % more room than demand, against these steps alone (most then go on to the auction): 0.52 with the
-// level's alone, 0.41 in turn; a tenth of 16384 rows over 256 experts alike 1.83 and 0.96; a quarter of 32768 rows over 64 experts alike up
-// to 3e-2, a quarter more room, 0.21 to 0.25 ms in 10 or 11 passes, 0.25 to 0.39 in 10 to 18, and 0.19 to 0.28 in 10 to 13.  Other
+// level's alone, 0.39 in turn; a tenth of 16384 rows over 256 experts alike 1.83 and 0.80; a quarter of 32768 rows over 64 experts alike up
+// to 3e-2, a quarter more room, 0.21 to 0.25 ms in 10 or 11 passes, 0.25 to 0.39 in 10 to 18, and 0.18 to 0.26 in 10 to 13.  Other
 // batches hardly ever come to it: 50 solves within 1 %.
 //
 // Bound by latency, and by what the sixteen wavefronts do alike (four of them share a SIMD): sums are taken over the
@@ -482,7 +482,7 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
         if (m2.excess == 0) m2.bound = 2;                // nothing to move
         for (int e = tid; e < E; e += kUThreads) s.now[e] = s.was[e];
     } else {
-        const bool damp = !sampled && m2.excess <= E, slow = spare && 2 * m2.excess > E && 2ll * m2.excess > mt.excess;
+        const bool damp = !sampled && m2.excess <= E, slow = spare && 2ll * m2.excess > mt.excess;
         const int plim = (1 << (31 - a.ib)) - 1;
         for (int e = tid; e < E; e += kUThreads) {
             int dp = s.now[e] - s.was[e];
