@@ -207,7 +207,7 @@ __device__ __forceinline__ unsigned row_mask(int row, int ib)      // equal valu
 // say.  Neither kind gets there by itself.  Solves of 40 batches of 4096 to 65536 tokens to 16 to 256 experts, a twentieth to half of them
 // alike up to 0.1 or 3e-2 and 2 to 50 % more room than demand, against these steps alone (most then go on to the auction): 0.52 with the
 // level's alone, 0.39 in turn; a tenth of 16384 rows over 256 experts alike 1.83 and 0.80; a quarter of 32768 rows over 64 experts alike up
-// to 3e-2, a quarter more room, 0.21 to 0.25 ms in 10 or 11 passes, 0.25 to 0.39 in 10 to 18, and 0.18 to 0.26 in 10 to 13.  Other
+// to 3e-2, a quarter more room, 0.21 to 0.25 ms in 10 or 11 passes, 0.25 to 0.39 in 10 to 18, and 0.18 to 0.26 in 10 to 14.  Other
 // batches hardly ever come to it: 50 solves within 1 %.
 //
 // Bound by latency, and by what the sixteen wavefronts do alike (four of them share a SIMD): sums are taken over the
@@ -302,7 +302,9 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
     const int excess = sampled ? (int)((long long)sx * a.T / nrows) : sx;
     const bool enough = !sampled && excess * (E <= 128 && !a.retry ? kEnough : 2 * kEnough) <= E && !s.worst;
     const bool moves = !enough || a.retry;               // (another try may have to go on all the same)
-    const int target = slack || ss == 0 ? Ct : (2 * sn + ss) / (2 * ss);      // the capacity, or the mean demand
+    // the capacity, or the mean demand (of the experts together no less than the capacity: one of them that has room is at its own mean)
+    int target = slack || ss == 0 ? Ct : (2 * sn + ss) / (2 * ss);
+    if (together && target < Ct) target = Ct;
     if (moves && wv * 64 < E + (over_all ? 1 : 0)) {
         const int j = tid;
         const bool common = j == E;

@@ -150,3 +150,20 @@ def test_near_copies_without_spare_room(ms, T, E, k, room, part, noise):
     auction = ms.assign_i32(q, k, C, finisher=False)["stats"]
     assert st["total_score_q"] == auction["total_score_q"] and st["rounds"] < 24
     assert (st["phases"], st["finish_passes"]) == (1, 1)
+
+
+@pytest.mark.parametrize("T,E,k,C,part,noise,scale,seed", [(2945, 4, 2, 1915, 0.5, 0.1, 3.0, 244), (3510, 4, 2, 2282, 0.8, 0.1, 3.0, 60),
+                                                           (2240, 8, 1, 283, 0.8, 0.1, 3.0, 400), (12875, 4, 1, 3251, 0.1, 0.1, 3.0, 423),
+                                                           (2346, 6, 3, 1525, 0.8, 0.1, 1.0, 330)])
+def test_few_experts_with_a_price(ms, T, E, k, C, part, noise, scale, seed):
+    """Near copies to few experts, of which one or two have a price: a step of these together by their own mean demand alone finds nothing to
+    do while they have room, and the auction had to solve these."""
+    print(f"few experts T={T} E={E} k={k} C={C} part={part} noise={noise}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    L = torch.randn(T, E, generator=gen, device="cuda") * scale
+    n = int(T * part)
+    L[:n] = L[0] + noise * torch.randn(n, E, generator=gen, device="cuda")
+    q = ms.softtopk(L, k, 1.0)[1]
+    st, auction = ms.assign_i32(q, k, C)["stats"], ms.assign_i32(q, k, C, finisher=False)["stats"]
+    assert st["total_score_q"] == auction["total_score_q"]
+    assert (st["phases"], st["finish_passes"]) == (1, 1)               # not by the auction
