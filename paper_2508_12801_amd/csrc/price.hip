@@ -476,7 +476,8 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
     const bool listed = !a.retry || s.reach;             // another try needs more exchanges than the one before
     // stuck: it no longer shrinks (it ends up alternating by a few); with spare capacity the step of the other kind is to be tried first, unless
     // there are few left (16384 tokens, a tenth of them alike, to 8 of 256: a search of 137 tokens took longer than the passes it saved)
-    const bool stalls = m2.excess <= E && m2.excess * 5 >= mt.excess * 4 && t >= 4, stuck = stalls && (!spare || 4 * m2.excess <= E || (mt.stalled && 2 * m2.excess <= E));
+    const bool stalls = m2.excess <= E && m2.excess * 5 >= mt.excess * 4 && t >= 4;
+    const bool stuck = stalls && (!spare || 4 * m2.excess <= E || (mt.stalled && 2 * m2.excess <= E));
     m2.stalled = stalls;
     if (!sampled && (s.maxd == 0 || (listed && (enough || stuck)))) {
         m2.done = 1;
