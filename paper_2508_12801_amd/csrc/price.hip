@@ -106,7 +106,7 @@ struct PriceMeta {
     int excess;       // tokens too many in all, as the pass found them (a sample's count is scaled up)
     int far;          // 1: too far from the end when the passes were nearly used up; some more follow
     int together;     // spare capacity: the step that comes next moves the experts that have a price together
-    int stalled;      // ... the last pass found few tokens less than the one before it
+    int stalled;      // ... passes so far that found few tokens less than the one before them
 };
 
 // Control words and tables inside the workspace (WorkspaceLayout::price_off).
@@ -142,6 +142,7 @@ struct PriceArgs {
     int retry;                                    // the search has failed at the prices or the bound before
     int arcs_wanted;                              // about so many exchanges are to lie under the bound
     int lists;                                    // of arcs: one or kPLists
+    int sampled;                                  // passes over a sample before the others
     int look;                                     // the pass that tells whether more than the usual ones are needed, or -1
 };
 
@@ -477,15 +478,16 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
     // stuck: it no longer shrinks (it ends up alternating by a few); with spare capacity the step of the other kind is to be tried first, unless
     // there are few left (16384 tokens, a tenth of them alike, to 8 of 256: a search of 137 tokens took longer than the passes it saved)
     const bool stalls = m2.excess <= E && m2.excess * 5 >= mt.excess * 4 && t >= 4;
-    const bool stuck = stalls && (!spare || 4 * m2.excess <= E || (mt.stalled && 2 * m2.excess <= E));
-    m2.stalled = stalls;
+    const bool stuck = stalls && (!spare || 4 * m2.excess <= E || (mt.stalled >= 1 && 2 * m2.excess <= E) || mt.stalled >= 4);
+    m2.stalled += stalls ? 1 : 0;
     if (!sampled && (s.maxd == 0 || (listed && (enough || stuck)))) {
         m2.done = 1;
         m2.w = mt.w;
         if (m2.excess == 0) m2.bound = 2;                // nothing to move
         for (int e = tid; e < E; e += kUThreads) s.now[e] = s.was[e];
     } else {
-        const bool damp = !sampled && m2.excess <= E, slow = spare && 2ll * m2.excess > mt.excess;
+        // (the first pass over all rows finds what the samples have left: nothing slow about that)
+        const bool damp = !sampled && m2.excess <= E, slow = spare && t > a.sampled && 2ll * m2.excess > mt.excess;
         const int plim = (1 << (31 - a.ib)) - 1;
         for (int e = tid; e < E; e += kUThreads) {
             int dp = s.now[e] - s.was[e];
@@ -1732,6 +1734,7 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     if (!price_shape(T, E, k, G, EPL, rows, a.n_wg) || a.n_wg > L.max_wg) return MAXSCORE_ERR_SHAPE;
     a.rows = rows;
     a.lists = a.n_wg >= kPListsFrom ? kPLists : 1;
+    a.sampled = n_sampled;
     a.look = a.mode != kModeSlack && !retry ? n_sampled + kTightPasses - 2 : -1;
     geom->rows = rows;
     geom->n_wg = a.n_wg;

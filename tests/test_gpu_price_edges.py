@@ -167,3 +167,16 @@ def test_few_experts_with_a_price(ms, T, E, k, C, part, noise, scale, seed):
     st, auction = ms.assign_i32(q, k, C)["stats"], ms.assign_i32(q, k, C, finisher=False)["stats"]
     assert st["total_score_q"] == auction["total_score_q"]
     assert (st["phases"], st["finish_passes"]) == (1, 1)               # not by the auction
+
+
+@pytest.mark.parametrize("T,E,k,C,seed,passes", [(150000, 96, 6, 10313, 9, 12), (524288, 64, 2, 20480, 8, 13)])
+def test_samples_before_all_rows(ms, T, E, k, C, seed, passes):
+    """Spare room beyond 131071 tokens: what the passes over samples leave the first pass over all rows finds, which must not be taken for
+    rows that are nearly alike."""
+    print(f"samples before all rows T={T} E={E} k={k}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    L = torch.randn(T, E, generator=gen, device="cuda") + 0.7 * torch.randn(E, generator=gen, device="cuda")
+    q = ms.softtopk(L, k, 1.0)[1]
+    st, auction = ms.assign_i32(q, k, C)["stats"], ms.assign_i32(q, k, C, finisher=False)["stats"]
+    assert st["total_score_q"] == auction["total_score_q"]
+    assert (st["phases"], st["finish_passes"]) == (1, 1) and st["rounds"] <= passes
