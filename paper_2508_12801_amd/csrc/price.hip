@@ -73,15 +73,21 @@ constexpr int kSampleRows = 8192;
 // it.  Without and with two passes over samples before the others, solves of 16384 to 32768 tokens take 0.84 to 0.86, to 65536 0.82 to
 // 0.86, to 131072 0.79 to 0.94, to 185000 1.01, to 262144 1.06, beyond 1.16 to 1.19 of the time (230 batches to 8 to 256 experts).
 constexpr int kSampleFrom = 16;
-constexpr int kArcsPerExpert = 16, kArcsWanted = 4500, kArcsMost = 5500;
+// (20 exchanges per expert 1.5 % slower, 16 0.4 %, 10 and 8 0.3 and 0.9 %, 600 solves)
+constexpr int kArcsPerExpert = 12, kArcsWanted = 4500, kArcsMost = 5500;
 constexpr int kMaxBound = (1 << 21) - 1;
 constexpr int kAllArcs = 4000;                    // problems with this few exchanges in all are searched with all of them
-constexpr int kEnough = 3, kWorst = 2;            // the passes end when a third of a token per expert (a sixth
-                                                  // beyond 128, where searches take longer) is too many, at
-                                                  // no expert more than two (its tokens leave one search at a time)
+// The passes end when five sixths of a token per expert are too many in all (in another try a sixth), and the step is taken all the same: what
+// a step leaves is the noise of where the displaced tokens went, which the prices it ends at need not be looked at for.  Of 555 drawn batches
+// (64 to 65536 tokens, 8 to 256 experts) solves took 0.915 of the time of passes that end at the prices they have looked at, with a third of a
+// token per expert (a sixth beyond 128) and no expert with more than two; that rule with the step 0.975, half a token 0.926, two
+// thirds 0.912, one 0.918, four thirds 0.936, two 0.968.  A search with more tokens to move takes more paths at a time.
+// From the seventh pass on, which only rows that are nearly alike come to, a third of a token per expert: of 256 experts their searches are long
+// (six such batches of 16384 tokens 1.17 of the time of before with five sixths throughout, 0.92 so; 40 others 0.97 and 0.95).
+constexpr int kEnough = 5, kLateEnough = 2, kRetryEnough = 1, kUsualPasses = 6;       // the first three are sixths of a token per expert
 // Steps are shortened by an eighth when few tokens are too many: experts that chase each other's last tokens settle sooner.  Of 500 drawn
 // batches (64 to 65536 tokens, 8 to 256 experts) solves took 3.6 % longer with three eighths (6 % at 64 and 128 experts, 1 % at 8 and 16); with a sixth,
-// a sixteenth or none within 1 % of an eighth; with half a token per expert left to the search 0.5 % longer.
+// a sixteenth or none within 1 % of an eighth; within 1 % the same with a twelfth and a twentieth.
 constexpr int kDamp = 8;
 constexpr int kSmallEntries = 1 << 16;            // rewards of a batch that one workgroup passes over by itself
 constexpr int kSmallThreads = 4096;               // ... with this many lanes at work in all
@@ -219,14 +225,14 @@ struct StepLds {
     int cum[64];
     __attribute__((aligned(16))) int part[kPriceMaxE / 64][8];      // sums of the wavefronts that have experts
     float level[2][kUThreads / 64];                                 // demand beyond the tokens there are, at so many levels
-    int maxd, ran_out, lam, worst, bound, wide, reach;
+    int maxd, ran_out, lam, bound, wide, reach;
 };
 
 __device__ __forceinline__ void step_clear(StepLds &s)
 {
     if (threadIdx.x < 64) s.cum[threadIdx.x] = 0;
     if (threadIdx.x == 0) {
-        s.maxd = s.ran_out = s.lam = s.worst = 0;
+        s.maxd = s.ran_out = s.lam = 0;
     }
 }
 
@@ -262,7 +268,6 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
         const int ne = tid < E ? s_hn[tid] : 0, over = tid < E && ne > Ct ? ne - Ct : 0;
         const bool in = tid < E && (!spare || s.was[tid] > 0);
         const int sn = wave_sum(in ? ne : 0), sx = wave_sum(over), sd = wave_sum(in && ne < Ct ? Ct - ne : 0);
-        if (in ? over > kWorst || Ct - ne > kWorst : over > kWorst) s.worst = 1;
         if (lane == 63) *(int4 *)&s.part[wv][0] = make_int4(sn, sx, sd, 0);
         if (together) {
             const int ss = wave_sum(in ? 1 : 0), sz = wave_sum(in ? 0 : over);
@@ -301,8 +306,8 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
     sx = sd > sx ? sd : sx;                                           // tokens too many or too few
     // enough: what is left is cheaper to move by the search
     const int excess = sampled ? (int)((long long)sx * a.T / nrows) : sx;
-    const bool enough = !sampled && excess * (E <= 128 && !a.retry ? kEnough : 2 * kEnough) <= E && !s.worst;
-    const bool moves = !enough || a.retry;               // (another try may have to go on all the same)
+    const bool enough = !sampled && 6 * excess <= E * (a.retry ? kRetryEnough : t - a.sampled < kUsualPasses ? kEnough : kLateEnough);
+    const bool moves = excess > 0 || sampled || a.retry;               // (another try may have to go on all the same)
     // the capacity, or the mean demand (of the experts together no less than the capacity: one of them that has room is at its own mean)
     int target = slack || ss == 0 ? Ct : (2 * sn + ss) / (2 * ss);
     if (together && target < Ct) target = Ct;
@@ -484,6 +489,8 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
         m2.done = 1;
         m2.w = mt.w;
         if (m2.excess == 0) m2.bound = 2;                // nothing to move
+    }
+    if (m2.done && (!enough || m2.excess == 0 || s.maxd == 0)) {
         for (int e = tid; e < E; e += kUThreads) s.now[e] = s.was[e];
     } else {
         // (the first pass over all rows finds what the samples have left: nothing slow about that)
@@ -496,7 +503,7 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
             if (spare) pn = pn < 0 ? 0 : pn;
             s.now[e] = pn > plim ? plim : (pn < -plim ? -plim : pn);
         }
-        if (slow) m2.together = !mt.together;
+        if (slow && !m2.done) m2.together = !mt.together;
     }
     return m2;
 }
