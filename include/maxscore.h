@@ -98,6 +98,8 @@ typedef struct {
 #define MAXSCORE_FLAG_NO_FINISHER 2u    /* exact solver: the auction, and it runs down to eps = 1 itself instead of handing
                                            its last phases to the cycle-cancelling finisher (slower; same optimum) */
 
+#define MAXSCORE_FLAG_PASSES_BEGUN 4u  /* maxscore_route_rewards: maxscore_route_begin has reported that it began this solve */
+
 /* Filled on the HOST when the call returns (may be NULL). */
 typedef struct {
     int64_t total_score_q; /* sum of q over the chosen pairs */
@@ -167,7 +169,7 @@ int32_t maxscore_softtopk_reading(const float *logits, int32_t T, int32_t E, int
  *                 its best alternatives, and unfilled experts have price 0 (the dual side of
  *                 Eq. 7-8 that certifies the optimum).  price_scale[1] (may be NULL) receives
  *                 the scale, a power of two > E.
- * Synchronises `stream`. */
+ * Synchronises `stream`: it returns when all that it has enqueued is done. */
 int32_t maxscore_assign_i32(const int32_t *q, int32_t T, int32_t E, int32_t k, int32_t C,
                             const maxscore_opts *opts, int32_t *assign, int64_t *prices,
                             int64_t *price_scale, maxscore_stats *stats, void *workspace,
@@ -357,6 +359,13 @@ int32_t maxscore_route_rewards(const float *scores, const int32_t *q, int32_t T,
                                const maxscore_opts *opts, int32_t *assign, float *gates, int32_t *expert_offsets,
                                int32_t *disp_token, float *disp_gate, int32_t *token_pos, int64_t *prices,
                                maxscore_stats *stats, void *workspace, size_t workspace_bytes, void *stream);
+
+/* Optional, ahead of maxscore_route_rewards: enqueues what that call would begin with and what writes none of its outputs, so that a caller
+ * can allocate these meanwhile (the price passes of a small batch; of others nothing).  *begun: whether it has; then the thread's next
+ * solve is to be that call, with the same q, sizes, prices_in, workspace and stream and MAXSCORE_FLAG_PASSES_BEGUN in its flags, and nothing else
+ * may use the workspace before it.  (With other arguments, or behind another solve, the flag has no effect.)  Only enqueues. */
+int32_t maxscore_route_begin(const int32_t *q, int32_t T, int32_t E, int32_t k, int32_t C, const maxscore_opts *opts,
+                             int32_t *begun, void *workspace, size_t workspace_bytes, void *stream);
 
 /* a1 + a2 + a3: scores[T,E] and/or q[T,E] from x and W_g (Eq. 2, then Eq. 6 and the rounding), in one kernel where
  * maxscore_route_xw can do so (same conditions, `workspace` as for maxscore_router_logits; logits_out may then be

@@ -93,6 +93,8 @@ _SIGS = {
                               [ctypes.c_size_t, ctypes.c_void_p]),
     "maxscore_route_rewards": (ctypes.c_int32, [ctypes.c_void_p] * 2 + [ctypes.c_int32] * 4 + [ctypes.c_void_p] * 10 +
                                [ctypes.c_size_t, ctypes.c_void_p]),
+    "maxscore_route_begin": (ctypes.c_int32, [ctypes.c_void_p] + [ctypes.c_int32] * 4 + [ctypes.c_void_p] * 3 +
+                             [ctypes.c_size_t, ctypes.c_void_p]),
     "maxscore_route_xw": (ctypes.c_int32, [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32,
                                            ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32,
                                            ctypes.c_int32, ctypes.c_void_p] + [ctypes.c_void_p] * 12 +
@@ -205,6 +207,8 @@ MAX_EXPERTS = 1024
 
 FLAG_NO_TAIL_PASS = 1
 FLAG_NO_FINISHER = 2
+FLAG_PASSES_BEGUN = 4
+SMALL_BATCH = 512                                # more tokens than this never have their price passes in one launch
 
 
 def _opts(t=1.0, quant_shift=20, max_rounds=200000, eps_div=12, assignment="exact", tail_pass=True, prices_in=None,
@@ -620,6 +624,13 @@ def route_xw(x, W, bias, k: int, C: int, t: float = 1.0, quant_shift: int = 20, 
         rc = load_library().maxscore_router_softtopk(
             _ptr(x), _ptr(W), _ptr(bias), _in_dtype(x), T, d, E, k, t, quant_shift, _ptr(scored["logits"]), _ptr(scored["scores"]),
             _ptr(scored["q"]), _ptr(ws), need, _stream())
+        if rc == OK and T <= SMALL_BATCH and opts.assignment == ASSIGNMENTS["exact"]:
+            # the projection of a small batch ends long before the outputs are there: what needs none of them goes ahead
+            begun = ctypes.c_int32()
+            brc = load_library().maxscore_route_begin(_ptr(scored["q"]), T, E, k, C, ctypes.byref(opts), ctypes.byref(begun), _ptr(ws),
+                                                      need, _stream())
+            if brc == OK and begun.value:        # (what it refuses the call below refuses as well)
+                opts.flags |= FLAG_PASSES_BEGUN
         o = _route_outputs(T, E, k, x.device, scored)
         if rc == OK:
             rc = load_library().maxscore_route_rewards(

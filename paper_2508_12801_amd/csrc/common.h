@@ -123,6 +123,8 @@ struct PriceGeometry {
     int one_launch;          // all price passes were one launch
 };
 bool price_supported(int T, int E, int k);
+// All of a try; the passes alone, if they are one launch (nothing otherwise); what follows them then.
+enum PricePart { kPriceAll, kPriceBegin, kPriceRest };
 // tables, and two words per block; the iterative assignment keeps its own there, with a word per (slot, 64 tokens)
 inline size_t price_area_bytes(int T, int k, int max_wg)
 {
@@ -143,10 +145,12 @@ inline bool iter_tiles_are_words(const WorkspaceLayout &L, int T, int E, int k)
 // expert), and the same as the device sees them.
 constexpr int kSolverWords = 16;
 int32_t solver_words(int **host, int **dev);
+// Waits until everything that has been enqueued in the stream is done.
+int32_t stream_done(hipStream_t s);
 // With kernel timing on, records the next of the calling thread's timing events: before and after the first kernel of a round
 // (auction) or pass (price solve) and after its second, three in all.
 int32_t solver_mark(hipStream_t s);
-int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_t *prices_in, int retry,
+int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_t *prices_in, int retry, PricePart part,
                       int32_t *assign, int64_t *prices, int64_t *price_scale, char *ws, SolverState *host_state_dev, PriceGeometry *geom, hipStream_t s);
 // Runs price_enqueue and the caller's work behind it and waits.  *solved: whether the result stands.
 int32_t price_run(const int32_t *q, int T, int E, int k, int C, const maxscore_opts &o, int32_t *assign, int64_t *prices,

@@ -22,6 +22,7 @@
 #include <climits>
 
 #include "common.h"
+#include "host_words.h"
 #include "iter_tail.h"
 #include "row_keys.h"
 
@@ -387,11 +388,11 @@ __device__ __forceinline__ void iter_report(const IterArgs &a, long long sum, in
             sum += s_sum[x];
             flow += s_w[x];
         }
-        *(volatile long long *)(host + kIterWordTotal) = sum;
-        ((volatile int *)host)[kIterWordFlow] = flow;
-        ((volatile int *)host)[kIterWordRounds] = rounds;
-        ((volatile int *)host)[kIterWordOpen] = open;
-        ((volatile int *)host)[0] = 1;              // (read when the stream has been waited for: a fence here took 3 us)
+        tell_host((long long *)(host + kIterWordTotal), sum);
+        tell_host(host + kIterWordFlow, flow);
+        tell_host(host + kIterWordRounds, rounds);
+        tell_host(host + kIterWordOpen, open);
+        tell_host(host, 1);              // (read when the stream has been waited for: a fence here took 3 us)
     }
 }
 
@@ -879,7 +880,8 @@ int32_t iter_run(const int32_t *q, int T, int E, int k, int C, int max_rounds, i
     }
     // what follows is enqueued while the last round runs
     const int32_t arc = after ? after(after_ctx, s) : MAXSCORE_OK;
-    MS_HIP(hipStreamSynchronize(s));
+    rc = stream_done(s);
+    if (rc) return rc;
     if (arc) return arc;
     if (!hw[0]) return MAXSCORE_ERR_HIP;
     if (total) *total = *(volatile long long *)(host + kIterWordTotal);

@@ -43,6 +43,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "host_words.h"
 #include "row_keys.h"
 
 namespace maxscore {
@@ -910,7 +911,7 @@ __global__ __launch_bounds__(kPThreads) void k_price_assign(PriceArgs a)
             s_arc_tok[at] = row;
         } else {                                           // (batches whose exchanges are all listed, in few blocks)
             const int pos = atomicAdd(n_list, 1);
-            if (pos < list_room) {
+            if ((unsigned)pos < (unsigned)list_room) {
                 ar->arc[list0 + pos] = r;
                 ar->arc_tok[list0 + pos] = row;
             }
@@ -952,7 +953,7 @@ __global__ __launch_bounds__(kPThreads) void k_price_assign(PriceArgs a)
     if (tid == 0) s_base = atomicAdd(n_list, n);
     __syncthreads();
     for (int i = tid; i < n; i += kPThreads)
-        if (s_base + i < list_room) {                      // (beyond: the search sees the count)
+        if ((unsigned)(s_base + i) < (unsigned)list_room) {                      // (beyond: the search sees the count)
             ar->arc[list0 + s_base + i] = s_arc[i];
             ar->arc_tok[list0 + s_base + i] = s_arc_tok[i];
         }
@@ -1044,7 +1045,7 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
         tok0[j] = ar->arc_tok[at];
     }
     const int n_upto = wave_sum(n_list), n_listed = __builtin_amdgcn_readlane(n_upto, 63);
-    bool ok = fail == 0 && !__any(n_list > list_room);
+    bool ok = fail == 0 && !__any((unsigned)n_list > (unsigned)list_room);
     int rounds = 0, augs = 0;
     bool close = false;                          // not solved, but near enough for another try
     const int A0 = slack ? 2 * E : 0;
@@ -1631,17 +1632,17 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
     __syncthreads();
     if (tid == 0) {
         if (certified && price_scale) *price_scale = (int64_t)1 << sb;
-        host_state->total = s.dsum;
-        host_state->flow = OS ? E * a.C : a.T * k;
-        host_state->round = mt.passes;
-        host_state->phases = 1;
-        host_state->status = MAXSCORE_OK;
-        host_state->fin = certified ? 2 : close ? 1 : 3;
-        host_state->fin_passes = 1;
-        host_state->fin_cycles = augs;
-        host_state->fin_dirty = rounds;
-        host_state->t_start = ar->t_start;
-        host_state->t_end = wall_clock64();
+        tell_host(&host_state->total, s.dsum);
+        tell_host(&host_state->flow, OS ? E * a.C : a.T * k);
+        tell_host(&host_state->round, mt.passes);
+        tell_host(&host_state->phases, 1);
+        tell_host(&host_state->status, (int)MAXSCORE_OK);
+        tell_host(&host_state->fin, certified ? 2 : close ? 1 : 3);
+        tell_host(&host_state->fin_passes, 1);
+        tell_host(&host_state->fin_cycles, augs);
+        tell_host(&host_state->fin_dirty, rounds);
+        tell_host(&host_state->t_start, ar->t_start);
+        tell_host(&host_state->t_end, (long long)wall_clock64());
     }
 }
 
@@ -1696,7 +1697,7 @@ bool price_supported(int T, int E, int k)
     return price_shape(T, E, k, G, EPL, rows, n_wg);
 }
 
-int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_t *prices_in, int retry, int32_t *assign, int64_t *prices,
+int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_t *prices_in, int retry, PricePart part, int32_t *assign, int64_t *prices,
                       int64_t *price_scale, char *ws, SolverState *host_state_dev, PriceGeometry *geom, hipStream_t s)
 {
     int *words = nullptr, *words_dev = nullptr;
@@ -1754,6 +1755,7 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     const bool small = (long long)T * G <= kSmallThreads && (long long)T * E <= kSmallEntries && shm + sizeof(StepLds) <= 64 * 1024;
     const int plim = (1 << (31 - a.ib)) - 1;
     geom->one_launch = small ? 1 : 0;
+    if (part == kPriceBegin && !small) return MAXSCORE_OK;
     if (!small)
         hipLaunchKernelGGL(k_price_init, dim3(64), dim3(kPThreads), 0, s, a.ar, a.quads, E, plim, prices_in, a.retry);
     for (int t = small ? n_pass : 0; t <= n_pass; ++t) {
@@ -1775,7 +1777,7 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
 #define MS_P(GG, PP)                                                                                                      \
     do {                                                                                                                  \
         if (fin) {                                                                                                        \
-            if (small) {                                                                                                  \
+            if (small && part != kPriceRest) {                                                                            \
                 mark();                                                                                                   \
                 if (a.mode == kModeTight) hipLaunchKernelGGL((k_price_small<GG, PP, kModeTight>), dim3(1), dim3(kUThreads), shm, s, a, kSmallPasses, plim, prices_in); \
                 else if (os) hipLaunchKernelGGL((k_price_small<GG, PP, kModeOver>), dim3(1), dim3(kUThreads), shm, s, a, kSmallPasses, plim, prices_in); \
@@ -1783,6 +1785,7 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
                 mark();                                                                                                   \
                 mark();                                                                                                   \
             }                                                                                                             \
+            if (part == kPriceBegin) break;                                                                               \
             if (os) hipLaunchKernelGGL((k_price_assign<GG, PP, true>), dim3(grid), dim3(kPThreads), 0, s, a);     \
             else hipLaunchKernelGGL((k_price_assign<GG, PP, false>), dim3(grid), dim3(kPThreads), 0, s, a);       \
         } else {                                                                                                          \
@@ -1826,6 +1829,10 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
 #undef MS_U
             mark();
         }
+    }
+    if (part == kPriceBegin) {
+        MS_HIP(hipGetLastError());
+        return mrc;
     }
 #define MS_F(PP)                                                                                                                            \
     do {                                                                                                                                    \

@@ -19,6 +19,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "host_words.h"
 #include "sums.h"
 
 namespace maxscore {
@@ -121,7 +122,7 @@ __global__ __launch_bounds__(1024) void k_sk_init(const int *__restrict__ counts
     for (int c = 0; c < kSkCopies; ++c) n += j < E ? counts[c * kMaxE + j] : 0;
     sk_targets(n, T, E, C, cap, target);
     if (j < E) {
-        if (caps) caps[j] = cap;
+        if (caps) tell_host(caps + j, cap);
         targets[j] = target;
         v[j] = 1.f;
     }
@@ -285,7 +286,7 @@ __global__ __launch_bounds__(kSkSmallThreads<EP>) void k_sk_small(const float *_
     if (tid < EP) {
         s_target[tid] = tid < E ? target : 0.f;
         s_v[tid] = tid < E && target > 0.f ? 1.f : 0.f;
-        if (tid < E && caps) caps[tid] = cap;
+        if (tid < E && caps) tell_host(caps + tid, cap);
     }
     __syncthreads();
 #pragma unroll
@@ -657,7 +658,8 @@ int32_t caps_words(int32_t *caps_host, int **words, int **words_dev)
 int32_t copy_caps(const int *words, int32_t *caps_host, int E, hipStream_t s)
 {
     if (!caps_host) return MAXSCORE_OK;
-    MS_HIP(hipStreamSynchronize(s));
+    const int32_t rc = stream_done(s);
+    if (rc) return rc;
     for (int e = 0; e < E; ++e) caps_host[e] = ((const volatile int *)words)[e];
     return MAXSCORE_OK;
 }

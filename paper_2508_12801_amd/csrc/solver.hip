@@ -36,11 +36,13 @@
 //     lists, in the few rounds that hand over to it).  The host enqueues rounds ahead of the
 //     device and polls `done` from pinned memory.
 #include <algorithm>
+#include <atomic>
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
 
 #include "common.h"
+#include "host_words.h"
 
 namespace maxscore {
 
@@ -1817,8 +1819,18 @@ struct SolverHost {
     int ahead_T = 0, ahead_E = 0, ahead_k = 0, ahead_ok = 1;
     std::vector<hipEvent_t> tev;      // pool of per-launch timing events (kernel timing only), three per round or pass
     size_t tev_used = 0;              // ... recorded by the solve in progress
+    struct {                          // price passes that maxscore_route_begin has enqueued; the thread's next solve uses them or not
+        const int32_t *q = nullptr;   // null: none
+        const int64_t *prices_in = nullptr;
+        char *ws = nullptr;
+        hipStream_t s = nullptr;
+        int T = 0, E = 0, k = 0, C = 0;
+    } begun;
+    unsigned done_seq = 0;            // what stream_done's word was last to be
     int device = -1;
 };
+
+constexpr int kDoneWord = kSolverWords + kMaxE + 16, kPinnedWords = kDoneWord + 16;      // stream_done's word, in a line to itself
 
 static int32_t solver_host(SolverHost **out)
 {
@@ -1833,7 +1845,7 @@ static int32_t solver_host(SolverHost **out)
         }
     if (!h) return MAXSCORE_ERR_HIP;
     if (h->device < 0) {
-        MS_HIP(hipHostMalloc((void **)&h->flag, sizeof(int) * (kSolverWords + kMaxE), hipHostMallocMapped));
+        MS_HIP(hipHostMalloc((void **)&h->flag, sizeof(int) * kPinnedWords, hipHostMallocMapped));
         MS_HIP(hipHostGetDevicePointer((void **)&h->flag_dev, h->flag, 0));
         MS_HIP(hipHostMalloc((void **)&h->state, sizeof(SolverState), hipHostMallocMapped));
         MS_HIP(hipHostGetDevicePointer((void **)&h->state_dev, h->state, 0));
@@ -1852,6 +1864,26 @@ int32_t solver_words(int **host, int **dev)
     if (rc) return rc;
     *host = hs->flag;
     *dev = hs->flag_dev;
+    return MAXSCORE_OK;
+}
+
+// Behind all that has been enqueued a kernel of one thread writes a word of pinned memory, which the host polls: hipStreamSynchronize
+// returns 6 us after such a word is there, and 20 where more than a handful of launches came before it.  A wait of more than about a
+// millisecond goes on in hipStreamSynchronize, which sleeps, and which reports an error of the stream.
+__global__ void k_done(unsigned *word, unsigned v) { tell_host(word, v); }
+
+int32_t stream_done(hipStream_t s)
+{
+    SolverHost *hs = nullptr;
+    const int32_t rc = solver_host(&hs);
+    if (rc) return rc;
+    const unsigned v = ++hs->done_seq;
+    hipLaunchKernelGGL(k_done, dim3(1), dim3(1), 0, s, (unsigned *)hs->flag_dev + kDoneWord, v);
+    MS_HIP(hipGetLastError());
+    volatile unsigned *word = (volatile unsigned *)hs->flag + kDoneWord;
+    for (int spin = 0; spin < 20000 && *word != v; ++spin) __builtin_ia32_pause();
+    if (*word != v) MS_HIP(hipStreamSynchronize(s));
+    std::atomic_thread_fence(std::memory_order_acquire);
     return MAXSCORE_OK;
 }
 
@@ -1919,18 +1951,58 @@ static int32_t add_launch_times(SolverHost *hs, size_t first, int n, int kernels
 
 constexpr long long kPriceMinPairs = 3;           // pairs per expert (with fewer the margins are too wide to step by)
 
+static bool price_takes(int T, int E, int k, int C, const maxscore_opts &o)
+{
+    return price_supported(T, E, k) && !(k == E && T > C) && !(E > 64 && (long long)T * k < kPriceMinPairs * E) &&
+           o.max_rounds >= kPriceTries * kPriceTryPasses &&         // (it counts its passes itself: the cap has to allow them all)
+           !(o.flags & (MAXSCORE_FLAG_NO_TAIL_PASS | MAXSCORE_FLAG_NO_FINISHER));
+}
+
+// The price passes of a small batch, ahead of the call that solves it.
+extern "C" int32_t maxscore_route_begin(const int32_t *q, int32_t T, int32_t E, int32_t k, int32_t C, const maxscore_opts *opts, int32_t *begun,
+                                        void *workspace, size_t workspace_bytes, void *stream)
+{
+    if (!q || !opts || !begun) return MAXSCORE_ERR_NULL;
+    *begun = 0;
+    if (T < 1 || T > (1 << kMaxTBits) || E < 1 || E > kMaxE || k < 1 || k > E || k > kMaxK || C < 1) return MAXSCORE_ERR_SHAPE;
+    if (!workspace || ((uintptr_t)workspace % 256) != 0 || workspace_bytes < workspace_layout(T, E, k).total) return MAXSCORE_ERR_WORKSPACE;
+    const int Ce = C < T ? C : T;
+    maxscore_opts o = *opts;
+    if (o.max_rounds <= 0) o.max_rounds = 200000;
+    if (o.assignment != MAXSCORE_ASSIGN_EXACT || g_kernel_timing || !price_takes(T, E, k, Ce, o)) return MAXSCORE_OK;
+    SolverHost *hs = nullptr;
+    int32_t rc = solver_host(&hs);
+    if (rc) return rc;
+    hipStream_t s = (hipStream_t)stream;
+    PriceGeometry pg;
+    hs->begun.q = nullptr;
+    rc = price_enqueue(q, T, E, k, Ce, o.prices_in, 0, kPriceBegin, nullptr, nullptr, nullptr, (char *)workspace, hs->state_dev, &pg, s);
+    if (rc || !pg.one_launch) return rc;
+    hs->begun.q = q;
+    hs->begun.prices_in = o.prices_in;
+    hs->begun.ws = (char *)workspace;
+    hs->begun.s = s;
+    hs->begun.T = T;
+    hs->begun.E = E;
+    hs->begun.k = k;
+    hs->begun.C = Ce;
+    *begun = 1;
+    return MAXSCORE_OK;
+}
+
 int32_t price_run(const int32_t *q, int T, int E, int k, int C, const maxscore_opts &o, int32_t *assign, int64_t *prices,
                   int64_t *price_scale, maxscore_stats *stats, char *ws, hipStream_t s, SolverGeometry *geom,
                   SolverAfter after, void *after_ctx, bool *solved)
 {
     *solved = false;
-    if (!price_supported(T, E, k) || (k == E && T > C) || (E > 64 && (long long)T * k < kPriceMinPairs * E) ||
-        o.max_rounds < kPriceTries * kPriceTryPasses ||         // (it counts its passes itself: the cap has to allow them all)
-        (o.flags & (MAXSCORE_FLAG_NO_TAIL_PASS | MAXSCORE_FLAG_NO_FINISHER)))
-        return MAXSCORE_OK;
     SolverHost *hs = nullptr;
     int32_t rc = solver_host(&hs);
     if (rc) return rc;
+    const auto &b = hs->begun;
+    const bool begun = (o.flags & MAXSCORE_FLAG_PASSES_BEGUN) && b.q && b.q == q && b.prices_in == o.prices_in && b.ws == ws && b.s == s && b.T == T &&
+                       b.E == E && b.k == k && b.C == C;
+    hs->begun.q = nullptr;
+    if (!price_takes(T, E, k, C, o)) return MAXSCORE_OK;
     hs->tev_used = 0;
     PriceGeometry pg;
     SolverState h;
@@ -1938,7 +2010,8 @@ int32_t price_run(const int32_t *q, int T, int E, int k, int C, const maxscore_o
     for (int attempt = 0;; ++attempt) {
         hs->state->fin = 0;
         const size_t mark = hs->tev_used;
-        rc = price_enqueue(q, T, E, k, C, o.prices_in, attempt, assign, prices, price_scale, ws, hs->state_dev, &pg, s);
+        rc = price_enqueue(q, T, E, k, C, o.prices_in, attempt, begun && attempt == 0 ? kPriceRest : kPriceAll, assign, prices, price_scale, ws,
+                           hs->state_dev, &pg, s);
         if (rc == MAXSCORE_OK && after) {
             const SolverGeometry g = {pg.rows, pg.n_wg, 0, 1, &hs->state_dev->t_after};
             rc = after(after_ctx, g, s, nullptr);
@@ -1947,8 +2020,8 @@ int32_t price_run(const int32_t *q, int T, int E, int k, int C, const maxscore_o
             (void)hipStreamSynchronize(s);
             return rc;
         }
-        MS_HIP(hipStreamSynchronize(s));
-        MS_HIP(hipGetLastError());
+        rc = stream_done(s);
+        if (rc) return rc;
         h = *hs->state;
         rc = add_launch_times(hs, mark, pg.one_launch ? 1 : h.round - passes, pg.one_launch ? 1 : 2, stats, s);
         if (rc) return rc;
