@@ -59,8 +59,6 @@ struct SolverState {
     int fin_cycles;        // negative cycles cancelled so far
     int fin_dirty;         // cycles cancelled since the arc matrix was last rebuilt
     int phase_round[28];   // round index at which each phase ended (diagnostic)
-    long long t_start, t_end;    // device clock (10 ns) at the first and last kernel of a price solve (host copy only)
-    long long t_after;           // ... and at the end of the caller's work behind it
 };
 
 struct WorkspaceLayout {
@@ -76,7 +74,7 @@ struct SolverGeometry {
     int n_wg;        // number of key blocks
     int tbits;       // the token id sits in the low tbits bits of a key
     int counts;      // 1: no key blocks; the pairs per (block, expert) are counted (price solves)
-    long long *clock;    // device pointer for the end time of the work behind a price solve (SolverState::t_after)
+    long long *clock;    // device pointer for the end time of the work behind a price solve (PriceReport::t_after)
 };
 
 WorkspaceLayout workspace_layout(int T, int E, int k, int d = 0);
@@ -108,17 +106,30 @@ int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore
                    void *after_ctx = nullptr);
 // Checks a device array of T per-token k (each 0..k) and returns its sum in *demand (synchronises the stream).
 int32_t kvec_check(const int32_t *kvec, int T, int E, int k, char *ws, long long *demand, hipStream_t s);
+// Waits until everything that has been enqueued in the stream is done, and brings `words` words (kDoneWords at most) from the device then.
+constexpr int kDoneWords = 31;
+int32_t stream_done(hipStream_t s, const void *dev = nullptr, void *host = nullptr, int words = 0);
 // --- price.hip
 // Exact assignment by equilibrium prices and shortest augmenting paths.  The host enqueues the passes as they are needed (it
 // polls the calling thread's pinned words), then the last pass and the search behind them, and does not wait for these.  The
-// outcome is left in the pinned host state (fin == 2: certified; 1: not, but another try from the prices reached and with
+// outcome is left in a PriceReport (fin == 2: certified; 1: not, but another try from the prices reached and with
 // more exchanges may do it, retry > 0 counts these; anything else: the auction has to solve the problem).
 // k <= E <= kPriceMaxE, one capacity for all experts, any relation of demand and capacity (rows that cannot be filled
 // end in -1).
 // Up to kPriceTries tries of up to kPriceTryPasses passes: a caller's round cap below that goes to the auction, which ends at
 // the cap with what it has.
 constexpr int kPriceTries = 3, kPriceTryPasses = 20;
+// What a try has come to, left on the device.
+struct PriceReport {
+    long long total;
+    long long t_end;         // device clock (10 ns) at the end of the search ...
+    long long t_after;       // ... and of the caller's work behind it
+    int flow, passes, fin, paths;
+    int ticks, pad;          // from the first kernel of the first try to t_end
+};
+static_assert(sizeof(PriceReport) / 4 <= kDoneWords, "stream_done brings it");
 struct PriceGeometry {
+    PriceReport *report;     // (device)
     int rows, n_wg;          // blocks of rows over which the pairs are counted (WorkspaceLayout::wcnt_off)
     int one_launch;          // all price passes were one launch
 };
@@ -145,13 +156,11 @@ inline bool iter_tiles_are_words(const WorkspaceLayout &L, int T, int E, int k)
 // expert), and the same as the device sees them.
 constexpr int kSolverWords = 16;
 int32_t solver_words(int **host, int **dev);
-// Waits until everything that has been enqueued in the stream is done.
-int32_t stream_done(hipStream_t s);
 // With kernel timing on, records the next of the calling thread's timing events: before and after the first kernel of a round
 // (auction) or pass (price solve) and after its second, three in all.
 int32_t solver_mark(hipStream_t s);
 int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_t *prices_in, int retry, PricePart part,
-                      int32_t *assign, int64_t *prices, int64_t *price_scale, char *ws, SolverState *host_state_dev, PriceGeometry *geom, hipStream_t s);
+                      int32_t *assign, int64_t *prices, int64_t *price_scale, char *ws, PriceGeometry *geom, hipStream_t s);
 // Runs price_enqueue and the caller's work behind it and waits.  *solved: whether the result stands.
 int32_t price_run(const int32_t *q, int T, int E, int k, int C, const maxscore_opts &o, int32_t *assign, int64_t *prices,
                   int64_t *price_scale, maxscore_stats *stats, char *ws, hipStream_t s, SolverGeometry *geom,

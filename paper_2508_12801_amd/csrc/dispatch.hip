@@ -6,7 +6,6 @@
 // recomputes each pair's stable rank inside its tile.  A tile is kTile consecutive slots of the
 // token-major [T, k] assignment and is owned by one wavefront.
 #include "common.h"
-#include "host_words.h"
 
 namespace maxscore {
 namespace {
@@ -420,7 +419,7 @@ __global__ __launch_bounds__(256) void k_count_scatter(const int *__restrict__ d
         token_pos[(size_t)row0 * k + idx] = pos;
         gates[(size_t)row0 * k + idx] = g_[i];
     }
-    if (clock && w == gridDim.x - 1 && tid == 0) tell_host(clock, (long long)wall_clock64());
+    if (clock && w == gridDim.x - 1 && tid == 0) *clock = wall_clock64();
 }
 
 }  // namespace

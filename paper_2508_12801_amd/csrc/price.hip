@@ -86,6 +86,9 @@ constexpr int kAllArcs = 4000;                    // problems with this few exch
 // From the seventh pass on, which only rows that are nearly alike come to, a third of a token per expert: of 256 experts their searches are long
 // (six such batches of 16384 tokens 1.17 of the time of before with five sixths throughout, 0.92 so; 40 others 0.97 and 0.95).
 constexpr int kEnough = 5, kLateEnough = 2, kRetryEnough = 1, kUsualPasses = 6;       // the first three are sixths of a token per expert
+// A pass that finds no more than kSoon times as many is likely to be the last but one.  (305 solves against four times: 1.005 with three, 1.008 with two
+// and six, 1.034 with one, 1.036 if the end is never enqueued ahead.)
+constexpr int kSoon = 4;
 // Steps are shortened by an eighth when few tokens are too many: experts that chase each other's last tokens settle sooner.  Of 500 drawn
 // batches (64 to 65536 tokens, 8 to 256 experts) solves took 3.6 % longer with three eighths (6 % at 64 and 128 experts, 1 % at 8 and 16); with a sixth,
 // a sixteenth or none within 1 % of an eighth; within 1 % the same with a twelfth and a twentieth.
@@ -102,8 +105,11 @@ constexpr int kSampledPasses = 2, kTightPasses = 6, kSlackPasses = 18, kRetryPas
 static_assert(kSampledPasses + kSlackPasses <= kPriceTryPasses && kSampledPasses + kTightPasses + kFarPasses <= kPriceTryPasses, "the round cap of a call allows every pass");
 constexpr int kPRowsMax = 128;                    // rows of a block of the final pass at most
 constexpr int kPriceWordDone = 0, kPriceWordPasses = 1;      // pinned words of the calling thread
-constexpr int kPriceFarBit = 16;                             // of the passes' word, from a pass that found more than kFar tokens per expert to move
+// Bits of the passes' word: a pass found more than kFar tokens per expert to move; the last one found so few that the next one may end the passes.
+constexpr int kPriceFarBit = 16, kPriceSoonBit = 17, kPricePassMask = (1 << kPriceFarBit) - 1;
 enum { kModeTight = 0, kModeSlack = 1, kModeOver = 2 };
+// So many sixths of a token per expert too many end the passes at pass t (not counting samples).
+__device__ __forceinline__ int enough_sixths(int t, int retry) { return retry ? kRetryEnough : t < kUsualPasses ? kEnough : kLateEnough; }
 
 struct PriceMeta {
     int w;            // margins below this were binned by the pass
@@ -124,6 +130,7 @@ struct PriceArea {
     int fail;
     int pad[7];
     long long t_start;
+    PriceReport report;
     long long pad2;
     // margins and holds, PriceArgs::copies times: (2 * nb + 1) rows of ES columns, filled by a pass (workgroup b adds to copy b
     // modulo their number), added up and cleared by the update behind it.  With one copy for all the additions took 25 us
@@ -150,6 +157,7 @@ struct PriceArgs {
     int arcs_wanted;                              // about so many exchanges are to lie under the bound
     int lists;                                    // of arcs: one or kPLists
     int sampled;                                  // passes over a sample before the others
+    int *host;                                    // pinned words
     int look;                                     // the pass that tells whether more than the usual ones are needed, or -1
 };
 
@@ -307,7 +315,7 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
     sx = sd > sx ? sd : sx;                                           // tokens too many or too few
     // enough: what is left is cheaper to move by the search
     const int excess = sampled ? (int)((long long)sx * a.T / nrows) : sx;
-    const bool enough = !sampled && 6 * excess <= E * (a.retry ? kRetryEnough : t - a.sampled < kUsualPasses ? kEnough : kLateEnough);
+    const bool enough = !sampled && 6 * excess <= E * enough_sixths(t - a.sampled, a.retry);
     const bool moves = excess > 0 || sampled || a.retry;               // (another try may have to go on all the same)
     // the capacity, or the mean demand (of the experts together no less than the capacity: one of them that has room is at its own mean)
     int target = slack || ss == 0 ? Ct : (2 * sn + ss) / (2 * ss);
@@ -561,7 +569,7 @@ constexpr int price_pieces(bool half) { return (kPTableInts / (half ? 8 : 4) + k
 // sums of the bins and the largest step taken behind the copies); with spare capacity 9 at 96, and 4.8 where the passes end.  As the first step of every workgroup of the next pass the same
 // work took 10 to 20 us.
 template <int N, int M, bool HALF, bool SPARE>
-__global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, int nrows, int *host)
+__global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, int nrows)
 {
     extern __shared__ __attribute__((aligned(16))) int s_h[];         // the sum of the copies
     __shared__ StepLds s;
@@ -580,10 +588,17 @@ __global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, 
     else m2 = price_step<true, SPARE, false>(a, t, nrows, mt, s_h, s);
     if (t == a.look) m2.far = m2.excess > kFar * E;
     for (int e = tid; e < E; e += kUThreads) ar->prices[e] = s.now[e];
-    if (tid == 0) {
-        ar->meta = m2;
-        __hip_atomic_store(host + (m2.done ? kPriceWordDone : kPriceWordPasses), m2.done ? 1 : (t + 1) | (m2.far << kPriceFarBit), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_SYSTEM);
+    if (tid == 0) ar->meta = m2;
+}
+
+// What the host is to know of the passes before pass t: the next launch tells it when it begins, as the step would have to wait a microsecond
+// for the word to get there before it ends.
+__device__ __forceinline__ void price_tell(const PriceArgs &a, const PriceMeta &mt, int t)
+{
+    if (mt.done) tell_host(a.host + kPriceWordDone, 1);
+    else if (t > 0) {
+        const bool soon = t > a.sampled && 6 * mt.excess <= kSoon * a.E * enough_sixths(t - a.sampled, a.retry);
+        tell_host(a.host + kPriceWordPasses, t | (mt.far << kPriceFarBit) | ((soon ? 1 : 0) << kPriceSoonBit));
     }
 }
 
@@ -686,7 +701,7 @@ __device__ __forceinline__ void price_rows(const PriceArgs &a, int W, int r_firs
 // 5.7, 13.0 and 13.0, one, with half as many wavefronts to a table, 10.6, 20.1 and 18.3; without any of the additions it would be 4.0,
 // 6.2 and 7.1.
 template <int G, int EPL, int MODE>
-__global__ __launch_bounds__(kQThreads) void k_price(PriceArgs a, int nrows, int stride, int shift, int rows_per_wg)
+__global__ __launch_bounds__(kQThreads) void k_price(PriceArgs a, int t, int nrows, int stride, int shift, int rows_per_wg)
 {
     using RK = RowKeys<G, EPL>;
     extern __shared__ __attribute__((aligned(16))) int s_hist[];      // (2 * nb + 1) x ES: margins of holds, of newcomers, holds
@@ -707,6 +722,7 @@ __global__ __launch_bounds__(kQThreads) void k_price(PriceArgs a, int nrows, int
     }
     const PriceMeta mt = ar->meta;
     for (int e = tid; e < E; e += kQThreads) s_p[e] = ar->prices[e];
+    if (blockIdx.x == 0 && tid == 0) price_tell(a, mt, t);
     if (mt.done) return;
     const int hquads = a.quads;
     for (int i = tid; i < hquads; i += kQThreads) ((int4 *)s_hist)[i] = make_int4(0, 0, 0, 0);
@@ -786,7 +802,7 @@ __global__ __launch_bounds__(kUThreads) void k_price_small(PriceArgs a, int n_pa
 // evaluated a second time for its arcs, which a block gathers in LDS: 18 us for 65536 tokens of 128 experts, 8.6 for 16384 of 64 (30 and
 // 16 while the rows were evaluated three times, to count the arcs and to write them in the order of the rows).
 template <int G, int EPL, bool OS>
-__global__ __launch_bounds__(kPThreads) void k_price_assign(PriceArgs a)
+__global__ __launch_bounds__(kPThreads) void k_price_assign(PriceArgs a, int if_done)          // if_done: nothing before that, a pass `if_done` will follow
 {
     using RK = RowKeys<G, EPL>;
     constexpr int NG = kPThreads / G;
@@ -813,6 +829,11 @@ __global__ __launch_bounds__(kPThreads) void k_price_assign(PriceArgs a)
     if (tid == 0) s_nq = s_narcs = s_bad = 0;
     for (int e = tid; e < E; e += kPThreads) s_p[e] = ar->prices[e];
     const int B = ar->meta.bound;
+    if (if_done) {
+        const PriceMeta mt = ar->meta;
+        if (w == 0 && tid == 0) price_tell(a, mt, if_done);
+        if (!mt.done) return;
+    }
     __syncthreads();
     const int bias = 1 << (31 - ib);
     const unsigned cmask = (1u << ib) - 1;
@@ -1019,7 +1040,7 @@ __device__ __forceinline__ int moved_slot(int u) { return (u ^ (u >> 10)) & (kMo
 // batches each: 65536 tokens of 128 experts 77 -> 61 us, 16384 of 256 155 -> 97, 10007 of 96 77 -> 47, 16384 of 64 52 -> 37, 4096 of 16 23
 // -> 18, 64 of 8 18 -> 15.  (The prices the passes end at are others since; a single batch may go the other way.)
 template <int TEPL, bool OS>
-__global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t *prices, int64_t *price_scale, SolverState *host_state)
+__global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t *prices, int64_t *price_scale, int if_done)
 {
     constexpr int NT = kFThreads, NW = NT / 64;
     constexpr int FIRST = 4;                     // arcs of every thread that are requested before their number is known
@@ -1044,6 +1065,7 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
         arc0[j] = ar->arc[at];
         tok0[j] = ar->arc_tok[at];
     }
+    if (if_done && !mt.done) return;
     const int n_upto = wave_sum(n_list), n_listed = __builtin_amdgcn_readlane(n_upto, 63);
     bool ok = fail == 0 && !__any((unsigned)n_list > (unsigned)list_room);
     int rounds = 0, augs = 0;
@@ -1632,17 +1654,14 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
     __syncthreads();
     if (tid == 0) {
         if (certified && price_scale) *price_scale = (int64_t)1 << sb;
-        tell_host(&host_state->total, s.dsum);
-        tell_host(&host_state->flow, OS ? E * a.C : a.T * k);
-        tell_host(&host_state->round, mt.passes);
-        tell_host(&host_state->phases, 1);
-        tell_host(&host_state->status, (int)MAXSCORE_OK);
-        tell_host(&host_state->fin, certified ? 2 : close ? 1 : 3);
-        tell_host(&host_state->fin_passes, 1);
-        tell_host(&host_state->fin_cycles, augs);
-        tell_host(&host_state->fin_dirty, rounds);
-        tell_host(&host_state->t_start, ar->t_start);
-        tell_host(&host_state->t_end, (long long)wall_clock64());
+        PriceReport &r = ar->report;
+        r.total = s.dsum;
+        r.flow = OS ? E * a.C : a.T * k;
+        r.passes = mt.passes;
+        r.fin = certified ? 2 : close ? 1 : 3;
+        r.paths = augs;
+        r.t_end = wall_clock64();
+        r.ticks = (int)(r.t_end - ar->t_start);
     }
 }
 
@@ -1698,7 +1717,7 @@ bool price_supported(int T, int E, int k)
 }
 
 int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_t *prices_in, int retry, PricePart part, int32_t *assign, int64_t *prices,
-                      int64_t *price_scale, char *ws, SolverState *host_state_dev, PriceGeometry *geom, hipStream_t s)
+                      int64_t *price_scale, char *ws, PriceGeometry *geom, hipStream_t s)
 {
     int *words = nullptr, *words_dev = nullptr;
     const int32_t wrc = solver_words(&words, &words_dev);
@@ -1708,6 +1727,7 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     WorkspaceLayout L = workspace_layout(T, E, k);
     PriceArgs a;
     a.q = q;
+    a.host = words_dev;
     a.assign = assign;
     a.ar = (PriceArea *)(ws + L.price_off);
     a.blkcnt = (int *)(ws + L.wcnt_off);
@@ -1744,6 +1764,7 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     a.lists = a.n_wg >= kPListsFrom ? kPLists : 1;
     a.sampled = n_sampled;
     a.look = a.mode != kModeSlack && !retry ? n_sampled + kTightPasses - 2 : -1;
+    geom->report = &a.ar->report;
     geom->rows = rows;
     geom->n_wg = a.n_wg;
 
@@ -1756,94 +1777,120 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     const int plim = (1 << (31 - a.ib)) - 1;
     geom->one_launch = small ? 1 : 0;
     if (part == kPriceBegin && !small) return MAXSCORE_OK;
-    if (!small)
-        hipLaunchKernelGGL(k_price_init, dim3(64), dim3(kPThreads), 0, s, a.ar, a.quads, E, plim, prices_in, a.retry);
-    for (int t = small ? n_pass : 0; t <= n_pass; ++t) {
-        // Pass t is enqueued when pass t - 2 has ended, so that one stays queued behind the one that runs: a pass that is still
-        // queued when the prices are done costs two empty launches (5 us; a batch with room to spare needs one of eighteen).
-        // The stream is looked at now and then: a stream that has drained or failed ends the wait.
-        for (unsigned spin = 1; t >= 2 && !small && !hw[kPriceWordDone] && (hw[kPriceWordPasses] & ((1 << kPriceFarBit) - 1)) < t - 1; ++spin) {
-            if ((spin & 4095) == 0 && hipStreamQuery(s) != hipErrorNotReady) break;
-            __builtin_ia32_pause();
-        }
-        if (t == a.look + 2 && a.look >= 0 && !small && hw[kPriceWordPasses] >> kPriceFarBit) n_pass += kFarPasses;
-        if (hw[kPriceWordDone]) t = n_pass;
-        const bool fin = t == n_pass;
-        const int st = t < n_sampled ? stride : 1;
-        const int nrows = st > 1 ? kSampleRows : T;
-        const int shift = st > 1 ? t * (st / 2) : 0;
-        const int rw = price_pass_rows(nrows, E, k);
-        const int grid = fin ? a.n_wg : (nrows + rw - 1) / rw;
+#define MS_PG(GG, XX)                                                                                                     \
+    do {                                                                                                                  \
+        if (EPL == 1) XX(GG, 1);                                                                                          \
+        else if (EPL == 2) XX(GG, 2);                                                                                     \
+        else if (EPL == 4) XX(GG, 4);                                                                                     \
+        else if (EPL == 8) XX(GG, 8);                                                                                     \
+        else XX(GG, 16);                                                                                                  \
+    } while (0)
+#define MS_SHAPED(XX)            \
+    do {                         \
+        if (G == 8) MS_PG(8, XX); \
+        else if (G == 16) MS_PG(16, XX); \
+        else if (G == 32) MS_PG(32, XX); \
+        else MS_PG(64, XX);      \
+    } while (0)
+    // a pass and its step
+    auto enqueue_pass = [&](int t) {
+        const int st = t < n_sampled ? stride : 1, nrows = st > 1 ? kSampleRows : T, shift = st > 1 ? t * (st / 2) : 0;
+        const int rw = price_pass_rows(nrows, E, k), grid = (nrows + rw - 1) / rw;
+        mark();
 #define MS_P(GG, PP)                                                                                                      \
     do {                                                                                                                  \
-        if (fin) {                                                                                                        \
-            if (small && part != kPriceRest) {                                                                            \
-                mark();                                                                                                   \
-                if (a.mode == kModeTight) hipLaunchKernelGGL((k_price_small<GG, PP, kModeTight>), dim3(1), dim3(kUThreads), shm, s, a, kSmallPasses, plim, prices_in); \
-                else if (os) hipLaunchKernelGGL((k_price_small<GG, PP, kModeOver>), dim3(1), dim3(kUThreads), shm, s, a, kSmallPasses, plim, prices_in); \
-                else hipLaunchKernelGGL((k_price_small<GG, PP, kModeSlack>), dim3(1), dim3(kUThreads), shm, s, a, kSmallPasses, plim, prices_in); \
-                mark();                                                                                                   \
-                mark();                                                                                                   \
-            }                                                                                                             \
-            if (part == kPriceBegin) break;                                                                               \
-            if (os) hipLaunchKernelGGL((k_price_assign<GG, PP, true>), dim3(grid), dim3(kPThreads), 0, s, a);     \
-            else hipLaunchKernelGGL((k_price_assign<GG, PP, false>), dim3(grid), dim3(kPThreads), 0, s, a);       \
-        } else {                                                                                                          \
-            mark();                                                                                                       \
-            if (a.mode == kModeTight) hipLaunchKernelGGL((k_price<GG, PP, kModeTight>), dim3(grid), dim3(kQThreads), shm, s, a, nrows, st, shift, rw); \
-            else if (os) hipLaunchKernelGGL((k_price<GG, PP, kModeOver>), dim3(grid), dim3(kQThreads), shm, s, a, nrows, st, shift, rw); \
-            else hipLaunchKernelGGL((k_price<GG, PP, kModeSlack>), dim3(grid), dim3(kQThreads), shm, s, a, nrows, st, shift, rw); \
-            mark();                                                                                                       \
-        }                                                                                                                 \
+        if (a.mode == kModeTight) hipLaunchKernelGGL((k_price<GG, PP, kModeTight>), dim3(grid), dim3(kQThreads), shm, s, a, t, nrows, st, shift, rw); \
+        else if (os) hipLaunchKernelGGL((k_price<GG, PP, kModeOver>), dim3(grid), dim3(kQThreads), shm, s, a, t, nrows, st, shift, rw); \
+        else hipLaunchKernelGGL((k_price<GG, PP, kModeSlack>), dim3(grid), dim3(kQThreads), shm, s, a, t, nrows, st, shift, rw); \
     } while (0)
-#define MS_PG(GG)                                                                                                         \
-    do {                                                                                                                  \
-        if (EPL == 1) MS_P(GG, 1);                                                                                        \
-        else if (EPL == 2) MS_P(GG, 2);                                                                                   \
-        else if (EPL == 4) MS_P(GG, 4);                                                                                   \
-        else if (EPL == 8) MS_P(GG, 8);                                                                                   \
-        else MS_P(GG, 16);                                                                                                \
-    } while (0)
-        if (G == 8) MS_PG(8);
-        else if (G == 16) MS_PG(16);
-        else if (G == 32) MS_PG(32);
-        else MS_PG(64);
-#undef MS_PG
+        MS_SHAPED(MS_P);
 #undef MS_P
-        if (!fin) {
+        mark();
 #define MS_U(NN, SS)                                                                                                      \
     do {                                                                                                                  \
-        if (!a.half) hipLaunchKernelGGL((k_price_update<NN, price_pieces(false), false, SS>), dim3(1), dim3(kUThreads), shm, s, a, t, nrows, words_dev); \
-        else if (a.quads <= 2 * kUThreads) hipLaunchKernelGGL((k_price_update<NN, 1, true, SS>), dim3(1), dim3(kUThreads), shm, s, a, t, nrows, words_dev); \
-        else hipLaunchKernelGGL((k_price_update<NN, price_pieces(true), true, SS>), dim3(1), dim3(kUThreads), shm, s, a, t, nrows, words_dev); \
+        if (!a.half) hipLaunchKernelGGL((k_price_update<NN, price_pieces(false), false, SS>), dim3(1), dim3(kUThreads), shm, s, a, t, nrows); \
+        else if (a.quads <= 2 * kUThreads) hipLaunchKernelGGL((k_price_update<NN, 1, true, SS>), dim3(1), dim3(kUThreads), shm, s, a, t, nrows); \
+        else hipLaunchKernelGGL((k_price_update<NN, price_pieces(true), true, SS>), dim3(1), dim3(kUThreads), shm, s, a, t, nrows); \
     } while (0)
 #define MS_US(NN)                                  \
     do {                                           \
         if (a.mode == kModeSlack) MS_U(NN, true);  \
         else MS_U(NN, false);                      \
     } while (0)
-            if (a.copies == 8) MS_US(8);
-            else if (a.copies == 4) MS_US(4);
-            else MS_US(2);
+        if (a.copies == 8) MS_US(8);
+        else if (a.copies == 4) MS_US(4);
+        else MS_US(2);
 #undef MS_US
 #undef MS_U
+        mark();
+    };
+    // the last pass and the search; if_done: unless the passes turn out to go on with pass if_done
+    auto enqueue_end = [&](int if_done) {
+#define MS_P(GG, PP)                                                                                                      \
+    do {                                                                                                                  \
+        if (os) hipLaunchKernelGGL((k_price_assign<GG, PP, true>), dim3(a.n_wg), dim3(kPThreads), 0, s, a, if_done);      \
+        else hipLaunchKernelGGL((k_price_assign<GG, PP, false>), dim3(a.n_wg), dim3(kPThreads), 0, s, a, if_done);        \
+    } while (0)
+        MS_SHAPED(MS_P);
+#undef MS_P
+#define MS_F(PP)                                                                                                          \
+    do {                                                                                                                  \
+        if (os) hipLaunchKernelGGL((k_price_finish<PP, true>), dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, if_done);  \
+        else hipLaunchKernelGGL((k_price_finish<PP, false>), dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, if_done);    \
+    } while (0)
+        if (E <= 64) MS_F(1);
+        else if (E <= 128) MS_F(2);
+        else if (E <= 256) MS_F(4);
+        else MS_F(8);
+#undef MS_F
+    };
+    if (small) {
+        if (part != kPriceRest) {
+            mark();
+#define MS_P(GG, PP)                                                                                                      \
+    do {                                                                                                                  \
+        if (a.mode == kModeTight) hipLaunchKernelGGL((k_price_small<GG, PP, kModeTight>), dim3(1), dim3(kUThreads), shm, s, a, kSmallPasses, plim, prices_in); \
+        else if (os) hipLaunchKernelGGL((k_price_small<GG, PP, kModeOver>), dim3(1), dim3(kUThreads), shm, s, a, kSmallPasses, plim, prices_in); \
+        else hipLaunchKernelGGL((k_price_small<GG, PP, kModeSlack>), dim3(1), dim3(kUThreads), shm, s, a, kSmallPasses, plim, prices_in); \
+    } while (0)
+            MS_SHAPED(MS_P);
+#undef MS_P
+            mark();
             mark();
         }
-    }
-    if (part == kPriceBegin) {
+        if (part != kPriceBegin) enqueue_end(0);
         MS_HIP(hipGetLastError());
         return mrc;
     }
-#define MS_F(PP)                                                                                                                            \
-    do {                                                                                                                                    \
-        if (os) hipLaunchKernelGGL((k_price_finish<PP, true>), dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, host_state_dev);     \
-        else hipLaunchKernelGGL((k_price_finish<PP, false>), dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, host_state_dev);       \
-    } while (0)
-    if (E <= 64) MS_F(1);
-    else if (E <= 128) MS_F(2);
-    else if (E <= 256) MS_F(4);
-    else MS_F(8);
-#undef MS_F
+    hipLaunchKernelGGL(k_price_init, dim3(64), dim3(kPThreads), 0, s, a.ar, a.quads, E, plim, prices_in, a.retry);
+    // until the passes before pass t have ended; the stream is looked at now and then: one that has drained or failed ends the wait
+    auto wait_for = [&](int t) {
+        for (unsigned spin = 1; !hw[kPriceWordDone] && (hw[kPriceWordPasses] & kPricePassMask) < t; ++spin) {
+            if ((spin & 4095) == 0 && hipStreamQuery(s) != hipErrorNotReady) break;
+            __builtin_ia32_pause();
+        }
+    };
+    // Pass t is enqueued when pass t - 1 has begun, so that one stays queued behind the one that runs: a pass that is still queued when the
+    // prices are done costs two empty launches (5 us).  So where the pass that runs is likely to be the last, the end is enqueued behind it
+    // instead, which looks at the prices first; if these are not done, that costs as much.
+    bool ended = false;
+    for (int t = 0; !ended; ++t) {
+        if (t >= 2 && (t < n_pass || t == a.look + 2)) {
+            wait_for(t - 1);
+            if (t == a.look + 2 && hw[kPriceWordPasses] >> kPriceFarBit & 1) n_pass += kFarPasses;
+            if (hw[kPriceWordDone]) break;
+            if (t < n_pass && hw[kPriceWordPasses] >> kPriceSoonBit & 1) {
+                enqueue_end(t);
+                wait_for(t);
+                ended = hw[kPriceWordDone] != 0;
+            }
+        }
+        if (t >= n_pass) break;
+        if (!ended) enqueue_pass(t);
+    }
+    if (!ended) enqueue_end(0);
+#undef MS_SHAPED
+#undef MS_PG
     MS_HIP(hipGetLastError());
     return mrc;
 }

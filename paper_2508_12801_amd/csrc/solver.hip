@@ -1826,11 +1826,12 @@ struct SolverHost {
         hipStream_t s = nullptr;
         int T = 0, E = 0, k = 0, C = 0;
     } begun;
-    unsigned done_seq = 0;            // what stream_done's word was last to be
+    unsigned done_seq = 0;            // waits in stream_done so far
     int device = -1;
 };
 
-constexpr int kDoneWord = kSolverWords + kMaxE + 16, kPinnedWords = kDoneWord + 16;      // stream_done's word, in a line to itself
+constexpr int kDoneWord = kSolverWords + kMaxE + 16, kPinnedWords = kDoneWord + 2 * (kDoneWords + 1);      // stream_done's words, of eight bytes each
+static_assert(kDoneWord % 16 == 0, "in lines to themselves");
 
 static int32_t solver_host(SolverHost **out)
 {
@@ -1867,22 +1868,34 @@ int32_t solver_words(int **host, int **dev)
     return MAXSCORE_OK;
 }
 
-// Behind all that has been enqueued a kernel of one thread writes a word of pinned memory, which the host polls: hipStreamSynchronize
-// returns 6 us after such a word is there, and 20 where more than a handful of launches came before it.  A wait of more than about a
+// Behind all that has been enqueued a kernel of one wavefront writes words of pinned memory, which the host polls: hipStreamSynchronize
+// returns 6 us after such a word is there, and 20 where more than a handful of launches came before it.  Every word carries the number of
+// the wait, so that no order among them is needed.  Results that are brought along need no words of their own, whose way to the host, a
+// microsecond or two, the kernel that found them would have to wait for before the next one begins.  A wait of more than about a
 // millisecond goes on in hipStreamSynchronize, which sleeps, and which reports an error of the stream.
-__global__ void k_done(unsigned *word, unsigned v) { tell_host(word, v); }
-
-int32_t stream_done(hipStream_t s)
+__global__ void k_done(unsigned long long *host, unsigned v, const int *__restrict__ words, int n)
 {
+    const int i = threadIdx.x;
+    if (i <= n) tell_host(host + i, (unsigned long long)v << 32 | (unsigned)(i < n ? words[i] : 0));
+}
+
+int32_t stream_done(hipStream_t s, const void *dev, void *host, int words)
+{
+    if (words < 0 || words > kDoneWords) return MAXSCORE_ERR_SHAPE;
     SolverHost *hs = nullptr;
     const int32_t rc = solver_host(&hs);
     if (rc) return rc;
     const unsigned v = ++hs->done_seq;
-    hipLaunchKernelGGL(k_done, dim3(1), dim3(1), 0, s, (unsigned *)hs->flag_dev + kDoneWord, v);
+    hipLaunchKernelGGL(k_done, dim3(1), dim3(64), 0, s, (unsigned long long *)(hs->flag_dev + kDoneWord), v, (const int *)dev, words);
     MS_HIP(hipGetLastError());
-    volatile unsigned *word = (volatile unsigned *)hs->flag + kDoneWord;
-    for (int spin = 0; spin < 20000 && *word != v; ++spin) __builtin_ia32_pause();
-    if (*word != v) MS_HIP(hipStreamSynchronize(s));
+    volatile unsigned long long *word = (volatile unsigned long long *)(hs->flag + kDoneWord);
+    int have = 0;
+    for (int spin = 0; spin < 20000 && have <= words; ++spin) {
+        if ((unsigned)(word[have] >> 32) == v) ++have;
+        else __builtin_ia32_pause();
+    }
+    if (have <= words) MS_HIP(hipStreamSynchronize(s));
+    for (int i = 0; i < words; ++i) ((int *)host)[i] = (int)(unsigned)word[i];
     std::atomic_thread_fence(std::memory_order_acquire);
     return MAXSCORE_OK;
 }
@@ -1976,7 +1989,7 @@ extern "C" int32_t maxscore_route_begin(const int32_t *q, int32_t T, int32_t E, 
     hipStream_t s = (hipStream_t)stream;
     PriceGeometry pg;
     hs->begun.q = nullptr;
-    rc = price_enqueue(q, T, E, k, Ce, o.prices_in, 0, kPriceBegin, nullptr, nullptr, nullptr, (char *)workspace, hs->state_dev, &pg, s);
+    rc = price_enqueue(q, T, E, k, Ce, o.prices_in, 0, kPriceBegin, nullptr, nullptr, nullptr, (char *)workspace, &pg, s);
     if (rc || !pg.one_launch) return rc;
     hs->begun.q = q;
     hs->begun.prices_in = o.prices_in;
@@ -2005,30 +2018,28 @@ int32_t price_run(const int32_t *q, int T, int E, int k, int C, const maxscore_o
     if (!price_takes(T, E, k, C, o)) return MAXSCORE_OK;
     hs->tev_used = 0;
     PriceGeometry pg;
-    SolverState h;
+    PriceReport h = {};
     int passes = o.prices_in ? -1 : 0;            // (the pass that checks given prices is a launch like the others)
     for (int attempt = 0;; ++attempt) {
-        hs->state->fin = 0;
         const size_t mark = hs->tev_used;
         rc = price_enqueue(q, T, E, k, C, o.prices_in, attempt, begun && attempt == 0 ? kPriceRest : kPriceAll, assign, prices, price_scale, ws,
-                           hs->state_dev, &pg, s);
+                           &pg, s);
         if (rc == MAXSCORE_OK && after) {
-            const SolverGeometry g = {pg.rows, pg.n_wg, 0, 1, &hs->state_dev->t_after};
+            const SolverGeometry g = {pg.rows, pg.n_wg, 0, 1, &pg.report->t_after};
             rc = after(after_ctx, g, s, nullptr);
         }
         if (rc != MAXSCORE_OK) {
             (void)hipStreamSynchronize(s);
             return rc;
         }
-        rc = stream_done(s);
+        rc = stream_done(s, pg.report, &h, sizeof(h) / 4);
         if (rc) return rc;
-        h = *hs->state;
-        rc = add_launch_times(hs, mark, pg.one_launch ? 1 : h.round - passes, pg.one_launch ? 1 : 2, stats, s);
+        rc = add_launch_times(hs, mark, pg.one_launch ? 1 : h.passes - passes, pg.one_launch ? 1 : 2, stats, s);
         if (rc) return rc;
-        passes = h.round;
+        passes = h.passes;
         if (h.fin == 2) break;
         if (h.fin != 1 || attempt + 1 >= kPriceTries) {
-            if (stats) stats->solver_ms += (float)(h.t_end - h.t_start) * 1e-5f;      // (the first try's start to here)
+            if (stats) stats->solver_ms += (float)h.ticks * 1e-5f;
             return MAXSCORE_OK;
         }
     }
@@ -2037,13 +2048,13 @@ int32_t price_run(const int32_t *q, int T, int E, int k, int C, const maxscore_o
     if (stats) {
         stats->total_score_q = h.total;
         stats->flow_value = h.flow;
-        stats->rounds = h.round;
-        stats->phases = h.phases;
-        stats->status = h.status;
-        stats->solver_ms = (float)(h.t_end - h.t_start) * 1e-5f;          // ticks of 10 ns
+        stats->rounds = h.passes;
+        stats->phases = 1;
+        stats->status = MAXSCORE_OK;
+        stats->solver_ms = (float)h.ticks * 1e-5f;          // ticks of 10 ns
         stats->gates_dispatch_ms = after ? (float)(h.t_after - h.t_end) * 1e-5f : 0.f;
-        stats->finish_passes = h.fin_passes;
-        stats->finish_cycles = h.fin_cycles;
+        stats->finish_passes = 1;
+        stats->finish_cycles = h.paths;
     }
     return MAXSCORE_OK;
 }
