@@ -5,6 +5,7 @@
 // A row is moved as 16-byte vectors by consecutive lanes, so every load and store of a wavefront is one
 // contiguous kilobyte; the per-row indices are wavefront-uniform and read through the scalar path.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 
@@ -12,6 +13,7 @@ namespace maxscore {
 namespace {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 template <bool NT, typename V>
@@ -20,8 +22,8 @@ __device__ __forceinline__ void put(V v, V *p)
     if (NT) __builtin_nontemporal_store(v, p);
     else *p = v;
 }
-template <bool NT>
-__device__ __forceinline__ u32x4 get(const u32x4 *p)
+template <bool NT, typename V>
+__device__ __forceinline__ V get(const V *p)
 {
     return NT ? __builtin_nontemporal_load(p) : *p;
 }
@@ -224,7 +226,9 @@ __device__ __forceinline__ float bf16_to_f32(unsigned short b) { return __uint_a
 
 // A wavefront takes PIECES kilobytes of a token's row, its neighbours the next ones, and ends: the k gate-weighted pieces are accumulated
 // in fp32, slot by slot, and written as fp32.  The indices of the slots (64 at most) are read by one lane each, and kCombineLoads pieces
-// of them are on their way together.  Bound by HBM beyond the last cache, which takes short-lived wavefronts in the order of the addresses
+// of them are on their way together.  A lane takes four columns at a time, its neighbours the next ones, so that a store is whole lines of
+// fp32 (eight columns a lane, in one load of bf16, made every line of two stores: layers of 16384 tokens of 2048 to 8 of 64 experts 364 -> 357 us,
+// 32768 612 -> 606, 65536 to 8 of 128 1246 -> 1236).  Bound by HBM beyond the last cache, which takes short-lived wavefronts in the order of the addresses
 // best (a plain fill: 6.8 TB/s with 16 bytes a thread and no loop, 4.0 to 5.6 with loops over a fixed grid): 65536 tokens of 2048 from 8 of
 // 128 experts 460 us (5.8 TB/s), 496 with whole rows and a loop over the tokens in every wavefront; 44032 of 1024 from 2 of 64 75 to 69.
 constexpr int kCombineLoads = 4;
@@ -232,17 +236,18 @@ constexpr int kCombineLoads = 4;
 // AHEAD: the pieces of those slots are really on their way together.  A load under a condition is waited for before the next one (its register
 // could hold something else), so a slot that is empty then reads what the one before it did, and a lane beyond the row its end; neither is used.
 template <bool BF16, bool NT, int PIECES, bool AHEAD>
-__global__ __launch_bounds__(256) void k_combine(const u32x4 *__restrict__ buf, const int32_t *__restrict__ assign,
+__global__ __launch_bounds__(256) void k_combine(const void *__restrict__ buf_, const int32_t *__restrict__ assign,
                                                  const int32_t *__restrict__ token_pos,
                                                  const float *__restrict__ gates, int T, int d, int E, int k, int C,
-                                                 int vec_per_row, int parts, float *__restrict__ y)
+                                                 int parts, float *__restrict__ y)
 {
-    constexpr int EPV = BF16 ? 8 : 4;         // elements per 16-byte vector
-    constexpr int SLOTS = kCombineLoads / PIECES;
-    const int lane = threadIdx.x & 63;
+    using V = std::conditional_t<BF16, u32x2, u32x4>;        // four elements
+    constexpr int QUADS = PIECES * (BF16 ? 2 : 1), SLOTS = kCombineLoads / PIECES;
+    const V *buf = (const V *)buf_;
+    const int lane = threadIdx.x & 63, quads_per_row = d >> 2;
     const unsigned item = blockIdx.x * 4u + (threadIdx.x >> 6), i = __builtin_amdgcn_readfirstlane(item / (unsigned)parts);
     if (i >= (unsigned)T) return;
-    const int c = (int)(item - i * (unsigned)parts) * (64 * PIECES) + lane;
+    const int c = (int)(item - i * (unsigned)parts) * (64 * QUADS) + lane;
     int e = -1, pos = 0;
     float g = 0.f;
     if (lane < k) {
@@ -253,62 +258,52 @@ __global__ __launch_bounds__(256) void k_combine(const u32x4 *__restrict__ buf, 
         // an empty slot, or a place outside the expert's buffer (an assignment made with another capacity)
         if (e >= E || pos < 0 || pos >= C) e = -1;
     }
-    float acc[PIECES][EPV];
+    f32x4 acc[QUADS];
 #pragma unroll
-    for (int u = 0; u < PIECES; ++u)
+    for (int u = 0; u < QUADS; ++u) acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int at[QUADS];
 #pragma unroll
-        for (int v = 0; v < EPV; ++v) acc[u][v] = 0.f;
-    int at[PIECES];
-#pragma unroll
-    for (int u = 0; u < PIECES; ++u) at[u] = c + 64 * u < vec_per_row ? c + 64 * u : vec_per_row - 1;
-    const u32x4 *row = buf;
+    for (int u = 0; u < QUADS; ++u) at[u] = c + 64 * u < quads_per_row ? c + 64 * u : quads_per_row - 1;
+    const V *row = buf;
     for (int s = 0; s < k; s += SLOTS) {
-        u32x4 vals[SLOTS][PIECES];
+        V vals[SLOTS][QUADS];
         bool have[SLOTS];
 #pragma unroll
         for (int z = 0; z < SLOTS; ++z) {
             if (AHEAD) {
                 const int sl = s + z < k ? s + z : k - 1, ea = __builtin_amdgcn_readlane(e, sl);
                 have[z] = s + z < k && ea >= 0;
-                row = ea >= 0 ? buf + ((size_t)ea * C + __builtin_amdgcn_readlane(pos, sl)) * vec_per_row : row;
+                row = ea >= 0 ? buf + ((size_t)ea * C + __builtin_amdgcn_readlane(pos, sl)) * quads_per_row : row;
 #pragma unroll
-                for (int u = 0; u < PIECES; ++u) vals[z][u] = get<NT>(row + at[u]);
+                for (int u = 0; u < QUADS; ++u) vals[z][u] = get<NT>(row + at[u]);
                 continue;
             }
             const int es = s + z < k ? __builtin_amdgcn_readlane(e, s + z) : -1;
             have[z] = es >= 0;
             if (!have[z]) continue;
-            const u32x4 *src = buf + ((size_t)es * C + __builtin_amdgcn_readlane(pos, s + z)) * vec_per_row;
+            const V *src = buf + ((size_t)es * C + __builtin_amdgcn_readlane(pos, s + z)) * quads_per_row;
 #pragma unroll
-            for (int u = 0; u < PIECES; ++u) vals[z][u] = c + 64 * u < vec_per_row ? get<NT>(src + c + 64 * u) : u32x4{0u, 0u, 0u, 0u};
+            for (int u = 0; u < QUADS; ++u) vals[z][u] = get<NT>(src + at[u]);
         }
 #pragma unroll
         for (int z = 0; z < SLOTS; ++z) {
             if (!have[z]) continue;
             const float gs = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g), s + z));
 #pragma unroll
-            for (int u = 0; u < PIECES; ++u) {
-                if (BF16) {
+            for (int u = 0; u < QUADS; ++u)
 #pragma unroll
-                    for (int w = 0; w < 4; ++w) {
-                        const unsigned word = vals[z][u][w];
-                        acc[u][2 * w] = fmaf(gs, bf16_to_f32((unsigned short)(word & 0xffffu)), acc[u][2 * w]);
-                        acc[u][2 * w + 1] = fmaf(gs, bf16_to_f32((unsigned short)(word >> 16)), acc[u][2 * w + 1]);
-                    }
-                } else {
-#pragma unroll
-                    for (int w = 0; w < 4; ++w) acc[u][w] = fmaf(gs, __uint_as_float(vals[z][u][w]), acc[u][w]);
+                for (int w = 0; w < 4; ++w) {
+                    float x;
+                    if constexpr (BF16) x = __uint_as_float(w % 2 ? vals[z][u][w / 2] & 0xffff0000u : vals[z][u][w / 2] << 16);
+                    else x = __uint_as_float(vals[z][u][w]);
+                    acc[u][w] = fmaf(gs, x, acc[u][w]);
                 }
-            }
         }
     }
+    f32x4 *dst = (f32x4 *)(y + (size_t)i * d);
 #pragma unroll
-    for (int u = 0; u < PIECES; ++u) {
-        if (c + 64 * u >= vec_per_row) continue;
-        f32x4 *dst = (f32x4 *)(y + (size_t)i * d + (size_t)(c + 64 * u) * EPV);
-        put<NT>(f32x4{acc[u][0], acc[u][1], acc[u][2], acc[u][3]}, dst);
-        if (BF16) put<NT>(f32x4{acc[u][4], acc[u][5], acc[u][6], acc[u][7]}, dst + 1);
-    }
+    for (int u = 0; u < QUADS; ++u)
+        if (c + 64 * u < quads_per_row) put<NT>(acc[u], dst + c + 64 * u);
 }
 
 template <bool BF16>
@@ -408,8 +403,8 @@ int32_t combine_run(const void *buf, int dtype, const int32_t *assign, const int
             const int n = std::min(most, T - i0);
             const size_t at = (size_t)i0 * k;
 #define MS_COMBINE(BB, NN, PP, AA)                                                                                                   \
-    hipLaunchKernelGGL((k_combine<BB, NN, PP, AA>), dim3((unsigned)(((size_t)n * parts + 3) / 4)), dim3(256), 0, s, (const u32x4 *)buf, assign + at, \
-                       token_pos + at, gates + at, n, d, E, k, C, vpr, parts, y + (size_t)i0 * d)
+    hipLaunchKernelGGL((k_combine<BB, NN, PP, AA>), dim3((unsigned)(((size_t)n * parts + 3) / 4)), dim3(256), 0, s, buf, assign + at, \
+                       token_pos + at, gates + at, n, d, E, k, C, parts, y + (size_t)i0 * d)
 #define MS_COMBINE_P(BB, NN)                         \
     do {                                             \
         if (two) MS_COMBINE(BB, NN, 2, true);        \
