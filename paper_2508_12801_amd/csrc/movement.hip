@@ -331,9 +331,19 @@ __global__ __launch_bounds__(256) void k_combine_elem(const void *__restrict__ b
 
 }  // namespace
 
-// Traffic beyond the 256 MB of the last cache goes past it (non-temporal): 16384 tokens of 2048 to 8 of 64 experts
-// (512 MB of buffers) out and back 231 us instead of 282, while of 128 MB the way back finds more in the cache: 71 us, not 79.
+// What does not fit the 256 MiB of the last cache goes past it (non-temporal).  Rows out: buffers as large as that, or, with the rows they are
+// read from and the results that come back, a third more: what is written then leaves the cache before it is read.  Buffers of 1024
+// columns to 64 experts, the rerouting's layers, past the cache against through it: top-2 of 160 MiB (400 in all) 220 against 249 us, 200 (500)
+// 258 and 280, top-4 of 200 (350) 217 and 231, top-6 of 240 (360) 235 and 243, fp32 top-1 of 120 (360) 226 and 236; but top-2 of 120 (300)
+// 193 and 189, top-8 of 200 (275) 205 and 193 and of 240 (330) 224 and 225, 10007 of 1000 in fp32 to 6 of 96 (328) 318 and 312.
+// Rows back: buffers and results of half of it (top-2 of 160 MiB in all 153 against 162 us, of 240 189 and 201, top-4 of 180 161 and 166,
+// top-8 of 250 193 and 200; of 150 and less the same).
 static bool beyond_caches(size_t bytes) { return bytes >= (size_t)256 << 20; }
+static bool out_past_caches(size_t x_bytes, size_t buf_bytes, size_t y_bytes)
+{
+    return beyond_caches(buf_bytes) || x_bytes + buf_bytes + y_bytes >= (size_t)336 << 20;
+}
+static bool back_past_caches(size_t bytes) { return bytes >= (size_t)128 << 20; }
 
 int32_t dispatch_tokens_run(const void *x, int dtype, const int32_t *offsets, const int32_t *disp_token, int T, int d,
                             int E, int C, void *out, hipStream_t s)
@@ -350,7 +360,9 @@ int32_t dispatch_tokens_run(const void *x, int dtype, const int32_t *offsets, co
     // places of the lists are in use at a time.  In a layer, tight and with a quarter more room: 65536 tokens of 2048 to 8 of 128 experts
     // 512 -> 492 us, to 2 of 32 157 -> 138 and 187 -> 169, 33000 of 4096 to 4 of 32 262 -> 241 and 304 -> 285.  Of 128 to 192 MiB of x it
     // depends: 65536 of 1536 to 8 of 128 370 -> 340, to 4 of 64 167 -> 171.  A single expert a token: 117 -> 106 to 128, 92 -> 92 to 8.
-    const bool nt = beyond_caches((size_t)n_rows * d * eb), wide = nt && T >= 16 * 1024 && E <= 128 * 16 && beyond_caches((size_t)T * d * eb);
+    const size_t x_bytes = (size_t)T * d * eb, buf_bytes = (size_t)n_rows * d * eb;
+    const bool nt = out_past_caches(x_bytes, buf_bytes, (size_t)T * d * 4);
+    const bool wide = beyond_caches(buf_bytes) && T >= 16 * 1024 && E <= 128 * 16 && beyond_caches(x_bytes);
     const int tb = wide ? 16 : T >= 32 * 1024 ? 32 : T >= 16 * 1024 ? 16 : T >= 8 * 1024 ? 8 : 4;
     if (vec && T >= 4096 && E <= 128 * tb && E <= kListMaxE && n_rows < (1ll << 32)) {
         const int n_tb = (T + tb - 1) / tb, n_pad = (int)std::min<long long>((n_rows + 255) / 256, 1024);
@@ -383,7 +395,7 @@ int32_t combine_run(const void *buf, int dtype, const int32_t *assign, const int
     if (vec) {
         const int vpr = (int)((size_t)d * eb / 16);
         const size_t traffic = (size_t)E * C * d * eb + (size_t)T * d * 4;
-        const bool nt = beyond_caches(traffic);
+        const bool nt = back_past_caches(traffic);
         // Two kilobytes of a row to a wavefront where the rows come from the last cache: there a second wavefront on the same row costs more
         // than it brings (4361 tokens of 552 from 4 of 64 experts 7.2 us, 9.1 with one; 10007 of 1000 in fp32 from 6 of 96 56 and 59; 7988 of
         // 832 from 6 of 32 15.8 and 17.4).  Below some 24 MiB in all, or ten wavefronts to a compute unit, the chip is not full with half as
