@@ -69,9 +69,10 @@ __global__ __launch_bounds__(256) void k_dispatch_tokens(const u32x4 *__restrict
 // 65536 tokens of 2048 to 8 of 128 experts: 683 to 441 us, 5.5 TB/s with x counted once (492 in a layer, behind the projection); 16384 to 8 of 64: 163 to 110 us.  The
 // same in other orders: shuffled 632 us (2.8 ms without the samples), descending 640 (13.9), shuffled by eight 680 (785 with a
 // list after the other instead of 64 together).
+// LAST: the rows of x are read past the cache as well, which leaves it to what the projection has brought there.
 constexpr int kBlockTokens = 32, kTokenRows = 16, kListMaxE = 2048, kListSamples = 8;
 
-template <bool NT, int THREADS>
+template <bool NT, bool LAST, int THREADS>
 __global__ __launch_bounds__(THREADS) void k_dispatch_tokens_blocked(const u32x4 *__restrict__ x,
                                                                  const int32_t *__restrict__ offsets,
                                                                  const int32_t *__restrict__ disp_token, int T, int E,
@@ -186,7 +187,7 @@ __global__ __launch_bounds__(THREADS) void k_dispatch_tokens_blocked(const u32x4
         for (int c0 = lane; c0 < vec_per_row; c0 += 256) {
             u32x4 v[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = c0 + 64 * u < vec_per_row ? src[c0 + 64 * u] : u32x4{0u, 0u, 0u, 0u};
+            for (int u = 0; u < 4; ++u) v[u] = c0 + 64 * u < vec_per_row ? get<LAST>(src + c0 + 64 * u) : u32x4{0u, 0u, 0u, 0u};
             for (int i = 0; i < n; ++i) {
                 u32x4 *dst = out + (size_t)(unsigned)__builtin_amdgcn_readlane((int)mine, i) * vec_per_row;
 #pragma unroll
@@ -366,12 +367,18 @@ int32_t dispatch_tokens_run(const void *x, int dtype, const int32_t *offsets, co
     const int tb = wide ? 16 : T >= 32 * 1024 ? 32 : T >= 16 * 1024 ? 16 : T >= 8 * 1024 ? 8 : 4;
     if (vec && T >= 4096 && E <= 128 * tb && E <= kListMaxE && n_rows < (1ll << 32)) {
         const int n_tb = (T + tb - 1) / tb, n_pad = (int)std::min<long long>((n_rows + 255) / 256, 1024);
-#define MS_BLOCKED(NN, TT)                                                                                                  \
-    hipLaunchKernelGGL((k_dispatch_tokens_blocked<NN, TT>), dim3(n_tb + n_pad), dim3(TT), sizeof(int) * 2 * E, s, (const u32x4 *)x, \
+#define MS_BLOCKED(NN, LL, TT)                                                                                              \
+    hipLaunchKernelGGL((k_dispatch_tokens_blocked<NN, LL, TT>), dim3(n_tb + n_pad), dim3(TT), sizeof(int) * 2 * E, s, (const u32x4 *)x, \
                        offsets, disp_token, T, E, C, (int)((size_t)d * eb / 16), tb, n_tb, (u32x4 *)out)
-        if (wide) MS_BLOCKED(true, 1024);
-        else if (nt) MS_BLOCKED(true, 256);
-        else MS_BLOCKED(false, 256);
+        // Rows of x of 100 MiB and more are read past the cache (those that are in it are found there all the same): layers with 64 and 96
+        // MiB of them the same, 112 MiB (28672 tokens of 2048 to 4 of 128) 440 -> 421 us, 128 (65536 of 1024 to 4 of 64) 454 -> 412, 160
+        // (40960 of 2048 to 8 of 64) 770 -> 731, 224 406 -> 403, 256 (65536 of 2048 to 8 of 128) 1234 -> 1207; 32768 with room to spare 606 -> 582.
+        // (The projection's loads past the cache: 1234 -> 1226 there, but with both 1226, and 32768 606 -> 635.)
+        const bool last = x_bytes >= (size_t)100 << 20;
+        if (wide) MS_BLOCKED(true, true, 1024);
+        else if (nt && last) MS_BLOCKED(true, true, 256);
+        else if (nt) MS_BLOCKED(true, false, 256);
+        else MS_BLOCKED(false, false, 256);
 #undef MS_BLOCKED
     } else if (vec) {
         hipLaunchKernelGGL(k_dispatch_tokens, dim3((unsigned)grid), dim3(256), 0, s, (const u32x4 *)x, offsets,

@@ -47,6 +47,7 @@ def test_combine_ends_of_rows(T, d, E, k, C, dtype):
     (22000, 1544, 16, 2, 2800, "bf16"),  # x, buffers and results 324 MiB
     (24001, 1544, 16, 2, 3050, "bf16"),  # ... 353 MiB, buffers 144
     (9001, 2056, 16, 3, 1700, "fp32"),   # ... 354 MiB, buffers 213
+    (13001, 2056, 16, 3, 1700, "fp32"),  # rows of 102 MiB, read past them as well
 ])
 def test_rows_out_either_side_of_the_caches(T, d, E, k, C, dtype):
     import paper_2508_12801_amd as ms
