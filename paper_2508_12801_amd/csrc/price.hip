@@ -798,6 +798,106 @@ __global__ __launch_bounds__(kUThreads) void k_price_small(PriceArgs a, int n_pa
     if (tid < kPLists) ar->n_arcs[tid][0] = 0;
 }
 
+// What the last pass does with a row; G lanes of a group each, s_p in LDS.
+template <int G, int EPL, bool OS>
+struct EndRow {
+    using RK = RowKeys<G, EPL>;
+    const int E, k, ib, lg, bias;
+    const unsigned cmask, keyo;                                        // keyo: an unfilled slot: reward 0, price 0
+    const int *s_p;
+    int pb[EPL];
+    bool bad = false;                                                  // something did not fit the packed keys
+
+    __device__ __forceinline__ EndRow(const PriceArgs &a, const int *prices, int lane)
+        : E(a.E), k(a.k), ib(a.ib), lg(lane), bias(1 << (31 - a.ib)), cmask((1u << a.ib) - 1), keyo(OS ? (unsigned)(1 << (31 - a.ib)) << a.ib : 0u), s_p(prices)
+    {
+#pragma unroll
+        for (int m = 0; m < EPL; ++m) pb[m] = RK::col(m, lg) < E ? bias - s_p[RK::col(m, lg)] : 0;
+    }
+    __device__ __forceinline__ void make_keys(int row, const int (&v)[EPL], unsigned (&key)[EPL])
+    {
+        const unsigned rot = row_mask(row, ib);
+#pragma unroll
+        for (int m = 0; m < EPL; ++m) {
+            const int c = RK::col(m, lg);
+            const unsigned x = (unsigned)(v[m] + pb[m]);
+            const bool wide = v[m] > (1 << 30) || v[m] < -(1 << 30) || x == 0u || (x >> (32 - ib)) != 0;
+            if (c < E) bad |= wide;
+            key[m] = c < E ? (x << ib) | ((unsigned)c ^ rot) : 0u;
+        }
+    }
+    // The row's k best experts: assigned, counted, their rewards added to `sum`.  True if it has exchanges under the bound B; its holds are the keys
+    // from `thr` on, `mine` that of slot lg, and `nxt` the best key below them.
+    __device__ __forceinline__ bool choose(int32_t *assign, int row, bool live, const unsigned (&key)[EPL], int B, int *s_cnt, long long &sum, unsigned &thr,
+                                           unsigned &mine, unsigned &nxt)
+    {
+        unsigned cur = RK::first(key), kth = cur, over = 0, under = 0;
+        mine = 0;
+        bool have_under = false;
+        for (int r = 0; r < k; ++r) {
+            if (r) cur = RK::below(key, cur);
+            if (lg == r) mine = cur;
+            if (OS) {
+                if (cur > keyo) over = cur;
+                else if (!have_under) {
+                    under = cur;
+                    have_under = true;
+                }
+            }
+        }
+        kth = cur;
+        nxt = RK::below(key, cur);
+        thr = kth;
+        if (!live) return false;
+        if (OS && !have_under) under = nxt;
+        const bool real = lg < k && (!OS || mine > keyo);
+        if (lg < k) {
+            const int c = (int)((mine & cmask) ^ row_mask(row, ib));
+            assign[(size_t)row * k + lg] = real ? c : -1;
+            if (real) {
+                if (c < E) atomicAdd(&s_cnt[c], 1);
+                else bad = true;
+                sum += (long long)(int)(mine >> ib) - bias + s_p[c < E ? c : 0];
+            }
+        }
+        if (OS) {
+            thr = kth > keyo ? kth : keyo + 1;
+            const unsigned alt = under > keyo ? under : keyo;
+            nxt = kth > keyo ? nxt : under;
+            return (over != 0 && (int)((over - alt) >> ib) <= B) || (have_under && (int)((keyo - under) >> ib) <= B);
+        }
+        return k < E && (int)((kth >> ib) - (nxt >> ib)) < B;
+    }
+    // The row's exchanges under the bound, store(place, cost, from, to, row); places are counted in *s_narcs.  `cur` is the row's best key, next(r, x) the
+    // one of slot r behind x, `nxt` the best below thr.
+    template <class Next, class Store>
+    __device__ __forceinline__ void list(int row, const unsigned (&key)[EPL], int B, unsigned thr, unsigned nxt, unsigned cur, const Next &next, int *s_narcs,
+                                         const Store &store)
+    {
+        const int vo = (int)(keyo >> ib), vb = (int)(nxt >> ib);       // vb: the best expert the token does not hold (0: there is none)
+        const unsigned rot = row_mask(row, ib);
+        auto from_slot = [&](int va, int from) {           // to this lane's columns
+            unsigned in = 0;
+#pragma unroll
+            for (int m = 0; m < EPL; ++m) in |= (RK::col(m, lg) < E && key[m] < thr && va - (int)(key[m] >> ib) < B ? 1u : 0u) << m;
+            if (!in) return;
+            int at = atomicAdd(s_narcs, __popc(in));
+#pragma unroll
+            for (int m = 0; m < EPL; ++m)
+                if ((in >> m) & 1u) store(at++, va - (int)(key[m] >> ib), from, RK::col(m, lg), row);
+        };
+        int held = 0;
+        for (int r = 0; r < k && cur >= thr; ++r) {
+            const int va = (int)(cur >> ib), from = (int)((cur & cmask) ^ rot);
+            ++held;
+            if (va - vb < B) from_slot(va, from);
+            if (OS && lg == 0 && va - vo < B) store(atomicAdd(s_narcs, 1), va - vo, from, E, row);
+            if (r + 1 < k) cur = next(r + 1, cur);
+        }
+        if (OS && held < k) from_slot(vo, E);
+    }
+};
+
 // The last pass: assignment, pairs per block and expert, sum of the rewards, and the arcs under the bound.  A row near a change is
 // evaluated a second time for its arcs, which a block gathers in LDS: 18 us for 65536 tokens of 128 experts, 8.6 for 16384 of 64 (30 and
 // 16 while the rows were evaluated three times, to count the arcs and to write them in the order of the rows).
@@ -814,15 +914,12 @@ __global__ __launch_bounds__(kPThreads) void k_price_assign(PriceArgs a, int if_
     __shared__ int s_nq, s_narcs, s_base, s_bad;
     __shared__ long long s_sum[kPThreads / 64];
     PriceArea *ar = a.ar;
-    const int tid = threadIdx.x, lane = tid & 63, lg = tid & (G - 1), gbase = lane & ~(G - 1), grp = tid / G;
-    const int E = a.E, k = a.k, ib = a.ib, w = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, lg = tid & (G - 1), grp = tid / G;
+    const int E = a.E, w = blockIdx.x;
     const bool vec = (E & 3) == 0 && (((size_t)a.q) & 15) == 0;
     const int row0 = w * a.rows;
     int nr = a.T - row0;
     nr = nr < a.rows ? nr : a.rows;
-    auto group_bits = [&](unsigned long long b) {
-        return G == 64 ? b : (b >> gbase) & ((1ull << (G & 63)) - 1);
-    };
     int nx[EPL];
     RK::load(a.q + (size_t)(row0 + (grp < nr ? grp : nr - 1)) * E, E, vec, lg, nx);
     for (int j = tid; j < kPStride; j += kPThreads) s_cnt[j] = 0;
@@ -835,77 +932,23 @@ __global__ __launch_bounds__(kPThreads) void k_price_assign(PriceArgs a, int if_
         if (!mt.done) return;
     }
     __syncthreads();
-    const int bias = 1 << (31 - ib);
-    const unsigned cmask = (1u << ib) - 1;
-    int pb[EPL];
-#pragma unroll
-    for (int m = 0; m < EPL; ++m) pb[m] = RK::col(m, lg) < E ? bias - s_p[RK::col(m, lg)] : 0;
-    const unsigned keyo = OS ? (unsigned)bias << ib : 0u;              // an unfilled slot: reward 0, price 0
-    bool bad = false;
-    auto make_keys = [&](int row, const int(&v)[EPL], unsigned(&key)[EPL]) {
-        const unsigned rot = row_mask(row, ib);
-#pragma unroll
-        for (int m = 0; m < EPL; ++m) {
-            const int c = RK::col(m, lg);
-            const unsigned x = (unsigned)(v[m] + pb[m]);
-            const bool wide = v[m] > (1 << 30) || v[m] < -(1 << 30) || x == 0u || (x >> (32 - ib)) != 0;
-            if (c < E) bad |= wide;
-            key[m] = c < E ? (x << ib) | ((unsigned)c ^ rot) : 0u;
-        }
-    };
+    EndRow<G, EPL, OS> er(a, s_p, lg);
     long long sum = 0;
     for (int l0 = grp; l0 - grp < nr; l0 += NG) {
         const bool live = l0 < nr;
-        const int lr = live ? l0 : nr - 1, row = row0 + lr;
+        const int lr = live ? l0 : nr - 1;
         int v[EPL];
 #pragma unroll
         for (int m = 0; m < EPL; ++m) v[m] = nx[m];
         if (l0 - grp + NG < nr) RK::load(a.q + (size_t)(row0 + (l0 + NG < nr ? l0 + NG : nr - 1)) * E, E, vec, lg, nx);
-        unsigned key[EPL];
-        make_keys(row, v, key);
-        unsigned cur = RK::first(key), mine = 0, kth = cur, over = 0, under = 0;
-        bool have_under = false;
-        for (int r = 0; r < k; ++r) {
-            if (r) cur = RK::below(key, cur);
-            if (lg == r) mine = cur;
-            if (OS) {
-                if (cur > keyo) over = cur;
-                else if (!have_under) {
-                    under = cur;
-                    have_under = true;
-                }
-            }
-        }
-        kth = cur;
-        const unsigned nxt = RK::below(key, cur);
-        if (live) {
-            if (OS && !have_under) under = nxt;
-            const bool real = lg < k && (!OS || mine > keyo);
-            if (lg < k) {
-                const int c = (int)((mine & cmask) ^ row_mask(row, ib));
-                a.assign[(size_t)row * k + lg] = real ? c : -1;
-                if (real) {
-                    if (c < E) atomicAdd(&s_cnt[c], 1);
-                    else bad = true;
-                    sum += (long long)(int)(mine >> ib) - bias + s_p[c < E ? c : 0];
-                }
-            }
-            bool queue;
-            unsigned thr = kth;
-            if (OS) {
-                thr = kth > keyo ? kth : keyo + 1;
-                const unsigned alt = under > keyo ? under : keyo;
-                queue = (over != 0 && (int)((over - alt) >> ib) <= B) || (have_under && (int)((keyo - under) >> ib) <= B);
-            } else {
-                queue = k < E && (int)((kth >> ib) - (nxt >> ib)) < B;
-            }
-            if (queue && lg == 0) {
-                s_thr[lr] = thr;
-                s_queue[atomicAdd(&s_nq, 1)] = (short)lr;
-            }
+        unsigned key[EPL], thr, mine, nxt;
+        er.make_keys(row0 + lr, v, key);
+        if (er.choose(a.assign, row0 + lr, live, key, B, s_cnt, sum, thr, mine, nxt) && lg == 0) {
+            s_thr[lr] = thr;
+            s_queue[atomicAdd(&s_nq, 1)] = (short)lr;
         }
     }
-    if (bad) s_bad = 1;
+    if (er.bad) s_bad = 1;
     for (int off = 32; off > 0; off >>= 1) {
         const unsigned lo = __shfl_xor((unsigned)sum, off), hi = __shfl_xor((unsigned)((unsigned long long)sum >> 32), off);
         sum += (long long)(((unsigned long long)hi << 32) | lo);
@@ -938,35 +981,15 @@ __global__ __launch_bounds__(kPThreads) void k_price_assign(PriceArgs a, int if_
             }
         }
     };
-    const int nq = s_nq, vo = (int)(keyo >> ib);
+    const int nq = s_nq;
     for (int i = grp; i < nq; i += NG) {
-        const int lr = s_queue[i], row = row0 + lr;
+        const int lr = s_queue[i];
         int v[EPL];
         unsigned key[EPL];
-        RK::load(a.q + (size_t)row * E, E, vec, lg, v);
-        make_keys(row, v, key);
-        const unsigned thr = s_thr[lr], rot = row_mask(row, ib);
-        const int vb = (int)(RK::below(key, thr) >> ib);   // the best expert the token does not hold (0: there is none)
-        auto from_slot = [&](int va, int from) {           // to this lane's columns
-            unsigned in = 0;
-#pragma unroll
-            for (int m = 0; m < EPL; ++m) in |= (RK::col(m, lg) < E && key[m] < thr && va - (int)(key[m] >> ib) < B ? 1u : 0u) << m;
-            if (!in) return;
-            int at = atomicAdd(&s_narcs, __popc(in));
-#pragma unroll
-            for (int m = 0; m < EPL; ++m)
-                if ((in >> m) & 1u) store(at++, va - (int)(key[m] >> ib), from, RK::col(m, lg), row);
-        };
-        int held = 0;
-        unsigned cur = RK::first(key);
-        for (int r = 0; r < k && cur >= thr; ++r) {
-            const int va = (int)(cur >> ib), from = (int)((cur & cmask) ^ rot);
-            ++held;
-            if (va - vb < B) from_slot(va, from);
-            if (OS && lg == 0 && va - vo < B) store(atomicAdd(&s_narcs, 1), va - vo, from, E, row);
-            cur = RK::below(key, cur);
-        }
-        if (OS && held < k) from_slot(vo, E);
+        RK::load(a.q + (size_t)(row0 + lr) * E, E, vec, lg, v);
+        er.make_keys(row0 + lr, v, key);
+        const unsigned thr = s_thr[lr];
+        er.list(row0 + lr, key, B, thr, RK::below(key, thr), RK::first(key), [&](int, unsigned x) { return RK::below(key, x); }, &s_narcs, store);
     }
     __syncthreads();
     const int n = s_narcs < kBlockArcs ? s_narcs : kBlockArcs;
@@ -1014,6 +1037,15 @@ static_assert(kMaxBound < (int)kWMax, "every arc under the bound can be followed
 static_assert(kMaxTBits <= 21, "a token + 1 and a node fit the words of the shortest paths, none of which is kPredNone");
 static_assert(kPriceMaxE < 1024 && kPStride <= 1024, "ten bits for a node, and for an arc of a search's paths");
 
+// The last pass of a small batch (k_price_finish): lanes to a row, rows of a block of the counts, and counts at most.
+constexpr int kEndLanes = 8, kEndBlock = kPThreads / kEndLanes;
+// The search makes the last pass itself where that costs its one compute unit less than the launch it saves, up to eight rewards to a lane.  A layer
+// around it, with a launch for the pass and without: 64 tokens of 8 experts 75.0 -> 70.4 us, of 64 to 8 102 -> 96.5, of 128 126 -> 112, 128 of 16 to 8
+// 79.8 -> 73, of 64 to 4 97 -> 92, 500 of 8 to 2 89 -> 83.5, of 16 97.7 -> 94.9; but 400 of 24 to 4 92 -> 95, 128 of 128 to 8 129 -> 130, 256 of 64 to 8
+// 113 -> 115, 512 of 64 133 -> 144.
+constexpr int kEndEntries = 8 * kFThreads;
+constexpr int kEndCounts = kEndEntries / kEndBlock + kEndLanes * 16;
+
 // A move in the log: token, what it cost (nothing, if it gained), from, to.  Arcs of Z (no token) have Z at one end.
 constexpr int kLogCostBits = 23;
 __device__ __forceinline__ unsigned long long log_word(int u, int cost, int from, int to)
@@ -1039,7 +1071,10 @@ __device__ __forceinline__ int moved_slot(int u) { return (u ^ (u >> 10)) & (kMo
 // of moved tokens are listed anew, from their rows, in every search.  Rows read in every search against moves at the end, means of eight
 // batches each: 65536 tokens of 128 experts 77 -> 61 us, 16384 of 256 155 -> 97, 10007 of 96 77 -> 47, 16384 of 64 52 -> 37, 4096 of 16 23
 // -> 18, 64 of 8 18 -> 15.  (The prices the passes end at are others since; a single batch may go the other way.)
-template <int TEPL, bool OS>
+//
+// SEPL > 0: a small batch, whose last pass this workgroup makes itself, eight lanes to a row and SEPL columns to a lane (kEndEntries).  Its arcs never
+// leave LDS, and each row lists them from the keys that it has at hand: a queue of rows evaluated anew, as in k_price_assign, took 2 to 4 us more.
+template <int TEPL, bool OS, int SEPL>
 __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t *prices, int64_t *price_scale, int if_done)
 {
     constexpr int NT = kFThreads, NW = NT / 64;
@@ -1051,71 +1086,136 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
     const int E = a.E, k = a.k, N = E + 1, mode = a.mode;
     const bool slack = !OS && mode == kModeSlack;
     const PriceMeta mt = ar->meta;
-    const int B = mt.bound, fail = ar->fail;
-    const int n_list = lane < a.lists ? ar->n_arcs[lane][0] : 0;            // of list `lane`
-    const bool many = a.lists > 1;
-    const int per_list = many ? FIRST * NT / kPLists : FIRST * NT, list_room = many ? kPArcBuf / kPLists : kPArcBuf;
-    static_assert(FIRST * NT / kPLists % 64 == 0, "a wavefront looks at one list at a time");
-    const int *pg = ar->prices;
-    unsigned long long arc0[FIRST];
-    int tok0[FIRST];
-#pragma unroll
-    for (int j = 0; j < FIRST; ++j) {
-        const int f = tid + j * NT, x = many ? __builtin_amdgcn_readfirstlane(f / (FIRST * NT / kPLists)) : 0, at = x * list_room + (f - x * per_list);
-        arc0[j] = ar->arc[at];
-        tok0[j] = ar->arc_tok[at];
-    }
-    if (if_done && !mt.done) return;
-    const int n_upto = wave_sum(n_list), n_listed = __builtin_amdgcn_readlane(n_upto, 63);
-    bool ok = fail == 0 && !__any((unsigned)n_list > (unsigned)list_room);
+    const int B = mt.bound, A0 = slack ? 2 * E : 0;
     int rounds = 0, augs = 0;
-    bool close = false;                          // not solved, but near enough for another try
-    const int A0 = slack ? 2 * E : 0;
-    if (A0 + n_listed > kPArcs) ok = false;
-    if (tid == 0) {
-        s.bad = s.bad_move = s.n_near[0] = 0;
-        s.dsum = 0;
-        s.n_arcs = A0 + n_listed;
-    }
+    bool ok = true, close = false;               // close: not solved, but near enough for another try
+    int fail = 0;
     long long sum = 0;
-    for (int w2 = tid; w2 < a.n_wg; w2 += NT) sum += a.wg_sum[w2];
+    int *s_cnt = (int *)s.near;                  // SEPL: pairs per (block of rows, expert)
+    if constexpr (SEPL > 0) {
+        using RK = RowKeys<kEndLanes, SEPL>;
+        constexpr int NG = NT / kEndLanes;
+        static_assert(sizeof(int) * kEndCounts <= sizeof s.near, "the search lists arcs there later");
+        const int lg = tid & (kEndLanes - 1), grp = tid / kEndLanes;
+        const bool vec = (E & 3) == 0 && (((size_t)a.q) & 15) == 0;
+        int nx[SEPL];
+        RK::load(a.q + (size_t)(grp < a.T ? grp : a.T - 1) * E, E, vec, lg, nx);
+        for (int i = tid; i < a.n_wg * E; i += NT) s_cnt[i] = 0;
+        if (tid < N) {
+            s.p[tid] = tid < E ? ar->prices[tid] : 0;
+            s.pi[tid] = 0;
+        }
+        if (tid == 0) {
+            s.bad = s.bad_move = s.n_near[0] = 0;
+            s.dsum = 0;
+            s.n_arcs = A0;
+        }
+        __syncthreads();
+        EndRow<kEndLanes, SEPL, OS> er(a, s.p, lg);
+        for (int l0 = grp; l0 - grp < a.T; l0 += NG) {
+            const bool live = l0 < a.T;
+            const int row = live ? l0 : a.T - 1;
+            int v[SEPL];
+#pragma unroll
+            for (int m = 0; m < SEPL; ++m) v[m] = nx[m];
+            if (l0 - grp + NG < a.T) RK::load(a.q + (size_t)(l0 + NG < a.T ? l0 + NG : a.T - 1) * E, E, vec, lg, nx);
+            unsigned key[SEPL], thr, mine, nxt;
+            er.make_keys(row, v, key);
+            if (!er.choose(a.assign, row, live, key, B, s_cnt + row / kEndBlock * E, sum, thr, mine, nxt)) continue;
+            er.list(row, key, B, thr, nxt, __shfl(mine, 0, kEndLanes), [&](int r, unsigned) { return __shfl(mine, r, kEndLanes); }, &s.n_arcs,
+                    [&](int at, int cost, int from, int to, int u) {
+                        if ((unsigned)at >= (unsigned)kPArcs) return;
+                        s.ft[at] = (unsigned)((from << 16) | to);
+                        s.cost[at] = (unsigned)cost;
+                        s.tok[at] = u;
+                    });
+        }
+        for (int i = tid; i < A0; i += NT) {
+            s.ft[i] = i < E ? (i << 16) | E : (E << 16) | (i - E);
+            s.cost[i] = 0;
+            s.tok[i] = -1;
+        }
+        if (er.bad) s.bad = 1;
+        __syncthreads();
+        fail = s.bad;
+        for (int i = tid; i < a.n_wg * E; i += NT) a.blkcnt[i] = s_cnt[i];
+        __syncthreads();
+        if (tid == 0) s.bad = 0;
+        ok = fail == 0 && s.n_arcs <= kPArcs;
+    }
     int tot;
     {
         int e0 = 0;
-        if (tid < N) {
-            const int v = tid;
-            int n = 0;
-            if (v < E)
-                for (int r = 0; r < 8; ++r) n += ar->loads[r][v];
-            const int p = v < E ? pg[v] : 0, sl = (slack && v < E && p == 0 && n < a.C) ? a.C - n : 0;
-            s.p[v] = p;
-            s.pi[v] = 0;
+        auto balance = [&](int v, int n, int p) {        // of the expert that n tokens have taken
+            const int sl = (slack && v < E && p == 0 && n < a.C) ? a.C - n : 0;
             s.sl[v] = sl;
             e0 = v < E ? n + sl - a.C : 0;
             s.ex[v] = e0;
-        }
-        if (ok) {
-            for (int i = tid; i < A0; i += NT) {
-                s.ft[i] = i < E ? (i << 16) | E : (E << 16) | (i - E);
-                s.cost[i] = 0;
-                s.tok[i] = -1;
+        };
+        if constexpr (SEPL > 0) {
+            if (tid < N) {
+                int n = 0;
+                for (int w2 = 0; w2 < a.n_wg && tid < E; ++w2) n += s_cnt[w2 * E + tid];
+                balance(tid, n, s.p[tid]);
             }
-            auto keep = [&](int i, unsigned long long r, int t) {
-                s.ft[A0 + i] = (unsigned)r;
-                s.cost[A0 + i] = (unsigned)(r >> 32);
-                s.tok[A0 + i] = t;
-            };
+        } else {
+            fail = ar->fail;
+            const int n_list = lane < a.lists ? ar->n_arcs[lane][0] : 0;            // of list `lane`
+            const bool many = a.lists > 1;
+            const int per_list = many ? FIRST * NT / kPLists : FIRST * NT, list_room = many ? kPArcBuf / kPLists : kPArcBuf;
+            static_assert(FIRST * NT / kPLists % 64 == 0, "a wavefront looks at one list at a time");
+            const int *pg = ar->prices;
+            unsigned long long arc0[FIRST];
+            int tok0[FIRST];
 #pragma unroll
             for (int j = 0; j < FIRST; ++j) {
-                const int f = tid + j * NT, x = many ? __builtin_amdgcn_readfirstlane(f / (FIRST * NT / kPLists)) : 0, i = f - x * per_list;
-                const int n = __builtin_amdgcn_readlane(n_list, x);
-                if (i < n) keep(__builtin_amdgcn_readlane(n_upto, x) - n + i, arc0[j], tok0[j]);
+                const int f = tid + j * NT, x = many ? __builtin_amdgcn_readfirstlane(f / (FIRST * NT / kPLists)) : 0, at = x * list_room + (f - x * per_list);
+                arc0[j] = ar->arc[at];
+                tok0[j] = ar->arc_tok[at];
             }
-            if (__any(n_list > per_list))
-                for (int x = 0; x < a.lists; ++x) {
-                    const int n = __builtin_amdgcn_readlane(n_list, x), first = __builtin_amdgcn_readlane(n_upto, x) - n;
-                    for (int i = per_list + tid; i < n; i += NT) keep(first + i, ar->arc[x * list_room + i], ar->arc_tok[x * list_room + i]);
+            if (if_done && !mt.done) return;
+            const int n_upto = wave_sum(n_list), n_listed = __builtin_amdgcn_readlane(n_upto, 63);
+            ok = fail == 0 && !__any((unsigned)n_list > (unsigned)list_room);
+            if (A0 + n_listed > kPArcs) ok = false;
+            if (tid == 0) {
+                s.bad = s.bad_move = s.n_near[0] = 0;
+                s.dsum = 0;
+                s.n_arcs = A0 + n_listed;
+            }
+            for (int w2 = tid; w2 < a.n_wg; w2 += NT) sum += a.wg_sum[w2];
+            if (tid < N) {
+                const int v = tid;
+                int n = 0;
+                if (v < E)
+                    for (int r = 0; r < 8; ++r) n += ar->loads[r][v];
+                const int p = v < E ? pg[v] : 0;
+                s.p[v] = p;
+                s.pi[v] = 0;
+                balance(v, n, p);
+            }
+            if (ok) {
+                for (int i = tid; i < A0; i += NT) {
+                    s.ft[i] = i < E ? (i << 16) | E : (E << 16) | (i - E);
+                    s.cost[i] = 0;
+                    s.tok[i] = -1;
                 }
+                auto keep = [&](int i, unsigned long long r, int t) {
+                    s.ft[A0 + i] = (unsigned)r;
+                    s.cost[A0 + i] = (unsigned)(r >> 32);
+                    s.tok[A0 + i] = t;
+                };
+#pragma unroll
+                for (int j = 0; j < FIRST; ++j) {
+                    const int f = tid + j * NT, x = many ? __builtin_amdgcn_readfirstlane(f / (FIRST * NT / kPLists)) : 0, i = f - x * per_list;
+                    const int n = __builtin_amdgcn_readlane(n_list, x);
+                    if (i < n) keep(__builtin_amdgcn_readlane(n_upto, x) - n + i, arc0[j], tok0[j]);
+                }
+                if (__any(n_list > per_list))
+                    for (int x = 0; x < a.lists; ++x) {
+                        const int n = __builtin_amdgcn_readlane(n_list, x), first = __builtin_amdgcn_readlane(n_upto, x) - n;
+                        for (int i = per_list + tid; i < n; i += NT) keep(first + i, ar->arc[x * list_room + i], ar->arc_tok[x * list_room + i]);
+                    }
+            }
         }
         const int t0 = wave_total(e0), q0 = wave_total(e0 > 0 ? e0 : 0);
         if (lane == 0) {
@@ -1776,6 +1876,7 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     const bool small = (long long)T * G <= kSmallThreads && (long long)T * E <= kSmallEntries && shm + sizeof(StepLds) <= 64 * 1024;
     const int plim = (1 << (31 - a.ib)) - 1;
     geom->one_launch = small ? 1 : 0;
+    const bool with_pass = small && G == kEndLanes && a.rows == kEndBlock && T * E <= kEndEntries;
     if (part == kPriceBegin && !small) return MAXSCORE_OK;
 #define MS_PG(GG, XX)                                                                                                     \
     do {                                                                                                                  \
@@ -1831,17 +1932,23 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
         if (os) hipLaunchKernelGGL((k_price_assign<GG, PP, true>), dim3(a.n_wg), dim3(kPThreads), 0, s, a, if_done);      \
         else hipLaunchKernelGGL((k_price_assign<GG, PP, false>), dim3(a.n_wg), dim3(kPThreads), 0, s, a, if_done);        \
     } while (0)
-        MS_SHAPED(MS_P);
+        if (!with_pass) MS_SHAPED(MS_P);
 #undef MS_P
-#define MS_F(PP)                                                                                                          \
+#define MS_F(PP, SS)                                                                                                      \
     do {                                                                                                                  \
-        if (os) hipLaunchKernelGGL((k_price_finish<PP, true>), dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, if_done);  \
-        else hipLaunchKernelGGL((k_price_finish<PP, false>), dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, if_done);    \
+        if (os) hipLaunchKernelGGL((k_price_finish<PP, true, SS>), dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, if_done);  \
+        else hipLaunchKernelGGL((k_price_finish<PP, false, SS>), dim3(1), dim3(kFThreads), 0, s, a, prices, price_scale, if_done);    \
     } while (0)
-        if (E <= 64) MS_F(1);
-        else if (E <= 128) MS_F(2);
-        else if (E <= 256) MS_F(4);
-        else MS_F(8);
+        if (with_pass) {
+            if (EPL == 1) MS_F(1, 1);
+            else if (EPL == 2) MS_F(1, 2);
+            else if (EPL == 4) MS_F(1, 4);
+            else if (EPL == 8) MS_F(1, 8);
+            else MS_F(2, 16);
+        } else if (E <= 64) MS_F(1, 0);
+        else if (E <= 128) MS_F(2, 0);
+        else if (E <= 256) MS_F(4, 0);
+        else MS_F(8, 0);
 #undef MS_F
     };
     if (small) {
