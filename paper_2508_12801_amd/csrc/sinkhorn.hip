@@ -16,6 +16,7 @@
 //   large    one wavefront per row, lane l holds experts l, l+64, ...; rows and columns are launches of their own
 // 20 iterations, before and after the first two ways: 4096 tokens of 16 experts 228 and 70 us (4097, the first the medium way
 // takes, 116), 16384 of 64 350 and 178 us.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -236,7 +237,11 @@ __device__ __forceinline__ float sk_reciprocal(float x)
     return fmaf(fmaf(-x, y, 1.f), y, y);
 }
 
-// threads: as many as there are rows, up to the register budget of 64 scores each
+// Threads: as many as there are rows, up to a wavefront a SIMD; then as many as have their 64 / EP rows each, which wavefronts that share a SIMD
+// would take in turn anyway, and a sum over the lanes for each.  Scores, choice and gates with a thread to a row, up to the 1024 there can be, and
+// so: 700 tokens of 16 experts 45.5 -> 38.0 us, 1000 55.3 -> 39.4, 2048 58.4 -> 46.6, 3000 65.3 -> 57.6, 2048 of 8 55.5 -> 39.8, 300 of 32 45.5 ->
+// 40.8; with up to 512 threads before that 300 of 16 39.0 (36.0 so), up to 128 37.1.
+constexpr int kSkFewThreads = 256;
 template <int EP>
 constexpr int kSkSmallThreads = EP <= 16 ? 1024 : 512;
 
@@ -757,7 +762,7 @@ int32_t sinkhorn_run(const float *scores, int T, int E, int C, float tau, int n_
     const int epl = (E + 63) / 64;
     const int ep = E <= 8 ? 8 : E <= 16 ? 16 : E <= 32 ? 32 : 64;
     if (E <= 64 && T <= (ep <= 16 ? 1024 : 512) * (64 / ep)) {
-        const int most = ep <= 16 ? 1024 : 512, nt = T >= most ? most : (T + 63) / 64 * 64;
+        const int rows = 64 / ep, nt = (std::max((T + rows - 1) / rows, std::min(T, kSkFewThreads)) + 63) / 64 * 64;
         int *words, *caps;
         const int32_t rc = caps_words(caps_host, &words, &caps);
         if (rc) return rc;

@@ -11,7 +11,7 @@ torch = pytest.importorskip("torch")
 
 
 @pytest.mark.parametrize("tau", [0.0125, 0.1])
-@pytest.mark.parametrize("T,E", [(8192, 8), (4096, 16), (4095, 16), (2048, 32), (64, 8)])
+@pytest.mark.parametrize("T,E", [(8192, 8), (4096, 16), (4095, 16), (2048, 32), (64, 8), (257, 16), (1025, 16), (2049, 8), (300, 32)])
 def test_rows_of_tiny_sums(T, E, tau):
     import paper_2508_12801_amd as ms
     print(f"sinkhorn tiny sums T={T} E={E} tau={tau}", flush=True)
