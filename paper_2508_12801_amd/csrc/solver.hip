@@ -1863,6 +1863,7 @@ int32_t solver_words(int **host, int **dev)
     SolverHost *hs = nullptr;
     const int32_t rc = solver_host(&hs);
     if (rc) return rc;
+    hs->begun.q = nullptr;            // (their caller may use the workspace as well)
     *host = hs->flag;
     *dev = hs->flag_dev;
     return MAXSCORE_OK;
@@ -2133,6 +2134,7 @@ int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore
     {
         int32_t rc = solver_host(&hs);
         if (rc) return rc;
+        hs->begun.q = nullptr;
     }
     hs->tev_used = 0;                     // (the marks of price tries have been read)
     // room = total capacity (sum of the vector, or E*Ce)

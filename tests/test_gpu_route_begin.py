@@ -1,5 +1,5 @@
 """GPU: price passes begun ahead of the call that solves the batch.  They are used by that call alone: with other rewards, behind another
-solve, or where the batch does not solve its passes in one launch, the call solves the batch as if nothing had been begun."""
+solve or rerouting, or where the batch does not solve its passes in one launch, the call solves the batch as if nothing had been begun."""
 import ctypes
 
 import numpy as np
@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
-@pytest.mark.parametrize("between", ["nothing", "other rewards", "another solve", "other sizes"])
+@pytest.mark.parametrize("between", ["nothing", "other rewards", "another solve", "rerouting", "other sizes"])
 @pytest.mark.parametrize("T,E,k,C,one_launch", [(64, 8, 2, 16, True), (512, 128, 8, 40, True), (512, 64, 8, 48, True), (513, 64, 8, 80, False),
                                                 (300, 16, 9, 200, False)])
 def test_begun_passes(T, E, k, C, one_launch, between):
@@ -29,6 +29,9 @@ def test_begun_passes(T, E, k, C, one_launch, between):
     opts.flags |= b.FLAG_PASSES_BEGUN
     if between == "another solve":
         assert torch.equal(ms.assign_i32(other, k, C)["assign"], want_other["assign"])
+    if between == "rerouting":
+        first, again = (ms.assign_iter_i32(other, k, C, allow_not_converged=True) for _ in range(2))
+        assert torch.equal(first["assign"], again["assign"]) and first["total"] == again["total"]
     use, C_use = (other, C) if between == "other rewards" else (q, C + 1) if between == "other sizes" else (q, C)
     if between == "other rewards":
         want = want_other
