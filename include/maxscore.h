@@ -361,7 +361,7 @@ int32_t maxscore_route_rewards(const float *scores, const int32_t *q, int32_t T,
                                maxscore_stats *stats, void *workspace, size_t workspace_bytes, void *stream);
 
 /* Optional, ahead of maxscore_route_rewards: enqueues what that call would begin with and what writes none of its outputs, so that a caller
- * can allocate these meanwhile (the price passes of a small batch; of others nothing).  *begun: whether it has; then the thread's next
+ * can allocate these meanwhile (the price passes of a small batch, the first two of others).  *begun: whether it has; then the thread's next
  * solve is to be that call, with the same q, sizes, prices_in, workspace and stream and MAXSCORE_FLAG_PASSES_BEGUN in its flags, and nothing else
  * may use the workspace before it.  (With other arguments, or behind another solve, the flag has no effect.)  Only enqueues. */
 int32_t maxscore_route_begin(const int32_t *q, int32_t T, int32_t E, int32_t k, int32_t C, const maxscore_opts *opts,

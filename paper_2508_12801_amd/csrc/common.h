@@ -134,7 +134,7 @@ struct PriceGeometry {
     int one_launch;          // all price passes were one launch
 };
 bool price_supported(int T, int E, int k);
-// All of a try; the passes alone, if they are one launch (nothing otherwise); what follows them then.
+// All of a try; the passes alone that need no look at others, all of a small batch; what follows these.
 enum PricePart { kPriceAll, kPriceBegin, kPriceRest };
 // tables, and two words per block; the iterative assignment keeps its own there, with a word per (slot, 64 tokens)
 inline size_t price_area_bytes(int T, int k, int max_wg)
@@ -156,6 +156,9 @@ inline bool iter_tiles_are_words(const WorkspaceLayout &L, int T, int E, int k)
 // expert), and the same as the device sees them.
 constexpr int kSolverWords = 16;
 int32_t solver_words(int **host, int **dev);
+// Those of the thread's price solves, and the number of the solve (kPriceSeqBits bits, not zero): of a new one, or of the last.
+constexpr int kPriceSeqBits = 14;
+int32_t price_words(int **host, int **dev, int *seq, bool next);
 // With kernel timing on, records the next of the calling thread's timing events: before and after the first kernel of a round
 // (auction) or pass (price solve) and after its second, three in all.
 int32_t solver_mark(hipStream_t s);

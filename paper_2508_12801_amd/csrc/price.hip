@@ -101,12 +101,17 @@ constexpr int kSmallPasses = kPriceTryPasses;
 // would cost every batch two empty launches).  16384 rows over 64 experts, top-8, half of them alike up to 0.1: 179 us in ten passes, a tenth
 // alike up to 3e-2 222 us, with a quarter less room and a quarter of them alike 190 us; in six passes the auction took over, 1.2 to 6.8 ms.
 constexpr int kFar = 4, kFarPasses = 4;
+constexpr int kPriceAhead = 2;                    // passes that are enqueued before the first is looked at
 constexpr int kSampledPasses = 2, kTightPasses = 6, kSlackPasses = 18, kRetryPasses = 4;
+static_assert(kPriceAhead <= kRetryPasses && kPriceAhead <= kTightPasses - 2, "passes that every solve has, before any is looked at");
 static_assert(kSampledPasses + kSlackPasses <= kPriceTryPasses && kSampledPasses + kTightPasses + kFarPasses <= kPriceTryPasses, "the round cap of a call allows every pass");
 constexpr int kPRowsMax = 128;                    // rows of a block of the final pass at most
-constexpr int kPriceWordDone = 0, kPriceWordPasses = 1;      // pinned words of the calling thread
-// Bits of the passes' word: a pass found more than kFar tokens per expert to move; the last one found so few that the next one may end the passes.
-constexpr int kPriceFarBit = 16, kPriceSoonBit = 17, kPricePassMask = (1 << kPriceFarBit) - 1;
+// Pinned words of the calling thread.  Both carry the number of the solve, as passes that were begun and given up may still tell of theirs.
+constexpr int kPriceWordDone = 0, kPriceWordPasses = 1;
+// Bits of the passes' word: a pass found more than kFar tokens per expert to move; the last one found so few that the next one may end the passes;
+// from kPriceSeqBit on the number of the solve.
+constexpr int kPriceFarBit = 16, kPriceSoonBit = 17, kPriceSeqBit = 18, kPricePassMask = (1 << kPriceFarBit) - 1;
+static_assert(kPriceSeqBit + kPriceSeqBits == 32, "the number of a solve fits above them");
 enum { kModeTight = 0, kModeSlack = 1, kModeOver = 2 };
 // So many sixths of a token per expert too many end the passes at pass t (not counting samples).
 __device__ __forceinline__ int enough_sixths(int t, int retry) { return retry ? kRetryEnough : t < kUsualPasses ? kEnough : kLateEnough; }
@@ -158,6 +163,7 @@ struct PriceArgs {
     int lists;                                    // of arcs: one or kPLists
     int sampled;                                  // passes over a sample before the others
     int *host;                                    // pinned words
+    int seq;                                      // number of the solve, not zero
     int look;                                     // the pass that tells whether more than the usual ones are needed, or -1
 };
 
@@ -595,10 +601,10 @@ __global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, 
 // for the word to get there before it ends.
 __device__ __forceinline__ void price_tell(const PriceArgs &a, const PriceMeta &mt, int t)
 {
-    if (mt.done) tell_host(a.host + kPriceWordDone, 1);
+    if (mt.done) tell_host(a.host + kPriceWordDone, a.seq);
     else if (t > 0) {
         const bool soon = t > a.sampled && 6 * mt.excess <= kSoon * a.E * enough_sixths(t - a.sampled, a.retry);
-        tell_host(a.host + kPriceWordPasses, t | (mt.far << kPriceFarBit) | ((soon ? 1 : 0) << kPriceSoonBit));
+        tell_host(a.host + kPriceWordPasses, (int)((unsigned)t | (unsigned)mt.far << kPriceFarBit | (soon ? 1u : 0u) << kPriceSoonBit | (unsigned)a.seq << kPriceSeqBit));
     }
 }
 
@@ -1819,13 +1825,16 @@ bool price_supported(int T, int E, int k)
 int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_t *prices_in, int retry, PricePart part, int32_t *assign, int64_t *prices,
                       int64_t *price_scale, char *ws, PriceGeometry *geom, hipStream_t s)
 {
-    int *words = nullptr, *words_dev = nullptr;
-    const int32_t wrc = solver_words(&words, &words_dev);
+    int *words = nullptr, *words_dev = nullptr, seq = 0;
+    const int32_t wrc = price_words(&words, &words_dev, &seq, part != kPriceRest);
     if (wrc) return wrc;
     volatile int *hw = words;
-    hw[kPriceWordDone] = hw[kPriceWordPasses] = 0;
+    if (part != kPriceRest) hw[kPriceWordDone] = hw[kPriceWordPasses] = 0;
+    auto done = [&] { return hw[kPriceWordDone] == seq; };
+    auto progress = [&] { const unsigned w = (unsigned)hw[kPriceWordPasses]; return (int)(w >> kPriceSeqBit) == seq ? w : 0u; };
     WorkspaceLayout L = workspace_layout(T, E, k);
     PriceArgs a;
+    a.seq = seq;
     a.q = q;
     a.host = words_dev;
     a.assign = assign;
@@ -1877,7 +1886,6 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     const int plim = (1 << (31 - a.ib)) - 1;
     geom->one_launch = small ? 1 : 0;
     const bool with_pass = small && G == kEndLanes && a.rows == kEndBlock && T * E <= kEndEntries;
-    if (part == kPriceBegin && !small) return MAXSCORE_OK;
 #define MS_PG(GG, XX)                                                                                                     \
     do {                                                                                                                  \
         if (EPL == 1) XX(GG, 1);                                                                                          \
@@ -1969,33 +1977,34 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
         MS_HIP(hipGetLastError());
         return mrc;
     }
-    hipLaunchKernelGGL(k_price_init, dim3(64), dim3(kPThreads), 0, s, a.ar, a.quads, E, plim, prices_in, a.retry);
+    if (part != kPriceRest) hipLaunchKernelGGL(k_price_init, dim3(64), dim3(kPThreads), 0, s, a.ar, a.quads, E, plim, prices_in, a.retry);
     // until the passes before pass t have ended; the stream is looked at now and then: one that has drained or failed ends the wait
     auto wait_for = [&](int t) {
-        for (unsigned spin = 1; !hw[kPriceWordDone] && (hw[kPriceWordPasses] & kPricePassMask) < t; ++spin) {
+        for (unsigned spin = 1; !done() && (int)(progress() & kPricePassMask) < t; ++spin) {
             if ((spin & 4095) == 0 && hipStreamQuery(s) != hipErrorNotReady) break;
             __builtin_ia32_pause();
         }
     };
     // Pass t is enqueued when pass t - 1 has begun, so that one stays queued behind the one that runs: a pass that is still queued when the
     // prices are done costs two empty launches (5 us).  So where the pass that runs is likely to be the last, the end is enqueued behind it
-    // instead, which looks at the prices first; if these are not done, that costs as much.
+    // instead, which looks at the prices first; if these are not done, that costs as much.  (kPriceBegin: those that nothing is waited for.)
     bool ended = false;
-    for (int t = 0; !ended; ++t) {
-        if (t >= 2 && (t < n_pass || t == a.look + 2)) {
+    for (int t = part == kPriceRest ? kPriceAhead : 0; !ended; ++t) {
+        if (part == kPriceBegin && t >= kPriceAhead) break;
+        if (t >= kPriceAhead && (t < n_pass || t == a.look + 2)) {
             wait_for(t - 1);
-            if (t == a.look + 2 && hw[kPriceWordPasses] >> kPriceFarBit & 1) n_pass += kFarPasses;
-            if (hw[kPriceWordDone]) break;
-            if (t < n_pass && hw[kPriceWordPasses] >> kPriceSoonBit & 1) {
+            if (t == a.look + 2 && progress() >> kPriceFarBit & 1) n_pass += kFarPasses;
+            if (done()) break;
+            if (t < n_pass && progress() >> kPriceSoonBit & 1) {
                 enqueue_end(t);
                 wait_for(t);
-                ended = hw[kPriceWordDone] != 0;
+                ended = done();
             }
         }
         if (t >= n_pass) break;
         if (!ended) enqueue_pass(t);
     }
-    if (!ended) enqueue_end(0);
+    if (!ended && part != kPriceBegin) enqueue_end(0);
 #undef MS_SHAPED
 #undef MS_PG
     MS_HIP(hipGetLastError());

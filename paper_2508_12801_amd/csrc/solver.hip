@@ -1827,11 +1827,12 @@ struct SolverHost {
         int T = 0, E = 0, k = 0, C = 0;
     } begun;
     unsigned done_seq = 0;            // waits in stream_done so far
+    unsigned price_seq = 0;           // price solves so far
     int device = -1;
 };
 
-constexpr int kDoneWord = kSolverWords + kMaxE + 16, kPinnedWords = kDoneWord + 2 * (kDoneWords + 1);      // stream_done's words, of eight bytes each
-static_assert(kDoneWord % 16 == 0, "in lines to themselves");
+constexpr int kDoneWord = kSolverWords + kMaxE + 16, kPriceWord = kDoneWord + 2 * (kDoneWords + 1), kPinnedWords = kPriceWord + 16;      // stream_done's words, of eight bytes each; the price solve's
+static_assert(kDoneWord % 16 == 0 && kPriceWord % 16 == 0, "in lines to themselves");
 
 static int32_t solver_host(SolverHost **out)
 {
@@ -1847,6 +1848,7 @@ static int32_t solver_host(SolverHost **out)
     if (!h) return MAXSCORE_ERR_HIP;
     if (h->device < 0) {
         MS_HIP(hipHostMalloc((void **)&h->flag, sizeof(int) * kPinnedWords, hipHostMallocMapped));
+        std::fill_n(h->flag, kPinnedWords, 0);
         MS_HIP(hipHostGetDevicePointer((void **)&h->flag_dev, h->flag, 0));
         MS_HIP(hipHostMalloc((void **)&h->state, sizeof(SolverState), hipHostMallocMapped));
         MS_HIP(hipHostGetDevicePointer((void **)&h->state_dev, h->state, 0));
@@ -1866,6 +1868,18 @@ int32_t solver_words(int **host, int **dev)
     hs->begun.q = nullptr;            // (their caller may use the workspace as well)
     *host = hs->flag;
     *dev = hs->flag_dev;
+    return MAXSCORE_OK;
+}
+
+int32_t price_words(int **host, int **dev, int *seq, bool next)
+{
+    SolverHost *hs = nullptr;
+    const int32_t rc = solver_host(&hs);
+    if (rc) return rc;
+    *host = hs->flag + kPriceWord;
+    *dev = hs->flag_dev + kPriceWord;
+    if (next) ++hs->price_seq;
+    *seq = 1 + (int)(hs->price_seq % ((1u << kPriceSeqBits) - 1));
     return MAXSCORE_OK;
 }
 
@@ -1972,7 +1986,7 @@ static bool price_takes(int T, int E, int k, int C, const maxscore_opts &o)
            !(o.flags & (MAXSCORE_FLAG_NO_TAIL_PASS | MAXSCORE_FLAG_NO_FINISHER));
 }
 
-// The price passes of a small batch, ahead of the call that solves it.
+// The first price passes, of a small batch all of them, ahead of the call that solves it.
 extern "C" int32_t maxscore_route_begin(const int32_t *q, int32_t T, int32_t E, int32_t k, int32_t C, const maxscore_opts *opts, int32_t *begun,
                                         void *workspace, size_t workspace_bytes, void *stream)
 {
@@ -1991,7 +2005,7 @@ extern "C" int32_t maxscore_route_begin(const int32_t *q, int32_t T, int32_t E, 
     PriceGeometry pg;
     hs->begun.q = nullptr;
     rc = price_enqueue(q, T, E, k, Ce, o.prices_in, 0, kPriceBegin, nullptr, nullptr, nullptr, (char *)workspace, &pg, s);
-    if (rc || !pg.one_launch) return rc;
+    if (rc) return rc;
     hs->begun.q = q;
     hs->begun.prices_in = o.prices_in;
     hs->begun.ws = (char *)workspace;
@@ -2013,7 +2027,7 @@ int32_t price_run(const int32_t *q, int T, int E, int k, int C, const maxscore_o
     int32_t rc = solver_host(&hs);
     if (rc) return rc;
     const auto &b = hs->begun;
-    const bool begun = (o.flags & MAXSCORE_FLAG_PASSES_BEGUN) && b.q && b.q == q && b.prices_in == o.prices_in && b.ws == ws && b.s == s && b.T == T &&
+    const bool begun = (o.flags & MAXSCORE_FLAG_PASSES_BEGUN) && !g_kernel_timing && b.q && b.q == q && b.prices_in == o.prices_in && b.ws == ws && b.s == s && b.T == T &&
                        b.E == E && b.k == k && b.C == C;
     hs->begun.q = nullptr;
     if (!price_takes(T, E, k, C, o)) return MAXSCORE_OK;
