@@ -765,7 +765,7 @@ __device__ __forceinline__ PriceMeta first_meta(const PriceArea *ar, const int64
     return PriceMeta{retry ? ar->meta.w : kFirstWindow, 0, 2, retry ? ar->meta.passes : prices_in ? -1 : 0, 0x7fffffff, 0, 0, 0};
 }
 
-// All passes of a small batch in one workgroup: a pass takes 4 to 11 us (64 tokens of 8 experts: three to five in 9 us; 256 of 64: 28)
+// All passes of a small batch in one workgroup: a pass takes 4 to 11 us (64 tokens of 8 experts: two to four in 7 us; 256 of 64: 22)
 // instead of two launches and their distance, none is launched in vain, and a batch that settles slowly may take more.
 template <int G, int EPL, int MODE>
 __global__ __launch_bounds__(kUThreads) void k_price_small(PriceArgs a, int n_pass, int plim, const int64_t *__restrict__ prices_in)
