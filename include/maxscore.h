@@ -118,7 +118,8 @@ typedef struct {
     float select_ms;       /* summed device time of the second kernel of the same rounds: the price steps (0 where
                               the passes are one launch), the select passes with the tail pass that runs inside
                               some of them (0 unless timing is on) */
-    float gates_dispatch_ms; /* maxscore_route_* only: device time of a5 + a6 between two events on `stream` */
+    float gates_dispatch_ms; /* maxscore_route_* only: device time of a5 + a6, from the end of a4 by the kernels' own clock behind a
+                              price solve and behind rerouting (up to 16 slots and 512 experts), else between two events on `stream` */
     int32_t finish_passes; /* price solve: 1 (its search); auction: passes of the cycle-cancelling finisher (0: it ran to
                               eps = 1 itself) */
     int32_t finish_cycles; /* price solve: augmenting paths taken; auction: negative cycles cancelled */

@@ -190,7 +190,7 @@ int32_t maxscore_assign_iter_i32(const int32_t *q, int32_t T, int32_t E, int32_t
     int32_t rc = check_ws(workspace, workspace_bytes, T, E, k);
     if (rc) return rc;
     if (max_rounds < 0) max_rounds = 1000;
-    rc = iter_run(q, T, E, k, C, max_rounds, assign, total, flow, rounds, (char *)workspace, (hipStream_t)stream, nullptr, nullptr);
+    rc = iter_run(q, T, E, k, C, max_rounds, assign, total, flow, rounds, nullptr, (char *)workspace, (hipStream_t)stream, nullptr, nullptr);
     MS_HIP(hipStreamSynchronize((hipStream_t)stream));
     return rc;
 }
@@ -354,20 +354,17 @@ static int32_t route_from_rewards(const float *scores, const int32_t *q, int T, 
         // the rounds leave the number of pairs per 64 tokens and expert: gates and dispatch are enqueued behind the last one
         struct AfterCtx {
             const float *scores; const int32_t *assign; int T, E, k; float *gates; int32_t *offsets, *disp_token;
-            float *disp_gate; int32_t *token_pos; char *ws; hipEvent_t ev_a, ev_b; bool called;
-        } ctx = {scores, assign, T, E, k, gates, expert_offsets, disp_token, disp_gate, token_pos, ws, ev_a, ev_b, false};
-        const IterAfter after = [](void *c, hipStream_t st) -> int32_t {
+            float *disp_gate; int32_t *token_pos; char *ws; bool called;
+        } ctx = {scores, assign, T, E, k, gates, expert_offsets, disp_token, disp_gate, token_pos, ws, false};
+        const IterAfter after = [](void *c, long long *clock, hipStream_t st) -> int32_t {
             AfterCtx *a = (AfterCtx *)c;
             a->called = true;
-            MS_HIP(hipEventRecord(a->ev_a, st));
-            const SolverGeometry g = {64, (a->T + 63) / 64, 0, 1, nullptr};
-            const int32_t rc = dispatch_from_keys(g, a->scores, a->assign, a->T, a->E, a->k, a->gates, a->offsets, a->disp_token, a->disp_gate,
-                                                  a->token_pos, a->ws, st);
-            if (rc) return rc;
-            MS_HIP(hipEventRecord(a->ev_b, st));
-            return MAXSCORE_OK;
+            const SolverGeometry g = {64, (a->T + 63) / 64, 0, 1, clock};
+            return dispatch_from_keys(g, a->scores, a->assign, a->T, a->E, a->k, a->gates, a->offsets, a->disp_token, a->disp_gate,
+                                      a->token_pos, a->ws, st);
         };
-        src = iter_run(q, T, E, k, C, o.max_rounds, assign, &total, &flow, &rounds, ws, s, k <= 16 && E <= kPriceMaxE ? after : nullptr, &ctx);
+        float after_ms = 0.f;
+        src = iter_run(q, T, E, k, C, o.max_rounds, assign, &total, &flow, &rounds, &after_ms, ws, s, k <= 16 && E <= kPriceMaxE ? after : nullptr, &ctx);
         if (stats) {
             stats->total_score_q = total;
             stats->flow_value = flow;
@@ -375,8 +372,7 @@ static int32_t route_from_rewards(const float *scores, const int32_t *q, int T, 
             stats->status = src;
         }
         if (ctx.called && (src == MAXSCORE_OK || src == MAXSCORE_ERR_NOT_CONVERGED)) {
-            float t = 0.f;               // (the rounds have waited for the stream)
-            if (stats && hipEventElapsedTime(&t, ev_a, ev_b) == hipSuccess) stats->gates_dispatch_ms = t;
+            if (stats) stats->gates_dispatch_ms = after_ms;
             return src;
         }
     } else {

@@ -47,6 +47,7 @@ struct IterArea {
     int any[4];                // whether there were proposals in round r, in word r & 3
     int rej[4];                // ... those there was no room for
     int room[4];               // ... whether an expert has room left
+    long long t_end, t_after;  // device clock (10 ns) behind the last round, and at the end of the caller's work behind that
 };
 
 struct IterArgs {
@@ -393,6 +394,7 @@ __device__ __forceinline__ void iter_report(const IterArgs &a, long long sum, in
         tell_host(host + kIterWordRounds, rounds);
         tell_host(host + kIterWordOpen, open);
         tell_host(host, 1);              // (read when the stream has been waited for: a fence here took 3 us)
+        a.ar->t_end = wall_clock64();
     }
 }
 
@@ -794,7 +796,7 @@ int32_t assign_total_run(const int32_t *q, const int32_t *assign, int T, int E, 
 }
 
 int32_t iter_run(const int32_t *q, int T, int E, int k, int C, int max_rounds, int32_t *assign, int64_t *total,
-                 int32_t *flow, int32_t *rounds, char *ws, hipStream_t s, IterAfter after, void *after_ctx)
+                 int32_t *flow, int32_t *rounds, float *after_ms, char *ws, hipStream_t s, IterAfter after, void *after_ctx)
 {
     WorkspaceLayout L = workspace_layout(T, E, k);
     IterArgs a;
@@ -879,10 +881,12 @@ int32_t iter_run(const int32_t *q, int T, int E, int k, int C, int max_rounds, i
         }
     }
     // what follows is enqueued while the last round runs
-    const int32_t arc = after ? after(after_ctx, s) : MAXSCORE_OK;
-    rc = stream_done(s);
+    const int32_t arc = after ? after(after_ctx, &a.ar->t_after, s) : MAXSCORE_OK;
+    long long clock[2];
+    rc = stream_done(s, &a.ar->t_end, clock, sizeof(clock) / 4);
     if (rc) return rc;
     if (arc) return arc;
+    if (after_ms) *after_ms = after ? (float)(clock[1] - clock[0]) * 1e-5f : 0.f;
     if (!hw[0]) return MAXSCORE_ERR_HIP;
     if (total) *total = *(volatile long long *)(host + kIterWordTotal);
     if (flow) *flow = hw[kIterWordFlow];

@@ -48,7 +48,7 @@ int32_t dispatch_core(const int32_t *, const float *, size_t, int, int, int32_t 
 {
     return MAXSCORE_OK;
 }
-int32_t iter_run(const int32_t *, int, int, int, int, int, int32_t *, int64_t *, int32_t *, int32_t *, char *,
+int32_t iter_run(const int32_t *, int, int, int, int, int, int32_t *, int64_t *, int32_t *, int32_t *, float *, char *,
                  hipStream_t, IterAfter, void *)
 {
     return MAXSCORE_OK;
