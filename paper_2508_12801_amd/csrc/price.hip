@@ -44,6 +44,7 @@
 
 #include "common.h"
 #include "host_words.h"
+#include "price_loop.h"
 #include "row_keys.h"
 
 namespace maxscore {
@@ -101,12 +102,12 @@ constexpr int kSmallPasses = kPriceTryPasses;
 // would cost every batch two empty launches).  16384 rows over 64 experts, top-8, half of them alike up to 0.1: 179 us in ten passes, a tenth
 // alike up to 3e-2 222 us, with a quarter less room and a quarter of them alike 190 us; in six passes the auction took over, 1.2 to 6.8 ms.
 constexpr int kFar = 4, kFarPasses = 4;
-constexpr int kPriceAhead = 2;                    // passes that are enqueued before the first is looked at
 constexpr int kSampledPasses = 2, kTightPasses = 6, kSlackPasses = 18, kRetryPasses = 4;
 static_assert(kPriceAhead <= kRetryPasses && kPriceAhead <= kTightPasses - 2, "passes that every solve has, before any is looked at");
 static_assert(kSampledPasses + kSlackPasses <= kPriceTryPasses && kSampledPasses + kTightPasses + kFarPasses <= kPriceTryPasses, "the round cap of a call allows every pass");
 constexpr int kPRowsMax = 128;                    // rows of a block of the final pass at most
-// Pinned words of the calling thread.  Both carry the number of the solve, as passes that were begun and given up may still tell of theirs.
+// Pinned words of the calling thread.  Both carry the number of the solve, as passes that were begun and given up may still tell of theirs (in the
+// same place only if another solve was begun and given up between them; words so lost are looked up in the solve's own state).
 constexpr int kPriceWordDone = 0, kPriceWordPasses = 1;
 // Bits of the passes' word: a pass found more than kFar tokens per expert to move; the last one found so few that the next one may end the passes;
 // from kPriceSeqBit on the number of the solve.
@@ -1830,8 +1831,6 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     if (wrc) return wrc;
     volatile int *hw = words;
     if (part != kPriceRest) hw[kPriceWordDone] = hw[kPriceWordPasses] = 0;
-    auto done = [&] { return hw[kPriceWordDone] == seq; };
-    auto progress = [&] { const unsigned w = (unsigned)hw[kPriceWordPasses]; return (int)(w >> kPriceSeqBit) == seq ? w : 0u; };
     WorkspaceLayout L = workspace_layout(T, E, k);
     PriceArgs a;
     a.seq = seq;
@@ -1881,7 +1880,7 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     auto mark = [&] { mrc = mrc ? mrc : solver_mark(s); };
     const bool os = a.mode == kModeOver;
     const size_t shm = sizeof(int4) * (size_t)a.quads;
-    int n_pass = n_sampled + (retry ? kRetryPasses : a.mode == kModeSlack ? kSlackPasses : kTightPasses);
+    const int n_pass = n_sampled + (retry ? kRetryPasses : a.mode == kModeSlack ? kSlackPasses : kTightPasses);
     const bool small = (long long)T * G <= kSmallThreads && (long long)T * E <= kSmallEntries && shm + sizeof(StepLds) <= 64 * 1024;
     const int plim = (1 << (31 - a.ib)) - 1;
     geom->one_launch = small ? 1 : 0;
@@ -1978,37 +1977,43 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
         return mrc;
     }
     if (part != kPriceRest) hipLaunchKernelGGL(k_price_init, dim3(64), dim3(kPThreads), 0, s, a.ar, a.quads, E, plim, prices_in, a.retry);
-    // until the passes before pass t have ended; the stream is looked at now and then: one that has drained or failed ends the wait
-    auto wait_for = [&](int t) {
-        for (unsigned spin = 1; !done() && (int)(progress() & kPricePassMask) < t; ++spin) {
-            if ((spin & 4095) == 0 && hipStreamQuery(s) != hipErrorNotReady) break;
-            __builtin_ia32_pause();
+    struct Words {
+        volatile int *hw;
+        int seq;
+        const PriceMeta *meta;
+        hipStream_t s;
+        PriceSeen told() const
+        {
+            const unsigned w = (unsigned)hw[kPriceWordPasses];
+            const bool mine = (int)(w >> kPriceSeqBit) == seq;
+            return {hw[kPriceWordDone] == seq, mine ? (int)(w & kPricePassMask) : 0, mine && (w >> kPriceFarBit & 1), mine && (w >> kPriceSoonBit & 1)};
         }
+        int idle() const
+        {
+            const hipError_t e = hipStreamQuery(s);
+            return e == hipErrorNotReady ? 0 : e == hipSuccess ? 1 : MAXSCORE_ERR_HIP;
+        }
+        int state(int t, PriceSeen *seen) const
+        {
+            PriceMeta m;
+            MS_HIP(hipMemcpyAsync(&m, meta, sizeof(m), hipMemcpyDeviceToHost, s));
+            MS_HIP(hipStreamSynchronize(s));
+            *seen = {m.done != 0, t, m.far != 0, false};
+            return MAXSCORE_OK;
+        }
+        void pause() const { __builtin_ia32_pause(); }
     };
-    // Pass t is enqueued when pass t - 1 has begun, so that one stays queued behind the one that runs: a pass that is still queued when the
-    // prices are done costs two empty launches (5 us).  So where the pass that runs is likely to be the last, the end is enqueued behind it
-    // instead, which looks at the prices first; if these are not done, that costs as much.  (kPriceBegin: those that nothing is waited for.)
-    bool ended = false;
-    for (int t = part == kPriceRest ? kPriceAhead : 0; !ended; ++t) {
-        if (part == kPriceBegin && t >= kPriceAhead) break;
-        if (t >= kPriceAhead && (t < n_pass || t == a.look + 2)) {
-            wait_for(t - 1);
-            if (t == a.look + 2 && progress() >> kPriceFarBit & 1) n_pass += kFarPasses;
-            if (done()) break;
-            if (t < n_pass && progress() >> kPriceSoonBit & 1) {
-                enqueue_end(t);
-                wait_for(t);
-                ended = done();
-            }
-        }
-        if (t >= n_pass) break;
-        if (!ended) enqueue_pass(t);
-    }
-    if (!ended && part != kPriceBegin) enqueue_end(0);
+    struct Queue {
+        decltype(enqueue_pass) &pass;
+        decltype(enqueue_end) &end;
+        Words words;
+        int seen(int t, PriceSeen *now) { return price_seen(words, t, now); }
+    } queue = {enqueue_pass, enqueue_end, {hw, seq, &a.ar->meta, s}};
+    const int32_t prc = price_passes(queue, n_pass, a.look, kFarPasses, part == kPriceBegin, part == kPriceRest);
 #undef MS_SHAPED
 #undef MS_PG
     MS_HIP(hipGetLastError());
-    return mrc;
+    return prc ? prc : mrc;
 }
 
 }  // namespace maxscore

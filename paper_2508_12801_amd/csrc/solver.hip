@@ -1831,7 +1831,9 @@ struct SolverHost {
     int device = -1;
 };
 
-constexpr int kDoneWord = kSolverWords + kMaxE + 16, kPriceWord = kDoneWord + 2 * (kDoneWords + 1), kPinnedWords = kPriceWord + 16;      // stream_done's words, of eight bytes each; the price solve's
+// stream_done's words, of eight bytes each; the price solve's, in two places that the solves take in turn: passes that were begun and given up
+// may still tell of theirs while the next solve runs in another stream.
+constexpr int kDoneWord = kSolverWords + kMaxE + 16, kPriceWord = kDoneWord + 2 * (kDoneWords + 1), kPinnedWords = kPriceWord + 2 * 16;
 static_assert(kDoneWord % 16 == 0 && kPriceWord % 16 == 0, "in lines to themselves");
 
 static int32_t solver_host(SolverHost **out)
@@ -1876,9 +1878,10 @@ int32_t price_words(int **host, int **dev, int *seq, bool next)
     SolverHost *hs = nullptr;
     const int32_t rc = solver_host(&hs);
     if (rc) return rc;
-    *host = hs->flag + kPriceWord;
-    *dev = hs->flag_dev + kPriceWord;
     if (next) ++hs->price_seq;
+    const int at = kPriceWord + 16 * (int)(hs->price_seq & 1);
+    *host = hs->flag + at;
+    *dev = hs->flag_dev + at;
     *seq = 1 + (int)(hs->price_seq % ((1u << kPriceSeqBits) - 1));
     return MAXSCORE_OK;
 }

@@ -68,3 +68,30 @@ def test_nothing_is_begun_without_a_price_solve():
         ms.set_kernel_timing(False)
     assert begin(b._opts()) == 1
     torch.cuda.synchronize()
+
+
+def test_given_up_in_another_stream():
+    """Passes that are given up run beside the thread's next solve, in a stream and a workspace of their own, and tell of themselves meanwhile."""
+    import paper_2508_12801_amd as ms
+    from paper_2508_12801_amd import binding as b
+    shapes = [(3000, 64, 8, 375), (5000, 64, 8, 800), (4096, 16, 2, 512), (700, 16, 2, 100)]
+    a, c, keep = torch.cuda.Stream(), torch.cuda.Stream(), []
+    lib = b.load_library()
+    for round_, (T, E, k, C) in enumerate(shapes * 3):
+        print(f"two streams {round_} T={T} E={E} k={k} C={C}", flush=True)
+        gen = torch.Generator(device="cuda").manual_seed(round_)
+        q, other = (ms.softtopk(torch.randn(T, E, generator=gen, device="cuda") + torch.randn(E, generator=gen, device="cuda"), k, 1.0)[1] for _ in range(2))
+        want = ms.assign_i32(other, k, C)
+        torch.cuda.synchronize()
+        for given_up in range(1 + round_ % 3):
+            with torch.cuda.stream(a):
+                ws, need = b._workspace(T, E, k, C, q.device)
+                opts, begun = b._opts(), ctypes.c_int32()
+                assert lib.maxscore_route_begin(b._ptr(q), T, E, k, C, ctypes.byref(opts), ctypes.byref(begun), b._ptr(ws), need, b._stream()) == 0
+                assert begun.value == 1
+                keep += [q, ws]
+        with torch.cuda.stream(c):
+            got = ms.assign_i32(other, k, C)
+        torch.cuda.synchronize()
+        assert got["stats"]["total_score_q"] == want["stats"]["total_score_q"] and got["stats"]["rounds"] == want["stats"]["rounds"]
+        assert torch.equal(got["assign"], want["assign"]) and torch.equal(got["prices"], want["prices"])
