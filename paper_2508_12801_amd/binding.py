@@ -104,6 +104,7 @@ _SIGS = {
                                                   ctypes.c_float, ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p,
                                                   ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]),
     "maxscore_set_kernel_timing": (None, [ctypes.c_int32]),
+    "maxscore_solve_account": (ctypes.c_int32, [ctypes.POINTER(ctypes.c_int32)]),
     "maxscore_copy_bytes": (ctypes.c_int32, [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]),
     "maxscore_status_string": (ctypes.c_char_p, [ctypes.c_int32]),
 }
@@ -222,6 +223,13 @@ def _opts(t=1.0, quant_shift=20, max_rounds=200000, eps_div=12, assignment="exac
 
 def set_kernel_timing(on: bool) -> None:
     load_library().maxscore_set_kernel_timing(1 if on else 0)
+
+
+def solve_account() -> dict:
+    """How the thread's last exact solve on the current device went."""
+    a = (ctypes.c_int32 * 4)()
+    _check(load_library().maxscore_solve_account(a), "solve_account")
+    return dict(zip(("tries", "begun", "ends_ahead", "ends_early"), a))
 
 
 def copy_bytes(src, dst) -> None:

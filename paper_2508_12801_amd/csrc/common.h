@@ -132,6 +132,7 @@ struct PriceGeometry {
     PriceReport *report;     // (device)
     int rows, n_wg;          // blocks of rows over which the pairs are counted (WorkspaceLayout::wcnt_off)
     int one_launch;          // all price passes were one launch
+    int ends_ahead, ends_early;      // ends enqueued before the passes were known to have ended; of these, before they had
 };
 bool price_supported(int T, int E, int k);
 // All of a try; the passes alone that need no look at others, all of a small batch; what follows these.

@@ -1875,6 +1875,7 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     geom->report = &a.ar->report;
     geom->rows = rows;
     geom->n_wg = a.n_wg;
+    geom->ends_ahead = geom->ends_early = 0;
 
     int32_t mrc = MAXSCORE_OK;                    // (timing marks)
     auto mark = [&] { mrc = mrc ? mrc : solver_mark(s); };
@@ -2005,10 +2006,24 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     };
     struct Queue {
         decltype(enqueue_pass) &pass;
-        decltype(enqueue_end) &end;
+        decltype(enqueue_end) &enqueue_end;
         Words words;
-        int seen(int t, PriceSeen *now) { return price_seen(words, t, now); }
-    } queue = {enqueue_pass, enqueue_end, {hw, seq, &a.ar->meta, s}};
+        PriceGeometry *geom;
+        bool ahead = false;
+        void end(int if_done)
+        {
+            enqueue_end(if_done);
+            ahead = if_done > 0;
+            geom->ends_ahead += ahead ? 1 : 0;
+        }
+        int seen(int t, PriceSeen *now)
+        {
+            const int rc = price_seen(words, t, now);
+            geom->ends_early += ahead && !rc && !now->done ? 1 : 0;
+            ahead = false;
+            return rc;
+        }
+    } queue = {enqueue_pass, enqueue_end, {hw, seq, &a.ar->meta, s}, geom};
     const int32_t prc = price_passes(queue, n_pass, a.look, kFarPasses, part == kPriceBegin, part == kPriceRest);
 #undef MS_SHAPED
 #undef MS_PG

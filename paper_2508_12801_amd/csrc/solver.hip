@@ -1828,6 +1828,7 @@ struct SolverHost {
     } begun;
     unsigned done_seq = 0;            // waits in stream_done so far
     unsigned price_seq = 0;           // price solves so far
+    int account[4] = {0, 0, 0, 0};    // maxscore_solve_account
     int device = -1;
 };
 
@@ -2005,7 +2006,7 @@ extern "C" int32_t maxscore_route_begin(const int32_t *q, int32_t T, int32_t E, 
     int32_t rc = solver_host(&hs);
     if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
-    PriceGeometry pg;
+    PriceGeometry pg = {};
     hs->begun.q = nullptr;
     rc = price_enqueue(q, T, E, k, Ce, o.prices_in, 0, kPriceBegin, nullptr, nullptr, nullptr, (char *)workspace, &pg, s);
     if (rc) return rc;
@@ -2033,15 +2034,20 @@ int32_t price_run(const int32_t *q, int T, int E, int k, int C, const maxscore_o
     const bool begun = (o.flags & MAXSCORE_FLAG_PASSES_BEGUN) && !g_kernel_timing && b.q && b.q == q && b.prices_in == o.prices_in && b.ws == ws && b.s == s && b.T == T &&
                        b.E == E && b.k == k && b.C == C;
     hs->begun.q = nullptr;
+    std::fill_n(hs->account, 4, 0);
     if (!price_takes(T, E, k, C, o)) return MAXSCORE_OK;
+    hs->account[1] = begun ? 1 : 0;
     hs->tev_used = 0;
-    PriceGeometry pg;
+    PriceGeometry pg = {};
     PriceReport h = {};
     int passes = o.prices_in ? -1 : 0;            // (the pass that checks given prices is a launch like the others)
     for (int attempt = 0;; ++attempt) {
         const size_t mark = hs->tev_used;
         rc = price_enqueue(q, T, E, k, C, o.prices_in, attempt, begun && attempt == 0 ? kPriceRest : kPriceAll, assign, prices, price_scale, ws,
                            &pg, s);
+        hs->account[0] = attempt + 1;
+        hs->account[2] += pg.ends_ahead;
+        hs->account[3] += pg.ends_early;
         if (rc == MAXSCORE_OK && after) {
             const SolverGeometry g = {pg.rows, pg.n_wg, 0, 1, &pg.report->t_after};
             rc = after(after_ctx, g, s, nullptr);
@@ -2058,6 +2064,7 @@ int32_t price_run(const int32_t *q, int T, int E, int k, int C, const maxscore_o
         if (h.fin == 2) break;
         if (h.fin != 1 || attempt + 1 >= kPriceTries) {
             if (stats) stats->solver_ms += (float)h.ticks * 1e-5f;
+            hs->account[0] = -hs->account[0];
             return MAXSCORE_OK;
         }
     }
@@ -2074,6 +2081,16 @@ int32_t price_run(const int32_t *q, int T, int E, int k, int C, const maxscore_o
         stats->finish_passes = 1;
         stats->finish_cycles = h.paths;
     }
+    return MAXSCORE_OK;
+}
+
+extern "C" int32_t maxscore_solve_account(int32_t account[4])
+{
+    if (!account) return MAXSCORE_ERR_NULL;
+    SolverHost *hs = nullptr;
+    const int32_t rc = solver_host(&hs);
+    if (rc) return rc;
+    std::copy_n(hs->account, 4, account);
     return MAXSCORE_OK;
 }
 
@@ -2152,6 +2169,7 @@ int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore
         int32_t rc = solver_host(&hs);
         if (rc) return rc;
         hs->begun.q = nullptr;
+        if (cap || kvec) std::fill_n(hs->account, 4, 0);
     }
     hs->tev_used = 0;                     // (the marks of price tries have been read)
     // room = total capacity (sum of the vector, or E*Ce)

@@ -8,19 +8,26 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
-@pytest.mark.parametrize("T,E,k,room,part,noise", [(700, 16, 2, 1.0, 0.0, 0.0), (700, 16, 2, 1.2, 0.3, 0.03), (3000, 64, 8, 1.0, 0.1, 0.1), (3000, 64, 8, 1.1, 0.5, 0.1),
-                                                   (3000, 64, 8, 0.8, 0.2, 0.1), (2000, 130, 3, 1.05, 0.1, 0.03), (5000, 24, 9, 1.02, 0.25, 0.03), (1000, 64, 4, 3.0, 0.0, 0.0)])
+BATCHES = [(700, 16, 2, 1.0, 0.0, 0.0), (700, 16, 2, 1.2, 0.3, 0.03), (3000, 64, 8, 1.0, 0.1, 0.1), (3000, 64, 8, 1.1, 0.5, 0.1),
+                                                   (3000, 64, 8, 0.8, 0.2, 0.1), (2000, 130, 3, 1.05, 0.1, 0.03), (5000, 24, 9, 1.02, 0.25, 0.03), (1000, 64, 4, 3.0, 0.0, 0.0)]
+
+
+def _batch(T, E, part, noise, seed):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    L = torch.randn(T, E, generator=gen, device="cuda") + 0.7 * torch.randn(E, generator=gen, device="cuda")
+    n = int(T * part)
+    if n:
+        L[:n] = L[0] + noise * torch.randn(n, E, generator=gen, device="cuda")
+    return L
+
+
+@pytest.mark.parametrize("T,E,k,room,part,noise", BATCHES)
 def test_end_ahead(T, E, k, room, part, noise):
     import paper_2508_12801_amd as ms
     print(f"end ahead T={T} E={E} k={k} room={room} part={part} noise={noise}", flush=True)
     C = min(T, -int(-room * T * k // E))
     for seed in range(4):
-        gen = torch.Generator(device="cuda").manual_seed(seed)
-        L = torch.randn(T, E, generator=gen, device="cuda") + 0.7 * torch.randn(E, generator=gen, device="cuda")
-        n = int(T * part)
-        if n:
-            L[:n] = L[0] + noise * torch.randn(n, E, generator=gen, device="cuda")
-        scores, q = ms.softtopk(L, k, 1.0)
+        scores, q = ms.softtopk(_batch(T, E, part, noise, seed), k, 1.0)
         a, b, r = ms.assign_i32(q, k, C), ms.assign_i32(q, k, C), ms.route_scores(scores, k, C)
         want = ms.assign_i32(q, k, C, finisher=False)["stats"]
         for out in (a, b, r):
@@ -28,3 +35,18 @@ def test_end_ahead(T, E, k, room, part, noise):
             assert (st["total_score_q"], st["flow_value"]) == (want["total_score_q"], min(T * k, E * C)) and st["rounds"] >= 1 and st["solver_ms"] > 0
             assert torch.equal(out["assign"], a["assign"]) and torch.equal(out["prices"], a["prices"])
         assert r["stats"]["gates_dispatch_ms"] > 0
+
+
+def test_ends_that_stand_and_ends_that_come_too_early():
+    """The batches above reach both: an end enqueued ahead that stands, and one that leaves and is enqueued again."""
+    import paper_2508_12801_amd as ms
+    stood = early = 0
+    for T, E, k, room, part, noise in BATCHES:
+        for seed in range(4):
+            ms.assign_i32(ms.softtopk(_batch(T, E, part, noise, seed), k, 1.0)[1], k, min(T, -int(-room * T * k // E)))
+            a = ms.solve_account()
+            print(T, E, k, room, part, a, flush=True)
+            assert 0 <= a["ends_early"] <= a["ends_ahead"] and (part or a["tries"] > 0)
+            stood += a["ends_ahead"] - a["ends_early"]
+            early += a["ends_early"]
+    assert stood and early

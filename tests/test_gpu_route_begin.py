@@ -42,6 +42,7 @@ def test_begun_passes(T, E, k, C, between):
         rc = lib.maxscore_route_rewards(
             b._ptr(scores), b._ptr(use), T, E, k, C_use, ctypes.byref(opts), b._ptr(o["assign"]), b._ptr(o["gates"]), b._ptr(o["expert_offsets"]),
             b._ptr(o["disp_token"]), b._ptr(o["disp_gate"]), b._ptr(o["token_pos"]), b._ptr(o["prices"]), ctypes.byref(stats), b._ptr(ws), need, b._stream())
+        assert ms.solve_account()["begun"] == (run == 0 and between == "nothing")
         assert rc == 0 and stats.total_score_q == want["stats"]["total_score_q"] and stats.rounds == want["stats"]["rounds"]
         assert torch.equal(o["assign"], want["assign"]) and torch.equal(o["prices"], want["prices"])
         held = o["assign"].long()
