@@ -75,8 +75,10 @@ constexpr int kSampleRows = 8192;
 // it.  Without and with two passes over samples before the others, solves of 16384 to 32768 tokens take 0.84 to 0.86, to 65536 0.82 to
 // 0.86, to 131072 0.79 to 0.94, to 185000 1.01, to 262144 1.06, beyond 1.16 to 1.19 of the time (230 batches to 8 to 256 experts).
 constexpr int kSampleFrom = 16;
-// (20 exchanges per expert 1.5 % slower, 16 0.4 %, 10 and 8 0.3 and 0.9 %, 600 solves)
-constexpr int kArcsPerExpert = 12, kArcsWanted = 4500, kArcsMost = 5500;
+// (20 exchanges per expert 1.5 % slower, 16 0.4 %, 10 and 8 0.3 and 0.9 %, 600 solves.)  From the seventh pass on, and in another try, 16: of 540 batches with
+// a twentieth to half of the rows nearly alike 5 take more than 1.25 times as long as with 16 throughout and a sixth or a third of a token per expert, and
+// none goes to the auction that did not then; with 12 in these too it was 25, and four such auctions (3 to 5 times as long).
+constexpr int kArcsPerExpert = 12, kLateArcsPerExpert = 16, kArcsWanted = 4500, kArcsMost = 5500;
 constexpr int kMaxBound = (1 << 21) - 1;
 constexpr int kAllArcs = 4000;                    // problems with this few exchanges in all are searched with all of them
 // The passes end when five sixths of a token per expert are too many in all (in another try a sixth), and the step is taken all the same: what
@@ -86,7 +88,17 @@ constexpr int kAllArcs = 4000;                    // problems with this few exch
 // thirds 0.912, one 0.918, four thirds 0.936, two 0.968.  A search with more tokens to move takes more paths at a time.
 // From the seventh pass on, which only rows that are nearly alike come to, a third of a token per expert: of 256 experts their searches are long
 // (six such batches of 16384 tokens 1.17 of the time of before with five sixths throughout, 0.92 so; 40 others 0.97 and 0.95).
-constexpr int kEnough = 5, kLateEnough = 2, kRetryEnough = 1, kUsualPasses = 6;       // the first three are sixths of a token per expert
+// Beyond 256 experts a third, and with more demand than room a sixth: a search has too many tokens to move there for the exchanges that it holds.  With five
+// sixths 28 of 120 such solves of 512 went into a second try or to the auction, and they took 1.10 times as long as with that earlier rule (worst 12
+// times); so 0.92 with spare room, 0.93 without, and 1.00 with less room than demand (1.10 with a third there).
+constexpr int kEnough = 5, kLateEnough = 2, kRetryEnough = 1, kUsualPasses = 6;       // the first three are sixths of a token per expert ...
+constexpr int kManyEnough = 2, kManyOverEnough = 1, kManyExperts = 256;               // ... and these
+// With spare room most experts may have no price, and what is too many is too many at the others: from 97 experts on, up to the sixth pass, these alone count.  10007 to 65536 tokens of
+// 128, 160 and 256 experts, a tenth to half more room than demand: 97 to 201 us, with all experts counted 175 to 460, as the search of a few that
+// far from their capacity did not stand.  Of 252 solves 0.87 of the time of the earlier rule, none beyond 1.25; with five sixths of a token for every expert 0.90,
+// nine beyond.  (Four thirds, of 144 solves: 0.88; two 0.88, five sixths 0.89.)  Up to 64 experts searches stand, and all counted is
+// better (0.88, 0.90 and 0.92 at 64, 32 and 16; 0.89, 0.93 and 0.94 so), at 96 too (0.90, 0.92).
+constexpr int kPricedFrom = 97, kPricedEnough = 8;
 // A pass that finds no more than kSoon times as many is likely to be the last but one.  (305 solves against four times: 1.005 with three, 1.008 with two
 // and six, 1.034 with one, 1.036 if the end is never enqueued ahead.)
 constexpr int kSoon = 4;
@@ -114,8 +126,6 @@ constexpr int kPriceWordDone = 0, kPriceWordPasses = 1;
 constexpr int kPriceFarBit = 16, kPriceSoonBit = 17, kPriceSeqBit = 18, kPricePassMask = (1 << kPriceFarBit) - 1;
 static_assert(kPriceSeqBit + kPriceSeqBits == 32, "the number of a solve fits above them");
 enum { kModeTight = 0, kModeSlack = 1, kModeOver = 2 };
-// So many sixths of a token per expert too many end the passes at pass t (not counting samples).
-__device__ __forceinline__ int enough_sixths(int t, int retry) { return retry ? kRetryEnough : t < kUsualPasses ? kEnough : kLateEnough; }
 
 struct PriceMeta {
     int w;            // margins below this were binned by the pass
@@ -125,6 +135,7 @@ struct PriceMeta {
     int excess;       // tokens too many in all, as the pass found them (a sample's count is scaled up)
     int far;          // 1: too far from the end when the passes were nearly used up; some more follow
     int together;     // spare capacity: the step that comes next moves the experts that have a price together
+    int counted;      // experts by whose number the tokens too many are judged
     int stalled;      // ... passes so far that found few tokens less than the one before them
 };
 
@@ -160,13 +171,21 @@ struct PriceArgs {
     int copies;                                   // ... their copies, a power of two ...
     int half;                                     // ... with counts of 16 bits (no copy's can reach 2^16), else of 32
     int retry;                                    // the search has failed at the prices or the bound before
-    int arcs_wanted;                              // about so many exchanges are to lie under the bound
+    int arcs_wanted, arcs_late;                   // about so many exchanges are to lie under the bound; from the kUsualPasses-th pass on
     int lists;                                    // of arcs: one or kPLists
     int sampled;                                  // passes over a sample before the others
     int *host;                                    // pinned words
     int seq;                                      // number of the solve, not zero
     int look;                                     // the pass that tells whether more than the usual ones are needed, or -1
 };
+
+// So many sixths of a token per expert too many end the passes at pass t.
+__device__ __forceinline__ int enough_sixths(const PriceArgs &a, int t)
+{
+    if (a.retry) return kRetryEnough;
+    if (a.E > kManyExperts) return a.mode == kModeOver ? kManyOverEnough : kManyEnough;
+    return t - a.sampled >= kUsualPasses ? kLateEnough : a.mode == kModeSlack && a.E >= kPricedFrom ? kPricedEnough : kEnough;
+}
 
 // Margins are binned relative to w0 = window / 2^9: linear up to w0, then two bins per octave (one beyond 256 experts).
 __device__ __forceinline__ int bin_of(int m, int w0, int bshift)
@@ -280,11 +299,13 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
     const int w0 = bin_w0(mt.w), bs = a.bshift;
     const int Ct = sampled ? (int)(((long long)a.C * nrows + a.T / 2) / a.T) : a.C;
     const int *s_hn = s_h + 2 * nb * ES;
+    const bool priced = spare && E >= kPricedFrom && !a.retry && t - a.sampled < kUsualPasses;
     if (wv < nwe) {
         const int ne = tid < E ? s_hn[tid] : 0, over = tid < E && ne > Ct ? ne - Ct : 0;
         const bool in = tid < E && (!spare || s.was[tid] > 0);
         const int sn = wave_sum(in ? ne : 0), sx = wave_sum(over), sd = wave_sum(in && ne < Ct ? Ct - ne : 0);
-        if (lane == 63) *(int4 *)&s.part[wv][0] = make_int4(sn, sx, sd, 0);
+        const int sc = priced ? wave_sum(tid < E && (s.was[tid] > 0 || ne >= Ct) ? 1 : 0) : 0;
+        if (lane == 63) *(int4 *)&s.part[wv][0] = make_int4(sn, sx, sd, sc);
         if (together) {
             const int ss = wave_sum(in ? 1 : 0), sz = wave_sum(in ? 0 : over);
             if (lane == 63) *(int2 *)&s.part[wv][4] = make_int2(ss, sz);
@@ -306,12 +327,13 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
         }
     }
     __syncthreads();
-    int sn = 0, sx = 0, sd = 0, ss = 0, sz = 0;              // ss: experts whose price counts; sz: tokens too many at the others
+    int sn = 0, sx = 0, sd = 0, sc = 0, ss = 0, sz = 0;      // sc: experts that have a price or are full; ss: whose price counts; sz: tokens too many at the others
     for (int x = 0; x < nwe; ++x) {
         const int4 p4 = *(const int4 *)&s.part[x][0];
         sn += p4.x;
         sx += p4.y;
         sd += p4.z;
+        sc += p4.w;
         if (together) {
             const int2 p2 = *(const int2 *)&s.part[x][4];
             ss += p2.x;
@@ -322,7 +344,8 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
     sx = sd > sx ? sd : sx;                                           // tokens too many or too few
     // enough: what is left is cheaper to move by the search
     const int excess = sampled ? (int)((long long)sx * a.T / nrows) : sx;
-    const bool enough = !sampled && 6 * excess <= E * enough_sixths(t - a.sampled, a.retry);
+    const int counted = priced ? sc : E;
+    const bool enough = !sampled && 6 * excess <= counted * enough_sixths(a, t);
     const bool moves = excess > 0 || sampled || a.retry;               // (another try may have to go on all the same)
     // the capacity, or the mean demand (of the experts together no less than the capacity: one of them that has room is at its own mean)
     int target = slack || ss == 0 ? Ct : (2 * sn + ss) / (2 * ss);
@@ -409,7 +432,7 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
     } else if (wv == NW - 1) {
         // the bound of the arc list: about kArcsPerExpert exchanges per expert lie under it.  h holds and n newcomers make
         // h * n / rows of them if they are spread over all rows, and the larger of the two if every row has one of each.
-        const float want = (float)a.arcs_wanted * (float)nrows / (float)a.T;
+        const float want = (float)(t - a.sampled < kUsualPasses ? a.arcs_wanted : a.arcs_late) * (float)nrows / (float)a.T;
         const float ch = (float)wave_sum(lane < nb ? s.cum[lane] : 0), cn = (float)wave_sum(lane < nb ? s.cum[nb + lane] : 0);
         const float cmin = fminf(fminf(ch, cn), (float)nrows), cum = cmin > 0.f ? ch * cn / cmin : 0.f;
         const unsigned long long fb = __ballot(lane < nb && cum >= want), fw = __ballot(lane < nb && cum >= 1.5f * want);
@@ -495,6 +518,7 @@ __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int n
     m2.w = w < 16 ? 16 : (w < (1 << 26) ? w : (1 << 26));
     ++m2.passes;
     m2.excess = excess;
+    m2.counted = counted;
     const bool listed = !a.retry || s.reach;             // another try needs more exchanges than the one before
     // stuck: it no longer shrinks (it ends up alternating by a few); with spare capacity the step of the other kind is to be tried first, unless
     // there are few left (16384 tokens, a tenth of them alike, to 8 of 256: a search of 137 tokens took longer than the passes it saved)
@@ -604,7 +628,7 @@ __device__ __forceinline__ void price_tell(const PriceArgs &a, const PriceMeta &
 {
     if (mt.done) tell_host(a.host + kPriceWordDone, a.seq);
     else if (t > 0) {
-        const bool soon = t > a.sampled && 6 * mt.excess <= kSoon * a.E * enough_sixths(t - a.sampled, a.retry);
+        const bool soon = t > a.sampled && 6 * mt.excess <= kSoon * mt.counted * enough_sixths(a, t);
         tell_host(a.host + kPriceWordPasses, (int)((unsigned)t | (unsigned)mt.far << kPriceFarBit | (soon ? 1u : 0u) << kPriceSoonBit | (unsigned)a.seq << kPriceSeqBit));
     }
 }
@@ -761,9 +785,9 @@ __device__ __forceinline__ int first_price(const int64_t *__restrict__ prices_in
     const long long p = prices_in && e < E ? prices_in[e] >> sb : 0;
     return p < 0 ? 0 : (p > plim ? plim : (int)p);
 }
-__device__ __forceinline__ PriceMeta first_meta(const PriceArea *ar, const int64_t *prices_in, int retry)
+__device__ __forceinline__ PriceMeta first_meta(const PriceArea *ar, const int64_t *prices_in, int retry, int E)
 {
-    return PriceMeta{retry ? ar->meta.w : kFirstWindow, 0, 2, retry ? ar->meta.passes : prices_in ? -1 : 0, 0x7fffffff, 0, 0, 0};
+    return PriceMeta{retry ? ar->meta.w : kFirstWindow, 0, 2, retry ? ar->meta.passes : prices_in ? -1 : 0, 0x7fffffff, 0, 0, E, 0};
 }
 
 // All passes of a small batch in one workgroup: a pass takes 4 to 11 us (64 tokens of 8 experts: two to four in 7 us; 256 of 64: 22)
@@ -778,7 +802,7 @@ __global__ __launch_bounds__(kUThreads) void k_price_small(PriceArgs a, int n_pa
     const int tid = threadIdx.x, lg = tid & (G - 1), grp = tid / G, E = a.E;
     const bool vec = (E & 3) == 0 && (((size_t)a.q) & 15) == 0;
     const int hquads = a.quads;
-    PriceMeta mt = first_meta(ar, prices_in, a.retry);
+    PriceMeta mt = first_meta(ar, prices_in, a.retry, E);
     if (tid == 0 && !a.retry) ar->t_start = wall_clock64();
     for (int e = tid; e < kPStride; e += kUThreads) s.was[e] = e >= E ? 0 : a.retry ? ar->prices[e] : first_price(prices_in, e, E, plim);
     for (int i = tid; i < 8 * kPStride; i += kUThreads) (&ar->loads[0][0])[i] = 0;
@@ -1783,7 +1807,7 @@ __global__ __launch_bounds__(kPThreads) void k_price_init(PriceArea *ar, int qua
     for (int i = i0; i < kPStride && !retry; i += n) ar->prices[i] = first_price(prices_in, i, E, plim);
     if (i0 == 0) {
         ar->fail = 0;
-        ar->meta = first_meta(ar, prices_in, retry);
+        ar->meta = first_meta(ar, prices_in, retry, E);
         if (!retry) ar->t_start = wall_clock64();
     }
 }
@@ -1858,7 +1882,8 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     }
     a.arcs_wanted = std::min(kArcsPerExpert * E, kArcsWanted);
     a.retry = retry > 0 ? 1 : 0;
-    if (retry) a.arcs_wanted = std::min((1 + retry) * a.arcs_wanted, kArcsMost);
+    a.arcs_late = std::min(kLateArcsPerExpert * E, kArcsWanted);
+    if (retry) a.arcs_wanted = a.arcs_late = std::min((1 + retry) * a.arcs_late, kArcsMost);
     a.ib = 1;
     while ((1 << a.ib) < E) ++a.ib;
     a.nb = price_bins(E);
