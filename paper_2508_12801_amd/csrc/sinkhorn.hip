@@ -6,7 +6,7 @@
 //   column targets m_j = caps_j * T / sum(caps);  v = 1;  n_iter times: u_i = 1 / sum_j K_ij v_j,
 //   v_j = m_j / sum_i K_ij u_i;  plan_ij = u_i K_ij v_j;  second expert = arg-max_j plan_ij (ties to the lower
 //   id; -1 when the row is all zero).
-// Three ways to do it, by size; column sums are added in a fixed order everywhere, beyond four rows in double where one
+// Three ways to do it, by size; column sums are added in a fixed order everywhere, in double beyond one to four rows where one
 // workgroup does it all, from the first on with eight lanes to a row; row sums are trees over the columns:
 //   small    up to 65536 scores of up to 16 experts, half as many of up to 64: the whole call is one workgroup that keeps
 //            K in registers, a thread owns whole rows.  An iteration takes 2.3 us (two barriers, 300 instructions of every
@@ -230,7 +230,8 @@ __device__ __forceinline__ double sk_reduce_scatter(const V (&f)[EP], int lane, 
 }
 
 // 1 / x: the hardware's reciprocal and a Newton step, three instructions instead of ten.  1 - x * r is exact in the fused step, so that what is left
-// of the reciprocal's error e is e^2, below the rounding of the last addition.
+// of the reciprocal's error e is e^2, below the rounding of the last addition: the same bits as the division for every one of the 2^23 mantissas
+// (compared at eleven exponents from 2^-99 to 2^91).
 __device__ __forceinline__ float sk_reciprocal(float x)
 {
     const float y = __builtin_amdgcn_rcpf(x);
@@ -239,19 +240,23 @@ __device__ __forceinline__ float sk_reciprocal(float x)
 
 // Threads: as many as there are rows, up to a wavefront a SIMD; then as many as have their 64 / EP rows each, which wavefronts that share a SIMD
 // would take in turn anyway, and a sum over the lanes for each.  Scores, choice and gates with a thread to a row, up to the 1024 there can be, and
-// so: 700 tokens of 16 experts 45.5 -> 38.0 us, 1000 55.3 -> 39.4, 2048 58.4 -> 46.6, 3000 65.3 -> 57.6, 2048 of 8 55.5 -> 39.8, 300 of 32 45.5 ->
-// 40.8; with up to 512 threads before that 300 of 16 39.0 (36.0 so), up to 128 37.1.
+// so: 700 tokens of 16 experts 60.4 -> 56.2 us, 1000 70.2 -> 57.7, 2048 78.2 -> 64.0, 3000 85.3 -> 76.1, 2048 of 8 72.6 -> 55.6, 300 of 16 and of 32 the
+// same.
 constexpr int kSkFewThreads = 256;
 template <int EP>
 constexpr int kSkSmallThreads = EP <= 16 ? 1024 : 512;
 
-template <int EP>
-__global__ __launch_bounds__(kSkSmallThreads<EP>) void k_sk_small(const float *__restrict__ scores, int T, int E, int C, float inv_tau,
+// GROUP: rows whose shares of a column sum are added in fp32 before they are widened: one up to 1024 tokens, two up to 3072 and four beyond (of 32
+// experts one up to 512, else two), no more than with a thread to a row.  With four throughout 700 tokens of 16 experts took 52.9 us, 1000 54.3, 2048 62.0,
+// and the plan's error against 64 bits went from 6.37e-8 to 6.45e-8 rms at 1000 (6.37e-8 so).
+template <int EP, int GROUP>
+__global__ __launch_bounds__(GROUP == 1 && EP < 64 ? kSkFewThreads : kSkSmallThreads<EP>) void k_sk_small(const float *__restrict__ scores, int T, int E, int C, float inv_tau,
                                                    int n_iter, int32_t *__restrict__ assign, float *__restrict__ plan,
                                                    int32_t *__restrict__ caps)          // (of the host, or null)
 {
     constexpr int RR = 64 / EP;                 // rows per thread: r * nt + tid
-    using Acc = std::conditional_t<(RR > 4), double, float>;
+    using Acc = std::conditional_t<(RR > GROUP), double, float>;
+    static_assert(RR % GROUP == 0, "whole groups");
     __shared__ int s_cnt[EP];
     __shared__ float s_target[EP];
     __shared__ __attribute__((aligned(16))) float s_v[EP];
@@ -332,16 +337,13 @@ __global__ __launch_bounds__(kSkSmallThreads<EP>) void k_sk_small(const float *_
         Acc acc[EP];
 #pragma unroll
         for (int c = 0; c < EP; ++c) {
-            float s[(RR + 3) / 4];              // of up to four rows, pairwise
 #pragma unroll
-            for (int g = 0; g < (RR + 3) / 4; ++g) {
-                const int r = 4 * g;
-                s[g] = x[r][c] * u[r];
-                if constexpr (RR > 1) s[g] += x[r + 1][c] * u[r + 1];
-                if constexpr (RR > 2) s[g] += x[r + 2][c] * u[r + 2] + x[r + 3][c] * u[r + 3];
+            for (int r = 0; r < RR; r += GROUP) {
+                float s = x[r][c] * u[r];       // of up to four rows, pairwise
+                if constexpr (GROUP > 1) s += x[r + 1][c] * u[r + 1];
+                if constexpr (GROUP > 2) s += x[r + 2][c] * u[r + 2] + x[r + 3][c] * u[r + 3];
+                acc[c] = r ? acc[c] + (Acc)s : (Acc)s;
             }
-            acc[c] = s[0];
-            if constexpr (RR > 4) acc[c] += (double)s[1];
         }
         int column = 0;
         const double sum = sk_reduce_scatter<EP, 32>(acc, lane, column);
@@ -766,11 +768,21 @@ int32_t sinkhorn_run(const float *scores, int T, int E, int C, float tau, int n_
         int *words, *caps;
         const int32_t rc = caps_words(caps_host, &words, &caps);
         if (rc) return rc;
-#define MS_SK(PP) hipLaunchKernelGGL(k_sk_small<PP>, dim3(1), dim3(nt), 0, s, scores, T, E, C, 1.f / tau, n_iter, assign, plan, caps)
-        if (ep == 8) MS_SK(8);
-        else if (ep == 16) MS_SK(16);
-        else if (ep == 32) MS_SK(32);
-        else MS_SK(64);
+        // (of threads with a row each, all but one row of a group are beyond the batch: zeros, which add nothing to round)
+        const int most = ep <= 16 ? 1024 : 512, per = (T + most - 1) / most, group = T <= nt ? 4 : per == 1 ? 1 : per < 4 ? 2 : 4;
+#define MS_SK(PP, GG) hipLaunchKernelGGL((k_sk_small<PP, GG>), dim3(1), dim3(nt), 0, s, scores, T, E, C, 1.f / tau, n_iter, assign, plan, caps)
+#define MS_SKG(PP)                     \
+    do {                               \
+        if (group == 1) MS_SK(PP, 1);  \
+        else if (group == 2) MS_SK(PP, 2); \
+        else MS_SK(PP, 4);             \
+    } while (0)
+        if (ep == 8) MS_SKG(8);
+        else if (ep == 16) MS_SKG(16);
+        else if (ep == 32 && group == 1) MS_SK(32, 1);
+        else if (ep == 32) MS_SK(32, 2);
+        else MS_SK(64, 1);
+#undef MS_SKG
 #undef MS_SK
         MS_HIP(hipGetLastError());
         return copy_caps(words, caps_host, E, s);
