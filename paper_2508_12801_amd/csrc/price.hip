@@ -148,11 +148,10 @@ struct PriceArea {
     int pad[7];
     long long t_start;
     PriceReport report;
-    long long pad2;
     // margins and holds, PriceArgs::copies times: (2 * nb + 1) rows of ES columns, filled by a pass (workgroup b adds to copy b
     // modulo their number), added up and cleared by the update behind it.  With one copy for all the additions took 25 us
     // (of 512 workgroups then): its lines travel from chiplet to chiplet with every addition.
-    int hist[kPCopies][kPTableInts];
+    alignas(16) int hist[kPCopies][kPTableInts];
     unsigned long long arc[kPArcBuf];             // cost << 32 | from << 16 | to, in PriceArgs::lists equal parts
     int arc_tok[kPArcBuf];
     int n_arcs[kPLists][32];                      // arcs of each part (a line to itself)
