@@ -108,7 +108,8 @@ typedef struct {
                               that only checks given prices is not counted), bid pass + select pass of an auction */
     int32_t phases;        /* 1 for a price solve; eps-scaling phases of an auction (restarts included) */
     int32_t status;        /* MAXSCORE_OK, MAXSCORE_ERR_RANGE or MAXSCORE_ERR_NOT_CONVERGED */
-    float solver_ms;       /* device time of a4: from its first kernel to its last in a price solve, between two events on
+    float solver_ms;       /* device time of a4: from its first kernel to its last in a price solve (without the time between
+                              maxscore_route_begin's kernels and those of the call that goes on from them), between two events on
                               `stream` in an auction; with price tries that did not stand before the auction, both */
     float bid_ms;          /* summed device time of the first kernel of every round inside a4 (0 unless timing was
                               switched on with maxscore_set_kernel_timing): the price passes over the rewards of a

@@ -124,8 +124,8 @@ struct PriceReport {
     long long total;
     long long t_end;         // device clock (10 ns) at the end of the search ...
     long long t_after;       // ... and of the caller's work behind it
+    long long ticks;         // from the first kernel of the first try to t_end, without the time between two calls that the solve was made in
     int flow, passes, fin, paths;
-    int ticks, pad;          // from the first kernel of the first try to t_end
 };
 static_assert(sizeof(PriceReport) / 4 <= kDoneWords, "stream_done brings it");
 struct PriceGeometry {

@@ -146,7 +146,7 @@ struct PriceArea {
     int loads[8][kPStride];                       // tokens per expert after the final pass, in eight partial counts
     int fail;
     int pad[7];
-    long long t_start;
+    long long t_start, t_pause, t_resume;         // device clock: the first kernel; the end of passes that were begun ahead, and the first one behind them (else both 0)
     PriceReport report;
     // margins and holds, PriceArgs::copies times: (2 * nb + 1) rows of ES columns, filled by a pass (workgroup b adds to copy b
     // modulo their number), added up and cleared by the update behind it.  With one copy for all the additions took 25 us
@@ -176,6 +176,8 @@ struct PriceArgs {
     int *host;                                    // pinned words
     int seq;                                      // number of the solve, not zero
     int look;                                     // the pass that tells whether more than the usual ones are needed, or -1
+    int pause;                                    // the last pass that is begun ahead, or -1
+    int resumes;                                  // the first launch behind these
 };
 
 // So many sixths of a token per expert too many end the passes at pass t.
@@ -618,7 +620,10 @@ __global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, 
     else m2 = price_step<true, SPARE, false>(a, t, nrows, mt, s_h, s);
     if (t == a.look) m2.far = m2.excess > kFar * E;
     for (int e = tid; e < E; e += kUThreads) ar->prices[e] = s.now[e];
-    if (tid == 0) ar->meta = m2;
+    if (tid == 0) {
+        ar->meta = m2;
+        if (a.pause >= 0 && (t == a.pause || m2.done)) ar->t_pause = wall_clock64();
+    }
 }
 
 // What the host is to know of the passes before pass t: the next launch tells it when it begins, as the step would have to wait a microsecond
@@ -752,7 +757,10 @@ __global__ __launch_bounds__(kQThreads) void k_price(PriceArgs a, int t, int nro
     }
     const PriceMeta mt = ar->meta;
     for (int e = tid; e < E; e += kQThreads) s_p[e] = ar->prices[e];
-    if (blockIdx.x == 0 && tid == 0) price_tell(a, mt, t);
+    if (blockIdx.x == 0 && tid == 0) {
+        price_tell(a, mt, t);
+        if (a.resumes) ar->t_resume = wall_clock64();
+    }
     if (mt.done) return;
     const int hquads = a.quads;
     for (int i = tid; i < hquads; i += kQThreads) ((int4 *)s_hist)[i] = make_int4(0, 0, 0, 0);
@@ -802,7 +810,10 @@ __global__ __launch_bounds__(kUThreads) void k_price_small(PriceArgs a, int n_pa
     const bool vec = (E & 3) == 0 && (((size_t)a.q) & 15) == 0;
     const int hquads = a.quads;
     PriceMeta mt = first_meta(ar, prices_in, a.retry, E);
-    if (tid == 0 && !a.retry) ar->t_start = wall_clock64();
+    if (tid == 0 && !a.retry) {
+        ar->t_start = wall_clock64();
+        ar->t_pause = ar->t_resume = 0;
+    }
     for (int e = tid; e < kPStride; e += kUThreads) s.was[e] = e >= E ? 0 : a.retry ? ar->prices[e] : first_price(prices_in, e, E, plim);
     for (int i = tid; i < 8 * kPStride; i += kUThreads) (&ar->loads[0][0])[i] = 0;
     for (int t = 0; t < n_pass && !mt.done; ++t) {
@@ -824,6 +835,7 @@ __global__ __launch_bounds__(kUThreads) void k_price_small(PriceArgs a, int n_pa
     if (tid == 0) {
         ar->meta = mt;
         ar->fail = 0;
+        if (a.pause >= 0) ar->t_pause = wall_clock64();
     }
     if (tid < kPLists) ar->n_arcs[tid][0] = 0;
 }
@@ -956,6 +968,7 @@ __global__ __launch_bounds__(kPThreads) void k_price_assign(PriceArgs a, int if_
     if (tid == 0) s_nq = s_narcs = s_bad = 0;
     for (int e = tid; e < E; e += kPThreads) s_p[e] = ar->prices[e];
     const int B = ar->meta.bound;
+    if (a.resumes && w == 0 && tid == 0) ar->t_resume = wall_clock64();
     if (if_done) {
         const PriceMeta mt = ar->meta;
         if (w == 0 && tid == 0) price_tell(a, mt, if_done);
@@ -1116,6 +1129,7 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
     const int E = a.E, k = a.k, N = E + 1, mode = a.mode;
     const bool slack = !OS && mode == kModeSlack;
     const PriceMeta mt = ar->meta;
+    if (a.resumes && tid == 0) ar->t_resume = wall_clock64();
     const int B = mt.bound, A0 = slack ? 2 * E : 0;
     int rounds = 0, augs = 0;
     bool ok = true, close = false;               // close: not solved, but near enough for another try
@@ -1791,7 +1805,7 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
         r.fin = certified ? 2 : close ? 1 : 3;
         r.paths = augs;
         r.t_end = wall_clock64();
-        r.ticks = (int)(r.t_end - ar->t_start);
+        r.ticks = (r.t_end - ar->t_start) - (ar->t_resume - ar->t_pause);
     }
 }
 
@@ -1807,7 +1821,10 @@ __global__ __launch_bounds__(kPThreads) void k_price_init(PriceArea *ar, int qua
     if (i0 == 0) {
         ar->fail = 0;
         ar->meta = first_meta(ar, prices_in, retry, E);
-        if (!retry) ar->t_start = wall_clock64();
+        if (!retry) {
+            ar->t_start = wall_clock64();
+            ar->t_pause = ar->t_resume = 0;
+        }
     }
 }
 
@@ -1896,6 +1913,8 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     a.lists = a.n_wg >= kPListsFrom ? kPLists : 1;
     a.sampled = n_sampled;
     a.look = a.mode != kModeSlack && !retry ? n_sampled + kTightPasses - 2 : -1;
+    a.pause = part == kPriceBegin ? kPriceAhead - 1 : -1;
+    a.resumes = part == kPriceRest ? 1 : 0;
     geom->report = &a.ar->report;
     geom->rows = rows;
     geom->n_wg = a.n_wg;
@@ -1938,6 +1957,7 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     } while (0)
         MS_SHAPED(MS_P);
 #undef MS_P
+        a.resumes = 0;
         mark();
 #define MS_U(NN, SS)                                                                                                      \
     do {                                                                                                                  \
@@ -1964,7 +1984,10 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
         if (os) hipLaunchKernelGGL((k_price_assign<GG, PP, true>), dim3(a.n_wg), dim3(kPThreads), 0, s, a, if_done);      \
         else hipLaunchKernelGGL((k_price_assign<GG, PP, false>), dim3(a.n_wg), dim3(kPThreads), 0, s, a, if_done);        \
     } while (0)
-        if (!with_pass) MS_SHAPED(MS_P);
+        if (!with_pass) {
+            MS_SHAPED(MS_P);
+            a.resumes = 0;
+        }
 #undef MS_P
 #define MS_F(PP, SS)                                                                                                      \
     do {                                                                                                                  \
