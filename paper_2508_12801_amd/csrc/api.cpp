@@ -359,7 +359,7 @@ static int32_t route_from_rewards(const float *scores, const int32_t *q, int T, 
         const IterAfter after = [](void *c, long long *clock, hipStream_t st) -> int32_t {
             AfterCtx *a = (AfterCtx *)c;
             a->called = true;
-            const SolverGeometry g = {64, (a->T + 63) / 64, 0, 1, clock};
+            const SolverGeometry g = {64, (a->T + 63) / 64, 0, 1, clock, nullptr, nullptr};
             return dispatch_from_keys(g, a->scores, a->assign, a->T, a->E, a->k, a->gates, a->offsets, a->disp_token, a->disp_gate,
                                       a->token_pos, a->ws, st);
         };
@@ -393,7 +393,7 @@ static int32_t route_from_rewards(const float *scores, const int32_t *q, int T, 
             if (solve_end) MS_HIP(hipEventRecord(a->ev_b, st));
             return MAXSCORE_OK;
         };
-        SolverGeometry geom = {0, 0, 0, 0, nullptr};
+        SolverGeometry geom = {0, 0, 0, 0, nullptr, nullptr, nullptr};
         // more demand than capacity: every expert ends full, rows come back with empty slots (-1) at their end
         if ((long long)T * k > (long long)E * Ce)
             src = over_run(q, T, E, k, Ce, o, assign, prices, nullptr, stats, ws, ws_bytes, s, &geom, after, &ctx);

@@ -67,6 +67,15 @@ struct WorkspaceLayout {
     int n_tiles, max_wg;
 };
 
+// What the last kernel of a call tells the host: words of the device, each with the number of the wait (stream_done).
+struct DoneTell {
+    unsigned long long *host;    // pinned words as the device sees them, n + 1 of them; null: it is not the last one
+    const int *words;
+    int n;
+    unsigned seq;
+    int *arrived;                // workgroups that have ended, zero before
+};
+
 // How the last solve laid out its bid keys (what the dispatch needs to read them): the key blocks of the final bid
 // pass hold one key per (token, expert) pair, sorted by expert inside each block of `rows` consecutive tokens.
 struct SolverGeometry {
@@ -75,6 +84,8 @@ struct SolverGeometry {
     int tbits;       // the token id sits in the low tbits bits of a key
     int counts;      // 1: no key blocks; the pairs per (block, expert) are counted (price solves)
     long long *clock;    // device pointer for the end time of the work behind a price solve (PriceReport::t_after)
+    const DoneTell *tell;    // for the last kernel behind it, if it can; told: whether it does
+    bool *told;
 };
 
 WorkspaceLayout workspace_layout(int T, int E, int k, int d = 0);
@@ -108,6 +119,9 @@ int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore
 int32_t kvec_check(const int32_t *kvec, int T, int E, int k, char *ws, long long *demand, hipStream_t s);
 // Waits until everything that has been enqueued in the stream is done, and brings `words` words (kDoneWords at most) from the device then.
 constexpr int kDoneWords = 31;
+int32_t done_ticket(DoneTell *t, const void *dev, int words);
+int32_t done_launch(const DoneTell &t, hipStream_t s);
+int32_t done_wait(const DoneTell &t, void *host, hipStream_t s);
 int32_t stream_done(hipStream_t s, const void *dev = nullptr, void *host = nullptr, int words = 0);
 // --- price.hip
 // Exact assignment by equilibrium prices and shortest augmenting paths.  The host enqueues the passes as they are needed (it
@@ -130,6 +144,7 @@ struct PriceReport {
 static_assert(sizeof(PriceReport) / 4 <= kDoneWords, "stream_done brings it");
 struct PriceGeometry {
     PriceReport *report;     // (device)
+    int *arrived;            // (device; zero behind the search)
     int rows, n_wg;          // blocks of rows over which the pairs are counted (WorkspaceLayout::wcnt_off)
     int one_launch;          // all price passes were one launch
     int ends_ahead, ends_early;      // ends enqueued before the passes were known to have ended; of these, before they had

@@ -148,6 +148,7 @@ struct PriceArea {
     int pad[7];
     long long t_start, t_pause, t_resume;         // device clock: the first kernel; the end of passes that were begun ahead, and the first one behind them (else both 0)
     PriceReport report;
+    int arrived;                                  // workgroups of the call's last kernel
     // margins and holds, PriceArgs::copies times: (2 * nb + 1) rows of ES columns, filled by a pass (workgroup b adds to copy b
     // modulo their number), added up and cleared by the update behind it.  With one copy for all the additions took 25 us
     // (of 512 workgroups then): its lines travel from chiplet to chiplet with every addition.
@@ -1798,6 +1799,7 @@ __global__ __launch_bounds__(kFThreads) void k_price_finish(PriceArgs a, int64_t
     __syncthreads();
     if (tid == 0) {
         if (certified && price_scale) *price_scale = (int64_t)1 << sb;
+        ar->arrived = 0;
         PriceReport &r = ar->report;
         r.total = s.dsum;
         r.flow = OS ? E * a.C : a.T * k;
@@ -1916,6 +1918,7 @@ int32_t price_enqueue(const int32_t *q, int T, int E, int k, int C, const int64_
     a.pause = part == kPriceBegin ? kPriceAhead - 1 : -1;
     a.resumes = part == kPriceRest ? 1 : 0;
     geom->report = &a.ar->report;
+    geom->arrived = &a.ar->arrived;
     geom->rows = rows;
     geom->n_wg = a.n_wg;
     geom->ends_ahead = geom->ends_early = 0;

@@ -1898,15 +1898,30 @@ __global__ void k_done(unsigned long long *host, unsigned v, const int *__restri
     if (i <= n) tell_host(host + i, (unsigned long long)v << 32 | (unsigned)(i < n ? words[i] : 0));
 }
 
-int32_t stream_done(hipStream_t s, const void *dev, void *host, int words)
+int32_t done_ticket(DoneTell *t, const void *dev, int words)
 {
     if (words < 0 || words > kDoneWords) return MAXSCORE_ERR_SHAPE;
     SolverHost *hs = nullptr;
     const int32_t rc = solver_host(&hs);
     if (rc) return rc;
-    const unsigned v = ++hs->done_seq;
-    hipLaunchKernelGGL(k_done, dim3(1), dim3(64), 0, s, (unsigned long long *)(hs->flag_dev + kDoneWord), v, (const int *)dev, words);
+    *t = {(unsigned long long *)(hs->flag_dev + kDoneWord), (const int *)dev, words, ++hs->done_seq, nullptr};
+    return MAXSCORE_OK;
+}
+
+int32_t done_launch(const DoneTell &t, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_done, dim3(1), dim3(64), 0, s, t.host, t.seq, t.words, t.n);
     MS_HIP(hipGetLastError());
+    return MAXSCORE_OK;
+}
+
+int32_t done_wait(const DoneTell &t, void *host, hipStream_t s)
+{
+    SolverHost *hs = nullptr;
+    const int32_t rc = solver_host(&hs);
+    if (rc) return rc;
+    const unsigned v = t.seq;
+    const int words = t.n;
     volatile unsigned long long *word = (volatile unsigned long long *)(hs->flag + kDoneWord);
     int have = 0;
     for (int spin = 0; spin < 20000 && have <= words; ++spin) {
@@ -1917,6 +1932,14 @@ int32_t stream_done(hipStream_t s, const void *dev, void *host, int words)
     for (int i = 0; i < words; ++i) ((int *)host)[i] = (int)(unsigned)word[i];
     std::atomic_thread_fence(std::memory_order_acquire);
     return MAXSCORE_OK;
+}
+
+int32_t stream_done(hipStream_t s, const void *dev, void *host, int words)
+{
+    DoneTell t;
+    int32_t rc = done_ticket(&t, dev, words);
+    if (rc == MAXSCORE_OK) rc = done_launch(t, s);
+    return rc ? rc : done_wait(t, host, s);
 }
 
 int32_t solver_mark(hipStream_t s)
@@ -2048,15 +2071,20 @@ int32_t price_run(const int32_t *q, int T, int E, int k, int C, const maxscore_o
         hs->account[0] = attempt + 1;
         hs->account[2] += pg.ends_ahead;
         hs->account[3] += pg.ends_early;
+        DoneTell tell = {};
+        bool told = false;
+        if (rc == MAXSCORE_OK) rc = done_ticket(&tell, pg.report, sizeof(h) / 4);
+        tell.arrived = pg.arrived;
         if (rc == MAXSCORE_OK && after) {
-            const SolverGeometry g = {pg.rows, pg.n_wg, 0, 1, &pg.report->t_after};
+            const SolverGeometry g = {pg.rows, pg.n_wg, 0, 1, &pg.report->t_after, &tell, &told};
             rc = after(after_ctx, g, s, nullptr);
         }
+        if (rc == MAXSCORE_OK && !told) rc = done_launch(tell, s);
         if (rc != MAXSCORE_OK) {
             (void)hipStreamSynchronize(s);
             return rc;
         }
-        rc = stream_done(s, pg.report, &h, sizeof(h) / 4);
+        rc = done_wait(tell, &h, s);
         if (rc) return rc;
         rc = add_launch_times(hs, mark, pg.one_launch ? 1 : h.passes - passes, pg.one_launch ? 1 : 2, stats, s);
         if (rc) return rc;
@@ -2069,7 +2097,7 @@ int32_t price_run(const int32_t *q, int T, int E, int k, int C, const maxscore_o
         }
     }
     *solved = true;
-    if (geom) *geom = {pg.rows, pg.n_wg, 0, 1, nullptr};
+    if (geom) *geom = {pg.rows, pg.n_wg, 0, 1, nullptr, nullptr, nullptr};
     if (stats) {
         stats->total_score_q = h.total;
         stats->flow_value = h.flow;
@@ -2296,7 +2324,7 @@ int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore
         if (after) {
             int tb = 1;                       // as k_setup computes it
             while ((1 << tb) < T) ++tb;
-            const SolverGeometry g = {rows, n_wg, tb, 0, nullptr};
+            const SolverGeometry g = {rows, n_wg, tb, 0, nullptr, nullptr, nullptr};
             const int32_t arc = after(after_ctx, g, s, hs->ev1);
             if (arc != MAXSCORE_OK) {
                 (void)hipStreamSynchronize(s);
