@@ -26,11 +26,17 @@
  *   - Return value: MAXSCORE_OK or a negative MAXSCORE_ERR_* code.  Argument errors are found on
  *     the host before anything is launched.  No entry point throws or allocates device memory.
  *   - Entry points that contain the assignment step (a4) pace their launches by the solver's progress and
- *     therefore SYNCHRONISE `stream` before returning; the others only enqueue work.  The progress words (rounds
- *     done, end of the solve, the finisher's report) and the final solver state live in two small blocks of pinned
- *     host memory (under 1 KiB together) that the first such call of a host thread allocates per device and keeps
- *     until the process ends; the calling thread polls them while the solve runs (one solve at a time per host
- *     thread; different threads may solve concurrently on different streams with different workspaces).
+ *     therefore SYNCHRONISE `stream` before returning: all that they have enqueued is done, and what it has written can be
+ *     read from any stream of the device.  The others only enqueue work.  The progress words (rounds done, end of the solve,
+ *     its report) and the final solver state live in two small blocks of pinned host memory (5 KiB together) that the first
+ *     such call of a host thread allocates per device and keeps until the process ends; the calling thread polls them while
+ *     the solve runs (one solve at a time per host thread; different threads may solve concurrently on different streams with
+ *     different workspaces).
+ *   - Price solves, rerouting and Sinkhorn wait by such a word and not by hipStreamSynchronize (beyond a millisecond by that
+ *     as well): the runtime has not looked at the stream yet when they return.  hipStreamQuery may still say that it is
+ *     busy, an asynchronous error of the stream is reported by the next call that asks for it, and the caller's next wait for
+ *     the device or the stream is the one that retires the launches: behind eight or more since the last one it returns about
+ *     20 us later than behind seven, whoever has made them.
  *   - Supported sizes: 1 <= k <= E <= 1024, k <= 64, 1 <= T <= 2^21, C >= 1 (C > T acts as T).
  *   - More demand than capacity, T*k > E*min(C,T) (never with a capacity c' = c_f*k*n/e, c_f >= 1, of Section 2.3):
  *     Eq. 7's equalities cannot all hold then; with the capacities of Table 1 the problem is still a flow problem

@@ -119,9 +119,9 @@ int32_t solver_run(const int32_t *q, int T, int E, int k, int Ce, const maxscore
 int32_t kvec_check(const int32_t *kvec, int T, int E, int k, char *ws, long long *demand, hipStream_t s);
 // Waits until everything that has been enqueued in the stream is done, and brings `words` words (kDoneWords at most) from the device then.
 constexpr int kDoneWords = 31;
+// In two steps, where a kernel of the call may tell the host itself; told: one does.
 int32_t done_ticket(DoneTell *t, const void *dev, int words);
-int32_t done_launch(const DoneTell &t, hipStream_t s);
-int32_t done_wait(const DoneTell &t, void *host, hipStream_t s);
+int32_t done_wait(const DoneTell &t, bool told, void *host, hipStream_t s);
 int32_t stream_done(hipStream_t s, const void *dev = nullptr, void *host = nullptr, int words = 0);
 // --- price.hip
 // Exact assignment by equilibrium prices and shortest augmenting paths.  The host enqueues the passes as they are needed (it

@@ -37,11 +37,13 @@
 //     device and polls `done` from pinned memory.
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
 
 #include "common.h"
+#include "done_wait.h"
 #include "host_words.h"
 
 namespace maxscore {
@@ -1890,7 +1892,7 @@ int32_t price_words(int **host, int **dev, int *seq, bool next)
 // Behind all that has been enqueued a kernel of one wavefront writes words of pinned memory, which the host polls: hipStreamSynchronize
 // returns 6 us after such a word is there, and 20 where more than a handful of launches came before it.  Every word carries the number of
 // the wait, so that no order among them is needed.  Results that are brought along need no words of their own, whose way to the host, a
-// microsecond or two, the kernel that found them would have to wait for before the next one begins.  A wait of more than about a
+// microsecond or two, the kernel that found them would have to wait for before the next one begins.  A wait of more than a
 // millisecond goes on in hipStreamSynchronize, which sleeps, and which reports an error of the stream.
 __global__ void k_done(unsigned long long *host, unsigned v, const int *__restrict__ words, int n)
 {
@@ -1908,28 +1910,36 @@ int32_t done_ticket(DoneTell *t, const void *dev, int words)
     return MAXSCORE_OK;
 }
 
-int32_t done_launch(const DoneTell &t, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_done, dim3(1), dim3(64), 0, s, t.host, t.seq, t.words, t.n);
-    MS_HIP(hipGetLastError());
-    return MAXSCORE_OK;
-}
+namespace {
 
-int32_t done_wait(const DoneTell &t, void *host, hipStream_t s)
+struct DoneWords {
+    volatile unsigned long long *word;
+    hipStream_t s;
+    const DoneTell *tell;
+    std::chrono::steady_clock::time_point since;
+    unsigned number(int i) const { return (unsigned)(word[i] >> 32); }
+    void pause() const { __builtin_ia32_pause(); }
+    bool late() const { return std::chrono::steady_clock::now() - since > std::chrono::milliseconds(1); }
+    int sync() const { return hipStreamSynchronize(s) == hipSuccess ? MAXSCORE_OK : MAXSCORE_ERR_HIP; }
+    int lost() const { return MAXSCORE_ERR_HIP; }
+    int launch() const
+    {
+        hipLaunchKernelGGL(k_done, dim3(1), dim3(64), 0, s, tell->host, tell->seq, tell->words, tell->n);
+        return hipGetLastError() == hipSuccess ? MAXSCORE_OK : MAXSCORE_ERR_HIP;
+    }
+};
+
+}  // namespace
+
+int32_t done_wait(const DoneTell &t, bool told, void *host, hipStream_t s)
 {
     SolverHost *hs = nullptr;
-    const int32_t rc = solver_host(&hs);
+    int32_t rc = solver_host(&hs);
     if (rc) return rc;
-    const unsigned v = t.seq;
-    const int words = t.n;
-    volatile unsigned long long *word = (volatile unsigned long long *)(hs->flag + kDoneWord);
-    int have = 0;
-    for (int spin = 0; spin < 20000 && have <= words; ++spin) {
-        if ((unsigned)(word[have] >> 32) == v) ++have;
-        else __builtin_ia32_pause();
-    }
-    if (have <= words) MS_HIP(hipStreamSynchronize(s));
-    for (int i = 0; i < words; ++i) ((int *)host)[i] = (int)(unsigned)word[i];
+    DoneWords w = {(volatile unsigned long long *)(hs->flag + kDoneWord), s, &t, std::chrono::steady_clock::now()};
+    rc = told ? wait_told(w, t.seq, t.n) : tell_and_wait(w, t.seq, t.n);
+    if (rc) return rc;
+    for (int i = 0; i < t.n; ++i) ((int *)host)[i] = (int)(unsigned)w.word[i];
     std::atomic_thread_fence(std::memory_order_acquire);
     return MAXSCORE_OK;
 }
@@ -1937,9 +1947,8 @@ int32_t done_wait(const DoneTell &t, void *host, hipStream_t s)
 int32_t stream_done(hipStream_t s, const void *dev, void *host, int words)
 {
     DoneTell t;
-    int32_t rc = done_ticket(&t, dev, words);
-    if (rc == MAXSCORE_OK) rc = done_launch(t, s);
-    return rc ? rc : done_wait(t, host, s);
+    const int32_t rc = done_ticket(&t, dev, words);
+    return rc ? rc : done_wait(t, false, host, s);
 }
 
 int32_t solver_mark(hipStream_t s)
@@ -2079,12 +2088,11 @@ int32_t price_run(const int32_t *q, int T, int E, int k, int C, const maxscore_o
             const SolverGeometry g = {pg.rows, pg.n_wg, 0, 1, &pg.report->t_after, &tell, &told};
             rc = after(after_ctx, g, s, nullptr);
         }
-        if (rc == MAXSCORE_OK && !told) rc = done_launch(tell, s);
         if (rc != MAXSCORE_OK) {
             (void)hipStreamSynchronize(s);
             return rc;
         }
-        rc = done_wait(tell, &h, s);
+        rc = done_wait(tell, told, &h, s);
         if (rc) return rc;
         rc = add_launch_times(hs, mark, pg.one_launch ? 1 : h.passes - passes, pg.one_launch ? 1 : 2, stats, s);
         if (rc) return rc;
