@@ -92,7 +92,9 @@ constexpr int kAllArcs = 4000;                    // problems with this few exch
 // sixths 28 of 120 such solves of 512 went into a second try or to the auction, and they took 1.10 times as long as with that earlier rule (worst 12
 // times); so 0.92 with spare room, 0.93 without, and 1.00 with less room than demand (1.10 with a third there).
 constexpr int kEnough = 5, kLateEnough = 2, kRetryEnough = 1, kUsualPasses = 6;       // the first three are sixths of a token per expert ...
-constexpr int kManyEnough = 2, kManyOverEnough = 1, kManyExperts = 256;               // ... and these
+// Up to eight places per expert a third as well: five sixths of a token are a large part of all there are.  1308 solves of two to twelve places: 0.84 of the
+// time of that rule, 25 beyond 1.25 (50 tokens to 8 of 128, three places each, 173 us, 268 with five sixths), else 0.86 and 52.
+constexpr int kManyEnough = 2, kManyOverEnough = 1, kManyExperts = 256, kFewPlaces = 8;      // ... and the first two here
 // With spare room most experts may have no price, and what is too many is too many at the others: from 97 experts on, up to the sixth pass, these alone count.  10007 to 65536 tokens of
 // 128, 160 and 256 experts, a tenth to half more room than demand: 97 to 201 us, with all experts counted 175 to 460, as the search of a few that
 // far from their capacity did not stand.  Of 252 solves 0.87 of the time of the earlier rule, none beyond 1.25; with five sixths of a token for every expert 0.90,
@@ -186,6 +188,7 @@ __device__ __forceinline__ int enough_sixths(const PriceArgs &a, int t)
 {
     if (a.retry) return kRetryEnough;
     if (a.E > kManyExperts) return a.mode == kModeOver ? kManyOverEnough : kManyEnough;
+    if (a.C <= kFewPlaces) return kManyEnough;
     return t - a.sampled >= kUsualPasses ? kLateEnough : a.mode == kModeSlack && a.E >= kPricedFrom ? kPricedEnough : kEnough;
 }
 
@@ -1086,7 +1089,8 @@ constexpr int kEndLanes = 8, kEndBlock = kPThreads / kEndLanes;
 // The search makes the last pass itself where that costs its one compute unit less than the launch it saves, up to eight rewards to a lane.  A layer
 // around it, with a launch for the pass and without: 64 tokens of 8 experts 75.0 -> 70.4 us, of 64 to 8 102 -> 96.5, of 128 126 -> 112, 128 of 16 to 8
 // 79.8 -> 73, of 64 to 4 97 -> 92, 500 of 8 to 2 89 -> 83.5, of 16 97.7 -> 94.9; but 400 of 24 to 4 92 -> 95, 128 of 128 to 8 129 -> 130, 256 of 64 to 8
-// 113 -> 115, 512 of 64 133 -> 144.
+// 113 -> 115, 512 of 64 133 -> 144.  With more demand than room and 65 to 128 experts the kernel spills 20 registers and is still no slower: assignment,
+// gates and dispatch of 64 tokens of 128 to 8 of three places 297 -> 251 us, of 100 156 -> 140, 85 of 96 137 -> 133, 110 of 70 118.5 and 118.8.
 constexpr int kEndEntries = 8 * kFThreads;
 constexpr int kEndCounts = kEndEntries / kEndBlock + kEndLanes * 16;
 

@@ -1,5 +1,5 @@
 """GPU: batches whose price solves end in their first try, or at all, by the limits of their class: more than 256 experts, few experts with a price
-among many with room, rows that are nearly alike.  (With one limit and one number of exchanges for all of them the first went into a second try or to
+among many with room, few places per expert, rows that are nearly alike.  (With one limit and one number of exchanges for all of them the first went into a second try or to
 the auction, 1.5 to 12 times as long.)  Totals of the smaller ones are the auction's."""
 import pytest
 
@@ -27,6 +27,7 @@ def _logits(T, E, kind, alike, noise, seed):
     (16384, 512, 2, 1.1, "zipf", 0, 0, 2512, 1),
     (10007, 128, 2, 1.5, "zipf", 0, 0, 2128, 1), (32768, 128, 2, 1.5, "zipf", 0, 0, 2128, 1), (16384, 160, 2, 1.1, "zipf", 0, 0, 2160, 1),
     (65536, 256, 2, 1.1, "zipf", 0, 0, 2256, 1),
+    (64, 128, 8, 0.75, "none", 0, 0, 0, 1), (64, 128, 8, 0.75, "normal", 0, 0, 1, 1), (64, 128, 8, 1.0, "none", 0, 0, 5, 1),
     (4096, 64, 4, 1.0, "normal", 0.1, 0.03, 1064, 3), (4096, 256, 4, 1.2, "none", 0.1, 0.03, 256, 3), (16384, 64, 4, 0.8, "normal", 0.5, 0.1, 1064, 3),
     (16384, 128, 4, 1.0, "none", 0.05, 0.03, 128, 3),
 ])
