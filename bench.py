@@ -31,6 +31,12 @@ def profile_value(name, key):
     return None
 
 
+def profile_traffic(rounds):
+    """Bytes that the counters saw a call at the headline configuration move, if it made as many passes as this one (else None)."""
+    name = "pass_cfg5_pmc_traffic.txt"
+    return profile_value(name, "pass_traffic_bytes") if profile_value(name, "pass_rounds") == rounds else None
+
+
 def hbm_frac(nbytes, ms):
     """Share of the HBM peak at which `nbytes` move in `ms` milliseconds (None where nothing was timed)."""
     return nbytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS if ms > 0 else None
@@ -189,7 +195,7 @@ def main():
     gd_ms = sorted(ms.route_scores(out["scores"], k, C)["stats"]["gates_dispatch_ms"] for _ in range(5))[2]
     roofline = solver_roofline(st, T, E, k, solve_ms, gd_ms)
     if args.config == "cfg5":
-        roofline["traffic"] = profile_value("pass_cfg5_pmc_traffic.txt", "pass_traffic_bytes")
+        roofline["traffic"] = profile_traffic(st["rounds"])
     # plain copy kernel of the same footprint: achievable-bandwidth reference
     src = torch.empty(256 << 20, dtype=torch.uint8, device=dev)
     dst = torch.empty_like(src)

@@ -33,6 +33,12 @@ def test_roofline(st, T):
     json.dumps(r)
 
 
+def test_traffic_is_that_of_as_many_passes():
+    rounds = bench.profile_value("pass_cfg5_pmc_traffic.txt", "pass_rounds")
+    assert rounds and bench.profile_traffic(int(rounds)) == bench.profile_value("pass_cfg5_pmc_traffic.txt", "pass_traffic_bytes") > 0
+    assert bench.profile_traffic(int(rounds) + 1) is None
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("config", ["cfg2", "cfg5"])
 def test_one_line(config, monkeypatch, capsys):
