@@ -337,6 +337,11 @@ __global__ __launch_bounds__(256) void k_combine_elem(const void *__restrict__ b
 // columns to 64 experts, the rerouting's layers, past the cache against through it: top-2 of 160 MiB (400 in all) 220 against 249 us, 200 (500)
 // 258 and 280, top-4 of 200 (350) 217 and 231, top-6 of 240 (360) 235 and 243, fp32 top-1 of 120 (360) 226 and 236; but top-2 of 120 (300)
 // 193 and 189, top-8 of 200 (275) 205 and 193 and of 240 (330) 224 and 225, 10007 of 1000 in fp32 to 6 of 96 (328) 318 and 312.
+// So it is with two matrix products between rows out and rows back, which could find buffers of that size in the cache: what the first one
+// loses, the rest of the layer gains.  Layers with experts of 256 to 1024 inner columns, past the cache against through it: 44032 of 1024 to 2 of 64 by rerouting 484
+// and 490 us, 52000 586 and 600, 60000 of 768 to 2 of 32 597 and 616, of 512 to 4 of 64 640 and 661, 28000 of 1024 to 4 554 and 569, 20480 of 2048 to 3
+// 776 and 787, 26000 to 2 604 and 613, 20000 of 1536 to 4 579 and 592, fp32 30000 of 1024 to 2 842 and 852; 12288 of 2048 to 5, 14336 to 4, 36000 of 1024
+// in fp32 to 1 and 12000 to 5 within 1 %.  (Rows out and the first product alone, of x that the cache holds: 1 to 5 % slower.)
 // Rows back: buffers and results of half of it (top-2 of 160 MiB in all 153 against 162 us, of 240 189 and 201, top-4 of 180 161 and 166,
 // top-8 of 250 193 and 200; of 150 and less the same).
 static bool beyond_caches(size_t bytes) { return bytes >= (size_t)256 << 20; }
