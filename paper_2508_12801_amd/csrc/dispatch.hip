@@ -435,6 +435,7 @@ __global__ __launch_bounds__(256) void k_count_scatter(const int *__restrict__ d
         if (tid == 0) s_last = atomicAdd(tell.arrived, 1) == (int)gridDim.x - 1;
         __syncthreads();
         if (s_last && tid <= tell.n) {
+            __threadfence();              // (the clock is another workgroup's)
             const int word = tid < tell.n ? __hip_atomic_load(tell.words + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
             tell_host(tell.host + tid, (unsigned long long)tell.seq << 32 | (unsigned)word);
         }
