@@ -26,7 +26,7 @@
 // excess left) the result is thrown away and the auction of solver.hip solves the problem instead.
 //
 // What bounds it: the passes read the rewards once each (34 MB for 65536 tokens over 128 experts, 11 us a pass including the
-// k-th best of every row, plus 6.4 us for the step between them, which one workgroup takes), the search is one serial chain of
+// k-th best of every row, plus 6.0 us for the step between them, which one workgroup takes), the search is one serial chain of
 // searches.  65536 tokens, 128 experts, top-8, capacity 1.0: 0.17 to 0.20 ms, of which five or six passes and their steps take 0.10,
 // the last pass 0.02 and the search 0.05 to 0.08; 1.6 to 1.8 ms for the auction, whose 46 rounds each read the rewards as
 // well.  16384 over 64 experts: 0.10 against 0.8 to 1.3 ms.
@@ -289,8 +289,8 @@ __device__ __forceinline__ float wave_sum_f(float v)        // the total in lane
 }
 
 // Behind step_clear and a barrier.  CUM: s.cum holds the sums of the bins already.  SPARE: there is spare capacity; the columns of s_h are
-// summed up then.  TOGETHER: the step of the other kind.  (Three kinds of code, as the branches of the others cost every step: 4.1 us at 16
-// experts and 5.8 at 64 and 128 without them, 4.5 and 6.3 with those of spare capacity; 7.2 at 96 with spare capacity, 7.6 with both.)
+// summed up then.  TOGETHER: the step of the other kind.  (Three kinds of code, as the branches of the others cost every step: 0.4 to 0.5 us at
+// 16, 64 and 128 experts those of spare capacity, and with that at 96 0.4 those of the other kind.)
 template <bool CUM, bool SPARE, bool TOGETHER>
 __device__ __forceinline__ PriceMeta price_step(const PriceArgs &a, int t, int nrows, const PriceMeta mt, int *s_h, StepLds &s)
 {
@@ -601,8 +601,8 @@ static_assert(2 * kPBins + 1 <= 64, "a sum per bin");
 constexpr int price_pieces(bool half) { return (kPTableInts / (half ? 8 : 4) + kUThreads) / kUThreads; }      // per thread, at most
 
 // One workgroup.  Half of it is the wait for the copies, which the pass's additions have left in memory; the rest two barriers' worth of
-// sums and searches: 4.4 us at 16 experts, 5.3 at 64, 6.4 at 128, 8.4 at 256 (5.7, 7.5, 9.8 and 9.7 with counts of 32 bits, and with the
-// sums of the bins and the largest step taken behind the copies); with spare capacity 9 at 96, and 4.8 where the passes end.  As the first step of every workgroup of the next pass the same
+// sums and searches: 3.8 us at 16 experts, 5.0 at 64, 6.0 at 128, 8.0 at 256 (1.3 to 3.4 more with counts of 32 bits, and with the
+// sums of the bins and the largest step taken behind the copies); with spare capacity 8.0 at 96, and 4.6 where the passes end.  As the first step of every workgroup of the next pass the same
 // work took 10 to 20 us.
 template <int N, int M, bool HALF, bool SPARE>
 __global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, int nrows)

@@ -9,12 +9,12 @@
 // Three ways to do it, by size; column sums are added in a fixed order everywhere, in double beyond one to four rows where one
 // workgroup does it all, from the first on with eight lanes to a row; row sums are trees over the columns:
 //   small    up to 65536 scores of up to 16 experts, half as many of up to 64: the whole call is one workgroup that keeps
-//            K in registers, a thread owns whole rows.  An iteration takes 2.3 us (two barriers, 300 instructions of every
+//            K in registers, a thread owns whole rows.  An iteration takes 1.8 us (two barriers, 300 instructions of every
 //            wavefront), two launches each 8.  The limit is that of the registers: 1024 threads of 64 entries, 512 beyond 16 columns.
 //   medium   up to 64 experts: eight lanes per row, K recomputed from the scores; one launch per iteration, whose
 //            workgroups begin by adding up the column sums of the iteration before
 //   large    one wavefront per row, lane l holds experts l, l+64, ...; rows and columns are launches of their own
-// 20 iterations, before and after the first two ways: 4096 tokens of 16 experts 228 and 70 us (4097, the first the medium way
+// 20 iterations, before and after the first two ways: 4096 tokens of 16 experts 228 and 67 us (4097, the first the medium way
 // takes, 116), 16384 of 64 350 and 178 us.
 #include <algorithm>
 #include <type_traits>
