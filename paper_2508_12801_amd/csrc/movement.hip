@@ -236,14 +236,15 @@ constexpr int kCombineLoads = 4;
 
 // AHEAD: the pieces of those slots are really on their way together.  A load under a condition is waited for before the next one (its register
 // could hold something else), so a slot that is empty then reads what the one before it did, and a lane beyond the row its end; neither is used.
-template <bool BF16, bool NT, int PIECES, bool AHEAD>
+// QUADS: a lane's columns by four, PIECES kilobytes of the row, or half of one: rows of bf16 that are no longer.
+template <bool BF16, bool NT, int QUADS, bool AHEAD>
 __global__ __launch_bounds__(256) void k_combine(const void *__restrict__ buf_, const int32_t *__restrict__ assign,
                                                  const int32_t *__restrict__ token_pos,
                                                  const float *__restrict__ gates, int T, int d, int E, int k, int C,
                                                  int parts, float *__restrict__ y)
 {
     using V = std::conditional_t<BF16, u32x2, u32x4>;        // four elements
-    constexpr int QUADS = PIECES * (BF16 ? 2 : 1), SLOTS = kCombineLoads / PIECES;
+    constexpr int PIECES = QUADS <= 2 && BF16 ? 1 : BF16 ? QUADS / 2 : QUADS, SLOTS = kCombineLoads / PIECES;
     const V *buf = (const V *)buf_;
     const int lane = threadIdx.x & 63, quads_per_row = d >> 2;
     const unsigned item = blockIdx.x * 4u + (threadIdx.x >> 6), i = __builtin_amdgcn_readfirstlane(item / (unsigned)parts);
@@ -343,7 +344,8 @@ __global__ __launch_bounds__(256) void k_combine_elem(const void *__restrict__ b
 // 776 and 787, 26000 to 2 604 and 613, 20000 of 1536 to 4 579 and 592, fp32 30000 of 1024 to 2 842 and 852; 12288 of 2048 to 5, 14336 to 4, 36000 of 1024
 // in fp32 to 1 and 12000 to 5 within 1 %.  (Rows out and the first product alone, of x that the cache holds: 1 to 5 % slower.)
 // Rows back: buffers and results of half of it (top-2 of 160 MiB in all 153 against 162 us, of 240 189 and 201, top-4 of 180 161 and 166,
-// top-8 of 250 193 and 200; of 150 and less the same).
+// top-8 of 250 193 and 200; of 150 and less the same; with two matrix products before them and a sum that reads the results behind them 13 layers of
+// 128 to 250 MiB take 0.98 to 1.005 of the time: 24000 of 1024 to 2 of 64 417 and 422, 44032 of 512 425 and 435, 10007 of 1000 in fp32 to 4 of 96 691 and 687).
 static bool beyond_caches(size_t bytes) { return bytes >= (size_t)256 << 20; }
 static bool out_past_caches(size_t x_bytes, size_t buf_bytes, size_t y_bytes)
 {
@@ -375,7 +377,8 @@ int32_t dispatch_tokens_run(const void *x, int dtype, const int32_t *offsets, co
 #define MS_BLOCKED(NN, LL, TT)                                                                                              \
     hipLaunchKernelGGL((k_dispatch_tokens_blocked<NN, LL, TT>), dim3(n_tb + n_pad), dim3(TT), sizeof(int) * 2 * E, s, (const u32x4 *)x, \
                        offsets, disp_token, T, E, C, (int)((size_t)d * eb / 16), tb, n_tb, (u32x4 *)out)
-        // Rows of x of 100 MiB and more are read past the cache (those that are in it are found there all the same): layers with 64 and 96
+        // Rows of x of 100 MiB and more are read past the cache (those that the projection has left in it are found there all the same; by themselves, the
+        // same x again and again, they come from memory every time: 44032 tokens of 2048 to 2 of 64 86 and 119 us): layers with 64 and 96
         // MiB of them the same, 112 MiB (28672 tokens of 2048 to 4 of 128) 440 -> 421 us, 128 (65536 of 1024 to 4 of 64) 454 -> 412, 160
         // (40960 of 2048 to 8 of 64) 770 -> 731, 224 406 -> 403, 256 (65536 of 2048 to 8 of 128) 1234 -> 1207; 32768 with room to spare 606 -> 582.
         // (The projection's loads past the cache: 1234 -> 1226 there, but with both 1226, and 32768 606 -> 635.)
@@ -421,19 +424,25 @@ int32_t combine_run(const void *buf, int dtype, const int32_t *assign, const int
         const bool ahead = k > 2 && traffic < (size_t)448 << 20;
         const bool two = ahead && vpr > 64 && (k > 4 || pieces % 2 == 0) && (long long)T * ((pieces + 1) / 2) >= 2560 &&
                          traffic >= (size_t)24 << 20;
+        // Rows of bf16 of up to 256 columns: a lane takes four of them, not eight of which four are none (44032 of 256 from 8 of 64 experts
+        // from memory 78.0 -> 75.5 us, of 64 49.4 -> 46.0, 16384 of 128 from 4 15.7 -> 14.8).
+        const bool narrow = eb == 2 && vpr <= 32;
         const int piece = two ? 128 : 64, parts = (vpr + piece - 1) / piece;
         const int most = std::max(1, (1 << 24) / parts);            // tokens a launch (its threads are counted in 32 bits)
         for (int i0 = 0; i0 < T; i0 += most) {
             const int n = std::min(most, T - i0);
             const size_t at = (size_t)i0 * k;
-#define MS_COMBINE(BB, NN, PP, AA)                                                                                                   \
-    hipLaunchKernelGGL((k_combine<BB, NN, PP, AA>), dim3((unsigned)(((size_t)n * parts + 3) / 4)), dim3(256), 0, s, buf, assign + at, \
+#define MS_COMBINE(BB, NN, QQ, AA)                                                                                                   \
+    hipLaunchKernelGGL((k_combine<BB, NN, QQ, AA>), dim3((unsigned)(((size_t)n * parts + 3) / 4)), dim3(256), 0, s, buf, assign + at, \
                        token_pos + at, gates + at, n, d, E, k, C, parts, y + (size_t)i0 * d)
 #define MS_COMBINE_P(BB, NN)                         \
     do {                                             \
-        if (two) MS_COMBINE(BB, NN, 2, true);        \
-        else if (ahead) MS_COMBINE(BB, NN, 1, true); \
-        else MS_COMBINE(BB, NN, 1, false);           \
+        constexpr int q = BB ? 2 : 1;                \
+        if (two) MS_COMBINE(BB, NN, 2 * q, true);    \
+        else if (BB && narrow && ahead) MS_COMBINE(BB, NN, 1, true); \
+        else if (BB && narrow) MS_COMBINE(BB, NN, 1, false); \
+        else if (ahead) MS_COMBINE(BB, NN, q, true); \
+        else MS_COMBINE(BB, NN, q, false);           \
     } while (0)
             if (eb == 2) {
                 if (nt) MS_COMBINE_P(true, true);

@@ -21,7 +21,7 @@ def _case(T, d, E, k, C, dtype):
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 @pytest.mark.parametrize("T,d,E,k,C", [
     (70, 8, 4, 1, 9), (70, 256, 4, 2, 9), (70, 264, 4, 2, 9), (70, 504, 5, 3, 9), (70, 512, 4, 1, 9), (70, 520, 6, 5, 9), (70, 776, 4, 2, 9),
-    (70, 1016, 9, 8, 9), (70, 1288, 9, 7, 9),
+    (70, 1016, 9, 8, 9), (70, 1288, 9, 7, 9), (70, 64, 9, 4, 9), (70, 200, 9, 8, 9), (70, 256, 9, 5, 9), (8200, 256, 64, 8, 1030),
     (3000, 1288, 16, 5, 900),           # two pieces to a wavefront
     (8200, 1800, 16, 4, 2050),          # past the caches, loads ahead
     (8200, 3080, 16, 2, 1025),          # ... one after the other
