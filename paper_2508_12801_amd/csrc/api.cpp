@@ -356,10 +356,10 @@ static int32_t route_from_rewards(const float *scores, const int32_t *q, int T, 
             const float *scores; const int32_t *assign; int T, E, k; float *gates; int32_t *offsets, *disp_token;
             float *disp_gate; int32_t *token_pos; char *ws; bool called;
         } ctx = {scores, assign, T, E, k, gates, expert_offsets, disp_token, disp_gate, token_pos, ws, false};
-        const IterAfter after = [](void *c, long long *clock, hipStream_t st) -> int32_t {
+        const IterAfter after = [](void *c, long long *clock, const DoneTell *tell, bool *told, hipStream_t st) -> int32_t {
             AfterCtx *a = (AfterCtx *)c;
             a->called = true;
-            const SolverGeometry g = {64, (a->T + 63) / 64, 0, 1, clock, nullptr, nullptr};
+            const SolverGeometry g = {64, (a->T + 63) / 64, 0, 1, clock, tell, told};
             return dispatch_from_keys(g, a->scores, a->assign, a->T, a->E, a->k, a->gates, a->offsets, a->disp_token, a->disp_gate,
                                       a->token_pos, a->ws, st);
         };

@@ -241,7 +241,7 @@ int32_t dispatch_core(const int32_t *list, const float *gates, size_t n, int E, 
                       hipStream_t s);
 // --- iter.hip
 // after: enqueues what follows the last round (on any outcome), called once when that round is in the stream and before it has ended.
-typedef int32_t (*IterAfter)(void *ctx, long long *clock, hipStream_t s);
+typedef int32_t (*IterAfter)(void *ctx, long long *clock, const DoneTell *tell, bool *told, hipStream_t s);
 int32_t iter_run(const int32_t *q, int T, int E, int k, int C, int max_rounds, int32_t *assign, int64_t *total,
                  int32_t *flow, int32_t *rounds, float *after_ms, char *ws, hipStream_t s, IterAfter after, void *after_ctx);
 // --- operators.hip

@@ -48,6 +48,7 @@ struct IterArea {
     int rej[4];                // ... those there was no room for
     int room[4];               // ... whether an expert has room left
     long long t_end, t_after;  // device clock (10 ns) behind the last round, and at the end of the caller's work behind that
+    int arrived;               // workgroups of that work's last kernel
 };
 
 struct IterArgs {
@@ -881,9 +882,13 @@ int32_t iter_run(const int32_t *q, int T, int E, int k, int C, int max_rounds, i
         }
     }
     // what follows is enqueued while the last round runs
-    const int32_t arc = after ? after(after_ctx, &a.ar->t_after, s) : MAXSCORE_OK;
     long long clock[2];
-    rc = stream_done(s, &a.ar->t_end, clock, sizeof(clock) / 4);
+    DoneTell tell = {};
+    bool told = false;
+    rc = done_ticket(&tell, &a.ar->t_end, sizeof(clock) / 4);
+    tell.arrived = &a.ar->arrived;
+    const int32_t arc = rc == MAXSCORE_OK && after ? after(after_ctx, &a.ar->t_after, &tell, &told, s) : rc;
+    rc = done_wait(tell, told, clock, s);
     if (rc) return rc;
     if (arc) return arc;
     if (after_ms) *after_ms = after ? (float)(clock[1] - clock[0]) * 1e-5f : 0.f;
