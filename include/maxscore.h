@@ -400,9 +400,12 @@ int32_t maxscore_route_xw(const void *x, const void *W, const float *bias, int32
  * off (0, default).  Timing adds three event records per round; it is meant for benchmarks. */
 void maxscore_set_kernel_timing(int32_t on);
 
-/* How the calling thread's last exact solve on the current device went (host bookkeeping, for tests and tuning): account[0] tries of the price solve
- * (0: it was not used, or more demand than capacity went on to the padded auction; negative: none of them stood, and an auction has solved it), [1] 1 if these went on from passes that maxscore_route_begin had begun, [2] times that the end of the passes was
- * enqueued before they were known to have ended, [3] of these that came too early and left everything as it was. */
+/* How the calling thread's last exact solve on the current device went (host bookkeeping, for tests and tuning):
+ * account[0]  tries of the price solve (0: it was not used, or more demand than capacity went on to the padded auction;
+ *             negative: none of them stood, and an auction has solved it)
+ * account[1]  1 if these went on from passes that maxscore_route_begin had begun
+ * account[2]  times that the end of the passes was enqueued before they were known to have ended
+ * account[3]  ... that it came too early and left everything as it was */
 int32_t maxscore_solve_account(int32_t account[4]);
 
 /* Plain device-to-device copy kernel of `bytes` bytes (multiple of 16), used by the benchmark to

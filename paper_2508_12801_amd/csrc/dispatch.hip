@@ -321,8 +321,8 @@ constexpr int kCountSelf = 4096;
 // Up to so many workgroups the last one to end tells the host that the call is done: its launch is the last then, and a caller who waits for the device
 // behind a small layer does so behind seven launches and not eight, which HIP takes 20 us less for.  Called alone, with that wait: 256 tokens of 64 experts
 // 132 -> 115 us, 128 of 96 163 -> 141; one behind the other 102 -> 103 and 135 the same.  (Rerouting by itself,
-// with two events less: 64 of 8 alone 104 -> 72, 256 of 64 135 -> 105, one behind the other 71 -> 63 and 103 -> 95.)  With more workgroups their fences and additions cost what the
-// launch does (4096 of 16, 128 of them, 123 -> 125; 2000 of 32 130 -> 135).
+// with two events less: 64 of 8 alone 104 -> 72, 256 of 64 135 -> 105, one behind the other 71 -> 63 and 103 -> 95.)  With more
+// workgroups their fences and additions cost what the launch does (4096 of 16, 128 of them, 123 -> 125; 2000 of 32 130 -> 135).
 constexpr int kTellBlocks = 16;
 static_assert(kCountMaxE >= kPriceMaxE, "tables for every expert count a price solve accepts");
 

@@ -95,8 +95,8 @@ constexpr int kEnough = 5, kLateEnough = 2, kRetryEnough = 1, kUsualPasses = 6; 
 // Up to eight places per expert a third as well: five sixths of a token are a large part of all there are.  1308 solves of two to twelve places: 0.84 of the
 // time of that rule, 25 beyond 1.25 (50 tokens to 8 of 128, three places each, 173 us, 268 with five sixths), else 0.86 and 52.
 constexpr int kManyEnough = 2, kManyOverEnough = 1, kManyExperts = 256, kFewPlaces = 8;      // ... and the first two here
-// With spare room most experts may have no price, and what is too many is too many at the others: from 97 experts on, up to the sixth pass, these alone count.  10007 to 65536 tokens of
-// 128, 160 and 256 experts, a tenth to half more room than demand: 97 to 201 us, with all experts counted 175 to 460, as the search of a few that
+// With spare room most experts may have no price, and what is too many is too many at the others: from 97 experts on, up to the sixth pass,
+// these alone count.  10007 to 65536 tokens of 128, 160 and 256 experts, a tenth to half more room than demand: 97 to 201 us, with all experts counted 175 to 460, as the search of a few that
 // far from their capacity did not stand.  Of 252 solves 0.87 of the time of the earlier rule, none beyond 1.25; with five sixths of a token for every expert 0.90,
 // nine beyond.  (Four thirds, of 144 solves: 0.88; two 0.88, five sixths 0.89.)  Up to 64 experts searches stand, and all counted is
 // better (0.88, 0.90 and 0.92 at 64, 32 and 16; 0.89, 0.93 and 0.94 so), at 96 too (0.90, 0.92).
@@ -602,8 +602,8 @@ constexpr int price_pieces(bool half) { return (kPTableInts / (half ? 8 : 4) + k
 
 // One workgroup.  Half of it is the wait for the copies, which the pass's additions have left in memory; the rest two barriers' worth of
 // sums and searches: 3.8 us at 16 experts, 5.0 at 64, 6.0 at 128, 8.0 at 256 (1.3 to 3.4 more with counts of 32 bits, and with the
-// sums of the bins and the largest step taken behind the copies); with spare capacity 8.0 at 96, and 4.6 where the passes end.  As the first step of every workgroup of the next pass the same
-// work took 10 to 20 us.
+// sums of the bins and the largest step taken behind the copies); with spare capacity 8.0 at 96, and 4.6 where the passes
+// end.  As the first step of every workgroup of the next pass the same work took 10 to 20 us.
 template <int N, int M, bool HALF, bool SPARE>
 __global__ __launch_bounds__(kUThreads) void k_price_update(PriceArgs a, int t, int nrows)
 {
